@@ -10,6 +10,14 @@ import torch
 from . import bspmm as K
 
 
+def _output(plan, transposed, rows, device):
+    """Room for a product.  The launch writes every row that belongs to an operation, so the rows
+    are cleared first only when some belong to none (1024 graphs of 8 to 500 nodes at F = 256:
+    clearing C and G took 16.8 us of a step's 71 us on the GPU)."""
+    make = torch.empty if plan.covered_rows(transposed) >= rows else torch.zeros
+    return make((rows, plan.F), dtype=torch.float32, device=device)
+
+
 class BatchedSpMM(torch.autograd.Function):
     """``C = BatchedSpMM.apply(plan, B)`` with ``plan`` a :class:`bspmm.Plan`; ``B`` is the packed
     dense input (``n_b_rows x F`` fp32 on the plan's device), ``C`` the packed output."""
@@ -20,7 +28,7 @@ class BatchedSpMM(torch.autograd.Function):
             raise TypeError("BatchedSpMM needs an fp32 CUDA tensor")
         B = B.contiguous()
         rows = int(n_c_rows) if n_c_rows is not None else int(B.shape[0])
-        C = torch.zeros((rows, plan.F), dtype=torch.float32, device=B.device)
+        C = _output(plan, False, rows, B.device)
         plan.run(B, C)
         ctx.plan = plan
         ctx.n_b_rows = int(B.shape[0])
@@ -29,7 +37,7 @@ class BatchedSpMM(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dY):
         dY = dY.contiguous()
-        G = torch.zeros((ctx.n_b_rows, ctx.plan.F), dtype=torch.float32, device=dY.device)
+        G = _output(ctx.plan, True, ctx.n_b_rows, dY.device)
         ctx.plan.run_transposed(dY, G)
         return None, G, None
 

@@ -1,5 +1,6 @@
-"""Thin ctypes binding of libbspmm.so: argument marshalling only, same names as the C ABI.
+"""Thin binding of libbspmm.so: argument marshalling only, same names as the C ABI.
 
+The run calls go through ``_native.so`` (``csrc/binding.cpp``), everything else through ctypes.
 Every step of the path (scheduling, staging, the products, the transposed build) runs inside
 the library; PyTorch is used for device memory and streams only.  There is no fallback: if the
 shared library is missing or a call fails, an exception is raised.
@@ -92,6 +93,7 @@ KERNEL_NAMES = ["lean", "general", "general_scalar", "front", "layer", "build", 
 STATIC_WORKSPACE_BYTES = 8 * 1024 * 1024
 
 _lib = None
+_native = None
 
 
 class BspmmError(RuntimeError):
@@ -151,6 +153,35 @@ def lib():
     return _lib
 
 
+def native():
+    """The extension module of the run calls (``csrc/binding.cpp``); raises if it is not built."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _native as module
+        except ImportError as e:
+            raise RuntimeError("_native.so is missing or does not load: build it with `python -m "
+                               "paper_1903_11409_amd.build` (there is no fallback path)") from e
+        module.setup(_check, _ld, _raw_stream, _current_device)
+        _native = module
+    return _native
+
+
+def _current_device() -> int:
+    """First use of the current stream: PyTorch's device state may have to be initialised; from
+    then on its own functions are asked directly."""
+    import torch
+    device = torch.cuda.current_device()
+    _native.setup(_check, _ld, torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    return device
+
+
+def _raw_stream(device: int) -> int:
+    import torch
+    return torch._C._cuda_getCurrentRawStream(device)
+
+
 def _check(code: int, where: str) -> None:
     if code != OK:
         raise BspmmError(code, where)
@@ -165,9 +196,12 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
-def _ld(t, width: int) -> int:
+def _ld(t, width: Optional[int]) -> int:
     """Leading dimension of a row-major matrix held in a tensor; a tensor with fewer than two
-    rows (torch gives an empty one strides of zero) has none of its own and takes its width."""
+    rows (torch gives an empty one strides of zero) has none of its own and takes its width
+    (``width`` None: nothing but its own)."""
+    if width is None:
+        width = t.shape[-1]
     if t.dim() != 2 or t.shape[0] < 2:
         return max(int(width), int(t.shape[-1]) if t.dim() else 0)
     return int(t.stride(0))
@@ -302,20 +336,16 @@ def bspmm_create_static(hb: HostBatch, F: int, options: Optional[bspmm_options] 
 
 
 def bspmm_run(plan: int, B, C, ldb: int, ldc: int, stream=None) -> None:
-    _check(lib().bspmm_run(plan, _ptr(B), _ptr(C), int(ldb), int(ldc), _stream_handle(stream)),
-           "bspmm_run")
+    (_native or native()).run(plan, B, C, int(ldb), int(ldc), stream)
 
 
 def bspmm_run_gcn(plan: int, X, ldx: int, W, ldw: int, bias, Y, ldy: int, accumulate: bool = False,
                   stream=None) -> None:
-    _check(lib().bspmm_run_gcn(plan, _ptr(X), int(ldx), _ptr(W), int(ldw), _ptr(bias), _ptr(Y),
-                               int(ldy), 1 if accumulate else 0, _stream_handle(stream)),
-           "bspmm_run_gcn")
+    (_native or native()).run_gcn(plan, X, W, bias, Y, int(ldx), int(ldw), int(ldy), accumulate, stream)
 
 
 def bspmm_run_transposed(plan: int, dY, G, ldy: int, ldg: int, stream=None) -> None:
-    _check(lib().bspmm_run_transposed(plan, _ptr(dY), _ptr(G), int(ldy), int(ldg),
-                                      _stream_handle(stream)), "bspmm_run_transposed")
+    (_native or native()).run_transposed(plan, dY, G, int(ldy), int(ldg), stream)
 
 
 def bspmm_export_transposed(plan: int, rpt_t, colids_t, values_t, stream=None) -> None:
@@ -361,6 +391,14 @@ def bspmm_destroy(plan: Optional[int]) -> None:
         lib().bspmm_destroy(plan)
 
 
+def _rows_from_zero(off, length) -> int:
+    """Rows that the blocks [off, off + length) cover from row 0 on without a gap."""
+    order = np.argsort(off, kind="stable")
+    end = np.maximum.accumulate(np.concatenate([[0], (off + length)[order]]))
+    gaps = np.flatnonzero(off[order] > end[:-1])
+    return int(end[gaps[0]] if len(gaps) else end[-1])
+
+
 class Plan:
     """Owns a plan handle plus the torch tensors it borrows (CSR arrays and workspace).
 
@@ -373,8 +411,11 @@ class Plan:
     def __init__(self, batch, F: Optional[int] = None, options: Optional[bspmm_options] = None,
                  device="cuda:0", stream=None, coo=None):
         import torch
+        native()
         self.torch = torch
+        self.n_x = max(1, int(options.front_features)) if options is not None else 1
         self.F = int(F if F is not None else batch.F)
+        self._covered = [None, None]
         self.device = torch.device(device)
         dev = self.device
         self.options = options
@@ -420,18 +461,23 @@ class Plan:
         self.handle = bspmm_create(self.hb, self.F, options, self.workspace, nbytes, stream)
 
     def run(self, B, C, stream=None):
-        bspmm_run(self.handle, B, C, _ld(B, self.F), _ld(C, self.F), stream)
-        return C
+        return _native.plan_run(self.handle, B, C, self.F, stream)
 
     def run_gcn(self, X, W, bias, Y, accumulate: bool = False, stream=None):
         """Y (+)= A (X W + bias) in one launch (plan created with ``front_features``)."""
-        bspmm_run_gcn(self.handle, X, _ld(X, X.shape[-1]), W, _ld(W, self.F), bias, Y, _ld(Y, self.F),
-                      accumulate, stream)
-        return Y
+        return _native.plan_run_gcn(self.handle, X, W, bias, Y, self.n_x, self.F, accumulate, stream)
 
     def run_transposed(self, dY, G, stream=None):
-        bspmm_run_transposed(self.handle, dY, G, _ld(dY, self.F), _ld(G, self.F), stream)
-        return G
+        return _native.plan_run_transposed(self.handle, dY, G, self.F, stream)
+
+    def covered_rows(self, transposed: bool = False) -> int:
+        """Rows from the first on that every product writes: C's, or G's when ``transposed``."""
+        key = 1 if transposed else 0
+        if self._covered[key] is None:
+            # HostBatch keeps (rows, cols, .., b_row_off, c_row_off), HostCooBatch one array less
+            a = self.hb.arrays
+            self._covered[key] = _rows_from_zero(a[-2], a[1]) if transposed else _rows_from_zero(a[-1], a[0])
+        return self._covered[key]
 
     def export_transposed(self, stream=None):
         t = self.torch

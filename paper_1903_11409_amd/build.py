@@ -1,14 +1,18 @@
-"""Builds libbspmm.so (HIP kernels + scheduler + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libbspmm.so (HIP kernels + scheduler + C ABI) for gfx950 with hipcc, and _native.so (the
+CPython side of the binding) beside it, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbspmm.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["kernels.hip", "schedule.cpp", "api.cpp"]
+NATIVE_SOURCES = ["binding.cpp"]
 HEADERS = ["plan.hpp", "schedule.hpp", os.path.join("..", "..", "include", "bspmm.h")]
 
 
@@ -17,10 +21,10 @@ def lib_path() -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + NATIVE_SOURCES + HEADERS)
 
 
 def build(verbose: bool = False) -> str:
@@ -38,13 +42,18 @@ def build(verbose: bool = False) -> str:
            "-x", "hip", os.path.join(CSRC, "schedule.cpp"),
            "-x", "hip", os.path.join(CSRC, "api.cpp"),
            "-o", LIB]
-    if verbose:
-        print(" ".join(cmd), file=sys.stderr)
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + r.stdout)
-    if verbose and r.stdout.strip():
-        print(r.stdout, file=sys.stderr)
+    # the extension module finds libbspmm.so in its own folder
+    native = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+              "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-L" + HERE,
+              "-l:libbspmm.so", "-Wl,-rpath,$ORIGIN", "-o", NATIVE]
+    for c in (cmd, native):
+        if verbose:
+            print(" ".join(c), file=sys.stderr)
+        r = subprocess.run(c, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(os.path.basename(c[0]) + " failed:\n" + r.stdout)
+        if verbose and r.stdout.strip():
+            print(r.stdout, file=sys.stderr)
     return LIB
 
 

@@ -1,0 +1,72 @@
+"""The binding's own decisions: leading dimensions and streams of the native run calls, and which
+outputs of the autograd wrapper have to be cleared first."""
+import numpy as np
+import pytest
+
+from paper_1903_11409_amd import bspmm as K
+from paper_1903_11409_amd import workloads as W
+
+
+@pytest.mark.parametrize("blocks", [[], [(0, 4)], [(4, 3), (0, 4)], [(1, 4)], [(0, 4), (5, 2)], [(0, 4), (4, 0), (4, 1)],
+                                    [(0, 4), (0, 4), (2, 5)], [(7, 2), (0, 3), (3, 3)]])
+def test_rows_covered_from_the_first_on(blocks):
+    off = np.array([b[0] for b in blocks], dtype=np.int64)
+    length = np.array([b[1] for b in blocks], dtype=np.int32)
+    hit = np.zeros(16, dtype=bool)
+    for o, n in blocks:
+        hit[o:o + n] = True
+    assert K._rows_from_zero(off, length) == int(np.argmin(hit))
+
+
+def test_native_calls_check_their_arguments():
+    n = K.native()
+    for call in (lambda: n.run(None, None, None, 1, 1, 0), lambda: n.run_transposed(None, None, None, 1, 1, 0),
+                 lambda: n.run_gcn(None, None, None, None, None, 1, 1, 1, False, 0)):
+        with pytest.raises(K.BspmmError) as e:
+            call()
+        assert e.value.code == K.EINVAL
+    with pytest.raises(TypeError):
+        n.run(None, None)
+    with pytest.raises(TypeError):
+        n.run(None, None, None, "x", 1, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,ld", [(1, 64), (1, 72), (7, 64), (7, 68), (7, 65)])
+@pytest.mark.parametrize("stream", ["current", "object", "handle"])
+def test_leading_dimension_and_stream_of_a_plan_call(rows, ld, stream):
+    import torch
+    b = W.identity_batch(3, 64, [rows])
+    plan = K.Plan(b, device="cuda:0")
+    B = torch.zeros((rows, ld), device="cuda:0")
+    B[:, :64] = torch.from_numpy(b.B)
+    C = torch.full((rows, ld), -7.0, device="cuda:0")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        given = {"current": None, "object": side, "handle": side.cuda_stream}[stream]
+        assert plan.run(B[:, :64], C[:, :64], given) is not None
+        D = torch.empty_like(C)[:, :64]
+        plan.run_transposed(C[:, :64], D, given)
+    side.synchronize()
+    assert torch.equal(C[:, :64].cpu(), torch.from_numpy(b.B)) and torch.equal(D.cpu(), torch.from_numpy(b.B))
+    assert bool((C[:, 64:] == -7.0).all())
+    with pytest.raises(K.BspmmError):
+        K.bspmm_run(plan.handle, B, C, 63, ld)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("gap", [False, True])
+def test_autograd_rows_of_no_operation_are_zero(gap):
+    import torch
+    from paper_1903_11409_amd.autograd import batched_spmm
+    b = W.random_general(5, 12, [(9, 9, 30), (4, 4, 0), (11, 11, 25)], shuffle_blocks=gap)
+    plan = K.Plan(b, device="cuda:0")
+    rows = b.n_c_rows + (5 if gap else 0)
+    torch.empty(1 << 16, device="cuda:0").fill_(float("nan"))     # what an uncleared output would show
+    C = batched_spmm(plan, torch.from_numpy(b.B).cuda().requires_grad_(), rows)
+    covered = np.zeros(rows, dtype=bool)
+    for o, m in zip(b.c_row_off, b.rows):
+        covered[int(o):int(o) + int(m)] = True
+    got = C.detach().cpu().numpy()
+    assert np.isfinite(got).all() and not got[~covered].any()
