@@ -21,6 +21,8 @@ hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec
                         bool hubs, bool merged, hipStream_t stream);
 hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes,
                              hipStream_t stream);
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, int vec, bool flat, int grid,
+                            int lds_bytes, hipStream_t stream);
 hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream);
 hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool accumulate,
                             bool sets, bool wide, hipStream_t stream);
@@ -661,15 +663,15 @@ void make_stream_plan(bspmm_plan& p)
     }
 }
 
-// The item table of the lean kernel for direction d, when the schedule is lean and every offset
-// fits the table's 32-bit fields (else the direction keeps the general kernel).
+// The compact item table of direction d, when the schedule is made of whole-workgroup items and every
+// offset fits the table's 32-bit fields (else the direction keeps the general kernel).
 void make_lean_items(bspmm_plan& p, int d)
 {
     const Schedule& sc = p.sched[d];
     std::vector<LeanItem>& out = p.lean_items[d];
     out.clear();
     p.lean_blocks[d] = false;
-    if (!sc.lean) return;
+    if (!sc.whole) return;
     out.reserve(sc.items.size());
     constexpr int64_t kLimit = (int64_t)1 << 31;
     int32_t most_k = 0, most_m = 0;
@@ -690,14 +692,15 @@ void make_lean_items(bspmm_plan& p, int d)
             t.out_row = (uint32_t)w.out_row_off;
             t.m = w.m, t.k = w.k, t.nnz = w.nnz, t.row0 = w.row0, t.nrows = w.nrows, t.f0 = w.f0;
             t.sh = sh;
+            t.flags = w.fw << 8;
             if (w.staged & 1) {
                 const StagedLayout L = staged_layout(w.m, w.k, w.nnz, w.fw, 0, false);
-                t.flags = (w.staged & 2) ? 1 : 0;
+                t.flags |= (w.staged & 2) ? 1 : 0;
                 t.cv_byte = 4 * L.cv_off;
                 t.b_byte = 4 * L.b_off;
                 t.tile_vecs = w.k << sh;
             } else {
-                t.flags = 2;    // a row block: its entry range is filled in on the device
+                t.flags |= 2;    // a row block: its entry range is filled in on the device
                 p.lean_blocks[d] = true;
             }
             most_k = std::max(most_k, w.k);
@@ -1222,21 +1225,30 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     const bool vec4 = p->F % 4 == 0 && ld_in % 4 == 0 && ld_out % 4 == 0 &&
                       (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    if (p->lean_items[d].empty()) {
+        const hipError_t e = launch_bspmm(P, sc.launch_grid, p->knobs.lds_words * 4, vec4, sc.has_slices,
+                                          p->knobs.hubs, !sc.merged_sets.empty(), s);
+        return e == hipSuccess ? BSPMM_OK : hip_fail(e);
+    }
+    const int hrc = enqueue_hints(p, d, s);
+    if (hrc != BSPMM_OK) return hrc;
+    const LeanItem* items = reinterpret_cast<const LeanItem*>(p->ws + p->lay.lean[d]);
     // the lean kernel forms 32-bit byte offsets inside an operation's dense blocks and multiplies
     // in 24 bits: leading dimensions below 4 Mi floats, blocks below 4 GiB
     constexpr int64_t kMul24 = (int64_t)1 << 22, kOff32 = (int64_t)1 << 30;
-    const bool lean = vec4 && !p->lean_items[d].empty() && ld_in < kMul24 && ld_out < kMul24 &&
+    const bool lean = sc.lean && vec4 && ld_in < kMul24 && ld_out < kMul24 &&
                       (int64_t)p->lean_rows[d] * ld_in < kOff32 &&
                       (int64_t)p->lean_out_rows[d] * ld_out < kOff32;
+    hipError_t e;
     if (lean) {
-        const int hrc = enqueue_hints(p, d, s);
-        if (hrc != BSPMM_OK) return hrc;
+        e = launch_bspmm_lean(items, P, sc.launch_grid, p->knobs.lds_words * 4, s);
+    } else {
+        // (row blocks gather float2 from the input itself, so it has to start on 8 bytes too)
+        const bool vec2 = p->F % 2 == 0 && ld_in % 2 == 0 && ld_out % 2 == 0 &&
+                          ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 7) == 0;
+        const bool flat = ld_in == p->F && (reinterpret_cast<uintptr_t>(in) & 15) == 0;
+        e = launch_bspmm_any(items, P, vec4 ? 4 : (vec2 ? 2 : 1), flat, sc.launch_grid, p->knobs.lds_words * 4, s);
     }
-    hipError_t e = lean
-        ? launch_bspmm_lean(reinterpret_cast<const LeanItem*>(p->ws + p->lay.lean[d]), P,
-                            sc.launch_grid, p->knobs.lds_words * 4, s)
-        : launch_bspmm(P, sc.launch_grid, p->knobs.lds_words * 4, vec4, sc.has_slices,
-                       p->knobs.hubs, !sc.merged_sets.empty(), s);
     return e == hipSuccess ? BSPMM_OK : hip_fail(e);
 }
 
@@ -1962,7 +1974,7 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
     }
     info->transposed_supported = plan->transposed_supported ? 1 : 0;
     info->transposed_built = plan->transposed_built ? 1 : 0;
-    for (int d = 0; d < 2; ++d) info->lean[d] = plan->lean_items[d].empty() ? 0 : 1;
+    for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].lean && !plan->lean_items[d].empty() ? 1 : 0;
     if (plan->stream.on()) {
         info->front_stream[0] = plan->stream.graphs;
         info->front_stream[1] = plan->stream.lists * plan->stream.tiles;

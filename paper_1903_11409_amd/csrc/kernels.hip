@@ -1001,6 +1001,249 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// The lean launch for every other width and alignment (tile rows that are no power-of-two number
+// of float4, F % 4 != 0, operands or leading dimensions off 16 bytes, offsets beyond 32 bits):
+// the same items, the same order of the additions inside a row.
+//   VEC     floats per lane in the gather and the store: 4, or 2 where rows, leading dimensions
+//           and the output start on 8 bytes, or 1.  A row takes exactly fw / VEC lanes (a power of
+//           two above it left up to half of the lanes idle: 14 of 64 at F = 50).
+//   staging the dense tile goes global -> LDS without staging registers, all of it in flight
+//           (the general kernel's scalar path had four rows per lane group in flight and took
+//           seven round trips for a tile of 110 rows):
+//             VEC = 4   16 bytes per lane, rows of float4
+//             flat      the tile is whole rows of a packed matrix, so it is one run of memory:
+//                       16 bytes per lane from the last 16-byte boundary before it (the tile then
+//                       starts 0 to 3 words into its place), single floats at the end
+//             else      4 bytes per lane
+// Bound: latency (a workgroup's chain of item, staging and gather).  200 rectangular operations
+// of 1 to 220 rows and columns, F = 50: forward 15.9 -> 6.4 us, transposed (rows of up to 660
+// entries) 33 -> 9.6 us against the general kernel's scalar path.
+// ---------------------------------------------------------------------------------------
+// n / d for 0 <= n < 2^21 and 1 <= d <= 256: (n + 1/2) / d is at least 1/512 away from a whole
+// number, further than the three roundings reach.
+__device__ __forceinline__ uint32_t div_small(uint32_t n, float inv_d)
+{
+    return (uint32_t)(((float)n + 0.5f) * inv_d);
+}
+
+template <int VEC> struct AnyVec;
+template <> struct AnyVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
+template <> struct AnyVec<2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct AnyVec<1> { typedef float type __attribute__((ext_vector_type(1))); };
+
+template <int VEC>
+__device__ __forceinline__ void any_fma(typename AnyVec<VEC>::type& acc, float a, const typename AnyVec<VEC>::type& b)
+{
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(a, b[i], acc[i]);
+}
+
+// Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's vector of the
+// entry's dense row.  Eight entries in flight while there are eight, then four at a time with
+// the entries past the end counting as zero (see gather_row).
+template <int VEC, typename Entry, typename Dense>
+__device__ __forceinline__ typename AnyVec<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
+{
+    using VT = typename AnyVec<VEC>::type;
+    VT acc = 0.f;
+    int p = p0;
+    for (; p + 8 <= p1; p += 8) {
+        int2 e[8];
+        VT b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = entry(p + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = dense(e[u].x);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) any_fma<VEC>(acc, __int_as_float(e[u].y), b[u]);
+    }
+    const int last = p1 - 1;
+    for (; p < p1; p += 4) {
+        int2 e[4];
+        VT b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = entry(min(p + u, last));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = dense(e[u].x);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) any_fma<VEC>(acc, p + u < p1 ? __int_as_float(e[u].y) : 0.f, b[u]);
+    }
+    return acc;
+}
+
+// (rows that start off 16 bytes share their first and last lines with their neighbours: only
+// whole-vector rows are stored past the caches)
+template <int VEC>
+__device__ __forceinline__ void any_store(float* p, const typename AnyVec<VEC>::type& v)
+{
+    using VT = typename AnyVec<VEC>::type;
+    if constexpr (VEC == 4)
+        __builtin_nontemporal_store(v, reinterpret_cast<VT*>(p));
+    else
+        *reinterpret_cast<VT*>(p) = v;
+}
+
+// Row block of the generic bin (see lean_row_block): dense rows gathered from global memory.
+template <int VEC>
+__device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const int32_t* __restrict__ rpt,
+                                              const int32_t* __restrict__ colids,
+                                              const float* __restrict__ values, const float* __restrict__ in,
+                                              float* __restrict__ out, int64_t ld_in, int64_t ld_out,
+                                              uint32_t lds_words)
+{
+    using VT = typename AnyVec<VEC>::type;
+    const uint32_t tid = threadIdx.x;
+    const int nrows = it.nrows, k = it.k, nnz = it.nnz;
+    const uint32_t nvec = max((uint32_t)it.flags >> 8, (uint32_t)VEC) / VEC;
+    const uint32_t groups = kThreads / nvec;
+    const uint32_t g = div_small(tid, 1.f / (float)nvec), l = tid - g * nvec;
+    const int pbeg = min(max(it.tile_vecs, 0), nnz);
+    const int cnt = min(max(it.count, 0), nnz - pbeg);
+    const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
+    const int32_t* __restrict__ ci = colids + it.nz_off + (uint32_t)pbeg;
+    const float* __restrict__ va = values + it.nz_off + (uint32_t)pbeg;
+    const uint32_t cv_off = (uint32_t)round_up(nrows + 1, 2);
+    const bool fits = cv_off + 2u * (uint32_t)cnt <= lds_words;
+    int2* cv = reinterpret_cast<int2*>(sm + cv_off);
+    if ((int)tid <= nrows) sm[tid] = min(max(rp[tid], 0), nnz);
+    for (int i = tid + kThreads; i <= nrows; i += kThreads) sm[i] = min(max(rp[i], 0), nnz);
+    if (fits)
+        for (int p = tid; p < cnt; p += kThreads) {
+            const int c = ci[p];
+            cv[p] = make_int2((unsigned)c < (unsigned)k ? c : 0, __float_as_int(va[p]));
+        }
+    __syncthreads();
+    if (g >= groups) return;
+    const float* __restrict__ src = in + ((int64_t)it.in_row * ld_in + it.f0 + (int)l * VEC);
+    float* __restrict__ dst = out + (((int64_t)it.out_row + it.row0) * ld_out + it.f0 + (int)l * VEC);
+    auto dense = [&](int c) { return *reinterpret_cast<const VT*>(src + c * ld_in); };
+    for (uint32_t i = g; i < (uint32_t)nrows; i += groups) {
+        const int p1 = min(max(sm[i + 1] - pbeg, 0), cnt);
+        const int p0 = min(max(sm[i] - pbeg, 0), p1);
+        const VT acc = fits ? any_row<VEC>(p0, p1, [&](int p) { return cv[p]; }, dense)
+                            : any_row<VEC>(p0, p1, [&](int p) {
+                                  const int c = ci[p];
+                                  return make_int2((unsigned)c < (unsigned)k ? c : 0, __float_as_int(va[p]));
+                              }, dense);
+        any_store<VEC>(dst + i * ld_out, acc);
+    }
+}
+
+template <int VEC>
+__global__ void __launch_bounds__(kThreads)
+bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
+                 const int32_t* __restrict__ colids, const float* __restrict__ values,
+                 const float* __restrict__ in, float* __restrict__ out, int64_t ld_in, int64_t ld_out,
+                 uint32_t lds_words, int flat)
+{
+    using VT = typename AnyVec<VEC>::type;
+    extern __shared__ __align__(16) int sm[];
+    const uint32_t tid = threadIdx.x;
+    const LeanItem it = items[blockIdx.x];
+    if (it.flags & 2) {        // (the same for the whole workgroup)
+        any_row_block<VEC>(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+        return;
+    }
+    const int m = it.m, k = it.k, nnz = it.nnz;
+    const uint32_t fw = max((uint32_t)it.flags >> 8, (uint32_t)VEC);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
+    char* lds = reinterpret_cast<char*>(sm);
+    char* bs = lds + it.b_byte;
+    typedef const void __attribute__((address_space(1)))* gptr;
+    typedef void __attribute__((address_space(3)))* lptr;
+
+    // ---- dense tile, global -> LDS
+    uint32_t shift = 0;                              // words the tile starts into its place
+    const int64_t at = (int64_t)it.in_row * ld_in + it.f0;
+    if (VEC == 4) {
+        const uint32_t nvec = fw / 4;
+        const float inv = 1.f / (float)nvec;
+        const uint32_t total = (uint32_t)k * nvec;
+        const float* __restrict__ src = in + at;
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
+            const uint32_t e = e0 + wl;
+            const uint32_t r = div_small(e, inv), c = e - r * nvec;
+            if (e < total)
+                __builtin_amdgcn_global_load_lds((gptr)(src + (r * ld_in + 4 * c)), (lptr)(bs + (e0 << 4)), 16, 0, 0);
+        }
+    } else if (flat && fw == (uint32_t)ld_in) {      // (f0 is 0 then)
+        shift = (uint32_t)at & 3;
+        const float* __restrict__ src = in + (at - shift);
+        const uint32_t words = (uint32_t)k * fw + shift, total = words >> 2, rest = words & 3;
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads)
+            if (e0 + wl < total)
+                __builtin_amdgcn_global_load_lds((gptr)(src + 4 * (e0 + wl)), (lptr)(bs + (e0 << 4)), 16, 0, 0);
+        if (wave == 0 && wl < rest)
+            __builtin_amdgcn_global_load_lds((gptr)(src + 4 * total + wl), (lptr)(bs + (total << 4)), 4, 0, 0);
+    } else {
+        const float inv = 1.f / (float)fw;
+        const uint32_t total = (uint32_t)k * fw;
+        const float* __restrict__ src = in + at;
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
+            const uint32_t e = e0 + wl;
+            const uint32_t r = div_small(e, inv), c = e - r * fw;
+            if (e < total)
+                __builtin_amdgcn_global_load_lds((gptr)(src + (r * ld_in + c)), (lptr)(bs + (e0 << 2)), 4, 0, 0);
+        }
+    }
+
+    // ---- CSR (as bspmm_lean_kernel; the first four entries of a lane in one round trip)
+    const int32_t* __restrict__ rp = rpt + it.rpt_off;
+    const int32_t* __restrict__ ci = colids + it.nz_off;
+    const float* __restrict__ va = values + it.nz_off;
+    const uint32_t nvec = fw / VEC, groups = kThreads / nvec;
+    const uint32_t g = div_small(tid, 1.f / (float)nvec), l = tid - g * nvec;
+    const uint32_t um = (uint32_t)m;
+    const uint32_t r_first = (uint32_t)it.row0 + g;
+    const int q0 = rp[min(r_first, um)];
+    const int q1 = rp[min(r_first + 1, um)];
+    const uint32_t ri = min(tid, um);
+    const int rv = rp[ri];
+    int c[4] = {0, 0, 0, 0};
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t last = (uint32_t)max(nnz - 1, 0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (nnz > u * kThreads) {                    // (the same for every lane)
+            const uint32_t i = min(tid + u * kThreads, last);
+            c[u] = ci[i];
+            a[u] = va[i];
+        }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- LDS writes, clamped as in bspmm_lean_kernel; an entry carries the byte offset of its
+    // dense row inside the tile
+    const uint32_t stride = fw << 2;
+    int2* cv = reinterpret_cast<int2*>(lds + it.cv_byte);
+    sm[ri] = min(max(rv, 0), nnz);
+    auto entry = [&](int col, float v) {
+        return make_int2((unsigned)col < (unsigned)k ? (int)__umul24((uint32_t)col, stride) : 0, __float_as_int(v));
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (nnz > u * kThreads) cv[min(tid + u * kThreads, last)] = entry(c[u], a[u]);
+    if (m >= kThreads)
+        for (int i = tid + kThreads; i <= m; i += kThreads) sm[i] = min(max(rp[i], 0), nnz);
+    if (nnz > 4 * kThreads)
+        for (int p = tid + 4 * kThreads; p < nnz; p += kThreads) cv[p] = entry(ci[p], va[p]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // direct-to-LDS loads landed
+    __syncthreads();
+
+    // ---- rows
+    if (g >= groups) return;
+    const char* bcol = bs + ((shift + l * VEC) << 2);
+    float* __restrict__ dst = out + ((int64_t)it.out_row * ld_out + it.f0 + (int)l * VEC);
+    const uint32_t row_end = (uint32_t)(it.row0 + it.nrows);
+    auto sum = [&](int p0, int p1) {
+        return any_row<VEC>(p0, p1, [&](int p) { return cv[p]; },
+                            [&](int off) { return *reinterpret_cast<const VT*>(bcol + off); });
+    };
+    if (r_first < row_end) any_store<VEC>(dst + r_first * ld_out, sum(min(max(q0, 0), nnz), min(max(q1, 0), nnz)));
+    for (uint32_t r = r_first + groups; r < row_end; r += groups)
+        any_store<VEC>(dst + r * ld_out, sum(sm[r], sm[r + 1]));
+}
+
 // Once per plan and direction: the position of every row block's entries goes into its item.
 __global__ void lean_hints_kernel(LeanItem* items, int n, const int32_t* __restrict__ rpt)
 {
@@ -2596,6 +2839,18 @@ hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int g
     hipLaunchKernelGGL(bspmm_lean_kernel, dim3(grid), dim3(kThreads), lds_bytes, stream, items,
                        P.rpt, P.colids, P.values, P.in, P.out, (uint32_t)P.ld_in,
                        (uint32_t)P.ld_out, (uint32_t)(lds_bytes / 4));
+    return hipGetLastError();
+}
+
+// vec: floats per lane (4, 2 or 1); flat: the dense input is packed (ld_in is the feature width)
+// and starts on 16 bytes.
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, int vec, bool flat, int grid,
+                            int lds_bytes, hipStream_t stream)
+{
+    if (grid <= 0) return hipSuccess;
+    auto* fn = vec == 4 ? bspmm_any_kernel<4> : (vec == 2 ? bspmm_any_kernel<2> : bspmm_any_kernel<1>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), lds_bytes, stream, items, P.rpt, P.colids, P.values, P.in,
+                       P.out, P.ld_in, P.ld_out, (uint32_t)(lds_bytes / 4), flat ? 1 : 0);
     return hipGetLastError();
 }
 

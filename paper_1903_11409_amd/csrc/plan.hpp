@@ -51,8 +51,8 @@ struct alignas(16) WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "WorkItem must be 64 bytes");
 
-// The same unit of work for the lean kernel (launches made only of whole-workgroup items with a
-// power-of-two tile): 32-bit offsets, and everything the host can derive - LDS placement, tile
+// The same unit of work for launches made only of whole-workgroup items (the lean kernel: float4
+// path, power-of-two tiles; bspmm_any_kernel: every other width): 32-bit offsets, and everything the host can derive - LDS placement, tile
 // shape - already derived, so that a workgroup's scalar preamble is a handful of instructions.
 // Two kinds: staged items (the operation and its dense tile in LDS) and row blocks of the
 // generic bin (operations too large for LDS: the dense rows are gathered from L2).  For a row
@@ -66,12 +66,12 @@ struct alignas(16) LeanItem {
     int32_t m, k, nnz;    // as WorkItem
     int32_t row0, nrows;  // output rows of this item
     int32_t f0;           // first feature column
-    int32_t sh;           // log2 of the float4 per tile row (tile width = 4 << sh floats)
+    int32_t sh;           // lean kernel: log2 of the float4 per tile row (tile width = 4 << sh floats)
     int32_t flags;        // bit 0: no other item reads this dense tile; bit 1: row block of the
-                          // generic bin
+                          // generic bin; bits 8 and up: tile width in floats
     int32_t cv_byte;      // staged: LDS byte offset of the (row offset, value) pairs
     int32_t b_byte;       // staged: LDS byte offset of the dense tile
-    int32_t tile_vecs;    // staged: float4 in the tile, k << sh
+    int32_t tile_vecs;    // staged: float4 in the tile, k << sh (lean kernel)
                           // row block: its first entry, rpt[row0] (filled on the device)
     int32_t count;        // row block: its entries, rpt[row0 + nrows] - rpt[row0] (filled on the
                           // device)

@@ -60,6 +60,14 @@ int bin_range(int bin)
 
 int draft_range(const Draft& x) { return x.fused >= 0 ? 1 : bin_range(x.bin); }
 
+// Output rows a whole workgroup has in flight (the kernels give a row exactly the lanes it
+// fills, two floats each where F is even but not a multiple of four).
+int rows_in_flight(int fw, int vec, int F)
+{
+    const int per_lane = vec == 4 ? 4 : (F % 2 == 0 ? 2 : 1);
+    return std::max(1, kThreads / std::max(1, (fw + per_lane - 1) / per_lane));
+}
+
 // Candidate tile widths, widest first.
 std::vector<int> tile_candidates(int F, const Knobs& kn)
 {
@@ -88,6 +96,7 @@ bool fits_slot(const DirOps& o, int i, int tile, int F, int vec, int lanes, int 
     if (max_passes > 0 && (lanes_wanted + lanes - 1) / lanes > max_passes) return false;
     const int64_t head = (int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i];
     int64_t need = (head + 3) / 4 * 4 + (int64_t)o.k[i] * (round_up(fw, 4) + kn.pad);
+    if (vec == 1) need += 4;   // (a tile copied in 16-byte pieces starts up to 3 words into its place)
     if (kn.hubs && lanes == kThreads) need += hub_words(o.nnz[i] / kHubMin, fw);   // as staged_layout()
     if (kn.front > 0)   // a weight tile and a bias tile per channel and at least 16 rows of X_i ride along
         need += 16 * (int64_t)kn.front +
@@ -181,7 +190,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     if (!sink.out) {    // counting: the same items in closed form
         auto per_tile = [&](int fw) {
             if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-                const int chunk = cap * (kThreads / lanes_per_row(fw, vec));
+                const int chunk = cap * rows_in_flight(fw, vec, F);
                 return (o.m[i] + chunk - 1) / chunk;
             }
             if (ch.bin != BSPMM_BIN_GENERIC) return 1;
@@ -199,8 +208,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     for (int f0 = 0; f0 < F; f0 += tile) {
         const int fw = std::min(tile, F - f0);
         if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-            const int rows_per_pass = kThreads / lanes_per_row(fw, vec);
-            const int chunk = cap * rows_per_pass;
+            const int chunk = cap * rows_in_flight(fw, vec, F);
             for (int r0 = 0; r0 < o.m[i]; r0 += chunk)
                 sink.add(o, i, ch.bin, r0, std::min(chunk, o.m[i] - r0), f0, fw, 1, -1);
         } else if (ch.bin != BSPMM_BIN_GENERIC) {
@@ -857,11 +865,12 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     s.item_op.resize(s.items.size(), -1);
     s.grid = wg;
     s.launch_grid = kn.persistent_wgs > 0 ? std::min(wg, W) : wg;
-    // The lean kernel serves launches made only of whole-workgroup items (staged operations and
-    // row blocks of the generic bin) on the float4 path whose tile rows are a power-of-two number
-    // of float4.
-    s.lean = vec == 4 && kn.pad == 0 && !kn.hubs && kn.front == 0 && kn.persistent_wgs == 0 &&
-             s.merged_sets.empty() && s.wg_end[0] == wg && wg > 0;
+    // Launches made only of whole-workgroup items (staged operations and row blocks of the generic
+    // bin) run from the compact item table; the lean kernel serves those on the float4 path whose
+    // tile rows are a power-of-two number of float4.
+    s.whole = kn.pad == 0 && !kn.hubs && kn.front == 0 && kn.persistent_wgs == 0 && s.merged_sets.empty() &&
+              s.wg_end[0] == wg && wg > 0;
+    s.lean = s.whole && vec == 4;
     for (const WorkItem& w : s.items) {
         if (!s.lean) break;
         if (w.nrows <= 0) continue;
