@@ -21,7 +21,7 @@ hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec
                         bool hubs, bool merged, hipStream_t stream);
 hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes,
                              hipStream_t stream);
-hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, int vec, bool flat, int grid,
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, int grid,
                             int lds_bytes, hipStream_t stream);
 hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream);
 hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool accumulate,
@@ -1241,13 +1241,9 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
                       (int64_t)p->lean_out_rows[d] * ld_out < kOff32;
     hipError_t e;
     if (lean) {
-        e = launch_bspmm_lean(items, P, sc.launch_grid, p->knobs.lds_words * 4, s);
+        e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, s);
     } else {
-        // (row blocks gather float2 from the input itself, so it has to start on 8 bytes too)
-        const bool vec2 = p->F % 2 == 0 && ld_in % 2 == 0 && ld_out % 2 == 0 &&
-                          ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 7) == 0;
-        const bool flat = ld_in == p->F && (reinterpret_cast<uintptr_t>(in) & 15) == 0;
-        e = launch_bspmm_any(items, P, vec4 ? 4 : (vec2 ? 2 : 1), flat, sc.launch_grid, p->knobs.lds_words * 4, s);
+        e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, sc.launch_grid, sc.lds_words * 4, s);
     }
     return e == hipSuccess ? BSPMM_OK : hip_fail(e);
 }

@@ -1005,21 +1005,28 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
 // The lean launch for every other width and alignment (tile rows that are no power-of-two number
 // of float4, F % 4 != 0, operands or leading dimensions off 16 bytes, offsets beyond 32 bits):
 // the same items, the same order of the additions inside a row.
-//   VEC     floats per lane in the gather and the store: 4, or 2 where rows, leading dimensions
-//           and the output start on 8 bytes, or 1.  A row takes exactly fw / VEC lanes (a power of
-//           two above it left up to half of the lanes idle: 14 of 64 at F = 50).
-//   staging the dense tile goes global -> LDS without staging registers, all of it in flight
-//           (the general kernel's scalar path had four rows per lane group in flight and took
-//           seven round trips for a tile of 110 rows):
-//             VEC = 4   16 bytes per lane, rows of float4
-//             flat      the tile is whole rows of a packed matrix, so it is one run of memory:
-//                       16 bytes per lane from the last 16-byte boundary before it (the tile then
-//                       starts 0 to 3 words into its place), single floats at the end
-//             else      4 bytes per lane
-// Bound: latency (a workgroup's chain of item, staging and gather).  200 rectangular operations
-// of 1 to 220 rows and columns, F = 50: forward 15.9 -> 6.4 us, transposed (rows of up to 660
-// entries) 33 -> 9.6 us against the general kernel's scalar path.
+//
+// Staging.  Instruction issue is what such a tile costs (a wavefront instruction takes four
+// cycles): copied word by word it is 25 instructions per 256 bytes, and 900 operations of 1 to
+// 220 rows at F = 127 spent half of their 33 us there.  So every row of the tile is copied as the
+// 16-byte words of memory it lies in, 1 KiB per wavefront instruction, straight into LDS: its
+// first column then sits zero to three words into the row's place, which an entry's offset
+// takes into account.  A tile that is whole rows of a packed matrix is one run of memory and is
+// copied as such.  Only a dense input that does not start on 16 bytes is copied word by word.
+//
+// Rows.  A row takes ceil(fw / 4) lanes of four floats, no power of two; the last lane stores what
+// is left of the row.  Operations whose rows average more than kLongRow entries take a lane per
+// float instead: the additions of a row are a serial chain, and four per entry and lane made
+// the chain of a row of 660 entries 2 us longer.
+// Bound: small launches the chain of item, staging and gather, large ones memory (900 operations of 1 to
+// 220 rows, F = 127: 100 MB in 22 us).  200 of them at F = 50: forward 15.9 -> 6.0 us, transposed (rows of up
+// to 660 entries) 33 -> 7.3 us against the general kernel's scalar path.
 // ---------------------------------------------------------------------------------------
+enum AnyMode {
+    kAnyWindows = 1,   // the dense input starts on 16 bytes: rows are copied as 16-byte words
+    kAnyTight = 2      // no room for such words beside a row (F % 4 == 0; windows then need ld_in % 4 == 0 too)
+};
+
 // n / d for 0 <= n < 2^21 and 1 <= d <= 256: (n + 1/2) / d is at least 1/512 away from a whole
 // number, further than the three roundings reach.
 __device__ __forceinline__ uint32_t div_small(uint32_t n, float inv_d)
@@ -1027,36 +1034,42 @@ __device__ __forceinline__ uint32_t div_small(uint32_t n, float inv_d)
     return (uint32_t)(((float)n + 0.5f) * inv_d);
 }
 
-template <int VEC> struct AnyVec;
-template <> struct AnyVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
-template <> struct AnyVec<2> { typedef float type __attribute__((ext_vector_type(2))); };
-template <> struct AnyVec<1> { typedef float type __attribute__((ext_vector_type(1))); };
+template <int VEC> struct Floats { typedef float type __attribute__((ext_vector_type(VEC))); };
+template <int VEC> struct FloatsAt4 { typedef float type __attribute__((ext_vector_type(VEC), aligned(4))); };
 
-template <int VEC>
-__device__ __forceinline__ void any_fma(typename AnyVec<VEC>::type& acc, float a, const typename AnyVec<VEC>::type& b)
+template <int VEC, bool ALIGNED>
+__device__ __forceinline__ typename Floats<VEC>::type any_load(const void* p)
 {
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(a, b[i], acc[i]);
+    using VT = typename Floats<VEC>::type;
+    if constexpr (ALIGNED)
+        return *reinterpret_cast<const VT*>(p);
+    else
+        return *reinterpret_cast<const typename FloatsAt4<VEC>::type*>(p);
 }
 
-// Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's vector of the
-// entry's dense row.  Eight entries in flight while there are eight, then four at a time with
-// the entries past the end counting as zero (see gather_row).
+// Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's floats of the
+// entry's dense row.  N entries in flight while there are as many, then four at a time with the
+// entries past the end counting as zero (see gather_row).
 template <int VEC, typename Entry, typename Dense>
-__device__ __forceinline__ typename AnyVec<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
+__device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
 {
-    using VT = typename AnyVec<VEC>::type;
+    using VT = typename Floats<VEC>::type;
+    constexpr int N = VEC == 4 ? 8 : 16;
     VT acc = 0.f;
     int p = p0;
-    for (; p + 8 <= p1; p += 8) {
-        int2 e[8];
-        VT b[8];
+    auto fma = [&](float a, const VT& b) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = entry(p + u);
+        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(a, b[i], acc[i]);
+    };
+    for (; p + N <= p1; p += N) {
+        int2 e[N];
+        VT b[N];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) b[u] = dense(e[u].x);
+        for (int u = 0; u < N; ++u) e[u] = entry(p + u);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) any_fma<VEC>(acc, __int_as_float(e[u].y), b[u]);
+        for (int u = 0; u < N; ++u) b[u] = dense(e[u].x);
+#pragma unroll
+        for (int u = 0; u < N; ++u) fma(__int_as_float(e[u].y), b[u]);
     }
     const int last = p1 - 1;
     for (; p < p1; p += 4) {
@@ -1067,37 +1080,87 @@ __device__ __forceinline__ typename AnyVec<VEC>::type any_row(int p0, int p1, En
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = dense(e[u].x);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) any_fma<VEC>(acc, p + u < p1 ? __int_as_float(e[u].y) : 0.f, b[u]);
+        for (int u = 0; u < 4; ++u) fma(p + u < p1 ? __int_as_float(e[u].y) : 0.f, b[u]);
     }
     return acc;
 }
 
-// (rows that start off 16 bytes share their first and last lines with their neighbours: only
-// whole-vector rows are stored past the caches)
-template <int VEC>
-__device__ __forceinline__ void any_store(float* p, const typename AnyVec<VEC>::type& v)
+// The lane's `n` floats of an output row (n < VEC on the last lane of a row only).  Rows off 16
+// bytes share lines with their neighbours, so only aligned rows are stored past the caches.
+template <int VEC, bool ALIGNED>
+__device__ __forceinline__ void any_store(float* p, const typename Floats<VEC>::type& v, int n)
 {
-    using VT = typename AnyVec<VEC>::type;
-    if constexpr (VEC == 4)
-        __builtin_nontemporal_store(v, reinterpret_cast<VT*>(p));
-    else
-        *reinterpret_cast<VT*>(p) = v;
+    if constexpr (VEC == 1) {
+        *p = v[0];
+    } else if constexpr (ALIGNED) {
+        __builtin_nontemporal_store(v, reinterpret_cast<typename Floats<VEC>::type*>(p));
+    } else if (n >= VEC) {
+        *reinterpret_cast<typename FloatsAt4<VEC>::type*>(p) = v;
+    } else {
+        p[0] = v[0];
+        if (n > 1) p[1] = v[1];
+        if (n > 2) p[2] = v[2];
+    }
 }
 
+// Rows [0, nrows) of an item: sum(p0, p1, dense) of every row with the row pointers row(i), lanes of
+// VEC floats.  `first` loads a lane's floats given its offset in floats from the row's start.
+template <int VEC, bool ALIGNED, typename Row, typename Entry, typename Dense>
+__device__ __forceinline__ void any_rows(uint32_t fw, int nrows, float* __restrict__ dst, int64_t ld_out, Row row,
+                                         Entry entry, Dense dense)
+{
+    const uint32_t nvec = (fw + VEC - 1) / VEC, groups = kThreads / nvec;
+    const uint32_t g = div_small(threadIdx.x, 1.f / (float)nvec), l = threadIdx.x - g * nvec;
+    if (g >= groups) return;
+    const int n = (int)(fw - VEC * l);
+    float* p = dst + (g * ld_out + VEC * l);
+    const int64_t step = groups * ld_out;
+    for (int i = g; i < nrows; i += groups, p += step) {
+        int p0, p1;
+        row(i, p0, p1);
+        any_store<VEC, ALIGNED>(p, any_row<VEC>(p0, p1, entry, [&](int key) {
+            return dense.template operator()<VEC>(key, (int)(VEC * l), n);
+        }), n);
+    }
+}
+
+// A lane's floats out of the LDS tile (the last lane of a row may read up to three words past
+// the row: LDS of this item) and out of global memory (nothing past the row's end is read).
+template <bool ALIGNED> struct TileRows {
+    const char* tile;
+    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int off, int l, int) const
+    {
+        return any_load<VEC, ALIGNED>(tile + off + 4 * l);
+    }
+};
+template <bool ALIGNED> struct GlobalRows {
+    const float* src;
+    int64_t ld;
+    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int c, int l, int n) const
+    {
+        const float* p = src + (c * ld + l);
+        if (ALIGNED || n >= VEC) return any_load<VEC, ALIGNED>(p);
+        typename Floats<VEC>::type v = 0.f;
+        v[0] = p[0];
+        if constexpr (VEC == 4) {
+            if (n > 1) v[1] = p[1];
+            if (n > 2) v[2] = p[2];
+        }
+        return v;
+    }
+};
+
 // Row block of the generic bin (see lean_row_block): dense rows gathered from global memory.
-template <int VEC>
+template <bool ALIGNED>
 __device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const int32_t* __restrict__ rpt,
                                               const int32_t* __restrict__ colids,
                                               const float* __restrict__ values, const float* __restrict__ in,
                                               float* __restrict__ out, int64_t ld_in, int64_t ld_out,
                                               uint32_t lds_words)
 {
-    using VT = typename AnyVec<VEC>::type;
     const uint32_t tid = threadIdx.x;
     const int nrows = it.nrows, k = it.k, nnz = it.nnz;
-    const uint32_t nvec = max((uint32_t)it.flags >> 8, (uint32_t)VEC) / VEC;
-    const uint32_t groups = kThreads / nvec;
-    const uint32_t g = div_small(tid, 1.f / (float)nvec), l = tid - g * nvec;
+    const uint32_t fw = max((uint32_t)it.flags >> 8, 1u);
     const int pbeg = min(max(it.tile_vecs, 0), nnz);
     const int cnt = min(max(it.count, 0), nnz - pbeg);
     const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
@@ -1106,69 +1169,61 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const
     const uint32_t cv_off = (uint32_t)round_up(nrows + 1, 2);
     const bool fits = cv_off + 2u * (uint32_t)cnt <= lds_words;
     int2* cv = reinterpret_cast<int2*>(sm + cv_off);
-    if ((int)tid <= nrows) sm[tid] = min(max(rp[tid], 0), nnz);
-    for (int i = tid + kThreads; i <= nrows; i += kThreads) sm[i] = min(max(rp[i], 0), nnz);
+    for (int i = tid; i <= nrows; i += kThreads) sm[i] = min(max(rp[i], 0), nnz);
+    auto global_entry = [&](int p) {
+        const int c = ci[p];
+        return make_int2((unsigned)c < (unsigned)k ? c : 0, __float_as_int(va[p]));
+    };
     if (fits)
-        for (int p = tid; p < cnt; p += kThreads) {
-            const int c = ci[p];
-            cv[p] = make_int2((unsigned)c < (unsigned)k ? c : 0, __float_as_int(va[p]));
-        }
+        for (int p = tid; p < cnt; p += kThreads) cv[p] = global_entry(p);
     __syncthreads();
-    if (g >= groups) return;
-    const float* __restrict__ src = in + ((int64_t)it.in_row * ld_in + it.f0 + (int)l * VEC);
-    float* __restrict__ dst = out + (((int64_t)it.out_row + it.row0) * ld_out + it.f0 + (int)l * VEC);
-    auto dense = [&](int c) { return *reinterpret_cast<const VT*>(src + c * ld_in); };
-    for (uint32_t i = g; i < (uint32_t)nrows; i += groups) {
-        const int p1 = min(max(sm[i + 1] - pbeg, 0), cnt);
-        const int p0 = min(max(sm[i] - pbeg, 0), p1);
-        const VT acc = fits ? any_row<VEC>(p0, p1, [&](int p) { return cv[p]; }, dense)
-                            : any_row<VEC>(p0, p1, [&](int p) {
-                                  const int c = ci[p];
-                                  return make_int2((unsigned)c < (unsigned)k ? c : 0, __float_as_int(va[p]));
-                              }, dense);
-        any_store<VEC>(dst + i * ld_out, acc);
-    }
+    float* __restrict__ dst = out + (((int64_t)it.out_row + it.row0) * ld_out + it.f0);
+    const GlobalRows<ALIGNED> dense = {in + ((int64_t)it.in_row * ld_in + it.f0), ld_in};
+    auto row = [&](int i, int& p0, int& p1) {
+        p1 = min(max(sm[i + 1] - pbeg, 0), cnt);
+        p0 = min(max(sm[i] - pbeg, 0), p1);
+    };
+    auto lds_entry = [&](int p) { return cv[p]; };
+    const bool long_rows = cnt > kLongRow * nrows;
+    if (!fits)
+        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, global_entry, dense);
+    else if (long_rows)
+        any_rows<1, false>(fw, nrows, dst, ld_out, row, lds_entry, dense);
+    else
+        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, lds_entry, dense);
 }
 
-template <int VEC>
+// mode: kAnyWindows, kAnyTight (ALIGNED implies both).
+template <bool ALIGNED>
 __global__ void __launch_bounds__(kThreads)
 bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                  const int32_t* __restrict__ colids, const float* __restrict__ values,
                  const float* __restrict__ in, float* __restrict__ out, int64_t ld_in, int64_t ld_out,
-                 uint32_t lds_words, int flat)
+                 uint32_t lds_words, int mode)
 {
-    using VT = typename AnyVec<VEC>::type;
     extern __shared__ __align__(16) int sm[];
     const uint32_t tid = threadIdx.x;
     const LeanItem it = items[blockIdx.x];
     if (it.flags & 2) {        // (the same for the whole workgroup)
-        any_row_block<VEC>(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+        any_row_block<ALIGNED>(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         return;
     }
     const int m = it.m, k = it.k, nnz = it.nnz;
-    const uint32_t fw = max((uint32_t)it.flags >> 8, (uint32_t)VEC);
+    const uint32_t fw = max((uint32_t)it.flags >> 8, 1u);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
     char* lds = reinterpret_cast<char*>(sm);
     char* bs = lds + it.b_byte;
     typedef const void __attribute__((address_space(1)))* gptr;
     typedef void __attribute__((address_space(3)))* lptr;
 
-    // ---- dense tile, global -> LDS
-    uint32_t shift = 0;                              // words the tile starts into its place
+    // ---- dense tile, global -> LDS: rows of `chunks` 16-byte words
     const int64_t at = (int64_t)it.in_row * ld_in + it.f0;
-    if (VEC == 4) {
-        const uint32_t nvec = fw / 4;
-        const float inv = 1.f / (float)nvec;
-        const uint32_t total = (uint32_t)k * nvec;
-        const float* __restrict__ src = in + at;
-        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
-            const uint32_t e = e0 + wl;
-            const uint32_t r = div_small(e, inv), c = e - r * nvec;
-            if (e < total)
-                __builtin_amdgcn_global_load_lds((gptr)(src + (r * ld_in + 4 * c)), (lptr)(bs + (e0 << 4)), 16, 0, 0);
-        }
-    } else if (flat && fw == (uint32_t)ld_in) {      // (f0 is 0 then)
-        shift = (uint32_t)at & 3;
+    const bool windows = ALIGNED || (mode & kAnyWindows);     // (the same for the whole launch)
+    const uint32_t chunks = (uint32_t)tile_stride((int)fw, ALIGNED || (mode & kAnyTight)) >> 2;
+    const bool run = !ALIGNED && windows && fw == (uint32_t)ld_in;   // (f0 is 0 then)
+    const uint32_t stride = run ? fw : chunks << 2;  // words from row to row in LDS
+    if (run) {
+        const uint32_t shift = (uint32_t)at & 3;
         const float* __restrict__ src = in + (at - shift);
         const uint32_t words = (uint32_t)k * fw + shift, total = words >> 2, rest = words & 3;
         for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads)
@@ -1176,15 +1231,36 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
                 __builtin_amdgcn_global_load_lds((gptr)(src + 4 * (e0 + wl)), (lptr)(bs + (e0 << 4)), 16, 0, 0);
         if (wave == 0 && wl < rest)
             __builtin_amdgcn_global_load_lds((gptr)(src + 4 * total + wl), (lptr)(bs + (total << 4)), 4, 0, 0);
-    } else {
-        const float inv = 1.f / (float)fw;
-        const uint32_t total = (uint32_t)k * fw;
-        const float* __restrict__ src = in + at;
+    } else if (windows) {
+        // the last chunk of the last row may reach past the operation's block: its words are
+        // copied one by one
+        const int64_t row_last = at + (int64_t)(k - 1) * ld_in;
+        const int64_t base_last = row_last & ~(int64_t)3;
+        const uint32_t full_last = (uint32_t)(row_last + fw - base_last) >> 2;      // whole chunks of the last row
+        const uint32_t total = k > 0 ? (uint32_t)(k - 1) * chunks + (ALIGNED ? chunks : full_last) : 0;
+        const float inv = 1.f / (float)chunks;
         for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
             const uint32_t e = e0 + wl;
-            const uint32_t r = div_small(e, inv), c = e - r * fw;
+            const uint32_t r = div_small(e, inv), c = e - r * chunks;
+            const int64_t row = at + r * ld_in;
             if (e < total)
-                __builtin_amdgcn_global_load_lds((gptr)(src + (r * ld_in + c)), (lptr)(bs + (e0 << 2)), 4, 0, 0);
+                __builtin_amdgcn_global_load_lds((gptr)(in + ((ALIGNED ? row : row & ~(int64_t)3) + 4 * c)),
+                                                 (lptr)(bs + (e0 << 4)), 16, 0, 0);
+        }
+        if (!ALIGNED && k > 0) {
+            const uint32_t rest = (uint32_t)(row_last + fw - base_last) & 3;
+            if (wave == 0 && wl < rest)
+                __builtin_amdgcn_global_load_lds((gptr)(in + (base_last + 4 * full_last + wl)),
+                                                 (lptr)(bs + (total << 4)), 4, 0, 0);
+        }
+    } else {
+        const float inv = 1.f / (float)stride;
+        const uint32_t total = (uint32_t)k * stride;
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
+            const uint32_t e = e0 + wl;
+            const uint32_t r = div_small(e, inv), c = e - r * stride;
+            if (e < total && c < fw)
+                __builtin_amdgcn_global_load_lds((gptr)(in + (at + r * ld_in + c)), (lptr)(bs + (e0 << 2)), 4, 0, 0);
         }
     }
 
@@ -1192,13 +1268,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     const int32_t* __restrict__ rp = rpt + it.rpt_off;
     const int32_t* __restrict__ ci = colids + it.nz_off;
     const float* __restrict__ va = values + it.nz_off;
-    const uint32_t nvec = fw / VEC, groups = kThreads / nvec;
-    const uint32_t g = div_small(tid, 1.f / (float)nvec), l = tid - g * nvec;
-    const uint32_t um = (uint32_t)m;
-    const uint32_t r_first = (uint32_t)it.row0 + g;
-    const int q0 = rp[min(r_first, um)];
-    const int q1 = rp[min(r_first + 1, um)];
-    const uint32_t ri = min(tid, um);
+    const uint32_t ri = min(tid, (uint32_t)m);
     const int rv = rp[ri];
     int c[4] = {0, 0, 0, 0};
     float a[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1214,11 +1284,14 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
 
     // ---- LDS writes, clamped as in bspmm_lean_kernel; an entry carries the byte offset of its
     // dense row inside the tile
-    const uint32_t stride = fw << 2;
     int2* cv = reinterpret_cast<int2*>(lds + it.cv_byte);
     sm[ri] = min(max(rv, 0), nnz);
+    const uint32_t at3 = windows ? (uint32_t)at : 0, ld3 = windows && !run ? (uint32_t)ld_in : 0;
     auto entry = [&](int col, float v) {
-        return make_int2((unsigned)col < (unsigned)k ? (int)__umul24((uint32_t)col, stride) : 0, __float_as_int(v));
+        const uint32_t r = (unsigned)col < (unsigned)k ? (uint32_t)col : 0;
+        uint32_t off = __umul24(r, stride << 2);
+        if (!ALIGNED) off += ((at3 + r * ld3) & 3) << 2;
+        return make_int2((int)off, __float_as_int(v));
     };
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -1231,17 +1304,16 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     __syncthreads();
 
     // ---- rows
-    if (g >= groups) return;
-    const char* bcol = bs + ((shift + l * VEC) << 2);
-    float* __restrict__ dst = out + ((int64_t)it.out_row * ld_out + it.f0 + (int)l * VEC);
-    const uint32_t row_end = (uint32_t)(it.row0 + it.nrows);
-    auto sum = [&](int p0, int p1) {
-        return any_row<VEC>(p0, p1, [&](int p) { return cv[p]; },
-                            [&](int off) { return *reinterpret_cast<const VT*>(bcol + off); });
+    float* __restrict__ dst = out + (((int64_t)it.out_row + it.row0) * ld_out + it.f0);
+    auto row = [&](int i, int& p0, int& p1) {
+        p0 = sm[it.row0 + i];
+        p1 = sm[it.row0 + i + 1];
     };
-    if (r_first < row_end) any_store<VEC>(dst + r_first * ld_out, sum(min(max(q0, 0), nnz), min(max(q1, 0), nnz)));
-    for (uint32_t r = r_first + groups; r < row_end; r += groups)
-        any_store<VEC>(dst + r * ld_out, sum(sm[r], sm[r + 1]));
+    auto lds_entry = [&](int p) { return cv[p]; };
+    if (nnz > kLongRow * m)
+        any_rows<1, false>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<false>{bs});
+    else
+        any_rows<4, ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
 }
 
 // Once per plan and direction: the position of every row block's entries goes into its item.
@@ -2842,15 +2914,16 @@ hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int g
     return hipGetLastError();
 }
 
-// vec: floats per lane (4, 2 or 1); flat: the dense input is packed (ld_in is the feature width)
-// and starts on 16 bytes.
-hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, int vec, bool flat, int grid,
+// aligned: F % 4 == 0 and every row of every tile is float4 on 16 bytes; quads: F % 4 == 0 (the schedule
+// then left no room for rows off 16 bytes in LDS).
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, int grid,
                             int lds_bytes, hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
-    auto* fn = vec == 4 ? bspmm_any_kernel<4> : (vec == 2 ? bspmm_any_kernel<2> : bspmm_any_kernel<1>);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), lds_bytes, stream, items, P.rpt, P.colids, P.values, P.in,
-                       P.out, P.ld_in, P.ld_out, (uint32_t)(lds_bytes / 4), flat ? 1 : 0);
+    const bool windows = (reinterpret_cast<uintptr_t>(P.in) & 15) == 0 && (!quads || P.ld_in % 4 == 0);
+    hipLaunchKernelGGL(aligned ? bspmm_any_kernel<true> : bspmm_any_kernel<false>, dim3(grid), dim3(kThreads),
+                       lds_bytes, stream, items, P.rpt, P.colids, P.values, P.in, P.out, P.ld_in, P.ld_out,
+                       (uint32_t)(lds_bytes / 4), (windows ? kAnyWindows : 0) | (quads ? kAnyTight : 0));
     return hipGetLastError();
 }
 

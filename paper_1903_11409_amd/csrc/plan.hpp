@@ -318,6 +318,17 @@ BSPMM_HD inline int compact_words(int chans, int kxt)
 }
 constexpr int kCompactRows = 1024;   // tile rows (channels x rows of X) of a set that is compacted, at most
 
+// bspmm_any_kernel: words from one row of the LDS tile to the next.  A row off 16 bytes is copied as
+// the 16-byte words it lies in and starts up to three words into the first.
+BSPMM_HD inline int tile_stride(int fw, bool aligned) { return round_up(aligned ? fw : fw + 3, 4); }
+constexpr int kLongRow = 16;   // entries per row from which a row takes a lane per float
+
+// LDS words of an item of bspmm_any_kernel (a lane may read up to three words past the tile).
+BSPMM_HD inline int64_t any_words(int m, int k, int nnz, int fw, bool aligned)
+{
+    return round_up(round_up(m + 1, 2) + 2 * nnz, 4) + (int64_t)k * tile_stride(fw, aligned) + 4;
+}
+
 // Lanes that share one output row: enough 4-float vectors to cover the tile, a power of two.
 BSPMM_HD inline int lanes_per_row(int fw, int vec)
 {

@@ -60,11 +60,10 @@ int bin_range(int bin)
 
 int draft_range(const Draft& x) { return x.fused >= 0 ? 1 : bin_range(x.bin); }
 
-// Output rows a whole workgroup has in flight (the kernels give a row exactly the lanes it
-// fills, two floats each where F is even but not a multiple of four).
-int rows_in_flight(int fw, int vec, int F)
+// Output rows of operation i that a whole workgroup has in flight (see bspmm_any_kernel).
+int rows_in_flight(const DirOps& o, int i, int fw, int vec)
 {
-    const int per_lane = vec == 4 ? 4 : (F % 2 == 0 ? 2 : 1);
+    const int per_lane = vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 4;
     return std::max(1, kThreads / std::max(1, (fw + per_lane - 1) / per_lane));
 }
 
@@ -72,6 +71,18 @@ int rows_in_flight(int fw, int vec, int F)
 std::vector<int> tile_candidates(int F, const Knobs& kn)
 {
     std::vector<int> c;
+    if (F % 4 != 0 && kn.front == 0) {
+        // Widths that no 16-byte load divides gain nothing from powers of two: the columns are
+        // split evenly (on even columns where F is even, for two-float lanes).
+        const int even = F % 2 == 0 ? 2 : 1;
+        for (int parts = (F + kn.max_tile - 1) / kn.max_tile; ; parts += (parts + 2) / 3) {
+            const int w = round_up((F + parts - 1) / parts, even);
+            if (!c.empty() && w < kn.min_odd_tile) break;
+            if (w <= kn.max_tile && (c.empty() || w < c.back())) c.push_back(w);
+            if (w <= even) break;
+        }
+        return c;
+    }
     int t = std::min(F, kn.max_tile);
     c.push_back(t);
     int p = 1;
@@ -96,7 +107,7 @@ bool fits_slot(const DirOps& o, int i, int tile, int F, int vec, int lanes, int 
     if (max_passes > 0 && (lanes_wanted + lanes - 1) / lanes > max_passes) return false;
     const int64_t head = (int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i];
     int64_t need = (head + 3) / 4 * 4 + (int64_t)o.k[i] * (round_up(fw, 4) + kn.pad);
-    if (vec == 1) need += 4;   // (a tile copied in 16-byte pieces starts up to 3 words into its place)
+    if (vec == 1) need = std::max(need, any_words(o.m[i], o.k[i], o.nnz[i], fw, false));
     if (kn.hubs && lanes == kThreads) need += hub_words(o.nnz[i] / kHubMin, fw);   // as staged_layout()
     if (kn.front > 0)   // a weight tile and a bias tile per channel and at least 16 rows of X_i ride along
         need += 16 * (int64_t)kn.front +
@@ -190,7 +201,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     if (!sink.out) {    // counting: the same items in closed form
         auto per_tile = [&](int fw) {
             if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-                const int chunk = cap * rows_in_flight(fw, vec, F);
+                const int chunk = cap * rows_in_flight(o, i, fw, vec);
                 return (o.m[i] + chunk - 1) / chunk;
             }
             if (ch.bin != BSPMM_BIN_GENERIC) return 1;
@@ -208,7 +219,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     for (int f0 = 0; f0 < F; f0 += tile) {
         const int fw = std::min(tile, F - f0);
         if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-            const int chunk = cap * rows_in_flight(fw, vec, F);
+            const int chunk = cap * rows_in_flight(o, i, fw, vec);
             for (int r0 = 0; r0 < o.m[i]; r0 += chunk)
                 sink.add(o, i, ch.bin, r0, std::min(chunk, o.m[i] - r0), f0, fw, 1, -1);
         } else if (ch.bin != BSPMM_BIN_GENERIC) {
@@ -441,7 +452,7 @@ Knobs resolve_knobs(const bspmm_options* o)
     if (o->lds_bytes > 0) k.lds_words = std::min(o->lds_bytes, kMaxLdsBytes) / 256 * 64;
     if (k.lds_words < 256) k.lds_words = 256;
     if (o->max_tile > 0) k.max_tile = std::min(std::max(o->max_tile, 4), 256) / 4 * 4;
-    if (o->min_tile > 0) k.min_tile = std::min(std::max(o->min_tile, 4), k.max_tile);
+    if (o->min_tile > 0) k.min_tile = k.min_odd_tile = std::min(std::max(o->min_tile, 4), k.max_tile);
     if (o->compute_units > 0) k.compute_units = o->compute_units;
     k.target_given = o->target_workgroups > 0;
     k.target_wgs = o->target_workgroups > 0 ? o->target_workgroups
@@ -578,15 +589,17 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
         return counter.workgroups();
     };
     int wgs = 0;
+    // (F % 4 != 0: the widest tile every operation can hold, and row ranges for parallelism - see below)
+    const bool wide_first = vec == 1 && kn.front == 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         for (size_t c = 0; c < cand.size(); ++c) {
             wgs = workgroups_of(c, fixed_cap, allow_small);
-            if (wgs >= kn.target_wgs || c + 1 == cand.size()) {
+            if (wide_first || wgs >= kn.target_wgs || c + 1 == cand.size()) {
                 chosen = c;
                 break;
             }
         }
-        if (allow_small || wgs <= kn.capacity_wgs || kn.front > 0) break;
+        if (allow_small || wgs <= kn.capacity_wgs || kn.front > 0 || wide_first) break;
         allow_small = true;
     }
     s.tile = cand[chosen];
@@ -599,7 +612,19 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     // graphs 5.9 -> 4.8 us; cut beyond what the chip holds, 384 graphs go from 4.9 to 5.9 us;
     // wide tiles of 100-row graphs cut to four rows each, 8.2 -> 9.2 us).
     int cap = fixed_cap;
-    if (kn.wg_passes == 0 && kn.front == 0) {
+    if (kn.wg_passes == 0 && wide_first) {
+        // Widths off 16 bytes: a tile of whole rows is one run of memory, cheaper to copy several
+        // times (out of L2) than column tiles whose rows start anywhere.  Ranges of at most eight
+        // passes over the lane groups (200 operations of 1 to 220 rows, F = 127: uncut 16.5 us, sixteen
+        // passes 12.3, eight 9.3), shorter until there are two workgroups per CU, but not in launches
+        // bound by bandwidth.
+        const int want = kn.target_given ? kn.target_wgs : 2 * kn.compute_units;
+        for (int c = 8; c >= 1; c /= 2) {
+            wgs = workgroups_of(chosen, c, allow_small);
+            cap = c;
+            if (wgs >= want || counted_tile_words > 3500000) break;
+        }
+    } else if (kn.wg_passes == 0 && kn.front == 0) {
         const int uncut = wgs;                         // (the tile search ended on this very count)
         const int64_t uncut_words = counted_tile_words;
         bool done = false;
@@ -641,7 +666,11 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     keep.block_of_op = &block_of_op;
     keep.tile_unit = std::max(4, std::min(cand.back(), F));
     keep.tiles_per_block = (F + keep.tile_unit - 1) / keep.tile_unit;
-    if (kn.front > 0) {   // every feature tile of an operation reads the whole of X_i: one group
+    // (fused front: every feature tile of an operation reads the whole of X_i.  Rows that are no whole
+    // number of 128-byte lines: column tiles share the lines at their edges - 900 operations of 1 to 220
+    // rows at F = 127 fetched 122 MB and wrote 60 MB instead of 50 each, and took 34 us instead of 22,
+    // with the tiles of an operation on different XCDs.)
+    if (kn.front > 0 || F % 32 != 0) {
         keep.tile_unit = std::max(4, F);
         keep.tiles_per_block = 1;
     }
@@ -876,6 +905,14 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
         if (w.nrows <= 0) continue;
         const int nvec = w.fw >> 2;
         s.lean = (w.fw & 3) == 0 && nvec > 0 && (nvec & (nvec - 1)) == 0 && nvec <= 64;
+    }
+    if (s.whole) {   // what the launch asks for: its largest item's LDS (row blocks: the whole budget)
+        int64_t most = 0;
+        for (const WorkItem& w : s.items) {
+            if (w.nrows <= 0) continue;
+            most = std::max<int64_t>(most, (w.staged & 1) ? any_words(w.m, w.k, w.nnz, w.fw, vec == 4) : kn.lds_words);
+        }
+        s.lds_words = (int)std::min<int64_t>(kn.lds_words, round_up((int)most, 64));
     }
     if (kn.front > 0) {
         int64_t most = 0;

@@ -25,6 +25,7 @@ struct Knobs {
     int force_bin = -1;       // -1 automatic, else BSPMM_BIN_*
     int lds_words = 6144;     // 24 KiB: six workgroups per CU
     int min_tile = 32;
+    int min_odd_tile = 8;     // the same for widths that are no multiple of four
     int max_tile = 256;
     int target_wgs = 1024;
     bool target_given = false;   // the caller fixed target_wgs
@@ -70,6 +71,7 @@ struct Schedule {
                                      // lean kernel
     bool has_slices = false;         // any 32- or 16-lane item: needs the larger kernel variant
     int tile = 0;
+    int lds_words = 0;               // `whole` launches: LDS the launch asks for (its largest item)
     int front_lds_words = 0;         // LDS the fused-front launch asks for (its largest item)
     int items_in_bin[BSPMM_NUM_BINS] = {0, 0, 0, 0, 0};
 };

@@ -1,0 +1,64 @@
+"""Products at widths, leading dimensions and offsets off 16 bytes (bspmm_any_kernel): tile rows copied as
+the 16-byte words they lie in, a last lane that holds part of a row, a lane per float for long rows,
+row blocks; compared with the oracle, with guards around everything that may be written."""
+import numpy as np
+import pytest
+
+from paper_1903_11409_amd import bspmm as K
+from paper_1903_11409_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SENTINEL = -12345.0
+# (rows, cols, entries): one row, one column, more rows than lanes, rows of hundreds of entries, more than
+# four entries per lane, nothing, too large for LDS at any width
+SHAPES = [(1, 1, 1), (1, 220, 300), (220, 1, 400), (31, 33, 90), (300, 20, 900), (5, 200, 1300), (0, 0, 0), (7, 9, 0),
+          (64, 64, 200), (3, 5000, 700), (900, 2500, 2600)]
+
+
+def _run(torch, plan, b, transposed, in_off, out_off, in_extra, out_extra):
+    src, rows = (b.dY, b.n_b_rows) if transposed else (b.B, b.n_c_rows)
+    ld_in, ld_out = b.F + in_extra, b.F + out_extra
+    store_in = torch.full((src.shape[0] * ld_in + in_off + 4,), float("nan"), device="cuda")
+    X = store_in[in_off:in_off + src.shape[0] * ld_in].view(-1, ld_in)
+    X[:, :b.F] = torch.from_numpy(src).cuda()
+    store = torch.full((rows * ld_out + out_off + 8,), SENTINEL, device="cuda")
+    Y = store[out_off:out_off + rows * ld_out].view(rows, ld_out)
+    (K.bspmm_run_transposed if transposed else K.bspmm_run)(plan.handle, X, Y, ld_in, ld_out)
+    torch.cuda.synchronize()
+    assert bool((store[:out_off] == SENTINEL).all()) and bool((store[out_off + rows * ld_out:] == SENTINEL).all())
+    assert bool((Y[:, b.F:] == SENTINEL).all())
+    return Y[:, :b.F].cpu().numpy()
+
+
+def _check(got, ref, scale, off, length):
+    owned = np.zeros(got.shape[0], dtype=bool)
+    for o, n in zip(off, length):
+        owned[int(o):int(o) + int(n)] = True
+    assert np.all(got[~owned] == SENTINEL)
+    err = np.abs(got.astype(np.float64) - ref)[owned]
+    assert not np.any(~(err <= 1e-5 * scale[owned])), "beyond 1e-5*S"
+
+
+@pytest.mark.parametrize("F", [1, 2, 3, 5, 50, 63, 65, 100, 127, 255, 257, 301])
+def test_every_width_both_directions(oracle, F):
+    import torch
+    b = W.random_general(900 + F, F=F, shapes=SHAPES, shuffle_blocks=True)
+    plan = K.Plan(b)
+    for transposed in (False, True):
+        got = _run(torch, plan, b, transposed, 0, 0, 0, 0)
+        ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
+        _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
+
+
+@pytest.mark.parametrize("F", [48, 50, 61])
+@pytest.mark.parametrize("in_off,out_off,in_extra,out_extra", [(1, 0, 0, 0), (2, 3, 0, 0), (0, 1, 0, 0), (0, 0, 1, 3),
+                                                               (4, 0, 2, 0), (3, 1, 5, 2)])
+def test_operands_off_16_bytes(oracle, F, in_off, out_off, in_extra, out_extra):
+    import torch
+    b = W.random_general(40 + F, F=F, shapes=SHAPES)
+    plan = K.Plan(b)
+    for transposed in (False, True):
+        got = _run(torch, plan, b, transposed, in_off, out_off, in_extra, out_extra)
+        ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
+        _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
