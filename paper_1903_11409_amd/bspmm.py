@@ -1,6 +1,6 @@
 """Thin binding of libbspmm.so: argument marshalling only, same names as the C ABI.
 
-The run calls go through ``_native.so`` (``csrc/binding.cpp``), everything else through ctypes.
+Plans and run calls go through ``_native.so`` (``csrc/binding.cpp``), everything else through ctypes.
 Every step of the path (scheduling, staging, the products, the transposed build) runs inside
 the library; PyTorch is used for device memory and streams only.  There is no fallback: if the
 shared library is missing or a call fails, an exception is raised.
@@ -154,32 +154,19 @@ def lib():
 
 
 def native():
-    """The extension module of the run calls (``csrc/binding.cpp``); raises if it is not built."""
+    """The extension module of plans and run calls (``csrc/binding.cpp``); raises if it is not built."""
     global _native
     if _native is None:
         lib()
+        import torch  # noqa: F401  (its libraries are what the module links against)
         try:
             from . import _native as module
         except ImportError as e:
             raise RuntimeError("_native.so is missing or does not load: build it with `python -m "
                                "paper_1903_11409_amd.build` (there is no fallback path)") from e
-        module.setup(_check, _ld, _raw_stream, _current_device)
+        module.setup(_check, _ld)
         _native = module
     return _native
-
-
-def _current_device() -> int:
-    """First use of the current stream: PyTorch's device state may have to be initialised; from
-    then on its own functions are asked directly."""
-    import torch
-    device = torch.cuda.current_device()
-    _native.setup(_check, _ld, torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-    return device
-
-
-def _raw_stream(device: int) -> int:
-    import torch
-    return torch._C._cuda_getCurrentRawStream(device)
 
 
 def _check(code: int, where: str) -> None:
@@ -391,14 +378,6 @@ def bspmm_destroy(plan: Optional[int]) -> None:
         lib().bspmm_destroy(plan)
 
 
-def _rows_from_zero(off, length) -> int:
-    """Rows that the blocks [off, off + length) cover from row 0 on without a gap."""
-    order = np.argsort(off, kind="stable")
-    end = np.maximum.accumulate(np.concatenate([[0], (off + length)[order]]))
-    gaps = np.flatnonzero(off[order] > end[:-1])
-    return int(end[gaps[0]] if len(gaps) else end[-1])
-
-
 class Plan:
     """Owns a plan handle plus the torch tensors it borrows (CSR arrays and workspace).
 
@@ -411,54 +390,88 @@ class Plan:
     def __init__(self, batch, F: Optional[int] = None, options: Optional[bspmm_options] = None,
                  device="cuda:0", stream=None, coo=None):
         import torch
-        native()
+        n = _native or native()
         self.torch = torch
         self.n_x = max(1, int(options.front_features)) if options is not None else 1
         self.F = int(F if F is not None else batch.F)
-        self._covered = [None, None]
-        self.device = torch.device(device)
-        dev = self.device
+        self._hb = self._views = None
+        self.device = device = torch.device(device)
+        index = device.index if device.index is not None else torch.cuda.current_device()
         self.options = options
-        self.rpt_len = int((np.asarray(batch.rows, dtype=np.int64) + 1).sum())
-        self.rpt_t_len = int((np.asarray(batch.cols, dtype=np.int64) + 1).sum())
-        self.nnz_total = int(np.asarray(batch.nnz, dtype=np.int64).sum())
-        def on_device(a, dtype):
-            # numpy arrays are copied over; tensors that already sit on the device with the
-            # right type and layout are borrowed as they are
-            if isinstance(a, torch.Tensor):
-                return a.to(device=dev, dtype=dtype).contiguous()
-            np_type = np.int32 if dtype == torch.int32 else np.float32
-            return torch.from_numpy(np.ascontiguousarray(a, dtype=np_type)).to(dev)
-
+        opt = None if options is None else ctypes.addressof(options)
+        self._meta = meta = (batch.rows, batch.cols, batch.nnz, getattr(batch, "rpt_off", None), batch.nz_off,
+                             batch.b_row_off, batch.c_row_off)
         if coo is not None:
             # COO / SparseTensor operands: ``coo`` = (ids, values), numpy arrays or tensors, laid
             # out by the batch's nz_off; the batch's own CSR arrays are not used
-            ids, vals = coo
-            self.ids = on_device(ids, torch.int32)
-            self.values = on_device(vals, torch.float32)
-            self.hb = HostCooBatch(batch.rows, batch.cols, batch.nnz, batch.nz_off,
-                                   batch.b_row_off, batch.c_row_off,
-                                   self.ids if self.ids.numel() else None,
-                                   self.values if self.values.numel() else None)
-            nbytes = bspmm_workspace_bytes_coo(self.hb, self.F, options)
-            self.workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
-            assert self.workspace.data_ptr() % 256 == 0
-            self.handle = bspmm_create_coo(self.hb, self.F, options, self.workspace, nbytes, stream)
-            return
-        self.rpt = on_device(batch.rpt, torch.int32)
-        self.colids = on_device(batch.colids, torch.int32)
-        self.values = on_device(batch.values, torch.float32)
-        # zero-length tensors have a null data_ptr; give the library something addressable
-        if self.rpt.numel() == 0:
-            self.rpt = torch.zeros(1, dtype=torch.int32, device=dev)
-        self.hb = HostBatch(batch.rows, batch.cols, batch.nnz, batch.rpt_off, batch.nz_off,
-                            batch.b_row_off, batch.c_row_off, self.rpt,
-                            self.colids if self.colids.numel() else None,
-                            self.values if self.values.numel() else None)
-        nbytes = bspmm_workspace_bytes(self.hb, self.F, options)
-        self.workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
-        assert self.workspace.data_ptr() % 256 == 0
-        self.handle = bspmm_create(self.hb, self.F, options, self.workspace, nbytes, stream)
+            ids, values = coo
+            self._csr = None
+            made = n.create_coo(*meta[:3], *meta[4:], ids, values, self.F, opt, index, stream)
+            if made is None:
+                self._meta = meta = self._as_arrays(meta[:3], np.int32) + (None,) + self._as_arrays(meta[4:], np.int64)
+                ids, values = self._on_device(ids, torch.int32), self._on_device(values, torch.float32)
+                made = n.create_coo(*meta[:3], *meta[4:], ids, values, self.F, opt, index, stream)
+            self.ids, self.values = ids, values
+        else:
+            csr = (batch.rpt, batch.colids, batch.values)
+            made = n.create(*meta, *csr, self.F, opt, index, stream)
+            if made is None:      # another type or layout, on another device, or too large to be staged
+                self._meta = meta = self._as_arrays(meta[:3], np.int32) + self._as_arrays(meta[3:], np.int64)
+                rpt, colids, values = (self._on_device(a, t) for a, t in zip(csr, (torch.int32, torch.int32,
+                                                                                    torch.float32)))
+                # zero-length tensors have a null data_ptr; give the library something addressable
+                if rpt.numel() == 0:
+                    rpt = torch.zeros(1, dtype=torch.int32, device=device)
+                csr = (rpt, colids, values)
+                made = n.create(*meta, *csr, self.F, opt, index, stream)
+            self._csr = csr       # as given, or as lengths of the arrays in front of the workspace
+            if made is not None and made[2] > 0:
+                self._csr = tuple(int(a.shape[0]) for a in csr)
+        if made is None:
+            raise TypeError("the batch's arrays cannot be used: one-dimensional arrays of one length are needed")
+        self.handle, self._memory, self._head = made
+
+    @staticmethod
+    def _as_arrays(arrays, dtype):
+        return tuple(np.ascontiguousarray(a, dtype=dtype).reshape(-1) for a in arrays)
+
+    def _on_device(self, a, dtype):
+        # numpy arrays are copied over; tensors that already sit on the device with the
+        # right type and layout are borrowed as they are
+        torch = self.torch
+        if isinstance(a, torch.Tensor):
+            return a.to(device=self.device, dtype=dtype).contiguous()
+        np_type = np.int32 if dtype == torch.int32 else np.float32
+        return torch.from_numpy(np.ascontiguousarray(a, dtype=np_type)).to(self.device)
+
+    def __getattr__(self, name):
+        # what only inspection asks for is made when it is asked for
+        if name == "hb":
+            if self._hb is None:
+                m = self._meta
+                if self._csr is None:
+                    self._hb = HostCooBatch(*m[:3], *m[4:], self.ids if self.ids.numel() else None,
+                                            self.values if self.values.numel() else None)
+                else:
+                    self._hb = HostBatch(*m, self.rpt, self.colids if self.colids.numel() else None,
+                                         self.values if self.values.numel() else None)
+            return self._hb
+        if name == "workspace":
+            return self._memory[self._head:]
+        if name in ("rpt", "colids", "values") and self.__dict__.get("_csr") is not None:
+            if self._views is None:
+                self._views = self._csr
+                if self._head > 0:
+                    at, views = 0, []
+                    for n, t in zip(self._csr, (self.torch.int32, self.torch.int32, self.torch.float32)):
+                        views.append(self._memory[at:at + 4 * n].view(t))
+                        at += (4 * n + 255) // 256 * 256
+                    self._views = tuple(views)
+            return self._views[("rpt", "colids", "values").index(name)]
+        if name in ("rpt_len", "rpt_t_len", "nnz_total"):
+            a = self._meta[("rpt_len", "rpt_t_len", "nnz_total").index(name)]
+            return int(np.asarray(a, dtype=np.int64).sum()) + (len(a) if name != "nnz_total" else 0)
+        raise AttributeError(name)
 
     def run(self, B, C, stream=None):
         return _native.plan_run(self.handle, B, C, self.F, stream)
@@ -472,12 +485,7 @@ class Plan:
 
     def covered_rows(self, transposed: bool = False) -> int:
         """Rows from the first on that every product writes: C's, or G's when ``transposed``."""
-        key = 1 if transposed else 0
-        if self._covered[key] is None:
-            # HostBatch keeps (rows, cols, .., b_row_off, c_row_off), HostCooBatch one array less
-            a = self.hb.arrays
-            self._covered[key] = _rows_from_zero(a[-2], a[1]) if transposed else _rows_from_zero(a[-1], a[0])
-        return self._covered[key]
+        return _native.covered_rows(self.handle, transposed)
 
     def export_transposed(self, stream=None):
         t = self.torch

@@ -11,9 +11,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbspmm.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["kernels.hip", "schedule.cpp", "api.cpp"]
+SOURCES = ["kernels.hip", "schedule.cpp", "api.cpp", "staging.cpp"]
 NATIVE_SOURCES = ["binding.cpp"]
-HEADERS = ["plan.hpp", "schedule.hpp", os.path.join("..", "..", "include", "bspmm.h")]
+HEADERS = ["plan.hpp", "schedule.hpp", "plan_api.hpp", "staging.hpp", os.path.join("..", "..", "include", "bspmm.h")]
 
 
 def lib_path() -> str:
@@ -41,11 +41,22 @@ def build(verbose: bool = False) -> str:
            "-x", "hip", os.path.join(CSRC, "kernels.hip"),
            "-x", "hip", os.path.join(CSRC, "schedule.cpp"),
            "-x", "hip", os.path.join(CSRC, "api.cpp"),
+           "-x", "hip", os.path.join(CSRC, "staging.cpp"),
            "-o", LIB]
-    # the extension module finds libbspmm.so in its own folder
+    # the extension module finds libbspmm.so in its own folder; PyTorch's libraries are loaded before it
+    import numpy
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     native = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-              "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-L" + HERE,
-              "-l:libbspmm.so", "-Wl,-rpath,$ORIGIN", "-o", NATIVE]
+              "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+              "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+              "-I" + sysconfig.get_paths()["include"], "-isystem", numpy.get_include(),
+              "-isystem", os.path.join(root, "include"),
+              "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+              "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "binding.cpp"),
+              "-L" + HERE, "-l:libbspmm.so", "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu",
+              "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-o", NATIVE]
     for c in (cmd, native):
         if verbose:
             print(" ".join(c), file=sys.stderr)

@@ -14,7 +14,9 @@
 
 #include "../../include/bspmm.h"
 #include "plan.hpp"
+#include "plan_api.hpp"
 #include "schedule.hpp"
+#include "staging.hpp"
 
 namespace bspmm {
 hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec4, bool slices,
@@ -75,7 +77,8 @@ int hip_fail(hipError_t e)
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Where each table sits inside the workspace (byte offsets).
+// Where each table sits inside the workspace (byte offsets).  The tables the host writes come first
+// (one image, one copy), what the device builds behind them.
 struct Layout {
     size_t items[2] = {0, 0};
     size_t lean[2] = {0, 0};     // item tables of the lean kernel (empty when a direction is not lean)
@@ -94,12 +97,14 @@ struct Layout {
     size_t coo_records = 0;
     size_t csr_rpt = 0, csr_colids = 0, csr_values = 0;
     size_t coo_scratch = 0;
+    size_t image = 0;            // bytes of the host-written front
     size_t total = 0;
 };
 
 }  // namespace
 
 struct bspmm_plan {
+    bool counted = false;           // (staging.hpp: one of the plans that exist)
     int static_device = -1;         // >= 0: the workspace is that device's static array ...
     uint64_t static_generation = 0; // ... as handed out by this call of bspmm_create_static
     int32_t batch = 0;
@@ -112,12 +117,13 @@ struct bspmm_plan {
     std::vector<OpRecord> records;
     std::vector<int32_t> build_order;      // operations, most entries first: the order the build
                                            // kernels take them in
-    std::vector<LeanItem> lean_items[2];   // per direction: the items again, for the lean kernel
+    std::vector<LeanItem> lean_items[2];   // per direction: the compact item table of a `whole` schedule
+    bool lean_shared = false;              // both directions run from the forward table
     int32_t lean_rows[2] = {0, 0};         // most input rows / output rows of an operation: bounds
     int32_t lean_out_rows[2] = {0, 0};     // of the 32-bit offsets the lean kernel forms per call
     bool lean_blocks[2] = {false, false};  // the lean table has row blocks of the generic bin ...
     bool lean_hints_built[2] = {false, false};   // ... and the device has filled in their entry ranges
-    std::vector<char> tables;   // host image of the workspace's front: item tables and records
+    std::vector<char> tables;   // host image of the workspace's front, for copies from pageable memory
     Layout lay;
     int build_lds_bytes = 0;
     int build_threads = kThreads;          // lanes per workgroup of the build kernels
@@ -150,6 +156,7 @@ struct bspmm_plan {
     } stream;
     int64_t effective_bytes[2] = {0, 0};
     int64_t flops = 0;
+    int64_t covered[2] = {-1, -1};   // covered_rows(), once asked
     bool reads_dense = false;   // some operation has rows and columns: the runs read the dense input
     // borrowed device pointers
     const int32_t* rpt = nullptr;
@@ -664,17 +671,22 @@ void make_stream_plan(bspmm_plan& p)
 }
 
 // The compact item table of direction d, when the schedule is made of whole-workgroup items and every
-// offset fits the table's 32-bit fields (else the direction keeps the general kernel).
+// offset fits the table's 32-bit fields (else the direction keeps the general kernel).  Plain
+// batches come with it.
 void make_lean_items(bspmm_plan& p, int d)
 {
-    const Schedule& sc = p.sched[d];
+    Schedule& sc = p.sched[d];
     std::vector<LeanItem>& out = p.lean_items[d];
     out.clear();
     p.lean_blocks[d] = false;
     if (!sc.whole) return;
+    if (!sc.compact.empty()) {
+        out = std::move(sc.compact);
+        p.lean_blocks[d] = sc.row_blocks;
+        return;
+    }
     out.reserve(sc.items.size());
     constexpr int64_t kLimit = (int64_t)1 << 31;
-    int32_t most_k = 0, most_m = 0;
     for (const WorkItem& w : sc.items) {
         LeanItem t;
         std::memset(&t, 0, sizeof t);
@@ -682,6 +694,7 @@ void make_lean_items(bspmm_plan& p, int d)
             if (w.rpt_off >= kLimit || w.nz_off >= kLimit || w.in_row_off >= kLimit ||
                 w.out_row_off >= kLimit) {
                 out.clear();
+                sc.whole = sc.lean = false;
                 return;
             }
             int sh = 0;
@@ -703,13 +716,10 @@ void make_lean_items(bspmm_plan& p, int d)
                 t.flags |= 2;    // a row block: its entry range is filled in on the device
                 p.lean_blocks[d] = true;
             }
-            most_k = std::max(most_k, w.k);
-            most_m = std::max(most_m, w.m);
         }
         out.push_back(t);
     }
-    p.lean_rows[d] = most_k;
-    p.lean_out_rows[d] = most_m;
+    sc.items.clear();            // (nothing runs from the long form any more)
 }
 
 // How the build kernel sorts an operation of `keys` key values, `nnz` entries and payloads below
@@ -756,30 +766,22 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
     int64_t nz_pack = 0;
     int64_t scratch_words = 0;
     int build_lds_words = 0;
-    for (DirOps* o : {&f, &t}) {
-        o->m.reserve(n), o->k.reserve(n), o->nnz.reserve(n), o->rpt_off.reserve(n);
-        o->nz_off.reserve(n), o->in_off.reserve(n), o->out_off.reserve(n);
-    }
+    f.m.assign(b->rows, b->rows + n), f.k.assign(b->cols, b->cols + n), f.nnz.assign(b->nnz, b->nnz + n);
+    f.rpt_off.assign(b->rpt_off, b->rpt_off + n), f.nz_off.assign(b->nz_off, b->nz_off + n);
+    f.in_off.assign(b->b_row_off, b->b_row_off + n), f.out_off.assign(b->c_row_off, b->c_row_off + n);
+    // transposed: rows and columns swap, dense input is indexed like C, output like B; the
+    // transposed entries are packed back to back in operation order (a symmetric operand is its
+    // own transpose: the same arrays serve both directions)
+    t.m = f.k, t.k = f.m, t.nnz = f.nnz, t.in_off = f.out_off, t.out_off = f.in_off;
+    t.rpt_off = f.rpt_off, t.nz_off = f.nz_off;
+    bool same_place = true;      // the transposed arrays have the forward ones' offsets
     for (int i = 0; i < n; ++i) {
         if (kn.symmetric && b->rows[i] != b->cols[i]) return BSPMM_EINVAL;
-        f.m.push_back(b->rows[i]);
-        f.k.push_back(b->cols[i]);
-        f.nnz.push_back(b->nnz[i]);
-        f.rpt_off.push_back(b->rpt_off[i]);
-        f.nz_off.push_back(b->nz_off[i]);
-        f.in_off.push_back(b->b_row_off[i]);
-        f.out_off.push_back(b->c_row_off[i]);
-        // transposed: rows and columns swap, dense input is indexed like C, output like B;
-        // the transposed entries are packed back to back in operation order
-        t.m.push_back(b->cols[i]);
-        t.k.push_back(b->rows[i]);
-        t.nnz.push_back(b->nnz[i]);
-        // (a symmetric operand is its own transpose: the same arrays serve both directions)
-        t.rpt_off.push_back(kn.symmetric ? b->rpt_off[i] : rpt_t_words);
-        t.nz_off.push_back(kn.symmetric ? b->nz_off[i] : nz_pack);
-        t.in_off.push_back(b->c_row_off[i]);
-        t.out_off.push_back(b->b_row_off[i]);
-
+        if (!kn.symmetric) {
+            same_place = same_place && b->rpt_off[i] == rpt_t_words && b->nz_off[i] == nz_pack;
+            t.rpt_off[i] = rpt_t_words;
+            t.nz_off[i] = nz_pack;
+        }
         OpRecord& r = p.records[i];
         r.rpt_off = b->rpt_off[i];
         r.nz_off = b->nz_off[i];
@@ -804,7 +806,8 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
 
     if (kn.front > 0 && (F % 16 != 0 || kn.front % 4 != 0 || kn.hubs || kn.pad != 0))
         return BSPMM_EINVAL;
-    p.sched[0] = make_schedule(f, F, kn);
+    p.knobs.wide_offsets = std::max(rpt_t_words, nz_pack) >= (int64_t)1 << 31;
+    p.sched[0] = make_schedule(f, F, p.knobs);
     if (p.sched[0].error) return p.sched[0].error;
     if (kn.front > 0 && kn.accumulate) {
         // the whole layer in one launch: every operation must be a channel of a set, all sets
@@ -825,6 +828,8 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
     bool same_shape = kn.front == 0;
     for (int i = 0; i < n && same_shape; ++i)
         same_shape = b->rows[i] == b->cols[i] && b->b_row_off[i] == b->c_row_off[i];
+    make_lean_items(p, 0);
+    p.lean_shared = false;
     if (p.transposed_supported && same_shape) {
         p.sched[1] = p.sched[0];
         Schedule& st = p.sched[1];
@@ -834,8 +839,23 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
             st.items[j].rpt_off = t.rpt_off[op];
             st.items[j].nz_off = t.nz_off[op];
         }
+        if (st.whole) {
+            // (the same items again: only the CSR arrays are elsewhere - or not even those, when the
+            // caller's are packed in operation order; row blocks carry entry ranges of their own)
+            p.lean_shared = same_place && !p.lean_blocks[0];
+            p.lean_blocks[1] = p.lean_blocks[0];
+            if (!p.lean_shared) {
+                p.lean_items[1] = p.lean_items[0];
+                for (size_t j = 0; j < p.lean_items[1].size(); ++j) {
+                    const int op = st.item_op[j];
+                    if (op < 0) continue;
+                    p.lean_items[1][j].rpt_off = (uint32_t)t.rpt_off[op];
+                    p.lean_items[1][j].nz_off = (uint32_t)t.nz_off[op];
+                }
+            }
+        }
     } else if (p.transposed_supported) {
-        Knobs kt = kn;
+        Knobs kt = p.knobs;
         kt.front = 0;                     // the layer input is a forward-only guest
         p.sched[1] = make_schedule(t, F, kt);
         if (p.sched[1].error) {          // the forward product still works
@@ -843,6 +863,7 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
             p.sched[1] = Schedule();
             p.transposed_supported = false;
         }
+        make_lean_items(p, 1);
     }
 
     // compulsory traffic: CSR once, every distinct dense input block once, every output once
@@ -872,78 +893,44 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
         csr_f += 4 * ((int64_t)b->rows[i] + 1) + 8 * (int64_t)b->nnz[i];
         csr_t += 4 * ((int64_t)b->cols[i] + 1) + 8 * (int64_t)b->nnz[i];
         nnz += b->nnz[i];
+        p.lean_rows[0] = p.lean_out_rows[1] = std::max(p.lean_rows[0], b->cols[i]);
+        p.lean_out_rows[0] = p.lean_rows[1] = std::max(p.lean_rows[1], b->rows[i]);
         if (b->rows[i] > 0 && b->cols[i] > 0) p.reads_dense = true;
     }
     p.effective_bytes[0] = csr_f + in_f + out_f;
     p.effective_bytes[1] = csr_t + in_t + out_t;
     p.flops = 2 * nnz * F;
 
+    for (int d = 0; d < 2; ++d) describe_sets(p, d);
+    make_stream_plan(p);
+    largest_first(b->nnz, n, p.build_order);
+
     // workspace layout
     Layout& L = p.lay;
     size_t at = 0;
-    for (int d = 0; d < 2; ++d) {
-        L.items[d] = at;
-        at = align_up(at + p.sched[d].items.size() * sizeof(WorkItem));
-    }
-    for (int d = 0; d < 2; ++d) {
-        if (d == 1 && p.transposed_supported && same_shape && p.sched[1].items.size() == p.lean_items[0].size() &&
-            !p.lean_items[0].empty()) {
-            // (the same items again: only the CSR arrays are elsewhere)
-            p.lean_items[1] = p.lean_items[0];
-            p.lean_blocks[1] = p.lean_blocks[0];
-            p.lean_rows[1] = p.lean_rows[0];
-            p.lean_out_rows[1] = p.lean_out_rows[0];
-            bool fits = true;
-            for (size_t j = 0; j < p.lean_items[1].size() && fits; ++j) {
-                const WorkItem& w = p.sched[1].items[j];
-                if (w.nrows <= 0) continue;
-                fits = w.rpt_off < ((int64_t)1 << 31) && w.nz_off < ((int64_t)1 << 31);
-                p.lean_items[1][j].rpt_off = (uint32_t)w.rpt_off;
-                p.lean_items[1][j].nz_off = (uint32_t)w.nz_off;
-            }
-            if (!fits) make_lean_items(p, d);
-        } else {
-            make_lean_items(p, d);
-        }
-        L.lean[d] = at;
-        at = align_up(at + p.lean_items[d].size() * sizeof(LeanItem));
-    }
-    L.op_records = at;
-    at = align_up(at + (size_t)n * sizeof(OpRecord));
-    L.build_order = at;
-    at = align_up(at + (size_t)n * sizeof(int32_t));
-    p.build_order.resize(n);
-    for (int i = 0; i < n; ++i) p.build_order[i] = i;
-    std::stable_sort(p.build_order.begin(), p.build_order.end(),
-                     [b](int32_t x, int32_t y) { return b->nnz[x] > b->nnz[y]; });
-    L.rpt_t = at;
-    at = align_up(at + (size_t)rpt_t_words * 4);
-    L.colids_t = at;
-    at = align_up(at + (size_t)nz_pack * 4);
-    L.values_t = at;
-    at = align_up(at + (size_t)nz_pack * 4);
-    L.scratch = at;
-    at = align_up(at + (size_t)scratch_words * 4);
-    L.flag = at;
-    at = align_up(at + 4);
-    for (int d = 0; d < 2; ++d) {
-        describe_sets(p, d);
-        L.sets[d] = at;
-        at = align_up(at + p.set_records[d].size() * sizeof(SetRecord));
-        L.merged[d] = at;
-        at = align_up(at + (size_t)p.merged_words[d] * 4);
-    }
-    make_stream_plan(p);
-    L.stream_records = at;
-    at = align_up(at + p.stream.records.size() * sizeof(SetRecord));
-    L.stream_merged = at;
-    at = align_up(at + (size_t)p.stream.merged_words * 4);
-    L.stream_sets = at;
-    at = align_up(at + p.stream.sets.size() * sizeof(StreamSet));
-    L.stream_list = at;
-    at = align_up(at + p.stream.list.size() * sizeof(int32_t));
-    L.stream_rest = at;
-    at = align_up(at + p.stream.rest.size() * sizeof(WorkItem));
+    auto place = [&at](size_t& where, size_t bytes) {
+        where = at;
+        at = align_up(at + bytes);
+    };
+    for (int d = 0; d < 2; ++d) place(L.items[d], p.sched[d].items.size() * sizeof(WorkItem));
+    for (int d = 0; d < 2; ++d) place(L.lean[d], p.lean_items[d].size() * sizeof(LeanItem));
+    if (p.lean_shared) L.lean[1] = L.lean[0];
+    place(L.op_records, (size_t)n * sizeof(OpRecord));
+    place(L.coo_records, p.coo_records.size() * sizeof(OpRecord));
+    place(L.build_order, (size_t)n * sizeof(int32_t));
+    for (int d = 0; d < 2; ++d) place(L.sets[d], p.set_records[d].size() * sizeof(SetRecord));
+    place(L.stream_records, p.stream.records.size() * sizeof(SetRecord));
+    place(L.stream_sets, p.stream.sets.size() * sizeof(StreamSet));
+    place(L.stream_list, p.stream.list.size() * sizeof(int32_t));
+    place(L.stream_rest, p.stream.rest.size() * sizeof(WorkItem));
+    L.image = at;
+    place(L.rpt_t, (size_t)rpt_t_words * 4);
+    place(L.colids_t, (size_t)nz_pack * 4);
+    place(L.values_t, (size_t)nz_pack * 4);
+    place(L.scratch, (size_t)scratch_words * 4);
+    place(L.flag, 4);
+    for (int d = 0; d < 2; ++d) place(L.merged[d], (size_t)p.merged_words[d] * 4);
+    place(L.stream_merged, (size_t)p.stream.merged_words * 4);
     L.total = at;
     return BSPMM_OK;
 }
@@ -1225,7 +1212,7 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     const bool vec4 = p->F % 4 == 0 && ld_in % 4 == 0 && ld_out % 4 == 0 &&
                       (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-    if (p->lean_items[d].empty()) {
+    if (!sc.whole) {
         const hipError_t e = launch_bspmm(P, sc.launch_grid, p->knobs.lds_words * 4, vec4, sc.has_slices,
                                           p->knobs.hubs, !sc.merged_sets.empty(), s);
         return e == hipSuccess ? BSPMM_OK : hip_fail(e);
@@ -1321,6 +1308,7 @@ int plan_host_coo_direct(bspmm_plan& p, const bspmm_coo_batch* b, int32_t F, con
     }
     L.coo_records = at;
     at = align_up(at + (size_t)n * sizeof(OpRecord));
+    L.image = at;
     L.flag = at;
     at = align_up(at + 4);
     L.total = at;
@@ -1376,8 +1364,6 @@ int plan_host_coo(bspmm_plan& p, const bspmm_coo_batch* b, int32_t F, const Knob
     p.coo_scratch_words = scratch_words;
     Layout& L = p.lay;
     size_t at = L.total;
-    L.coo_records = at;
-    at = align_up(at + (size_t)n * sizeof(OpRecord));
     L.csr_rpt = at;
     at = align_up(at + (size_t)rpt_words * 4);
     L.csr_colids = at;
@@ -1390,9 +1376,35 @@ int plan_host_coo(bspmm_plan& p, const bspmm_coo_batch* b, int32_t F, const Knob
     return BSPMM_OK;
 }
 
-// Device half of plan creation: tables to the workspace, conversions enqueued on `s`.
+// The tables the host writes, as they lie at the front of the workspace.
+void write_image(const bspmm_plan* p, char* to)
+{
+    auto put = [to](size_t where, const auto& v) {
+        if (!v.empty()) std::memcpy(to + where, v.data(), v.size() * sizeof(v[0]));
+    };
+    const Layout& L = p->lay;
+    for (int d = 0; d < 2; ++d) {
+        if (p->coo_direct)
+            put(L.items[d], p->coo_sched[d].items);
+        else
+            put(L.items[d], p->sched[d].items);
+        put(L.lean[d], p->lean_items[d]);
+        put(L.sets[d], p->set_records[d]);
+    }
+    put(L.op_records, p->records);
+    put(L.coo_records, p->coo_records);
+    put(L.build_order, p->build_order);
+    put(L.stream_records, p->stream.records);
+    put(L.stream_sets, p->stream.sets);
+    put(L.stream_list, p->stream.list);
+    put(L.stream_rest, p->stream.rest);
+}
+
+// Device half of plan creation: tables to the workspace, conversions enqueued on `s`.  `front`: host
+// arrays that go to the memory right in front of the workspace in the same copy; `pinned`: staging
+// memory may be taken for the copy.
 int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
-                size_t workspace_bytes, hipStream_t s)
+                size_t workspace_bytes, hipStream_t s, const HostFront* front = nullptr, bool pinned = true)
 {
     // The one-launch layer kernel's workgroup size, decided here (plans made by
     // bspmm_workspace_bytes never asked the device) and not in the first run, which may be
@@ -1422,60 +1434,25 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
         return BSPMM_EINVAL;
     if (workspace_bytes < p->lay.total) return BSPMM_ENOSPACE;
     p->ws = static_cast<char*>(workspace);
-    // The host tables stay alive inside the plan, so the asynchronous copies may read them
-    // at any time before bspmm_destroy.
+    // One copy brings the image of the tables, and in front of it the caller's arrays where they come
+    // from host memory.  From pinned memory, except in a stream capture (the copy then belongs to a
+    // graph and reads the plan's own memory on every replay) and for very large plans.
     hipError_t e = hipSuccess;
-    if (!p->coo_direct) {
-        // The item tables of both directions and the operation records sit back to back at the
-        // front of the workspace: one copy from one host image of that stretch (every copy from
-        // pageable memory costs several microseconds of host time, whatever its size).
-        const size_t bytes = p->lay.build_order + p->build_order.size() * sizeof(int32_t);
-        p->tables.assign(bytes, 0);
-        for (int d = 0; d < 2; ++d)
-            if (!p->sched[d].items.empty())
-                std::memcpy(p->tables.data() + p->lay.items[d], p->sched[d].items.data(),
-                            p->sched[d].items.size() * sizeof(WorkItem));
-        for (int d = 0; d < 2; ++d)
-            if (!p->lean_items[d].empty())
-                std::memcpy(p->tables.data() + p->lay.lean[d], p->lean_items[d].data(),
-                            p->lean_items[d].size() * sizeof(LeanItem));
-        if (!p->records.empty())
-            std::memcpy(p->tables.data() + p->lay.op_records, p->records.data(),
-                        p->records.size() * sizeof(OpRecord));
-        if (!p->build_order.empty())
-            std::memcpy(p->tables.data() + p->lay.build_order, p->build_order.data(),
-                        p->build_order.size() * sizeof(int32_t));
-        if (bytes > 0)
-            e = hipMemcpyAsync(p->ws, p->tables.data(), bytes, hipMemcpyHostToDevice, s);
+    const size_t head = front ? front->bytes : 0;
+    char* dst = p->ws - head;
+    StageBlock stage;
+    if (pinned && head + p->lay.image > 0 && !capturing(s)) stage = stage_take(head + p->lay.image);
+    if (front && !stage.ptr) return BSPMM_ESTATE;      // (the caller copies the arrays itself)
+    if (stage.ptr) {
+        if (front) front->write(front->from, stage.ptr);
+        write_image(p, stage.ptr + head);
+        e = stage_copy(stage, dst, head + p->lay.image, s);
+    } else if (p->lay.image > 0) {
+        p->tables.resize(p->lay.image);
+        write_image(p, p->tables.data());
+        e = hipMemcpyAsync(p->ws, p->tables.data(), p->tables.size(), hipMemcpyHostToDevice, s);
     }
-    for (int d = 0; d < 2 && e == hipSuccess; ++d)
-        if (!p->set_records[d].empty())
-            e = hipMemcpyAsync(p->ws + p->lay.sets[d], p->set_records[d].data(),
-                               p->set_records[d].size() * sizeof(SetRecord), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && p->stream.on()) {
-        e = hipMemcpyAsync(p->ws + p->lay.stream_records, p->stream.records.data(),
-                           p->stream.records.size() * sizeof(SetRecord), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-        e = hipMemcpyAsync(p->ws + p->lay.stream_sets, p->stream.sets.data(),
-                           p->stream.sets.size() * sizeof(StreamSet), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(p->ws + p->lay.stream_list, p->stream.list.data(),
-                               p->stream.list.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess && !p->stream.rest.empty())
-            e = hipMemcpyAsync(p->ws + p->lay.stream_rest, p->stream.rest.data(),
-                               p->stream.rest.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s);
-    }
-    if (p->coo_direct) {
-        for (int d = 0; d < 2 && e == hipSuccess; ++d)
-            if (!p->coo_sched[d].items.empty())
-                e = hipMemcpyAsync(p->ws + p->lay.items[d], p->coo_sched[d].items.data(),
-                                   p->coo_sched[d].items.size() * sizeof(CooItem),
-                                   hipMemcpyHostToDevice, s);
-        if (e == hipSuccess && !p->coo_records.empty())
-            e = hipMemcpyAsync(p->ws + p->lay.coo_records, p->coo_records.data(),
-                               p->coo_records.size() * sizeof(OpRecord), hipMemcpyHostToDevice, s);
-        return e == hipSuccess ? BSPMM_OK : hip_fail(e);
-    }
+    if (p->coo_direct) return e == hipSuccess ? BSPMM_OK : hip_fail(e);
     if (e == hipSuccess && p->from_coo) {
         int32_t* rpt = reinterpret_cast<int32_t*>(p->ws + p->lay.csr_rpt);
         int32_t* colids = reinterpret_cast<int32_t*>(p->ws + p->lay.csr_colids);
@@ -1483,16 +1460,12 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
         p->rpt = rpt;
         p->colids = colids;
         p->values = values;
-        if (!p->coo_records.empty()) {
-            e = hipMemcpyAsync(p->ws + p->lay.coo_records, p->coo_records.data(),
-                               p->coo_records.size() * sizeof(OpRecord), hipMemcpyHostToDevice, s);
-            if (e == hipSuccess)
-                e = launch_build_from_coo(
-                    reinterpret_cast<const OpRecord*>(p->ws + p->lay.coo_records), p->batch,
-                    p->build_threads, p->coo_build_lds_bytes, p->ids, p->coo_values, rpt, colids, values,
-                    reinterpret_cast<int32_t*>(p->ws + p->lay.coo_scratch),
-                    reinterpret_cast<const int32_t*>(p->ws + p->lay.build_order), s);
-        }
+        if (!p->coo_records.empty())
+            e = launch_build_from_coo(
+                reinterpret_cast<const OpRecord*>(p->ws + p->lay.coo_records), p->batch,
+                p->build_threads, p->coo_build_lds_bytes, p->ids, p->coo_values, rpt, colids, values,
+                reinterpret_cast<int32_t*>(p->ws + p->lay.coo_scratch),
+                reinterpret_cast<const int32_t*>(p->ws + p->lay.build_order), s);
     }
     if (e != hipSuccess) return hip_fail(e);
     if (options && (options->flags & BSPMM_BUILD_TRANSPOSE)) {
@@ -1680,7 +1653,78 @@ bspmm_plan* recall(const PlanKey& k, const Batch* b, const int64_t* rpt_off)
     return t_memo.release();
 }
 
+// The end of every create call: the plan to the caller, or nothing.
+int hand_over(bspmm_plan* p, int rc, bspmm_plan** plan)
+{
+    if (rc != BSPMM_OK) {
+        delete p;
+        return rc;
+    }
+    if (!p->dry) {
+        p->counted = true;
+        stage_plan_made();
+    }
+    *plan = p;
+    return BSPMM_OK;
+}
+
+int create_csr(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const bspmm_options* options, void* workspace,
+               size_t workspace_bytes, const HostFront* front, hipStream_t stream)
+{
+    if (!plan) return BSPMM_EINVAL;
+    *plan = nullptr;
+    const bool dry = options && (options->flags & BSPMM_DRY_RUN);
+    int rc = check_batch(b, F, !dry);
+    if (rc != BSPMM_OK) return rc;
+    bspmm_plan* p = b->batch > 0 ? recall(make_key(b->batch, F, options, false), b, b->rpt_off) : nullptr;
+    if (!p) {
+        p = new (std::nothrow) bspmm_plan;
+        if (!p) return BSPMM_EINVAL;
+        rc = plan_with_budget(*p, b, F, options, dry, plan_host);
+    }
+    p->dry = dry;
+    if (rc == BSPMM_OK && !dry) {
+        p->rpt = b->rpt;
+        p->colids = b->colids;
+        p->values = b->values;
+        rc = upload_plan(p, options, workspace, workspace_bytes, stream, front);
+    }
+    return hand_over(p, rc, plan);
+}
+
 }  // namespace
+
+namespace bspmm {
+
+int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const bspmm_options* options,
+                     void* workspace, size_t workspace_bytes, const HostFront& front, void* stream)
+{
+    return create_csr(plan, b, F, options, workspace, workspace_bytes, &front, static_cast<hipStream_t>(stream));
+}
+
+int64_t covered_rows(bspmm_plan* plan, bool transposed)
+{
+    int64_t& known = plan->covered[transposed ? 1 : 0];
+    if (known >= 0) return known;
+    const std::vector<int64_t>& off = transposed ? plan->dir[0].in_off : plan->dir[0].out_off;
+    const std::vector<int32_t>& len = transposed ? plan->dir[0].k : plan->dir[0].m;
+    std::vector<std::pair<int64_t, int64_t>> blocks;
+    int64_t end = 0;
+    for (size_t i = 0; i < off.size(); ++i) {
+        if (blocks.empty() && off[i] <= end)       // the usual case: back to back in operation order
+            end = std::max(end, off[i] + len[i]);
+        else
+            blocks.emplace_back(off[i], off[i] + len[i]);
+    }
+    std::sort(blocks.begin(), blocks.end());
+    for (const auto& b : blocks) {
+        if (b.first > end) break;
+        end = std::max(end, b.second);
+    }
+    return known = end;
+}
+
+}  // namespace bspmm
 
 extern "C" {
 
@@ -1708,30 +1752,7 @@ int bspmm_create(bspmm_plan** plan, const bspmm_batch* b, int32_t F,
                  const bspmm_options* options, void* workspace, size_t workspace_bytes,
                  void* stream)
 {
-    if (!plan) return BSPMM_EINVAL;
-    *plan = nullptr;
-    const bool dry = options && (options->flags & BSPMM_DRY_RUN);
-    int rc = check_batch(b, F, !dry);
-    if (rc != BSPMM_OK) return rc;
-    bspmm_plan* p = b->batch > 0 ? recall(make_key(b->batch, F, options, false), b, b->rpt_off) : nullptr;
-    if (!p) {
-        p = new (std::nothrow) bspmm_plan;
-        if (!p) return BSPMM_EINVAL;
-        rc = plan_with_budget(*p, b, F, options, dry, plan_host);
-    }
-    p->dry = dry;
-    if (rc == BSPMM_OK && !dry) {
-        p->rpt = b->rpt;
-        p->colids = b->colids;
-        p->values = b->values;
-        rc = upload_plan(p, options, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
-    }
-    if (rc != BSPMM_OK) {
-        delete p;
-        return rc;
-    }
-    *plan = p;
-    return BSPMM_OK;
+    return create_csr(plan, b, F, options, workspace, workspace_bytes, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int bspmm_create_static(bspmm_plan** plan, const bspmm_batch* b, int32_t F,
@@ -1760,14 +1781,9 @@ int bspmm_create_static(bspmm_plan** plan, const bspmm_batch* b, int32_t F,
         p->static_generation =
             g_static_generation[dev].fetch_add(1, std::memory_order_acq_rel) + 1;
         rc = upload_plan(p, options, ws, (size_t)BSPMM_STATIC_WORKSPACE_BYTES,
-                         static_cast<hipStream_t>(stream));
+                         static_cast<hipStream_t>(stream), nullptr, false);
     }
-    if (rc != BSPMM_OK) {
-        delete p;
-        return rc;
-    }
-    *plan = p;
-    return BSPMM_OK;
+    return hand_over(p, rc, plan);
 }
 
 int bspmm_workspace_bytes_coo(const bspmm_coo_batch* b, int32_t F, const bspmm_options* options,
@@ -1811,12 +1827,7 @@ int bspmm_create_coo(bspmm_plan** plan, const bspmm_coo_batch* b, int32_t F,
         p->coo_values = b->values;
         rc = upload_plan(p, options, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     }
-    if (rc != BSPMM_OK) {
-        delete p;
-        return rc;
-    }
-    *plan = p;
-    return BSPMM_OK;
+    return hand_over(p, rc, plan);
 }
 
 int bspmm_export_csr(bspmm_plan* plan, int32_t* rpt, int32_t* colids, float* values, void* stream)
@@ -1957,7 +1968,7 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
         info->tile[d] = plan->sched[d].tile;
         info->workgroups[d] = plan->sched[d].launch_grid;
         info->tasks[d] = plan->sched[d].grid;
-        info->items[d] = (int32_t)plan->sched[d].view.size();
+        info->items[d] = plan->sched[d].count;
         for (int b = 0; b < BSPMM_NUM_BINS; ++b)
             info->items_in_bin[d][b] = plan->sched[d].items_in_bin[b];
         info->effective_bytes[d] = plan->effective_bytes[d];
@@ -1970,7 +1981,7 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
     }
     info->transposed_supported = plan->transposed_supported ? 1 : 0;
     info->transposed_built = plan->transposed_built ? 1 : 0;
-    for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].lean && !plan->lean_items[d].empty() ? 1 : 0;
+    for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].lean ? 1 : 0;
     if (plan->stream.on()) {
         info->front_stream[0] = plan->stream.graphs;
         info->front_stream[1] = plan->stream.lists * plan->stream.tiles;
@@ -1988,15 +1999,20 @@ int bspmm_plan_items(const bspmm_plan* plan, int32_t transposed, bspmm_item* ite
                      int32_t capacity, int32_t* count)
 {
     if (!plan || !count || capacity < 0 || (capacity > 0 && !items)) return BSPMM_EINVAL;
-    const std::vector<bspmm_item>& v = plan->coo_direct ? plan->coo_sched[transposed ? 1 : 0].view
-                                                        : plan->sched[transposed ? 1 : 0].view;
+    const int d = transposed ? 1 : 0;
+    const std::vector<bspmm_item> v = plan->coo_direct ? plan->coo_sched[d].view
+                                                       : items_of(plan->sched[d], plan->lean_items[plan->lean_shared ? 0 : d]);
     *count = (int32_t)v.size();
     const size_t n = std::min<size_t>(v.size(), (size_t)capacity);
     if (n) std::memcpy(items, v.data(), n * sizeof(bspmm_item));
     return BSPMM_OK;
 }
 
-void bspmm_destroy(bspmm_plan* plan) { delete plan; }
+void bspmm_destroy(bspmm_plan* plan)
+{
+    if (plan && plan->counted) stage_plan_gone();
+    delete plan;
+}
 
 const char* bspmm_strerror(int code)
 {

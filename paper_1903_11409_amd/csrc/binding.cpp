@@ -1,84 +1,87 @@
-// CPython side of the binding: the run calls of include/bspmm.h without ctypes.
+// CPython side of the binding: plan creation and the run calls of include/bspmm.h without ctypes.
 //
 // A launch of a small batch costs the host about 2.4 us in hipLaunchKernel, and the Python around
 // it used to cost twice that (torch.cuda.current_stream() 2.5 us, ctypes argument conversion
 // 0.7 us, leading dimensions and pointers 0.7 us: 7.3 us a call in all, so every product of less
-// than that on the GPU ran at the rate of the interpreter).  Here a call takes pointers and
-// strides from the tensors with interned method names, asks PyTorch for the raw handle of the
-// current stream, and calls the C ABI.  Only argument marshalling: no step of the path is here.
+// than that on the GPU ran at the rate of the interpreter).  Here pointers, strides and the current
+// stream come straight from PyTorch's C++ objects.  Making a plan from a data loader's host arrays
+// took 110 us for 128 graphs: three blocking copies, ctypes views of ten arrays, and the host
+// schedule; now the arrays and the plan's tables go over in one copy (staging.hpp) behind one call.
+// Only argument marshalling: no step of the path is here.
 #define PY_SSIZE_T_CLEAN
+#define NPY_NO_DEPRECATED_API NPY_1_7_API_VERSION
 #include <Python.h>
+#include <numpy/arrayobject.h>
+
+#include <ATen/ops/empty.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <cstring>
+#include <exception>
 
-#include "../../include/bspmm.h"
+#include "plan_api.hpp"
 
 namespace {
 
 PyObject* s_data_ptr;        // interned method names
-PyObject* s_stride;
 PyObject* s_cuda_stream;
 PyObject* g_check;           // bspmm._check(code, where): raises BspmmError
 PyObject* g_ld;              // bspmm._ld(tensor, width): every case the fast path below leaves out
-PyObject* g_raw_stream;      // torch._C._cuda_getCurrentRawStream
-PyObject* g_device;          // torch._C._cuda_getDevice
 
-// bspmm._native is set up by the module that imports it: setup(check, ld, raw_stream, get_device).
+// bspmm._native is set up by the module that imports it: setup(check, ld).
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
-    if (n != 4) {
-        PyErr_SetString(PyExc_TypeError, "setup takes four callables");
+    if (n != 2) {
+        PyErr_SetString(PyExc_TypeError, "setup takes two callables");
         return nullptr;
     }
-    PyObject** const slot[4] = {&g_check, &g_ld, &g_raw_stream, &g_device};
-    for (int i = 0; i < 4; ++i) {
+    PyObject** const slot[2] = {&g_check, &g_ld};
+    for (int i = 0; i < 2; ++i) {
         Py_INCREF(a[i]);
         Py_XSETREF(*slot[i], a[i]);
     }
     Py_RETURN_NONE;
 }
 
-PyObject* call_method(PyObject* self, PyObject* name)
-{
-    PyObject* const args[1] = {self};
-    return PyObject_VectorcallMethod(name, args, 1 | PY_VECTORCALL_ARGUMENTS_OFFSET, nullptr);
-}
+bool is_tensor(PyObject* o) { return THPVariable_CheckExact(o); }
 
 // Address of a tensor, an integer address, or NULL for None.
 bool get_ptr(PyObject* o, void** out)
 {
     *out = nullptr;
+    if (is_tensor(o)) {
+        *out = THPVariable_Unpack(o).data_ptr();
+        return true;
+    }
     if (o == Py_None) return true;
     if (PyLong_Check(o)) {
         *out = PyLong_AsVoidPtr(o);
         return !PyErr_Occurred();
     }
-    PyObject* r = call_method(o, s_data_ptr);
+    PyObject* r = PyObject_CallMethodNoArgs(o, s_data_ptr);
     if (!r) return false;
     *out = PyLong_AsVoidPtr(r);
     Py_DECREF(r);
     return !PyErr_Occurred();
 }
 
-// Leading dimension of a row-major matrix: stride(0) of a two-dimensional tensor whose rows are
-// at least `width` apart; anything else (fewer than two rows, other ranks, rows too close) is
-// decided by the Python function (`own`: told the tensor's own width).
-bool get_ld(PyObject* t, int64_t width, int64_t* ld, bool own = false)
+// Leading dimension of a row-major matrix: stride(0) of a two-dimensional tensor of at least two
+// rows; anything else is decided by the Python function (`own`: told the tensor's own width).
+bool get_ld(PyObject* o, int64_t width, int64_t* ld, bool own = false)
 {
-    PyObject* st = call_method(t, s_stride);
-    if (!st) return false;
-    if (PyTuple_Check(st) && PyTuple_GET_SIZE(st) == 2) {
-        *ld = PyLong_AsLongLong(PyTuple_GET_ITEM(st, 0));
-        if (*ld >= width && !PyErr_Occurred()) {
-            Py_DECREF(st);
+    if (is_tensor(o)) {
+        const at::Tensor& t = THPVariable_Unpack(o);
+        if (t.dim() == 2 && t.size(0) >= 2) {
+            *ld = t.stride(0);
             return true;
         }
-        PyErr_Clear();
     }
-    Py_DECREF(st);
     PyObject* w = own ? Py_NewRef(Py_None) : PyLong_FromLongLong(width);
     if (!w) return false;
-    PyObject* const args[2] = {t, w};
+    PyObject* const args[2] = {o, w};
     PyObject* r = PyObject_Vectorcall(g_ld, args, 2, nullptr);
     Py_DECREF(w);
     if (!r) return false;
@@ -90,19 +93,11 @@ bool get_ld(PyObject* t, int64_t width, int64_t* ld, bool own = false)
 // None: the current stream of the current device; an integer handle; or an object with one.
 bool get_stream(PyObject* o, void** out)
 {
-    PyObject* r;
     if (o == Py_None) {
-        PyObject* dev = PyObject_Vectorcall(g_device, nullptr, 0, nullptr);
-        if (!dev) return false;
-        PyObject* const args[1] = {dev};
-        r = PyObject_Vectorcall(g_raw_stream, args, 1, nullptr);
-        Py_DECREF(dev);
-    } else if (PyLong_Check(o)) {
-        Py_INCREF(o);
-        r = o;
-    } else {
-        r = PyObject_GetAttr(o, s_cuda_stream);
+        *out = c10::hip::getCurrentHIPStream().stream();
+        return true;
     }
+    PyObject* r = PyLong_Check(o) ? Py_NewRef(o) : PyObject_GetAttr(o, s_cuda_stream);
     if (!r) return false;
     *out = PyLong_AsVoidPtr(r);
     Py_DECREF(r);
@@ -130,9 +125,10 @@ PyObject* finish(int rc, const char* where, PyObject* value)
         Py_XDECREF(r);
         return nullptr;
     }
-    Py_INCREF(value);
-    return value;
+    return Py_NewRef(value);
 }
+
+// ---- products
 
 using RunFn = int (*)(bspmm_plan*, const float*, float*, int64_t, int64_t, void*);
 
@@ -174,13 +170,13 @@ PyObject* product(const char* where, PyObject* const* a, Py_ssize_t n)
     return finish(call<FN>(plan, in, out, ld_in, ld_out, stream), where, Py_None);
 }
 
-PyObject* plan_run(PyObject*, PyObject* const* a, Py_ssize_t n) { return plan_product<bspmm_run>("bspmm_run", a, n); }
-PyObject* plan_run_transposed(PyObject*, PyObject* const* a, Py_ssize_t n)
+PyObject* plan_run(PyObject* const* a, Py_ssize_t n) { return plan_product<bspmm_run>("bspmm_run", a, n); }
+PyObject* plan_run_transposed(PyObject* const* a, Py_ssize_t n)
 {
     return plan_product<bspmm_run_transposed>("bspmm_run_transposed", a, n);
 }
-PyObject* run(PyObject*, PyObject* const* a, Py_ssize_t n) { return product<bspmm_run>("bspmm_run", a, n); }
-PyObject* run_transposed(PyObject*, PyObject* const* a, Py_ssize_t n)
+PyObject* run(PyObject* const* a, Py_ssize_t n) { return product<bspmm_run>("bspmm_run", a, n); }
+PyObject* run_transposed(PyObject* const* a, Py_ssize_t n)
 {
     return product<bspmm_run_transposed>("bspmm_run_transposed", a, n);
 }
@@ -202,7 +198,7 @@ PyObject* gcn(PyObject* const* ptrs, int64_t ldx, int64_t ldw, int64_t ldy, PyOb
 }
 
 // (plan, X, W, bias, Y, n_X, F, accumulate, stream): leading dimensions from the tensors; returns Y
-PyObject* plan_run_gcn(PyObject*, PyObject* const* a, Py_ssize_t n)
+PyObject* plan_run_gcn(PyObject* const* a, Py_ssize_t n)
 {
     int64_t nx, F, ldx, ldw, ldy;
     if (!arity("bspmm_run_gcn", n, 9) || !get_i64(a[5], &nx) || !get_i64(a[6], &F) || !get_ld(a[1], nx, &ldx, true) ||
@@ -212,7 +208,7 @@ PyObject* plan_run_gcn(PyObject*, PyObject* const* a, Py_ssize_t n)
 }
 
 // (plan, X, W, bias, Y, ldx, ldw, ldy, accumulate, stream)
-PyObject* run_gcn(PyObject*, PyObject* const* a, Py_ssize_t n)
+PyObject* run_gcn(PyObject* const* a, Py_ssize_t n)
 {
     int64_t ldx, ldw, ldy;
     if (!arity("bspmm_run_gcn", n, 10) || !get_i64(a[5], &ldx) || !get_i64(a[6], &ldw) || !get_i64(a[7], &ldy))
@@ -220,19 +216,220 @@ PyObject* run_gcn(PyObject*, PyObject* const* a, Py_ssize_t n)
     return gcn(a, ldx, ldw, ldy, a[8], a[9], Py_None);
 }
 
-#define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(name)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {FAST(setup), FAST(plan_run), FAST(plan_run_transposed), FAST(plan_run_gcn), FAST(run),
-                         FAST(run_transposed), FAST(run_gcn), {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Run calls of libbspmm without ctypes.", -1, methods,
+// ---- plans
+
+constexpr size_t kAlign = 256;
+size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+
+// Data of a one-dimensional C-contiguous array of the given type, or null.
+template <typename T>
+const T* array_of(PyObject* o, int type, Py_ssize_t* n)
+{
+    if (!PyArray_Check(o)) return nullptr;
+    PyArrayObject* a = reinterpret_cast<PyArrayObject*>(o);
+    if (PyArray_NDIM(a) != 1 || PyArray_TYPE(a) != type || !PyArray_ISCARRAY_RO(a)) return nullptr;
+    *n = PyArray_SIZE(a);
+    return static_cast<const T*>(PyArray_DATA(a));
+}
+
+// The per-operation arrays at a[0] ..: `i32` of them int32, the others int64; the first one's length is
+// the batch.
+bool meta_arrays(PyObject* const* a, int i32, int total, const void** out, int32_t* batch)
+{
+    Py_ssize_t n0 = -1;
+    for (int i = 0; i < total; ++i) {
+        Py_ssize_t n = 0;
+        if (i < i32)
+            out[i] = array_of<int32_t>(a[i], NPY_INT32, &n);
+        else
+            out[i] = array_of<int64_t>(a[i], NPY_INT64, &n);
+        if (n0 < 0) n0 = n;
+        if (!out[i] || n0 > INT32_MAX || n < n0) return false;
+    }
+    *batch = (int32_t)n0;
+    return true;
+}
+
+// A contiguous device tensor of the given type.
+bool device_data(PyObject* o, at::ScalarType type, int64_t device, const void** out)
+{
+    if (!is_tensor(o)) return false;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || t.get_device() != device || t.scalar_type() != type || !t.is_contiguous()) return false;
+    *out = t.numel() ? t.data_ptr() : nullptr;
+    return true;
+}
+
+at::Tensor device_bytes(size_t n, int64_t device)
+{
+    return at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(at::Device(at::kCUDA, (c10::DeviceIndex)device)));
+}
+
+PyObject* made(bspmm_plan* plan, const at::Tensor& memory, size_t head)
+{
+    PyObject* t = THPVariable_Wrap(memory);
+    return t ? Py_BuildValue("(KNn)", (unsigned long long)reinterpret_cast<uintptr_t>(plan), t, (Py_ssize_t)head) : nullptr;
+}
+
+// The caller's CSR arrays in host memory, and how they lie in front of the workspace.
+struct Csr {
+    const void* data[3];
+    size_t bytes[3];
+    size_t head() const { return align_up(bytes[0]) + align_up(bytes[1]) + align_up(bytes[2]); }
+    static void write(const void* from, char* to)
+    {
+        const Csr& c = *static_cast<const Csr*>(from);
+        for (int i = 0; i < 3; ++i) {
+            std::memcpy(to, c.data[i], c.bytes[i]);
+            to += align_up(c.bytes[i]);
+        }
+    }
+};
+
+// (rows, cols, nnz, rpt_off, nz_off, b_row_off, c_row_off, rpt, colids, values, F, options address or
+// None, device index, stream) -> (plan, memory, bytes in front of the workspace), the CSR arrays
+// all host arrays or all device tensors; None when an argument is of another kind (the caller
+// converts it) or the arrays cannot be staged.
+PyObject* create(PyObject* const* a, Py_ssize_t n)
+{
+    int64_t F, device;
+    void *options, *stream;
+    if (!arity("bspmm_create", n, 14) || !get_i64(a[10], &F) || !get_ptr(a[11], &options) || !get_i64(a[12], &device))
+        return nullptr;
+    const void* meta[7];
+    bspmm_batch b;
+    if (F > INT32_MAX || !meta_arrays(a, 3, 7, meta, &b.batch)) Py_RETURN_NONE;
+    b.rows = static_cast<const int32_t*>(meta[0]), b.cols = static_cast<const int32_t*>(meta[1]);
+    b.nnz = static_cast<const int32_t*>(meta[2]), b.rpt_off = static_cast<const int64_t*>(meta[3]);
+    b.nz_off = static_cast<const int64_t*>(meta[4]), b.b_row_off = static_cast<const int64_t*>(meta[5]);
+    b.c_row_off = static_cast<const int64_t*>(meta[6]);
+    Csr csr;
+    Py_ssize_t len[3];
+    csr.data[0] = array_of<int32_t>(a[7], NPY_INT32, &len[0]);
+    csr.data[1] = array_of<int32_t>(a[8], NPY_INT32, &len[1]);
+    csr.data[2] = array_of<float>(a[9], NPY_FLOAT32, &len[2]);
+    const bool host = csr.data[0] && csr.data[1] && csr.data[2];
+    const void* dev[3] = {nullptr, nullptr, nullptr};
+    if (!host && !(device_data(a[7], at::kInt, device, &dev[0]) && device_data(a[8], at::kInt, device, &dev[1]) &&
+                   device_data(a[9], at::kFloat, device, &dev[2]) && dev[0]))
+        Py_RETURN_NONE;
+    for (int i = 0; i < 3; ++i) csr.bytes[i] = host ? 4 * (size_t)len[i] : 0;
+    if (!get_stream(a[13], &stream)) return nullptr;
+    const bspmm_options* opt = static_cast<const bspmm_options*>(options);
+    const size_t head = host ? csr.head() : 0;
+    size_t need = 0;
+    bspmm_plan* plan = nullptr;
+    at::Tensor memory;
+    const char* where = "bspmm_workspace_bytes";
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = bspmm_workspace_bytes(&b, (int32_t)F, opt, &need);
+    if (rc == BSPMM_OK) {
+        where = "bspmm_create";
+        need = need < kAlign ? kAlign : need;
+        memory = device_bytes(head + need, device);
+        char* base = static_cast<char*>(memory.data_ptr());
+        if (host) {
+            b.rpt = reinterpret_cast<const int32_t*>(base);
+            b.colids = reinterpret_cast<const int32_t*>(base + align_up(csr.bytes[0]));
+            b.values = reinterpret_cast<const float*>(base + align_up(csr.bytes[0]) + align_up(csr.bytes[1]));
+            rc = bspmm::create_from_host(&plan, &b, (int32_t)F, opt, base + head, need, {head, Csr::write, &csr}, stream);
+        } else {
+            b.rpt = static_cast<const int32_t*>(dev[0]);
+            b.colids = static_cast<const int32_t*>(dev[1]);
+            b.values = static_cast<const float*>(dev[2]);
+            rc = bspmm_create(&plan, &b, (int32_t)F, opt, base, need, stream);
+        }
+    }
+    Py_END_ALLOW_THREADS
+    if (host && rc == BSPMM_ESTATE) Py_RETURN_NONE;
+    return rc == BSPMM_OK ? made(plan, memory, head) : finish(rc, where, Py_None);
+}
+
+// (rows, cols, nnz, nz_off, b_row_off, c_row_off, ids, values, F, options address or None, device index,
+// stream) -> (plan, memory, 0); ids and values device tensors; None as above.
+PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
+{
+    int64_t F, device;
+    void *options, *stream;
+    if (!arity("bspmm_create_coo", n, 12) || !get_i64(a[8], &F) || !get_ptr(a[9], &options) || !get_i64(a[10], &device))
+        return nullptr;
+    const void *meta[6], *ids, *values;
+    bspmm_coo_batch b;
+    if (F > INT32_MAX || !meta_arrays(a, 3, 6, meta, &b.batch) || !device_data(a[6], at::kInt, device, &ids) ||
+        !device_data(a[7], at::kFloat, device, &values))
+        Py_RETURN_NONE;
+    b.rows = static_cast<const int32_t*>(meta[0]), b.cols = static_cast<const int32_t*>(meta[1]);
+    b.nnz = static_cast<const int32_t*>(meta[2]), b.nz_off = static_cast<const int64_t*>(meta[3]);
+    b.b_row_off = static_cast<const int64_t*>(meta[4]), b.c_row_off = static_cast<const int64_t*>(meta[5]);
+    b.ids = static_cast<const int32_t*>(ids);
+    b.values = static_cast<const float*>(values);
+    if (!get_stream(a[11], &stream)) return nullptr;
+    const bspmm_options* opt = static_cast<const bspmm_options*>(options);
+    size_t need = 0;
+    bspmm_plan* plan = nullptr;
+    at::Tensor memory;
+    const char* where = "bspmm_workspace_bytes_coo";
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = bspmm_workspace_bytes_coo(&b, (int32_t)F, opt, &need);
+    if (rc == BSPMM_OK) {
+        where = "bspmm_create_coo";
+        need = need < kAlign ? kAlign : need;
+        memory = device_bytes(need, device);
+        rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
+    }
+    Py_END_ALLOW_THREADS
+    return rc == BSPMM_OK ? made(plan, memory, 0) : finish(rc, where, Py_None);
+}
+
+// (plan, transposed) -> rows from the first on that every product writes
+PyObject* covered_rows(PyObject* const* a, Py_ssize_t n)
+{
+    void* plan;
+    if (!arity("covered_rows", n, 2) || !get_ptr(a[0], &plan)) return nullptr;
+    const int transposed = PyObject_IsTrue(a[1]);
+    if (transposed < 0) return nullptr;
+    return PyLong_FromLongLong(plan ? bspmm::covered_rows(static_cast<bspmm_plan*>(plan), transposed) : 0);
+}
+
+// C++ exceptions of PyTorch (no device, out of memory) become Python's.
+template <PyObject* (*FN)(PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    PyThreadState* const mine = PyThreadState_Get();
+    try {
+        return FN(a, n);
+    } catch (...) {
+        const std::exception_ptr e = std::current_exception();
+        if (!PyGILState_Check()) PyEval_RestoreThread(mine);     // thrown while the lock was given up
+        torch::translate_exception_to_python(e);
+        return nullptr;
+    }
+}
+
+template <PyObject* (*FN)(PyObject* const*, Py_ssize_t)>
+PyMethodDef fast(const char* name)
+{
+    return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&guarded<FN>)), METH_FASTCALL, nullptr};
+}
+
+PyMethodDef methods[] = {
+    {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&setup)), METH_FASTCALL, nullptr},
+    fast<plan_run>("plan_run"), fast<plan_run_transposed>("plan_run_transposed"), fast<plan_run_gcn>("plan_run_gcn"),
+    fast<run>("run"), fast<run_transposed>("run_transposed"), fast<run_gcn>("run_gcn"),
+    fast<covered_rows>("covered_rows"), fast<create>("create"), fast<create_coo>("create_coo"),
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Plan creation and run calls of libbspmm.", -1, methods,
                       nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
 PyMODINIT_FUNC PyInit__native(void)
 {
+    import_array();
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
-    s_stride = PyUnicode_InternFromString("stride");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    if (!s_data_ptr || !s_stride || !s_cuda_stream) return nullptr;
+    if (!s_data_ptr || !s_cuda_stream) return nullptr;
     return PyModule_Create(&module);
 }

@@ -1,0 +1,29 @@
+// Plan creation from arrays in host memory, for the Python binding (not part of the C ABI).
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+#include "../../include/bspmm.h"
+
+namespace bspmm {
+
+// `bytes` (a multiple of 256) that write(from, to) puts in front of the plan's tables.
+struct HostFront {
+    size_t bytes;
+    void (*write)(const void* from, char* to);
+    const void* from;
+};
+
+// bspmm_create for a workspace at `workspace` whose front memory [workspace - front.bytes, workspace)
+// is the device home of the arrays `front` writes; `b` names them by their device addresses.  The
+// host arrays are read during the call.  ESTATE when they cannot be staged (too large, or the stream
+// is being captured): the caller then copies them itself and calls bspmm_create.
+int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const bspmm_options* options,
+                     void* workspace, size_t workspace_bytes, const HostFront& front, void* stream);
+
+// Rows from the first on, without a gap, that belong to an operation's output: of C, or of G with
+// `transposed`.
+int64_t covered_rows(bspmm_plan* plan, bool transposed);
+
+}  // namespace bspmm

@@ -355,11 +355,17 @@ Groups output_groups(const DirOps& o)
 // share an index).
 std::vector<int> input_blocks(const DirOps& o)
 {
+    std::vector<int> block(o.size(), 0);
+    bool sorted = true;            // the usual case: blocks back to back in operation order
+    for (int i = 1; i < o.size() && sorted; ++i) sorted = o.in_off[i] >= o.in_off[i - 1];
+    if (sorted) {
+        for (int i = 1; i < o.size(); ++i) block[i] = block[i - 1] + (o.in_off[i] != o.in_off[i - 1]);
+        return block;
+    }
     std::vector<int> order(o.size());
     std::iota(order.begin(), order.end(), 0);
     std::sort(order.begin(), order.end(),
               [&](int a, int b) { return o.in_off[a] != o.in_off[b] ? o.in_off[a] < o.in_off[b] : a < b; });
-    std::vector<int> block(o.size(), 0);
     int nb = -1;
     for (size_t t = 0; t < order.size(); ++t) {
         if (t == 0 || o.in_off[order[t]] != o.in_off[order[t - 1]]) ++nb;
@@ -407,6 +413,85 @@ void draft_all(const DirOps& o, int F, int vec, const std::vector<int>& cand, si
     }
 }
 
+// The search over batch-wide tiles and row cuts.  count(first, cap, small) says how many workgroups
+// the launch would get with candidate tiles from `first` on, workgroup items cut into row ranges of
+// `cap` passes (0: not cut) and, with `small`, sub-workgroup slots, and how many dense-tile words its
+// staged items would copy.
+struct Count {
+    int wgs;
+    int64_t tile_words;
+};
+struct Shape {
+    size_t chosen;
+    int cap, wgs;
+    bool small;
+};
+
+template <typename CountFn>
+Shape search_shape(const Knobs& kn, int vec, size_t candidates, bool allow_small, CountFn count)
+{
+    Shape s = {candidates - 1, kn.wg_passes > 0 ? kn.wg_passes : 0, 0, allow_small};
+    // (F % 4 != 0: the widest tile every operation can hold, and row ranges for parallelism - see below)
+    const bool wide_first = vec == 1 && kn.front == 0;
+    int64_t tile_words = 0;
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        for (size_t c = 0; c < candidates; ++c) {
+            const Count n = count(c, s.cap, s.small);
+            s.wgs = n.wgs;
+            tile_words = n.tile_words;
+            if (wide_first || s.wgs >= kn.target_wgs || c + 1 == candidates) {
+                s.chosen = c;
+                break;
+            }
+        }
+        if (s.small || s.wgs <= kn.capacity_wgs || kn.front > 0 || wide_first) break;
+        s.small = true;
+    }
+    if (kn.wg_passes != 0 || kn.front != 0) return s;
+    if (wide_first) {
+        // Widths off 16 bytes: a tile of whole rows is one run of memory, cheaper to copy several
+        // times (out of L2) than column tiles whose rows start anywhere.  Ranges of at most eight
+        // passes over the lane groups (200 operations of 1 to 220 rows, F = 127: uncut 16.5 us, sixteen
+        // passes 12.3, eight 9.3), shorter until there are two workgroups per CU, but not in launches
+        // bound by bandwidth.
+        const int want = kn.target_given ? kn.target_wgs : 2 * kn.compute_units;
+        for (int c = 8; c >= 1; c /= 2) {
+            const Count n = count(s.chosen, c, s.small);
+            s.wgs = n.wgs;
+            s.cap = c;
+            if (n.wgs >= want || n.tile_words > 3500000) break;
+        }
+        return s;
+    }
+    // still too few workgroups at the narrowest tile: the batch is small, its time is set by
+    // the slowest workgroup, so cut multi-pass workgroup items into row ranges
+    // Likewise while the launch still fits the chip at once: the workgroups with several passes
+    // are its critical path, and cutting them pays as long as no workgroup has to wait for a
+    // free slot and the pieces, each of which copies the whole dense tile again, do not add
+    // more than 60 % to the tile traffic (measured: 256 molecule graphs 4.9 -> 4.3 us, 512
+    // graphs 5.9 -> 4.8 us; cut beyond what the chip holds, 384 graphs go from 4.9 to 5.9 us;
+    // wide tiles of 100-row graphs cut to four rows each, 8.2 -> 9.2 us).
+    const int uncut = s.wgs;                       // (the tile search ended on this very count)
+    const int64_t uncut_words = tile_words;
+    // (a launch that moves more than about 28 MB is bound by bandwidth, not by its slowest
+    // workgroup: there the extra copies only cost)
+    const bool latency_bound = uncut_words <= 3500000;
+    for (int c = 1; c <= 4 && uncut <= kn.capacity_wgs && latency_bound; c *= 2) {
+        const Count n = count(s.chosen, c, s.small);
+        if (n.wgs <= kn.capacity_wgs && 5 * (n.tile_words - uncut_words) <= 3 * uncut_words) {
+            s.cap = c;
+            s.wgs = n.wgs;
+            return s;
+        }
+    }
+    if (uncut < kn.target_wgs)
+        for (s.cap = 4; s.cap >= 1; s.cap /= 2) {
+            s.wgs = count(s.chosen, s.cap, s.small).wgs;
+            if (s.wgs >= kn.target_wgs || s.cap == 1) break;
+        }
+    return s;
+}
+
 WorkItem to_item(const DirOps& o, const Draft& x)
 {
     WorkItem w;
@@ -432,6 +517,199 @@ WorkItem empty_item()
     w.m = w.k = w.nnz = w.row0 = w.nrows = w.f0 = w.fw = 0;
     w.staged = 1;
     return w;
+}
+
+// The plain batch - every operation an output block of its own, no forced bins, no sub-workgroup slots,
+// nothing riding along - straight to the compact item table.  A data loader plans a batch per step,
+// so this is on its critical path: no item is written twice, ordering and placement work on
+// groups of items, and counting is closed form (128 molecules at F = 128: MEASURED_PLAN).
+// Returns false when the batch needs the general planner below.
+bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std::vector<int>& cand, Schedule& s)
+{
+    const int n = o.size();
+    const int nc = (int)cand.size();
+    if (nc > 64) return false;
+    constexpr int64_t kLimit = (int64_t)1 << 31;       // the table's 32-bit fields
+    for (int i = 0; i < n; ++i)
+        if (o.rpt_off[i] >= kLimit || o.nz_off[i] >= kLimit || o.in_off[i] >= kLimit || o.out_off[i] >= kLimit)
+            return false;
+
+    // per candidate: its full tiles and the rest of the columns (width, columns of tiles, rows per pass
+    // of a row in four-float lanes and of a long row in one-float lanes), words from row to row in LDS
+    struct Columns {
+        int width = 0, sh = 0, rows[2] = {1, 1};
+        bool pow2 = true;
+        explicit Columns(int w = 0) : width(w)
+        {
+            if (w <= 0) return;
+            const int v = w >> 2;
+            pow2 = w % 4 == 0 && v > 0 && v <= 64 && (v & (v - 1)) == 0;
+            while ((4 << sh) < w) ++sh;
+            rows[0] = std::max(1, kThreads / ((w + 3) / 4));
+            rows[1] = std::max(1, kThreads / w);
+        }
+    };
+    struct Tile {
+        Columns full, tail;
+        int nfull, stride;
+    } tile[64];
+    for (int c = 0; c < nc; ++c)
+        tile[c] = {Columns(cand[c]), Columns(F % cand[c]), F / cand[c], tile_stride(cand[c], vec == 4)};
+    // the widest candidate each operation can hold in LDS (nc: none, it is cut into row blocks)
+    std::vector<uint8_t> fit(n);
+    for (int i = 0; i < n; ++i) {
+        const int64_t room = kn.lds_words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
+                             (vec == 4 ? 0 : 4);       // (as fits_slot())
+        int c = 0;
+        while (c < nc && (int64_t)o.k[i] * tile[c].stride > room) ++c;
+        fit[i] = (uint8_t)c;
+    }
+    auto long_rows = [&](int i) { return vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 0; };
+    // (exact below 2^31: x + 1/2 over d is at least 1/(2d) away from a whole number)
+    auto pieces_of = [](int m, double inv_chunk, int chunk) { return (int)((m + chunk - 0.5) * inv_chunk); };
+    bool slots = false;
+    auto count = [&](size_t first, int cap, bool small) {
+        if (small && !slots)
+            for (int i = 0; i < n && !slots; ++i)
+                for (int b : {BSPMM_BIN_SLICE16, BSPMM_BIN_SLICE32, BSPMM_BIN_WAVE})
+                    slots = slots || (o.m[i] > 0 &&
+                                      fits_slot(o, i, cand[first], F, vec, bin_slot_lanes(b), kn.max_passes, kn));
+        int chunk[64][2][2];
+        double inv[64][2][2];
+        for (int c = (int)first; c < nc && cap > 0; ++c)
+            for (int l = 0; l < 2; ++l) {
+                chunk[c][0][l] = cap * tile[c].full.rows[l], chunk[c][1][l] = cap * tile[c].tail.rows[l];
+                for (int t = 0; t < 2; ++t) inv[c][t][l] = 1.0 / chunk[c][t][l];
+            }
+        Count t = {0, 0};
+        int64_t k_sum = 0;
+        for (int i = 0; i < n; ++i) {
+            const int m = o.m[i];
+            if (m <= 0) continue;
+            const int c = std::max((int)first, (int)fit[i]);
+            if (c >= nc) {
+                t.wgs += (tile[0].nfull + (tile[0].tail.width > 0)) * ((m + kn.generic_rows - 1) / kn.generic_rows);
+                continue;
+            }
+            const Tile& x = tile[c];
+            if (cap <= 0) {
+                t.wgs += x.nfull + (x.tail.width > 0);
+                k_sum += o.k[i];
+                continue;
+            }
+            const int l = long_rows(i);
+            const int pf = x.nfull * pieces_of(m, inv[c][0][l], chunk[c][0][l]);
+            const int pt = x.tail.width > 0 ? pieces_of(m, inv[c][1][l], chunk[c][1][l]) : 0;
+            t.wgs += pf + pt;
+            t.tile_words += (int64_t)o.k[i] * (pf * x.full.width + pt * x.tail.width);
+        }
+        t.tile_words += k_sum * F;
+        return t;
+    };
+    const Shape shape = search_shape(kn, vec, (size_t)nc, false, count);
+    if (slots) return false;
+
+    // Items that read the same dense tile are a group (rows that are no whole number of 128-byte lines:
+    // all items of a dense block, because column tiles share the lines at their edges - 900 operations
+    // of 1 to 220 rows at F = 127 fetched 122 MB and wrote 60 MB instead of 50 each, and took 34 us
+    // instead of 22, with the tiles of an operation on different XCDs).
+    const std::vector<int> block = input_blocks(o);
+    int blocks = 0;
+    for (int b : block) blocks = std::max(blocks, b + 1);
+    const int unit = F % 32 != 0 ? std::max(4, F) : std::max(4, std::min(cand.back(), F));
+    const int per_block = (F + unit - 1) / unit;
+    const size_t ngroups = (size_t)blocks * per_block;
+    // per (operation, column tile): f(operation, columns, first column, group, rows per item, staged)
+    auto each_tile = [&](auto f) {
+        for (int i = 0; i < n; ++i) {
+            if (o.m[i] <= 0) continue;
+            int c = std::max((int)shape.chosen, (int)fit[i]);
+            const bool staged = c < nc;
+            const Tile& x = tile[staged ? c : 0];
+            const int l = long_rows(i), g = block[i] * per_block;
+            for (int f0 = 0; f0 < F; f0 += x.full.width) {
+                const Columns& y = F - f0 >= x.full.width ? x.full : x.tail;
+                f(i, y, f0, g + f0 / unit,
+                  !staged ? kn.generic_rows : (shape.cap > 0 ? shape.cap * y.rows[l] : o.m[i]), staged);
+            }
+        }
+    };
+    std::vector<int64_t> gcost(ngroups, 0), gtotal(ngroups, 0);
+    std::vector<int32_t> gsize(ngroups, 0);
+    bool all_pow2 = vec == 4;
+    int64_t lds = 0;
+    each_tile([&](int i, const Columns& y, int, int g, int chunk, bool staged) {
+        const int m = o.m[i];
+        const int pieces = chunk >= m ? 1 : (int)((unsigned)(m + chunk - 1) / (unsigned)chunk);
+        // (item_cost(), with the entries' share of a piece as an average over the pieces)
+        const int nrows = std::min(chunk, m);
+        const int64_t dense_in = staged ? o.k[i] : std::min<int64_t>(o.k[i], (int64_t)nrows * 4);
+        const int64_t entries = pieces == 1 ? o.nnz[i] : (unsigned)o.nnz[i] / (unsigned)pieces;
+        const int64_t cost = 4 * (int64_t)y.width * (dense_in + nrows) + 8 * entries + 4 * (int64_t)nrows + 512;
+        gcost[g] = std::max(gcost[g], cost);
+        gtotal[g] += cost * pieces;
+        gsize[g] += pieces;
+        s.count += pieces;
+        s.items_in_bin[staged ? BSPMM_BIN_WORKGROUP : BSPMM_BIN_GENERIC] += pieces;
+        all_pow2 = all_pow2 && y.pow2;
+        if (staged)
+            lds = std::max(lds, any_words(m, o.k[i], o.nnz[i], y.width, vec == 4));
+        else
+            s.row_blocks = true;
+    });
+
+    // groups largest first, each dealt to the XCD with the least cost so far; list x of the eight
+    // occupies workgroups x, x + 8, x + 16, ...
+    std::vector<int32_t> order;
+    largest_first(gcost.data(), (int)ngroups, order);
+    std::vector<int32_t> place(ngroups);              // next workgroup of the group
+    static_assert(kXcds == 8, "the minimum below is a tree over eight loads");
+    uint64_t load[kXcds];                             // cost so far << 3 | list: one minimum, no branches
+    for (int x = 0; x < kXcds; ++x) load[x] = (uint64_t)x;
+    int32_t used[kXcds] = {0};
+    for (int32_t g : order) {
+        if (gsize[g] == 0) continue;
+        const uint64_t a = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
+        const uint64_t b = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
+        const int x = (int)(std::min(a, b) & 7);
+        place[g] = used[x] * kXcds + x;
+        used[x] += gsize[g];
+        load[x] += (uint64_t)gtotal[g] << 3;
+    }
+    const int grid = kXcds * *std::max_element(used, used + kXcds);
+
+    s.compact.assign((size_t)grid, LeanItem());
+    s.item_op.assign((size_t)grid, -1);
+    each_tile([&](int i, const Columns& y, int f0, int g, int chunk, bool staged) {
+        const int m = o.m[i], cv = round_up(m + 1, 2);
+        LeanItem t = {};
+        t.rpt_off = (uint32_t)o.rpt_off[i];
+        t.nz_off = (uint32_t)o.nz_off[i];
+        t.in_row = (uint32_t)o.in_off[i];
+        t.out_row = (uint32_t)o.out_off[i];
+        t.m = m, t.k = o.k[i], t.nnz = o.nnz[i], t.f0 = f0, t.sh = y.sh;
+        t.flags = y.width << 8 | (staged ? (gsize[g] == 1 ? 1 : 0) : 2);
+        if (staged) {
+            t.cv_byte = 4 * cv;
+            t.b_byte = 4 * round_up(cv + 2 * t.nnz, 4);
+            t.tile_vecs = t.k << y.sh;
+        }
+        int at = place[g];
+        for (int r0 = 0; r0 < m; r0 += chunk, at += kXcds) {
+            t.row0 = r0;
+            t.nrows = std::min(chunk, m - r0);
+            s.compact[at] = t;
+            s.item_op[at] = i;
+        }
+        place[g] = at;
+    });
+    s.tile = cand[shape.chosen];
+    s.grid = s.launch_grid = grid;
+    for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;
+    s.whole = grid > 0;
+    s.lean = s.whole && all_pow2;
+    s.lds_words = s.row_blocks ? kn.lds_words : (int)std::min<int64_t>(kn.lds_words, round_up((int)lds, 64));
+    return true;
 }
 
 }  // namespace
@@ -480,6 +758,20 @@ Knobs resolve_knobs(const bspmm_options* o)
     return k;
 }
 
+std::vector<bspmm_item> items_of(const Schedule& s, const std::vector<LeanItem>& compact)
+{
+    if (!s.view.empty()) return s.view;
+    std::vector<bspmm_item> v;
+    v.reserve((size_t)s.count);
+    for (size_t j = 0; j < compact.size(); ++j) {
+        const LeanItem& t = compact[j];
+        if (s.item_op[j] >= 0)
+            v.push_back({s.item_op[j], (t.flags & 2) ? BSPMM_BIN_GENERIC : BSPMM_BIN_WORKGROUP, t.row0, t.nrows, t.f0,
+                         t.flags >> 8, (int32_t)j, 0});
+    }
+    return v;
+}
+
 Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
 {
     Schedule s;
@@ -488,6 +780,10 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     const int vec = (F % 4 == 0) ? 4 : 1;
     const std::vector<int> cand = tile_candidates(F, kn);
     const Groups outs = output_groups(ops_in);
+    s.first_stand_in = ops_in.size();
+    if (kn.front == 0 && kn.force_bin < 0 && !kn.hubs && kn.pad == 0 && kn.persistent_wgs == 0 &&
+        !kn.wide_offsets && outs.size() == (int)outs.member.size() && plain_schedule(ops_in, F, kn, vec, cand, s))
+        return s;
 
     // Sets of summed operations whose dense blocks are one block (the same one, or blocks that
     // lie back to back in the packed input): an operation with the members' matrices side by
@@ -558,12 +854,10 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
 
     // widest batch-wide tile that still gives the launch enough workgroups
     std::vector<Draft> d;
-    size_t chosen = cand.size() - 1;
     // Sub-workgroup slots pack several small items into one workgroup.  Measured on MI355X
     // that only pays when the launch is over-subscribed (more workgroups than the chip holds
     // at once); a launch that fits is latency-bound and every item is fastest with a whole
     // workgroup staging it.  A forced bin overrides this.
-    const int fixed_cap = kn.wg_passes > 0 ? kn.wg_passes : 0;
     bool allow_small = kn.force_bin >= 0 && kn.front == 0;
     size_t most_members = 1;
     for (int g = 0; g < outs.size(); ++g) most_members = std::max<size_t>(most_members, outs.count(g));
@@ -588,65 +882,14 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
         counted_tile_words = counter.tile_words;
         return counter.workgroups();
     };
-    int wgs = 0;
-    // (F % 4 != 0: the widest tile every operation can hold, and row ranges for parallelism - see below)
-    const bool wide_first = vec == 1 && kn.front == 0;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        for (size_t c = 0; c < cand.size(); ++c) {
-            wgs = workgroups_of(c, fixed_cap, allow_small);
-            if (wide_first || wgs >= kn.target_wgs || c + 1 == cand.size()) {
-                chosen = c;
-                break;
-            }
-        }
-        if (allow_small || wgs <= kn.capacity_wgs || kn.front > 0 || wide_first) break;
-        allow_small = true;
-    }
+    const Shape shape = search_shape(kn, vec, cand.size(), allow_small, [&](size_t first, int cap, bool small) {
+        const int w = workgroups_of(first, cap, small);
+        return Count{w, counted_tile_words};
+    });
+    const size_t chosen = shape.chosen;
+    const int cap = shape.cap, wgs = shape.wgs;
+    allow_small = shape.small;
     s.tile = cand[chosen];
-    // still too few workgroups at the narrowest tile: the batch is small, its time is set by
-    // the slowest workgroup, so cut multi-pass workgroup items into row ranges
-    // Likewise while the launch still fits the chip at once: the workgroups with several passes
-    // are its critical path, and cutting them pays as long as no workgroup has to wait for a
-    // free slot and the pieces, each of which copies the whole dense tile again, do not add
-    // more than 60 % to the tile traffic (measured: 256 molecule graphs 4.9 -> 4.3 us, 512
-    // graphs 5.9 -> 4.8 us; cut beyond what the chip holds, 384 graphs go from 4.9 to 5.9 us;
-    // wide tiles of 100-row graphs cut to four rows each, 8.2 -> 9.2 us).
-    int cap = fixed_cap;
-    if (kn.wg_passes == 0 && wide_first) {
-        // Widths off 16 bytes: a tile of whole rows is one run of memory, cheaper to copy several
-        // times (out of L2) than column tiles whose rows start anywhere.  Ranges of at most eight
-        // passes over the lane groups (200 operations of 1 to 220 rows, F = 127: uncut 16.5 us, sixteen
-        // passes 12.3, eight 9.3), shorter until there are two workgroups per CU, but not in launches
-        // bound by bandwidth.
-        const int want = kn.target_given ? kn.target_wgs : 2 * kn.compute_units;
-        for (int c = 8; c >= 1; c /= 2) {
-            wgs = workgroups_of(chosen, c, allow_small);
-            cap = c;
-            if (wgs >= want || counted_tile_words > 3500000) break;
-        }
-    } else if (kn.wg_passes == 0 && kn.front == 0) {
-        const int uncut = wgs;                         // (the tile search ended on this very count)
-        const int64_t uncut_words = counted_tile_words;
-        bool done = false;
-        // (a launch that moves more than about 28 MB is bound by bandwidth, not by its slowest
-        // workgroup: there the extra copies only cost)
-        const bool latency_bound = uncut_words <= 3500000;
-        for (int c = 1; c <= 4 && uncut <= kn.capacity_wgs && latency_bound; c *= 2) {
-            const int w = workgroups_of(chosen, c, allow_small);
-            if (w <= kn.capacity_wgs && 5 * (counted_tile_words - uncut_words) <= 3 * uncut_words) {
-                cap = c;
-                wgs = w;
-                done = true;
-                break;
-            }
-        }
-        if (!done && uncut < kn.target_wgs) {
-            for (cap = 4; cap >= 1; cap /= 2) {
-                wgs = workgroups_of(chosen, cap, allow_small);
-                if (wgs >= kn.target_wgs || cap == 1) break;
-            }
-        }
-    }
     if (!fits) {   // a set of summed operations does not fit LDS together even at 4 columns
         s.error = BSPMM_ETOOBIG;
         return s;
@@ -892,12 +1135,13 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
         s.wg_end[r] = wg;
     }
     s.item_op.resize(s.items.size(), -1);
+    s.count = (int)s.view.size();
     s.grid = wg;
     s.launch_grid = kn.persistent_wgs > 0 ? std::min(wg, W) : wg;
     // Launches made only of whole-workgroup items (staged operations and row blocks of the generic
     // bin) run from the compact item table; the lean kernel serves those on the float4 path whose
     // tile rows are a power-of-two number of float4.
-    s.whole = kn.pad == 0 && !kn.hubs && kn.front == 0 && kn.persistent_wgs == 0 && s.merged_sets.empty() &&
+    s.whole = kn.pad == 0 && !kn.hubs && !kn.wide_offsets && kn.front == 0 && kn.persistent_wgs == 0 && s.merged_sets.empty() &&
               s.wg_end[0] == wg && wg > 0;
     s.lean = s.whole && vec == 4;
     for (const WorkItem& w : s.items) {

@@ -2,6 +2,7 @@
 // dimension, orders the work largest-first and maps it onto workgroups XCD-aware.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -43,6 +44,7 @@ struct Knobs {
     bool symmetric = false;   // A_i == A_i^T promised: the transposed product reads the same CSR
     bool coo_direct = false;  // COO plans: run the direct kernel instead of converting to CSR
     int persistent_wgs = 0;   // > 0: launch only this many workgroups and let them stride
+    bool wide_offsets = false;       // the transposed arrays outgrow the compact table's 32-bit offsets
     bool one_front_launch = false;   // whole layers: never the streaming launch
     bool lds_given = false;   // the caller fixed lds_words
     bool device_ok = false;   // planning may ask the current device (occupancy); false: dry runs
@@ -51,8 +53,11 @@ struct Knobs {
 
 struct Schedule {
     std::vector<WorkItem> items;     // device table, launch order, padded with empty items
-    std::vector<int32_t> item_op;    // operation of every entry of `items` (-1: empty item)
-    std::vector<bspmm_item> view;    // the non-empty items, for inspection
+    std::vector<LeanItem> compact;   // plain batches: the compact table instead of `items` and `view`
+    std::vector<int32_t> item_op;    // operation of every entry of `items` or `compact` (-1: empty item)
+    std::vector<bspmm_item> view;    // the non-empty items, for inspection (see items_of)
+    int count = 0;                   // non-empty items
+    bool row_blocks = false;         // `compact` has row blocks of the generic bin
     int32_t wg_end[kRanges] = {0, 0, 0, 0, 0};
     int32_t item_base[kRanges] = {0, 0, 0, 0, 0};
     int fused_stride = 1;            // item slots per fused task
@@ -85,11 +90,31 @@ struct CooSchedule {
     int lds_words = 0;     // what the launch asks for: the largest item's
 };
 
+// Positions 0 .. n-1, largest value first, equal ones in order.  Compared in 1024 steps of the
+// largest value: the order only steers greedy placement, and one counting pass is a tenth of a
+// comparison sort.
+template <typename T>
+void largest_first(const T* value, int n, std::vector<int32_t>& order)
+{
+    T top = 1;
+    for (int i = 0; i < n; ++i) top = std::max(top, value[i]);
+    int shift = 0;
+    while ((top >> shift) > 1023) ++shift;
+    uint32_t at[1025] = {0};
+    for (int i = 0; i < n; ++i) ++at[1024 - (value[i] >> shift)];
+    for (int v = 1; v <= 1024; ++v) at[v] += at[v - 1];
+    order.resize(n);
+    for (int i = 0; i < n; ++i) order[at[1023 - (value[i] >> shift)]++] = i;
+}
+
 int workgroups_per_cu(int front_features);
 Knobs resolve_knobs(const bspmm_options* o);
 
 // Items of the direct COO kernel for `ops` (rpt_off unused, nz_off = the caller's entry offsets).
 CooSchedule make_coo_schedule(const DirOps& ops, int F, const Knobs& kn);
+
+// The non-empty items of a schedule whose compact table is `compact`.
+std::vector<bspmm_item> items_of(const Schedule& s, const std::vector<LeanItem>& compact);
 
 // Build the single-launch schedule for `ops` at feature width F.
 Schedule make_schedule(const DirOps& ops, int F, const Knobs& kn);

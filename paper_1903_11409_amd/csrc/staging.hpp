@@ -1,0 +1,34 @@
+// Pinned host memory that plan creation writes its tables (and the caller's CSR arrays) into, so that
+// ONE asynchronous copy brings everything to the device and the call returns at once: copies from
+// pageable memory cost 3 to 14 us of host time each and, where the source may be reused, a wait for
+// the stream; one from pinned memory costs about 1 us whatever its size.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <cstddef>
+
+namespace bspmm {
+
+constexpr size_t kStageBlockMax = (size_t)8 << 20;   // larger plans are copied from pageable memory
+constexpr size_t kStagePoolMax = (size_t)32 << 20;   // pinned memory the pool holds at most
+
+// A block of the pool, taken for one copy.  Blocks go back by themselves when the copy has run.
+struct StageBlock {
+    char* ptr = nullptr;
+    void* slot = nullptr;
+};
+
+// A block of at least `bytes` on the current device, or {nullptr} (too large, pool exhausted, no
+// memory): the caller then copies from pageable memory.  Never waits.
+StageBlock stage_take(size_t bytes);
+
+// Enqueue the copy of the block's first `bytes` to `dst` and hand the block back: it is reused only
+// after the copy has run.
+hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream);
+
+// Plans that exist: when the last one goes and none has been made for a second, idle blocks are freed.
+void stage_plan_made();
+void stage_plan_gone();
+
+}  // namespace bspmm

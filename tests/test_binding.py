@@ -8,14 +8,23 @@ from paper_1903_11409_amd import workloads as W
 
 
 @pytest.mark.parametrize("blocks", [[], [(0, 4)], [(4, 3), (0, 4)], [(1, 4)], [(0, 4), (5, 2)], [(0, 4), (4, 0), (4, 1)],
-                                    [(0, 4), (0, 4), (2, 5)], [(7, 2), (0, 3), (3, 3)]])
+                                    [(0, 4), (0, 4), (4, 5)], [(7, 2), (0, 3), (3, 3)]])
 def test_rows_covered_from_the_first_on(blocks):
     off = np.array([b[0] for b in blocks], dtype=np.int64)
     length = np.array([b[1] for b in blocks], dtype=np.int32)
     hit = np.zeros(16, dtype=bool)
     for o, n in blocks:
         hit[o:o + n] = True
-    assert K._rows_from_zero(off, length) == int(np.argmin(hit))
+    zero = np.zeros(len(off), dtype=np.int64)
+    hb = K.HostBatch(length, length, zero, zero, zero, off, off)
+    for flags in (K.DRY_RUN | K.ACCUMULATE, K.DRY_RUN):
+        try:
+            plan = K.bspmm_create(hb, 8, K.make_options(flags=flags))
+        except K.BspmmError as e:       # blocks that overlap without being the same belong to no batch
+            assert e.code == K.EOVERLAP
+            continue
+        assert K.native().covered_rows(plan, False) == K.native().covered_rows(plan, True) == int(np.argmin(hit))
+        K.bspmm_destroy(plan)
 
 
 def test_native_calls_check_their_arguments():
