@@ -609,100 +609,129 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     const Shape shape = search_shape(kn, vec, (size_t)nc, false, count);
     if (slots) return false;
 
-    // Items that read the same dense tile are a group (rows that are no whole number of 128-byte lines:
-    // all items of a dense block, because column tiles share the lines at their edges - 900 operations
-    // of 1 to 220 rows at F = 127 fetched 122 MB and wrote 60 MB instead of 50 each, and took 34 us
-    // instead of 22, with the tiles of an operation on different XCDs).
-    const std::vector<int> block = input_blocks(o);
-    int blocks = 0;
-    for (int b : block) blocks = std::max(blocks, b + 1);
-    const int unit = F % 32 != 0 ? std::max(4, F) : std::max(4, std::min(cand.back(), F));
-    const int per_block = (F + unit - 1) / unit;
-    const size_t ngroups = (size_t)blocks * per_block;
-    // per (operation, column tile): f(operation, columns, first column, group, rows per item, staged)
-    auto each_tile = [&](auto f) {
-        for (int i = 0; i < n; ++i) {
-            if (o.m[i] <= 0) continue;
-            int c = std::max((int)shape.chosen, (int)fit[i]);
-            const bool staged = c < nc;
-            const Tile& x = tile[staged ? c : 0];
-            const int l = long_rows(i), g = block[i] * per_block;
-            for (int f0 = 0; f0 < F; f0 += x.full.width) {
-                const Columns& y = F - f0 >= x.full.width ? x.full : x.tail;
-                f(i, y, f0, g + f0 / unit,
-                  !staged ? kn.generic_rows : (shape.cap > 0 ? shape.cap * y.rows[l] : o.m[i]), staged);
-            }
-        }
+    // A unit is a dense block and the operations that read it; the items of a unit that read the same
+    // dense tile are a group and go to one XCD (rows that are no whole number of 128-byte lines: the
+    // whole unit, because column tiles share the lines at their edges - 900 operations of 1 to 220 rows
+    // at F = 127 fetched 122 MB and wrote 60 MB instead of 50 each, and took 34 us instead of 22, with
+    // the tiles of an operation on different XCDs).
+    const std::vector<int> unit_of = input_blocks(o);
+    int units = 0;
+    bool in_order = true;
+    for (int i = 0; i < n; ++i) {
+        units = std::max(units, unit_of[i] + 1);
+        in_order = in_order && (i == 0 || unit_of[i] >= unit_of[i - 1]);
+    }
+    const int columns = F % 32 != 0 ? std::max(4, F) : std::max(4, std::min(cand.back(), F));   // of a group
+    std::vector<int32_t> first((size_t)units + 1, 0), member(in_order ? 0 : n);   // the operations of every unit
+    for (int i = 0; i < n; ++i) ++first[unit_of[i] + 1];
+    for (int u = 0; u < units; ++u) first[u + 1] += first[u];
+    if (!in_order) {
+        std::vector<int32_t> at(first.begin(), first.end() - 1);
+        for (int i = 0; i < n; ++i) member[at[unit_of[i]]++] = i;
+    }
+    // bytes an item of one row range moves (as item_cost(), the entries spread evenly over the ranges)
+    auto ranges_of = [](int m, int chunk) { return chunk >= m ? 1 : (int)((unsigned)(m + chunk - 1) / (unsigned)chunk); };
+    auto chunk_of = [&](int i, const Columns& y, bool staged) {
+        return !staged ? kn.generic_rows : (shape.cap > 0 ? shape.cap * y.rows[long_rows(i)] : o.m[i]);
     };
-    std::vector<int64_t> gcost(ngroups, 0), gtotal(ngroups, 0);
-    std::vector<int32_t> gsize(ngroups, 0);
-    bool all_pow2 = vec == 4;
-    int64_t lds = 0;
-    each_tile([&](int i, const Columns& y, int, int g, int chunk, bool staged) {
-        const int m = o.m[i];
-        const int pieces = chunk >= m ? 1 : (int)((unsigned)(m + chunk - 1) / (unsigned)chunk);
-        // (item_cost(), with the entries' share of a piece as an average over the pieces)
-        const int nrows = std::min(chunk, m);
+    auto cost_of = [&](int i, const Columns& y, int chunk, int ranges, bool staged) {
+        const int nrows = std::min(chunk, o.m[i]);
         const int64_t dense_in = staged ? o.k[i] : std::min<int64_t>(o.k[i], (int64_t)nrows * 4);
-        const int64_t entries = pieces == 1 ? o.nnz[i] : (unsigned)o.nnz[i] / (unsigned)pieces;
-        const int64_t cost = 4 * (int64_t)y.width * (dense_in + nrows) + 8 * entries + 4 * (int64_t)nrows + 512;
-        gcost[g] = std::max(gcost[g], cost);
-        gtotal[g] += cost * pieces;
-        gsize[g] += pieces;
-        s.count += pieces;
-        s.items_in_bin[staged ? BSPMM_BIN_WORKGROUP : BSPMM_BIN_GENERIC] += pieces;
-        all_pow2 = all_pow2 && y.pow2;
-        if (staged)
-            lds = std::max(lds, any_words(m, o.k[i], o.nnz[i], y.width, vec == 4));
-        else
-            s.row_blocks = true;
-    });
-
-    // groups largest first, each dealt to the XCD with the least cost so far; list x of the eight
-    // occupies workgroups x, x + 8, x + 16, ...
+        const int64_t entries = ranges == 1 ? o.nnz[i] : (unsigned)o.nnz[i] / (unsigned)ranges;
+        return 4 * (int64_t)y.width * (dense_in + nrows) + 8 * entries + 4 * (int64_t)nrows + 512;
+    };
+    auto choice_of = [&](int i) { return std::max((int)shape.chosen, (int)fit[i]); };
+    std::vector<int64_t> cost((size_t)units, 0);
+    for (int i = 0; i < n; ++i) {
+        if (o.m[i] <= 0) continue;
+        const int c = choice_of(i);
+        const bool staged = c < nc;
+        const Columns& y = tile[staged ? c : 0].full;
+        const int chunk = chunk_of(i, y, staged);
+        cost[unit_of[i]] = std::max(cost[unit_of[i]], cost_of(i, y, chunk, ranges_of(o.m[i], chunk), staged));
+    }
     std::vector<int32_t> order;
-    largest_first(gcost.data(), (int)ngroups, order);
-    std::vector<int32_t> place(ngroups);              // next workgroup of the group
+    largest_first(cost.data(), units, order);
+
+    // units largest first, each group dealt to the XCD with the least cost so far; list x of the eight
+    // occupies workgroups x, x + 8, x + 16, ...
     static_assert(kXcds == 8, "the minimum below is a tree over eight loads");
     uint64_t load[kXcds];                             // cost so far << 3 | list: one minimum, no branches
     for (int x = 0; x < kXcds; ++x) load[x] = (uint64_t)x;
     int32_t used[kXcds] = {0};
-    for (int32_t g : order) {
-        if (gsize[g] == 0) continue;
-        const uint64_t a = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
-        const uint64_t b = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
-        const int x = (int)(std::min(a, b) & 7);
-        place[g] = used[x] * kXcds + x;
-        used[x] += gsize[g];
-        load[x] += (uint64_t)gtotal[g] << 3;
+    std::vector<int8_t> list_of((size_t)((F + columns - 1) / columns));           // of the unit's groups, -1: none yet
+    s.compact.resize((size_t)round_up(shape.wgs + shape.wgs / 8 + 64, kXcds));
+    s.item_op.resize(s.compact.size(), -1);
+    bool all_pow2 = vec == 4;
+    int64_t lds = 0;
+    for (int32_t u : order) {
+        std::fill(list_of.begin(), list_of.end(), (int8_t)-1);
+        for (int32_t j = first[u]; j < first[u + 1]; ++j) {
+            const int i = in_order ? j : member[j];
+            const int m = o.m[i];
+            if (m <= 0) continue;
+            const int c = choice_of(i);
+            const bool staged = c < nc;
+            const Tile& x = tile[staged ? c : 0];
+            LeanItem t = {};
+            t.rpt_off = (uint32_t)o.rpt_off[i];
+            t.nz_off = (uint32_t)o.nz_off[i];
+            t.in_row = (uint32_t)o.in_off[i];
+            t.out_row = (uint32_t)o.out_off[i];
+            t.m = m, t.k = o.k[i], t.nnz = o.nnz[i];
+            if (staged) {
+                const int cv = round_up(m + 1, 2);
+                t.cv_byte = 4 * cv;
+                t.b_byte = 4 * round_up(cv + 2 * t.nnz, 4);
+                lds = std::max(lds, any_words(m, t.k, t.nnz, x.nfull > 0 ? x.full.width : x.tail.width, vec == 4));
+            } else {
+                s.row_blocks = true;
+            }
+            const Columns* last = nullptr;
+            int chunk = 0, ranges = 0;
+            uint64_t here = 0;
+            for (int f0 = 0; f0 < F; f0 += x.full.width) {
+                const Columns& y = F - f0 >= x.full.width ? x.full : x.tail;
+                if (&y != last) {
+                    last = &y;
+                    chunk = chunk_of(i, y, staged);
+                    ranges = ranges_of(m, chunk);
+                    here = (uint64_t)cost_of(i, y, chunk, ranges, staged) * (uint64_t)ranges << 3;
+                    all_pow2 = all_pow2 && y.pow2;
+                    t.sh = y.sh;
+                    // bit 0: no other item reads the tile
+                    const bool once = ranges == 1 && first[u + 1] - first[u] == 1 && (F % 32 == 0 || y.width == F);
+                    t.flags = y.width << 8 | (staged ? (once ? 1 : 0) : 2);
+                    t.tile_vecs = staged ? t.k << y.sh : 0;
+                }
+                int8_t& list = list_of[(size_t)(f0 / columns)];
+                if (list < 0) {
+                    const uint64_t a = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
+                    const uint64_t b = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
+                    list = (int8_t)(std::min(a, b) & 7);
+                }
+                load[list] += here;
+                size_t at = (size_t)used[list] * kXcds + (size_t)list;
+                used[list] += ranges;
+                if ((size_t)used[list] * kXcds > s.compact.size()) {
+                    s.compact.resize(2 * (size_t)used[list] * kXcds);
+                    s.item_op.resize(s.compact.size(), -1);
+                }
+                t.f0 = f0;
+                for (int r0 = 0; r0 < m; r0 += chunk, at += kXcds) {
+                    t.row0 = r0;
+                    t.nrows = std::min(chunk, m - r0);
+                    s.compact[at] = t;
+                    s.item_op[at] = i;
+                }
+                s.count += ranges;
+                s.items_in_bin[staged ? BSPMM_BIN_WORKGROUP : BSPMM_BIN_GENERIC] += ranges;
+            }
+        }
     }
     const int grid = kXcds * *std::max_element(used, used + kXcds);
-
-    s.compact.assign((size_t)grid, LeanItem());
-    s.item_op.assign((size_t)grid, -1);
-    each_tile([&](int i, const Columns& y, int f0, int g, int chunk, bool staged) {
-        const int m = o.m[i], cv = round_up(m + 1, 2);
-        LeanItem t = {};
-        t.rpt_off = (uint32_t)o.rpt_off[i];
-        t.nz_off = (uint32_t)o.nz_off[i];
-        t.in_row = (uint32_t)o.in_off[i];
-        t.out_row = (uint32_t)o.out_off[i];
-        t.m = m, t.k = o.k[i], t.nnz = o.nnz[i], t.f0 = f0, t.sh = y.sh;
-        t.flags = y.width << 8 | (staged ? (gsize[g] == 1 ? 1 : 0) : 2);
-        if (staged) {
-            t.cv_byte = 4 * cv;
-            t.b_byte = 4 * round_up(cv + 2 * t.nnz, 4);
-            t.tile_vecs = t.k << y.sh;
-        }
-        int at = place[g];
-        for (int r0 = 0; r0 < m; r0 += chunk, at += kXcds) {
-            t.row0 = r0;
-            t.nrows = std::min(chunk, m - r0);
-            s.compact[at] = t;
-            s.item_op[at] = i;
-        }
-        place[g] = at;
-    });
+    s.compact.resize((size_t)grid);
+    s.item_op.resize((size_t)grid);
     s.tile = cand[shape.chosen];
     s.grid = s.launch_grid = grid;
     for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;
