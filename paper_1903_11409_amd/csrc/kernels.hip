@@ -2857,6 +2857,25 @@ int bspmm_max_resident_workgroups(int lds_bytes, bool slices, bool hubs)
     return per_cu > 0 && cus > 0 ? per_cu * cus : 0;
 }
 
+// Copy from pinned host memory (plan creation, see staging.hpp): every workgroup copies its 16-byte words
+// and then writes `mark` to its word of `done`, also pinned: the host may reuse what it has read.
+// Bound: the round trip over PCIe (160 KB: COPY_US).
+__global__ void __launch_bounds__(kThreads)
+stage_copy_kernel(const uint4* __restrict__ from, uint4* __restrict__ to, uint32_t words, uint32_t* done, uint32_t mark)
+{
+    const uint32_t step = gridDim.x * kThreads;
+    uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    for (; i + step < words; i += 2 * step) {
+        const uint4 a = from[i], b = from[i + step];
+        to[i] = a;
+        to[i + step] = b;
+    }
+    if (i < words) to[i] = from[i];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done + blockIdx.x, mark, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // hipLaunchKernel with its arguments in place: 0.15 us less host time than the <<< >>> form, which
 // pushes and pops the launch configuration around it.
 template <typename... P>
@@ -2909,6 +2928,13 @@ hipError_t kernel_resources(int which, int lds_bytes, int out[7])
     out[5] = per_cu;
     out[6] = cus;
     return hipSuccess;
+}
+
+hipError_t launch_stage_copy(const void* from, void* to, size_t bytes, uint32_t* done, uint32_t mark, int grid,
+                             hipStream_t stream)
+{
+    return launch(stage_copy_kernel, grid, kThreads, 0, stream, static_cast<const uint4*>(from),
+                  static_cast<uint4*>(to), (uint32_t)(bytes / 16), done, mark);
 }
 
 hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec4, bool slices,

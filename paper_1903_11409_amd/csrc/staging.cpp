@@ -1,29 +1,43 @@
 // Pool of pinned staging blocks (see staging.hpp).
 #include "staging.hpp"
 
+#include <algorithm>
 #include <chrono>
+#include <cstdint>
+#include <cstring>
 #include <memory>
 #include <mutex>
 #include <vector>
 
 namespace bspmm {
 
+hipError_t launch_stage_copy(const void* from, void* to, size_t bytes, uint32_t* done, uint32_t mark, int grid,
+                             hipStream_t stream);
+
 namespace {
 
 using Clock = std::chrono::steady_clock;
 
+// In front of a block's data: a word per workgroup of the copy kernel, which writes the copy's mark
+// there when it has read its share (an event instead costs 1 us of host time per plan).
+constexpr size_t kMarks = 64, kHeader = 256;
+
 struct Slot {
-    char* ptr = nullptr;
-    size_t size = 0;
+    char* base = nullptr;
+    size_t size = 0;             // bytes of data
     int device = -1;
-    hipEvent_t done = nullptr;
+    uint32_t mark = 0;           // of the copy under way
+    int grid = 0;                // ... and its workgroups
     enum State { kIdle, kTaken, kCopying } state = kIdle;
+    char* data() const { return base + kHeader; }
+    uint32_t* marks() const { return reinterpret_cast<uint32_t*>(base); }
 };
 
 struct Pool {
     std::mutex lock;
     std::vector<std::unique_ptr<Slot>> slots;
     size_t bytes = 0;
+    size_t next = 0;             // where the search for an idle block begins: the one longest in use
     int64_t plans = 0;
     Clock::time_point last_plan = Clock::now();
 };
@@ -35,8 +49,8 @@ Pool& pool()
     return *p;
 }
 
-// Event queries and pinned allocations are harmless to a stream capture that another thread has open,
-// but count as unsafe there unless the calling thread says so.
+// Allocating and freeing pinned memory is harmless to a stream capture that another thread has open,
+// but counts as unsafe there unless the calling thread says so.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     RelaxedCapture() { swap(); }
@@ -50,19 +64,26 @@ struct RelaxedCapture {
 bool idle(Slot& s)
 {
     if (s.state == Slot::kCopying) {
-        const hipError_t e = hipEventQuery(s.done);
-        if (e == hipSuccess)
-            s.state = Slot::kIdle;
-        else if (e != hipErrorNotReady)
-            (void)hipGetLastError();
+        for (int i = 0; i < s.grid; ++i)
+            if (__atomic_load_n(s.marks() + i, __ATOMIC_ACQUIRE) != s.mark) return false;
+        s.state = Slot::kIdle;
     }
     return s.state == Slot::kIdle;
 }
 
-void free_slot(Slot& s)
+// Idle blocks go, until at most `keep` bytes are held.
+void shrink(Pool& p, size_t keep)
 {
-    if (s.done) (void)hipEventDestroy(s.done);
-    if (s.ptr) (void)hipHostFree(s.ptr);
+    for (size_t i = 0; i < p.slots.size() && p.bytes > keep;) {
+        if (!idle(*p.slots[i])) {
+            ++i;
+            continue;
+        }
+        p.bytes -= p.slots[i]->size;
+        (void)hipHostFree(p.slots[i]->base);
+        p.slots.erase(p.slots.begin() + (ptrdiff_t)i);
+    }
+    p.next = 0;
 }
 
 }  // namespace
@@ -78,58 +99,46 @@ StageBlock stage_take(size_t bytes)
     const RelaxedCapture relaxed;
     Pool& p = pool();
     std::lock_guard<std::mutex> g(p.lock);
-    for (auto& s : p.slots)
-        if (s->device == dev && s->size >= bytes && s->size <= 16 * bytes + ((size_t)1 << 20) && idle(*s)) {
-            s->state = Slot::kTaken;
-            return {s->ptr, s.get()};
+    for (size_t j = 0; j < p.slots.size(); ++j) {
+        const size_t at = (p.next + j) % p.slots.size();
+        Slot& s = *p.slots[at];
+        if (s.device == dev && s.size >= bytes && s.size <= 16 * bytes + ((size_t)1 << 20) && idle(s)) {
+            s.state = Slot::kTaken;
+            p.next = at + 1;
+            return {s.data(), &s};
         }
+    }
     size_t size = (size_t)256 << 10;
     while (size < bytes) size *= 2;
-    // room for it: idle blocks (of other sizes, of other devices) go first
-    for (size_t i = 0; i < p.slots.size() && p.bytes + size > kStagePoolMax;) {
-        if (idle(*p.slots[i])) {
-            p.bytes -= p.slots[i]->size;
-            free_slot(*p.slots[i]);
-            p.slots.erase(p.slots.begin() + (ptrdiff_t)i);
-        } else {
-            ++i;
-        }
-    }
+    if (p.bytes + size > kStagePoolMax) shrink(p, kStagePoolMax - size);
     if (p.bytes + size > kStagePoolMax) return {};
+    void* q = nullptr;
+    if (hipHostMalloc(&q, kHeader + size, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return {};
+    }
     auto s = std::make_unique<Slot>();
+    s->base = static_cast<char*>(q);
     s->device = dev;
     s->size = size;
-    void* q = nullptr;
-    if (hipHostMalloc(&q, size, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return {};
-    }
-    s->ptr = static_cast<char*>(q);
-    if (hipEventCreateWithFlags(&s->done, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        s->done = nullptr;
-        free_slot(*s);
-        return {};
-    }
     s->state = Slot::kTaken;
+    std::memset(s->base, 0, kHeader);
     p.bytes += size;
     p.slots.push_back(std::move(s));
-    return {p.slots.back()->ptr, p.slots.back().get()};
+    return {p.slots.back()->data(), p.slots.back().get()};
 }
 
 hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream)
 {
     Slot& s = *static_cast<Slot*>(b.slot);
-    const bool asked = dst != nullptr && bytes > 0;
-    hipError_t e = asked ? hipMemcpyAsync(dst, b.ptr, bytes, hipMemcpyHostToDevice, stream) : hipSuccess;
-    bool recorded = false;
-    if (asked && e == hipSuccess) {
-        e = hipEventRecord(s.done, stream);
-        recorded = e == hipSuccess;
-        if (!recorded) (void)hipStreamSynchronize(stream);     // (the copy may be in flight: the block is not handed back before it)
-    }
+    // (4 KiB a workgroup: 16 bytes a lane, all of a plan's tables in flight at once)
+    const int grid = (int)std::min<size_t>(kMarks, (bytes + 4095) / 4096);
+    const uint32_t mark = s.mark + 1;
+    const hipError_t e = launch_stage_copy(b.ptr, dst, bytes, s.marks(), mark, grid, stream);
     std::lock_guard<std::mutex> g(pool().lock);
-    s.state = recorded ? Slot::kCopying : Slot::kIdle;
+    s.mark = mark;
+    s.grid = e == hipSuccess ? grid : 0;
+    s.state = Slot::kCopying;
     return e;
 }
 
@@ -147,15 +156,7 @@ void stage_plan_gone()
     std::lock_guard<std::mutex> g(p.lock);
     if (--p.plans > 0 || p.slots.empty() || Clock::now() - p.last_plan < std::chrono::seconds(1)) return;
     const RelaxedCapture relaxed;
-    for (size_t i = 0; i < p.slots.size();) {
-        if (idle(*p.slots[i])) {
-            p.bytes -= p.slots[i]->size;
-            free_slot(*p.slots[i]);
-            p.slots.erase(p.slots.begin() + (ptrdiff_t)i);
-        } else {
-            ++i;
-        }
-    }
+    shrink(p, 0);
 }
 
 }  // namespace bspmm
