@@ -21,7 +21,7 @@
 namespace bspmm {
 hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec4, bool slices,
                         bool hubs, bool merged, hipStream_t stream);
-hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes,
+hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged,
                              hipStream_t stream);
 hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, int grid,
                             int lds_bytes, hipStream_t stream);
@@ -117,7 +117,7 @@ struct bspmm_plan {
     std::vector<OpRecord> records;
     std::vector<int32_t> build_order;      // operations, most entries first: the order the build
                                            // kernels take them in
-    std::vector<LeanItem> lean_items[2];   // per direction: the compact item table of a `whole` schedule
+    ItemTable lean_items[2];            // per direction: the compact item table of a `whole` schedule
     bool lean_shared = false;              // both directions run from the forward table
     int32_t lean_rows[2] = {0, 0};         // most input rows / output rows of an operation: bounds
     int32_t lean_out_rows[2] = {0, 0};     // of the 32-bit offsets the lean kernel forms per call
@@ -676,7 +676,7 @@ void make_stream_plan(bspmm_plan& p)
 void make_lean_items(bspmm_plan& p, int d)
 {
     Schedule& sc = p.sched[d];
-    std::vector<LeanItem>& out = p.lean_items[d];
+    ItemTable& out = p.lean_items[d];
     out.clear();
     p.lean_blocks[d] = false;
     if (!sc.whole) return;
@@ -685,8 +685,11 @@ void make_lean_items(bspmm_plan& p, int d)
         p.lean_blocks[d] = sc.row_blocks;
         return;
     }
-    out.reserve(sc.items.size());
     constexpr int64_t kLimit = (int64_t)1 << 31;
+    if (p.merged_words[d] >= kLimit) {
+        sc.whole = sc.pow2 = false;
+        return;
+    }
     for (const WorkItem& w : sc.items) {
         LeanItem t;
         std::memset(&t, 0, sizeof t);
@@ -694,7 +697,7 @@ void make_lean_items(bspmm_plan& p, int d)
             if (w.rpt_off >= kLimit || w.nz_off >= kLimit || w.in_row_off >= kLimit ||
                 w.out_row_off >= kLimit) {
                 out.clear();
-                sc.whole = sc.lean = false;
+                sc.whole = sc.pow2 = false;
                 return;
             }
             int sh = 0;
@@ -708,7 +711,7 @@ void make_lean_items(bspmm_plan& p, int d)
             t.flags = w.fw << 8;
             if (w.staged & 1) {
                 const StagedLayout L = staged_layout(w.m, w.k, w.nnz, w.fw, 0, false);
-                t.flags |= (w.staged & 2) ? 1 : 0;
+                t.flags |= ((w.staged & 2) ? 1 : 0) | ((w.staged & 4) ? 4 : 0);
                 t.cv_byte = 4 * L.cv_off;
                 t.b_byte = 4 * L.b_off;
                 t.tile_vecs = w.k << sh;
@@ -828,7 +831,8 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
     bool same_shape = kn.front == 0;
     for (int i = 0; i < n && same_shape; ++i)
         same_shape = b->rows[i] == b->cols[i] && b->b_row_off[i] == b->c_row_off[i];
-    make_lean_items(p, 0);
+    const bool plain = !p.sched[0].compact.empty();
+    if (plain) make_lean_items(p, 0);
     p.lean_shared = false;
     if (p.transposed_supported && same_shape) {
         p.sched[1] = p.sched[0];
@@ -839,7 +843,7 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
             st.items[j].rpt_off = t.rpt_off[op];
             st.items[j].nz_off = t.nz_off[op];
         }
-        if (st.whole) {
+        if (plain) {
             // (the same items again: only the CSR arrays are elsewhere - or not even those, when the
             // caller's are packed in operation order; row blocks carry entry ranges of their own)
             p.lean_shared = same_place && !p.lean_blocks[0];
@@ -863,8 +867,10 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
             p.sched[1] = Schedule();
             p.transposed_supported = false;
         }
-        make_lean_items(p, 1);
     }
+    for (int d = 0; d < 2; ++d) describe_sets(p, d);
+    if (!plain) make_lean_items(p, 0);
+    if (!plain || !same_shape) make_lean_items(p, 1);
 
     // compulsory traffic: CSR once, every distinct dense input block once, every output once
     int64_t csr_f = 0, csr_t = 0, out_f = 0, out_t = 0, in_f = 0, in_t = 0, nnz = 0;
@@ -901,7 +907,6 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
     p.effective_bytes[1] = csr_t + in_t + out_t;
     p.flops = 2 * nnz * F;
 
-    for (int d = 0; d < 2; ++d) describe_sets(p, d);
     make_stream_plan(p);
     largest_first(b->nnz, n, p.build_order);
 
@@ -1223,12 +1228,12 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     // the lean kernel forms 32-bit byte offsets inside an operation's dense blocks and multiplies
     // in 24 bits: leading dimensions below 4 Mi floats, blocks below 4 GiB
     constexpr int64_t kMul24 = (int64_t)1 << 22, kOff32 = (int64_t)1 << 30;
-    const bool lean = sc.lean && vec4 && ld_in < kMul24 && ld_out < kMul24 &&
+    const bool lean = sc.pow2 && vec4 && ld_in < kMul24 && ld_out < kMul24 &&
                       (int64_t)p->lean_rows[d] * ld_in < kOff32 &&
                       (int64_t)p->lean_out_rows[d] * ld_out < kOff32;
     hipError_t e;
     if (lean) {
-        e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, s);
+        e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, !sc.merged_sets.empty(), s);
     } else {
         e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, sc.launch_grid, sc.lds_words * 4, s);
     }
@@ -1981,7 +1986,7 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
     }
     info->transposed_supported = plan->transposed_supported ? 1 : 0;
     info->transposed_built = plan->transposed_built ? 1 : 0;
-    for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].lean ? 1 : 0;
+    for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].pow2 && plan->sched[d].merged_sets.empty() ? 1 : 0;
     if (plan->stream.on()) {
         info->front_stream[0] = plan->stream.graphs;
         info->front_stream[1] = plan->stream.lists * plan->stream.tiles;

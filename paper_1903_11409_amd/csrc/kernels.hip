@@ -1201,7 +1201,7 @@ __global__ void __launch_bounds__(kThreads)
 bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                  const int32_t* __restrict__ colids, const float* __restrict__ values,
                  const float* __restrict__ in, float* __restrict__ out, int64_t ld_in, int64_t ld_out,
-                 uint32_t lds_words, int mode)
+                 uint32_t lds_words, int mode, const int32_t* __restrict__ merged)
 {
     extern __shared__ __align__(16) int sm[];
     const uint32_t tid = threadIdx.x;
@@ -1267,9 +1267,10 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     }
 
     // ---- CSR (as bspmm_lean_kernel; the first four entries of a lane in one round trip)
-    const int32_t* __restrict__ rp = rpt + it.rpt_off;
-    const int32_t* __restrict__ ci = colids + it.nz_off;
-    const float* __restrict__ va = values + it.nz_off;
+    const bool summed = (it.flags & 4) != 0;
+    const int32_t* __restrict__ rp = (summed ? merged : rpt) + it.rpt_off;
+    const int32_t* __restrict__ ci = (summed ? merged : colids) + it.nz_off;
+    const float* __restrict__ va = summed ? reinterpret_cast<const float*>(ci + round_up(nnz, 4)) : values + it.nz_off;
     const uint32_t ri = min(tid, (uint32_t)m);
     const int rv = rp[ri];
     int c[4] = {0, 0, 0, 0};
@@ -1332,11 +1333,15 @@ __global__ void lean_hints_kernel(LeanItem* items, int n, const int32_t* __restr
     it.count = max(b - a, 0);
 }
 
+// MERGED: items with flag bit 2 read their CSR from the merged arrays of summed sets (a template
+// parameter: the selects cost the plain kernel).  512 graphs of four channels with dense blocks of their
+// own, F = 128, summed: MERGED_LEAN us through the general kernel.
+template <bool MERGED>
 __global__ void __launch_bounds__(kThreads)
 bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                   const int32_t* __restrict__ colids, const float* __restrict__ values,
                   const float* __restrict__ in, float* __restrict__ out, uint32_t ld_in,
-                  uint32_t ld_out, uint32_t lds_words)
+                  uint32_t ld_out, uint32_t lds_words, const int32_t* __restrict__ merged)
 {
     extern __shared__ __align__(16) int sm[];
     const uint32_t tid = threadIdx.x;
@@ -1388,9 +1393,10 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     // ---- CSR: the row pointers of this lane group's first row (they stay in registers), all
     // row pointers and the entries (on their way to LDS).  Indices are clamped instead of
     // predicated: a lane past the end reads, and later writes, what the last lane does.
-    const int32_t* __restrict__ rp = rpt + it.rpt_off;
-    const int32_t* __restrict__ ci = colids + it.nz_off;
-    const float* __restrict__ va = values + it.nz_off;
+    const bool summed = MERGED && (it.flags & 4) != 0;
+    const int32_t* __restrict__ rp = (summed ? merged : rpt) + it.rpt_off;
+    const int32_t* __restrict__ ci = (summed ? merged : colids) + it.nz_off;
+    const float* __restrict__ va = summed ? reinterpret_cast<const float*>(ci + round_up(nnz, 4)) : values + it.nz_off;
     const uint32_t r_first = (uint32_t)it.row0 + (tid >> sh);
     const uint32_t um = (uint32_t)m;
     const int q0 = rp[min(r_first, um)];
@@ -2898,7 +2904,7 @@ hipError_t kernel_resources(int which, int lds_bytes, int out[7])
     const void* fn = nullptr;
     int threads = kThreads;
     switch (which) {
-        case 0: fn = reinterpret_cast<const void*>(&bspmm_lean_kernel); break;
+        case 0: fn = reinterpret_cast<const void*>(&bspmm_lean_kernel<false>); break;
         case 1: fn = reinterpret_cast<const void*>(&bspmm_kernel<4, false, false, false>); break;
         case 2: fn = reinterpret_cast<const void*>(&bspmm_kernel<1, false, false, false>); break;
         case 3: fn = reinterpret_cast<const void*>(&bspmm_gcn_kernel<false, false>); break;
@@ -2944,12 +2950,13 @@ hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec
     return launch(kernel_variant(vec4, slices, hubs, merged), grid, kThreads, lds_bytes, stream, P);
 }
 
-hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes,
+hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged,
                              hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
-    return launch(bspmm_lean_kernel, grid, kThreads, lds_bytes, stream, items, P.rpt, P.colids, P.values, P.in, P.out,
-                  (uint32_t)P.ld_in, (uint32_t)P.ld_out, (uint32_t)(lds_bytes / 4));
+    return launch(merged ? bspmm_lean_kernel<true> : bspmm_lean_kernel<false>, grid, kThreads, lds_bytes, stream, items,
+                  P.rpt, P.colids, P.values, P.in, P.out, (uint32_t)P.ld_in, (uint32_t)P.ld_out,
+                  (uint32_t)(lds_bytes / 4), reinterpret_cast<const int32_t*>(P.w));
 }
 
 // aligned: F % 4 == 0 and every row of every tile is float4 on 16 bytes; quads: F % 4 == 0 (the schedule
@@ -2961,7 +2968,7 @@ hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool a
     const bool windows = (reinterpret_cast<uintptr_t>(P.in) & 15) == 0 && (!quads || P.ld_in % 4 == 0);
     return launch(aligned ? bspmm_any_kernel<true> : bspmm_any_kernel<false>, grid, kThreads, lds_bytes, stream, items,
                   P.rpt, P.colids, P.values, P.in, P.out, P.ld_in, P.ld_out, (uint32_t)(lds_bytes / 4),
-                  (windows ? kAnyWindows : 0) | (quads ? kAnyTight : 0));
+                  (windows ? kAnyWindows : 0) | (quads ? kAnyTight : 0), reinterpret_cast<const int32_t*>(P.w));
 }
 
 hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream)

@@ -68,7 +68,9 @@ struct alignas(16) LeanItem {
     int32_t f0;           // first feature column
     int32_t sh;           // lean kernel: log2 of the float4 per tile row (tile width = 4 << sh floats)
     int32_t flags;        // bit 0: no other item reads this dense tile; bit 1: row block of the
-                          // generic bin; bits 8 and up: tile width in floats
+                          // generic bin; bit 2: the item stands in for a set of summed
+                          // operations, its CSR is the set's merged one (columns and values at
+                          // nz_off); bits 8 and up: tile width in floats
     int32_t cv_byte;      // staged: LDS byte offset of the (row offset, value) pairs
     int32_t b_byte;       // staged: LDS byte offset of the dense tile
     int32_t tile_vecs;    // staged: float4 in the tile, k << sh (lean kernel)

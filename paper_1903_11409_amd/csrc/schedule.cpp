@@ -653,19 +653,21 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     std::vector<int32_t> order;
     largest_first(cost.data(), units, order);
 
-    // units largest first, each group dealt to the XCD with the least cost so far; list x of the eight
-    // occupies workgroups x, x + 8, x + 16, ...
+    // units largest first: the groups of a unit go to neighbouring XCDs, from the one with the least
+    // cost so far on (halves or quarters of the eight where the groups are four or two: the loads of a
+    // half stay level); list x of the eight occupies workgroups x, x + 8, x + 16, ...
     static_assert(kXcds == 8, "the minimum below is a tree over eight loads");
     uint64_t load[kXcds];                             // cost so far << 3 | list: one minimum, no branches
     for (int x = 0; x < kXcds; ++x) load[x] = (uint64_t)x;
     int32_t used[kXcds] = {0};
-    std::vector<int8_t> list_of((size_t)((F + columns - 1) / columns));           // of the unit's groups, -1: none yet
     s.compact.resize((size_t)round_up(shape.wgs + shape.wgs / 8 + 64, kXcds));
-    s.item_op.resize(s.compact.size(), -1);
+    s.item_op.assign(s.compact.size(), -1);
     bool all_pow2 = vec == 4;
     int64_t lds = 0;
     for (int32_t u : order) {
-        std::fill(list_of.begin(), list_of.end(), (int8_t)-1);
+        const uint64_t la = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
+        const uint64_t lb = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
+        const int start = (int)(std::min(la, lb) & 7);
         for (int32_t j = first[u]; j < first[u + 1]; ++j) {
             const int i = in_order ? j : member[j];
             const int m = o.m[i];
@@ -687,10 +689,14 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             } else {
                 s.row_blocks = true;
             }
+            const int groups = columns >= F ? 1 : x.nfull + (x.tail.width > 0);   // of this operation
+            const int base = groups == 4 || groups == 2 ? start & ~(groups - 1) : start;
+            const int next = columns >= F ? 0 : 1;
+            int group = 0;
             const Columns* last = nullptr;
             int chunk = 0, ranges = 0;
             uint64_t here = 0;
-            for (int f0 = 0; f0 < F; f0 += x.full.width) {
+            for (int f0 = 0; f0 < F; f0 += x.full.width, group += next) {
                 const Columns& y = F - f0 >= x.full.width ? x.full : x.tail;
                 if (&y != last) {
                     last = &y;
@@ -704,12 +710,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
                     t.flags = y.width << 8 | (staged ? (once ? 1 : 0) : 2);
                     t.tile_vecs = staged ? t.k << y.sh : 0;
                 }
-                int8_t& list = list_of[(size_t)(f0 / columns)];
-                if (list < 0) {
-                    const uint64_t a = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
-                    const uint64_t b = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
-                    list = (int8_t)(std::min(a, b) & 7);
-                }
+                const int list = (base + group) & 7;
                 load[list] += here;
                 size_t at = (size_t)used[list] * kXcds + (size_t)list;
                 used[list] += ranges;
@@ -732,11 +733,13 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     const int grid = kXcds * *std::max_element(used, used + kXcds);
     s.compact.resize((size_t)grid);
     s.item_op.resize((size_t)grid);
+    for (int x = 0; x < kXcds; ++x)                   // the ends of the shorter lists: empty items
+        for (int at = used[x] * kXcds + x; at < grid; at += kXcds) s.compact[at] = LeanItem();
     s.tile = cand[shape.chosen];
     s.grid = s.launch_grid = grid;
     for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;
     s.whole = grid > 0;
-    s.lean = s.whole && all_pow2;
+    s.pow2 = s.whole && all_pow2;
     s.lds_words = s.row_blocks ? kn.lds_words : (int)std::min<int64_t>(kn.lds_words, round_up((int)lds, 64));
     return true;
 }
@@ -787,7 +790,7 @@ Knobs resolve_knobs(const bspmm_options* o)
     return k;
 }
 
-std::vector<bspmm_item> items_of(const Schedule& s, const std::vector<LeanItem>& compact)
+std::vector<bspmm_item> items_of(const Schedule& s, const ItemTable& compact)
 {
     if (!s.view.empty()) return s.view;
     std::vector<bspmm_item> v;
@@ -1170,14 +1173,14 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     // Launches made only of whole-workgroup items (staged operations and row blocks of the generic
     // bin) run from the compact item table; the lean kernel serves those on the float4 path whose
     // tile rows are a power-of-two number of float4.
-    s.whole = kn.pad == 0 && !kn.hubs && !kn.wide_offsets && kn.front == 0 && kn.persistent_wgs == 0 && s.merged_sets.empty() &&
+    s.whole = kn.pad == 0 && !kn.hubs && !kn.wide_offsets && kn.front == 0 && kn.persistent_wgs == 0 &&
               s.wg_end[0] == wg && wg > 0;
-    s.lean = s.whole && vec == 4;
+    s.pow2 = s.whole && vec == 4;
     for (const WorkItem& w : s.items) {
-        if (!s.lean) break;
+        if (!s.pow2) break;
         if (w.nrows <= 0) continue;
         const int nvec = w.fw >> 2;
-        s.lean = (w.fw & 3) == 0 && nvec > 0 && (nvec & (nvec - 1)) == 0 && nvec <= 64;
+        s.pow2 = (w.fw & 3) == 0 && nvec > 0 && (nvec & (nvec - 1)) == 0 && nvec <= 64;
     }
     if (s.whole) {   // what the launch asks for: its largest item's LDS (row blocks: the whole budget)
         int64_t most = 0;

@@ -4,6 +4,9 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstring>
+#include <memory>
+#include <utility>
 #include <vector>
 
 #include "../../include/bspmm.h"
@@ -51,9 +54,62 @@ struct Knobs {
     bool need_both = false;   // planning: a transposed product that does not fit is an error too
 };
 
+// An item table whose memory is not cleared before it is written.
+class ItemTable {
+public:
+    ItemTable() = default;
+    ItemTable(ItemTable&& o) noexcept : p_(std::move(o.p_)), n_(o.n_), room_(o.room_) { o.n_ = o.room_ = 0; }
+    ItemTable(const ItemTable& o) { *this = o; }
+    ItemTable& operator=(ItemTable&& o) noexcept
+    {
+        p_ = std::move(o.p_);
+        n_ = o.n_, room_ = o.room_;
+        o.n_ = o.room_ = 0;
+        return *this;
+    }
+    ItemTable& operator=(const ItemTable& o)
+    {
+        if (this == &o) return *this;
+        n_ = 0;
+        resize(o.n_);
+        if (n_) std::memcpy(p_.get(), o.p_.get(), n_ * sizeof(LeanItem));
+        return *this;
+    }
+    void resize(size_t n)      // keeps what is there, clears nothing
+    {
+        if (n > room_) {
+            std::unique_ptr<LeanItem[]> q(new LeanItem[n]);
+            if (n_) std::memcpy(q.get(), p_.get(), n_ * sizeof(LeanItem));
+            p_ = std::move(q);
+            room_ = n;
+        }
+        n_ = n;
+    }
+    void push_back(const LeanItem& t)
+    {
+        if (n_ == room_) {
+            const size_t n = n_;
+            resize(2 * n + 64);
+            n_ = n;
+        }
+        p_[n_++] = t;
+    }
+    void clear() { n_ = 0; }
+    bool empty() const { return n_ == 0; }
+    size_t size() const { return n_; }
+    LeanItem* data() const { return p_.get(); }
+    LeanItem& operator[](size_t i) const { return p_[i]; }
+    LeanItem* begin() const { return p_.get(); }
+    LeanItem* end() const { return p_.get() + n_; }
+
+private:
+    std::unique_ptr<LeanItem[]> p_;
+    size_t n_ = 0, room_ = 0;
+};
+
 struct Schedule {
     std::vector<WorkItem> items;     // device table, launch order, padded with empty items
-    std::vector<LeanItem> compact;   // plain batches: the compact table instead of `items` and `view`
+    ItemTable compact;               // plain batches: the compact table instead of `items` and `view`
     std::vector<int32_t> item_op;    // operation of every entry of `items` or `compact` (-1: empty item)
     std::vector<bspmm_item> view;    // the non-empty items, for inspection (see items_of)
     int count = 0;                   // non-empty items
@@ -72,7 +128,7 @@ struct Schedule {
     int launch_grid = 0;             // workgroups of the persistent launch
     bool whole = false;              // every task is one whole-workgroup item: the launch runs from
                                      // the compact item table (lean kernel, bspmm_any_kernel)
-    bool lean = false;               // ... on the float4 path with power-of-two tiles: it may take the
+    bool pow2 = false;               // ... on the float4 path with power-of-two tiles: it may take the
                                      // lean kernel
     bool has_slices = false;         // any 32- or 16-lane item: needs the larger kernel variant
     int tile = 0;
@@ -114,7 +170,7 @@ Knobs resolve_knobs(const bspmm_options* o);
 CooSchedule make_coo_schedule(const DirOps& ops, int F, const Knobs& kn);
 
 // The non-empty items of a schedule whose compact table is `compact`.
-std::vector<bspmm_item> items_of(const Schedule& s, const std::vector<LeanItem>& compact);
+std::vector<bspmm_item> items_of(const Schedule& s, const ItemTable& compact);
 
 // Build the single-launch schedule for `ops` at feature width F.
 Schedule make_schedule(const DirOps& ops, int F, const Knobs& kn);
