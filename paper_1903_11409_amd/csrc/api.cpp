@@ -1039,7 +1039,7 @@ int plan_with_budget(bspmm_plan& p, const Batch* b, int32_t F, const bspmm_optio
     kn.need_both = open && !front;
     int rc = plan_fn(p, b, F, kn);
     if (rc == BSPMM_OK && open && !front && !p.coo_direct && F >= 512 && p.effective_bytes[0] > 28000000 &&
-        p.sched[0].grid > kn.capacity_wgs) {
+        p.sched[0].uncut_wgs > kn.capacity_wgs) {
         // Wide feature matrices moved by a launch of more than one round of workgroups, which
         // runs at the rate of the memory system: with 24 KiB the larger operations get tiles of
         // 32 columns (row segments of 128 bytes), each staging the operation's CSR again.  A
@@ -1057,7 +1057,7 @@ int plan_with_budget(bspmm_plan& p, const Batch* b, int32_t F, const bspmm_optio
         wide.lds_given = false;
         bspmm_plan q;
         if (plan_fn(q, b, F, wide) == BSPMM_OK &&
-            10 * (int64_t)q.sched[0].grid * kn.capacity_wgs <= 11 * (int64_t)p.sched[0].grid * wide.capacity_wgs)
+            10 * (int64_t)q.sched[0].grid * kn.capacity_wgs <= 11 * (int64_t)p.sched[0].uncut_wgs * wide.capacity_wgs)
             p = std::move(q);
         return BSPMM_OK;
     }
@@ -1235,7 +1235,9 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     if (lean) {
         e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, !sc.merged_sets.empty(), s);
     } else {
-        e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, sc.launch_grid, sc.lds_words * 4, s);
+        // (the table's packed items follow the launch's own: here each is a workgroup)
+        const int grid = (int)p->lean_items[p->lean_shared ? 0 : d].size();
+        e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, grid, sc.lds_words * 4, s);
     }
     return e == hipSuccess ? BSPMM_OK : hip_fail(e);
 }

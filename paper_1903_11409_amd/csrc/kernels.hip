@@ -1206,6 +1206,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     extern __shared__ __align__(16) int sm[];
     const uint32_t tid = threadIdx.x;
     const LeanItem it = items[blockIdx.x];
+    if (it.flags & 8) return;  // (small items packed for the lean kernel: this launch has a workgroup for each)
     if (it.flags & 2) {        // (the same for the whole workgroup)
         any_row_block<ALIGNED>(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         return;
@@ -1333,6 +1334,67 @@ __global__ void lean_hints_kernel(LeanItem* items, int n, const int32_t* __restr
     it.count = max(b - a, 0);
 }
 
+// A small operation on one wavefront of a lean launch (four of them share a workgroup, see plain_schedule):
+// the staged path of bspmm_lean_kernel with 64 lanes and its own quarter of the LDS; the wavefront waits for
+// itself only.
+__device__ __forceinline__ void lean_wave_item(const LeanItem& it, char* lds, const int32_t* __restrict__ rpt,
+                                               const int32_t* __restrict__ colids, const float* __restrict__ values,
+                                               const float* __restrict__ in, float* __restrict__ out, uint32_t ld_in,
+                                               uint32_t ld_out)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const int m = it.m, k = it.k, nnz = it.nnz, sh = it.sh;
+    const uint32_t nvec = 1u << sh;
+    int* sm = reinterpret_cast<int*>(lds);
+    {
+        const char* __restrict__ src =
+            reinterpret_cast<const char*>(in + ((uint64_t)it.in_row * ld_in + (uint32_t)it.f0));
+        const uint32_t row_bytes = ld_in << 2, total = (uint32_t)it.tile_vecs;
+        char* bs = lds + it.b_byte;
+        for (uint32_t e0 = 0; e0 < total; e0 += 64) {
+            const uint32_t e = e0 + lane;
+            if (e < total)
+                __builtin_amdgcn_global_load_lds(
+                    (const void __attribute__((address_space(1)))*)(
+                        src + (__umul24(e >> sh, row_bytes) + ((e & (nvec - 1)) << 4))),
+                    (void __attribute__((address_space(3)))*)(bs + (e0 << 4)), 16, 0, 0);
+        }
+    }
+    const int32_t* __restrict__ rp = rpt + it.rpt_off;
+    const int32_t* __restrict__ ci = colids + it.nz_off;
+    const float* __restrict__ va = values + it.nz_off;
+    const uint32_t ri = min(lane, (uint32_t)m), last = (uint32_t)max(nnz - 1, 0);
+    const int rv = rp[ri];
+    int c[2] = {0, 0};
+    float a[2] = {0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (nnz > u * 64) {
+            c[u] = ci[min(lane + u * 64, last)];
+            a[u] = va[min(lane + u * 64, last)];
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    const int lsh = sh + 4;
+    int2* cv = reinterpret_cast<int2*>(lds + it.cv_byte);
+    auto entry = [&](int col, float v) { return make_int2((unsigned)col < (unsigned)k ? col << lsh : 0, __float_as_int(v)); };
+    sm[ri] = min(max(rv, 0), nnz);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (nnz > u * 64) cv[min(lane + u * 64, last)] = entry(c[u], a[u]);
+    for (int i = lane + 64; i <= m; i += 64) sm[i] = min(max(rp[i], 0), nnz);
+    for (int p = lane + 128; p < nnz; p += 64) cv[p] = entry(ci[p], va[p]);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+
+    const uint32_t l = lane & (nvec - 1);
+    const char* bcol = lds + it.b_byte + (l << 4);
+    char* __restrict__ dst = reinterpret_cast<char*>(out + ((uint64_t)it.out_row * ld_out + (uint32_t)it.f0));
+    const uint32_t out_row_bytes = ld_out << 2;
+    for (uint32_t r = lane >> sh; r < (uint32_t)m; r += 64u >> sh)
+        store_out<4>(reinterpret_cast<float*>(dst + (__umul24(r, out_row_bytes) + (l << 4))),
+                     gather_row(cv, bcol, sm[r], sm[r + 1]));
+}
+
 // MERGED: items with flag bit 2 read their CSR from the merged arrays of summed sets (a template
 // parameter: the selects cost the plain kernel).  512 graphs of four channels with dense blocks of their
 // own, F = 128, summed: MERGED_LEAN us through the general kernel.
@@ -1351,8 +1413,17 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     // as well, not after the barrier where they are first used.
     const LeanItem it = items[blockIdx.x];
     asm volatile("" ::"s"(out), "s"(ld_out));
-    if (it.flags & 2) {        // (the same for the whole workgroup)
-        lean_row_block(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+    if (it.flags & 10) {       // (the same for the whole workgroup)
+        if (it.flags & 2) {
+            lean_row_block(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+        } else {
+            const int w = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
+            if (w < it.count) {
+                const LeanItem small = items[it.tile_vecs + w];
+                lean_wave_item(small, reinterpret_cast<char*>(sm) + w * ((lds_words / kWaves) & ~3u) * 4, rpt, colids,
+                               values, in, out, ld_in, ld_out);
+            }
+        }
         return;
     }
     const int m = it.m, k = it.k, nnz = it.nnz;

@@ -13,6 +13,7 @@
 namespace bspmm {
 
 constexpr int kThreads = 256;      // lanes per workgroup (4 wavefronts of 64)
+constexpr int kWaves = kThreads / 64;
 constexpr int kRanges = 5;         // launch ranges: 256 lanes, fused 256, then 64, 32, 16 lanes
 constexpr int kMaxMembers = 8;     // operations one fused task may add up
 constexpr int kMaxLdsBytes = 160 * 1024;    // LDS one workgroup can have on gfx950 (the whole CU's)
@@ -70,7 +71,8 @@ struct alignas(16) LeanItem {
     int32_t flags;        // bit 0: no other item reads this dense tile; bit 1: row block of the
                           // generic bin; bit 2: the item stands in for a set of summed
                           // operations, its CSR is the set's merged one (columns and values at
-                          // nz_off); bits 8 and up: tile width in floats
+                          // nz_off); bit 3: `count` small items, one per wavefront, at index
+                          // `tile_vecs` of the table; bits 8 and up: tile width in floats
     int32_t cv_byte;      // staged: LDS byte offset of the (row offset, value) pairs
     int32_t b_byte;       // staged: LDS byte offset of the dense tile
     int32_t tile_vecs;    // staged: float4 in the tile, k << sh (lean kernel)

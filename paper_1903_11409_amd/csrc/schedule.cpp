@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <initializer_list>
 #include <map>
 #include <numeric>
 #include <utility>
@@ -413,10 +414,10 @@ void draft_all(const DirOps& o, int F, int vec, const std::vector<int>& cand, si
     }
 }
 
-// The search over batch-wide tiles and row cuts.  count(first, cap, small) says how many workgroups
-// the launch would get with candidate tiles from `first` on, workgroup items cut into row ranges of
-// `cap` passes (0: not cut) and, with `small`, sub-workgroup slots, and how many dense-tile words its
-// staged items would copy.
+// The search over batch-wide tiles and row cuts (plain batches without a caller's knobs have a rule
+// of their own: plain_shape).  count(first, cap) says how many workgroups the launch would get with
+// candidate tiles from `first` on and workgroup items cut into row ranges of `cap` passes (0: not cut),
+// and how many dense-tile words its staged items would copy.
 struct Count {
     int wgs;
     int64_t tile_words;
@@ -424,28 +425,23 @@ struct Count {
 struct Shape {
     size_t chosen;
     int cap, wgs;
-    bool small;
 };
 
 template <typename CountFn>
-Shape search_shape(const Knobs& kn, int vec, size_t candidates, bool allow_small, CountFn count)
+Shape search_shape(const Knobs& kn, int vec, size_t candidates, CountFn count)
 {
-    Shape s = {candidates - 1, kn.wg_passes > 0 ? kn.wg_passes : 0, 0, allow_small};
+    Shape s = {candidates - 1, kn.wg_passes > 0 ? kn.wg_passes : 0, 0};
     // (F % 4 != 0: the widest tile every operation can hold, and row ranges for parallelism - see below)
     const bool wide_first = vec == 1 && kn.front == 0;
     int64_t tile_words = 0;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        for (size_t c = 0; c < candidates; ++c) {
-            const Count n = count(c, s.cap, s.small);
-            s.wgs = n.wgs;
-            tile_words = n.tile_words;
-            if (wide_first || s.wgs >= kn.target_wgs || c + 1 == candidates) {
-                s.chosen = c;
-                break;
-            }
+    for (size_t c = 0; c < candidates; ++c) {
+        const Count n = count(c, s.cap);
+        s.wgs = n.wgs;
+        tile_words = n.tile_words;
+        if (wide_first || s.wgs >= kn.target_wgs || c + 1 == candidates) {
+            s.chosen = c;
+            break;
         }
-        if (s.small || s.wgs <= kn.capacity_wgs || kn.front > 0 || wide_first) break;
-        s.small = true;
     }
     if (kn.wg_passes != 0 || kn.front != 0) return s;
     if (wide_first) {
@@ -456,7 +452,7 @@ Shape search_shape(const Knobs& kn, int vec, size_t candidates, bool allow_small
         // bound by bandwidth.
         const int want = kn.target_given ? kn.target_wgs : 2 * kn.compute_units;
         for (int c = 8; c >= 1; c /= 2) {
-            const Count n = count(s.chosen, c, s.small);
+            const Count n = count(s.chosen, c);
             s.wgs = n.wgs;
             s.cap = c;
             if (n.wgs >= want || n.tile_words > 3500000) break;
@@ -477,7 +473,7 @@ Shape search_shape(const Knobs& kn, int vec, size_t candidates, bool allow_small
     // workgroup: there the extra copies only cost)
     const bool latency_bound = uncut_words <= 3500000;
     for (int c = 1; c <= 4 && uncut <= kn.capacity_wgs && latency_bound; c *= 2) {
-        const Count n = count(s.chosen, c, s.small);
+        const Count n = count(s.chosen, c);
         if (n.wgs <= kn.capacity_wgs && 5 * (n.tile_words - uncut_words) <= 3 * uncut_words) {
             s.cap = c;
             s.wgs = n.wgs;
@@ -486,7 +482,7 @@ Shape search_shape(const Knobs& kn, int vec, size_t candidates, bool allow_small
     }
     if (uncut < kn.target_wgs)
         for (s.cap = 4; s.cap >= 1; s.cap /= 2) {
-            s.wgs = count(s.chosen, s.cap, s.small).wgs;
+            s.wgs = count(s.chosen, s.cap).wgs;
             if (s.wgs >= kn.target_wgs || s.cap == 1) break;
         }
     return s;
@@ -517,6 +513,54 @@ WorkItem empty_item()
     w.m = w.k = w.nnz = w.row0 = w.nrows = w.f0 = w.fw = 0;
     w.staged = 1;
     return w;
+}
+
+// The rule for plain batches on the float4 path without a caller's knobs.  The widest tile an operation
+// can hold is always taken; parallelism comes from row ranges, which copy their tile again (out of
+// L2) but stage the CSR once per range instead of once per column tile.  fit(words) plans the tiles for
+// that LDS budget.  Measured on MI355X over 44 batches (8 to 6000 graphs of molecule, 20-100-node,
+// heavy-tailed and random-matrix sizes, F = 16 to 1024) against all tiles, budgets and cuts:
+//  - A launch that fits the chip at once (six workgroups of 24 KiB per CU) lasts as long as its slowest
+//    workgroup: the shortest row ranges with which it still fits (256 molecules at F = 128 3.44 ->
+//    3.24 us, 60 graphs of 20-100 nodes at F = 256 4.25 -> 3.4, 450 molecules 4.24 -> 3.86), except
+//    where it moves more than 28 MB and the copies cost more than they gain.
+//  - One that does not is planned for 20 KiB, eight workgroups per CU: where that holds all of it at
+//    once, ranges as short as leave an eighth of the room free (1600 molecules at F = 64 5.65 -> 4.72);
+//    otherwise ranges of two passes, of eight below F = 128, whose passes are 16 rows and more
+//    (1000 graphs of 20-100 nodes at F = 256 26.4 -> 22.9 us, 1024 heavy-tailed ones 29.2 -> 25.0,
+//    6000 molecules at F = 128 30.0 -> 26.8).
+template <typename CountFn, typename FitFn>
+Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, int* uncut_wgs)
+{
+    Shape s = {0, 0, 0};
+    Count n = count(0, 0);
+    s.wgs = *uncut_wgs = n.wgs;
+    auto shortest = [&](std::initializer_list<int> caps, int most) {
+        for (int c : caps) {
+            const int w = count(0, c).wgs;
+            if (w > most) continue;
+            s.cap = c;
+            s.wgs = w;
+            return true;
+        }
+        return false;
+    };
+    if (n.wgs <= kn.capacity_wgs) {
+        if (n.tile_words <= 3500000) shortest({1, 2, 4, 8}, kn.capacity_wgs);
+        return s;
+    }
+    const int eight = 8 * kn.compute_units;            // (other widths: the kernel's registers allow six)
+    if (pow2) {
+        fit(20 * 1024 / 4);
+        s.wgs = count(0, 0).wgs;
+    }
+    if (pow2 && s.wgs <= eight) {
+        shortest({2, 4, 8}, eight - eight / 8);
+    } else {
+        s.cap = F >= 128 ? 2 : 8;
+        s.wgs = count(0, s.cap).wgs;
+    }
+    return s;
 }
 
 // The plain batch - every operation an output block of its own, no forced bins, no sub-workgroup slots,
@@ -557,23 +601,22 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         tile[c] = {Columns(cand[c]), Columns(F % cand[c]), F / cand[c], tile_stride(cand[c], vec == 4)};
     // the widest candidate each operation can hold in LDS (nc: none, it is cut into row blocks)
     std::vector<uint8_t> fit(n);
+    int lds_words = kn.lds_words;
+    auto fit_all = [&](int words) {
+    lds_words = words;
     for (int i = 0; i < n; ++i) {
-        const int64_t room = kn.lds_words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
+        const int64_t room = words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
                              (vec == 4 ? 0 : 4);       // (as fits_slot())
         int c = 0;
         while (c < nc && (int64_t)o.k[i] * tile[c].stride > room) ++c;
         fit[i] = (uint8_t)c;
     }
+    };
+    fit_all(kn.lds_words);
     auto long_rows = [&](int i) { return vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 0; };
     // (exact below 2^31: x + 1/2 over d is at least 1/(2d) away from a whole number)
     auto pieces_of = [](int m, double inv_chunk, int chunk) { return (int)((m + chunk - 0.5) * inv_chunk); };
-    bool slots = false;
-    auto count = [&](size_t first, int cap, bool small) {
-        if (small && !slots)
-            for (int i = 0; i < n && !slots; ++i)
-                for (int b : {BSPMM_BIN_SLICE16, BSPMM_BIN_SLICE32, BSPMM_BIN_WAVE})
-                    slots = slots || (o.m[i] > 0 &&
-                                      fits_slot(o, i, cand[first], F, vec, bin_slot_lanes(b), kn.max_passes, kn));
+    auto count = [&](size_t first, int cap) {
         int chunk[64][2][2];
         double inv[64][2][2];
         for (int c = (int)first; c < nc && cap > 0; ++c)
@@ -606,8 +649,10 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         t.tile_words += k_sum * F;
         return t;
     };
-    const Shape shape = search_shape(kn, vec, (size_t)nc, false, count);
-    if (slots) return false;
+    const bool open = vec == 4 && kn.lds_words == Knobs().lds_words && !kn.lds_given && !kn.target_given && kn.wg_passes == 0;
+    const Shape shape = open ? plain_shape(kn, F, tile[0].full.pow2 && tile[0].tail.pow2, count, fit_all, &s.uncut_wgs)
+                             : search_shape(kn, vec, (size_t)nc, count);
+    if (!open) s.uncut_wgs = shape.wgs;
 
     // A unit is a dense block and the operations that read it; the items of a unit that read the same
     // dense tile are a group and go to one XCD (rows that are no whole number of 128-byte lines: the
@@ -660,10 +705,30 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     uint64_t load[kXcds];                             // cost so far << 3 | list: one minimum, no branches
     for (int x = 0; x < kXcds; ++x) load[x] = (uint64_t)x;
     int32_t used[kXcds] = {0};
+    // Launches of many rounds at narrow widths are bound by the rate at which workgroups start (about
+    // one a nanosecond): operations of at most two passes of a wavefront share a workgroup, one
+    // wavefront each (16000 molecules at F = 16: PACKED us).
+    std::vector<int32_t> packed;
+    const bool pack = shape.wgs > 8 * kn.compute_units && tile[0].full.pow2 && tile[0].nfull == 1 && tile[0].tail.width == 0;
+    const int wave_rows = pack ? 2 * 64 / (tile[0].full.width / 4) : 0;
     s.compact.resize((size_t)round_up(shape.wgs + shape.wgs / 8 + 64, kXcds));
     s.item_op.assign(s.compact.size(), -1);
     bool all_pow2 = vec == 4;
     int64_t lds = 0;
+    auto item_of = [&](int i, bool staged) {
+        LeanItem t = {};
+        t.rpt_off = (uint32_t)o.rpt_off[i];
+        t.nz_off = (uint32_t)o.nz_off[i];
+        t.in_row = (uint32_t)o.in_off[i];
+        t.out_row = (uint32_t)o.out_off[i];
+        t.m = o.m[i], t.k = o.k[i], t.nnz = o.nnz[i];
+        if (staged) {
+            const int cv = round_up(t.m + 1, 2);
+            t.cv_byte = 4 * cv;
+            t.b_byte = 4 * round_up(cv + 2 * t.nnz, 4);
+        }
+        return t;
+    };
     for (int32_t u : order) {
         const uint64_t la = std::min(std::min(load[0], load[1]), std::min(load[2], load[3]));
         const uint64_t lb = std::min(std::min(load[4], load[5]), std::min(load[6], load[7]));
@@ -675,16 +740,12 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             const int c = choice_of(i);
             const bool staged = c < nc;
             const Tile& x = tile[staged ? c : 0];
-            LeanItem t = {};
-            t.rpt_off = (uint32_t)o.rpt_off[i];
-            t.nz_off = (uint32_t)o.nz_off[i];
-            t.in_row = (uint32_t)o.in_off[i];
-            t.out_row = (uint32_t)o.out_off[i];
-            t.m = m, t.k = o.k[i], t.nnz = o.nnz[i];
+            if (m <= wave_rows && c == 0 && 4 * any_words(m, o.k[i], o.nnz[i], F, true) <= lds_words) {
+                packed.push_back(i);
+                continue;
+            }
+            LeanItem t = item_of(i, staged);
             if (staged) {
-                const int cv = round_up(m + 1, 2);
-                t.cv_byte = 4 * cv;
-                t.b_byte = 4 * round_up(cv + 2 * t.nnz, 4);
                 lds = std::max(lds, any_words(m, t.k, t.nnz, x.nfull > 0 ? x.full.width : x.tail.width, vec == 4));
             } else {
                 s.row_blocks = true;
@@ -730,17 +791,39 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             }
         }
     }
-    const int grid = kXcds * *std::max_element(used, used + kXcds);
-    s.compact.resize((size_t)grid);
-    s.item_op.resize((size_t)grid);
+    const int whole = kXcds * *std::max_element(used, used + kXcds);
+    const int groups = ((int)packed.size() + kWaves - 1) / kWaves, grid = whole + groups;
+    s.compact.resize((size_t)grid + packed.size());
+    s.item_op.resize((size_t)grid + packed.size());
     for (int x = 0; x < kXcds; ++x)                   // the ends of the shorter lists: empty items
-        for (int at = used[x] * kXcds + x; at < grid; at += kXcds) s.compact[at] = LeanItem();
+        for (int at = used[x] * kXcds + x; at < whole; at += kXcds) s.compact[at] = LeanItem();
+    for (int j = 0; j < (int)packed.size(); ++j) {    // behind the launch's own items: the packed ones
+        const int i = packed[j];
+        LeanItem t = item_of(i, true);
+        t.nrows = t.m;
+        t.sh = tile[0].full.sh;
+        t.tile_vecs = t.k << t.sh;
+        t.flags = F << 8 | (first[unit_of[i] + 1] - first[unit_of[i]] == 1 ? 1 : 0);
+        s.compact[grid + j] = t;
+        s.item_op[grid + j] = i;
+        lds = std::max(lds, kWaves * (int64_t)round_up((int)any_words(t.m, t.k, t.nnz, F, true), 4));
+    }
+    for (int g = 0; g < groups; ++g) {
+        LeanItem t = {};
+        t.flags = 8;
+        t.tile_vecs = grid + g * kWaves;
+        t.count = std::min(kWaves, (int)packed.size() - g * kWaves);
+        s.compact[whole + g] = t;
+        s.item_op[whole + g] = -1;
+    }
+    s.count += (int)packed.size();
+    s.items_in_bin[BSPMM_BIN_WAVE] += (int)packed.size();
     s.tile = cand[shape.chosen];
     s.grid = s.launch_grid = grid;
-    for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;
+    for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;   // (the compact table's launches do not ask)
     s.whole = grid > 0;
     s.pow2 = s.whole && all_pow2;
-    s.lds_words = s.row_blocks ? kn.lds_words : (int)std::min<int64_t>(kn.lds_words, round_up((int)lds, 64));
+    s.lds_words = s.row_blocks ? lds_words : (int)std::min<int64_t>(lds_words, round_up((int)lds, 64));
     return true;
 }
 
@@ -795,11 +878,16 @@ std::vector<bspmm_item> items_of(const Schedule& s, const ItemTable& compact)
     if (!s.view.empty()) return s.view;
     std::vector<bspmm_item> v;
     v.reserve((size_t)s.count);
-    for (size_t j = 0; j < compact.size(); ++j) {
+    auto add = [&](size_t j, int bin, int workgroup, int slot) {
         const LeanItem& t = compact[j];
-        if (s.item_op[j] >= 0)
-            v.push_back({s.item_op[j], (t.flags & 2) ? BSPMM_BIN_GENERIC : BSPMM_BIN_WORKGROUP, t.row0, t.nrows, t.f0,
-                         t.flags >> 8, (int32_t)j, 0});
+        v.push_back({s.item_op[j], bin, t.row0, t.nrows, t.f0, t.flags >> 8, workgroup, slot});
+    };
+    for (int j = 0; j < s.launch_grid; ++j) {
+        const LeanItem& t = compact[(size_t)j];
+        if (t.flags & 8)
+            for (int w = 0; w < t.count; ++w) add((size_t)(t.tile_vecs + w), BSPMM_BIN_WAVE, j, w);
+        else if (s.item_op[(size_t)j] >= 0)
+            add((size_t)j, (t.flags & 2) ? BSPMM_BIN_GENERIC : BSPMM_BIN_WORKGROUP, j, 0);
     }
     return v;
 }
@@ -886,11 +974,7 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
 
     // widest batch-wide tile that still gives the launch enough workgroups
     std::vector<Draft> d;
-    // Sub-workgroup slots pack several small items into one workgroup.  Measured on MI355X
-    // that only pays when the launch is over-subscribed (more workgroups than the chip holds
-    // at once); a launch that fits is latency-bound and every item is fastest with a whole
-    // workgroup staging it.  A forced bin overrides this.
-    bool allow_small = kn.force_bin >= 0 && kn.front == 0;
+    const bool allow_small = kn.force_bin >= 0 && kn.front == 0;   // sub-workgroup slots: forced bins only
     size_t most_members = 1;
     for (int g = 0; g < outs.size(); ++g) most_members = std::max<size_t>(most_members, outs.count(g));
     if (most_members > (size_t)kMaxMembers) {
@@ -908,19 +992,18 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
                     break;
                 }
     const std::vector<uint8_t>* fit_table = kn.front == 0 && kn.force_bin < 0 && cand.size() < 255 ? &widest_fit : nullptr;
-    auto workgroups_of = [&](size_t first, int cap, bool small) {
+    auto workgroups_of = [&](size_t first, int cap) {
         Sink counter;
-        draft_all(ops, F, vec, cand, first, kn, cap, small, outs, stand_in, &fits, counter, fit_table);
+        draft_all(ops, F, vec, cand, first, kn, cap, allow_small, outs, stand_in, &fits, counter, fit_table);
         counted_tile_words = counter.tile_words;
         return counter.workgroups();
     };
-    const Shape shape = search_shape(kn, vec, cand.size(), allow_small, [&](size_t first, int cap, bool small) {
-        const int w = workgroups_of(first, cap, small);
+    const Shape shape = search_shape(kn, vec, cand.size(), [&](size_t first, int cap) {
+        const int w = workgroups_of(first, cap);
         return Count{w, counted_tile_words};
     });
     const size_t chosen = shape.chosen;
     const int cap = shape.cap, wgs = shape.wgs;
-    allow_small = shape.small;
     s.tile = cand[chosen];
     if (!fits) {   // a set of summed operations does not fit LDS together even at 4 columns
         s.error = BSPMM_ETOOBIG;
@@ -1168,6 +1251,7 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     }
     s.item_op.resize(s.items.size(), -1);
     s.count = (int)s.view.size();
+    s.uncut_wgs = wg;
     s.grid = wg;
     s.launch_grid = kn.persistent_wgs > 0 ? std::min(wg, W) : wg;
     // Launches made only of whole-workgroup items (staged operations and row blocks of the generic

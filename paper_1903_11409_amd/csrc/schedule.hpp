@@ -113,6 +113,7 @@ struct Schedule {
     std::vector<int32_t> item_op;    // operation of every entry of `items` or `compact` (-1: empty item)
     std::vector<bspmm_item> view;    // the non-empty items, for inspection (see items_of)
     int count = 0;                   // non-empty items
+    int uncut_wgs = 0;               // workgroups without row cuts, at the first LDS budget
     bool row_blocks = false;         // `compact` has row blocks of the generic bin
     int32_t wg_end[kRanges] = {0, 0, 0, 0, 0};
     int32_t item_base[kRanges] = {0, 0, 0, 0, 0};
