@@ -421,6 +421,7 @@ void draft_all(const DirOps& o, int F, int vec, const std::vector<int>& cand, si
 struct Count {
     int wgs;
     int64_t tile_words;
+    bool row_blocks;      // some operations are cut into row blocks that gather from memory
 };
 struct Shape {
     size_t chosen;
@@ -521,14 +522,19 @@ WorkItem empty_item()
 // that LDS budget.  Measured on MI355X over 44 batches (8 to 6000 graphs of molecule, 20-100-node,
 // heavy-tailed and random-matrix sizes, F = 16 to 1024) against all tiles, budgets and cuts:
 //  - A launch that fits the chip at once (six workgroups of 24 KiB per CU) lasts as long as its slowest
-//    workgroup: the shortest row ranges with which it still fits (256 molecules at F = 128 3.44 ->
-//    3.24 us, 60 graphs of 20-100 nodes at F = 256 4.25 -> 3.4, 450 molecules 4.24 -> 3.86), except
-//    where it moves more than 28 MB and the copies cost more than they gain.
+//    workgroup: row ranges of one pass, or of two, if it still fits with them (256 molecules at F = 128
+//    3.44 -> 3.24 us, 60 graphs of 20-100 nodes at F = 256 4.25 -> 3.4, 450 molecules 4.24 -> 3.86), except
+//    where it moves more than 28 MB and the copies cost more than they gain.  (Ranges of four and more
+//    copy the tile of an operation of five passes twice for nothing: 200 graphs of 8 to 140 nodes at
+//    F = 256 6.5 us uncut, 8.1 cut to four.)
 //  - One that does not is planned for 20 KiB, eight workgroups per CU: where that holds all of it at
 //    once, ranges as short as leave an eighth of the room free (1600 molecules at F = 64 5.65 -> 4.72);
 //    otherwise ranges of two passes, of eight below F = 128, whose passes are 16 rows and more
-//    (1000 graphs of 20-100 nodes at F = 256 26.4 -> 22.9 us, 1024 heavy-tailed ones 29.2 -> 25.0,
+//    (1000 graphs of 20-100 nodes at F = 256 26.4 -> 22.9 us, 1024 heavy-tailed ones 29.2 -> 24.5,
 //    6000 molecules at F = 128 30.0 -> 26.8).
+//  - From F = 256 on (four rows a pass) with operations in row blocks and more than 8 MB of tiles: ranges of
+//    one pass at 20 KiB whatever the launch's size; staging and row blocks then overlap (300 heavy-
+//    tailed graphs 12.0 -> 8.9 us, 200 of them 8.3 -> 6.9).
 template <typename CountFn, typename FitFn>
 Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, int* uncut_wgs)
 {
@@ -545,8 +551,14 @@ Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, i
         }
         return false;
     };
+    if (pow2 && n.row_blocks && F >= 256 && n.tile_words > 2000000) {
+        fit(20 * 1024 / 4);
+        s.cap = 1;
+        s.wgs = count(0, 1).wgs;
+        return s;
+    }
     if (n.wgs <= kn.capacity_wgs) {
-        if (n.tile_words <= 3500000) shortest({1, 2, 4, 8}, kn.capacity_wgs);
+        if (n.tile_words <= 3500000) shortest({1, 2}, kn.capacity_wgs);
         return s;
     }
     const int eight = 8 * kn.compute_units;            // (other widths: the kernel's registers allow six)
@@ -613,6 +625,9 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     }
     };
     fit_all(kn.lds_words);
+    // rows of a row block: what the workgroup has in flight (2000 heavy-tailed graphs at F = 64: 16.8 us with
+    // eight rows, half of the lanes idle, 15.7 with sixteen), sixty-four at most
+    const int generic_rows = kn.generic_given ? kn.generic_rows : std::max(kn.generic_rows, std::min(tile[0].full.rows[0], 64));
     auto long_rows = [&](int i) { return vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 0; };
     // (exact below 2^31: x + 1/2 over d is at least 1/(2d) away from a whole number)
     auto pieces_of = [](int m, double inv_chunk, int chunk) { return (int)((m + chunk - 0.5) * inv_chunk); };
@@ -624,14 +639,15 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
                 chunk[c][0][l] = cap * tile[c].full.rows[l], chunk[c][1][l] = cap * tile[c].tail.rows[l];
                 for (int t = 0; t < 2; ++t) inv[c][t][l] = 1.0 / chunk[c][t][l];
             }
-        Count t = {0, 0};
+        Count t = {0, 0, false};
         int64_t k_sum = 0;
         for (int i = 0; i < n; ++i) {
             const int m = o.m[i];
             if (m <= 0) continue;
             const int c = std::max((int)first, (int)fit[i]);
             if (c >= nc) {
-                t.wgs += (tile[0].nfull + (tile[0].tail.width > 0)) * ((m + kn.generic_rows - 1) / kn.generic_rows);
+                t.wgs += (tile[0].nfull + (tile[0].tail.width > 0)) * ((m + generic_rows - 1) / generic_rows);
+                t.row_blocks = true;
                 continue;
             }
             const Tile& x = tile[c];
@@ -677,12 +693,12 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     // bytes an item of one row range moves (as item_cost(), the entries spread evenly over the ranges)
     auto ranges_of = [](int m, int chunk) { return chunk >= m ? 1 : (int)((unsigned)(m + chunk - 1) / (unsigned)chunk); };
     auto chunk_of = [&](int i, const Columns& y, bool staged) {
-        return !staged ? kn.generic_rows : (shape.cap > 0 ? shape.cap * y.rows[long_rows(i)] : o.m[i]);
+        return !staged ? generic_rows : (shape.cap > 0 ? shape.cap * y.rows[long_rows(i)] : o.m[i]);
     };
     auto cost_of = [&](int i, const Columns& y, int chunk, int ranges, bool staged) {
         const int nrows = std::min(chunk, o.m[i]);
-        const int64_t dense_in = staged ? o.k[i] : std::min<int64_t>(o.k[i], (int64_t)nrows * 4);
         const int64_t entries = ranges == 1 ? o.nnz[i] : (unsigned)o.nnz[i] / (unsigned)ranges;
+        const int64_t dense_in = staged ? o.k[i] : entries;      // (a row block gathers a row per entry)
         return 4 * (int64_t)y.width * (dense_in + nrows) + 8 * entries + 4 * (int64_t)nrows + 512;
     };
     auto choice_of = [&](int i) { return std::max((int)shape.chosen, (int)fit[i]); };
@@ -853,7 +869,8 @@ Knobs resolve_knobs(const bspmm_options* o)
     if (o->lds_pad > 0) k.pad = std::min(o->lds_pad, 64) / 4 * 4;
     if (o->lds_pad < 0) k.pad = 0;
     if (o->max_passes > 0) k.max_passes = o->max_passes;
-    if (o->generic_rows > 0) k.generic_rows = o->generic_rows;
+    if (o->generic_rows > 0) k.generic_rows = std::min(o->generic_rows, kThreads - 1);   // (a row pointer per lane)
+    k.generic_given = o->generic_rows > 0;
     k.wg_passes = o->wg_passes;
     if (o->resident_workgroups > 0) k.persistent_wgs = o->resident_workgroups;
     k.hubs = (o->flags & BSPMM_SPLIT_HUB_ROWS) != 0;
@@ -1000,7 +1017,7 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     };
     const Shape shape = search_shape(kn, vec, cand.size(), [&](size_t first, int cap) {
         const int w = workgroups_of(first, cap);
-        return Count{w, counted_tile_words};
+        return Count{w, counted_tile_words, false};
     });
     const size_t chosen = shape.chosen;
     const int cap = shape.cap, wgs = shape.wgs;

@@ -37,6 +37,7 @@ struct Knobs {
     int pad = 0;
     int max_passes = 1;
     int generic_rows = 8;
+    bool generic_given = false;
     int wg_passes = 0;        // 0 automatic, >0 cap on passes of a workgroup item, <0 never cut
     int capacity_wgs = 1536;  // workgroups the chip holds at once (lean kernel variant)
     int capacity_wgs_slices = 1024;   // same for the kernel variant with 32/16-lane slots
