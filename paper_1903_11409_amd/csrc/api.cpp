@@ -1039,6 +1039,7 @@ int plan_with_budget(bspmm_plan& p, const Batch* b, int32_t F, const bspmm_optio
     kn.need_both = open && !front;
     int rc = plan_fn(p, b, F, kn);
     if (rc == BSPMM_OK && open && !front && !p.coo_direct && F >= 512 && p.effective_bytes[0] > 28000000 &&
+        p.effective_bytes[0] < 70000000 && !p.sched[0].row_blocks &&
         p.sched[0].uncut_wgs > kn.capacity_wgs) {
         // Wide feature matrices moved by a launch of more than one round of workgroups, which
         // runs at the rate of the memory system: with 24 KiB the larger operations get tiles of
@@ -1048,7 +1049,10 @@ int plan_with_budget(bspmm_plan& p, const Batch* b, int32_t F, const bspmm_optio
         // instead of six (measured, 128 graphs of 20-100 nodes: F = 1024, six seeds, 1.35-1.45
         // rounds before and 1.39-1.47 after, 14.3-15.2 -> 13.4-14.4 us, 4.24-4.34 -> 4.49-4.56 TB/s;
         // F = 512, 0.71 -> 1.33 rounds, 7.46 -> 8.79 us: not taken; 1024 graphs of 25 nodes at
-        // F = 512, 2.19 -> 2.82 rounds, 21.0 -> 21.3 us: not taken).
+        // F = 512, 2.19 -> 2.82 rounds, 21.0 -> 21.3 us: not taken).  Beyond 70 MB, and where some
+        // operations are row blocks, the row ranges of the first plan are ahead (300 graphs of 20-100
+        // nodes at F = 512 15.8 -> 14.0 us, 200 at F = 1024 20.3 -> 17.7; 80 random matrices at
+        // F = 512 10.1 -> 8.7).
         bspmm_options o = options ? *options : bspmm_options{};
         o.lds_bytes = 53248;
         Knobs wide = knobs_for(&o, !dry);

@@ -531,10 +531,12 @@ WorkItem empty_item()
 //    once, ranges as short as leave an eighth of the room free (1600 molecules at F = 64 5.65 -> 4.72);
 //    otherwise ranges of two passes, of eight below F = 128, whose passes are 16 rows and more
 //    (1000 graphs of 20-100 nodes at F = 256 26.4 -> 22.9 us, 1024 heavy-tailed ones 29.2 -> 24.5,
-//    6000 molecules at F = 128 30.0 -> 26.8).
-//  - From F = 256 on (four rows a pass) with operations in row blocks and more than 8 MB of tiles: ranges of
-//    one pass at 20 KiB whatever the launch's size; staging and row blocks then overlap (300 heavy-
-//    tailed graphs 12.0 -> 8.9 us, 200 of them 8.3 -> 6.9).
+//    6000 molecules at F = 128 30.0 -> 27.3).  Past 88 MB of dense input, where input and output no longer
+//    stay in the 256 MB memory-side cache together, second copies cost more: ranges of four passes at
+//    24 KiB (8000 molecules 40.8 -> 39.8, 16384 of them 82.5 -> 81.0, ranges of two 86.2).
+//  - From F = 256 on (four rows a pass) with operations in row blocks: ranges of one pass at 20 KiB
+//    whatever the launch's size; staging and row blocks then overlap (300 heavy-tailed graphs 12.0 -> 8.9
+//    us, 150 of them 6.3 -> 5.3; 80 random matrices of 3 entries a row, half in row blocks, 6.5 -> 5.2).
 template <typename CountFn, typename FitFn>
 Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, int* uncut_wgs)
 {
@@ -551,7 +553,7 @@ Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, i
         }
         return false;
     };
-    if (pow2 && n.row_blocks && F >= 256 && n.tile_words > 2000000) {
+    if (pow2 && n.row_blocks && F >= 256) {
         fit(20 * 1024 / 4);
         s.cap = 1;
         s.wgs = count(0, 1).wgs;
@@ -562,14 +564,15 @@ Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, i
         return s;
     }
     const int eight = 8 * kn.compute_units;            // (other widths: the kernel's registers allow six)
-    if (pow2) {
+    const bool streams = F >= 128 && n.tile_words > 22000000;
+    if (pow2 && !streams) {
         fit(20 * 1024 / 4);
         s.wgs = count(0, 0).wgs;
     }
     if (pow2 && s.wgs <= eight) {
         shortest({2, 4, 8}, eight - eight / 8);
     } else {
-        s.cap = F >= 128 ? 2 : 8;
+        s.cap = streams ? 4 : F >= 128 ? 2 : 8;
         s.wgs = count(0, s.cap).wgs;
     }
     return s;
@@ -578,7 +581,7 @@ Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, i
 // The plain batch - every operation an output block of its own, no forced bins, no sub-workgroup slots,
 // nothing riding along - straight to the compact item table.  A data loader plans a batch per step,
 // so this is on its critical path: no item is written twice, ordering and placement work on
-// groups of items, and counting is closed form (128 molecules at F = 128: MEASURED_PLAN).
+// groups of items, and counting is closed form (128 molecules at F = 128: 33 us before, 8 now).
 // Returns false when the batch needs the general planner below.
 bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std::vector<int>& cand, Schedule& s)
 {
@@ -615,14 +618,14 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     std::vector<uint8_t> fit(n);
     int lds_words = kn.lds_words;
     auto fit_all = [&](int words) {
-    lds_words = words;
-    for (int i = 0; i < n; ++i) {
-        const int64_t room = words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
-                             (vec == 4 ? 0 : 4);       // (as fits_slot())
-        int c = 0;
-        while (c < nc && (int64_t)o.k[i] * tile[c].stride > room) ++c;
-        fit[i] = (uint8_t)c;
-    }
+        lds_words = words;
+        for (int i = 0; i < n; ++i) {
+            const int64_t room = words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
+                                 (vec == 4 ? 0 : 4);   // (as fits_slot())
+            int c = 0;
+            while (c < nc && (int64_t)o.k[i] * tile[c].stride > room) ++c;
+            fit[i] = (uint8_t)c;
+        }
     };
     fit_all(kn.lds_words);
     // rows of a row block: what the workgroup has in flight (2000 heavy-tailed graphs at F = 64: 16.8 us with
@@ -723,7 +726,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     int32_t used[kXcds] = {0};
     // Launches of many rounds at narrow widths are bound by the rate at which workgroups start (about
     // one a nanosecond): operations of at most two passes of a wavefront share a workgroup, one
-    // wavefront each (16000 molecules at F = 16: PACKED us).
+    // wavefront each (16000 molecules at F = 16: 17.7 us one to a workgroup, 13.4 packed).
     std::vector<int32_t> packed;
     const bool pack = shape.wgs > 8 * kn.compute_units && tile[0].full.pow2 && tile[0].nfull == 1 && tile[0].tail.width == 0;
     const int wave_rows = pack ? 2 * 64 / (tile[0].full.width / 4) : 0;

@@ -3,7 +3,7 @@
 // pageable memory cost 3 to 14 us of host time each and, where the source may be reused, a wait for
 // the stream.  The copy is a kernel that reads the pinned memory: a copy engine's transfer takes
 // 8 us for 160 KB however small, and the queues wait for each other before and after it (128
-// molecules, plan + two products: 36 us a step through the copy engine, STEP_US with the kernel).
+// molecules, plan + two products: 36 us a step through the copy engine, 30 us with the kernel).
 #pragma once
 
 #include <hip/hip_runtime_api.h>

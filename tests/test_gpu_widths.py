@@ -62,3 +62,21 @@ def test_operands_off_16_bytes(oracle, F, in_off, out_off, in_extra, out_extra):
         got = _run(torch, plan, b, transposed, in_off, out_off, in_extra, out_extra)
         ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
         _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
+
+
+@pytest.mark.parametrize("F", [4, 8, 16, 32, 64, 128])
+@pytest.mark.parametrize("in_off", [0, 1])
+def test_small_operations_share_a_workgroup(oracle, F, in_off):
+    """More small operations than the chip holds workgroups: four to a workgroup, one wavefront each (up to
+    two passes of rows), next to those that are too large for it; the same table off 16 bytes."""
+    import torch
+    limit = 512 // F
+    one = [(limit, 9, 60), (limit - 1, 40, 190), (1, 1, 1), (limit, 3, 0), (0, 0, 0), (limit + 1, 20, 70), (2, 5, 7),
+           (3 * limit, 30, 129)]
+    b = W.random_general(77 + F, F=F, shapes=one * 500)
+    plan = K.Plan(b)
+    assert plan.info().items_in_bin[0][K.BIN_WAVE] > 0
+    for transposed in (False, True):
+        got = _run(torch, plan, b, transposed, in_off, 0, 0, 0)
+        ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
+        _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
