@@ -422,6 +422,7 @@ struct Count {
     int wgs;
     int64_t tile_words;
     bool row_blocks;      // some operations are cut into row blocks that gather from memory
+    int64_t in_words;     // of the dense blocks of all operations
 };
 struct Shape {
     size_t chosen;
@@ -449,9 +450,10 @@ Shape search_shape(const Knobs& kn, int vec, size_t candidates, CountFn count)
         // Widths off 16 bytes: a tile of whole rows is one run of memory, cheaper to copy several
         // times (out of L2) than column tiles whose rows start anywhere.  Ranges of at most eight
         // passes over the lane groups (200 operations of 1 to 220 rows, F = 127: uncut 16.5 us, sixteen
-        // passes 12.3, eight 9.3), shorter until there are two workgroups per CU, but not in launches
-        // bound by bandwidth.
-        const int want = kn.target_given ? kn.target_wgs : 2 * kn.compute_units;
+        // passes 12.3, eight 9.3), shorter until there are three and a half workgroups per CU (two per
+        // CU: 100 operations 7.5 us instead of 6.6, 150 9.3 instead of 8.1; five: 6.9 and 8.1), but not in
+        // launches bound by bandwidth.
+        const int want = kn.target_given ? kn.target_wgs : 7 * kn.compute_units / 2;
         for (int c = 8; c >= 1; c /= 2) {
             const Count n = count(s.chosen, c);
             s.wgs = n.wgs;
@@ -518,8 +520,8 @@ WorkItem empty_item()
 
 // The rule for plain batches on the float4 path without a caller's knobs.  The widest tile an operation
 // can hold is always taken; parallelism comes from row ranges, which copy their tile again (out of
-// L2) but stage the CSR once per range instead of once per column tile.  fit(words) plans the tiles for
-// that LDS budget.  Measured on MI355X over 44 batches (8 to 6000 graphs of molecule, 20-100-node,
+// L2) but stage the CSR once per range instead of once per column tile.  fit(words, c) plans the tiles for
+// that LDS budget and row blocks for candidate c.  Measured on MI355X over 44 batches (8 to 6000 graphs of molecule, 20-100-node,
 // heavy-tailed and random-matrix sizes, F = 16 to 1024) against all tiles, budgets and cuts:
 //  - A launch that fits the chip at once (six workgroups of 24 KiB per CU) lasts as long as its slowest
 //    workgroup: row ranges of one pass, or of two, if it still fits with them (256 molecules at F = 128
@@ -536,16 +538,33 @@ WorkItem empty_item()
 //    24 KiB (8000 molecules 40.8 -> 39.8, 16384 of them 82.5 -> 81.0, ranges of two 86.2).
 //  - From F = 256 on (four rows a pass) with operations in row blocks: ranges of one pass at 20 KiB
 //    whatever the launch's size; staging and row blocks then overlap (300 heavy-tailed graphs 12.0 -> 8.9
-//    us, 150 of them 6.3 -> 5.3; 80 random matrices of 3 entries a row, half in row blocks, 6.5 -> 5.2).
+//    us, 150 of them 6.3 -> 5.3; 80 random matrices of 3 entries a row, half in row blocks, 6.5 -> 5.2),
+//    of two from 48 MB of input on (700 heavy-tailed graphs at F = 512 36.4 -> 33.5), of four from 80.
+//  - Row blocks past 104 MB fetch what they gather from memory again: uncut at 40 KiB where that saves
+//    a third of the workgroups (3000 heavy-tailed graphs at F = 256 107 us at 20 KiB, 76.5 at 24, 75.1;
+//    10000 random matrices at F = 32 90 -> 76).
+//  - Dense blocks that several operations read (edge types as channels): ranges of four passes at 24 KiB,
+//    the tiles come out of L2 (900 molecules of four channels at F = 128 10.7 -> 9.9).
+//  - Widths of whole 128-byte lines that are no power of two (96, 160, 192): one tile of the whole row keeps
+//    part of the lanes idle but copies and stages once, which wins in launches of several rounds that stay
+//    in cache (3000 molecules at F = 192 20.3 us, 22 in tiles of 128 and 64).  Tiles that are powers of two
+//    win where latency or the memory itself bounds, up to 14 MB in one round (400 molecules 5.3 -> 4.8,
+//    100 graphs of 20-100 nodes 5.0 -> 4.2) and past 88 MB (2500 of these graphs 49.3 -> 44.9), and where
+//    most operations are too large for the whole row anyway (400 of them 9.4 -> 8.8).
+//  - Rows off the 128-byte lines (F = 100): column tiles share lines, so operations that need them at 24 KiB
+//    get 40 once the launch does not fit the chip at once anyway, where that saves a quarter of the
+//    tiles and none are row blocks, and ranges of four passes (5000 graphs of 20-100 nodes 79.8 -> 58.9
+//    us, 2000 of them 27.2 -> 20.9; 2000 molecules, of which few need it, 9.7 -> 11.0: not taken).
+// narrow: the first candidate from which on all tiles are powers of two (-1: none).
 template <typename CountFn, typename FitFn>
-Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, int* uncut_wgs)
+Shape plain_shape(const Knobs& kn, int F, int narrow, bool shared, CountFn count, FitFn fit, int* uncut_wgs)
 {
     Shape s = {0, 0, 0};
     Count n = count(0, 0);
     s.wgs = *uncut_wgs = n.wgs;
     auto shortest = [&](std::initializer_list<int> caps, int most) {
         for (int c : caps) {
-            const int w = count(0, c).wgs;
+            const int w = count(s.chosen, c).wgs;
             if (w > most) continue;
             s.cap = c;
             s.wgs = w;
@@ -553,28 +572,55 @@ Shape plain_shape(const Knobs& kn, int F, bool pow2, CountFn count, FitFn fit, i
         }
         return false;
     };
-    if (pow2 && n.row_blocks && F >= 256) {
-        fit(20 * 1024 / 4);
-        s.cap = 1;
-        s.wgs = count(0, 1).wgs;
+    auto cut = [&](int cap) {
+        s.cap = cap;
+        s.wgs = count(s.chosen, cap).wgs;
         return s;
+    };
+    const bool small = n.tile_words <= 3500000;
+    const bool streams = F >= 128 && n.in_words > 22000000;
+    bool pow2 = narrow == 0;
+    if (narrow > 0 && F % 32 == 0) {
+        const Count t = count((size_t)narrow, 0);
+        if ((small && t.wgs <= kn.capacity_wgs) ||
+            (!n.row_blocks && (streams || 4 * (int64_t)t.wgs <= 5 * (int64_t)n.wgs))) {
+            fit(small ? 20 * 1024 / 4 : kn.lds_words, narrow);
+            pow2 = !small || count((size_t)narrow, 0).wgs <= kn.capacity_wgs;
+            if (pow2) {
+                s.chosen = (size_t)narrow;
+                s.wgs = *uncut_wgs = t.wgs;
+            } else {
+                fit(kn.lds_words, 0);
+            }
+        }
     }
-    if (n.wgs <= kn.capacity_wgs) {
-        if (n.tile_words <= 3500000) shortest({1, 2}, kn.capacity_wgs);
-        return s;
+    if (n.row_blocks && F % 32 == 0 && n.in_words > 26000000) {
+        fit(40 * 1024 / 4, (int)s.chosen);
+        if (3 * (int64_t)count(s.chosen, 0).wgs <= 2 * (int64_t)s.wgs) return cut(0);
+        fit(kn.lds_words, (int)s.chosen);
+    } else if (n.row_blocks && pow2 && F >= 256) {
+        fit(20 * 1024 / 4, (int)s.chosen);
+        return cut(n.in_words > 20000000 ? 4 : n.in_words > 12000000 ? 2 : 1);
     }
     const int eight = 8 * kn.compute_units;            // (other widths: the kernel's registers allow six)
-    const bool streams = F >= 128 && n.tile_words > 22000000;
-    if (pow2 && !streams) {
-        fit(20 * 1024 / 4);
-        s.wgs = count(0, 0).wgs;
+    if (s.wgs <= kn.capacity_wgs) {
+        if (!small) return s;
+        if (shortest({1}, kn.capacity_wgs)) return s;
+        if (s.chosen == 0 && pow2)
+            shortest({2}, kn.capacity_wgs);
+        else
+            shortest({2, 4}, pow2 ? eight - eight / 8 : kn.capacity_wgs);
+        return s;
     }
-    if (pow2 && s.wgs <= eight) {
-        shortest({2, 4, 8}, eight - eight / 8);
-    } else {
-        s.cap = streams ? 4 : F >= 128 ? 2 : 8;
-        s.wgs = count(0, s.cap).wgs;
+    if (!pow2 && F % 32 != 0 && !n.row_blocks) {
+        fit(40 * 1024 / 4, 0);
+        if (4 * (int64_t)count(0, 0).wgs > 3 * (int64_t)s.wgs) fit(kn.lds_words, 0);
     }
+    if (!pow2 || streams || (shared && F >= 128)) return cut(4);
+    fit(20 * 1024 / 4, (int)s.chosen);
+    s.wgs = count(s.chosen, 0).wgs;
+    if (s.wgs > eight) return cut(F >= 128 ? 2 : 8);
+    shortest({2, 4, 8}, eight - eight / 8);
     return s;
 }
 
@@ -617,8 +663,10 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     // the widest candidate each operation can hold in LDS (nc: none, it is cut into row blocks)
     std::vector<uint8_t> fit(n);
     int lds_words = kn.lds_words;
-    auto fit_all = [&](int words) {
+    int blocks = 0;                                    // the candidate whose columns row blocks take
+    auto fit_all = [&](int words, int block_tile) {
         lds_words = words;
+        blocks = block_tile;
         for (int i = 0; i < n; ++i) {
             const int64_t room = words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
                                  (vec == 4 ? 0 : 4);   // (as fits_slot())
@@ -627,7 +675,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             fit[i] = (uint8_t)c;
         }
     };
-    fit_all(kn.lds_words);
+    fit_all(kn.lds_words, 0);
     // rows of a row block: what the workgroup has in flight (2000 heavy-tailed graphs at F = 64: 16.8 us with
     // eight rows, half of the lanes idle, 15.7 with sixteen), sixty-four at most
     const int generic_rows = kn.generic_given ? kn.generic_rows : std::max(kn.generic_rows, std::min(tile[0].full.rows[0], 64));
@@ -642,14 +690,15 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
                 chunk[c][0][l] = cap * tile[c].full.rows[l], chunk[c][1][l] = cap * tile[c].tail.rows[l];
                 for (int t = 0; t < 2; ++t) inv[c][t][l] = 1.0 / chunk[c][t][l];
             }
-        Count t = {0, 0, false};
+        Count t = {0, 0, false, 0};
         int64_t k_sum = 0;
         for (int i = 0; i < n; ++i) {
             const int m = o.m[i];
             if (m <= 0) continue;
+            t.in_words += o.k[i];
             const int c = std::max((int)first, (int)fit[i]);
             if (c >= nc) {
-                t.wgs += (tile[0].nfull + (tile[0].tail.width > 0)) * ((m + generic_rows - 1) / generic_rows);
+                t.wgs += (tile[blocks].nfull + (tile[blocks].tail.width > 0)) * ((m + generic_rows - 1) / generic_rows);
                 t.row_blocks = true;
                 continue;
             }
@@ -666,10 +715,21 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             t.tile_words += (int64_t)o.k[i] * (pf * x.full.width + pt * x.tail.width);
         }
         t.tile_words += k_sum * F;
+        t.in_words *= F;
         return t;
     };
+    const std::vector<int> unit_of = input_blocks(o);
+    int units = 0;
+    bool in_order = true;
+    for (int i = 0; i < n; ++i) {
+        units = std::max(units, unit_of[i] + 1);
+        in_order = in_order && (i == 0 || unit_of[i] >= unit_of[i - 1]);
+    }
     const bool open = vec == 4 && kn.lds_words == Knobs().lds_words && !kn.lds_given && !kn.target_given && kn.wg_passes == 0;
-    const Shape shape = open ? plain_shape(kn, F, tile[0].full.pow2 && tile[0].tail.pow2, count, fit_all, &s.uncut_wgs)
+    int narrow = -1;
+    for (int c = std::min(nc, 2) - 1; c >= 0; --c)
+        if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
+    const Shape shape = open ? plain_shape(kn, F, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
                              : search_shape(kn, vec, (size_t)nc, count);
     if (!open) s.uncut_wgs = shape.wgs;
 
@@ -678,13 +738,6 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     // whole unit, because column tiles share the lines at their edges - 900 operations of 1 to 220 rows
     // at F = 127 fetched 122 MB and wrote 60 MB instead of 50 each, and took 34 us instead of 22, with
     // the tiles of an operation on different XCDs).
-    const std::vector<int> unit_of = input_blocks(o);
-    int units = 0;
-    bool in_order = true;
-    for (int i = 0; i < n; ++i) {
-        units = std::max(units, unit_of[i] + 1);
-        in_order = in_order && (i == 0 || unit_of[i] >= unit_of[i - 1]);
-    }
     const int columns = F % 32 != 0 ? std::max(4, F) : std::max(4, std::min(cand.back(), F));   // of a group
     std::vector<int32_t> first((size_t)units + 1, 0), member(in_order ? 0 : n);   // the operations of every unit
     for (int i = 0; i < n; ++i) ++first[unit_of[i] + 1];
@@ -710,7 +763,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         if (o.m[i] <= 0) continue;
         const int c = choice_of(i);
         const bool staged = c < nc;
-        const Columns& y = tile[staged ? c : 0].full;
+        const Columns& y = tile[staged ? c : blocks].full;
         const int chunk = chunk_of(i, y, staged);
         cost[unit_of[i]] = std::max(cost[unit_of[i]], cost_of(i, y, chunk, ranges_of(o.m[i], chunk), staged));
     }
@@ -758,7 +811,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             if (m <= 0) continue;
             const int c = choice_of(i);
             const bool staged = c < nc;
-            const Tile& x = tile[staged ? c : 0];
+            const Tile& x = tile[staged ? c : blocks];
             if (m <= wave_rows && c == 0 && 4 * any_words(m, o.k[i], o.nnz[i], F, true) <= lds_words) {
                 packed.push_back(i);
                 continue;
