@@ -429,7 +429,7 @@ class Plan:
                 self._csr = tuple(int(a.shape[0]) for a in csr)
         if made is None:
             raise TypeError("the batch's arrays cannot be used: one-dimensional arrays of one length are needed")
-        self.handle, self._memory, self._head = made
+        self.handle, self._memory, self._head, self.rpt_len, self.rpt_t_len, self.nnz_total = made
 
     @staticmethod
     def _as_arrays(arrays, dtype):
@@ -468,9 +468,6 @@ class Plan:
                         at += (4 * n + 255) // 256 * 256
                     self._views = tuple(views)
             return self._views[("rpt", "colids", "values").index(name)]
-        if name in ("rpt_len", "rpt_t_len", "nnz_total"):
-            a = self._meta[("rpt_len", "rpt_t_len", "nnz_total").index(name)]
-            return int(np.asarray(a, dtype=np.int64).sum()) + (len(a) if name != "nnz_total" else 0)
         raise AttributeError(name)
 
     def run(self, B, C, stream=None):

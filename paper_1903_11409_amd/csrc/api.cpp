@@ -123,6 +123,8 @@ struct bspmm_plan {
     int32_t lean_out_rows[2] = {0, 0};     // of the 32-bit offsets the lean kernel forms per call
     bool lean_blocks[2] = {false, false};  // the lean table has row blocks of the generic bin ...
     bool lean_hints_built[2] = {false, false};   // ... and the device has filled in their entry ranges
+    StagedCopy upload;          // the copy of the tables from pinned memory, until it is known to have run ...
+    hipStream_t upload_stream = nullptr;   // ... and the stream it was enqueued on
     std::vector<char> tables;   // host image of the workspace's front, for copies from pageable memory
     Layout lay;
     int build_lds_bytes = 0;
@@ -1094,6 +1096,15 @@ bool capturing(hipStream_t s)
     return st == hipStreamCaptureStatusActive;
 }
 
+// Before work on `s` that reads the plan's tables: a plan may be used on another stream than it was
+// made on without the caller ordering the two, as when the tables went over in blocking copies.
+void settle(bspmm_plan* p, hipStream_t s)
+{
+    if (!p->upload.slot || s == p->upload_stream) return;
+    stage_wait(p->upload);
+    p->upload.slot = nullptr;
+}
+
 int enqueue_build(bspmm_plan* p, hipStream_t s)
 {
     if (p->transposed_built || p->knobs.symmetric) return BSPMM_OK;
@@ -1457,7 +1468,8 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
     if (stage.ptr) {
         if (front) front->write(front->from, stage.ptr);
         write_image(p, stage.ptr + head);
-        e = stage_copy(stage, dst, head + p->lay.image, s);
+        p->upload_stream = s;
+        e = stage_copy(stage, dst, head + p->lay.image, s, &p->upload);
     } else if (p->lay.image > 0) {
         p->tables.resize(p->lay.image);
         write_image(p, p->tables.data());
@@ -1866,6 +1878,7 @@ int bspmm_run(bspmm_plan* plan, const float* B, float* C, int64_t ldb, int64_t l
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || displaced(plan)) return BSPMM_ESTATE;
+    settle(plan, static_cast<hipStream_t>(stream));
     return run_direction(plan, 0, B, C, ldb, ldc, static_cast<hipStream_t>(stream));
 }
 
@@ -1874,6 +1887,7 @@ int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W,
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || plan->knobs.front <= 0 || plan->coo_direct || displaced(plan)) return BSPMM_ESTATE;
+    settle(plan, static_cast<hipStream_t>(stream));
     return run_gcn(plan, X, ldx, W, ldw, bias, Y, ldy, accumulate, static_cast<hipStream_t>(stream));
 }
 
@@ -1882,6 +1896,7 @@ int bspmm_run_transposed(bspmm_plan* plan, const float* dY, float* G, int64_t ld
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || !plan->transposed_supported || displaced(plan)) return BSPMM_ESTATE;
+    settle(plan, static_cast<hipStream_t>(stream));
     if (plan->coo_direct)
         return run_direction(plan, 1, dY, G, ldy, ldg, static_cast<hipStream_t>(stream));
     if (plan->sched[1].grid > 0 && ((!dY && plan->reads_dense) || !G || ldy < plan->F || ldg < plan->F))
@@ -1897,6 +1912,7 @@ int bspmm_export_transposed(bspmm_plan* plan, int32_t* rpt_t, int32_t* colids_t,
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || plan->coo_direct || plan->knobs.symmetric || displaced(plan)) return BSPMM_ESTATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    settle(plan, s);
     int rc = enqueue_build(plan, s);
     if (rc != BSPMM_OK) return rc;
     size_t rpt_words = 0, nz = 0;
@@ -1927,6 +1943,7 @@ int bspmm_validate(bspmm_plan* plan, int32_t* bad_op, void* stream)
     if (plan->dry || displaced(plan)) return BSPMM_ESTATE;
     if (bad_op) *bad_op = -1;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    settle(plan, s);
     int32_t* flag = reinterpret_cast<int32_t*>(plan->ws + plan->lay.flag);
     hipError_t e = plan->from_coo
         ? launch_validate_coo(reinterpret_cast<const OpRecord*>(plan->ws + plan->lay.coo_records),

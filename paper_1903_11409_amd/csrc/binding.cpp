@@ -265,10 +265,17 @@ at::Tensor device_bytes(size_t n, int64_t device)
     return at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(at::Device(at::kCUDA, (c10::DeviceIndex)device)));
 }
 
-PyObject* made(bspmm_plan* plan, const at::Tensor& memory, size_t head)
+// (plan, memory, bytes in front of the workspace, row pointers, transposed row pointers, entries): the
+// caller may reuse the arrays afterwards, so their sums are taken now.
+template <typename Batch>
+PyObject* made(bspmm_plan* plan, const Batch& b, const at::Tensor& memory, size_t head)
 {
+    long long rows = b.batch, cols = b.batch, nnz = 0;
+    for (int32_t i = 0; i < b.batch; ++i) rows += b.rows[i], cols += b.cols[i], nnz += b.nnz[i];
     PyObject* t = THPVariable_Wrap(memory);
-    return t ? Py_BuildValue("(KNn)", (unsigned long long)reinterpret_cast<uintptr_t>(plan), t, (Py_ssize_t)head) : nullptr;
+    return t ? Py_BuildValue("(KNnLLL)", (unsigned long long)reinterpret_cast<uintptr_t>(plan), t, (Py_ssize_t)head, rows,
+                             cols, nnz)
+             : nullptr;
 }
 
 // The caller's CSR arrays in host memory, and how they lie in front of the workspace.
@@ -287,9 +294,9 @@ struct Csr {
 };
 
 // (rows, cols, nnz, rpt_off, nz_off, b_row_off, c_row_off, rpt, colids, values, F, options address or
-// None, device index, stream) -> (plan, memory, bytes in front of the workspace), the CSR arrays
-// all host arrays or all device tensors; None when an argument is of another kind (the caller
-// converts it) or the arrays cannot be staged.
+// None, device index, stream) -> what made() returns, the CSR arrays all host arrays or all device
+// tensors; None when an argument is of another kind (the caller converts it) or the arrays cannot be
+// staged.
 PyObject* create(PyObject* const* a, Py_ssize_t n)
 {
     int64_t F, device;
@@ -315,6 +322,9 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
         Py_RETURN_NONE;
     for (int i = 0; i < 3; ++i) csr.bytes[i] = host ? 4 * (size_t)len[i] : 0;
     if (!get_stream(a[13], &stream)) return nullptr;
+    // The memory belongs to the current stream: on another one the caller copies the arrays first, so
+    // that a plan dropped early leaves no copy on its way to memory that is somebody else's by then.
+    if (host && a[13] != Py_None && stream != c10::hip::getCurrentHIPStream().stream()) Py_RETURN_NONE;
     const bspmm_options* opt = static_cast<const bspmm_options*>(options);
     const size_t head = host ? csr.head() : 0;
     size_t need = 0;
@@ -343,11 +353,11 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
     }
     Py_END_ALLOW_THREADS
     if (host && rc == BSPMM_ESTATE) Py_RETURN_NONE;
-    return rc == BSPMM_OK ? made(plan, memory, head) : finish(rc, where, Py_None);
+    return rc == BSPMM_OK ? made(plan, b, memory, head) : finish(rc, where, Py_None);
 }
 
 // (rows, cols, nnz, nz_off, b_row_off, c_row_off, ids, values, F, options address or None, device index,
-// stream) -> (plan, memory, 0); ids and values device tensors; None as above.
+// stream) -> as above; ids and values device tensors; None as above.
 PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
 {
     int64_t F, device;
@@ -380,7 +390,7 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
         rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
     }
     Py_END_ALLOW_THREADS
-    return rc == BSPMM_OK ? made(plan, memory, 0) : finish(rc, where, Py_None);
+    return rc == BSPMM_OK ? made(plan, b, memory, 0) : finish(rc, where, Py_None);
 }
 
 // (plan, transposed) -> rows from the first on that every product writes

@@ -2,11 +2,13 @@
 #include "staging.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cstdint>
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 namespace bspmm {
@@ -128,18 +130,38 @@ StageBlock stage_take(size_t bytes)
     return {p.slots.back()->data(), p.slots.back().get()};
 }
 
-hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream)
+hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream, StagedCopy* copy)
 {
     Slot& s = *static_cast<Slot*>(b.slot);
+    static std::atomic<uint32_t> next_mark{0};
+    // (no two copies under way have the same one; a new block's words are zero)
+    uint32_t mark = ++next_mark;
+    if (mark == 0) mark = ++next_mark;
     // (4 KiB a workgroup: 16 bytes a lane, all of a plan's tables in flight at once)
     const int grid = (int)std::min<size_t>(kMarks, (bytes + 4095) / 4096);
-    const uint32_t mark = s.mark + 1;
     const hipError_t e = launch_stage_copy(b.ptr, dst, bytes, s.marks(), mark, grid, stream);
     std::lock_guard<std::mutex> g(pool().lock);
     s.mark = mark;
     s.grid = e == hipSuccess ? grid : 0;
     s.state = Slot::kCopying;
+    *copy = {&s, mark};
     return e;
+}
+
+void stage_wait(const StagedCopy& copy)
+{
+    Pool& p = pool();
+    for (;;) {
+        {
+            // (a block that has gone, or carries another mark, was idle in between: the copy has run)
+            std::lock_guard<std::mutex> g(p.lock);
+            bool under_way = false;
+            for (auto& s : p.slots)
+                if (s.get() == copy.slot && s->mark == copy.mark && s->state == Slot::kCopying) under_way = !idle(*s);
+            if (!under_way) return;
+        }
+        std::this_thread::yield();
+    }
 }
 
 void stage_plan_made()

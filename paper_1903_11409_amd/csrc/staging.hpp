@@ -9,6 +9,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <cstddef>
+#include <cstdint>
 
 namespace bspmm {
 
@@ -25,9 +26,18 @@ struct StageBlock {
 // memory): the caller then copies from pageable memory.  Never waits.
 StageBlock stage_take(size_t bytes);
 
+// A copy that has been enqueued.
+struct StagedCopy {
+    const void* slot = nullptr;
+    uint32_t mark = 0;
+};
+
 // Enqueue the copy of the block's first `bytes` (a multiple of 16) to `dst` and hand the block back:
 // it is reused only after the copy has run.
-hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream);
+hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream, StagedCopy* copy);
+
+// Returns when the copy has run and what it wrote is visible to work enqueued from now on, on any stream.
+void stage_wait(const StagedCopy& copy);
 
 // Plans that exist: when the last one goes and none has been made for a second, idle blocks are freed.
 void stage_plan_made();

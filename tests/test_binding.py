@@ -79,3 +79,40 @@ def test_autograd_rows_of_no_operation_are_zero(gap):
         covered[int(o):int(o) + int(m)] = True
     got = C.detach().cpu().numpy()
     assert np.isfinite(got).all() and not got[~covered].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("made_on", ["current", "given"])
+def test_plan_runs_on_another_stream_than_it_was_made_on(made_on):
+    """No ordering between the streams by the caller: the tables (and the CSR arrays, from host memory)
+    have arrived before the first launch, and the data loader may reuse its arrays at once."""
+    import copy
+    import torch
+    from oracle import reference
+    b = W.random_general(11, 48, [(40, 30, 200), (7, 7, 0), (90, 110, 500)])
+    C0, S = reference.forward_batch(b)
+    G0, SG = reference.transposed_batch(b)
+    B, dY = torch.from_numpy(b.B).cuda(), torch.from_numpy(b.dY).cuda()
+    side, busy = torch.cuda.Stream(), torch.randn((2048, 2048), device="cuda:0")
+    torch.cuda.synchronize()
+    for _ in range(4):
+        loader = copy.deepcopy(b)
+        with torch.cuda.stream(torch.cuda.current_stream() if made_on == "given" else side):
+            with torch.cuda.stream(side):
+                for _ in range(4):
+                    busy @ busy            # the copy waits behind these
+            plan = K.Plan(loader, device="cuda:0", stream=side if made_on == "given" else None)
+            sizes = plan.rpt_len, plan.rpt_t_len, plan.nnz_total
+            for a in (loader.rows, loader.cols, loader.nnz, loader.rpt, loader.colids, loader.values):
+                a[:] = 0
+            assert sizes == (plan.rpt_len, plan.rpt_t_len, plan.nnz_total)
+            assert sizes == (int(b.rows.sum()) + 3, int(b.cols.sum()) + 3, int(b.nnz.sum()))
+        other = torch.cuda.Stream()
+        with torch.cuda.stream(other):
+            C = plan.run(B, torch.zeros((b.n_c_rows, b.F), device="cuda:0"))
+            G = plan.run_transposed(dY, torch.zeros((b.n_b_rows, b.F), device="cuda:0"))
+        other.synchronize()
+        # the bound of the other parity tests: 1e-5 of the sum of the products' magnitudes
+        assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
+        assert np.all(np.abs(G.cpu().numpy() - G0) <= 1e-5 * SG)
+        torch.cuda.synchronize()
