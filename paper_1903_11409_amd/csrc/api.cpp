@@ -1100,9 +1100,7 @@ bool capturing(hipStream_t s)
 // made on without the caller ordering the two, as when the tables went over in blocking copies.
 void settle(bspmm_plan* p, hipStream_t s)
 {
-    if (!p->upload.slot || s == p->upload_stream) return;
-    stage_wait(p->upload);
-    p->upload.slot = nullptr;
+    if (s != p->upload_stream) settle_upload(p);
 }
 
 int enqueue_build(bspmm_plan* p, hipStream_t s)
@@ -1723,6 +1721,13 @@ int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const b
                      void* workspace, size_t workspace_bytes, const HostFront& front, void* stream)
 {
     return create_csr(plan, b, F, options, workspace, workspace_bytes, &front, static_cast<hipStream_t>(stream));
+}
+
+void settle_upload(bspmm_plan* plan)
+{
+    if (!plan->upload.slot) return;
+    stage_wait(plan->upload);
+    plan->upload.slot = nullptr;
 }
 
 int64_t covered_rows(bspmm_plan* plan, bool transposed)

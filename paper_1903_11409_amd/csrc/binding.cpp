@@ -322,9 +322,11 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
         Py_RETURN_NONE;
     for (int i = 0; i < 3; ++i) csr.bytes[i] = host ? 4 * (size_t)len[i] : 0;
     if (!get_stream(a[13], &stream)) return nullptr;
-    // The memory belongs to the current stream: on another one the caller copies the arrays first, so
-    // that a plan dropped early leaves no copy on its way to memory that is somebody else's by then.
-    if (host && a[13] != Py_None && stream != c10::hip::getCurrentHIPStream().stream()) Py_RETURN_NONE;
+    // The memory belongs to the current stream: on another one the caller copies the arrays first and
+    // the tables have arrived when the call returns, so that a plan dropped early leaves no copy on its
+    // way to memory that is somebody else's by then.
+    const bool foreign = a[13] != Py_None && stream != c10::hip::getCurrentHIPStream().stream();
+    if (host && foreign) Py_RETURN_NONE;
     const bspmm_options* opt = static_cast<const bspmm_options*>(options);
     const size_t head = host ? csr.head() : 0;
     size_t need = 0;
@@ -350,6 +352,7 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
             b.values = static_cast<const float*>(dev[2]);
             rc = bspmm_create(&plan, &b, (int32_t)F, opt, base, need, stream);
         }
+        if (rc == BSPMM_OK && foreign) bspmm::settle_upload(plan);
     }
     Py_END_ALLOW_THREADS
     if (host && rc == BSPMM_ESTATE) Py_RETURN_NONE;
@@ -375,6 +378,7 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
     b.ids = static_cast<const int32_t*>(ids);
     b.values = static_cast<const float*>(values);
     if (!get_stream(a[11], &stream)) return nullptr;
+    const bool foreign = a[11] != Py_None && stream != c10::hip::getCurrentHIPStream().stream();   // (as in create)
     const bspmm_options* opt = static_cast<const bspmm_options*>(options);
     size_t need = 0;
     bspmm_plan* plan = nullptr;
@@ -388,6 +392,7 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
         need = need < kAlign ? kAlign : need;
         memory = device_bytes(need, device);
         rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
+        if (rc == BSPMM_OK && foreign) bspmm::settle_upload(plan);
     }
     Py_END_ALLOW_THREADS
     return rc == BSPMM_OK ? made(plan, b, memory, 0) : finish(rc, where, Py_None);

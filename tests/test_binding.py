@@ -116,3 +116,30 @@ def test_plan_runs_on_another_stream_than_it_was_made_on(made_on):
         assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
         assert np.all(np.abs(G.cpu().numpy() - G0) <= 1e-5 * SG)
         torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("coo", [False, True])
+def test_plan_made_on_another_stream_and_dropped_leaves_no_copy_behind(coo):
+    """The workspace goes back to the current stream's allocator: nothing may still be on its way there."""
+    import torch
+    b = W.random_general(11, 48, [(40, 30, 200), (7, 7, 0), (90, 110, 500)])
+    loader = type("Loader", (), dict(vars(b)))()
+    if not coo:
+        loader.rpt, loader.colids, loader.values = (torch.from_numpy(a).cuda() for a in (b.rpt, b.colids, b.values))
+    ids = np.zeros(2 * int(b.nnz.sum()), dtype=np.int32)
+    pairs = (torch.from_numpy(ids).cuda(), torch.zeros(int(b.nnz.sum()), device="cuda:0"))
+    options = K.make_options(flags=K.COO_DIRECT) if coo else None
+    side, busy = torch.cuda.Stream(), torch.randn((4096, 4096), device="cuda:0")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(4):
+            busy @ busy
+    plan = K.Plan(loader, b.F, options, device="cuda:0", stream=side, coo=pairs if coo else None)
+    size, at = plan.workspace.numel(), plan.workspace.data_ptr()
+    plan.close()
+    del plan
+    taken = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
+    assert taken.data_ptr() == at
+    torch.cuda.synchronize()
+    assert not bool(taken.any())
