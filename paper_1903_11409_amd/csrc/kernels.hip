@@ -860,13 +860,44 @@ __global__ void __launch_bounds__(kThreads) bspmm_kernel(const LaunchParams P)
 // arithmetic of the copies is scalar wherever the item decides it.
 // Results are bit for bit those of bspmm_kernel: same order of the additions inside a row.
 // ---------------------------------------------------------------------------------------
+// The second to fourth entry of a trip, of which `left` are the row's own: each is added by the lanes that
+// still have one.  (Adding the others with value zero would make a NaN of an infinite b.)  The three
+// sets of lanes are each part of the one before, so three compares that write the execution mask
+// and one move that restores it do, instead of a compare and a select per entry.
+__device__ __forceinline__ void add_rest(float4& acc, int left, float v1, const float4& b1, float v2,
+                                         const float4& b2, float v3, const float4& b3)
+{
+    uint64_t lanes;
+    asm("s_mov_b64 %[lanes], exec\n\t"
+        "v_cmpx_lt_i32_e32 vcc, 1, %[left]\n\t"
+        "v_fmac_f32_e32 %[x], %[v1], %[b1x]\n\t"
+        "v_fmac_f32_e32 %[y], %[v1], %[b1y]\n\t"
+        "v_fmac_f32_e32 %[z], %[v1], %[b1z]\n\t"
+        "v_fmac_f32_e32 %[w], %[v1], %[b1w]\n\t"
+        "v_cmpx_lt_i32_e32 vcc, 2, %[left]\n\t"
+        "v_fmac_f32_e32 %[x], %[v2], %[b2x]\n\t"
+        "v_fmac_f32_e32 %[y], %[v2], %[b2y]\n\t"
+        "v_fmac_f32_e32 %[z], %[v2], %[b2z]\n\t"
+        "v_fmac_f32_e32 %[w], %[v2], %[b2w]\n\t"
+        "v_cmpx_lt_i32_e32 vcc, 3, %[left]\n\t"
+        "v_fmac_f32_e32 %[x], %[v3], %[b3x]\n\t"
+        "v_fmac_f32_e32 %[y], %[v3], %[b3y]\n\t"
+        "v_fmac_f32_e32 %[z], %[v3], %[b3z]\n\t"
+        "v_fmac_f32_e32 %[w], %[v3], %[b3w]\n\t"
+        "s_mov_b64 exec, %[lanes]"
+        : [x] "+v"(acc.x), [y] "+v"(acc.y), [z] "+v"(acc.z), [w] "+v"(acc.w), [lanes] "=&s"(lanes)
+        : [left] "v"(left), [v1] "v"(v1), [b1x] "v"(b1.x), [b1y] "v"(b1.y), [b1z] "v"(b1.z), [b1w] "v"(b1.w),
+          [v2] "v"(v2), [b2x] "v"(b2.x), [b2y] "v"(b2.y), [b2z] "v"(b2.z), [b2w] "v"(b2.w), [v3] "v"(v3),
+          [b3x] "v"(b3.x), [b3y] "v"(b3.y), [b3z] "v"(b3.z), [b3w] "v"(b3.w)
+        : "vcc");
+}
+
 __device__ __forceinline__ float4 gather_row(const int2* cv, const char* bcol, int p0, int p1)
 {
     using V = Vec<4>;
     float4 acc = V::zero();
     // Four entries per trip, all their LDS reads in flight together, also on the last trip of
-    // a row: an entry past the end reads the row's last one and counts with value zero (the
-    // sum starts at +0 and can never become -0, so adding 0 * b leaves its bits unchanged).
+    // a row: an entry past the end reads the row's last one and is not added.
     const int last = p1 - 1;
     for (int p = p0; p < p1; p += 4) {
         const int2 e0 = cv[p], e1 = cv[min(p + 1, last)], e2 = cv[min(p + 2, last)],
@@ -876,9 +907,7 @@ __device__ __forceinline__ float4 gather_row(const int2* cv, const char* bcol, i
         const float4 b2 = *reinterpret_cast<const float4*>(bcol + e2.x);
         const float4 b3 = *reinterpret_cast<const float4*>(bcol + e3.x);
         V::fma(acc, __int_as_float(e0.y), b0);
-        V::fma(acc, p + 1 < p1 ? __int_as_float(e1.y) : 0.f, b1);
-        V::fma(acc, p + 2 < p1 ? __int_as_float(e2.y) : 0.f, b2);
-        V::fma(acc, p + 3 < p1 ? __int_as_float(e3.y) : 0.f, b3);
+        add_rest(acc, p1 - p, __int_as_float(e1.y), b1, __int_as_float(e2.y), b2, __int_as_float(e3.y), b3);
     }
     return acc;
 }
@@ -900,8 +929,9 @@ __device__ __forceinline__ float4 gather_row_global(const int2* cv, const char* 
         for (int u = 0; u < 4; ++u) e[u] = cv[min(p + u, last)];
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = *reinterpret_cast<const float4*>(src_l + (uint32_t)e[u].x);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) V::fma(acc, p + u < p1 ? __int_as_float(e[u].y) : 0.f, b[u]);
+        V::fma(acc, __int_as_float(e[0].y), b[0]);
+        add_rest(acc, p1 - p, __int_as_float(e[1].y), b[1], __int_as_float(e[2].y), b[2], __int_as_float(e[3].y),
+                 b[3]);
     }
     return acc;
 }
@@ -989,14 +1019,14 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
                     const int q = min(p + u, p1 - 1);
                     const int c = ci[q];
                     cc[u] = (unsigned)c < (unsigned)k ? c : 0;
-                    aa[u] = p + u < p1 ? va[q] : 0.f;
+                    aa[u] = va[q];
                 }
                 float4 b[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     b[u] = *reinterpret_cast<const float4*>(src_l + __umul24((uint32_t)cc[u], row_bytes));
-#pragma unroll
-                for (int u = 0; u < 4; ++u) Vec<4>::fma(acc, aa[u], b[u]);
+                Vec<4>::fma(acc, aa[0], b[0]);
+                add_rest(acc, p1 - p, aa[1], b[1], aa[2], b[2], aa[3], b[3]);
             }
         }
         store_out<4>(reinterpret_cast<float*>(dst + (__umul24(i, out_row_bytes) + (l << 4))), acc);
@@ -1051,7 +1081,7 @@ __device__ __forceinline__ typename Floats<VEC>::type any_load(const void* p)
 
 // Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's floats of the
 // entry's dense row.  N entries in flight while there are as many, then four at a time with the
-// entries past the end counting as zero (see gather_row).
+// entries past the end left out (see gather_row).
 template <int VEC, typename Entry, typename Dense>
 __device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
 {
@@ -1081,8 +1111,21 @@ __device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, En
         for (int u = 0; u < 4; ++u) e[u] = entry(min(p + u, last));
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = dense(e[u].x);
+        fma(__int_as_float(e[0].y), b[0]);
+        if constexpr (VEC == 4) {
+            auto f4 = [](const VT& v) { return make_float4(v[0], v[1], v[2], v[3]); };
+            float4 sum = f4(acc);
+            add_rest(sum, p1 - p, __int_as_float(e[1].y), f4(b[1]), __int_as_float(e[2].y), f4(b[2]),
+                     __int_as_float(e[3].y), f4(b[3]));
+            acc[0] = sum.x, acc[1] = sum.y, acc[2] = sum.z, acc[3] = sum.w;
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) fma(p + u < p1 ? __int_as_float(e[u].y) : 0.f, b[u]);
+            for (int u = 1; u < 4; ++u) {
+                const VT old = acc;
+                fma(__int_as_float(e[u].y), b[u]);
+                if (p + u >= p1) acc = old;
+            }
+        }
     }
     return acc;
 }

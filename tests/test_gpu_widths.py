@@ -80,3 +80,38 @@ def test_small_operations_share_a_workgroup(oracle, F, in_off):
         got = _run(torch, plan, b, transposed, in_off, 0, 0, 0)
         ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
         _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
+
+
+@pytest.mark.parametrize("F,flags", [(50, 0), (100, 0), (127, 0), (64, 0), (128, 0), (64, K.ACCUMULATE),
+                                     (50, K.ACCUMULATE)])
+@pytest.mark.parametrize("shapes", [SHAPES, [(30, 40, 85)] * 12, [(8, 9, 31)] * 4000])
+def test_infinite_and_nan_inputs(oracle, F, flags, shapes):
+    """Infinities stay infinities: entries that fill up the last trip of a row count as nothing, not as
+    0 * inf (staged tiles, row blocks, long rows, small operations, summed sets)."""
+    import torch
+    b = W.random_general(5 + F, F=F, shapes=shapes)
+    if flags & K.ACCUMULATE:                           # pairs of operations of one shape, summed
+        for i in range(1, b.batch, 2):
+            if b.rows[i] == b.rows[i - 1]:
+                b.c_row_off[i] = b.c_row_off[i - 1]
+    rng = np.random.default_rng(F)
+    for x in (b.B, b.dY):
+        x[rng.random(x.shape) < 0.03] = np.inf
+        x[rng.random(x.shape) < 0.03] = -np.inf
+        x[rng.random(x.shape) < 0.002] = np.nan
+    plan = K.Plan(b, F, K.make_options(flags=flags))
+    got = torch.zeros((b.n_c_rows, F), device="cuda")
+    plan.run(torch.from_numpy(b.B).cuda(), got)
+    got = got.cpu().numpy()
+    ref = np.zeros((b.n_c_rows, F))
+    with np.errstate(invalid="ignore"):
+        for i in range(b.batch):
+            rpt = b.rpt[b.rpt_off[i]:b.rpt_off[i] + b.rows[i] + 1]
+            at = slice(b.nz_off[i], b.nz_off[i] + b.nnz[i])
+            row = np.repeat(np.arange(b.rows[i]), np.diff(rpt))
+            np.add.at(ref, b.c_row_off[i] + row,
+                      b.values[at, None].astype(np.float64) * b.B[b.b_row_off[i] + b.colids[at]])
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    finite = np.isfinite(ref)
+    np.testing.assert_array_equal(got[~finite], ref[~finite].astype(np.float32))
+    assert np.isfinite(got[finite]).all()
