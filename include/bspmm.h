@@ -170,20 +170,24 @@ typedef struct bspmm_coo_batch {
 typedef struct bspmm_options {
     uint32_t flags;            /* BSPMM_DRY_RUN | BSPMM_BUILD_TRANSPOSE | BSPMM_SPLIT_HUB_ROWS */
     int32_t  force_bin;        /* 0 = automatic; 1+b forces bin b for every op that fits it    */
-    int32_t  lds_bytes;        /* LDS per workgroup; <= 160 KiB (all of a CU's).  0 = 24 KiB,
+    int32_t  lds_bytes;        /* LDS per workgroup; <= 160 KiB (all of a CU's).  0 = 20, 24
+                                  or 40 KiB by what bounds the launch,
                                   and 80 KiB, then 160 KiB, are tried before a batch whose
                                   summed operations need more is refused with ETOOBIG; 52 KiB
                                   (tiles twice as wide) for F >= 512 when the launch moves
-                                  more than 28 MB in more than one round of workgroups and
+                                  28 to 70 MB in more than one round of workgroups and
                                   needs at most a tenth more rounds that way.  bspmm_info.lds_bytes says
                                   what was taken                                              */
     int32_t  min_tile;         /* narrowest feature tile in floats, 0 = default (32)           */
     int32_t  max_tile;         /* widest feature tile in floats, 0 = default (256), <= 256     */
-    int32_t  target_workgroups;/* split tiles until the launch has this many, 0 = 4 per CU    */
+    int32_t  target_workgroups;/* split tiles until the launch has this many, 0 = 4 per CU, or,
+                                  where every operation has an output block of its own, the
+                                  widest tiles and row ranges by what bounds the launch       */
     int32_t  compute_units;    /* 0 = ask the device (256 assumed for dry runs)                */
     int32_t  lds_pad;          /* floats added to each staged B row, 0 = default, -1 = none    */
     int32_t  max_passes;       /* row passes a sub-workgroup slot may take, 0 = default (1)    */
-    int32_t  generic_rows;     /* rows per generic row block, 0 = default (8)                   */
+    int32_t  generic_rows;     /* rows per generic row block, 0 = default (8; up to 64 at narrow
+                                  widths, as many as a workgroup has in flight)               */
     int32_t  wg_passes;        /* row passes of a workgroup item before it is cut into row
                                   ranges: 0 = cut only while the launch is short of
                                   target_workgroups, N > 0 = always cap at N, -1 = never cut   */
