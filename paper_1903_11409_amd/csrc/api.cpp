@@ -119,8 +119,8 @@ struct bspmm_plan {
                                            // kernels take them in
     ItemTable lean_items[2];            // per direction: the compact item table of a `whole` schedule
     bool lean_shared = false;              // both directions run from the forward table
-    int32_t lean_rows[2] = {0, 0};         // most input rows / output rows of an operation: bounds
-    int32_t lean_out_rows[2] = {0, 0};     // of the 32-bit offsets the lean kernel forms per call
+    int32_t lean_rows[2] = {0, 0};         // most input rows / output rows of an operation, or of a summed
+    int32_t lean_out_rows[2] = {0, 0};     // set that is one item: bounds of the lean kernel's 32-bit offsets
     bool lean_blocks[2] = {false, false};  // the lean table has row blocks of the generic bin ...
     bool lean_hints_built[2] = {false, false};   // ... and the device has filled in their entry ranges
     StagedCopy upload;          // the copy of the tables from pinned memory, until it is known to have run ...
@@ -693,6 +693,8 @@ void make_lean_items(bspmm_plan& p, int d)
         return;
     }
     for (const WorkItem& w : sc.items) {
+        p.lean_rows[d] = std::max(p.lean_rows[d], w.k);   // (a summed set's: the rows of all its members)
+        p.lean_out_rows[d] = std::max(p.lean_out_rows[d], w.m);
         LeanItem t;
         std::memset(&t, 0, sizeof t);
         if (w.nrows > 0) {
@@ -771,6 +773,7 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
     int64_t nz_pack = 0;
     int64_t scratch_words = 0;
     int build_lds_words = 0;
+    for (int d = 0; d < 2; ++d) p.lean_rows[d] = p.lean_out_rows[d] = 0;
     f.m.assign(b->rows, b->rows + n), f.k.assign(b->cols, b->cols + n), f.nnz.assign(b->nnz, b->nnz + n);
     f.rpt_off.assign(b->rpt_off, b->rpt_off + n), f.nz_off.assign(b->nz_off, b->nz_off + n);
     f.in_off.assign(b->b_row_off, b->b_row_off + n), f.out_off.assign(b->c_row_off, b->c_row_off + n);
@@ -901,8 +904,10 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
         csr_f += 4 * ((int64_t)b->rows[i] + 1) + 8 * (int64_t)b->nnz[i];
         csr_t += 4 * ((int64_t)b->cols[i] + 1) + 8 * (int64_t)b->nnz[i];
         nnz += b->nnz[i];
-        p.lean_rows[0] = p.lean_out_rows[1] = std::max(p.lean_rows[0], b->cols[i]);
-        p.lean_out_rows[0] = p.lean_rows[1] = std::max(p.lean_rows[1], b->rows[i]);
+        for (int d = 0; d < 2; ++d) {
+            p.lean_rows[d] = std::max(p.lean_rows[d], d ? b->rows[i] : b->cols[i]);
+            p.lean_out_rows[d] = std::max(p.lean_out_rows[d], d ? b->cols[i] : b->rows[i]);
+        }
         if (b->rows[i] > 0 && b->cols[i] > 0) p.reads_dense = true;
     }
     p.effective_bytes[0] = csr_f + in_f + out_f;
@@ -1238,14 +1243,8 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     const int hrc = enqueue_hints(p, d, s);
     if (hrc != BSPMM_OK) return hrc;
     const LeanItem* items = reinterpret_cast<const LeanItem*>(p->ws + p->lay.lean[d]);
-    // the lean kernel forms 32-bit byte offsets inside an operation's dense blocks and multiplies
-    // in 24 bits: leading dimensions below 4 Mi floats, blocks below 4 GiB
-    constexpr int64_t kMul24 = (int64_t)1 << 22, kOff32 = (int64_t)1 << 30;
-    const bool lean = sc.pow2 && vec4 && ld_in < kMul24 && ld_out < kMul24 &&
-                      (int64_t)p->lean_rows[d] * ld_in < kOff32 &&
-                      (int64_t)p->lean_out_rows[d] * ld_out < kOff32;
     hipError_t e;
-    if (lean) {
+    if (vec4 && takes_lean_kernel(p, d, ld_in, ld_out)) {
         e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, !sc.merged_sets.empty(), s);
     } else {
         // (the table's packed items follow the launch's own: here each is a workgroup)
@@ -1728,6 +1727,16 @@ void settle_upload(bspmm_plan* plan)
     if (!plan->upload.slot) return;
     stage_wait(plan->upload);
     plan->upload.slot = nullptr;
+}
+
+// (it forms 32-bit byte offsets inside an operation's dense blocks and multiplies in 24 bits: leading
+// dimensions below 4 Mi floats, blocks below 4 GiB)
+bool takes_lean_kernel(const bspmm_plan* plan, bool transposed, int64_t ld_in, int64_t ld_out)
+{
+    constexpr int64_t kMul24 = (int64_t)1 << 22, kOff32 = (int64_t)1 << 30;
+    const int d = transposed ? 1 : 0;
+    return plan->sched[d].pow2 && ld_in < kMul24 && ld_out < kMul24 &&
+           (int64_t)plan->lean_rows[d] * ld_in < kOff32 && (int64_t)plan->lean_out_rows[d] * ld_out < kOff32;
 }
 
 int64_t covered_rows(bspmm_plan* plan, bool transposed)

@@ -408,6 +408,18 @@ PyObject* covered_rows(PyObject* const* a, Py_ssize_t n)
     return PyLong_FromLongLong(plan ? bspmm::covered_rows(static_cast<bspmm_plan*>(plan), transposed) : 0);
 }
 
+// (plan, transposed, ld_in, ld_out) -> whether that product runs in the lean kernel
+PyObject* takes_lean_kernel(PyObject* const* a, Py_ssize_t n)
+{
+    void* plan;
+    int64_t ld_in, ld_out;
+    if (!arity("takes_lean_kernel", n, 4) || !get_ptr(a[0], &plan) || !get_i64(a[2], &ld_in) || !get_i64(a[3], &ld_out))
+        return nullptr;
+    const int transposed = PyObject_IsTrue(a[1]);
+    if (transposed < 0) return nullptr;
+    return PyBool_FromLong(plan && bspmm::takes_lean_kernel(static_cast<bspmm_plan*>(plan), transposed, ld_in, ld_out));
+}
+
 // C++ exceptions of PyTorch (no device, out of memory) become Python's.
 template <PyObject* (*FN)(PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject*, PyObject* const* a, Py_ssize_t n)
@@ -433,7 +445,7 @@ PyMethodDef methods[] = {
     {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&setup)), METH_FASTCALL, nullptr},
     fast<plan_run>("plan_run"), fast<plan_run_transposed>("plan_run_transposed"), fast<plan_run_gcn>("plan_run_gcn"),
     fast<run>("run"), fast<run_transposed>("run_transposed"), fast<run_gcn>("run_gcn"),
-    fast<covered_rows>("covered_rows"), fast<create>("create"), fast<create_coo>("create_coo"),
+    fast<covered_rows>("covered_rows"), fast<takes_lean_kernel>("takes_lean_kernel"), fast<create>("create"), fast<create_coo>("create_coo"),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Plan creation and run calls of libbspmm.", -1, methods,
                       nullptr, nullptr, nullptr, nullptr};

@@ -1,4 +1,5 @@
-// Plan creation from arrays in host memory, for the Python binding (not part of the C ABI).
+// What the Python binding and the tests ask a plan beside the C ABI: creation from arrays in host memory,
+// covered rows, the kernel a product takes.
 #pragma once
 
 #include <cstddef>
@@ -28,5 +29,8 @@ void settle_upload(bspmm_plan* plan);
 // Rows from the first on, without a gap, that belong to an operation's output: of C, or of G with
 // `transposed`.
 int64_t covered_rows(bspmm_plan* plan, bool transposed);
+
+// Whether a product with these leading dimensions, on operands aligned to 16 bytes, runs in the lean kernel.
+bool takes_lean_kernel(const bspmm_plan* plan, bool transposed, int64_t ld_in, int64_t ld_out);
 
 }  // namespace bspmm

@@ -778,6 +778,24 @@ def test_what_the_lean_kernel_does_not_do_keeps_the_general_one(why, maker, F, o
     assert lean == [0, 0], why
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+def test_lean_kernel_needs_offsets_of_32_bits_inside_a_summed_set(transposed):
+    """Eight operations of 40 rows that are summed run as one item of 320 dense rows: what has to stay
+    below 4 GiB is that block, not one member's (the kernel would wrap round and read other rows)."""
+    n = np.full(8, 40, dtype=np.int32)
+    at, zero = 40 * np.arange(8, dtype=np.int64), np.zeros(8, dtype=np.int64)
+    own, one = (zero, at) if transposed else (at, zero)       # (b_row_off, c_row_off)
+    hb = K.HostBatch(n, n, np.full(8, 60, np.int32), 41 * np.arange(8), 60 * np.arange(8), own, one)
+    plan = K.bspmm_create(hb, 16, K.make_options(flags=K.DRY_RUN | K.ACCUMULATE))
+    info, lean = K.bspmm_plan_info(plan), K.native().takes_lean_kernel
+    assert info.transposed_supported == 1 and info.fused_tasks[int(transposed)] == 0
+    limit = (1 << 30) // 320                                  # floats from row to row at which 320 of them reach it
+    assert lean(plan, transposed, 16, 16) and lean(plan, transposed, limit - 4, 16)
+    assert 40 * (limit + 4) < 1 << 30 and not lean(plan, transposed, limit + 4, 16)
+    assert lean(plan, transposed, 16, (1 << 22) - 4) and not lean(plan, transposed, 16, 1 << 22)
+    K.bspmm_destroy(plan)
+
+
 def test_summed_channels_and_fused_fronts_keep_the_general_kernel():
     c = W.config3_multichannel(graphs=32, accumulate=True)
     assert _lean_of(c, flags=K.ACCUMULATE)[0] == [0, 0]
