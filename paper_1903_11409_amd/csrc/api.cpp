@@ -1729,13 +1729,14 @@ void settle_upload(bspmm_plan* plan)
     plan->upload.slot = nullptr;
 }
 
-// (it forms 32-bit byte offsets inside an operation's dense blocks and multiplies in 24 bits: leading
-// dimensions below 4 Mi floats, blocks below 4 GiB)
+// (it forms 32-bit byte offsets inside an operation's dense blocks and multiplies a row's index and its
+// bytes in 24 bits each: leading dimensions below 4 Mi floats, blocks below 4 GiB and 16 Mi rows)
 bool takes_lean_kernel(const bspmm_plan* plan, bool transposed, int64_t ld_in, int64_t ld_out)
 {
     constexpr int64_t kMul24 = (int64_t)1 << 22, kOff32 = (int64_t)1 << 30;
+    constexpr int32_t kRows24 = 1 << 24;
     const int d = transposed ? 1 : 0;
-    return plan->sched[d].pow2 && ld_in < kMul24 && ld_out < kMul24 &&
+    return plan->sched[d].pow2 && ld_in < kMul24 && ld_out < kMul24 && plan->lean_rows[d] <= kRows24 &&
            (int64_t)plan->lean_rows[d] * ld_in < kOff32 && (int64_t)plan->lean_out_rows[d] * ld_out < kOff32;
 }
 

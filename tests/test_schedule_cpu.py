@@ -796,6 +796,15 @@ def test_lean_kernel_needs_offsets_of_32_bits_inside_a_summed_set(transposed):
     K.bspmm_destroy(plan)
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+def test_lean_kernel_needs_row_indices_of_24_bits(extra):
+    one, zero = np.ones(1, dtype=np.int32), np.zeros(1, dtype=np.int64)
+    hb = K.HostBatch(4 * one, ((1 << 24) + extra) * one, 5 * one, zero, zero, zero, zero)
+    plan = K.bspmm_create(hb, 16, K.make_options(flags=K.DRY_RUN))
+    assert K.native().takes_lean_kernel(plan, False, 16, 16) == (extra == 0)
+    K.bspmm_destroy(plan)
+
+
 def test_summed_channels_and_fused_fronts_keep_the_general_kernel():
     c = W.config3_multichannel(graphs=32, accumulate=True)
     assert _lean_of(c, flags=K.ACCUMULATE)[0] == [0, 0]
