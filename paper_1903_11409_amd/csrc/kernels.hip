@@ -1269,7 +1269,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     const bool run = !ALIGNED && windows && fw == (uint32_t)ld_in;   // (f0 is 0 then)
     const uint32_t stride = run ? fw : chunks << 2;  // words from row to row in LDS
     if (run) {
-        const uint32_t shift = (uint32_t)at & 3;
+        const uint32_t shift = k > 0 ? (uint32_t)at & 3 : 0;     // (no rows: nothing is read, `in` may be null)
         const float* __restrict__ src = in + (at - shift);
         const uint32_t words = (uint32_t)k * fw + shift, total = words >> 2, rest = words & 3;
         for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads)

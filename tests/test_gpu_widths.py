@@ -51,6 +51,22 @@ def test_every_width_both_directions(oracle, F):
         _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
 
 
+@pytest.mark.parametrize("F", [1, 3, 50, 127])
+def test_operations_without_columns_read_nothing(F):
+    """No operation has columns, so there is no dense input at all, wherever the (empty) blocks start."""
+    import torch
+    rows, zero = np.array([5, 300], dtype=np.int32), np.zeros(2, dtype=np.int64)
+    rpt = torch.zeros(307, dtype=torch.int32, device="cuda")
+    hb = K.HostBatch(rows, zero, zero, [0, 6], zero, [1, 2], [0, 5], rpt)
+    ws = torch.empty(K.bspmm_workspace_bytes(hb, F), dtype=torch.uint8, device="cuda")
+    plan = K.bspmm_create(hb, F, None, ws, ws.numel())
+    C = torch.full((305, F), SENTINEL, device="cuda")
+    K.bspmm_run(plan, None, C, F, F)
+    torch.cuda.synchronize()
+    assert not bool(C.any())
+    K.bspmm_destroy(plan)
+
+
 @pytest.mark.parametrize("F", [48, 50, 61])
 @pytest.mark.parametrize("in_off,out_off,in_extra,out_extra", [(1, 0, 0, 0), (2, 3, 0, 0), (0, 1, 0, 0), (0, 0, 1, 3),
                                                                (4, 0, 2, 0), (3, 1, 5, 2)])
