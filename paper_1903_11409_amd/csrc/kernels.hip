@@ -1266,7 +1266,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     const int64_t at = (int64_t)it.in_row * ld_in + it.f0;
     const bool windows = ALIGNED || (mode & kAnyWindows);     // (the same for the whole launch)
     const uint32_t chunks = (uint32_t)tile_stride((int)fw, ALIGNED || (mode & kAnyTight)) >> 2;
-    const bool run = !ALIGNED && windows && fw == (uint32_t)ld_in;   // (f0 is 0 then)
+    const bool run = !ALIGNED && windows && (int64_t)fw == ld_in;   // (f0 is 0 then)
     const uint32_t stride = run ? fw : chunks << 2;  // words from row to row in LDS
     if (run) {
         const uint32_t shift = k > 0 ? (uint32_t)at & 3 : 0;     // (no rows: nothing is read, `in` may be null)

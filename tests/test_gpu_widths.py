@@ -67,6 +67,22 @@ def test_operations_without_columns_read_nothing(F):
     K.bspmm_destroy(plan)
 
 
+def test_leading_dimension_that_is_the_width_in_its_low_32_bits():
+    """Two rows 16 GiB apart are not a packed matrix (17 floats wide: 2^32 + 17 floats from row to row)."""
+    import torch
+    F, ld = 17, (1 << 32) + 17
+    store = torch.empty(ld + F, device="cuda")
+    store[F:2 * F] = float("nan")                         # what a packed second row would be
+    b = W.random_general(3, F, [(6, 2, 12)])
+    for r in range(2):
+        store[r * ld:r * ld + F] = torch.from_numpy(b.B[r]).cuda()
+    plan = K.Plan(b)
+    got, want = torch.empty((6, F), device="cuda"), torch.empty((6, F), device="cuda")
+    K.bspmm_run(plan.handle, store, got, ld, F)
+    plan.run(torch.from_numpy(b.B).cuda(), want)
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("F", [48, 50, 61])
 @pytest.mark.parametrize("in_off,out_off,in_extra,out_extra", [(1, 0, 0, 0), (2, 3, 0, 0), (0, 1, 0, 0), (0, 0, 1, 3),
                                                                (4, 0, 2, 0), (3, 1, 5, 2)])
