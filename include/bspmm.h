@@ -39,7 +39,7 @@
  * are best created with that flag or run once before the capture).  Calls on one plan must be
  * issued from one host thread at a time and on the stream order the caller wants.  The first call
  * on another stream than the plan was created on waits on the host, if need be, until creation's
- * copy of the tables has run.
+ * copy of the tables has run (EHIP when the work before it failed and it never will).
  *
  * Errors.  Every int-returning call returns BSPMM_OK or a negative BSPMM_E* code; nothing is
  * printed, thrown or aborted.  Device-side contents of rpt/colids are trusted by run calls;

@@ -1103,9 +1103,9 @@ bool capturing(hipStream_t s)
 
 // Before work on `s` that reads the plan's tables: a plan may be used on another stream than it was
 // made on without the caller ordering the two, as when the tables went over in blocking copies.
-void settle(bspmm_plan* p, hipStream_t s)
+int settle(bspmm_plan* p, hipStream_t s)
 {
-    if (s != p->upload_stream) settle_upload(p);
+    return s != p->upload_stream ? settle_upload(p) : BSPMM_OK;
 }
 
 int enqueue_build(bspmm_plan* p, hipStream_t s)
@@ -1722,11 +1722,13 @@ int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const b
     return create_csr(plan, b, F, options, workspace, workspace_bytes, &front, static_cast<hipStream_t>(stream));
 }
 
-void settle_upload(bspmm_plan* plan)
+int settle_upload(bspmm_plan* plan)
 {
-    if (!plan->upload.slot) return;
-    stage_wait(plan->upload);
+    if (!plan->upload.slot) return BSPMM_OK;
+    const hipError_t e = stage_wait(plan->upload, plan->upload_stream);
+    if (e != hipSuccess) return hip_fail(e);
     plan->upload.slot = nullptr;
+    return BSPMM_OK;
 }
 
 // (it forms 32-bit byte offsets inside an operation's dense blocks and multiplies a row's index and its
@@ -1893,7 +1895,8 @@ int bspmm_run(bspmm_plan* plan, const float* B, float* C, int64_t ldb, int64_t l
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || displaced(plan)) return BSPMM_ESTATE;
-    settle(plan, static_cast<hipStream_t>(stream));
+    const int rc = settle(plan, static_cast<hipStream_t>(stream));
+    if (rc != BSPMM_OK) return rc;
     return run_direction(plan, 0, B, C, ldb, ldc, static_cast<hipStream_t>(stream));
 }
 
@@ -1902,7 +1905,8 @@ int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W,
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || plan->knobs.front <= 0 || plan->coo_direct || displaced(plan)) return BSPMM_ESTATE;
-    settle(plan, static_cast<hipStream_t>(stream));
+    const int rc = settle(plan, static_cast<hipStream_t>(stream));
+    if (rc != BSPMM_OK) return rc;
     return run_gcn(plan, X, ldx, W, ldw, bias, Y, ldy, accumulate, static_cast<hipStream_t>(stream));
 }
 
@@ -1911,12 +1915,13 @@ int bspmm_run_transposed(bspmm_plan* plan, const float* dY, float* G, int64_t ld
 {
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || !plan->transposed_supported || displaced(plan)) return BSPMM_ESTATE;
-    settle(plan, static_cast<hipStream_t>(stream));
+    int rc = settle(plan, static_cast<hipStream_t>(stream));
+    if (rc != BSPMM_OK) return rc;
     if (plan->coo_direct)
         return run_direction(plan, 1, dY, G, ldy, ldg, static_cast<hipStream_t>(stream));
     if (plan->sched[1].grid > 0 && ((!dY && plan->reads_dense) || !G || ldy < plan->F || ldg < plan->F))
         return BSPMM_EINVAL;
-    int rc = enqueue_build(plan, static_cast<hipStream_t>(stream));
+    rc = enqueue_build(plan, static_cast<hipStream_t>(stream));
     if (rc != BSPMM_OK) return rc;
     return run_direction(plan, 1, dY, G, ldy, ldg, static_cast<hipStream_t>(stream));
 }
@@ -1927,8 +1932,8 @@ int bspmm_export_transposed(bspmm_plan* plan, int32_t* rpt_t, int32_t* colids_t,
     if (!plan) return BSPMM_EINVAL;
     if (plan->dry || plan->coo_direct || plan->knobs.symmetric || displaced(plan)) return BSPMM_ESTATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    settle(plan, s);
-    int rc = enqueue_build(plan, s);
+    int rc = settle(plan, s);
+    if (rc == BSPMM_OK) rc = enqueue_build(plan, s);
     if (rc != BSPMM_OK) return rc;
     size_t rpt_words = 0, nz = 0;
     for (int i = 0; i < plan->batch; ++i) {
@@ -1958,7 +1963,8 @@ int bspmm_validate(bspmm_plan* plan, int32_t* bad_op, void* stream)
     if (plan->dry || displaced(plan)) return BSPMM_ESTATE;
     if (bad_op) *bad_op = -1;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    settle(plan, s);
+    const int rc = settle(plan, s);
+    if (rc != BSPMM_OK) return rc;
     int32_t* flag = reinterpret_cast<int32_t*>(plan->ws + plan->lay.flag);
     hipError_t e = plan->from_coo
         ? launch_validate_coo(reinterpret_cast<const OpRecord*>(plan->ws + plan->lay.coo_records),

@@ -352,7 +352,7 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
             b.values = static_cast<const float*>(dev[2]);
             rc = bspmm_create(&plan, &b, (int32_t)F, opt, base, need, stream);
         }
-        if (rc == BSPMM_OK && foreign) bspmm::settle_upload(plan);
+        if (rc == BSPMM_OK && foreign && (rc = bspmm::settle_upload(plan)) != BSPMM_OK) bspmm_destroy(plan);
     }
     Py_END_ALLOW_THREADS
     if (host && rc == BSPMM_ESTATE) Py_RETURN_NONE;
@@ -392,7 +392,7 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
         need = need < kAlign ? kAlign : need;
         memory = device_bytes(need, device);
         rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
-        if (rc == BSPMM_OK && foreign) bspmm::settle_upload(plan);
+        if (rc == BSPMM_OK && foreign && (rc = bspmm::settle_upload(plan)) != BSPMM_OK) bspmm_destroy(plan);
     }
     Py_END_ALLOW_THREADS
     return rc == BSPMM_OK ? made(plan, b, memory, 0) : finish(rc, where, Py_None);

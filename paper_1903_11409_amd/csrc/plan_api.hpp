@@ -23,8 +23,8 @@ struct HostFront {
 int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const bspmm_options* options,
                      void* workspace, size_t workspace_bytes, const HostFront& front, void* stream);
 
-// Returns when the plan's tables are on the device.
-void settle_upload(bspmm_plan* plan);
+// Returns when the plan's tables are on the device; EHIP when they will not get there.
+int settle_upload(bspmm_plan* plan);
 
 // Rows from the first on, without a gap, that belong to an operation's output: of C, or of G with
 // `transposed`.

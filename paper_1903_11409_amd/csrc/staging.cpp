@@ -148,20 +148,28 @@ hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream,
     return e;
 }
 
-void stage_wait(const StagedCopy& copy)
+hipError_t stage_wait(const StagedCopy& copy, hipStream_t stream)
 {
     Pool& p = pool();
-    for (;;) {
-        {
-            // (a block that has gone, or carries another mark, was idle in between: the copy has run)
-            std::lock_guard<std::mutex> g(p.lock);
-            bool under_way = false;
-            for (auto& s : p.slots)
-                if (s.get() == copy.slot && s->mark == copy.mark && s->state == Slot::kCopying) under_way = !idle(*s);
-            if (!under_way) return;
-        }
-        std::this_thread::yield();
-    }
+    auto done = [&] {
+        // (a block that has gone, or carries another mark, was idle in between: the copy has run)
+        std::lock_guard<std::mutex> g(p.lock);
+        for (auto& s : p.slots)
+            if (s.get() == copy.slot && s->mark == copy.mark && s->state == Slot::kCopying) return idle(*s);
+        return true;
+    };
+    auto state = [&]() -> hipError_t {
+        if (stream == hipStreamPerThread) return hipErrorNotReady;     // (names this thread's stream here)
+        const RelaxedCapture relaxed;      // (the caller may be recording a graph on its stream)
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(stream, &st);
+        // (a stream that has begun to record since then, or the null stream while another one records, cannot
+        // be asked; what came before still runs)
+        if (e == hipSuccess) e = st == hipStreamCaptureStatusNone ? hipStreamQuery(stream) : hipErrorNotReady;
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipErrorStreamCaptureImplicit ? hipErrorNotReady : e;
+    };
+    return wait_until(done, state);
 }
 
 void stage_plan_made()

@@ -8,8 +8,10 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <chrono>
 #include <cstddef>
 #include <cstdint>
+#include <thread>
 
 namespace bspmm {
 
@@ -36,8 +38,26 @@ struct StagedCopy {
 // it is reused only after the copy has run.
 hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream, StagedCopy* copy);
 
-// Returns when the copy has run and what it wrote is visible to work enqueued from now on, on any stream.
-void stage_wait(const StagedCopy& copy);
+// Returns hipSuccess when the copy, which was enqueued on `stream`, has run and what it wrote is visible to
+// work enqueued from now on, on any stream; the error when it never will.
+hipError_t stage_wait(const StagedCopy& copy, hipStream_t stream);
+
+// The wait itself: until done(), but no longer than state() (what the runtime says of the work waited for)
+// is hipErrorNotReady.  state() is asked from the second millisecond on only, ten times a millisecond.
+template <typename Done, typename State>
+hipError_t wait_until(Done done, State state)
+{
+    using Clock = std::chrono::steady_clock;
+    Clock::time_point ask = Clock::now() + std::chrono::milliseconds(1);
+    while (!done()) {
+        std::this_thread::yield();
+        if (Clock::now() < ask) continue;
+        const hipError_t e = state();
+        if (e != hipErrorNotReady) return done() ? hipSuccess : e == hipSuccess ? hipErrorUnknown : e;
+        std::this_thread::sleep_for(std::chrono::microseconds(100));
+    }
+    return hipSuccess;
+}
 
 // Plans that exist: when the last one goes and none has been made for a second, idle blocks are freed.
 void stage_plan_made();

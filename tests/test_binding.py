@@ -40,6 +40,40 @@ def test_native_calls_check_their_arguments():
         n.run(None, None, None, "x", 1, 0)
 
 
+WAIT = r"""
+#include "staging.hpp"
+#include <cstdio>
+int main()
+{
+    using bspmm::wait_until;
+    int asked = 0, turns = 0;
+    auto state = [&](hipError_t last, int after) { return [&asked, last, after] { return ++asked > after ? last : hipErrorNotReady; }; };
+    auto never = [] { return false; };
+    auto soon = [&] { return ++turns > 3; };
+    if (wait_until(soon, state(hipErrorUnknown, 0)) != hipSuccess || asked != 0) return 1;     // not asked at once
+    if (wait_until(never, state(hipErrorLaunchFailure, 2)) != hipErrorLaunchFailure || asked != 3) return 2;
+    asked = 0;
+    if (wait_until(never, state(hipSuccess, 1)) != hipErrorUnknown) return 3;   // the stream is through, the copy is not
+    asked = 0;
+    if (wait_until([&] { return asked > 4; }, state(hipSuccess, 4)) != hipSuccess) return 4;    // done while it was asked
+    std::puts("ok");
+}
+"""
+
+
+def test_wait_for_the_tables_ends_with_the_error_of_the_stream(tmp_path):
+    """A copy that never runs is an error of the call that waits for it, not a wait without end."""
+    import os
+    import subprocess
+    from paper_1903_11409_amd import build
+    src, exe = tmp_path / "wait.cpp", tmp_path / "wait"
+    src.write_text(WAIT)
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-I" + build.CSRC,
+                    "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), str(src), "-o",
+                    str(exe), "-pthread"], check=True, timeout=120)
+    assert subprocess.run([str(exe)], capture_output=True, timeout=30, text=True).stdout == "ok\n"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,ld", [(1, 64), (1, 72), (7, 64), (7, 68), (7, 65)])
 @pytest.mark.parametrize("stream", ["current", "object", "handle"])
