@@ -1103,9 +1103,10 @@ bool capturing(hipStream_t s)
 
 // Before work on `s` that reads the plan's tables: a plan may be used on another stream than it was
 // made on without the caller ordering the two, as when the tables went over in blocking copies.
+// (hipStreamPerThread is one handle for the streams of all threads)
 int settle(bspmm_plan* p, hipStream_t s)
 {
-    return s != p->upload_stream ? settle_upload(p) : BSPMM_OK;
+    return s != p->upload_stream || s == hipStreamPerThread ? settle_upload(p) : BSPMM_OK;
 }
 
 int enqueue_build(bspmm_plan* p, hipStream_t s)

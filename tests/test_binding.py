@@ -153,6 +153,38 @@ def test_plan_runs_on_another_stream_than_it_was_made_on(made_on):
 
 
 @pytest.mark.gpu
+def test_plan_made_and_run_on_the_per_thread_streams_of_two_threads():
+    """hipStreamPerThread is the same handle on both threads and two streams that nothing orders."""
+    import threading
+    import torch
+    from oracle import reference
+    per_thread = 2                         # (hipStream_t)2 in hip_runtime_api.h
+    b = W.random_general(11, 48, [(40, 30, 200), (7, 7, 0), (90, 110, 500)])
+    C0, S = reference.forward_batch(b)
+    arrays = [torch.from_numpy(a).cuda() for a in (b.rpt, b.colids, b.values)]
+    hb = K.HostBatch(b.rows, b.cols, b.nnz, b.rpt_off, b.nz_off, b.b_row_off, b.c_row_off, *arrays)
+    need = K.bspmm_workspace_bytes(hb, b.F)
+    ws, busy = torch.zeros(need, dtype=torch.uint8, device="cuda"), torch.ones(1 << 28, device="cuda")
+    B, C = torch.from_numpy(b.B).cuda(), torch.full((b.n_c_rows, b.F), -7.0, device="cuda")
+    torch.cuda.synchronize()
+    made = []
+
+    def make():
+        with torch.cuda.stream(torch.cuda.ExternalStream(per_thread)):
+            for _ in range(60):
+                busy.mul_(1.0)             # the copy waits behind these
+        made.append(K.bspmm_create(hb, b.F, None, ws, need, per_thread))
+
+    t = threading.Thread(target=make)
+    t.start()
+    t.join()
+    K.bspmm_run(made[0], B, C, b.F, b.F, per_thread)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
+    K.bspmm_destroy(made[0])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("coo", [False, True])
 def test_plan_made_on_another_stream_and_dropped_leaves_no_copy_behind(coo):
     """The workspace goes back to the current stream's allocator: nothing may still be on its way there."""
