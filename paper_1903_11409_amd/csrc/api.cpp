@@ -1732,6 +1732,26 @@ int settle_upload(bspmm_plan* plan)
     return BSPMM_OK;
 }
 
+int run_after(void* stream, void* earlier)
+{
+    const hipStream_t s = static_cast<hipStream_t>(stream), first = static_cast<hipStream_t>(earlier);
+    if (capturing(s) || capturing(first)) return BSPMM_OK;
+    hipEvent_t done;
+    hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+    if (e != hipSuccess) return hip_fail(e);
+    e = hipEventRecord(done, first);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, done, 0);
+    (void)hipEventDestroy(done);           // (released when what refers to it has run)
+    return e == hipSuccess ? BSPMM_OK : hip_fail(e);
+}
+
+int run_out(void* stream)
+{
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipError_t e = capturing(s) ? hipSuccess : hipStreamSynchronize(s);
+    return e == hipSuccess ? BSPMM_OK : hip_fail(e);
+}
+
 // (it forms 32-bit byte offsets inside an operation's dense blocks and multiplies a row's index and its
 // bytes in 24 bits each: leading dimensions below 4 Mi floats, blocks below 4 GiB and 16 Mi rows)
 bool takes_lean_kernel(const bspmm_plan* plan, bool transposed, int64_t ld_in, int64_t ld_out)

@@ -260,6 +260,10 @@ bool device_data(PyObject* o, at::ScalarType type, int64_t device, const void** 
     return true;
 }
 
+// The memory is the current stream's.  A plan made on another one waits for what the current one holds (the
+// block may have been in use there a moment ago), and the call returns when all that creation
+// enqueued has run, conversions and builds included: a plan dropped early leaves nothing on its way to
+// memory that is somebody else's by then.
 at::Tensor device_bytes(size_t n, int64_t device)
 {
     return at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(at::Device(at::kCUDA, (c10::DeviceIndex)device)));
@@ -322,10 +326,9 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
         Py_RETURN_NONE;
     for (int i = 0; i < 3; ++i) csr.bytes[i] = host ? 4 * (size_t)len[i] : 0;
     if (!get_stream(a[13], &stream)) return nullptr;
-    // The memory belongs to the current stream: on another one the caller copies the arrays first and
-    // the tables have arrived when the call returns, so that a plan dropped early leaves no copy on its
-    // way to memory that is somebody else's by then.
-    const bool foreign = a[13] != Py_None && stream != c10::hip::getCurrentHIPStream().stream();
+    // On another stream than the current one the caller copies the arrays first.
+    void* const current = c10::hip::getCurrentHIPStream().stream();
+    const bool foreign = a[13] != Py_None && stream != current;
     if (host && foreign) Py_RETURN_NONE;
     const bspmm_options* opt = static_cast<const bspmm_options*>(options);
     const size_t head = host ? csr.head() : 0;
@@ -346,13 +349,13 @@ PyObject* create(PyObject* const* a, Py_ssize_t n)
             b.colids = reinterpret_cast<const int32_t*>(base + align_up(csr.bytes[0]));
             b.values = reinterpret_cast<const float*>(base + align_up(csr.bytes[0]) + align_up(csr.bytes[1]));
             rc = bspmm::create_from_host(&plan, &b, (int32_t)F, opt, base + head, need, {head, Csr::write, &csr}, stream);
-        } else {
+        } else if (!foreign || (rc = bspmm::run_after(stream, current)) == BSPMM_OK) {
             b.rpt = static_cast<const int32_t*>(dev[0]);
             b.colids = static_cast<const int32_t*>(dev[1]);
             b.values = static_cast<const float*>(dev[2]);
             rc = bspmm_create(&plan, &b, (int32_t)F, opt, base, need, stream);
         }
-        if (rc == BSPMM_OK && foreign && (rc = bspmm::settle_upload(plan)) != BSPMM_OK) bspmm_destroy(plan);
+        if (rc == BSPMM_OK && foreign && (rc = bspmm::run_out(stream)) != BSPMM_OK) bspmm_destroy(plan);
     }
     Py_END_ALLOW_THREADS
     if (host && rc == BSPMM_ESTATE) Py_RETURN_NONE;
@@ -378,7 +381,8 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
     b.ids = static_cast<const int32_t*>(ids);
     b.values = static_cast<const float*>(values);
     if (!get_stream(a[11], &stream)) return nullptr;
-    const bool foreign = a[11] != Py_None && stream != c10::hip::getCurrentHIPStream().stream();   // (as in create)
+    void* const current = c10::hip::getCurrentHIPStream().stream();
+    const bool foreign = a[11] != Py_None && stream != current;
     const bspmm_options* opt = static_cast<const bspmm_options*>(options);
     size_t need = 0;
     bspmm_plan* plan = nullptr;
@@ -391,8 +395,9 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
         where = "bspmm_create_coo";
         need = need < kAlign ? kAlign : need;
         memory = device_bytes(need, device);
-        rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
-        if (rc == BSPMM_OK && foreign && (rc = bspmm::settle_upload(plan)) != BSPMM_OK) bspmm_destroy(plan);
+        if (foreign) rc = bspmm::run_after(stream, current);
+        if (rc == BSPMM_OK) rc = bspmm_create_coo(&plan, &b, (int32_t)F, opt, memory.data_ptr(), need, stream);
+        if (rc == BSPMM_OK && foreign && (rc = bspmm::run_out(stream)) != BSPMM_OK) bspmm_destroy(plan);
     }
     Py_END_ALLOW_THREADS
     return rc == BSPMM_OK ? made(plan, b, memory, 0) : finish(rc, where, Py_None);

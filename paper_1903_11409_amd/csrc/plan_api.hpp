@@ -26,6 +26,13 @@ int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const b
 // Returns when the plan's tables are on the device; EHIP when they will not get there.
 int settle_upload(bspmm_plan* plan);
 
+// Work enqueued on `stream` from now on runs after what `earlier` holds.  Recording streams are left alone:
+// the order inside a graph is its maker's.
+int run_after(void* stream, void* earlier);
+
+// Returns when everything that `stream` holds has run (a recording stream: at once); EHIP when it failed.
+int run_out(void* stream);
+
 // Rows from the first on, without a gap, that belong to an operation's output: of C, or of G with
 // `transposed`.
 int64_t covered_rows(bspmm_plan* plan, bool transposed);

@@ -209,3 +209,56 @@ def test_plan_made_on_another_stream_and_dropped_leaves_no_copy_behind(coo):
     assert taken.data_ptr() == at
     torch.cuda.synchronize()
     assert not bool(taken.any())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["converted", "transposed"])
+def test_plan_made_on_another_stream_and_dropped_leaves_no_build_behind(kind):
+    """As above for what creation enqueues behind the copy: the conversion of index pairs and the
+    transposed CSR, both of which write for longer than it takes to clear the memory again."""
+    import torch
+    b = W.random_general(11, 16, [(400, 300, 6000)] * 600)
+    loader = type("Loader", (), dict(vars(b)))()
+    loader.rpt, loader.colids, loader.values = (torch.from_numpy(a).cuda() for a in (b.rpt, b.colids, b.values))
+    coo = tuple(torch.from_numpy(a).cuda() for a in W.coo_view(b)) if kind == "converted" else None
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    plan = K.Plan(loader, b.F, K.make_options(flags=K.BUILD_TRANSPOSE), device="cuda:0", stream=side, coo=coo)
+    size, at = plan.workspace.numel(), plan.workspace.data_ptr()
+    plan.close()
+    del plan
+    taken = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
+    assert taken.data_ptr() == at
+    torch.cuda.synchronize()
+    assert not bool(taken.any())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("coo", [False, True])
+def test_plan_made_on_another_stream_waits_for_what_used_its_memory_before(coo):
+    """The allocator hands out a block whose last use is still waiting on the current stream."""
+    import torch
+    from oracle import reference
+    b = W.random_general(11, 48, [(40, 30, 200), (7, 7, 0), (90, 110, 500)] * 40)
+    C0, S = reference.forward_batch(b)
+    loader = type("Loader", (), dict(vars(b)))()
+    loader.rpt, loader.colids, loader.values = (torch.from_numpy(a).cuda() for a in (b.rpt, b.colids, b.values))
+    pairs = tuple(torch.from_numpy(a).cuda() for a in W.coo_view(b)) if coo else None
+    first = K.Plan(loader, b.F, coo=pairs)
+    size, at = first.workspace.numel(), first.workspace.data_ptr()
+    B, C = torch.from_numpy(b.B).cuda(), torch.zeros((b.n_c_rows, b.F), device="cuda:0")
+    side, busy = torch.cuda.Stream(), torch.randn((4096, 4096), device="cuda:0")
+    torch.cuda.synchronize()
+    first.close()
+    del first
+    used = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+    assert used.data_ptr() == at
+    for _ in range(8):
+        busy @ busy
+    used.fill_(1)                          # waits behind these
+    del used
+    plan = K.Plan(loader, b.F, device="cuda:0", stream=side, coo=pairs)
+    assert plan.workspace.data_ptr() == at
+    plan.run(B, C, side)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
