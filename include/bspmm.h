@@ -443,8 +443,10 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info);
 int bspmm_plan_items(const bspmm_plan* plan, int32_t transposed, bspmm_item* items,
                      int32_t capacity, int32_t* count);
 
-/* Release the host side of the plan.  Does not touch the stream: the caller keeps the
- * workspace alive until work already enqueued has finished.  NULL is allowed. */
+/* Release the host side of the plan.  Orders nothing: the caller keeps the workspace alive until
+ * work already enqueued has finished.  (The last plan of a process that has made none for a second
+ * takes the library's pinned memory with it, and freeing that may wait for the device.)  NULL is
+ * allowed. */
 void bspmm_destroy(bspmm_plan* plan);
 
 /* Static description of an error code. */

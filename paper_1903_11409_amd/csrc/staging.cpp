@@ -73,8 +73,18 @@ bool idle(Slot& s)
     return s.state == Slot::kIdle;
 }
 
+// Blocks that have left the pool.  Freeing pinned memory may wait for the device, so it is done after the
+// lock has been given up: declared before the lock's guard.
+struct Gone {
+    std::vector<char*> blocks;
+    ~Gone()
+    {
+        for (char* b : blocks) (void)hipHostFree(b);
+    }
+};
+
 // Idle blocks go, until at most `keep` bytes are held.
-void shrink(Pool& p, size_t keep)
+void shrink(Pool& p, size_t keep, Gone& gone)
 {
     for (size_t i = 0; i < p.slots.size() && p.bytes > keep;) {
         if (!idle(*p.slots[i])) {
@@ -82,7 +92,7 @@ void shrink(Pool& p, size_t keep)
             continue;
         }
         p.bytes -= p.slots[i]->size;
-        (void)hipHostFree(p.slots[i]->base);
+        gone.blocks.push_back(p.slots[i]->base);
         p.slots.erase(p.slots.begin() + (ptrdiff_t)i);
     }
     p.next = 0;
@@ -99,6 +109,7 @@ StageBlock stage_take(size_t bytes)
         return {};
     }
     const RelaxedCapture relaxed;
+    Gone gone;
     Pool& p = pool();
     std::lock_guard<std::mutex> g(p.lock);
     for (size_t j = 0; j < p.slots.size(); ++j) {
@@ -112,7 +123,7 @@ StageBlock stage_take(size_t bytes)
     }
     size_t size = (size_t)256 << 10;
     while (size < bytes) size *= 2;
-    if (p.bytes + size > kStagePoolMax) shrink(p, kStagePoolMax - size);
+    if (p.bytes + size > kStagePoolMax) shrink(p, kStagePoolMax - size, gone);
     if (p.bytes + size > kStagePoolMax) return {};
     void* q = nullptr;
     if (hipHostMalloc(&q, kHeader + size, hipHostMallocDefault) != hipSuccess) {
@@ -182,11 +193,12 @@ void stage_plan_made()
 
 void stage_plan_gone()
 {
+    const RelaxedCapture relaxed;
+    Gone gone;
     Pool& p = pool();
     std::lock_guard<std::mutex> g(p.lock);
     if (--p.plans > 0 || p.slots.empty() || Clock::now() - p.last_plan < std::chrono::seconds(1)) return;
-    const RelaxedCapture relaxed;
-    shrink(p, 0);
+    shrink(p, 0, gone);
 }
 
 }  // namespace bspmm

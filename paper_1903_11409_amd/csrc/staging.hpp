@@ -25,7 +25,8 @@ struct StageBlock {
 };
 
 // A block of at least `bytes` on the current device, or {nullptr} (too large, pool exhausted, no
-// memory): the caller then copies from pageable memory.  Never waits.
+// memory): the caller then copies from pageable memory.  Waits for no copy; making room in a full pool
+// frees blocks, which may wait for the device.
 StageBlock stage_take(size_t bytes);
 
 // A copy that has been enqueued.
@@ -59,7 +60,8 @@ hipError_t wait_until(Done done, State state)
     return hipSuccess;
 }
 
-// Plans that exist: when the last one goes and none has been made for a second, idle blocks are freed.
+// Plans that exist: when the last one goes and none has been made for a second, idle blocks are freed
+// (which may wait for the device).
 void stage_plan_made();
 void stage_plan_gone();
 

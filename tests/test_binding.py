@@ -74,6 +74,70 @@ def test_wait_for_the_tables_ends_with_the_error_of_the_stream(tmp_path):
     assert subprocess.run([str(exe)], capture_output=True, timeout=30, text=True).stdout == "ok\n"
 
 
+POOL = r"""
+#include "staging.hpp"
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+// The runtime's part: freeing waits for the device, here for another thread that takes a block meanwhile.
+static std::atomic<int> freeing{0}, taken{0};
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
+hipError_t hipHostFree(void* p)
+{
+    freeing = 1;
+    for (int i = 0; i < 2000 && !taken; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus*) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+}
+namespace bspmm {
+hipError_t launch_stage_copy(const void*, void*, size_t, uint32_t* done, uint32_t mark, int grid, hipStream_t)
+{
+    for (int i = 0; i < grid; ++i) done[i] = mark;
+    return hipSuccess;
+}
+}
+int main()
+{
+    using namespace bspmm;
+    std::vector<StageBlock> blocks;
+    for (size_t held = 0; held < kStagePoolMax; held += (size_t)256 << 10) blocks.push_back(stage_take(1));   // full
+    if (!blocks.back().ptr) return 1;
+    StagedCopy copy;
+    for (StageBlock& b : blocks)
+        if (stage_copy(b, nullptr, 16, nullptr, &copy) != hipSuccess) return 2;
+    std::thread other([] {
+        while (!freeing) std::this_thread::yield();
+        if (stage_take(1).ptr) taken = 1;
+    });
+    const bool got = stage_take(kStageBlockMax).ptr != nullptr;      // makes room
+    const bool meanwhile = taken;
+    other.join();
+    std::puts(got && meanwhile ? "ok" : "waited");
+}
+"""
+
+
+def test_room_in_the_staging_pool_is_made_outside_its_lock(tmp_path):
+    """Freeing pinned memory may wait for the device: other threads go on making plans meanwhile."""
+    import os
+    import subprocess
+    from paper_1903_11409_amd import build
+    src, exe = tmp_path / "pool.cpp", tmp_path / "pool"
+    src.write_text(POOL)
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-I" + build.CSRC,
+                    "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), str(src),
+                    os.path.join(build.CSRC, "staging.cpp"), "-o", str(exe), "-pthread"], check=True, timeout=120)
+    assert subprocess.run([str(exe)], capture_output=True, timeout=60, text=True).stdout == "ok\n"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,ld", [(1, 64), (1, 72), (7, 64), (7, 68), (7, 65)])
 @pytest.mark.parametrize("stream", ["current", "object", "handle"])
