@@ -518,109 +518,131 @@ WorkItem empty_item()
     return w;
 }
 
-// The rule for plain batches on the float4 path without a caller's knobs.  The widest tile an operation
-// can hold is always taken; parallelism comes from row ranges, which copy their tile again (out of
-// L2) but stage the CSR once per range instead of once per column tile.  fit(words, c) plans the tiles for
-// that LDS budget and row blocks for candidate c.  Measured on MI355X over 44 batches (8 to 6000 graphs of molecule, 20-100-node,
-// heavy-tailed and random-matrix sizes, F = 16 to 1024) against all tiles, budgets and cuts:
+// The rule for plain batches on the float4 path without a caller's knobs.  fit(words, c) plans the tiles for
+// that LDS budget and row blocks for candidate c.  Row ranges copy their tile again and column tiles
+// stage the CSR again.  Out of the caches the copies of a tile that row ranges make are cheap, on operands
+// that come from memory they are not: the two orders disagree, and where they do the rule goes by the
+// operands from memory.  Measured on MI355X over 110 batches (8 to 8192 graphs of molecule, 20-100-node,
+// heavy-tailed and random-matrix sizes, F = 16 to 1024), times in us on operands from memory / out of
+// the caches:
 //  - A launch that fits the chip at once (six workgroups of 24 KiB per CU) lasts as long as its slowest
-//    workgroup: row ranges of one pass, or of two, if it still fits with them (256 molecules at F = 128
-//    3.44 -> 3.24 us, 60 graphs of 20-100 nodes at F = 256 4.25 -> 3.4, 450 molecules 4.24 -> 3.86), except
-//    where it moves more than 28 MB and the copies cost more than they gain.  (Ranges of four and more
-//    copy the tile of an operation of five passes twice for nothing: 200 graphs of 8 to 140 nodes at
-//    F = 256 6.5 us uncut, 8.1 cut to four.)
-//  - One that does not is planned for 20 KiB, eight workgroups per CU: where that holds all of it at
-//    once, ranges as short as leave an eighth of the room free (1600 molecules at F = 64 5.65 -> 4.72);
-//    otherwise ranges of two passes, of eight below F = 128, whose passes are 16 rows and more
-//    (1000 graphs of 20-100 nodes at F = 256 26.4 -> 22.9 us, 1024 heavy-tailed ones 29.2 -> 24.5,
-//    6000 molecules at F = 128 30.0 -> 27.3).  Past 88 MB of dense input, where input and output no longer
-//    stay in the 256 MB memory-side cache together, second copies cost more: ranges of four passes at
-//    24 KiB (8000 molecules 40.8 -> 39.8, 16384 of them 82.5 -> 81.0, ranges of two 86.2).
-//  - From F = 256 on (four rows a pass) with operations in row blocks: ranges of one pass at 20 KiB
-//    whatever the launch's size; staging and row blocks then overlap (300 heavy-tailed graphs 12.0 -> 8.9
-//    us, 150 of them 6.3 -> 5.3; 80 random matrices of 3 entries a row, half in row blocks, 6.5 -> 5.2),
-//    of two from 48 MB of input on (700 heavy-tailed graphs at F = 512 36.4 -> 33.5), of four from 80.
+//    workgroup: ranges of 32 rows, of 64 if it then fits, at the narrowest tile at which it does (128
+//    molecules at F = 128 2.93 / 2.78 in 32 columns, 3.10 / 2.61 in 128 columns cut to 8 rows; at F = 256
+//    3.37 / 3.25 against 3.91 / 3.00; 384 of them at F = 128 3.79 / 3.53 in 64 columns, 4.29 / 3.34; 20
+//    heavy-tailed graphs at F = 256 3.6 / 3.2 against 4.7 / 3.8), unless it moves more than 28 MB.  With
+//    operations in row blocks: the narrowest tile only, and where at least half of the dense input is
+//    staged (20 random matrices at F = 512 6.1 / 3.6 in 32 columns, 4.1 / 3.7 uncut in 128).  Up to F = 64
+//    ranges of one pass, 16 rows at F = 64, or of two, if it then fits: the orders are within 4 % of each
+//    other (512 molecules at F = 64 3.44 / 3.06, in 32 columns 3.30 / 3.20), and a fifth more items to
+//    plan and send cost a data loader more (plan and two products from index pairs 50.1, 47.6).
+//  - One that does not is not cut below 32 rows, and planned for 40 KiB where that saves a quarter of the
+//    workgroups, none are row blocks and F >= 128 (1000 graphs of 20-100 nodes at F = 128 13.2 / 11.8,
+//    ranges of 16 rows at 20 KiB 16.1 / 11.8, uncut at 24 14.3 / 12.8; 400 of them at F = 256 10.6 / 8.8
+//    against 11.6 / 10.4), for 20 KiB, eight workgroups per CU, where that holds all of it at once (no row
+//    blocks) or costs at most a twentieth more of them (4096 molecules at
+//    F = 64 11.4 / 10.4, 12.8 / 11.9 at 24), else for 24 (2048 molecules at F = 128 11.4 / 9.9 uncut, 12.6 /
+//    10.0 in ranges of 16 rows; 300 random matrices of 3 entries a row 10.6 / 7.7 against 12.9 / 7.7).  Past
+//    88 MB of dense input, where input and output no longer stay in the 256 MB memory-side cache
+//    together: ranges of four passes at 24 KiB (4096 molecules at F = 256 38.6 / 38.5, uncut 40.9 / 39.9).
+//  - From F = 256 on with operations in row blocks that do not: uncut tiles and row blocks of 128 columns (150
+//    heavy-tailed graphs at F = 512 10.5 / 10.2, ranges of one pass at 20 KiB 12.0 / 7.7, 32 columns
+//    11.1 / 10.4; 700 at F = 256 19.4 / 19.0, 26.2 / 17.8, 19.7 / 18.9; 100 random matrices 8.0 / 5.6, 9.5 /
+//    5.2, 8.9 / 8.4), past 48 MB of dense input of 256 columns at 40 KiB (1024 heavy-tailed graphs 27.3 /
+//    26.6, in 128 columns 27.9 / 27.9, cut to one pass 33.1 / 24.4).
 //  - Row blocks past 104 MB fetch what they gather from memory again: uncut at 40 KiB where that saves
-//    a third of the workgroups (3000 heavy-tailed graphs at F = 256 107 us at 20 KiB, 76.5 at 24, 75.1;
-//    10000 random matrices at F = 32 90 -> 76).
+//    a third of the workgroups (3000 heavy-tailed graphs at F = 256 107 at 20 KiB, 76.5 at 24, 75.1; 10000
+//    random matrices at F = 32 90 -> 76).
 //  - Dense blocks that several operations read (edge types as channels): ranges of four passes at 24 KiB,
-//    the tiles come out of L2 (900 molecules of four channels at F = 128 10.7 -> 9.9).
+//    the tiles come out of L2 (900 molecules of four channels at F = 128 10.0 / 9.7, uncut 10.3 / 10.0).
 //  - Widths of whole 128-byte lines that are no power of two (96, 160, 192): one tile of the whole row keeps
 //    part of the lanes idle but copies and stages once, which wins in launches of several rounds that stay
-//    in cache (3000 molecules at F = 192 20.3 us, 22 in tiles of 128 and 64).  Tiles that are powers of two
-//    win where latency or the memory itself bounds, up to 14 MB in one round (400 molecules 5.3 -> 4.8,
-//    100 graphs of 20-100 nodes 5.0 -> 4.2) and past 88 MB (2500 of these graphs 49.3 -> 44.9), and where
-//    most operations are too large for the whole row anyway (400 of them 9.4 -> 8.8).
+//    in cache (3000 molecules at F = 192 24.1 / 19.6 uncut, tiles of 64 22.7 / 22.2).  Tiles that are powers
+//    of two win past 88 MB (2500 graphs of 20-100 nodes 49.3 -> 44.9), and where most operations are too
+//    large for the whole row anyway (400 of them 9.4 -> 8.8).
 //  - Rows off the 128-byte lines (F = 100): column tiles share lines, so operations that need them at 24 KiB
 //    get 40 once the launch does not fit the chip at once anyway, where that saves a quarter of the
-//    tiles and none are row blocks, and ranges of four passes (5000 graphs of 20-100 nodes 79.8 -> 58.9
-//    us, 2000 of them 27.2 -> 20.9; 2000 molecules, of which few need it, 9.7 -> 11.0: not taken).
+//    tiles and none are row blocks, and ranges of four passes (2000 graphs of 20-100 nodes 26.1 / 20.4
+//    against 40.0 / 39.7; 2000 molecules, of which few need it, 9.7 -> 11.0: not taken).
 // narrow: the first candidate from which on all tiles are powers of two (-1: none).
 template <typename CountFn, typename FitFn>
-Shape plain_shape(const Knobs& kn, int F, int narrow, bool shared, CountFn count, FitFn fit, int* uncut_wgs)
+Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narrow, bool shared, CountFn count, FitFn fit,
+                  int* uncut_wgs)
 {
     Shape s = {0, 0, 0};
-    Count n = count(0, 0);
+    const Count n = count(0, 0);
     s.wgs = *uncut_wgs = n.wgs;
-    auto shortest = [&](std::initializer_list<int> caps, int most) {
-        for (int c : caps) {
-            const int w = count(s.chosen, c).wgs;
-            if (w > most) continue;
-            s.cap = c;
-            s.wgs = w;
-            return true;
-        }
-        return false;
+    auto take = [&](size_t first, int cap, int most) {
+        const int w = count(first, cap).wgs;
+        if (w > most) return false;
+        s = {first, cap, w};
+        return true;
     };
     auto cut = [&](int cap) {
-        s.cap = cap;
-        s.wgs = count(s.chosen, cap).wgs;
+        take(s.chosen, cap, INT32_MAX);
         return s;
     };
     const bool small = n.tile_words <= 3500000;
     const bool streams = F >= 128 && n.in_words > 22000000;
-    bool pow2 = narrow == 0;
-    if (narrow > 0 && F % 32 == 0) {
-        const Count t = count((size_t)narrow, 0);
-        if ((small && t.wgs <= kn.capacity_wgs) ||
-            (!n.row_blocks && (streams || 4 * (int64_t)t.wgs <= 5 * (int64_t)n.wgs))) {
-            fit(small ? 20 * 1024 / 4 : kn.lds_words, narrow);
-            pow2 = !small || count((size_t)narrow, 0).wgs <= kn.capacity_wgs;
-            if (pow2) {
-                s.chosen = (size_t)narrow;
-                s.wgs = *uncut_wgs = t.wgs;
-            } else {
-                fit(kn.lds_words, 0);
+    const bool lines = F % 32 == 0;
+    if (lines && F > 64 && small && s.wgs <= kn.capacity_wgs && 2 * n.tile_words >= n.in_words) {
+        const int last = (int)cand.size() - 1;
+        if (n.row_blocks) fit(kn.lds_words, last);
+        for (int c = last; c >= (n.row_blocks ? last : 0); --c)
+            for (int rows : {32, 64}) {    // (a pass of 32 columns is 32 rows)
+                const int cap = std::max(1, rows * cand[c] / 1024);
+                const int w = count((size_t)c, cap).wgs;
+                if (w <= kn.capacity_wgs) return {(size_t)c, cap, w};
             }
+        if (!n.row_blocks) return s;
+        fit(kn.lds_words, 0);
+    }
+    bool pow2 = narrow == 0;
+    if (narrow > 0 && lines && !small && !n.row_blocks) {
+        const Count t = count((size_t)narrow, 0);
+        if (streams || 4 * (int64_t)t.wgs <= 5 * (int64_t)n.wgs) {
+            pow2 = true;
+            s = {(size_t)narrow, 0, t.wgs};
+            *uncut_wgs = t.wgs;
         }
     }
-    if (n.row_blocks && F % 32 == 0 && n.in_words > 26000000) {
+    if (n.row_blocks && lines && n.in_words > 26000000) {
         fit(40 * 1024 / 4, (int)s.chosen);
         if (3 * (int64_t)count(s.chosen, 0).wgs <= 2 * (int64_t)s.wgs) return cut(0);
         fit(kn.lds_words, (int)s.chosen);
-    } else if (n.row_blocks && pow2 && F >= 256) {
-        fit(20 * 1024 / 4, (int)s.chosen);
-        return cut(n.in_words > 20000000 ? 4 : n.in_words > 12000000 ? 2 : 1);
+    }
+    if (n.row_blocks && pow2 && F >= 256) {
+        if (n.in_words > 12000000) {
+            fit(40 * 1024 / 4, 0);
+            return cut(0);
+        }
+        while (cand[s.chosen] > 128 && s.chosen + 1 < cand.size()) ++s.chosen;
+        fit(kn.lds_words, (int)s.chosen);
+        return cut(8);
     }
     const int eight = 8 * kn.compute_units;            // (other widths: the kernel's registers allow six)
     if (s.wgs <= kn.capacity_wgs) {
-        if (!small) return s;
-        if (shortest({1}, kn.capacity_wgs)) return s;
-        if (s.chosen == 0 && pow2)
-            shortest({2}, kn.capacity_wgs);
-        else
-            shortest({2, 4}, pow2 ? eight - eight / 8 : kn.capacity_wgs);
+        if (!small || take(s.chosen, 1, kn.capacity_wgs) || take(s.chosen, 2, kn.capacity_wgs)) return s;
+        if (!pow2) take(s.chosen, 4, kn.capacity_wgs);
         return s;
     }
-    if (!pow2 && F % 32 != 0 && !n.row_blocks) {
-        fit(40 * 1024 / 4, 0);
-        if (4 * (int64_t)count(0, 0).wgs > 3 * (int64_t)s.wgs) fit(kn.lds_words, 0);
-    }
-    if (!pow2 || streams || (shared && F >= 128)) return cut(4);
+    auto saves_at_40 = [&] {
+        fit(40 * 1024 / 4, (int)s.chosen);
+        if (4 * (int64_t)count(s.chosen, 0).wgs <= 3 * (int64_t)s.wgs) return true;
+        fit(kn.lds_words, (int)s.chosen);
+        return false;
+    };
+    if (!pow2 && !lines && !n.row_blocks) saves_at_40();
+    if (streams || (shared && F >= 128)) return cut(4);
+    if (!pow2) return cut(lines && F > 128 ? 8 : 4);
+    if (F >= 128 && !n.row_blocks && saves_at_40()) return cut(0);
     fit(20 * 1024 / 4, (int)s.chosen);
-    s.wgs = count(s.chosen, 0).wgs;
-    if (s.wgs > eight) return cut(F >= 128 ? 2 : 8);
-    shortest({2, 4, 8}, eight - eight / 8);
+    const int w20 = count(s.chosen, 0).wgs;
+    const bool more = 20 * (int64_t)w20 > 21 * (int64_t)s.wgs;
+    if (more && (w20 > eight || n.row_blocks)) fit(kn.lds_words, (int)s.chosen);
+    if (w20 > eight || (more && n.row_blocks)) return cut(8);
+    s.wgs = w20;
+    for (int c : {2, 4, 8})
+        if (take(s.chosen, c, eight - eight / 8)) break;
     return s;
 }
 
@@ -663,10 +685,14 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     // the widest candidate each operation can hold in LDS (nc: none, it is cut into row blocks)
     std::vector<uint8_t> fit(n);
     int lds_words = kn.lds_words;
-    int blocks = 0;                                    // the candidate whose columns row blocks take
+    int blocks = 0;                                    // the candidate whose columns row blocks take ...
+    int generic_rows = kn.generic_rows;                // ... and their rows
     auto fit_all = [&](int words, int block_tile) {
         lds_words = words;
         blocks = block_tile;
+        // what the workgroup has in flight (2000 heavy-tailed graphs at F = 64: 16.8 us with eight rows, half
+        // of the lanes idle, 15.7 with sixteen), sixty-four at most
+        if (!kn.generic_given) generic_rows = std::max(kn.generic_rows, std::min(tile[blocks].full.rows[0], 64));
         for (int i = 0; i < n; ++i) {
             const int64_t room = words - ((int64_t)round_up(o.m[i] + 1, 2) + 2 * (int64_t)o.nnz[i] + 3) / 4 * 4 -
                                  (vec == 4 ? 0 : 4);   // (as fits_slot())
@@ -676,9 +702,6 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         }
     };
     fit_all(kn.lds_words, 0);
-    // rows of a row block: what the workgroup has in flight (2000 heavy-tailed graphs at F = 64: 16.8 us with
-    // eight rows, half of the lanes idle, 15.7 with sixteen), sixty-four at most
-    const int generic_rows = kn.generic_given ? kn.generic_rows : std::max(kn.generic_rows, std::min(tile[0].full.rows[0], 64));
     auto long_rows = [&](int i) { return vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 0; };
     // (exact below 2^31: x + 1/2 over d is at least 1/(2d) away from a whole number)
     auto pieces_of = [](int m, double inv_chunk, int chunk) { return (int)((m + chunk - 0.5) * inv_chunk); };
@@ -729,7 +752,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     int narrow = -1;
     for (int c = std::min(nc, 2) - 1; c >= 0; --c)
         if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
-    const Shape shape = open ? plain_shape(kn, F, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
+    const Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
                              : search_shape(kn, vec, (size_t)nc, count);
     if (!open) s.uncut_wgs = shape.wgs;
 

@@ -455,6 +455,23 @@ def test_wide_traffic_bound_launches_take_a_third_of_the_lds():
     assert info_of(W.config2_molecule(F=512, graphs=1024)).lds_bytes == 24576   # 2.2 -> 2.8 rounds
 
 
+@pytest.mark.parametrize("batch", [lambda: W.config2_molecule(F=128), lambda: W.config2_molecule(F=256),
+                                   lambda: W.config2_molecule(F=128, graphs=2048),
+                                   lambda: W.config4_wide(F=256), lambda: W.config4_wide(F=128, graphs=1000),
+                                   lambda: W.config5_skewed(graphs=60), lambda: W.config5_skewed(), lambda: W.random_square(9, 512, 20, (32, 256), 3)])
+def test_row_ranges_hold_32_rows(batch):
+    """Every row range copies the operation's whole dense tile: on operands that come from memory ranges
+    of a few rows cost more than they gain (128 molecules at F = 128: 3.1 us instead of 2.9)."""
+    b = batch()
+    h = K.dry_plan(b, b.F)
+    try:
+        for it in K.bspmm_plan_items(h):
+            if it.bin == K.BIN_WORKGROUP and it.row0 + it.nrows < b.rows[it.op]:
+                assert it.nrows >= 32
+    finally:
+        K.bspmm_destroy(h)
+
+
 def test_direct_coo_sorts_on_chip_where_the_entries_fit():
     """Without a caller's budget the launch takes the smallest LDS size at which every operation's
     entries are sorted on chip (slot bit 4); a small budget from the caller is kept and the
