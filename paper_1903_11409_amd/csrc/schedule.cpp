@@ -642,7 +642,7 @@ Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narr
     if (w20 > eight || (more && n.row_blocks)) return cut(8);
     s.wgs = w20;
     for (int c : {2, 4, 8})
-        if (take(s.chosen, c, eight - eight / 8)) break;
+        if (32 * c >= cand[s.chosen] && take(s.chosen, c, eight - eight / 8)) break;
     return s;
 }
 
