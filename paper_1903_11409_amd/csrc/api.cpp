@@ -125,6 +125,7 @@ struct bspmm_plan {
     bool lean_hints_built[2] = {false, false};   // ... and the device has filled in their entry ranges
     StagedCopy upload;          // the copy of the tables from pinned memory, until it is known to have run ...
     hipStream_t upload_stream = nullptr;   // ... and the stream it was enqueued on
+    hipEvent_t copied = nullptr;           // ... or the event behind the copy from pageable memory
     std::vector<char> tables;   // host image of the workspace's front, for copies from pageable memory
     Layout lay;
     int build_lds_bytes = 0;
@@ -1472,6 +1473,11 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
         p->tables.resize(p->lay.image);
         write_image(p, p->tables.data());
         e = hipMemcpyAsync(p->ws, p->tables.data(), p->tables.size(), hipMemcpyHostToDevice, s);
+        p->upload_stream = s;
+        if (e == hipSuccess && !capturing(s)) {
+            e = hipEventCreateWithFlags(&p->copied, hipEventDisableTiming);
+            if (e == hipSuccess) e = hipEventRecord(p->copied, s);
+        }
     }
     if (p->coo_direct) return e == hipSuccess ? BSPMM_OK : hip_fail(e);
     if (e == hipSuccess && p->from_coo) {
@@ -1678,6 +1684,7 @@ bspmm_plan* recall(const PlanKey& k, const Batch* b, const int64_t* rpt_off)
 int hand_over(bspmm_plan* p, int rc, bspmm_plan** plan)
 {
     if (rc != BSPMM_OK) {
+        if (p->copied) (void)hipEventDestroy(p->copied);
         delete p;
         return rc;
     }
@@ -1725,6 +1732,12 @@ int create_from_host(bspmm_plan** plan, const bspmm_batch* b, int32_t F, const b
 
 int settle_upload(bspmm_plan* plan)
 {
+    if (plan->copied) {
+        const hipError_t e = event_wait(plan->copied);
+        if (e != hipSuccess) return hip_fail(e);
+        (void)hipEventDestroy(plan->copied);
+        plan->copied = nullptr;
+    }
     if (!plan->upload.slot) return BSPMM_OK;
     const hipError_t e = stage_wait(plan->upload, plan->upload_stream);
     if (e != hipSuccess) return hip_fail(e);
@@ -2080,6 +2093,7 @@ int bspmm_plan_items(const bspmm_plan* plan, int32_t transposed, bspmm_item* ite
 
 void bspmm_destroy(bspmm_plan* plan)
 {
+    if (plan && plan->copied) (void)hipEventDestroy(plan->copied);
     if (plan && plan->counted) stage_plan_gone();
     delete plan;
 }

@@ -183,6 +183,12 @@ hipError_t stage_wait(const StagedCopy& copy, hipStream_t stream)
     return wait_until(done, state);
 }
 
+hipError_t event_wait(hipEvent_t copied)
+{
+    const RelaxedCapture relaxed;
+    return hipEventSynchronize(copied);
+}
+
 void stage_plan_made()
 {
     Pool& p = pool();

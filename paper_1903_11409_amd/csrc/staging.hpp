@@ -43,6 +43,9 @@ hipError_t stage_copy(StageBlock b, void* dst, size_t bytes, hipStream_t stream,
 // work enqueued from now on, on any stream; the error when it never will.
 hipError_t stage_wait(const StagedCopy& copy, hipStream_t stream);
 
+// The same for a copy from pageable memory, by an event that was recorded behind it.
+hipError_t event_wait(hipEvent_t copied);
+
 // The wait itself: until done(), but no longer than state() (what the runtime says of the work waited for)
 // is hipErrorNotReady.  state() is asked from the second millisecond on only, ten times a millisecond.
 template <typename Done, typename State>

@@ -96,6 +96,7 @@ hipError_t hipHostFree(void* p)
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus*) { return hipSuccess; }
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 }
 namespace bspmm {
 hipError_t launch_stage_copy(const void*, void*, size_t, uint32_t* done, uint32_t mark, int grid, hipStream_t)
@@ -246,6 +247,32 @@ def test_plan_made_and_run_on_the_per_thread_streams_of_two_threads():
     torch.cuda.synchronize()
     assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
     K.bspmm_destroy(made[0])
+
+
+@pytest.mark.gpu
+def test_plan_of_large_tables_runs_on_another_stream_than_it_was_made_on():
+    """Tables beyond a staging block go over from pageable memory; a run on a stream that nothing orders
+    behind that copy waits for it too."""
+    import torch
+    n, F = 140_000, 4                      # 64 bytes an item and 48 a record: more than 8 MiB
+    one, at = np.ones(n, dtype=np.int32), np.arange(n, dtype=np.int64)
+    rpt = torch.tensor([0, 1], dtype=torch.int32, device="cuda").repeat(n)
+    cols, vals = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.randn(n, device="cuda")
+    hb = K.HostBatch(one, one, one, 2 * at, at, at, at, rpt, cols, vals)
+    need = K.bspmm_workspace_bytes(hb, F)
+    assert need > 8 << 20
+    ws, busy = torch.zeros(need, dtype=torch.uint8, device="cuda"), torch.ones(1 << 28, device="cuda")
+    B, C = torch.randn((n, F), device="cuda"), torch.zeros((n, F), device="cuda")
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(60):
+            busy.mul_(1.0)                 # the copy waits behind these
+    plan = K.bspmm_create(hb, F, None, ws, need, side.cuda_stream)
+    K.bspmm_run(plan, B, C, F, F, other.cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(C, vals[:, None] * B)
+    K.bspmm_destroy(plan)
 
 
 @pytest.mark.gpu
