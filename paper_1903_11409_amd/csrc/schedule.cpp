@@ -61,11 +61,21 @@ int bin_range(int bin)
 
 int draft_range(const Draft& x) { return x.fused >= 0 ? 1 : bin_range(x.bin); }
 
-// Output rows of operation i that a whole workgroup has in flight (see bspmm_any_kernel).
-int rows_in_flight(const DirOps& o, int i, int fw, int vec)
+// Whether these knobs leave every launch to bspmm_kernel (see Schedule::whole).
+bool general_only(const Knobs& kn)
+{
+    return kn.front > 0 || kn.hubs || kn.pad != 0 || kn.persistent_wgs > 0 || kn.wide_offsets;
+}
+
+// Output rows of operation i that a whole workgroup has in flight (see bspmm_any_kernel); in launches that
+// run in bspmm_kernel, which gives a row a power of two of lanes, at most four of its passes (200 operations
+// of 1 to 220 rows with hub rows split: F = 17 10.2 -> 9.1 us, F = 50 10.5 -> 9.8, F = 127 17.6 -> 14.8; one
+// pass instead of four: F = 17 8.3, but F = 127 18.3 and F = 301 37.0 against 26.4).
+int rows_in_flight(const DirOps& o, int i, int fw, int vec, const Knobs& kn)
 {
     const int per_lane = vec == 1 && o.nnz[i] > kLongRow * o.m[i] ? 1 : 4;
-    return std::max(1, kThreads / std::max(1, (fw + per_lane - 1) / per_lane));
+    const int rows = std::max(1, kThreads / std::max(1, (fw + per_lane - 1) / per_lane));
+    return general_only(kn) ? std::min(rows, 4 * (kThreads / lanes_per_row(fw, vec))) : rows;
 }
 
 // Candidate tile widths, widest first.
@@ -202,7 +212,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     if (!sink.out) {    // counting: the same items in closed form
         auto per_tile = [&](int fw) {
             if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-                const int chunk = cap * rows_in_flight(o, i, fw, vec);
+                const int chunk = cap * rows_in_flight(o, i, fw, vec, kn);
                 return (o.m[i] + chunk - 1) / chunk;
             }
             if (ch.bin != BSPMM_BIN_GENERIC) return 1;
@@ -220,7 +230,7 @@ void draft_op(const DirOps& o, int i, int F, int vec, const Choice& ch, const Kn
     for (int f0 = 0; f0 < F; f0 += tile) {
         const int fw = std::min(tile, F - f0);
         if (ch.bin == BSPMM_BIN_WORKGROUP && cap > 0) {
-            const int chunk = cap * rows_in_flight(o, i, fw, vec);
+            const int chunk = cap * rows_in_flight(o, i, fw, vec, kn);
             for (int r0 = 0; r0 < o.m[i]; r0 += chunk)
                 sink.add(o, i, ch.bin, r0, std::min(chunk, o.m[i] - r0), f0, fw, 1, -1);
         } else if (ch.bin != BSPMM_BIN_GENERIC) {

@@ -472,6 +472,20 @@ def test_row_ranges_hold_32_rows(batch):
         K.bspmm_destroy(h)
 
 
+@pytest.mark.parametrize("options", [dict(flags=K.SPLIT_HUB_ROWS), dict(lds_pad=4), dict(resident_workgroups=1024)])
+def test_row_ranges_of_the_general_kernel_count_its_own_lanes(options):
+    """At 17 columns bspmm_kernel gives a row 32 lanes, so a range of 51 rows (what the other kernel has in
+    flight) was seven passes; a launch that is short of workgroups takes four."""
+    rng = np.random.default_rng(5)
+    b = W.random_general(7, 17, [(int(m), int(k), 3 * int(m)) for m, k in rng.integers(1, 221, (100, 2))], with_dY=False)
+    h = K.dry_plan(b, 17, **options)
+    try:
+        staged = [it for it in K.bspmm_plan_items(h) if it.bin == K.BIN_WORKGROUP]
+        assert staged and max(it.nrows for it in staged) == 4 * 256 // 32
+    finally:
+        K.bspmm_destroy(h)
+
+
 def test_direct_coo_sorts_on_chip_where_the_entries_fit():
     """Without a caller's budget the launch takes the smallest LDS size at which every operation's
     entries are sorted on chip (slot bit 4); a small budget from the caller is kept and the
