@@ -177,7 +177,7 @@ typedef struct bspmm_options {
                                   (tiles twice as wide) for F >= 512 when the launch moves
                                   28 to 70 MB in more than one round of workgroups and
                                   needs at most a tenth more rounds that way.  bspmm_info.lds_bytes says
-                                  what was taken                                              */
+                                  what was taken (the larger of the two directions')           */
     int32_t  min_tile;         /* narrowest feature tile in floats, 0 = default (32)           */
     int32_t  max_tile;         /* widest feature tile in floats, 0 = default (256), <= 256     */
     int32_t  target_workgroups;/* split tiles until the launch has this many, 0 = 4 per CU, or,

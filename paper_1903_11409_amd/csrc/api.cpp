@@ -2043,7 +2043,7 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
     std::memset(info, 0, sizeof(*info));
     info->batch = plan->batch;
     info->F = plan->F;
-    info->lds_bytes = plan->knobs.lds_words * 4;
+    info->lds_bytes = 4 * std::max(plan->sched[0].budget_words, plan->sched[1].budget_words);
     if (plan->coo_direct)      // the direct COO launches ask for their largest item's LDS
         info->lds_bytes = 4 * std::max(plan->coo_sched[0].lds_words, plan->coo_sched[1].lds_words);
     info->compute_units = plan->knobs.compute_units;

@@ -928,6 +928,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     for (int r = 0; r < kRanges; ++r) s.wg_end[r] = grid;   // (the compact table's launches do not ask)
     s.whole = grid > 0;
     s.pow2 = s.whole && all_pow2;
+    s.budget_words = lds_words;
     s.lds_words = s.row_blocks ? lds_words : (int)std::min<int64_t>(lds_words, round_up((int)lds, 64));
     return true;
 }
@@ -1003,6 +1004,7 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     Schedule s;
     Knobs kn = kn_in;
     if (!kn_in.target_wgs) kn.target_wgs = 4 * kn.compute_units;
+    s.budget_words = kn.lds_words;
     const int vec = (F % 4 == 0) ? 4 : 1;
     const std::vector<int> cand = tile_candidates(F, kn);
     const Groups outs = output_groups(ops_in);

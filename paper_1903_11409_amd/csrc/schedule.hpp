@@ -135,6 +135,7 @@ struct Schedule {
     bool has_slices = false;         // any 32- or 16-lane item: needs the larger kernel variant
     int tile = 0;
     int lds_words = 0;               // `whole` launches: LDS the launch asks for (its largest item)
+    int budget_words = 0;            // LDS per workgroup the items were planned for
     int front_lds_words = 0;         // LDS the fused-front launch asks for (its largest item)
     int items_in_bin[BSPMM_NUM_BINS] = {0, 0, 0, 0, 0};
 };

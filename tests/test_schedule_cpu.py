@@ -448,11 +448,31 @@ def test_wide_traffic_bound_launches_take_a_third_of_the_lds():
     assert wide.lds_bytes == 53248 and wide.workgroups[0] * 6 <= 2168 * 3 and list(wide.lean) == [1, 1]
     assert info_of(W.config4_wide(F=1024), lds_bytes=24576).lds_bytes == 24576
     assert info_of(W.config4_wide(F=512)).lds_bytes == 24576          # one round at 24 KiB, two at 52
-    assert info_of(W.config2_molecule(F=1024, graphs=512)).lds_bytes == 24576   # small graphs: wide tiles already
-    assert info_of(W.config5_skewed()).lds_bytes == 24576             # F = 256
+    assert info_of(W.config2_molecule(F=1024, graphs=512)).lds_bytes == 40960   # small graphs: wide tiles already
+    assert info_of(W.config5_skewed()).lds_bytes == 40960             # F = 256
     for seed in (7000, 7007, 7008, 7009):                             # other batches of the same kind
         assert info_of(W.config4_wide(seed=seed, F=1024)).lds_bytes == 53248
-    assert info_of(W.config2_molecule(F=512, graphs=1024)).lds_bytes == 24576   # 2.2 -> 2.8 rounds
+    assert info_of(W.config2_molecule(F=512, graphs=1024)).lds_bytes == 40960   # 2.2 -> 2.8 rounds at 52
+
+
+@pytest.mark.parametrize("batch,want", [(lambda: W.config2_molecule(F=16, graphs=4000), 20480),
+                                        (lambda: W.config2_molecule(F=64, graphs=2048), 20480),
+                                        (lambda: W.config2_molecule(F=128), 24576),
+                                        (lambda: W.config2_molecule(F=128, graphs=4096), 24576),
+                                        (lambda: W.config4_wide(F=128, graphs=1000), 40960),
+                                        (lambda: W.config5_skewed(), 40960)])
+def test_plans_report_the_lds_they_were_made_for(batch, want):
+    """Every staged operation fits what the plan reports; at 40 KiB some need more than 24."""
+    b = batch()
+    h = K.dry_plan(b, b.F)
+    try:
+        assert K.bspmm_plan_info(h).lds_bytes == want
+        words = [_lds_words(int(b.rows[it.op]), int(b.cols[it.op]), int(b.nnz[it.op]), it.fw, 0, 256, False)
+                 for it in K.bspmm_plan_items(h) if it.bin == K.BIN_WORKGROUP]
+        assert words and 4 * max(words) <= want
+        assert want < 40960 or 4 * max(words) > 24576
+    finally:
+        K.bspmm_destroy(h)
 
 
 @pytest.mark.parametrize("batch", [lambda: W.config2_molecule(F=128), lambda: W.config2_molecule(F=256),
