@@ -178,7 +178,8 @@ typedef struct bspmm_options {
                                   28 to 70 MB in more than one round of workgroups and
                                   needs at most a tenth more rounds that way.  bspmm_info.lds_bytes says
                                   what was taken (the larger of the two directions')           */
-    int32_t  min_tile;         /* narrowest feature tile in floats, 0 = default (32)           */
+    int32_t  min_tile;         /* narrowest feature tile in floats, 0 = default (32; 8 where
+                                  F % 4 != 0)                                                 */
     int32_t  max_tile;         /* widest feature tile in floats, 0 = default (256), <= 256     */
     int32_t  target_workgroups;/* split tiles until the launch has this many, 0 = 4 per CU, or,
                                   where every operation has an output block of its own, the

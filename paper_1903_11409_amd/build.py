@@ -27,8 +27,19 @@ def is_stale() -> bool:
     return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + NATIVE_SOURCES + HEADERS)
 
 
-def build(verbose: bool = False) -> str:
-    """Compile every source for gfx950 and link the shared library.  Always recompiles."""
+def _run(cmd, verbose: bool) -> None:
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + r.stdout)
+    if verbose and r.stdout.strip():
+        print(r.stdout, file=sys.stderr)
+
+
+def build_library(verbose: bool = False) -> str:
+    """Compile every source for gfx950 and link libbspmm.so, which needs neither PyTorch nor numpy.  Always
+    recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -43,6 +54,13 @@ def build(verbose: bool = False) -> str:
            "-x", "hip", os.path.join(CSRC, "api.cpp"),
            "-x", "hip", os.path.join(CSRC, "staging.cpp"),
            "-o", LIB]
+    _run(cmd, verbose)
+    return LIB
+
+
+def build(verbose: bool = False) -> str:
+    """The library, then the extension module that binds it to PyTorch.  Always recompiles."""
+    build_library(verbose)
     # the extension module finds libbspmm.so in its own folder; PyTorch's libraries are loaded before it
     import numpy
     import torch
@@ -57,16 +75,9 @@ def build(verbose: bool = False) -> str:
               "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "binding.cpp"),
               "-L" + HERE, "-l:libbspmm.so", "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu",
               "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-o", NATIVE]
-    for c in (cmd, native):
-        if verbose:
-            print(" ".join(c), file=sys.stderr)
-        r = subprocess.run(c, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(os.path.basename(c[0]) + " failed:\n" + r.stdout)
-        if verbose and r.stdout.strip():
-            print(r.stdout, file=sys.stderr)
+    _run(native, verbose)
     return LIB
 
 
 if __name__ == "__main__":
-    print(build(verbose=True))
+    print((build_library if sys.argv[1:] == ["library"] else build)(verbose=True))

@@ -74,6 +74,22 @@ def test_wait_for_the_tables_ends_with_the_error_of_the_stream(tmp_path):
     assert subprocess.run([str(exe)], capture_output=True, timeout=30, text=True).stdout == "ok\n"
 
 
+def test_library_is_built_without_pytorch():
+    """A user of the C ABI has neither PyTorch nor numpy; the compiler is left out here."""
+    import subprocess
+    import sys
+    from paper_1903_11409_amd import build
+    code = ("import importlib.util, os, sys\n"
+            "sys.modules['torch'] = sys.modules['numpy'] = None\n"
+            "os.environ['HIPCC'] = '/bin/true'\n"
+            "spec = importlib.util.spec_from_file_location('build', sys.argv[1])\n"
+            "m = importlib.util.module_from_spec(spec)\n"
+            "spec.loader.exec_module(m)\n"
+            "print(m.build_library())\n")
+    r = subprocess.run([sys.executable, "-c", code, build.__file__], capture_output=True, text=True, timeout=60)
+    assert r.stdout.strip() == build.LIB, r.stderr
+
+
 POOL = r"""
 #include "staging.hpp"
 #include <atomic>
