@@ -197,7 +197,8 @@ PyObject* gcn(PyObject* const* ptrs, int64_t ldx, int64_t ldw, int64_t ldy, PyOb
     return finish(rc, "bspmm_run_gcn", value);
 }
 
-// (plan, X, W, bias, Y, n_X, F, accumulate, stream): leading dimensions from the tensors; returns Y
+// (plan, X, W, bias, Y, n_X, F, accumulate, stream): leading dimensions from the tensors (X's by its own
+// width, not by n_X); returns Y
 PyObject* plan_run_gcn(PyObject* const* a, Py_ssize_t n)
 {
     int64_t nx, F, ldx, ldw, ldy;

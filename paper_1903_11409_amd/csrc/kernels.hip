@@ -1148,8 +1148,8 @@ __device__ __forceinline__ void any_store(float* p, const typename Floats<VEC>::
     }
 }
 
-// Rows [0, nrows) of an item: sum(p0, p1, dense) of every row with the row pointers row(i), lanes of
-// VEC floats.  `first` loads a lane's floats given its offset in floats from the row's start.
+// Rows [0, nrows) of an item in lanes of VEC floats: row(i, p0, p1) gives row i's entries, entry(p) the
+// (key, value) of one, dense(key, l, n) the floats at l of the dense row it names, n of them in the row.
 template <int VEC, bool ALIGNED, typename Row, typename Entry, typename Dense>
 __device__ __forceinline__ void any_rows(uint32_t fw, int nrows, float* __restrict__ dst, int64_t ld_out, Row row,
                                          Entry entry, Dense dense)
