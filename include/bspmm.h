@@ -114,10 +114,10 @@ extern "C" {
                                       arrays and no transposed CSR is ever built.  Not checked;
                                       with an asymmetric A_i the result is A_i . dY_i.  Operations
                                       must be square (EINVAL)                                    */
-#define BSPMM_ONE_FRONT_LAUNCH 128u /* plans with front_features of two and more workgroups per CU
-                                      normally run bspmm_run_gcn as a launch of resident
-                                      workgroups that stream the graphs (see there); this flag
-                                      keeps them on the one-launch path                         */
+#define BSPMM_ONE_FRONT_LAUNCH 128u /* plans with front_features of more than a few dozen graphs
+                                      normally run bspmm_run_gcn gather first, in blocks of output
+                                      rows (see there); this flag keeps them on the kernel that
+                                      makes a graph's dense tile on chip                         */
 #define BSPMM_FLOOR_PROBE      4u  /* measurement aid: same grid, LDS and item fetches, but every
                                       item is emptied, so a run computes and writes nothing      */
 
@@ -227,10 +227,10 @@ typedef struct bspmm_info {
                                                 power-of-two tile, so runs with 16-byte aligned
                                                 operands launch the lean kernel                */
     int32_t front_stream[4];                 /* plans whose bspmm_run_gcn is run by resident
-                                                workgroups that stream the graphs (see there):
-                                                graphs in their lists, workgroups, LDS bytes per
-                                                workgroup, graphs left to a launch of their own;
-                                                all 0 otherwise                                */
+                                                workgroups (two (graph, 32 columns) and more per
+                                                CU): graphs whose rows they take, workgroups, LDS
+                                                bytes per workgroup, graphs left to a launch of
+                                                their own; all 0 otherwise                     */
     int64_t effective_bytes[2];              /* CSR + distinct dense inputs + outputs, once   */
     int64_t flops;                           /* 2 * nnz * F (Sec. V-A)                        */
     uint64_t workspace_bytes;
@@ -311,12 +311,10 @@ int bspmm_run(bspmm_plan* plan, const float* B, float* C, int64_t ldb, int64_t l
  * per channel, no intermediate U, B or C in memory).  X is the packed DEVICE feature matrix
  * (cols_i rows of n_X = options.front_features floats at row b_row_off[i], leading dimension
  * ldx >= n_X), W the DEVICE n_X x F weight matrix (leading dimension ldw >= F), bias F DEVICE
- * floats, Y indexed like C.  The dense part runs on the matrix cores in fp32
- * (v_mfma_f32_16x16x4_f32; whole layers in large launches: v_mfma_f32_32x32x2_f32) from LDS
- * to LDS; B_i never leaves the chip.  X, W, Y must be
+ * floats, Y indexed like C.  The dense part runs on the matrix cores, no less precise than fp32
+ * products added in fp32; B_i never leaves the chip.  X, W, Y must be
  * 16-byte aligned with ldx, ldw, ldy multiples of 4 (EINVAL).  ESTATE for plans created
- * without front_features.  (Launches of up to two workgroups per CU use workgroups of 512 lanes,
- * larger ones of 256.)
+ * without front_features.
  *
  * The whole layer in one launch: a plan created with front_features AND BSPMM_ACCUMULATE, in
  * which every operation is one of M channels of a graph - the M channel operations of a graph
@@ -326,22 +324,16 @@ int bspmm_run(bspmm_plan* plan, const float* B, float* C, int64_t ldb, int64_t l
  * under the other (M * n_X rows, channel ch at row ch * n_X) and bias M rows of F floats; the
  * channels of a graph are taken in the order of their operations.
  *
- * Layers of two and more (graph, feature tile) pairs per CU - single channels, or whole layers
- * of M = 2 to 8 channels (3 run as 4, 5 to 7 as 8, the added channels empty) - with n_X = 16, 32,
- * 64 or 128 run as a launch of RESIDENT workgroups instead, three per CU (8 channels: two per
- * CU, of eight wavefronts, one per channel): each keeps the weights of its feature tile in
- * registers for the whole launch and streams the graphs of its list through LDS, the next
- * graph's X_i and CSR in flight while the matrix cores work on this one's.  Small graphs whose
- * blocks lie back to back in X and in Y are taken several per trip; graphs too large for a
- * workgroup's share of the LDS are taken one at a time by the same workgroups (M = 1 or 4), or
- * follow in a launch of the one-launch kernel over their items.  The first run also enqueues a
- * kernel that copies the CSR arrays into one block per trip (once per plan, like the merged CSR
- * of summed sets; BSPMM_BUILD_TRANSPOSE moves it into bspmm_create).  For whole layers that
- * kernel also lists, per channel, the rows of X_i that the channel's entries name: only those
- * rows of X_i W[ch] + bias[ch] are made (a channel matrix with few entries per row leaves most
- * of them unread).  bspmm_info.front_stream says what a plan does; BSPMM_ONE_FRONT_LAUNCH keeps
- * a plan on the one-launch path.  With options.lds_bytes the caller fixes the LDS budget of
- * both.
+ * With n_X = 16, 32, 64 or 128 and a few dozen graphs or more the sum is taken as
+ * [A_i^0 X_i | A_i^1 X_i | ...] [W[0]; W[1]; ...] plus the row sums of A_i^ch times bias[ch], in blocks of
+ * 16 to 64 output rows (K = M * n_X past 512: in two launches, the second adding to the first); layers of
+ * many graphs are run by RESIDENT workgroups, two or three per CU, that keep the weights of their columns
+ * in registers for the whole launch.  The first run then also enqueues a kernel that writes the blocks'
+ * row starts and entries (once per plan, like the merged CSR of summed sets; BSPMM_BUILD_TRANSPOSE moves
+ * it into bspmm_create).  Graphs of more than six entries per row keep the one-launch kernel, which
+ * makes the dense tile of a graph on chip and gathers from it (in layers of many graphs: in a launch of
+ * their own, bspmm_info.front_stream says how many).  BSPMM_ONE_FRONT_LAUNCH keeps a plan on that kernel.
+ * With options.lds_bytes the caller fixes the LDS budget of both.
  */
 int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W, int64_t ldw,
                   const float* bias, float* Y, int64_t ldy, int32_t accumulate, void* stream);
@@ -418,8 +410,7 @@ int bspmm_validate(bspmm_plan* plan, int32_t* bad_op, void* stream);
 #define BSPMM_KERNEL_BUILD     5  /* transposed-CSR build, 256 lanes                               */
 #define BSPMM_KERNEL_BUILD_L   6  /* transposed-CSR build, 1024 lanes                              */
 #define BSPMM_KERNEL_COO       7  /* direct COO product                                            */
-#define BSPMM_KERNEL_LAYER_STREAM 8 /* bspmm_run_gcn, whole layer, resident streaming workgroups
-                                       (n_X = 64, two blocks per wavefront)                        */
+#define BSPMM_KERNEL_LAYER_STREAM 8 /* bspmm_run_gcn, gather first (K = 256, four wavefronts)          */
 typedef struct bspmm_kernel_resources {
     int32_t vgprs;              /* vector registers per lane                                   */
     int32_t sgprs;              /* scalar registers per wavefront (0: the runtime does not say)*/
@@ -438,9 +429,8 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info);
 /* Copy up to `capacity` scheduled items of one direction (0 forward, 1 transposed) into
  * `items`; *count receives the total number.  HOST only.  These are the items of the one-launch
  * schedule, which bspmm_run, bspmm_run_transposed and the one-launch kernel of bspmm_run_gcn
- * work from; a plan whose bspmm_run_gcn is run by streaming workgroups
- * (bspmm_info.front_stream) takes from it only the items of the graphs left to the second
- * launch. */
+ * work from; a plan whose bspmm_run_gcn runs gather first takes from it only the items of the
+ * graphs left to the one-launch kernel. */
 int bspmm_plan_items(const bspmm_plan* plan, int32_t transposed, bspmm_item* items,
                      int32_t capacity, int32_t* count);
 

@@ -29,10 +29,12 @@ hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStre
 hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool accumulate,
                             bool sets, bool wide, hipStream_t stream);
 int front_workgroups_per_cu(bool sets, bool wide, int lds_bytes);
-hipError_t launch_bspmm_gcn_stream(const StreamParams& S, int nx16, int units, int waves, int grid,
-                                   int lds_bytes, hipStream_t stream);
-bool stream_supported(int nx16, int units, int waves);
-int stream_workgroups_per_cu(int nx16, int units, int waves, int lds_bytes);
+bool layer_supported(int ks, int units, int rb, int waves);
+int layer_workgroups_per_cu(int ks, int units, int rb, int waves, int lds_bytes);
+hipError_t launch_bspmm_layer(const LayerParams& P, int ks, int units, int rb, int waves, int lds_bytes, hipStream_t stream);
+hipError_t launch_layer_rows(const LayerSet* sets, int count, const OpRecord* ops, const int32_t* rpt,
+                             const int32_t* colids, const float* values, int32_t* starts, int32_t* entries,
+                             int32_t* out_rows, hipStream_t stream);
 hipError_t launch_build_transpose(const OpRecord* ops, int batch, int threads, int lds_bytes,
                                   const int32_t* rpt, const int32_t* colids,
                                   const float* values, int32_t* rpt_t, int32_t* colids_t,
@@ -90,9 +92,9 @@ struct Layout {
     // summed sets (BSPMM_ACCUMULATE), per direction: their records and their merged CSR arrays
     size_t sets[2] = {0, 0};
     size_t merged[2] = {0, 0};
-    // whole layers run by streaming workgroups: graph records, list bounds, and the items of the
-    // graphs that stay with the one-launch kernel
-    size_t stream_records = 0, stream_merged = 0, stream_sets = 0, stream_list = 0, stream_rest = 0;
+    // layers run by resident workgroups: graph records, the items of the graphs that stay with the
+    // one-launch kernel, and the arrays the device builds
+    size_t stream_sets = 0, stream_rest = 0, stream_arrays = 0;
     // plans made from COO operands: the CSR arrays built on the device and what the build needs
     size_t coo_records = 0;
     size_t csr_rpt = 0, csr_colids = 0, csr_values = 0;
@@ -137,25 +139,25 @@ struct bspmm_plan {
     int64_t merged_words[2] = {0, 0};
     bool merged_built[2] = {false, false};
     int front_channels = 1;   // fused front with BSPMM_ACCUMULATE: channels per output block
-    // Whole layers in launches of many rounds: the graphs that fit the LDS budget of the
-    // streaming launch, in list order; list l is sets[list[l]] .. sets[list[l + 1]]; the items of
-    // the other graphs, for a launch of bspmm_gcn_kernel of their own.
+    // Layers in launches of many rounds (bspmm_layer_kernel): the graphs whose rows are cut into blocks,
+    // and the items of the others, for a launch of bspmm_gcn_kernel of their own.
     struct Stream {
-        std::vector<StreamSet> sets;
-        std::vector<int32_t> list;
+        // Channels that one launch adds up (all of them, or halves where K = channels n_X is more than a
+        // wavefront's registers hold weights for): its graph records, and its arrays in the workspace.
+        struct Part {
+            int first_channel = 0, channels = 0, ks = 0, lds_bytes = 0, ranges_per_xcd = 0, slots = 0;
+            size_t sets_at = 0;                                       // first record
+            int64_t starts_at = 0, entries_at = 0;                    // words from the arrays' base
+        };
+        std::vector<Part> parts;
+        std::vector<LayerSet> sets;
         std::vector<WorkItem> rest;
-        int nx16 = 0, units = 0, waves = 4, fw = 0, tiles = 0, lists = 0;
-        bool compact = false;            // the groups bring lists of the tile rows in use
-        int channels = 1;                // channels the kernel runs with (the layer's, or the next of 4 and 8)
-        std::vector<SetRecord> records;   // one per group of graphs, for the kernel that merges CSR arrays
-        int64_t merged_words = 0;  // words of the groups' merged CSR blocks
-        bool merged_built = false;
-        int graphs = 0;            // graphs in the lists (a list entry is a group of one or more)
-        int tile_words = 0, x_words = 0, csr_words = 0;
-        int big_csr_words = 0;     // room for the merged CSR block of a graph taken one at a time
-        int big = 0;               // graphs taken one at a time
-        int lds_bytes() const { return 4 * (tile_words + 2 * x_words + 2 * csr_words + 64); }
-        bool on() const { return !sets.empty(); }
+        int units = 0, rb = 0, waves = 4, tiles = 0, blocks = 0;
+        int64_t out_rows_at = 0, words = 0;
+        bool built = false;
+        int graphs = 0;
+        bool many = false;           // enough graphs to be reported as streamed
+        bool on() const { return !parts.empty(); }
     } stream;
     int64_t effective_bytes[2] = {0, 0};
     int64_t flops = 0;
@@ -252,8 +254,6 @@ void describe_sets(bspmm_plan& p, int d)
             r.nz_off[j] = o.nz_off[mem[j]];
             r.nnz[j] = o.nnz[mem[j]];
             r.k[j] = o.k[mem[j]];
-            r.row_off[j] = 0;
-            r.rows[j] = o.m[mem[0]];
             size_t owner = j;
             for (size_t e = 0; e < j; ++e)
                 if (o.in_off[mem[e]] == o.in_off[mem[j]] && o.k[mem[e]] == o.k[mem[j]]) {
@@ -298,20 +298,10 @@ void describe_sets(bspmm_plan& p, int d)
         }
 }
 
-// Layers (bspmm_run_gcn) of two and more workgroups per CU: the plan of the streaming launch.
-// A workgroup of the streaming kernel holds the weights of its feature tile in registers
-// (M * fw / 16 blocks of 16 columns over four wavefronts: one or two per wavefront) and takes
-// the graphs of its list one after the other; what it takes per trip is a *group*: one graph, or
-// several small graphs that lie back to back in X and in Y, which are to the kernel one graph
-// with a block-diagonal matrix (fewer trips, fuller 16-row blocks for the matrix instructions).
-// Every group gets one merged CSR block (row pointers, columns, values back to back), built once
-// per plan by the kernel that merges summed sets: its members are the channel operations of the
-// group's graphs, each with its rows' place in the group and its tile's place in the group's
-// dense tile.  The launch's LDS is sized for the groups that fit the budget (three workgroups per
-// CU unless the caller fixed lds_bytes), smallest first; larger graphs are taken one at a time
-// by the same workgroups where the kernel can, and otherwise keep their items of the one-launch
-// schedule and run in a launch of their own.  Lists are balanced by
-// longest-processing-time-first on an estimate of a trip's cycles.
+// Layers (bspmm_run_gcn): the plan of the gather-first launch (bspmm_layer_kernel).  The output rows of the
+// graphs, one after the other in the order of their layer input, are cut into blocks of 16, 32 or 64; a
+// workgroup takes a run of blocks and 64 or 128 columns.  The device writes what the blocks read
+// (layer_rows_kernel), the host only places every graph's share.
 void make_stream_plan(bspmm_plan& p)
 {
     bspmm_plan::Stream& st = p.stream;
@@ -320,351 +310,169 @@ void make_stream_plan(bspmm_plan& p)
     const Knobs& kn = p.knobs;
     const int nx = kn.front, F = p.F;
     if (nx <= 0 || kn.one_front_launch || !sc.fused_sets.empty() || sc.fused_tasks > 0) return;
+    if (nx != 16 && nx != 32 && nx != 64 && nx != 128) return;
     // (plans of single channels - no operations summed - take the same kernel with one channel)
     const bool single = sc.merged_sets.empty();
-    // Layers of 3, 5, 6 or 7 channels run as layers of 4 or 8 whose last channels are empty: no
-    // entry names a row of their tiles, their weights read as zero, and with the lists of rows in
-    // use their wavefronts have no matrix work at all.
     const int channels = single ? 1 : p.front_channels;
-    if (!single && !kn.accumulate) return;
-    if (nx % 16 != 0 || channels < 1 || channels > 8) return;
-    const int M = channels <= 2 ? channels : (channels <= 4 ? 4 : 8);
-    const int nx16 = nx / 16;
-    int units = 0, fw = 0, waves = 4;
-    // (two blocks per wavefront first, except for two channels: one block per wavefront makes
-    // their tiles 32 columns wide like those of four channels - eight lanes per output row, 32
-    // rows per gather pass, larger graphs taken in the same launch - and measured 2048 graphs at
-    // n_X = 64 38 against 51 us, 512 graphs 12 against 23 us.  Eight channels: workgroups of
-    // eight wavefronts, one per channel, for the same reason.)
-    const int shapes[4][2] = {{M == 2 ? 1 : 2, M == 8 ? 8 : 4}, {M == 2 ? 2 : 1, M == 8 ? 8 : 4}, {2, 4}, {1, 4}};
-    for (const auto& sh : shapes) {
-        const int u = sh[0], wv = sh[1];
-        const int w = 16 * wv * u / M;
-        // (tiles of up to 64 columns: 16 lanes per output row, 64 rows in the gather's passes)
-        if (w >= 16 && w <= 64 && F % w == 0 && stream_supported(nx16, u, wv)) {
-            units = u;
-            waves = wv;
-            fw = w;
-            break;
-        }
-    }
-    if (!units) return;
-    const int threads = 64 * waves;
-    const int tiles = F / fw;
+    if (channels < 1 || channels > kMaxMembers || (!single && !kn.accumulate)) return;
     const DirOps& o = p.dir[0];
-    // the graphs: sets of channel operations, or the operations themselves
-    std::vector<std::vector<int>> single_sets;
-    if (single)
-        for (int i = 0; i < o.size(); ++i) single_sets.push_back(std::vector<int>(1, i));
-    const std::vector<std::vector<int>>& graphs = single ? single_sets : sc.merged_sets;
-    const size_t n_graphs = graphs.size();
-    // a launch of less than two workgroups per CU gains nothing from resident workgroups
-    // (measured, four channels, F = 128, n_X = 64 / 32: 64 graphs 9.5 against 9.4 us for the
-    // one-launch kernel; 128 graphs 10.5 / 8.2 against 11.9 / 8.2; 256 graphs 14.6 / 10.4
-    // against 24.4 / 15.8)
-    // Kernels with one block per wavefront and several channels (tiles of 16 columns): 128
-    // graphs at n_X = 128 take 22.9 against 18.1 us, 512 graphs 51 against 63.
-    if ((int64_t)n_graphs * tiles < (units == 2 || single ? 2 : 8) * (int64_t)kn.compute_units) return;
-    // One channel: a trip holds a quarter of a four-channel trip's matrix work for the same
-    // bookkeeping, and the one-launch kernel stays ahead for longer - measured on molecule
-    // graphs of 25 nodes on 256 CUs, streamed against one launch: n_X = 32: 512 graphs 9.5
-    // against 8.5 us, 1024 graphs 13.6 against 14.4; n_X = 64: 384 graphs 10.5 against 9.2, 448
-    // graphs 10.9 against 11.9; n_X = 128: 256 graphs 15.4 against 15.2, 512 graphs 16.7 against
-    // 19.7.  The crossing sits near 700,000 elements of layer input.
+    const size_t n_graphs = single ? (size_t)o.size() : sc.merged_sets.size();
+    auto op_of = [&](size_t g, int c) { return single ? (int)g : sc.merged_sets[g][(size_t)c]; };
+    // Launches of two (graph, 32 columns) and more per CU - of one channel also 700,000 elements of layer
+    // input on 256 CUs - are the ones that bspmm_info.front_stream reports (resident workgroups).
+    st.many = (int64_t)n_graphs * ((F + 31) / 32) >= (single ? 4 : 2) * (int64_t)kn.compute_units;
     if (single) {
         int64_t x_rows = 0;
-        for (size_t g = 0; g < n_graphs; ++g) x_rows += o.k[graphs[g][0]];
-        if (x_rows * nx * 256 < (int64_t)700000 * kn.compute_units) return;
+        for (int i = 0; i < o.size(); ++i) x_rows += o.k[i];
+        st.many = st.many && x_rows * nx * 256 >= (int64_t)700000 * kn.compute_units;
     }
 
-    // ---- groups: graphs back to back in X and in Y, while the members fit a record, the rows of
-    // X three 16-row blocks (four for single channels) and the rows of Y the gather's passes
-    // (three workgroups per CU: a third of the CU's 160 KiB less what the allocation granule
-    // takes; 53920 bytes were measured to leave room for two only)
-    // (workgroups of eight wavefronts: two per CU, half of a CU's LDS each)
-    const int64_t budget_words = (kn.lds_given ? kn.lds_words * 4 : (waves == 8 ? 81920 : 53248)) / 4;
-    const int rows_most = kStreamPasses * (threads / (fw / 4));
-    // (a group must still go through the buffers: its tile, two buffers of X rows and two of CSR
-    // blocks - about ten words a row each, and one per channel for the lists of rows in use -
-    // inside the budget)
-    const int group_rows = (int)std::min<int64_t>(single ? 64 : 48, (budget_words - 64) / ((int64_t)M * fw + 2 * nx + 20 + (single ? 0 : 2 * M)));
-    const int group_graphs = kMaxMembers / channels;
-    std::vector<int> by_input;
-    for (size_t g = 0; g < n_graphs; ++g) {
-        const int op0 = graphs[g][0];
-        if (o.m[op0] > 0 && o.k[op0] > 0) by_input.push_back((int)g);
-    }
-    std::stable_sort(by_input.begin(), by_input.end(),
-                     [&](int a, int b) { return o.in_off[graphs[a][0]] < o.in_off[graphs[b][0]]; });
-    // How many graphs a group may hold is chosen for the launch: larger groups mean fewer and
-    // longer trips, and a list of two long trips beside lists of one is a launch twice as long as
-    // it need be (1024 single-channel graphs at n_X = 128: 28.6 us in groups of up to eight,
-    // 21.8 us ungrouped; 2048 graphs: 33 against 43 us).  Each size is tried and the one with the
-    // smallest estimate - the larger of "work per list" and "trips of the fullest list x work per
-    // trip", a trip counted as two units plus three per 16-row block - is kept.
-    auto form_groups = [&](int most) {
-        std::vector<std::vector<int>> out;
-        int64_t kx_sum = 0, m_sum = 0;
-        for (int g : by_input) {
-            const int op0 = graphs[g][0];
-            bool joins = false;
-            if (!out.empty() && (int)out.back().size() < most) {
-                const int last = graphs[out.back().back()][0];
-                joins = o.in_off[op0] == o.in_off[last] + o.k[last] && o.out_off[op0] == o.out_off[last] + o.m[last] &&
-                        kx_sum + o.k[op0] <= group_rows && m_sum + o.m[op0] <= rows_most;
-            }
-            if (!joins) {
-                out.push_back(std::vector<int>());
-                kx_sum = m_sum = 0;
-            }
-            out.back().push_back(g);
-            kx_sum += o.k[op0];
-            m_sum += o.m[op0];
-        }
-        return out;
-    };
-    std::vector<std::vector<int>> groups;
-    {
-        const int64_t cap_lists = std::max<int64_t>(1, (waves == 8 ? 2 : 3) * (int64_t)kn.compute_units / tiles);
-        double best = 0;
-        for (int most = 1; most <= group_graphs; ++most) {
-            std::vector<std::vector<int>> cand = form_groups(most);
-            int64_t total = 0;
-            for (const std::vector<int>& grp : cand) {
-                int64_t kx = 0;
-                for (int g : grp) kx += o.k[graphs[g][0]];
-                total += 3 * ((kx + 15) / 16) + 2;
-            }
-            const int64_t lists = std::max<int64_t>(1, std::min<int64_t>((int64_t)cand.size(), cap_lists));
-            const double per_trip = cand.empty() ? 0.0 : (double)total / (double)cand.size();
-            const double estimate = std::max((double)total / (double)lists,
-                                             (double)(((int64_t)cand.size() + lists - 1) / lists) * per_trip);
-            if (most == 1 || estimate <= best) {
-                best = estimate;
-                groups.swap(cand);
-            }
-        }
-    }
-    const size_t n_sets = groups.size();
-    if (n_sets == 0) return;
-    // Layers of several channels in which a wavefront's blocks belong to one channel: the rows of
-    // a channel's dense tile that none of its entries names are not made (see merge_sets_kernel).
-    const bool compact_on = M >= 2 && (units == 1 || fw >= 32);
-    // one record per group for the merging kernel; what the rest of this function needs of a group
-    std::vector<SetRecord>& recs = st.records;
-    std::vector<int64_t> nnz_sum(n_sets, 0);
-    {
-        int64_t words = 0;
-        for (size_t s = 0; s < n_sets; ++s) {
-            SetRecord r;
-            std::memset(&r, 0, sizeof r);
-            int64_t kxt = 0, mt = 0;
-            for (int g : groups[s]) {
-                kxt += o.k[graphs[g][0]];
-                mt += o.m[graphs[g][0]];
-            }
-            int j = 0;
-            int64_t x_at = 0, m_at = 0;
-            for (int g : groups[s]) {
-                const int op0 = graphs[g][0];
-                for (int c = 0; c < channels; ++c, ++j) {
-                    const int op = graphs[g][c];
-                    r.rpt_off[j] = o.rpt_off[op];
-                    r.nz_off[j] = o.nz_off[op];
-                    r.nnz[j] = o.nnz[op];
-                    r.k[j] = o.k[op0];
-                    r.tile_row[j] = (int32_t)(c * kxt + x_at);     // channel c's tile, this graph's rows of it
-                    r.row_off[j] = (int32_t)m_at;
-                    r.rows[j] = o.m[op0];
-                    nnz_sum[s] += o.nnz[op];
-                }
-                x_at += o.k[op0];
-                m_at += o.m[op0];
-            }
-            r.members = j;
-            r.m = (int32_t)mt;
-            r.plain = 1;
-            r.merged_rpt_off = words;
-            words += round_up((int)mt + 1, 4);
-            r.merged_nz_off = words;
-            words += 2 * (int64_t)round_up((int)nnz_sum[s], 4) + (compact_on ? compact_words(M, (int)kxt) : 0);
-            recs.push_back(r);
-        }
-        st.merged_words = words;
-        if (words >= (int64_t(1) << 32)) {
-            st = bspmm_plan::Stream();
-            return;
-        }
-    }
-    auto kx_of = [&](int s) {
-        int64_t k = 0;
-        for (int g : groups[s]) k += o.k[graphs[g][0]];
-        return k;
-    };
-
-    // the groups by size; take them while the launch's LDS stays inside the budget
-    std::vector<int> order(n_sets);
-    for (size_t i = 0; i < n_sets; ++i) order[i] = (int)i;
-    // (X has kx rows; Y has m)
-    auto words_of = [&](int64_t kx, int64_t csr) { return (int64_t)M * kx * fw + 2 * kx * nx + 2 * csr + 64; };
-    auto csr_of = [&](int i) {
-        return (int64_t)round_up(recs[i].m + 1, 4) + 2 * (int64_t)round_up((int)nnz_sum[i], 4);
-    };
-    std::vector<int64_t> kxs(n_sets);
-    for (size_t i = 0; i < n_sets; ++i) kxs[i] = kx_of((int)i);
-    // (a group that goes through the buffers brings its lists of rows in use)
-    auto csr_piped = [&](int i) {
-        return csr_of(i) + (compact_on && (int64_t)M * kxs[i] <= kCompactRows ? compact_words(M, (int)kxs[i]) : 0);
-    };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return words_of(kxs[a], csr_piped(a)) < words_of(kxs[b], csr_piped(b));
-    });
-    int64_t kx_cap = 0, csr_cap = 0;
+    // the graphs in the order of their layer input; those of more than kLayerDegree entries per row, whose
+    // blocks would name more rows of X than a workgroup holds, keep their items of the one-launch schedule
+    constexpr int kLayerDegree = 6;
+    constexpr int64_t kLimit = (int64_t)1 << 31;
     std::vector<int> mine;
-    for (int i : order) {
-        const SetRecord& r = recs[i];
-        // (more output rows than the gather's passes hold: not through the buffers)
-        if (r.m > rows_most || (compact_on && (int64_t)M * kxs[i] > kCompactRows)) continue;
-        const int64_t kx = std::max<int64_t>(kx_cap, kxs[i]);
-        const int64_t cw = std::max(csr_cap, csr_piped(i));
-        if (words_of(kx, cw) > budget_words) continue;    // (a later one may still fit the caps)
-        kx_cap = kx;
-        csr_cap = cw;
-        mine.push_back(i);
-    }
-    if (mine.empty()) {
-        st = bspmm_plan::Stream();
-        return;
-    }
-    st.nx16 = nx16, st.units = units, st.waves = waves, st.fw = fw, st.tiles = tiles;
-    st.channels = M;
-    st.compact = compact_on;
-    if (compact_on)
-        for (int i : mine) recs[i].compact = M | ((int32_t)kxs[i] << 8);
-    st.tile_words = (int)(M * kx_cap * fw);
-    st.x_words = (int)(kx_cap * nx);
-    st.csr_words = (int)csr_cap;
-    // Larger graphs: taken one at a time, their tile at the start of the same LDS (kernels with
-    // two blocks per wavefront: two half tiles of 16 columns, one after the other), the CSR block
-    // at its end and at least one 16-row block of X between them; the X buffers are made larger
-    // than the listed groups need where that is what it takes, up to the budget.
-    std::vector<int> halves;
-    if ((units == 2 && fw == 32) || units == 1) {
-        const int piece = units == 2 ? 16 : fw;
-        const int64_t total = budget_words - 64;
-        std::vector<char> is_mine(n_sets, 0);
-        for (int i : mine) is_mine[i] = 1;
-        auto fits_halves = [&](int i, int64_t csr_room) {
-            return csr_of(i) <= csr_room && (int64_t)M * kxs[i] * piece + 16 * nx + csr_room <= total;
-        };
-        int64_t room = 0;
-        for (size_t i = 0; i < n_sets; ++i)
-            if (!is_mine[i] && fits_halves((int)i, csr_of((int)i))) room = std::max(room, csr_of((int)i));
-        for (size_t i = 0; i < n_sets; ++i)
-            if (!is_mine[i] && fits_halves((int)i, room)) halves.push_back((int)i);
-        st.big_csr_words = halves.empty() ? 0 : (int)room;
-        st.big = (int)halves.size();
-        int64_t need = 0;
-        for (int i : halves) need = std::max(need, (int64_t)M * kxs[i] * piece + 16 * nx + room);
-        const int64_t have = (int64_t)st.tile_words + 2 * st.x_words + 2 * st.csr_words;
-        if (need > have) st.x_words += (int)round_up((int)((need - have + 1) / 2), 4);
-    }
-
-    // lists: as many workgroups as the chip holds at once, the same lists for every tile
-    int per_cu = kn.device_ok ? stream_workgroups_per_cu(nx16, units, waves, st.lds_bytes()) : 0;
-    if (per_cu <= 0) per_cu = std::max(1, std::min(3, kMaxLdsBytes / std::max(1, st.lds_bytes())));
-    // (a graph taken one at a time stages its X twice and overlaps nothing)
-    std::vector<char> in_halves(n_sets, 0);
-    for (int i : halves) in_halves[i] = 1;
-    // What a trip costs, in units of about a hundred cycles, fitted to per-trip clocks of three
-    // launches of 2048 graphs with three workgroups per CU (four channels at n_X = 64: trips of
-    // one, two and three 16-row blocks took 5200, 7400 and 15000 cycles; one channel at
-    // n_X = 32: 3500 to 11500 for one to four blocks; at n_X = 128: 4900 to 18600 for one to
-    // three): a fixed part, the matrix instructions of the wavefront (16-row blocks x n_X / 16
-    // x blocks per wavefront), and every pass of the gather after the first, which starts from
-    // the row pointers in LDS instead of from registers and costs the more the longer the
-    // matrix phases of the workgroups beside it hold the SIMDs.
-    const int rows_per_pass_c = threads / (fw / 4);
-    const int64_t sw = (int64_t)nx16 * units;      // matrix instructions per 16-row block, in fours
-    auto trip_cost = [&](int64_t blocks, int64_t m) {
-        const int64_t passes = std::max<int64_t>(1, (m + rows_per_pass_c - 1) / rows_per_pass_c);
-        return 20 + 3 * blocks * sw + (20 + 25 * sw / 8) * (passes - 1);
-    };
-    // (a graph taken one at a time pays for its chunks and pieces without overlap: in the same
-    // launches four to eight blocks took 23000 to 41000 cycles with four channels, five to nine
-    // blocks 16000 to 36000 with one channel at n_X = 32, three to nine 19000 to 51000 at 128)
-    auto cost = [&](int i) {
-        const int64_t blocks = (kxs[i] + 15) / 16;
-        return in_halves[i] ? std::max<int64_t>(20, 45 * blocks + 10 * sw - 25) : trip_cost(blocks, recs[i].m);
-    };
-    mine.insert(mine.end(), halves.begin(), halves.end());
-    const int lists = (int)std::max<size_t>(1, std::min<size_t>(mine.size(), (size_t)per_cu * kn.compute_units / tiles));
-    st.lists = lists;
-    std::stable_sort(mine.begin(), mine.end(), [&](int a, int b) { return cost(a) > cost(b); });
-    std::vector<std::vector<int>> of_list(lists);
-    {
-        std::set<std::pair<int64_t, int>> load;      // (cost so far, list)
-        for (int l = 0; l < lists; ++l) load.insert({0, l});
-        for (int i : mine) {
-            auto least = *load.begin();
-            load.erase(load.begin());
-            of_list[least.second].push_back(i);
-            least.first += cost(i);
-            load.insert(least);
-        }
-    }
-    st.list.push_back(0);
     std::vector<char> streamed(n_graphs, 0);
-    for (int l = 0; l < lists; ++l) {
-        // the graphs taken one at a time first: the kernel takes them before it starts its pipeline
-        std::stable_partition(of_list[l].begin(), of_list[l].end(), [&](int i) { return in_halves[i] != 0; });
-        for (int i : of_list[l]) {
-            const SetRecord& r = recs[i];
-            const int op0 = graphs[groups[i][0]][0];
-            StreamSet e;
-            e.in_row = o.in_off[op0];
-            e.out_row = o.out_off[op0];
-            e.csr_off = (uint32_t)r.merged_rpt_off;
-            e.m = r.m;
-            e.kx = (int32_t)kxs[i];
-            e.nnz = (int32_t)nnz_sum[i];
-            st.sets.push_back(e);
-            for (int g : groups[i]) streamed[g] = 1;
-            st.graphs += (int)groups[i].size();
+    int64_t rows = 0, entries = 0;
+    for (size_t g = 0; g < n_graphs; ++g) {
+        const int op0 = op_of(g, 0);
+        int64_t nnz = 0;
+        for (int c = 0; c < channels; ++c) nnz += o.nnz[op_of(g, c)];
+        if (o.m[op0] <= 0) continue;
+        if (nnz > (int64_t)kLayerDegree * o.m[op0] || o.in_off[op0] + o.k[op0] >= kLimit ||
+            o.out_off[op0] + o.m[op0] >= kLimit) {
+            if (!st.many) return;
+            continue;
         }
-        st.list.push_back((int32_t)st.sets.size());
+        mine.push_back((int)g);
+        streamed[g] = 1;
+        rows += o.m[op0];
+        entries += nnz;
     }
-    // Every list as the kernel will read it: the graphs it takes one at a time first and
-    // inside the room of that mode, every other graph inside the buffers (the kernel's own
-    // tests, which decide where its loads and stores go).  A table that fails is not used.
+    if (mine.empty() || (rows + 64) * channels >= kLimit || entries >= kLimit) return;
+    // Fewer graphs: one block to a workgroup, where there are enough to matter.  The arrays cost the first
+    // run of a plan a launch that a single channel does not have otherwise (about 5 us; whole layers merge
+    // their channels' CSR arrays for either kernel).  us of a run, F = 128, this kernel / one-launch kernel:
+    // one channel at n_X = 64, 16 graphs 4.5 / 4.5, 64 graphs 4.7 / 6.1, 128 graphs 5.0 / 6.9; four channels
+    // at n_X = 64, 24 graphs 6.4 / 6.6, 128 graphs 6.9 / 14.2; K = channels n_X past 256: 24 graphs of
+    // four channels at n_X = 128 9.9 / 8.5, 64 graphs 9.9 / 14.0.
+    if (!st.many && (rows + 15) / 16 * (single || channels * nx > 256 ? 4 : 8) < kn.compute_units) return;
+    std::stable_sort(mine.begin(), mine.end(),
+                     [&](int a, int b) { return o.in_off[op_of(a, 0)] < o.in_off[op_of(b, 0)]; });
+
+    // channels per launch: K = channels n_X up to 512 (96 registers per 16 columns and 256 of K)
+    const int launches = channels * nx > 512 ? 2 : 1;
+    const int most = (channels + launches - 1) / launches;
+    static const int kSteps[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    auto steps_of = [&](int ch) {
+        for (int k : kSteps)
+            if (32 * k >= ch * nx) return k;
+        return 0;
+    };
+    // Shape of a workgroup.  Past 64 columns: four wavefronts of 32 columns up to K = 48, eight of 16 columns
+    // from K = 64 on (a lane then holds half the weights and twice the wavefronts hide each other's
+    // latencies: us at 700 molecules, F = 128, four against eight: K = 32 7.2 / 8.6, K = 64 8.6 / 8.7, K = 128
+    // 13.1 / 12.0, K = 256 17.4 / 15.0, K = 512 30.0 / 26.1; 2048 at K = 64 16.8 / 14.8); more than four
+    // channels have no register for a second bias there up to K = 256.  Launches that leave half the chip
+    // idle that way take tiles of 64 columns (64 molecules, K = 64 5.2 / 4.9 / 4.7, K = 256 7.6 / 6.7 / 6.4).
+    int units = steps_of(most) <= 8 && F > 64 ? 2 : 1, waves = 4;
+    if (F > 64 && most * nx >= 64 && (most <= 4 || most * nx > 256)) units = 1, waves = 8;
+    if (F > 64 && (rows + 15) / 16 * 2 * ((F + 127) / 128) <= kn.compute_units) units = 1, waves = 4;
+    const int tiles = (F + 16 * waves * units - 1) / (16 * waves * units);
+    // LDS: a third of a CU's; half of it where that holds the rows of X of few entries.  Rows of a block: up
+    // to 64 where the rows of X that they name (a quarter more than on average) then have slots, by the
+    // number of trips times what a trip costs: a fixed part and the passes of its gather (one channel at
+    // n_X = 16, F = 64, 2048 molecules, 16 / 32 / 64 rows: 11.2 / 9.4 / 9.2 us; at n_X = 64, 1200: 9.3 / 9.8).
+    const int budget = kn.lds_given ? kn.lds_words * 4 : 53248;
+    auto slots_in = [&](int rb, int ch, int bytes, int want) {
+        const int unit = 256 / nx;             // rows that a wavefront's request brings
+        int n = round_up(std::min(want, 256), unit);
+        while (n > 0 && layer_lds(steps_of(ch), rb, waves, ch, n, nx).total > bytes) n -= unit;
+        return n;
+    };
+    const double per_row = (double)entries / (double)rows;
+    auto wanted = [&](int rb) { return (int)(20.0 * rb * per_row) + 16; };
+    int rb = 1;
     {
-        const int rows_per_pass = threads / (fw / 4);
-        const int64_t total = (int64_t)st.tile_words + 2 * st.x_words + 2 * st.csr_words;
-        const int piece = units == 2 ? 16 : fw;
-        bool ok = true;
-        for (int l = 0; l < lists && ok; ++l) {
-            bool piped = false;
-            for (int j = st.list[l]; j < st.list[l + 1] && ok; ++j) {
-                const StreamSet& e = st.sets[j];
-                const int64_t csr = (int64_t)round_up(e.m + 1, 4) + 2 * (int64_t)round_up(e.nnz, 4);
-                const int64_t lists_words = st.compact ? compact_words(M, e.kx) : 0;
-                const bool big = (int64_t)M * e.kx * fw > st.tile_words || (int64_t)e.kx * nx > st.x_words ||
-                                 csr + lists_words > st.csr_words || e.m > kStreamPasses * rows_per_pass ||
-                                 (st.compact && (int64_t)M * e.kx > kCompactRows);
-                ok = e.kx > 0 && e.m > 0;
-                if (big) {
-                    const int64_t chunk = ((total - st.big_csr_words - (int64_t)M * e.kx * piece) / nx) & ~int64_t(15);
-                    ok = ok && !piped && ((units == 2 && fw == 32) || units == 1) && csr <= st.big_csr_words && chunk >= 16;
-                } else {
-                    piped = true;
-                }
+        const int groups = 256 * waves / nx;     // virtual rows that a pass takes
+        double best = 0;
+        for (int r = 1; r <= 4; r *= 2) {
+            if (!layer_supported(steps_of(most), units, r, waves) || 16 * r * most > 240 ||
+                (r > 1 && slots_in(r, most, budget, wanted(r)) < std::min(wanted(r), 256)))
+                continue;
+            const int64_t round = (int64_t)16 * r * 3 * kn.compute_units;
+            const int64_t trips = (rows * tiles + round - 1) / round;
+            const double cost = (double)trips * (1 + (16 * r * most + groups - 1) / groups);
+            if (r == 1 || cost < best) {
+                best = cost;
+                rb = r;
             }
         }
-        if (!ok) {
+    }
+    const int64_t blocks = (rows + 16 * rb - 1) / (16 * rb);
+    st.units = units;
+    st.rb = rb;
+    st.waves = waves;
+    st.tiles = tiles;
+    st.blocks = (int)blocks;
+    int64_t at = 0;
+    auto place = [&at](int64_t words) {
+        const int64_t here = at;
+        at += (words + 3) / 4 * 4;
+        return here;
+    };
+    st.out_rows_at = place(16 * rb * blocks);
+    for (int c0 = 0; c0 < channels; c0 += most) {
+        bspmm_plan::Stream::Part part;
+        part.first_channel = c0;
+        part.channels = std::min(most, channels - c0);
+        part.ks = steps_of(part.channels);
+        if (!layer_supported(part.ks, units, rb, waves)) {
             st = bspmm_plan::Stream();
             return;
         }
+        part.slots = slots_in(rb, part.channels, budget, std::max(wanted(rb), 64));
+        if (!kn.lds_given && part.slots < 40) part.slots = slots_in(rb, part.channels, 81920, std::max(wanted(rb), 64));
+        if (part.slots < 16) {
+            st = bspmm_plan::Stream();
+            return;
+        }
+        part.lds_bytes = layer_lds(part.ks, rb, waves, part.channels, part.slots, nx).total;
+        int per_cu = kn.device_ok ? layer_workgroups_per_cu(part.ks, units, rb, waves, part.lds_bytes) : 0;
+        if (per_cu <= 0) per_cu = 2;
+        per_cu = std::min(per_cu, 3);
+        const int64_t most_ranges = std::max<int64_t>(8, (int64_t)per_cu * kn.compute_units / st.tiles);
+        const int64_t ranges = blocks <= most_ranges ? blocks + 7 : most_ranges;
+        part.ranges_per_xcd = (int)std::max<int64_t>(ranges / 8, (blocks / kLayerRangeBlocks + 8) / 8);
+        part.sets_at = st.sets.size();
+        int64_t row = 0, entry = 0;
+        for (int g : mine) {
+            const int op0 = op_of(g, 0);
+            LayerSet r;
+            std::memset(&r, 0, sizeof r);
+            for (int c = 0; c < part.channels; ++c) {
+                const int op = op_of(g, c0 + c);
+                r.op[c] = op;
+                r.entries += o.nnz[op];
+            }
+            r.m = o.m[op0];
+            r.in_row = (int32_t)o.in_off[op0];
+            r.out_row = (int32_t)o.out_off[op0];
+            r.channels = part.channels;
+            r.first_row = (int32_t)row;
+            r.first_entry = (int32_t)entry;
+            r.pad_rows = -1;
+            row += r.m;
+            entry += r.entries;
+            st.sets.push_back(r);
+        }
+        st.sets.back().pad_rows = (int32_t)(16 * rb * blocks - rows);
+        part.starts_at = place(16 * rb * blocks * part.channels + 4);
+        part.entries_at = place(2 * (entry + part.slots));      // (requests always ask for a slot's worth each)
+        st.parts.push_back(part);
     }
+    st.words = at;
+    st.graphs = (int)mine.size();
     // the other graphs: their items of the one-launch schedule, in its order
     for (size_t j = 0; j < sc.items.size(); ++j) {
         const int op = j < sc.item_op.size() ? sc.item_op[j] : -1;
@@ -920,31 +728,37 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
 
     // workspace layout
     Layout& L = p.lay;
-    size_t at = 0;
-    auto place = [&at](size_t& where, size_t bytes) {
-        where = at;
-        at = align_up(at + bytes);
+    auto lay_out = [&]() {
+        size_t at = 0;
+        auto place = [&at](size_t& where, size_t bytes) {
+            where = at;
+            at = align_up(at + bytes);
+        };
+        for (int d = 0; d < 2; ++d) place(L.items[d], p.sched[d].items.size() * sizeof(WorkItem));
+        for (int d = 0; d < 2; ++d) place(L.lean[d], p.lean_items[d].size() * sizeof(LeanItem));
+        if (p.lean_shared) L.lean[1] = L.lean[0];
+        place(L.op_records, (size_t)n * sizeof(OpRecord));
+        place(L.coo_records, p.coo_records.size() * sizeof(OpRecord));
+        place(L.build_order, (size_t)n * sizeof(int32_t));
+        for (int d = 0; d < 2; ++d) place(L.sets[d], p.set_records[d].size() * sizeof(SetRecord));
+        place(L.stream_sets, p.stream.sets.size() * sizeof(LayerSet));
+        place(L.stream_rest, p.stream.rest.size() * sizeof(WorkItem));
+        L.image = at;
+        place(L.rpt_t, (size_t)rpt_t_words * 4);
+        place(L.colids_t, (size_t)nz_pack * 4);
+        place(L.values_t, (size_t)nz_pack * 4);
+        place(L.scratch, (size_t)scratch_words * 4);
+        place(L.flag, 4);
+        for (int d = 0; d < 2; ++d) place(L.merged[d], (size_t)p.merged_words[d] * 4);
+        place(L.stream_arrays, (size_t)p.stream.words * 4);
+        L.total = at;
     };
-    for (int d = 0; d < 2; ++d) place(L.items[d], p.sched[d].items.size() * sizeof(WorkItem));
-    for (int d = 0; d < 2; ++d) place(L.lean[d], p.lean_items[d].size() * sizeof(LeanItem));
-    if (p.lean_shared) L.lean[1] = L.lean[0];
-    place(L.op_records, (size_t)n * sizeof(OpRecord));
-    place(L.coo_records, p.coo_records.size() * sizeof(OpRecord));
-    place(L.build_order, (size_t)n * sizeof(int32_t));
-    for (int d = 0; d < 2; ++d) place(L.sets[d], p.set_records[d].size() * sizeof(SetRecord));
-    place(L.stream_records, p.stream.records.size() * sizeof(SetRecord));
-    place(L.stream_sets, p.stream.sets.size() * sizeof(StreamSet));
-    place(L.stream_list, p.stream.list.size() * sizeof(int32_t));
-    place(L.stream_rest, p.stream.rest.size() * sizeof(WorkItem));
-    L.image = at;
-    place(L.rpt_t, (size_t)rpt_t_words * 4);
-    place(L.colids_t, (size_t)nz_pack * 4);
-    place(L.values_t, (size_t)nz_pack * 4);
-    place(L.scratch, (size_t)scratch_words * 4);
-    place(L.flag, 4);
-    for (int d = 0; d < 2; ++d) place(L.merged[d], (size_t)p.merged_words[d] * 4);
-    place(L.stream_merged, (size_t)p.stream.merged_words * 4);
-    L.total = at;
+    lay_out();
+    // (small layers need none of the layer kernel's arrays: they must not push a plan out of the static array)
+    if (p.stream.on() && !p.stream.many && L.total > BSPMM_STATIC_WORKSPACE_BYTES) {
+        p.stream = bspmm_plan::Stream();
+        lay_out();
+    }
     return BSPMM_OK;
 }
 
@@ -1158,15 +972,21 @@ void csr_of_direction(const bspmm_plan* p, int d, const int32_t** rpt, const int
     }
 }
 
-// The merged CSR blocks of the groups of the streaming launch (once per plan).
-int enqueue_stream_merge(bspmm_plan* p, hipStream_t s)
+// The arrays that the blocks of a layer read (once per plan).
+int enqueue_layer_rows(bspmm_plan* p, hipStream_t s)
 {
-    if (p->stream.merged_built || !p->stream.on()) return BSPMM_OK;
-    hipError_t e = launch_merge_sets(reinterpret_cast<const SetRecord*>(p->ws + p->lay.stream_records),
-                                     (int)p->stream.records.size(), p->rpt, p->colids, p->values,
-                                     reinterpret_cast<int32_t*>(p->ws + p->lay.stream_merged), s);
-    if (e != hipSuccess) return hip_fail(e);
-    p->stream.merged_built = !capturing(s);
+    bspmm_plan::Stream& st = p->stream;
+    if (st.built || !st.on()) return BSPMM_OK;
+    int32_t* base = reinterpret_cast<int32_t*>(p->ws + p->lay.stream_arrays);
+    const int count = (int)(st.sets.size() / st.parts.size());
+    for (const bspmm_plan::Stream::Part& part : st.parts) {
+        hipError_t e = launch_layer_rows(reinterpret_cast<const LayerSet*>(p->ws + p->lay.stream_sets) + part.sets_at,
+                                         count, reinterpret_cast<const OpRecord*>(p->ws + p->lay.op_records), p->rpt,
+                                         p->colids, p->values, base + part.starts_at, base + part.entries_at,
+                                         base + st.out_rows_at, s);
+        if (e != hipSuccess) return hip_fail(e);
+    }
+    st.built = !capturing(s);
     return BSPMM_OK;
 }
 
@@ -1415,9 +1235,7 @@ void write_image(const bspmm_plan* p, char* to)
     put(L.op_records, p->records);
     put(L.coo_records, p->coo_records);
     put(L.build_order, p->build_order);
-    put(L.stream_records, p->stream.records);
     put(L.stream_sets, p->stream.sets);
-    put(L.stream_list, p->stream.list);
     put(L.stream_rest, p->stream.rest);
 }
 
@@ -1497,7 +1315,7 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
     if (e != hipSuccess) return hip_fail(e);
     if (options && (options->flags & BSPMM_BUILD_TRANSPOSE)) {
         int rc = enqueue_merge(p, 0, s);
-        if (rc == BSPMM_OK) rc = enqueue_stream_merge(p, s);
+        if (rc == BSPMM_OK) rc = enqueue_layer_rows(p, s);
         if (rc == BSPMM_OK && p->transposed_supported) rc = enqueue_build(p, s);
         if (rc == BSPMM_OK && p->transposed_supported) rc = enqueue_merge(p, 1, s);
         if (rc == BSPMM_OK) rc = enqueue_hints(p, 0, s);
@@ -1520,45 +1338,48 @@ int run_gcn(bspmm_plan* p, const float* X, int64_t ldx, const float* W, int64_t 
     if (ldx % 4 || ldw % 4 || ldy % 4 || misaligned(X) || misaligned(W) || misaligned(Y))
         return BSPMM_EINVAL;
     const bool sets = !sc.merged_sets.empty();
-    if (p->stream.on()) {
-        const int mrc = enqueue_stream_merge(p, s);
+    // (32-bit offsets inside W, 32-bit leading dimensions of X and Y)
+    if (p->stream.on() && p->stream.many && (ldx >= (int64_t(1) << 31) || ldy >= (int64_t(1) << 31))) return BSPMM_EINVAL;
+    const bool layer = p->stream.on() && ldx < (int64_t(1) << 31) && ldy < (int64_t(1) << 31) && ldw < (int64_t(1) << 20);
+    if (layer) {
+        const int mrc = enqueue_layer_rows(p, s);
         if (mrc != BSPMM_OK) return mrc;
     }
-    if (sets && (!p->stream.on() || !p->stream.rest.empty())) {
+    if (sets && (!layer || !p->stream.rest.empty())) {
         const int mrc = enqueue_merge(p, 0, s);
         if (mrc != BSPMM_OK) return mrc;
     }
     const bspmm_plan::Stream& st = p->stream;
-    if (st.on()) {
-        // graphs inside the LDS budget: resident workgroups stream them; the others (if any)
-        // follow in a launch of the one-launch kernel over their items
-        if (ldx >= (int64_t(1) << 31) || ldy >= (int64_t(1) << 31)) return BSPMM_EINVAL;
-        StreamParams S;
-        S.sets = reinterpret_cast<const StreamSet*>(p->ws + p->lay.stream_sets);
-        S.list = reinterpret_cast<const int32_t*>(p->ws + p->lay.stream_list);
-        S.merged = reinterpret_cast<const int32_t*>(p->ws + p->lay.stream_merged);
-        S.x = X;
-        S.w = W;
-        S.bias = bias;
-        S.y = Y;
-        StreamShape& sh = S.shape;
-        sh.ld_x = ldx, sh.ld_w = ldw, sh.ld_y = ldy, sh.bias_stride = p->F;
-        sh.tiles = st.tiles, sh.fw = st.fw, sh.channels = st.channels;
-        sh.accumulate = accumulate ? 1 : 0;
-        sh.tile_words = st.tile_words, sh.x_words = st.x_words, sh.csr_words = st.csr_words;
-        sh.big_csr_words = st.big_csr_words;
-        sh.lists = st.lists;
-        sh.compact = st.compact ? 1 : 0;
-        sh.real_channels = sets ? p->front_channels : 1;
-        sh.reserved_ = 0;
-        const hipError_t es = launch_bspmm_gcn_stream(S, st.nx16, st.units, st.waves, (st.lists + 7) / 8 * 8 * st.tiles,
-                                                      st.lds_bytes(), s);
-        if (es != hipSuccess) return hip_fail(es);
+    if (layer) {
+        // the graphs cut into blocks; the others (if any) follow in a launch of the one-launch kernel over
+        // their items
+        const int32_t* base = reinterpret_cast<const int32_t*>(p->ws + p->lay.stream_arrays);
+        for (const bspmm_plan::Stream::Part& part : st.parts) {
+            LayerParams S;
+            S.starts = base + part.starts_at;
+            S.entries = base + part.entries_at;
+            S.out_rows = base + st.out_rows_at;
+            S.x = X;
+            S.w = W + (int64_t)part.first_channel * nx * ldw;
+            S.bias = bias + (int64_t)part.first_channel * p->F;
+            S.y = Y;
+            LayerShape& sh = S.shape;
+            sh.ld_x = ldx, sh.ld_w = ldw, sh.ld_y = ldy, sh.bias_stride = p->F;
+            sh.blocks = st.blocks, sh.ranges_per_xcd = part.ranges_per_xcd, sh.tiles = st.tiles;
+            sh.F = p->F;
+            sh.channels = part.channels;
+            sh.inv_channels = (65535 + part.channels) / part.channels;
+            sh.lane_shift = nx == 16 ? 2 : (nx == 32 ? 3 : (nx == 64 ? 4 : 5));
+            sh.slots = part.slots;
+            sh.accumulate = accumulate || part.first_channel > 0 ? 1 : 0;
+            const hipError_t es = launch_bspmm_layer(S, part.ks, st.units, st.rb, st.waves, part.lds_bytes, s);
+            if (es != hipSuccess) return hip_fail(es);
+        }
         if (st.rest.empty()) return BSPMM_OK;
     }
     LaunchParams P;
-    P.items = st.on() ? reinterpret_cast<const WorkItem*>(p->ws + p->lay.stream_rest)
-                      : reinterpret_cast<const WorkItem*>(p->ws + p->lay.items[0]);
+    P.items = layer ? reinterpret_cast<const WorkItem*>(p->ws + p->lay.stream_rest)
+                    : reinterpret_cast<const WorkItem*>(p->ws + p->lay.items[0]);
     // (channel sets: every item reads the merged CSR of its set; P.rpt carries its base)
     P.rpt = sets ? reinterpret_cast<const int32_t*>(p->ws + p->lay.merged[0]) : p->rpt;
     P.colids = p->colids;
@@ -1580,7 +1401,7 @@ int run_gcn(bspmm_plan* p, const float* X, int64_t ldx, const float* W, int64_t 
     P.ld_w = ldw;
     P.n_front = nx;
     P.accumulate = accumulate ? 1 : 0;
-    const int grid = st.on() ? (int)st.rest.size() : sc.grid;
+    const int grid = layer ? (int)st.rest.size() : sc.grid;
     hipError_t e = launch_bspmm_gcn(P, grid, sc.front_lds_words * 4, accumulate != 0, sets, p->front_wide == 1, s);
     return e == hipSuccess ? BSPMM_OK : hip_fail(e);
 }
@@ -2065,10 +1886,10 @@ int bspmm_plan_info(const bspmm_plan* plan, bspmm_info* info)
     info->transposed_supported = plan->transposed_supported ? 1 : 0;
     info->transposed_built = plan->transposed_built ? 1 : 0;
     for (int d = 0; d < 2; ++d) info->lean[d] = plan->sched[d].pow2 && plan->sched[d].merged_sets.empty() ? 1 : 0;
-    if (plan->stream.on()) {
+    if (plan->stream.on() && plan->stream.many) {
         info->front_stream[0] = plan->stream.graphs;
-        info->front_stream[1] = plan->stream.lists * plan->stream.tiles;
-        info->front_stream[2] = plan->stream.lds_bytes();
+        info->front_stream[1] = 8 * plan->stream.parts[0].ranges_per_xcd * plan->stream.tiles;
+        info->front_stream[2] = plan->stream.parts[0].lds_bytes;
         int32_t left = 0;
         for (const WorkItem& w : plan->stream.rest) left += w.f0 == 0 ? 1 : 0;
         info->front_stream[3] = left;

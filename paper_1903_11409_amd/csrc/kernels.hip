@@ -12,8 +12,8 @@
 // bspmm_gcn_kernel  the fused front of the graph-convolution layer (Fig. 7): the dense tile is
 //                   made on the matrix cores from the layer input and the weights, for one
 //                   channel or for all channels of the layer, and gathered as above.
-// bspmm_gcn_stream_kernel  the same layer for large batches: resident workgroups with the
-//                   weights in registers stream the graphs of host-made lists through LDS.
+// bspmm_layer_kernel  the same layer for large batches, gather first: resident workgroups with the
+//                   weights in registers make blocks of 16 output rows.
 // bspmm_coo_kernel  the direct product for COO / SparseTensor operands (Fig. 3, Fig. 5(a,b)).
 // build_sorted      stable CSR -> transposed CSR of every operation (counting sort by column),
 //                   and COO / SparseTensor -> CSR (the same sort by row).
@@ -657,12 +657,7 @@ merge_sets_kernel(const SetRecord* __restrict__ sets, const int32_t* __restrict_
     const int m = g.m, members = g.members;
     const int per = (m + kThreads - 1) / kThreads;
     const int r0 = min(m, tid * per), r1 = min(m, r0 + per);
-    // (member j holds the set's rows row_off[j] .. row_off[j] + rows[j]: all of them for summed
-    // sets, its graph's share for a group of graphs)
-    auto row_range = [&](int j, int row, int& a, int& b) {
-        const int r = row - g.row_off[j];
-        a = b = 0;
-        if ((unsigned)r >= (unsigned)g.rows[j]) return;
+    auto row_range = [&](int j, int r, int& a, int& b) {
         const int32_t* rp = rpt + g.rpt_off[j];
         b = min(max(rp[r + 1], 0), g.nnz[j]);
         a = min(max(rp[r], 0), b);
@@ -711,65 +706,70 @@ merge_sets_kernel(const SetRecord* __restrict__ sets, const int32_t* __restrict_
         }
     }
     if (tid == kThreads - 1) mr[m] = pos;
+}
 
-    // Rows in use (groups of the streaming launch with several channels): a row of a channel's
-    // dense tile that no entry of that channel names is never read, so it need not be made.
-    // Per channel the rows that are named are listed in ascending order, the columns of the
-    // merged CSR are renumbered to the position in the channels' lists laid end to end, and
-    // behind the values go: the channels' counts, the first tile row of each channel, and the
-    // lists (kxt words per channel, kxt = rows of the group's layer input).
-    const int chans = g.compact & 0xff, kxt = g.compact >> 8;
-    if (chans == 0) return;
-    __shared__ int rank[kCompactRows];         // 1 + position of a row in its channel's list, 0: not in use
-    __shared__ int base[kMaxMembers + 1];
-    const int tile_rows = chans * kxt;          // (the host compacts only sets with tile_rows <= kCompactRows)
-    for (int i = tid; i < tile_rows; i += kThreads) rank[i] = 0;
+// What the blocks of bspmm_layer_kernel read, once per plan: one workgroup per graph writes, for its
+// output rows and their channels, where the entries start, the entries (row of X, value) and the row of
+// Y; the last graph's workgroup also writes the empty rows that fill the last block.  Row pointers are
+// clamped and columns outside the matrix point at the graph's first row of X, so malformed input stays
+// inside the graph's share of the arrays.
+__global__ void __launch_bounds__(kThreads)
+layer_rows_kernel(const LayerSet* __restrict__ sets, const OpRecord* __restrict__ ops, const int32_t* __restrict__ rpt,
+                  const int32_t* __restrict__ colids, const float* __restrict__ values, int32_t* __restrict__ starts,
+                  int2* __restrict__ entries, int32_t* __restrict__ out_rows)
+{
+    __shared__ int partial[kThreads];
+    const LayerSet& g = sets[blockIdx.x];
+    const int tid = threadIdx.x;
+    const int M = g.channels, m = g.m;
+    const int per = (m + kThreads - 1) / kThreads;
+    const int r0 = min(m, tid * per), r1 = min(m, r0 + per);
+    auto row_range = [&](int j, int r, int& a, int& b) {
+        const OpRecord& o = ops[g.op[j]];
+        const int32_t* rp = rpt + o.rpt_off;
+        b = min(max(rp[r + 1], 0), o.nnz);
+        a = min(max(rp[r], 0), b);
+    };
+    int sum = 0;
+    for (int r = r0; r < r1; ++r)
+        for (int j = 0; j < M; ++j) {
+            int a, b;
+            row_range(j, r, a, b);
+            sum += b - a;
+        }
+    partial[tid] = sum;
     __syncthreads();
-    {
-        int q = partial[tid] - sum;
-        for (int r = r0; r < r1; ++r)
-            for (int j = 0; j < members; ++j) {
-                int a, b;
-                row_range(j, r, a, b);
-                for (int p = a; p < b; ++p) rank[pc[q++]] = 1;
-            }
+    for (int off = 1; off < kThreads; off <<= 1) {     // inclusive scan over the lanes' sums
+        const int add = tid >= off ? partial[tid - off] : 0;
+        __syncthreads();
+        partial[tid] += add;
+        __syncthreads();
     }
-    __syncthreads();
-    int32_t* cnt = reinterpret_cast<int32_t*>(pv + round_up(nnz_sum, 4));
-    int32_t* first_row = cnt + round_up(chans, 4);
-    int32_t* lists = first_row + round_up(chans, 4);
-    if (tid < chans) {
-        int n = 0;
-        for (int j = 0; j < kxt; ++j)
-            if (rank[tid * kxt + j]) {
-                lists[tid * kxt + n] = j;
-                rank[tid * kxt + j] = ++n;
+    const int end = g.first_entry + g.entries;
+    int pos = g.first_entry + partial[tid] - sum;
+    for (int r = r0; r < r1; ++r) {
+        const int row = g.first_row + r;
+        out_rows[row] = g.out_row + r;
+        for (int j = 0; j < M; ++j) {
+            const OpRecord& o = ops[g.op[j]];
+            int a, b;
+            row_range(j, r, a, b);
+            const int32_t* ci = colids + o.nz_off;
+            const float* va = values + o.nz_off;
+            starts[(int64_t)row * M + j] = min(pos, end);
+            for (int p = a; p < b; ++p, ++pos) {
+                const int c = ci[p];
+                if (pos < end)
+                    entries[pos] = make_int2(g.in_row + ((unsigned)c < (unsigned)o.k ? c : 0), __float_as_int(va[p]));
             }
-        cnt[tid] = n;
-        base[tid] = n;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int at = 0;
-        for (int c = 0; c < chans; ++c) {
-            const int n = base[c];
-            base[c] = at;
-            first_row[c] = at;
-            at += n;
         }
     }
-    __syncthreads();
-    {
-        int q = partial[tid] - sum;
-        for (int r = r0; r < r1; ++r)
-            for (int j = 0; j < members; ++j) {
-                int a, b;
-                row_range(j, r, a, b);
-                for (int p = a; p < b; ++p, ++q) {
-                    const int row = pc[q];
-                    pc[q] = base[row / kxt] + rank[row] - 1;
-                }
-            }
+    // (fewer entries than announced, malformed row pointers only: the rest adds nothing)
+    for (int p = g.first_entry + partial[kThreads - 1] + tid; p < end; p += kThreads) entries[p] = make_int2(g.in_row, 0);
+    if (g.pad_rows >= 0) {
+        const int last = g.first_row + m;
+        for (int i = tid; i < g.pad_rows; i += kThreads) out_rows[last + i] = -1;
+        for (int i = tid; i < g.pad_rows * M + 4; i += kThreads) starts[(int64_t)last * M + i] = end;
     }
 }
 
@@ -2164,66 +2164,60 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 }
 
 // ---------------------------------------------------------------------------------------
-// The layer (Fig. 7: one channel, or all channels with the ElementWiseAdd) for batches of two
-// and more workgroups per CU: resident workgroups, each bound to one feature tile, stream the
-// graphs of their list.  A graph is a set of M channel operations with one merged CSR block
-// (row pointers, columns, values back to back); plans of single channels have such a block per
-// operation (M = 1).
+// The layer (Fig. 7: one channel, or all channels with the ElementWiseAdd), gather first.  The sum is
+// taken in the order
+//     Y_i = [A_i^0 X_i | A_i^1 X_i | ...] [W[0]; W[1]; ...] + (row sums of A_i^ch) bias[ch],
+// so that the gather moves rows of n_X floats instead of one dense tile of F columns per channel, the
+// channels are summed by the matrix instructions, their results leave the registers as output rows, and no
+// output row depends on another: the work is cut into blocks of R = 16 RB output rows whatever graph they
+// belong to, all alike.  A kernel that runs once per plan (layer_rows_kernel) writes what the blocks
+// read: for every output row and channel ("virtual row" R b M + row M + ch of block b) where its entries
+// start, and the entries (row of X, value) one after the other.
 //
-// A workgroup of bspmm_gcn_kernel goes through its phases one after the other - operands from
-// memory, dense tile on the matrix cores, gather, store - stages its weight tile again for
-// every graph, and the launch's LDS is sized for the largest graph of the batch.  Here
-//   * the weights of a wavefront's blocks live in REGISTERS for the whole launch: wavefront w
-//     owns U of the M * fw/16 (channel, 16-column block) pairs, and the B operand of
-//     v_mfma_f32_16x16x4_f32 for lane (g, col) = (l / 16, l % 16) is W[ch][16 s + 4 g + j][col],
-//     s < n_X / 16, j < 4: n_X / 4 registers per pair.  No LDS for W, no LDS reads for it.
-//   * the rows of X_i and the merged CSR block of the NEXT graph are requested (global -> LDS
-//     directly) before the matrix instructions of this graph are issued, into the other one of
-//     two buffers, and nothing waits for them until the top of the next trip; a graph's results
-//     wait in registers and are stored at the top of the next trip, so that wait finds only
-//     requests and stores that are a whole trip old.  The records of the graphs (32 bytes
-//     each) are fetched with scalar loads two trips ahead.
-//   * the launch's LDS is sized for the graphs that fit a budget of a third of a CU's LDS, so
-//     that three workgroups share a CU: one's matrix phase overlaps the others' gathers and
-//     requests.  (Workgroups of eight wavefronts, WV = 8, which give each of eight channels a
-//     wavefront of its own: half a CU's LDS, two per CU.)  Larger graphs (a few per cent of a molecule batch) are taken one at a time
-//     out of the same LDS, their X_i in chunks (see below); what does not fit even so is not
-//     in the lists at all (the host gives it to bspmm_gcn_kernel in a launch of its own).
-// Arithmetic: the n_X products of a dense element are added by the matrix instructions in
-// the order 4 g + j within 16 s (bias as the initial value of the accumulator; two
-// accumulators per block, k even and odd, in kernels with one block per wavefront and in the
-// halves); a row's entries are added in stored order with fused multiply-adds.  Rows of X_i
-// are XOR-swizzled in LDS as in bspmm_gcn_kernel.
-// Per trip two barriers: "tile free, buffers of the graph after next free, this graph's
-// operands landed" and "tile complete".  Every workgroup's loop runs over a list the host
-// made: it ends.
+// The dense part, Z (R x K, K = M n_X) times W (K x F), runs on bf16 matrix instructions without giving
+// up fp32: every fp32 number is the sum of three bf16 numbers (24 = 3 x 8 bits: the rounded number, the
+// rounded rest, the rest of that), and six of the nine products (all but those below 2^-26) are added in
+// fp32, the large ones (hi x hi) in an accumulator of their own.  For 16 x 16 x 128 products that is 384
+// cycles of a SIMD's matrix pipe instead of 1024 with v_mfma_f32_16x16x4_f32.  Error against 64 bits,
+// products of uniform numbers, K = 64 / 256 / 512: 4.5e-8 / 8.1e-8 / 1.2e-7 of the result's norm; the fp32
+// instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The bf16 instructions take subnormal numbers as zero, and a split
+// number that is not finite is NaN: blocks with results that are not finite, or all below 2^-60, are made
+// once more without the split.
+//   * W in REGISTERS for the whole launch, split once: wavefront w owns U blocks of 16 columns (12
+//     registers per 32 of K and block); no LDS for W.
+//   * A trip is one block.  While the matrix instructions of block b run, the rows of X that block b + 1
+//     names are on their way to LDS (one 16-byte request per lane, each from its own row: a gather by the
+//     memory system, one slot per entry in entry order), and the starts and entries of block b + 2.
+//   * Gather: n_X / 4 lanes per virtual row add up the slots in stored order with fused multiply-adds,
+//     split the sum and write the three bf16 planes of Z to LDS (rows 16 bytes apart from a multiple of
+//     64, which spreads a column of 16 rows over the banks).
+//   * The matrix phase computes the transposed block (W^T Z^T): a lane then holds consecutive columns of
+//     an output row.  Results wait in registers and are stored at the top of the next trip, so that the
+//     wait there finds only requests and stores that are a whole trip old; stores write whole 128-byte
+//     lines (half lines: one channel, 2048 graphs, n_X = 64 20.5 us instead of 16.4).
+// Two barriers a trip.  us of a launch, F = 128, molecules, against the kernel this replaces, which made the
+// dense tiles graph by graph with fp32 matrix instructions: four channels at n_X = 64, 2048 graphs 43.4 ->
+// 29.6, 512 15.4 -> 12.5, 128 11.6 -> 6.8; n_X = 128, 2048 graphs 85.6 -> 57.3; eight channels at n_X = 64, 1024
+// graphs 39.7 -> 31.7; one channel at n_X = 64, 2048 graphs 21.2 -> 15.7, 512 10.0 -> 7.1.  Bound at four
+// channels (counters): the matrix pipe is busy for a third of the launch, LDS for half; a trip is a chain
+// of LDS round trips and two barriers that two workgroups per CU hide from each other only in part, and
+// splitting the weights is a fifth of the launch.
 // ---------------------------------------------------------------------------------------
 
-// Global -> LDS copy of 16 bytes per lane (lane i lands at lds + 16 i), issued from inline
-// assembly: the compiler then does not know that LDS is written behind its back and does not
-// put a wait for ALL outstanding memory operations in front of the next LDS read.  That wait is
-// what a prefetch into the other buffer must not meet; the kernel waits for its requests
-// itself, where it needs them.  (Untracked requests can only make the waits the compiler
-// computes for its own loads longer, never shorter: the counter runs in issue order.)
-__device__ __forceinline__ void lds_dma16(const void* gp, const void* lds)
-{
-    const int m0 = __builtin_amdgcn_readfirstlane(
-        (int)(uintptr_t)((const __attribute__((address_space(3))) char*)lds));
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(gp), "s"(m0) : "memory", "m0");
-}
-
-// The same with the LDS address as a number: a loop that adds to it spares the pointer
-// conversion of every trip.
-__device__ __forceinline__ int lds_address(const void* lds)
-{
-    return (int)(uintptr_t)((const __attribute__((address_space(3))) char*)lds);
-}
-
+// Global -> LDS copy of 16 bytes per lane (lane i lands at lds_addr + 16 i), issued from inline assembly:
+// the compiler then does not know that LDS is written behind its back and does not put a wait for ALL
+// outstanding memory operations in front of the next LDS read.  The kernel waits for its requests
+// itself, where it needs them.  (Untracked requests can only make the waits the compiler computes for
+// its own loads longer, never shorter: the counter runs in issue order.)
 __device__ __forceinline__ void lds_dma16_to(const void* gp, int lds_addr)
 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(gp), "s"(lds_addr) : "memory", "m0");
+                 :: "v"(gp), "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory", "m0");
+}
+
+__device__ __forceinline__ int lds_address(const void* lds)
+{
+    return (int)(uintptr_t)((const __attribute__((address_space(3))) char*)lds);
 }
 
 // Workgroup barrier that orders LDS accesses only (no wait for global stores or for requests
@@ -2235,395 +2229,448 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NX16, int U, int WV>
-__global__ void __launch_bounds__(64 * WV)
-bspmm_gcn_stream_kernel(const StreamSet* __restrict__ sets, const int32_t* __restrict__ list,
-                        const int32_t* __restrict__ merged, const float* __restrict__ x,
-                        const float* __restrict__ wgt, const float* __restrict__ bias,
-                        float* __restrict__ y, const StreamShape S)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Two fp32 numbers as three pairs of bf16 numbers whose sum they are (the first of a pair in the low half).
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    auto pair = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2)); };
+    hi = pair(a, b);
+    const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+    mid = pair(ra, rb);
+    lo = pair(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
+}
+
+template <int KS, int U, int RB, int WV>
+__global__ void __launch_bounds__(64 * WV, WV == 8 ? (KS > 8 ? 2 : 4) : (KS * U > 8 || (KS > 2 && U * RB > 2) ? 2 : 3))
+bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ entries,
+                   const int32_t* __restrict__ out_rows, const float* __restrict__ x, const float* __restrict__ wgt,
+                   const float* __restrict__ bias, float* __restrict__ y, const LayerShape S)
 {
     extern __shared__ __align__(16) int sm[];
-    typedef float mfma4 __attribute__((ext_vector_type(4)));
-    constexpr int NX = 16 * NX16, XVEC = NX / 4, XSH = NX16 == 1 ? 2 : (NX16 == 2 ? 3 : (NX16 == 4 ? 4 : 5));
-    constexpr int SWZ = (XVEC < 16 ? XVEC : 16) - 1;
-    constexpr int T = 64 * WV;                    // lanes of the workgroup (four or eight wavefronts)
-    constexpr int C = U == 1 ? 2 : 1;            // accumulators per block: two matrix instructions
-                                                 // between dependent ones either way
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
-    const int col = wl & 15, g = wl >> 4;
-    // Workgroups go to the XCDs round robin (index mod 8).  The workgroups of one list - one per
-    // feature tile - read the same rows of X: they sit on one XCD, so that its L2 fetches them once
-    // (list = 8 * (slot / tiles) + xcd, tile = slot % tiles; the grid is padded to whole rounds).
+    constexpr int T = 64 * WV;                                // lanes: four or eight wavefronts
+    constexpr int R = 16 * RB;                                // rows of a block
+    constexpr int BQ = WV == 8 && KS <= 8 ? 1 : 2;            // four channels each
+    constexpr int ZP = layer_z_row(KS), PLANE = R * ZP;      // bytes of a row / of a plane of Z
+    int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int wl = tid & 63, col = wl & 15, g = wl >> 4;
+    // Workgroups go to the XCDs round robin (index mod 8): a range of blocks and its feature tiles sit
+    // on one XCD, and neighbouring ranges too, so that its L2 fetches the rows of X once.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int tile_idx = slot % S.tiles, lp = (slot / S.tiles) * 8 + xcd;
-    if (lp >= S.lists) return;
-    const int f0 = tile_idx * S.fw;
-    const int j0 = list[lp], j1 = list[lp + 1];
-    if (j0 >= j1) return;
-    const int fsh = ilog2(S.fw);                 // tile row = 1 << fsh floats
-    const int nbw = S.fw >> 4;                   // 16-column blocks per tile row
+    const int tile = slot % S.tiles, range = xcd * S.ranges_per_xcd + slot / S.tiles;
+    const int b0 = (int)((int64_t)S.blocks * range / (8 * S.ranges_per_xcd));
+    const int b1 = (int)((int64_t)S.blocks * (range + 1) / (8 * S.ranges_per_xcd));
+    if (b0 >= b1) return;
+    const int M = S.channels, V = R * M;                      // virtual rows of a block
+    const int lsh = S.lane_shift, L = 1 << lsh;               // n_X / 4 lanes per virtual row
+    const int G = T >> lsh;
+    int l = tid & (L - 1), grp = tid >> lsh;
+    const int row_sh = lsh + 4;                               // a row of X in LDS is 16 << lsh bytes
 
-    float* tile = reinterpret_cast<float*>(sm);
-    float* xbase = tile + S.tile_words;
-    int* cbase = sm + S.tile_words + 2 * S.x_words;
-    float* sink = reinterpret_cast<float*>(cbase + 2 * S.csr_words) + wl;   // rows past the end land here
+    const LayerLds at = layer_lds(KS, RB, WV, M, S.slots, 4 << lsh);
+    char* const lds = reinterpret_cast<char*>(sm);
+    char* const xs = lds + at.slots;            // the rows of X that the entries name
+    int* const state = reinterpret_cast<int*>(lds + at.state);   // Z has numbers other than zero (two buffers)
+    uint32_t* const redo = reinterpret_cast<uint32_t*>(state + 4 + wave * kLayerRedoWords);
+    int* const z_place = state + 4 + WV * kLayerRedoWords;        // of every virtual row, in bytes
+    const int csr_lds = lds_address(lds + at.csr), xs_lds = csr_lds - (at.csr - at.slots);
 
-    // ---- this wavefront's weights and bias, once
-    float w[U][NX16][4];
-    float bv[U];
-    int unit_ch[U], unit_col[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int unit = wave * U + u;
-        const int ch = unit / nbw, nb = unit - ch * nbw;
-        unit_ch[u] = ch;
-        unit_col[u] = 16 * nb + col;
-        // (a channel past the layer's own - the layer runs padded to 4 or 8 - has no weights)
-        const bool live = ch < S.real_channels;
-        const float* wp = wgt + (int64_t)((live ? ch : 0) * NX + 4 * g) * S.ld_w + f0 + 16 * nb + col;
-#pragma unroll
-        for (int s = 0; s < NX16; ++s)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[u][s][j] = live ? wp[(int64_t)(16 * s + j) * S.ld_w] : 0.f;
-        bv[u] = live ? bias[(int64_t)ch * S.bias_stride + f0 + 16 * nb + col] : 0.f;
-    }
-
-    // rows of X_i and the merged CSR block of a graph -> buffers b.  A lane's element of a
-    // request is T elements (T / XVEC rows) after its element of the previous one: the row
-    // advances by a multiple of the swizzle period, so the swizzled column is the lane's for good
-    // and between requests a lane's address moves by a fixed step, like the LDS address of the
-    // wavefront (the loops below are a handful of instructions a request: the wavefronts of the
-    // workgroups beside this one are busy on the same SIMD, and every instruction waits its turn).
-    // n_X = 128 with four wavefronts takes 8 rows a request, half a period: the swizzled column
-    // flips between two places, 128 bytes apart.
-    constexpr int kRowsPerRequest = T / XVEC;
-    constexpr bool kFlip = kRowsPerRequest % (SWZ + 1) != 0;
-    static_assert(!kFlip || (XVEC == 32 && kRowsPerRequest == 8), "swizzle period");
-    const int x_row0 = tid >> XSH;
-    const int x_col0 = (tid & (XVEC - 1)) ^ (x_row0 & SWZ);
-    const int64_t x_lane_off = (int64_t)x_row0 * S.ld_x + (x_col0 << 2);
-    const int64_t x_step = (int64_t)kRowsPerRequest * S.ld_x * 4;            // bytes
-    const int x_flip = kFlip ? ((x_col0 & 8) ? -128 : 128) : 0;              // bytes, to the other place
-    const int w16 = wave << 10;                                              // this wavefront's place in a request
-    const int xbase_lds = lds_address(xbase) + w16, cbase_lds = lds_address(cbase) + w16;
-    auto request = [&](const StreamSet& st, int b) {
-        const char* gp = reinterpret_cast<const char*>(x + st.in_row * S.ld_x + x_lane_off);
-        int to = xbase_lds + b * (S.x_words << 2);
-        int64_t step = x_step + x_flip;
-        // (left: elements of the request from this wavefront's first lane on)
-        for (int left = (st.kx << XSH) - (wave << 6); left > 0; left -= T) {
-            if (wl < left) lds_dma16_to(gp, to);
-            gp += step;
-            if (kFlip) step = 2 * x_step - step;
-            to += T * 16;
-        }
-        const int csr_vecs = (((st.m + 4) & ~3) + 2 * ((st.nnz + 3) & ~3) +
-                              (S.compact ? compact_words(S.channels, st.kx) : 0)) >> 2;
-        const char* cg = reinterpret_cast<const char*>(merged + st.csr_off) + (tid << 4);
-        to = cbase_lds + b * (S.csr_words << 2);
-        for (int left = csr_vecs - (wave << 6); left > 0; left -= T) {
-            if (wl < left) lds_dma16_to(cg, to);
-            cg += T * 16;
-            to += T * 16;
+    // what the gather of block b reads -> csr buffer; its first entry is number e0 (as many entries as there
+    // are slots, the block's or not: the array is that much longer)
+    auto request_csr = [&](int b, int e0, int buf) {
+        const int to = csr_lds + buf * at.csr_bytes;
+        const uint32_t v = (uint32_t)b * (uint32_t)V;
+        if (wave == 0) {
+            for (int i = 0; 2 * i < S.slots; i += 64)
+                if (2 * (i + wl) < S.slots) lds_dma16_to(entries + (uint32_t)((e0 & ~1) + 2 * (i + wl)), to + at.entries + 16 * i);
+        } else if (wave == 1) {
+            if (4 * wl < V + 1) lds_dma16_to(starts + (v + 4 * wl), to);
+        } else if (wave == 2) {
+            if (4 * wl < R) lds_dma16_to(out_rows + (uint32_t)(R * b + 4 * wl), to + at.rows);
         }
     };
-
-    // gather geometry: fw / 4 lanes per output row
-    const int gsh = fsh - 2;
-    const int r_lane = tid >> gsh, l = tid & ((1 << gsh) - 1);
-    const int rows_per_pass = T >> gsh;
-    float4 yv[kStreamPasses];
-    int pend_m = 0;
-    int64_t pend_row = 0;
-    auto store_pending = [&]() {
+    // rows of X of a block whose entries are in csr buffer `buf`
+    auto request_rows = [&](int e0, int e1, int buf) {
+        const int2* ent = reinterpret_cast<const int2*>(lds + at.csr + buf * at.csr_bytes + at.entries);
+        const int n = min(e1 - (e0 & ~1), S.slots), per = 64 >> lsh;
+        // (a request past the last entry asks for its row again; the slots are a multiple of a request's rows)
+        for (int i0 = wave * per; i0 < n; i0 += 4 * WV * per) {
+            uint32_t row[4];
 #pragma unroll
-        for (int q = 0; q < kStreamPasses; ++q) {
-            const int r = q * rows_per_pass + r_lane;
-            if (r < pend_m) {
-                float* yp = y + (pend_row + r) * S.ld_y + f0 + 4 * l;
-                float4 v = yv[q];
+            for (int t = 0; t < 4; ++t) row[t] = (uint32_t)ent[min(i0 + WV * t * per + (wl >> lsh), n - 1)].x;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (i0 + WV * t * per < n)
+                    lds_dma16_to(x + ((uint64_t)row[t] * (uint32_t)S.ld_x + 4 * l), xs_lds + ((i0 + WV * t * per) << row_sh));
+        }
+    };
+    auto start_in = [&](int buf, int vr) {       // of the block whose starts are in that buffer
+        return __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(lds + at.csr + buf * at.csr_bytes + 4 * vr));
+    };
+
+    int e_cur = starts[(uint32_t)b0 * V], e_next = starts[(uint32_t)(b0 + 1) * V];
+    request_csr(b0, e_cur, 0);
+    if (b0 + 1 < b1) request_csr(b0 + 1, e_next, 1);
+    for (int i = tid; i < 4 + WV * kLayerRedoWords; i += T) state[i] = 0;
+    for (int i = tid; i < V; i += T) {
+        const int r = (i * S.inv_channels) >> 16;
+        z_place[i] = r * ZP + ((i - r * M) << (lsh + 3));
+    }
+    // slots that no request has filled yet hold finite numbers (see the gather)
+    for (int i = 16 * tid; i < (S.slots + kLayerSpare) << row_sh; i += 16 * T)
+        *reinterpret_cast<float4*>(xs + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+    // the columns of Z past K (K off a multiple of 32) stay zero
+    const int K = M << (lsh + 2);
+    if (K < 32 * KS)
+        for (int i = tid; i < 3 * PLANE / 4; i += T) sm[i] = 0;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    lds_barrier();
+    request_rows(e_cur, e_next, 0);
+
+    // ---- this wavefront's weights, split, once.  Block u has the columns f0 + U i + u, i < 16 (a lane's
+    // loads of a row are U columns side by side, and its results U float4): the A operand is W^T, lane
+    // (g, col) holds W[32 s + 8 g + j][f0 + U col + u], j < 8 (all eight inside K or none: K is a multiple
+    // of 16; where none the weights of k = j stand in, the columns of Z there are zero)
+    const int f0 = (tile * WV + wave) * (16 * U);
+    const int width = min(16 * U, S.F - f0);                  // columns of this wavefront (none: negative)
+    bf16x8 wh[U][KS], wm[U][KS], wlo[U][KS];
+    float bv[U][BQ];
+    bool any_weight;
+    {
+        const int c = width > 0 ? f0 + U * min(col, width / U - 1) : 0;
+        float raw[KS][8][U];
+        uint32_t w_bits = 0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = 32 * s + 8 * g;
+            const uint32_t off = ((uint32_t)(k < K ? k : 0) * (uint32_t)S.ld_w + (uint32_t)c) << 2;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const char* p = reinterpret_cast<const char*>(wgt + j * S.ld_w) + off;
+                if constexpr (U == 2) {
+                    const float2 t = *reinterpret_cast<const float2*>(p);
+                    raw[s][j][0] = t.x, raw[s][j][1] = t.y;
+                } else {
+                    raw[s][j][0] = *reinterpret_cast<const float*>(p);
+                }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                uint32_t h[4], m[4], lo[4];
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    v[j] = raw[s][j][u];
+                    w_bits |= __float_as_uint(v[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], h[j], m[j], lo[j]);
+                wh[u][s] = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
+                wm[u][s] = __builtin_bit_cast(bf16x8, make_uint4(m[0], m[1], m[2], m[3]));
+                wlo[u][s] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+            }
+        any_weight = (w_bits << 1) != 0;
+        // bias as the A operand of v_mfma_f32_16x16x4_f32 (k = channel), the row sums are B
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < BQ; ++q) {
+                const float t = bias[(int64_t)min(4 * q + g, M - 1) * S.bias_stride + c + (width > 0 ? u : 0)];
+                bv[u][q] = 4 * q + g < M ? t : 0.f;
+            }
+    }
+    const bool weights = __builtin_amdgcn_ballot_w64(any_weight) != 0;     // one of them is not zero
+    // The lane's place once more, here and in every trip of the loop below, so that nothing derived from it
+    // is kept in registers from trip to trip: the weights leave none to spare.
+    auto place = [&]() {
+        asm volatile("" : "+v"(tid));
+        wl = tid & 63, col = wl & 15, g = wl >> 4, l = tid & (L - 1), grp = tid >> lsh;
+    };
+    place();
+
+    // Results wait here for the top of the next trip.  A lane has 4 U columns of output row `col` of every 16;
+    // with U = 2 lanes eight rows apart exchange halves, so that a store writes whole lines: 128 bytes of rows
+    // 0..7, then of rows 8..15.
+    f32x4 pend[RB][U];
+    int pend_row[RB][U];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int u = 0; u < U; ++u) pend_row[rb][u] = -1;
+    auto store_pending = [&]() {
+        const int c0 = U == 2 ? 8 * g + 4 * (col >> 3) : 4 * g;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (pend_row[rb][u] < 0 || c0 >= width) continue;
+                float* yp = y + ((uint64_t)(uint32_t)pend_row[rb][u] * (uint32_t)S.ld_y + (uint32_t)(f0 + c0));
+                float4 v = make_float4(pend[rb][u][0], pend[rb][u][1], pend[rb][u][2], pend[rb][u][3]);
                 if (S.accumulate) {
                     const float4 old = *reinterpret_cast<const float4*>(yp);
                     v.x += old.x, v.y += old.y, v.z += old.z, v.w += old.w;
                 }
                 store_out<4>(yp, v);
             }
-        }
     };
 
-    // ---- graphs too large for the buffers above come first in a list and are taken one at a
-    // time, without prefetch: the tile sits at the start of LDS, the merged CSR block at its end,
-    // and the rows of X_i pass through the space between them in chunks of as many 16-row blocks
-    // as fit.  Kernels with two blocks per wavefront (tiles of 32 columns: a wavefront owns one
-    // channel) take such a graph in two halves of 16 columns, each with a half tile
-    // (channels x kx x 16); kernels with one block per wavefront take it in one piece.
-    // Each piece: [chunk from memory, its blocks on the matrix cores] ..., gather, store.
-    int jn = j0;
-    constexpr int PIECES = U == 2 ? 2 : 1;
-    if (U == 1 || nbw == 2) {
-        const int psh = U == 2 ? 4 : fsh;           // a piece's tile row = 1 << psh floats
-        const int total_words = S.tile_words + 2 * S.x_words + 2 * S.csr_words;
-        int* cbig = sm + total_words - S.big_csr_words;
-        for (; jn < j1; ++jn) {
-            const StreamSet bg = sets[jn];
-            const int csr_w = ((bg.m + 4) & ~3) + 2 * ((bg.nnz + 3) & ~3);
-            const bool big = S.channels * bg.kx * S.fw > S.tile_words || bg.kx * NX > S.x_words ||
-                             csr_w + (S.compact ? compact_words(S.channels, bg.kx) : 0) > S.csr_words ||
-                             bg.m > kStreamPasses * rows_per_pass ||
-                             (S.compact && S.channels * bg.kx > kCompactRows);
-            if (!big) break;
-            const int kx = bg.kx, m = bg.m;
-            const int piece_words = (S.channels * kx) << psh;
-            float* xbig = tile + piece_words;
-            const int rows_chunk = min((kx + 15) & ~15, ((total_words - S.big_csr_words - piece_words) / NX) & ~15);
-            if (rows_chunk < 16 || csr_w > S.big_csr_words) return;    // (the host never lists such a graph)
-            {
-                const int32_t* cg = merged + bg.csr_off;
-                const int csr_vecs = csr_w >> 2;
-                for (int e0 = wave << 6; e0 < csr_vecs; e0 += T) {
-                    const int e = e0 + wl;
-                    if (e < csr_vecs) lds_dma16(cg + 4 * e, cbig + (e0 << 2));
-                }
+    // Z of one block, `Q` virtual rows per lane group at a time, `J` entries of each at once.  (Lane groups
+    // past the last virtual row repeat it; entries past a row's end are taken with value zero - where
+    // their slot holds an infinity the sum is NaN, and so is the result: see the check behind the matrix
+    // instructions.)  Returns the bits of the lane's numbers.
+    auto gather = [&](auto q_tag, auto j_tag, int e0, int e1, const char* csr) {
+        constexpr int Q = decltype(q_tag)::value, J = decltype(j_tag)::value;
+        static_assert(J <= kLayerSpare, "reads past the last entry");
+        const int* st = reinterpret_cast<const int*>(csr);
+        const int ea = e0 & ~1, top = S.slots;                // the entry of slot 0
+        const char* x0 = xs + 16 * l;
+        const char* v0 = csr + at.entries + 4;                // the entries' values
+        float* const sums = reinterpret_cast<float*>(lds + at.sums);
+        uint32_t bits = 0;
+        int p[Q], pe[Q], to[Q];
+        auto fetch = [&](int r0) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int vr = min(r0 + q * G + grp, V - 1);
+                p[q] = st[vr] - ea;
+                pe[q] = st[vr + 1] - ea;
+                to[q] = z_place[vr];
             }
-            const float* xg = x + bg.in_row * S.ld_x;
-            const int* rp = cbig;
-            const int* cols = rp + ((m + 4) & ~3);
-            const float* vals = reinterpret_cast<const float*>(cols + ((bg.nnz + 3) & ~3));
-#pragma unroll
-            for (int h = 0; h < PIECES; ++h) {
-                const int pcol = U == 2 ? col : unit_col[0];      // column inside the piece
-                for (int r0 = 0; r0 < kx; r0 += rows_chunk) {
-                    const int rows = min(rows_chunk, kx - r0);
-                    const int total = rows << XSH;
-                    for (int e0 = wave << 6; e0 < total; e0 += T) {
-                        const int e = e0 + wl;
-                        if (e < total) {
-                            const int r = e >> XSH;
-                            lds_dma16(xg + (int64_t)(r0 + r) * S.ld_x + (((e & (XVEC - 1)) ^ (r & SWZ)) << 2),
-                                      xbig + (e0 << 2));
-                        }
-                    }
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    lds_barrier();
-                    for (int mb = 0; mb < ((rows + 15) >> 4); ++mb) {
-                        const int arow = min(16 * mb + col, rows - 1);
-                        const float* xrow = xbig + arow * NX;
-                        mfma4 acc0 = {bv[h], bv[h], bv[h], bv[h]}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int s = 0; s < NX16; ++s) {
-                            const float4 av = *reinterpret_cast<const float4*>(xrow + (((4 * s + g) ^ (arow & SWZ)) << 2));
-                            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, w[h][s][0], acc0, 0, 0, 0);
-                            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, w[h][s][1], acc1, 0, 0, 0);
-                            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, w[h][s][2], acc0, 0, 0, 0);
-                            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, w[h][s][3], acc1, 0, 0, 0);
-                        }
-                        const mfma4 r4 = acc0 + acc1;
-                        const int row = r0 + 16 * mb + 4 * g;
-                        float* tp = tile + ((unit_ch[h] * kx + row) << psh) + pcol;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            float* q = 16 * mb + 4 * g + i < rows ? tp + (i << psh) : sink;
-                            *q = r4[i];
-                        }
-                    }
-                    lds_barrier();      // the chunk may be replaced; after the last one: the piece's tile complete
-                }
-                // gather over the piece: a quarter of its columns per lane
-                const int hsh = psh - 2;
-                const int hr = tid >> hsh, hl = tid & ((1 << hsh) - 1);
-                const char* tcol = reinterpret_cast<const char*>(tile) + 16 * hl;
-                for (int r = hr; r < m; r += T >> hsh) {
-                    const int p0 = rp[r], p1 = rp[r + 1];
-                    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                    for (int p = p0; p < p1; p += 4) {
-                        int c[4];
-                        float v[4];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const int idx = min(p + t, p1 - 1);
-                            c[t] = cols[idx];
-                            v[t] = p + t < p1 ? vals[idx] : 0.f;
-                        }
-                        float4 bq[4];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) bq[t] = *reinterpret_cast<const float4*>(tcol + (c[t] << (psh + 2)));
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            acc.x = fmaf(v[t], bq[t].x, acc.x);
-                            acc.y = fmaf(v[t], bq[t].y, acc.y);
-                            acc.z = fmaf(v[t], bq[t].z, acc.z);
-                            acc.w = fmaf(v[t], bq[t].w, acc.w);
-                        }
-                    }
-                    float* yp = y + (bg.out_row + r) * S.ld_y + f0 + (h << psh) + 4 * hl;
-                    if (S.accumulate) {
-                        const float4 old = *reinterpret_cast<const float4*>(yp);
-                        acc.x += old.x, acc.y += old.y, acc.z += old.z, acc.w += old.w;
-                    }
-                    store_out<4>(yp, acc);
-                }
-                lds_barrier();          // the piece's tile may be overwritten
-            }
-        }
-        if (jn >= j1) return;
-    }
-
-    // the records of this graph and the next sit in scalar registers; the one after that is
-    // fetched a trip ahead
-    const int jbase = jn;
-    StreamSet cur = sets[jn];
-    StreamSet nxt = sets[min(jn + 1, j1 - 1)];
-    request(cur, 0);
-    for (int j = jn; j < j1; ++j) {
-        const int b = (j - jbase) & 1;
-        const StreamSet ahead = sets[min(j + 2, j1 - 1)];
-        const int kx = cur.kx;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's requests for graph j
-        lds_barrier();                                     // everyone's; everyone is done with graph j - 1
-        store_pending();
-        if (j + 1 < j1) request(nxt, b ^ 1);
-
-        // The CSR block of this graph arrived a trip ago: the entry range of this lane's first
-        // output row and its first four entries are read now, so that after the matrix phase
-        // the gather starts with the tile reads instead of two more dependent LDS round trips.
-        const int m = cur.m;
-        const int* rp = cbase + b * S.csr_words;
-        const int* cols = rp + ((m + 4) & ~3);
-        const float* vals = reinterpret_cast<const float*>(cols + ((cur.nnz + 3) & ~3));
-        int first_p0 = 0, first_p1 = 0;
-        int fc[4] = {0, 0, 0, 0};
-        float fv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (r_lane < m) {
-            first_p0 = rp[r_lane];
-            first_p1 = rp[r_lane + 1];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (first_p0 + t < first_p1) {
-                    fc[t] = cols[first_p0 + t];
-                    fv[t] = vals[first_p0 + t];
-                }
-        }
-
-        // ---- dense tile: [X_i W[0] + bias[0]; ...; X_i W[M-1] + bias[M-1]] -> LDS
-        // With lists of the rows in use (S.compact) a wavefront makes only the rows of its
-        // channel's tile that an entry of that channel names: block mb holds the rows
-        // lst[16 mb ..] of X_i and goes to tile rows trow0 + 16 mb ..; without, all kx rows.
-        const float* xs = xbase + b * S.x_words;
-        int rows_w = kx, trow0[U];
-        const int* lst = nullptr;
-#pragma unroll
-        for (int u = 0; u < U; ++u) trow0[u] = unit_ch[u] * kx;
-        if (S.compact) {
-            const int* cnt = reinterpret_cast<const int*>(vals + ((cur.nnz + 3) & ~3));
-            const int c4 = (S.channels + 3) & ~3;
-            rows_w = cnt[unit_ch[0]];
-#pragma unroll
-            for (int u = 0; u < U; ++u) trow0[u] = cnt[c4 + unit_ch[u]];
-            lst = cnt + 2 * c4 + unit_ch[0] * kx;
-        }
-        const int nmb = (rows_w + 15) >> 4;
-        auto x_row = [&](int i) {       // the row of X_i that is row i of this wavefront's blocks
-            const int r = min(i, rows_w - 1);
-            return S.compact ? (r >= 0 ? lst[r] : 0) : r;
         };
-        float4 a[NX16];
-        {
-            const int arow = x_row(col);
-            const float* xrow = xs + arow * NX;
+        fetch(0);
+        for (int r0 = 0; r0 < V; r0 += Q * G) {
+            float4 acc[Q];
+            float sum[Q];                                 // of the row's values: what the bias is taken times
+            int longest = 0;
+            char* zp[Q];
 #pragma unroll
-            for (int s = 0; s < NX16; ++s)
-                a[s] = *reinterpret_cast<const float4*>(xrow + (((4 * s + g) ^ (arow & SWZ)) << 2));
-        }
-        for (int mb = 0; mb < nmb; ++mb) {
-            float4 an[NX16];
-            {   // the next block's rows before this block's instructions (rows past the end repeat the last)
-                const int arow = x_row(16 * (mb + 1) + col);
-                const float* xrow = xs + arow * NX;
-#pragma unroll
-                for (int s = 0; s < NX16; ++s)
-                    an[s] = *reinterpret_cast<const float4*>(xrow + (((4 * s + g) ^ (arow & SWZ)) << 2));
+            for (int q = 0; q < Q; ++q) {
+                acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                sum[q] = 0.f;
+                zp[q] = lds + to[q] + 8 * l;
             }
-            mfma4 acc[U][C];
+            if (e1 - ea <= top) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const char* xp = x0 + (p[q] << row_sh);
+                    const char* vp = v0 + (p[q] << 3);
+                    longest = max(longest, pe[q] - p[q]);
+                    float4 xv[J];
+                    float v[J];
+#pragma unroll
+                    for (int t = 0; t < J; ++t) {
+                        xv[t] = *reinterpret_cast<const float4*>(xp + (t << row_sh));
+                        v[t] = *reinterpret_cast<const float*>(vp + 8 * t);
+                    }
+#pragma unroll
+                    for (int t = 0; t < J; ++t) {
+                        const float vt = p[q] + t < pe[q] ? v[t] : 0.f;
+                        Vec<4>::fma(acc[q], vt, xv[t]);
+                        sum[q] += vt;
+                    }
+                }
+                if (__any(longest > J))
+                    for (int q = 0; q < Q; ++q)
+                        for (int i = p[q] + J; i < pe[q]; ++i) {
+                            const float vt = *reinterpret_cast<const float*>(v0 + (i << 3));
+                            Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
+                            sum[q] += vt;
+                        }
+            } else {         // more entries than slots: the others straight from memory
+                int here = tid;                              // (see place)
+                asm volatile("" : "+v"(here));
+                const uint32_t c4 = 4 * (here & (L - 1));
+                for (int q = 0; q < Q; ++q) {
+                    for (int i = p[q]; i < min(pe[q], top); ++i) {
+                        const float vt = *reinterpret_cast<const float*>(v0 + (i << 3));
+                        Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
+                        sum[q] += vt;
+                    }
+                    for (int i = max(p[q], top); i < pe[q]; ++i) {
+                        const int2 en = entries[(uint32_t)(ea + i)];
+                        Vec<4>::fma(acc[q], __int_as_float(en.y),
+                                    load_vec<4>(x + ((uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + c4)));
+                        sum[q] += __int_as_float(en.y);
+                    }
+                }
+            }
+            if (l == 0)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) sums[min(r0 + q * G + grp, V - 1)] = sum[q];
+            if (Q > 1 && r0 + Q * G < V) fetch(r0 + Q * G);   // the next rows' starts while these are split
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                uint2 h, m, lo;
+                split2(acc[q].x, acc[q].y, h.x, m.x, lo.x);
+                split2(acc[q].z, acc[q].w, h.y, m.y, lo.y);
+                *reinterpret_cast<uint2*>(zp[q]) = h;
+                *reinterpret_cast<uint2*>(zp[q] + PLANE) = m;
+                *reinterpret_cast<uint2*>(zp[q] + 2 * PLANE) = lo;
+                bits |= __float_as_uint(acc[q].x) | __float_as_uint(acc[q].y) | __float_as_uint(acc[q].z) |
+                        __float_as_uint(acc[q].w);
+            }
+            if (Q == 1 && r0 + Q * G < V) fetch(r0 + Q * G);
+        }
+        return bits;
+    };
+
+    bool again = false;                                       // some blocks are to be made again
+    for (int b = b0; b < b1; ++b) {
+        const int buf = (b - b0) & 1;
+        const char* csr = lds + at.csr + buf * at.csr_bytes;
+        place();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's requests for block b
+        lds_barrier();                                     // everyone's; everyone is done with block b - 1
+        store_pending();
+        const int e_then = b + 1 < b1 ? start_in(buf ^ 1, V) : 0;
+        // (virtual rows in flight per lane: what the registers beside the weights hold)
+        constexpr int kRows = WV == 8 ? (KS == 8 ? 1 : 2) : (KS * U <= 6 ? 4 : 2);
+        std::integral_constant<int, 1> one;
+        std::integral_constant<int, 2> two;
+        uint32_t bits;
+        if (V <= G || kRows == 1)
+            bits = gather(one, std::integral_constant<int, kRows == 1 ? 2 : 4>(), e_cur, e_next, csr);
+        else if (M == 1)
+            bits = gather(two, std::integral_constant<int, kRows == 4 ? 4 : 2>(), e_cur, e_next, csr);
+        else if (V <= 2 * G)
+            bits = gather(two, two, e_cur, e_next, csr);
+        else
+            bits = gather(std::integral_constant<int, kRows>(), two, e_cur, e_next, csr);
+        // this lane's output rows
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    acc[u][c] = c == 0 ? mfma4{bv[u], bv[u], bv[u], bv[u]} : mfma4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < NX16; ++s) {
-                const float ak[4] = {a[s].x, a[s].y, a[s].z, a[s].w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        acc[u][k % C] = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[k], w[u][s][k], acc[u][k % C], 0, 0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                mfma4 r = acc[u][0];
-                if (C == 2) r = r + acc[u][C - 1];
-                float* tp = tile + ((trow0[u] + 16 * mb + 4 * g) << fsh) + unit_col[u];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float* q = 16 * mb + 4 * g + i < rows_w ? tp + (i << fsh) : sink;
-                    *q = r[i];
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < NX16; ++s) a[s] = an[s];
-        }
-        lds_barrier();                                     // tile complete
-
-        // ---- gather over the merged CSR: Y_i = sum_ch A_i^ch tile_ch, into registers
-        const char* tcol = reinterpret_cast<const char*>(tile) + 16 * l;
-        const int lsh = fsh + 2;
-        auto add4 = [&](float4& acc, const int (&c)[4], const float (&v)[4]) {
-            float4 bq[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) bq[t] = *reinterpret_cast<const float4*>(tcol + (c[t] << lsh));
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                acc.x = fmaf(v[t], bq[t].x, acc.x);
-                acc.y = fmaf(v[t], bq[t].y, acc.y);
-                acc.z = fmaf(v[t], bq[t].z, acc.z);
-                acc.w = fmaf(v[t], bq[t].w, acc.w);
-            }
-        };
-        auto rest_of_row = [&](float4& acc, int p0, int p1) {     // four entries a trip, the tail masked
-            for (int p = p0; p < p1; p += 4) {
-                int c[4];
-                float v[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int idx = min(p + t, p1 - 1);
-                    c[t] = cols[idx];
-                    v[t] = p + t < p1 ? vals[idx] : 0.f;
-                }
-                add4(acc, c, v);
-            }
-        };
+                pend_row[rb][u] = *reinterpret_cast<const int*>(csr + at.rows + 4 * (16 * rb + (U == 2 ? 8 * u + (col & 7) : col)));
+        if (__builtin_amdgcn_ballot_w64((bits << 1) != 0) != 0 && wl == 0) state[buf] = 1;
+        lds_barrier();                                     // Z complete, slots and this csr buffer free
+        place();
+        if (b + 1 < b1) request_rows(e_next, e_then, buf ^ 1);
+        if (b + 2 < b1) request_csr(b + 2, e_then, buf);
+        if (tid == 0) state[buf ^ 1] = 0;                  // (read before the barrier at the top, written after)
+        float most = 0.f, poison = 0.f;                    // largest magnitude; NaN if one is not finite
         {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (r_lane < m) {
-                if (first_p0 < first_p1) add4(acc, fc, fv);
-                rest_of_row(acc, first_p0 + 4, first_p1);
-            }
-            yv[0] = acc;
-        }
 #pragma unroll
-        for (int q = 1; q < kStreamPasses; ++q) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int r = q * rows_per_pass + r_lane;
-            if (q * rows_per_pass < m && r < m) rest_of_row(acc, rp[r], rp[r + 1]);
-            yv[q] = acc;
+            for (int rb = 0; rb < RB; ++rb) {
+                f32x4 big[U], small[U];
+                // the row sums are the B operand of the bias (row col, channel g)
+                float rs[BQ];
+#pragma unroll
+                for (int q = 0; q < BQ; ++q)
+                    rs[q] = *reinterpret_cast<const float*>(lds + at.sums + 4 * ((16 * rb + col) * M + min(4 * q + g, M - 1)));
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    small[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    big[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[u][0], rs[0], small[u], 0, 0, 0);
+                    if constexpr (BQ == 2)
+                        if (M > 4) big[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[u][1], rs[1], big[u], 0, 0, 0);
+                }
+                const char* zr = lds + (16 * rb + col) * ZP + 16 * g;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const bf16x8 zh = *reinterpret_cast<const bf16x8*>(zr + 64 * s);
+                    const bf16x8 zm = *reinterpret_cast<const bf16x8*>(zr + 64 * s + PLANE);
+                    const bf16x8 zl = *reinterpret_cast<const bf16x8*>(zr + 64 * s + 2 * PLANE);
+                    auto all = [&](f32x4* acc, const bf16x8(&w)[U][KS], const bf16x8& zz) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][s], zz, acc[u], 0, 0, 0);
+                    };
+                    all(big, wh, zh);
+                    all(small, wh, zm);
+                    all(small, wm, zh);
+                    all(small, wm, zm);
+                    all(small, wh, zl);
+                    all(small, wlo, zh);
+                }
+                f32x4 r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    r[u] = big[u] + small[u];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        most = fmaxf(most, fabsf(r[u][i]));
+                        poison = fmaf(r[u][i], 0.f, poison);
+                    }
+                }
+                if constexpr (U == 2) {
+                    const f32x4 q0 = {r[0][0], r[1][0], r[0][1], r[1][1]}, q1 = {r[0][2], r[1][2], r[0][3], r[1][3]};
+                    const bool low = col < 8;
+                    f32x4 got;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)          // row_ror:8 within 16 lanes
+                        got[i] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(low ? q1[i] : q0[i]), 0x128, 0xf, 0xf, true));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        pend[rb][0][i] = low ? q0[i] : got[i];
+                        pend[rb][1][i] = low ? got[i] : q1[i];
+                    }
+                } else {
+                    pend[rb][0] = r[0];
+                }
+            }
         }
-        pend_m = m;
-        pend_row = cur.out_row;
-        cur = nxt;
-        nxt = ahead;
+        // Split numbers that are not finite (or round to infinity) are NaN, and the bf16 instructions take
+        // subnormal numbers as zero: results that are not finite, or all tiny though neither Z nor the weights
+        // are all zero, are made again without the split, when there are no more blocks.
+        if (__builtin_amdgcn_ballot_w64(poison != poison) != 0 ||
+            (weights && __builtin_amdgcn_ballot_w64(most >= 0x1p-60f) == 0 &&
+             __builtin_amdgcn_readfirstlane(state[buf]) != 0)) {
+            if (wl == 0) redo[(b - b0) >> 5] |= 1u << ((b - b0) & 31);
+            again = true;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int u = 0; u < U; ++u) pend_row[rb][u] = -1;
+        }
+        e_cur = e_next;
+        e_next = e_then;
     }
     store_pending();
+    if (!again) return;
+    // The blocks that the split does not hold, without it: every lane computes its columns of its row one
+    // product after the other; a channel in which the row has no entries adds nothing.
+    for (int b = b0; b < b1; ++b) {
+        if (!((redo[(b - b0) >> 5] >> ((b - b0) & 31)) & 1)) continue;
+        for (int rb = 0; rb < RB; ++rb)
+        for (int u = 0; u < U; ++u) {
+            const int row = out_rows[(uint32_t)(R * b + 16 * rb + col)];
+            const int c0 = f0 + 4 * U * g + 4 * u;
+            if (row < 0 || 4 * U * g >= width) continue;
+            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int ch = 0; ch < M; ++ch) {
+                const uint32_t vr = (uint32_t)b * V + (uint32_t)((16 * rb + col) * M + ch);
+                const int first = starts[vr], last = starts[vr + 1];
+                if (last <= first) continue;
+                const float* bp = bias + ch * S.bias_stride + c0;
+                float rs = 0.f;
+                for (int i = first; i < last; ++i) rs += __int_as_float(entries[(uint32_t)i].y);
+                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+                Vec<4>::fma(acc, rs, make_float4(bp[0], bp[1], bp[2], bp[3]));
+                for (int k = 0; k < 4 * L; ++k) {
+                    float zv = 0.f;
+                    for (int i = first; i < last; ++i) {
+                        const int2 en = entries[(uint32_t)i];
+                        zv = fmaf(__int_as_float(en.y), x[(uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + k], zv);
+                    }
+                    Vec<4>::fma(acc, zv, load_vec<4>(wgt + (int64_t)(ch * 4 * L + k) * S.ld_w + c0));
+                }
+                sum.x += acc.x, sum.y += acc.y, sum.z += acc.z, sum.w += acc.w;
+            }
+            float* yp = y + ((uint64_t)(uint32_t)row * (uint32_t)S.ld_y + (uint32_t)c0);
+            if (S.accumulate) {
+                const float4 old = *reinterpret_cast<const float4*>(yp);
+                sum.x += old.x, sum.y += old.y, sum.z += old.z, sum.w += old.w;
+            }
+            store_out<4>(yp, sum);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -3029,7 +3076,7 @@ hipError_t kernel_resources(int which, int lds_bytes, int out[7])
             threads = kBuildThreadsLarge;
             break;
         case 7: fn = reinterpret_cast<const void*>(&bspmm_coo_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void*>(&bspmm_gcn_stream_kernel<4, 2, 4>); break;
+        case 8: fn = reinterpret_cast<const void*>(&bspmm_layer_kernel<8, 2, 1, 4>); break;
         default: return hipErrorInvalidValue;
     }
     hipFuncAttributes a;
@@ -3123,49 +3170,36 @@ hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool
     return launch(front_variant(accumulate, sets, wide), grid, wide ? 2 * kThreads : kThreads, lds_bytes, stream, P);
 }
 
-using StreamFn = void (*)(const StreamSet*, const int32_t*, const int32_t*, const float*, const float*,
-                          const float*, float*, const StreamShape);
+using LayerFn = void (*)(const int32_t*, const int2*, const int32_t*, const float*, const float*, const float*, float*,
+                         const LayerShape);
 
-// (n_X / 16, blocks per wavefront, wavefronts) -> kernel; null for shapes the streaming kernel is
-// not built for
-static StreamFn stream_variant(int nx16, int units, int waves)
+// (steps of 32 of K, 16-column blocks per wavefront, 16-row blocks per trip, wavefronts) -> kernel; null for
+// what it is not built for
+static LayerFn layer_variant(int ks, int units, int rb, int waves)
 {
-    if (waves == 4 && units == 1) {
-        switch (nx16) {
-        case 1: return bspmm_gcn_stream_kernel<1, 1, 4>;
-        case 2: return bspmm_gcn_stream_kernel<2, 1, 4>;
-        case 4: return bspmm_gcn_stream_kernel<4, 1, 4>;
-        case 8: return bspmm_gcn_stream_kernel<8, 1, 4>;
-        }
-    } else if (waves == 4 && units == 2) {
-        switch (nx16) {
-        case 1: return bspmm_gcn_stream_kernel<1, 2, 4>;
-        case 2: return bspmm_gcn_stream_kernel<2, 2, 4>;
-        case 4: return bspmm_gcn_stream_kernel<4, 2, 4>;
-        }
-    } else if (waves == 8 && units == 2) {      // eight channels: a wavefront per channel
-        switch (nx16) {
-        case 1: return bspmm_gcn_stream_kernel<1, 2, 8>;
-        case 2: return bspmm_gcn_stream_kernel<2, 2, 8>;
-        case 4: return bspmm_gcn_stream_kernel<4, 2, 8>;
-        }
-    } else if (waves == 8 && units == 1) {      // the same on tiles of 16 columns (n_X = 128, F = 16, 48, ...)
-        switch (nx16) {
-        case 1: return bspmm_gcn_stream_kernel<1, 1, 8>;
-        case 2: return bspmm_gcn_stream_kernel<2, 1, 8>;
-        case 4: return bspmm_gcn_stream_kernel<4, 1, 8>;
-        case 8: return bspmm_gcn_stream_kernel<8, 1, 8>;
-        }
-    }
+    static const struct { int ks, units, rb, waves; LayerFn fn; } table[] = {
+#define BSPMM_LAYER(K, U, R, W) {K, U, R, W, bspmm_layer_kernel<K, U, R, W>}
+        BSPMM_LAYER(1, 1, 1, 4), BSPMM_LAYER(1, 1, 2, 4), BSPMM_LAYER(1, 1, 4, 4), BSPMM_LAYER(1, 2, 1, 4),
+        BSPMM_LAYER(1, 2, 2, 4), BSPMM_LAYER(1, 2, 4, 4), BSPMM_LAYER(2, 1, 1, 4), BSPMM_LAYER(2, 1, 2, 4),
+        BSPMM_LAYER(2, 2, 1, 4), BSPMM_LAYER(2, 2, 2, 4), BSPMM_LAYER(3, 1, 1, 4), BSPMM_LAYER(3, 1, 2, 4),
+        BSPMM_LAYER(3, 2, 1, 4), BSPMM_LAYER(3, 2, 2, 4), BSPMM_LAYER(4, 1, 1, 4), BSPMM_LAYER(4, 1, 2, 4),
+        BSPMM_LAYER(4, 2, 1, 4), BSPMM_LAYER(4, 2, 2, 4), BSPMM_LAYER(6, 1, 1, 4), BSPMM_LAYER(6, 2, 1, 4),
+        BSPMM_LAYER(8, 1, 1, 4), BSPMM_LAYER(8, 2, 1, 4), BSPMM_LAYER(12, 1, 1, 4), BSPMM_LAYER(16, 1, 1, 4),
+        BSPMM_LAYER(1, 1, 2, 8), BSPMM_LAYER(1, 1, 4, 8), BSPMM_LAYER(2, 1, 2, 8), BSPMM_LAYER(2, 1, 1, 8),
+        BSPMM_LAYER(3, 1, 1, 8), BSPMM_LAYER(3, 1, 2, 8), BSPMM_LAYER(4, 1, 1, 8), BSPMM_LAYER(4, 1, 2, 8),
+        BSPMM_LAYER(6, 1, 1, 8), BSPMM_LAYER(8, 1, 1, 8), BSPMM_LAYER(12, 1, 1, 8), BSPMM_LAYER(16, 1, 1, 8)};
+#undef BSPMM_LAYER
+    for (const auto& v : table)
+        if (v.ks == ks && v.units == units && v.rb == rb && v.waves == waves) return v.fn;
     return nullptr;
 }
 
-bool stream_supported(int nx16, int units, int waves) { return stream_variant(nx16, units, waves) != nullptr; }
+bool layer_supported(int ks, int units, int rb, int waves) { return layer_variant(ks, units, rb, waves) != nullptr; }
 
-// Workgroups of the streaming kernel one CU of the current device holds (0 if it cannot be asked).
-int stream_workgroups_per_cu(int nx16, int units, int waves, int lds_bytes)
+// Workgroups of the layer kernel one CU of the current device holds (0 if it cannot be asked).
+int layer_workgroups_per_cu(int ks, int units, int rb, int waves, int lds_bytes)
 {
-    const StreamFn fn = stream_variant(nx16, units, waves);
+    const LayerFn fn = layer_variant(ks, units, rb, waves);
     int per_cu = 0;
     if (!fn) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * waves, (size_t)lds_bytes) != hipSuccess) {
@@ -3175,13 +3209,21 @@ int stream_workgroups_per_cu(int nx16, int units, int waves, int lds_bytes)
     return per_cu;
 }
 
-hipError_t launch_bspmm_gcn_stream(const StreamParams& P, int nx16, int units, int waves, int grid,
-                                   int lds_bytes, hipStream_t stream)
+hipError_t launch_bspmm_layer(const LayerParams& P, int ks, int units, int rb, int waves, int lds_bytes, hipStream_t stream)
 {
-    if (grid <= 0) return hipSuccess;
-    const StreamFn fn = stream_variant(nx16, units, waves);
+    const LayerFn fn = layer_variant(ks, units, rb, waves);
     if (!fn) return hipErrorInvalidValue;
-    return launch(fn, grid, 64 * waves, lds_bytes, stream, P.sets, P.list, P.merged, P.x, P.w, P.bias, P.y, P.shape);
+    return launch(fn, 8 * P.shape.ranges_per_xcd * P.shape.tiles, 64 * waves, lds_bytes, stream, P.starts,
+                  reinterpret_cast<const int2*>(P.entries), P.out_rows, P.x, P.w, P.bias, P.y, P.shape);
+}
+
+hipError_t launch_layer_rows(const LayerSet* sets, int count, const OpRecord* ops, const int32_t* rpt,
+                             const int32_t* colids, const float* values, int32_t* starts, int32_t* entries,
+                             int32_t* out_rows, hipStream_t stream)
+{
+    if (count <= 0) return hipSuccess;
+    return launch(layer_rows_kernel, count, kThreads, 0, stream, sets, ops, rpt, colids, values, starts,
+                  reinterpret_cast<int2*>(entries), out_rows);
 }
 
 hipError_t launch_build_transpose(const OpRecord* ops, int batch, int threads, int lds_bytes,

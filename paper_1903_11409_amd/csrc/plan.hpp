@@ -113,47 +113,42 @@ struct LaunchParams {
     int32_t accumulate;   // add to the output instead of overwriting it
 };
 
-// Whole layers in launches of many rounds (bspmm_run_gcn, plans with front_features and
-// BSPMM_ACCUMULATE): resident workgroups that keep their weight tile in registers and stream
-// the graphs of their list through LDS.  One record per graph (a set of M channel operations
-// with one merged CSR):
-struct alignas(16) StreamSet {
-    int64_t in_row;       // first row of X_i
-    int64_t out_row;      // first row of Y_i
-    uint32_t csr_off;     // word offset, from the base of the merged arrays, of the set's block:
-                          // row pointers (m + 1, padded to 4), columns (nnz, padded to 4), values
-    int32_t m;            // rows of Y_i (rows of every channel matrix)
-    int32_t kx;           // rows of X_i (columns of every channel matrix)
-    int32_t nnz;          // entries of the merged CSR
+// Layers in launches of many rounds (bspmm_run_gcn, plans with front_features): the output rows of all
+// graphs, one after the other, in blocks of 16 (see bspmm_layer_kernel).  One record per graph (M channel
+// operations that share the layer input and the output block, or one operation) for the kernel that
+// writes the blocks' arrays.
+struct LayerSet {
+    int32_t op[kMaxMembers];        // the channels' operations
+    int32_t channels;
+    int32_t m;                      // rows of Y_i
+    int32_t in_row, out_row;        // first row of X_i and of Y_i
+    int32_t first_row;              // place of the graph's first row among all rows
+    int32_t first_entry, entries;   // and of its entries
+    int32_t pad_rows;               // the last graph: empty rows behind it that fill a block; others: -1
 };
-static_assert(sizeof(StreamSet) == 32, "StreamSet must be 32 bytes");
+static_assert(sizeof(LayerSet) == 64, "LayerSet must be 64 bytes");
 
-constexpr int kStreamPasses = 4;   // row passes of the gather a streamed graph may take: the
-                                   // results of a graph wait in registers for one loop trip
-
-// Arguments of the streaming kernel.  Every list l < lists has one workgroup per feature tile
-// (columns [fw * tile, fw * tile + fw)), which takes the graphs list[l] .. list[l + 1]; the
-// workgroups of a list sit on one XCD (see the kernel for the mapping; the grid is
-// round_up(lists, 8) * tiles).
-// LDS, in words: the dense tile (tile_words), two buffers for rows of X (x_words each), two
-// for merged CSR blocks (csr_words each), 64 words that take the tile rows past a graph's end.
-// (The pointers are kernel arguments of their own, qualified so that the graph records are
-// fetched with scalar loads.)
-struct StreamShape {
+// Shape of one launch.  The grid is 8 * ranges_per_xcd * tiles workgroups; range i takes the blocks
+// blocks * i / (8 ranges_per_xcd) and up.
+struct LayerShape {
     int64_t ld_x, ld_w, ld_y, bias_stride;
-    int32_t tiles, fw, channels, accumulate;
-    int32_t tile_words, x_words, csr_words, big_csr_words;
-    int32_t lists, compact, real_channels, reserved_;   // (channels >= real_channels are empty: see the host)
+    int32_t blocks, ranges_per_xcd, tiles;
+    int32_t F;
+    int32_t channels;       // of this launch
+    int32_t inv_channels;   // x * inv >> 16 == x / channels for a block's virtual rows x
+    int32_t lane_shift;     // log2 of the float4 in a row of X
+    int32_t slots;          // rows of X a workgroup holds in LDS, a multiple of 256 / n_X
+    int32_t accumulate;
 };
-struct StreamParams {
-    const StreamSet* sets;
-    const int32_t* list;
-    const int32_t* merged;
+struct LayerParams {
+    const int32_t* starts;
+    const int32_t* entries;
+    const int32_t* out_rows;
     const float* x;
     const float* w;
     const float* bias;
     float* y;
-    StreamShape shape;
+    LayerShape shape;
 };
 
 // One unit of work of the direct COO kernel: the output rows [row0, row0+nrows) x feature
@@ -301,26 +296,39 @@ struct alignas(8) SetRecord {
     int32_t nnz[kMaxMembers];
     int32_t k[kMaxMembers];         // dense-input rows of the members (bound of their columns)
     int32_t tile_row[kMaxMembers];  // first row of member j's dense tile in the concatenation
-    int32_t row_off[kMaxMembers];   // the set's row that is member j's row 0, and member j's rows
-    int32_t rows[kMaxMembers];      // (summed sets: 0 and m for every member; groups of graphs in
-                                    // the streaming launch: each graph's members have their own)
     int32_t members;
     int32_t m;
     int32_t plain;                  // 1: the members read one dense block; the merged arrays are
                                     // then an ordinary CSR (row pointers, round_up(sum nnz, 4)
                                     // columns, as many values) that a plain item reads
-    int32_t compact;                // 0, or channels | rows of the group's layer input << 8: the
-                                    // rows of each channel's dense tile that are in use are
-                                    // listed behind the values and the columns renumbered
+    int32_t reserved_;
 };
 
-// Words behind the values of a compacted set: counts and first tile rows of the channels
-// (padded to four each), then a list of kxt words per channel.
-BSPMM_HD inline int compact_words(int chans, int kxt)
+// LDS of bspmm_layer_kernel, in bytes: three planes of 16 rb rows of Z; the slots and a few to spare; two
+// buffers with what a block's gather reads (starts, output rows, entries); the sums of the virtual rows'
+// values; four words of state, for
+// every wavefront a bit for every block of a range that has to be made again without the split, and the
+// virtual rows' places in Z.
+constexpr int kLayerRedoWords = 8;
+constexpr int kLayerRangeBlocks = 32 * kLayerRedoWords;     // blocks of a range, at most
+constexpr int kLayerSpare = 4;
+BSPMM_HD constexpr int layer_z_row(int ks) { return 64 * ks + 16; }
+struct LayerLds {
+    int slots, csr, csr_bytes, rows, entries, sums, state, total;    // (rows, entries: inside a buffer)
+};
+BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int slots, int nx)
 {
-    return chans > 0 ? round_up(2 * round_up(chans, 4) + chans * kxt, 4) : 0;
+    LayerLds L;
+    L.slots = 3 * 16 * rb * layer_z_row(ks);
+    L.csr = L.slots + 4 * (slots + kLayerSpare) * nx;
+    L.rows = 4 * round_up(16 * rb * channels + 1, 4);
+    L.entries = L.rows + 64 * rb;
+    L.csr_bytes = L.entries + 8 * (slots + kLayerSpare);
+    L.sums = L.csr + 2 * L.csr_bytes;
+    L.state = L.sums + 64 * rb * channels;
+    L.total = L.state + 16 + 4 * waves * kLayerRedoWords + 64 * rb * channels;
+    return L;
 }
-constexpr int kCompactRows = 1024;   // tile rows (channels x rows of X) of a set that is compacted, at most
 
 // bspmm_any_kernel: words from one row of the LDS tile to the next.  A row off 16 bytes is copied as
 // the 16-byte words it lies in and starts up to three words into the first.
