@@ -94,7 +94,7 @@ struct Layout {
     size_t merged[2] = {0, 0};
     // layers run by resident workgroups: graph records, the items of the graphs that stay with the
     // one-launch kernel, and the arrays the device builds
-    size_t stream_sets = 0, stream_rest = 0, stream_arrays = 0;
+    size_t stream_sets = 0, stream_items = 0, stream_rest = 0, stream_arrays = 0;
     // plans made from COO operands: the CSR arrays built on the device and what the build needs
     size_t coo_records = 0;
     size_t csr_rpt = 0, csr_colids = 0, csr_values = 0;
@@ -151,8 +151,9 @@ struct bspmm_plan {
         };
         std::vector<Part> parts;
         std::vector<LayerSet> sets;
+        std::vector<LayerItem> items;    // small layers of one channel: the blocks, read from the CSR arrays
         std::vector<WorkItem> rest;
-        int units = 0, rb = 0, waves = 4, tiles = 0, blocks = 0;
+        int units = 0, rb = 0, waves = 4, tiles = 0, blocks = 0, direct_entries = 0;
         int64_t out_rows_at = 0, words = 0;
         bool built = false;
         int graphs = 0;
@@ -350,13 +351,25 @@ void make_stream_plan(bspmm_plan& p)
         entries += nnz;
     }
     if (mine.empty() || (rows + 64) * channels >= kLimit || entries >= kLimit) return;
-    // Fewer graphs: one block to a workgroup, where there are enough to matter.  The arrays cost the first
-    // run of a plan a launch that a single channel does not have otherwise (about 5 us; whole layers merge
-    // their channels' CSR arrays for either kernel).  us of a run, F = 128, this kernel / one-launch kernel:
-    // one channel at n_X = 64, 16 graphs 4.5 / 4.5, 64 graphs 4.7 / 6.1, 128 graphs 5.0 / 6.9; four channels
-    // at n_X = 64, 24 graphs 6.4 / 6.6, 128 graphs 6.9 / 14.2; K = channels n_X past 256: 24 graphs of
-    // four channels at n_X = 128 9.9 / 8.5, 64 graphs 9.9 / 14.0.
+    // Fewer graphs: one block to a workgroup, where there are enough to matter.  Blocks of one channel are rows
+    // of one operation then, whose CSR arrays the kernel reads as they are: the first run of a plan needs no
+    // other launch (whole layers merge their channels' CSR arrays for either kernel).  us of a run, F = 128, this
+    // kernel / one-launch kernel: one channel at n_X = 64, 32 graphs 5.4 / 5.6, 64 graphs 4.6 / 6.1, 128 graphs 5.3 /
+    // 6.6, 300 graphs 6.6 / 8.5; at n_X = 16, F = 64, 1000 graphs 7.2 / 7.5; four channels at n_X = 64, 24 graphs
+    // 6.4 / 6.6, 128 graphs 6.9 / 14.2; K = channels n_X past 256: 24 graphs of four channels at n_X = 128 9.9 /
+    // 8.5, 64 graphs 9.9 / 14.0.
+    const bool direct = single && !st.many;
     if (!st.many && (rows + 15) / 16 * (single || channels * nx > 256 ? 4 : 8) < kn.compute_units) return;
+    int most_k = 0, most_nnz = 0;                        // of an operation: it has to fit on chip
+    if (direct) {
+        int64_t words = 0;                               // (32-bit offsets)
+        for (int g : mine) {
+            words = std::max({words, o.rpt_off[g] + o.m[g] + 1, o.nz_off[g] + o.nnz[g]});
+            most_k = std::max(most_k, o.k[g]);
+            most_nnz = std::max(most_nnz, o.nnz[g]);
+        }
+        if (words >= kLimit || most_nnz > 4096) return;
+    }
     std::stable_sort(mine.begin(), mine.end(),
                      [&](int a, int b) { return o.in_off[op_of(a, 0)] < o.in_off[op_of(b, 0)]; });
 
@@ -387,7 +400,7 @@ void make_stream_plan(bspmm_plan& p)
     auto slots_in = [&](int rb, int ch, int bytes, int want) {
         const int unit = 256 / nx;             // rows that a wavefront's request brings
         int n = round_up(std::min(want, 256), unit);
-        while (n > 0 && layer_lds(steps_of(ch), rb, waves, ch, n, nx).total > bytes) n -= unit;
+        while (n > 0 && layer_lds(steps_of(ch), rb, waves, ch, n, n, nx).total > bytes) n -= unit;
         return n;
     };
     const double per_row = (double)entries / (double)rows;
@@ -396,7 +409,7 @@ void make_stream_plan(bspmm_plan& p)
     {
         const int groups = 256 * waves / nx;     // virtual rows that a pass takes
         double best = 0;
-        for (int r = 1; r <= 4; r *= 2) {
+        for (int r = 1; r <= (direct ? 1 : 4); r *= 2) {
             if (!layer_supported(steps_of(most), units, r, waves) || 16 * r * most > 240 ||
                 (r > 1 && slots_in(r, most, budget, wanted(r)) < std::min(wanted(r), 256)))
                 continue;
@@ -409,7 +422,20 @@ void make_stream_plan(bspmm_plan& p)
             }
         }
     }
-    const int64_t blocks = (rows + 16 * rb - 1) / (16 * rb);
+    int64_t blocks = (rows + 16 * rb - 1) / (16 * rb);
+    if (direct)
+        for (int g : mine)
+            for (int r0 = 0; r0 < o.m[g]; r0 += 16) {
+                LayerItem t = {};
+                t.rpt_off = (uint32_t)(o.rpt_off[g] + r0);
+                t.nz_off = (uint32_t)o.nz_off[g];
+                t.in_row = (uint32_t)o.in_off[g];
+                t.out_row = (uint32_t)(o.out_off[g] + r0);
+                t.nrows = std::min(16, o.m[g] - r0);
+                t.k = o.k[g], t.nnz = o.nnz[g];
+                st.items.push_back(t);
+            }
+    if (direct) blocks = (int64_t)st.items.size();
     st.units = units;
     st.rb = rb;
     st.waves = waves;
@@ -421,29 +447,40 @@ void make_stream_plan(bspmm_plan& p)
         at += (words + 3) / 4 * 4;
         return here;
     };
-    st.out_rows_at = place(16 * rb * blocks);
+    if (!direct) st.out_rows_at = place(16 * rb * blocks);
     for (int c0 = 0; c0 < channels; c0 += most) {
         bspmm_plan::Stream::Part part;
         part.first_channel = c0;
         part.channels = std::min(most, channels - c0);
         part.ks = steps_of(part.channels);
-        if (!layer_supported(part.ks, units, rb, waves)) {
+        if (!layer_supported(part.ks, units, direct ? 0 : rb, waves)) {
             st = bspmm_plan::Stream();
             return;
         }
         part.slots = slots_in(rb, part.channels, budget, std::max(wanted(rb), 64));
-        if (!kn.lds_given && part.slots < 40) part.slots = slots_in(rb, part.channels, 81920, std::max(wanted(rb), 64));
-        if (part.slots < 16) {
+        if (direct) part.slots = round_up(std::max(most_k, 1), 256 / nx);
+        else if (!kn.lds_given && part.slots < 40) part.slots = slots_in(rb, part.channels, 81920, std::max(wanted(rb), 64));
+        if (part.slots < 16 && !direct) {
             st = bspmm_plan::Stream();
             return;
         }
-        part.lds_bytes = layer_lds(part.ks, rb, waves, part.channels, part.slots, nx).total;
-        int per_cu = kn.device_ok ? layer_workgroups_per_cu(part.ks, units, rb, waves, part.lds_bytes) : 0;
+        part.lds_bytes = layer_lds(part.ks, rb, waves, part.channels, part.slots, direct ? most_nnz : part.slots, nx).total;
+        // (operations that do not fit half of a CU's LDS: the one-launch kernel)
+        if (direct && part.lds_bytes > (kn.lds_given ? budget : 81920)) {
+            st = bspmm_plan::Stream();
+            return;
+        }
+        st.direct_entries = most_nnz;
+        int per_cu = kn.device_ok ? layer_workgroups_per_cu(part.ks, units, direct ? 0 : rb, waves, part.lds_bytes) : 0;
         if (per_cu <= 0) per_cu = 2;
         per_cu = std::min(per_cu, 3);
         const int64_t most_ranges = std::max<int64_t>(8, (int64_t)per_cu * kn.compute_units / st.tiles);
-        const int64_t ranges = blocks <= most_ranges ? blocks + 7 : most_ranges;
+        const int64_t ranges = direct || blocks <= most_ranges ? blocks + 7 : most_ranges;
         part.ranges_per_xcd = (int)std::max<int64_t>(ranges / 8, (blocks / kLayerRangeBlocks + 8) / 8);
+        if (direct) {
+            st.parts.push_back(part);
+            break;
+        }
         part.sets_at = st.sets.size();
         int64_t row = 0, entry = 0;
         for (int g : mine) {
@@ -742,6 +779,7 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
         place(L.build_order, (size_t)n * sizeof(int32_t));
         for (int d = 0; d < 2; ++d) place(L.sets[d], p.set_records[d].size() * sizeof(SetRecord));
         place(L.stream_sets, p.stream.sets.size() * sizeof(LayerSet));
+        place(L.stream_items, p.stream.items.size() * sizeof(LayerItem));
         place(L.stream_rest, p.stream.rest.size() * sizeof(WorkItem));
         L.image = at;
         place(L.rpt_t, (size_t)rpt_t_words * 4);
@@ -976,7 +1014,7 @@ void csr_of_direction(const bspmm_plan* p, int d, const int32_t** rpt, const int
 int enqueue_layer_rows(bspmm_plan* p, hipStream_t s)
 {
     bspmm_plan::Stream& st = p->stream;
-    if (st.built || !st.on()) return BSPMM_OK;
+    if (st.built || !st.on() || !st.items.empty()) return BSPMM_OK;
     int32_t* base = reinterpret_cast<int32_t*>(p->ws + p->lay.stream_arrays);
     const int count = (int)(st.sets.size() / st.parts.size());
     for (const bspmm_plan::Stream::Part& part : st.parts) {
@@ -1236,6 +1274,7 @@ void write_image(const bspmm_plan* p, char* to)
     put(L.coo_records, p->coo_records);
     put(L.build_order, p->build_order);
     put(L.stream_sets, p->stream.sets);
+    put(L.stream_items, p->stream.items);
     put(L.stream_rest, p->stream.rest);
 }
 
@@ -1363,16 +1402,21 @@ int run_gcn(bspmm_plan* p, const float* X, int64_t ldx, const float* W, int64_t 
             S.w = W + (int64_t)part.first_channel * nx * ldw;
             S.bias = bias + (int64_t)part.first_channel * p->F;
             S.y = Y;
+            S.direct = {reinterpret_cast<const LayerItem*>(p->ws + p->lay.stream_items), p->rpt, p->colids, p->values};
             LayerShape& sh = S.shape;
             sh.ld_x = ldx, sh.ld_w = ldw, sh.ld_y = ldy, sh.bias_stride = p->F;
             sh.blocks = st.blocks, sh.ranges_per_xcd = part.ranges_per_xcd, sh.tiles = st.tiles;
+            const int ranges = 8 * part.ranges_per_xcd;
+            sh.blocks_each = st.blocks / ranges, sh.blocks_over = st.blocks % ranges;
+            sh.inv_tiles = st.tiles > 1 ? (uint32_t)(((uint64_t(1) << 32) + st.tiles - 1) / st.tiles) : 0;
             sh.F = p->F;
             sh.channels = part.channels;
             sh.inv_channels = (65535 + part.channels) / part.channels;
             sh.lane_shift = nx == 16 ? 2 : (nx == 32 ? 3 : (nx == 64 ? 4 : 5));
             sh.slots = part.slots;
+            sh.entries = st.direct_entries;
             sh.accumulate = accumulate || part.first_channel > 0 ? 1 : 0;
-            const hipError_t es = launch_bspmm_layer(S, part.ks, st.units, st.rb, st.waves, part.lds_bytes, s);
+            const hipError_t es = launch_bspmm_layer(S, part.ks, st.units, st.items.empty() ? st.rb : 0, st.waves, part.lds_bytes, s);
             if (es != hipSuccess) return hip_fail(es);
         }
         if (st.rest.empty()) return BSPMM_OK;

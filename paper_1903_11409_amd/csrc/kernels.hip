@@ -2195,6 +2195,10 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 //     an output row.  Results wait in registers and are stored at the top of the next trip, so that the
 //     wait there finds only requests and stores that are a whole trip old; stores write whole 128-byte
 //     lines (half lines: one channel, 2048 graphs, n_X = 64 20.5 us instead of 16.4).
+// DIRECT: small layers of one channel, a block of 16 rows of one operation to a workgroup.  X_i, the
+// operation's entries and its row pointers are requested at once and no other launch is needed (128 graphs,
+// n_X = 64, F = 128: 5.3 us; with row pointers, entries and rows of X one after the other 5.7; from arrays
+// built once per plan 4.9, but the first run 8 us longer; the one-launch kernel 6.6).
 // Two barriers a trip.  us of a launch, F = 128, molecules, against the kernel this replaces, which made the
 // dense tiles graph by graph with fp32 matrix instructions: four channels at n_X = 64, 2048 graphs 43.4 ->
 // 29.6, 512 15.4 -> 12.5, 128 11.6 -> 6.8; n_X = 128, 2048 graphs 85.6 -> 57.3; eight channels at n_X = 64, 1024
@@ -2244,11 +2248,11 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t&
     lo = pair(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
 }
 
-template <int KS, int U, int RB, int WV>
+template <int KS, int U, int RB, int WV, bool DIRECT>
 __global__ void __launch_bounds__(64 * WV, WV == 8 ? (KS > 8 ? 2 : 4) : (KS * U > 8 || (KS > 2 && U * RB > 2) ? 2 : 3))
 bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ entries,
                    const int32_t* __restrict__ out_rows, const float* __restrict__ x, const float* __restrict__ wgt,
-                   const float* __restrict__ bias, float* __restrict__ y, const LayerShape S)
+                   const float* __restrict__ bias, float* __restrict__ y, const LayerDirect D, const LayerShape S)
 {
     extern __shared__ __align__(16) int sm[];
     constexpr int T = 64 * WV;                                // lanes: four or eight wavefronts
@@ -2261,17 +2265,50 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     // Workgroups go to the XCDs round robin (index mod 8): a range of blocks and its feature tiles sit
     // on one XCD, and neighbouring ranges too, so that its L2 fetches the rows of X once.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int tile = slot % S.tiles, range = xcd * S.ranges_per_xcd + slot / S.tiles;
-    const int b0 = (int)((int64_t)S.blocks * range / (8 * S.ranges_per_xcd));
-    const int b1 = (int)((int64_t)S.blocks * (range + 1) / (8 * S.ranges_per_xcd));
+    const int pair = S.tiles == 1 ? slot : (int)__umulhi((uint32_t)slot, S.inv_tiles);
+    const int tile = slot - pair * S.tiles, range = xcd * S.ranges_per_xcd + pair;
+    const int b0 = DIRECT ? range : range * S.blocks_each + min(range, S.blocks_over);
+    const int b1 = DIRECT ? min(range + 1, S.blocks) : b0 + S.blocks_each + (range < S.blocks_over ? 1 : 0);
     if (b0 >= b1) return;
+    // DIRECT: one channel, one block to a workgroup, 16 rows of one operation.  Its row pointers, all of the
+    // operation's entries and all of X_i are requested at once (the slots are the rows of X_i, in their
+    // order): one trip to memory instead of one for the row pointers, one for the entries, one for the rows
+    // of X.
+    LayerItem it;
+    if constexpr (DIRECT) it = D.items[b0];
     const int M = S.channels, V = R * M;                      // virtual rows of a block
     const int lsh = S.lane_shift, L = 1 << lsh;               // n_X / 4 lanes per virtual row
     const int G = T >> lsh;
     int l = tid & (L - 1), grp = tid >> lsh;
     const int row_sh = lsh + 4;                               // a row of X in LDS is 16 << lsh bytes
 
-    const LayerLds at = layer_lds(KS, RB, WV, M, S.slots, 4 << lsh);
+    // ---- this wavefront's weights.  Block u has the columns f0 + U i + u, i < 16 (a lane's loads of a row are U columns side by side, and its
+    // results U float4): the A operand is W^T, lane (g, col) holds W[32 s + 8 g + j][f0 + U col + u], j < 8 (all
+    // eight inside K or none: K is a multiple of 16; where none the weights of k = j stand in, the columns of Z
+    // there are zero)
+    const int K = M << (lsh + 2);
+    const int f0 = (tile * WV + wave) * (16 * U);
+    const int width = min(16 * U, S.F - f0);                  // columns of this wavefront (none: negative)
+    const int w_col = width > 0 ? f0 + U * min(col, width / U - 1) : 0;
+    float raw[KS][8][U];
+    auto request_weights = [&]() {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = 32 * s + 8 * g;
+            const uint32_t off = ((uint32_t)(k < K ? k : 0) * (uint32_t)S.ld_w + (uint32_t)w_col) << 2;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const char* p = reinterpret_cast<const char*>(wgt + j * S.ld_w) + off;
+                if constexpr (U == 2) {
+                    const float2 t = *reinterpret_cast<const float2*>(p);
+                    raw[s][j][0] = t.x, raw[s][j][1] = t.y;
+                } else {
+                    raw[s][j][0] = *reinterpret_cast<const float*>(p);
+                }
+            }
+        }
+    };
+    const LayerLds at = layer_lds(KS, RB, WV, M, S.slots, DIRECT ? S.entries : S.slots, 4 << lsh);
     char* const lds = reinterpret_cast<char*>(sm);
     char* const xs = lds + at.slots;            // the rows of X that the entries name
     int* const state = reinterpret_cast<int*>(lds + at.state);   // Z has numbers other than zero (two buffers)
@@ -2312,53 +2349,60 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         return __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(lds + at.csr + buf * at.csr_bytes + 4 * vr));
     };
 
-    int e_cur = starts[(uint32_t)b0 * V], e_next = starts[(uint32_t)(b0 + 1) * V];
-    request_csr(b0, e_cur, 0);
-    if (b0 + 1 < b1) request_csr(b0 + 1, e_next, 1);
+    int e_cur = 0, e_next = 0;
+    if constexpr (DIRECT) {
+        const char* xi = reinterpret_cast<const char*>(x + ((uint64_t)it.in_row * (uint32_t)S.ld_x + 4 * l));
+        for (int i0 = wave * (64 >> lsh); i0 < it.k; i0 += T >> lsh) {
+            const int r = min(i0 + (wl >> lsh), it.k - 1);
+            lds_dma16_to(xi + (uint64_t)(uint32_t)r * ((uint32_t)S.ld_x * 4ull), xs_lds + (i0 << row_sh));
+        }
+        const int rp = D.rpt[it.rpt_off + (uint32_t)min(tid, it.nrows)];
+        const int n = max(it.nnz, 1) - 1;
+        const int c0 = it.nnz > 0 ? D.colids[it.nz_off + (uint32_t)min(tid, n)] : 0;
+        const float a0 = it.nnz > 0 ? D.values[it.nz_off + (uint32_t)min(tid, n)] : 0.f;
+        request_weights();
+        int* st = reinterpret_cast<int*>(lds + at.csr);
+        int2* ent = reinterpret_cast<int2*>(lds + at.csr + at.entries);      // (place in the slots, value)
+        auto place_of = [&](int c) { return ((unsigned)c < (unsigned)it.k ? c : 0) << row_sh; };
+        if (tid <= 16) st[tid] = min(max(rp, 0), it.nnz);
+        if (tid < 16) *reinterpret_cast<int*>(lds + at.csr + at.rows + 4 * tid) = tid < it.nrows ? (int)it.out_row + tid : -1;
+        if (tid < it.nnz) ent[tid] = make_int2(place_of(c0), __float_as_int(a0));
+        for (int i = tid + T; i < it.nnz; i += T)
+            ent[i] = make_int2(place_of(D.colids[it.nz_off + (uint32_t)i]), __float_as_int(D.values[it.nz_off + (uint32_t)i]));
+        if (tid < kLayerSpare) ent[it.nnz + tid] = make_int2(0, 0);
+        e_next = it.nnz;
+    } else {
+        e_cur = starts[(uint32_t)b0 * V], e_next = starts[(uint32_t)(b0 + 1) * V];
+        request_csr(b0, e_cur, 0);
+        if (b0 + 1 < b1) request_csr(b0 + 1, e_next, 1);
+    }
     for (int i = tid; i < 4 + WV * kLayerRedoWords; i += T) state[i] = 0;
     for (int i = tid; i < V; i += T) {
         const int r = (i * S.inv_channels) >> 16;
         z_place[i] = r * ZP + ((i - r * M) << (lsh + 3));
     }
     // slots that no request has filled yet hold finite numbers (see the gather)
+    if constexpr (!DIRECT)
     for (int i = 16 * tid; i < (S.slots + kLayerSpare) << row_sh; i += 16 * T)
         *reinterpret_cast<float4*>(xs + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     // the columns of Z past K (K off a multiple of 32) stay zero
-    const int K = M << (lsh + 2);
     if (K < 32 * KS)
         for (int i = tid; i < 3 * PLANE / 4; i += T) sm[i] = 0;
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    lds_barrier();
-    request_rows(e_cur, e_next, 0);
+    if constexpr (!DIRECT) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        lds_barrier();
+        request_rows(e_cur, e_next, 0);
+    }
 
-    // ---- this wavefront's weights, split, once.  Block u has the columns f0 + U i + u, i < 16 (a lane's
-    // loads of a row are U columns side by side, and its results U float4): the A operand is W^T, lane
-    // (g, col) holds W[32 s + 8 g + j][f0 + U col + u], j < 8 (all eight inside K or none: K is a multiple
-    // of 16; where none the weights of k = j stand in, the columns of Z there are zero)
-    const int f0 = (tile * WV + wave) * (16 * U);
-    const int width = min(16 * U, S.F - f0);                  // columns of this wavefront (none: negative)
+    // (behind the first rows of X, which would wait for them: four channels at n_X = 64, 512 graphs 13.4 us
+    // instead of 12.5)
+    if constexpr (!DIRECT) request_weights();
+    // ---- the weights, split once
     bf16x8 wh[U][KS], wm[U][KS], wlo[U][KS];
     float bv[U][BQ];
     bool any_weight;
     {
-        const int c = width > 0 ? f0 + U * min(col, width / U - 1) : 0;
-        float raw[KS][8][U];
         uint32_t w_bits = 0;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int k = 32 * s + 8 * g;
-            const uint32_t off = ((uint32_t)(k < K ? k : 0) * (uint32_t)S.ld_w + (uint32_t)c) << 2;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const char* p = reinterpret_cast<const char*>(wgt + j * S.ld_w) + off;
-                if constexpr (U == 2) {
-                    const float2 t = *reinterpret_cast<const float2*>(p);
-                    raw[s][j][0] = t.x, raw[s][j][1] = t.y;
-                } else {
-                    raw[s][j][0] = *reinterpret_cast<const float*>(p);
-                }
-            }
-        }
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -2382,7 +2426,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int q = 0; q < BQ; ++q) {
-                const float t = bias[(int64_t)min(4 * q + g, M - 1) * S.bias_stride + c + (width > 0 ? u : 0)];
+                const float t = bias[(int64_t)min(4 * q + g, M - 1) * S.bias_stride + w_col + (width > 0 ? u : 0)];
                 bv[u][q] = 4 * q + g < M ? t : 0.f;
             }
     }
@@ -2456,7 +2500,29 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 sum[q] = 0.f;
                 zp[q] = lds + to[q] + 8 * l;
             }
-            if (e1 - ea <= top) {
+            if constexpr (DIRECT) {
+                const char* ep = csr + at.entries;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    int2 en[J];
+                    float4 xv[J];
+#pragma unroll
+                    for (int t = 0; t < J; ++t) en[t] = *reinterpret_cast<const int2*>(ep + ((p[q] + t) << 3));
+#pragma unroll
+                    for (int t = 0; t < J; ++t) xv[t] = *reinterpret_cast<const float4*>(x0 + en[t].x);
+#pragma unroll
+                    for (int t = 0; t < J; ++t) {
+                        const float vt = p[q] + t < pe[q] ? __int_as_float(en[t].y) : 0.f;
+                        Vec<4>::fma(acc[q], vt, xv[t]);
+                        sum[q] += vt;
+                    }
+                    for (int i = p[q] + J; i < pe[q]; ++i) {
+                        const int2 e = *reinterpret_cast<const int2*>(ep + (i << 3));
+                        Vec<4>::fma(acc[q], __int_as_float(e.y), *reinterpret_cast<const float4*>(x0 + e.x));
+                        sum[q] += __int_as_float(e.y);
+                    }
+                }
+            } else if (e1 - ea <= top) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
                     const char* xp = x0 + (p[q] << row_sh);
@@ -2529,7 +2595,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's requests for block b
         lds_barrier();                                     // everyone's; everyone is done with block b - 1
         store_pending();
-        const int e_then = b + 1 < b1 ? start_in(buf ^ 1, V) : 0;
+        const int e_then = !DIRECT && b + 1 < b1 ? start_in(buf ^ 1, V) : 0;
         // (virtual rows in flight per lane: what the registers beside the weights hold)
         constexpr int kRows = WV == 8 ? (KS == 8 ? 1 : 2) : (KS * U <= 6 ? 4 : 2);
         std::integral_constant<int, 1> one;
@@ -2552,8 +2618,8 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         if (__builtin_amdgcn_ballot_w64((bits << 1) != 0) != 0 && wl == 0) state[buf] = 1;
         lds_barrier();                                     // Z complete, slots and this csr buffer free
         place();
-        if (b + 1 < b1) request_rows(e_next, e_then, buf ^ 1);
-        if (b + 2 < b1) request_csr(b + 2, e_then, buf);
+        if (!DIRECT && b + 1 < b1) request_rows(e_next, e_then, buf ^ 1);
+        if (!DIRECT && b + 2 < b1) request_csr(b + 2, e_then, buf);
         if (tid == 0) state[buf ^ 1] = 0;                  // (read before the barrier at the top, written after)
         float most = 0.f, poison = 0.f;                    // largest magnitude; NaN if one is not finite
         {
@@ -2640,23 +2706,33 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         if (!((redo[(b - b0) >> 5] >> ((b - b0) & 31)) & 1)) continue;
         for (int rb = 0; rb < RB; ++rb)
         for (int u = 0; u < U; ++u) {
-            const int row = out_rows[(uint32_t)(R * b + 16 * rb + col)];
+            const int row = DIRECT ? *reinterpret_cast<const int*>(lds + at.csr + at.rows + 4 * col)
+                                   : out_rows[(uint32_t)(R * b + 16 * rb + col)];
             const int c0 = f0 + 4 * U * g + 4 * u;
             if (row < 0 || 4 * U * g >= width) continue;
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
             for (int ch = 0; ch < M; ++ch) {
                 const uint32_t vr = (uint32_t)b * V + (uint32_t)((16 * rb + col) * M + ch);
-                const int first = starts[vr], last = starts[vr + 1];
+                const int* st = reinterpret_cast<const int*>(lds + at.csr);
+                const int first = DIRECT ? st[col] : starts[vr], last = DIRECT ? st[col + 1] : starts[vr + 1];
                 if (last <= first) continue;
                 const float* bp = bias + ch * S.bias_stride + c0;
                 float rs = 0.f;
-                for (int i = first; i < last; ++i) rs += __int_as_float(entries[(uint32_t)i].y);
+                auto entry = [&](int i) {                // (row of X, value)
+                    if constexpr (DIRECT) {
+                        const int2 e = reinterpret_cast<const int2*>(lds + at.csr + at.entries)[i];
+                        return make_int2((int)it.in_row + (e.x >> row_sh), e.y);
+                    } else {
+                        return entries[(uint32_t)i];
+                    }
+                };
+                for (int i = first; i < last; ++i) rs += __int_as_float(entry(i).y);
                 float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
                 Vec<4>::fma(acc, rs, make_float4(bp[0], bp[1], bp[2], bp[3]));
                 for (int k = 0; k < 4 * L; ++k) {
                     float zv = 0.f;
                     for (int i = first; i < last; ++i) {
-                        const int2 en = entries[(uint32_t)i];
+                        const int2 en = entry(i);
                         zv = fmaf(__int_as_float(en.y), x[(uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + k], zv);
                     }
                     Vec<4>::fma(acc, zv, load_vec<4>(wgt + (int64_t)(ch * 4 * L + k) * S.ld_w + c0));
@@ -3076,7 +3152,7 @@ hipError_t kernel_resources(int which, int lds_bytes, int out[7])
             threads = kBuildThreadsLarge;
             break;
         case 7: fn = reinterpret_cast<const void*>(&bspmm_coo_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void*>(&bspmm_layer_kernel<8, 2, 1, 4>); break;
+        case 8: fn = reinterpret_cast<const void*>(&bspmm_layer_kernel<8, 2, 1, 4, false>); break;
         default: return hipErrorInvalidValue;
     }
     hipFuncAttributes a;
@@ -3171,14 +3247,17 @@ hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool
 }
 
 using LayerFn = void (*)(const int32_t*, const int2*, const int32_t*, const float*, const float*, const float*, float*,
-                         const LayerShape);
+                         const LayerDirect, const LayerShape);
 
-// (steps of 32 of K, 16-column blocks per wavefront, 16-row blocks per trip, wavefronts) -> kernel; null for
-// what it is not built for
+// (steps of 32 of K, 16-column blocks per wavefront, 16-row blocks per trip - 0: from an operation's own CSR
+// arrays -, wavefronts) -> kernel; null for what it is not built for
 static LayerFn layer_variant(int ks, int units, int rb, int waves)
 {
     static const struct { int ks, units, rb, waves; LayerFn fn; } table[] = {
-#define BSPMM_LAYER(K, U, R, W) {K, U, R, W, bspmm_layer_kernel<K, U, R, W>}
+#define BSPMM_LAYER(K, U, R, W) {K, U, R, W, bspmm_layer_kernel<K, U, R, W, false>}
+#define BSPMM_LAYER_DIRECT(K, U, W) {K, U, 0, W, bspmm_layer_kernel<K, U, 1, W, true>}
+        BSPMM_LAYER_DIRECT(1, 1, 4), BSPMM_LAYER_DIRECT(1, 2, 4), BSPMM_LAYER_DIRECT(2, 1, 4), BSPMM_LAYER_DIRECT(2, 1, 8),
+        BSPMM_LAYER_DIRECT(4, 1, 4), BSPMM_LAYER_DIRECT(4, 1, 8),
         BSPMM_LAYER(1, 1, 1, 4), BSPMM_LAYER(1, 1, 2, 4), BSPMM_LAYER(1, 1, 4, 4), BSPMM_LAYER(1, 2, 1, 4),
         BSPMM_LAYER(1, 2, 2, 4), BSPMM_LAYER(1, 2, 4, 4), BSPMM_LAYER(2, 1, 1, 4), BSPMM_LAYER(2, 1, 2, 4),
         BSPMM_LAYER(2, 2, 1, 4), BSPMM_LAYER(2, 2, 2, 4), BSPMM_LAYER(3, 1, 1, 4), BSPMM_LAYER(3, 1, 2, 4),
@@ -3189,6 +3268,7 @@ static LayerFn layer_variant(int ks, int units, int rb, int waves)
         BSPMM_LAYER(3, 1, 1, 8), BSPMM_LAYER(3, 1, 2, 8), BSPMM_LAYER(4, 1, 1, 8), BSPMM_LAYER(4, 1, 2, 8),
         BSPMM_LAYER(6, 1, 1, 8), BSPMM_LAYER(8, 1, 1, 8), BSPMM_LAYER(12, 1, 1, 8), BSPMM_LAYER(16, 1, 1, 8)};
 #undef BSPMM_LAYER
+#undef BSPMM_LAYER_DIRECT
     for (const auto& v : table)
         if (v.ks == ks && v.units == units && v.rb == rb && v.waves == waves) return v.fn;
     return nullptr;
@@ -3214,7 +3294,7 @@ hipError_t launch_bspmm_layer(const LayerParams& P, int ks, int units, int rb, i
     const LayerFn fn = layer_variant(ks, units, rb, waves);
     if (!fn) return hipErrorInvalidValue;
     return launch(fn, 8 * P.shape.ranges_per_xcd * P.shape.tiles, 64 * waves, lds_bytes, stream, P.starts,
-                  reinterpret_cast<const int2*>(P.entries), P.out_rows, P.x, P.w, P.bias, P.y, P.shape);
+                  reinterpret_cast<const int2*>(P.entries), P.out_rows, P.x, P.w, P.bias, P.y, P.direct, P.shape);
 }
 
 hipError_t launch_layer_rows(const LayerSet* sets, int count, const OpRecord* ops, const int32_t* rpt,

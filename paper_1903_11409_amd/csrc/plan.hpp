@@ -128,16 +128,34 @@ struct LayerSet {
 };
 static_assert(sizeof(LayerSet) == 64, "LayerSet must be 64 bytes");
 
-// Shape of one launch.  The grid is 8 * ranges_per_xcd * tiles workgroups; range i takes the blocks
-// blocks * i / (8 ranges_per_xcd) and up.
+// One block of a small layer of one channel: up to 16 rows of one operation, whose CSR arrays the kernel reads
+// itself.
+struct alignas(16) LayerItem {
+    uint32_t rpt_off, nz_off;       // of the first row's pointer, and of the operation's entries
+    uint32_t in_row, out_row;       // first row of X_i; the block's first row of Y
+    int32_t nrows, k, nnz;
+    int32_t reserved_;
+};
+static_assert(sizeof(LayerItem) == 32, "LayerItem must be 32 bytes");
+struct LayerDirect {
+    const LayerItem* items;
+    const int32_t* rpt;
+    const int32_t* colids;
+    const float* values;
+};
+
+// Shape of one launch.  The grid is 8 * ranges_per_xcd * tiles workgroups; the first `blocks_over` of the
+// 8 ranges_per_xcd ranges take blocks_each + 1 blocks, the others blocks_each.
 struct LayerShape {
     int64_t ld_x, ld_w, ld_y, bias_stride;
-    int32_t blocks, ranges_per_xcd, tiles;
+    int32_t blocks, blocks_each, blocks_over, ranges_per_xcd, tiles;
+    uint32_t inv_tiles;     // 2^32 / tiles, rounded up (more than one tile)
     int32_t F;
     int32_t channels;       // of this launch
     int32_t inv_channels;   // x * inv >> 16 == x / channels for a block's virtual rows x
     int32_t lane_shift;     // log2 of the float4 in a row of X
     int32_t slots;          // rows of X a workgroup holds in LDS, a multiple of 256 / n_X
+    int32_t entries;        // blocks from the operations' own arrays: the most entries of one
     int32_t accumulate;
 };
 struct LayerParams {
@@ -148,6 +166,7 @@ struct LayerParams {
     const float* w;
     const float* bias;
     float* y;
+    LayerDirect direct;
     LayerShape shape;
 };
 
@@ -316,14 +335,14 @@ BSPMM_HD constexpr int layer_z_row(int ks) { return 64 * ks + 16; }
 struct LayerLds {
     int slots, csr, csr_bytes, rows, entries, sums, state, total;    // (rows, entries: inside a buffer)
 };
-BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int slots, int nx)
+BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int slots, int entries, int nx)
 {
     LayerLds L;
     L.slots = 3 * 16 * rb * layer_z_row(ks);
     L.csr = L.slots + 4 * (slots + kLayerSpare) * nx;
     L.rows = 4 * round_up(16 * rb * channels + 1, 4);
     L.entries = L.rows + 64 * rb;
-    L.csr_bytes = L.entries + 8 * (slots + kLayerSpare);
+    L.csr_bytes = round_up(L.entries + 8 * (entries + kLayerSpare), 16);
     L.sums = L.csr + 2 * L.csr_bytes;
     L.state = L.sums + 64 * rb * channels;
     L.total = L.state + 16 + 4 * waves * kLayerRedoWords + 64 * rb * channels;

@@ -37,7 +37,8 @@ def _batch(graphs, F, chans):
 
 
 @pytest.mark.parametrize("graphs,chans,n_x,F", [
-    # one, two and four 16-row blocks a trip; K = channels n_x from one step of 32 to sixteen, off steps
+    # one channel: blocks of one operation from its own arrays (few graphs), and blocks across graphs; one, two
+    # and four 16-row blocks a trip; K = channels n_x from one step of 32 to sixteen, off steps
     # (16, 48, 80, 112), and past what one launch adds up (5 and 8 channels of 128)
     (700, 1, 16, 64), (700, 1, 32, 128), (90, 1, 64, 128), (700, 1, 64, 256), (90, 1, 128, 16), (90, 1, 128, 144),
     (90, 2, 16, 48), (500, 2, 32, 64), (90, 2, 64, 80), (90, 2, 128, 128), (90, 3, 16, 128), (90, 3, 32, 96),
@@ -72,9 +73,9 @@ def test_every_shape_of_a_workgroup(torch_cuda, oracle, graphs, chans, n_x, F): 
         assert np.array_equal(added[~owned], np.zeros_like(added[~owned]))
 
 
-@pytest.mark.parametrize("chans", [1, 3])
+@pytest.mark.parametrize("chans,cus", [(1, 1), (1, 0), (3, 1)])
 @pytest.mark.parametrize("n_x", [16, 64, 128])
-def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, n_x):  # noqa: F811
+def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, cus, n_x):  # noqa: F811
     """A star: one row names every node, all others name one; a block's entries do not fit its slots."""
     torch = torch_cuda
     rng = np.random.default_rng(3)
@@ -91,7 +92,7 @@ def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, n_x):  # n
     b = W.assemble("stars", F, ops, block, [n] * graphs, rng, n_graphs=graphs, c_block_of_op=block)
     X, Ws, biases = _layer(b, n_x, 2, channels=chans)
     Xd, Wd, bd = _device(torch, X, Ws, biases)
-    plan = _plan(b, n_x, chans, compute_units=4)
+    plan = _plan(b, n_x, chans, compute_units=cus)
     Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
     plan.run_gcn(Xd, Wd, bd, Yd)
     torch.cuda.synchronize()
@@ -100,15 +101,15 @@ def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, n_x):  # n
                   max(1e-5, chans * (n_x + n) * 2.0 ** -23), "stars")
 
 
-@pytest.mark.parametrize("chans,n_x,F", [(1, 64, 128), (4, 64, 128), (2, 16, 64)])
-def test_numbers_that_do_not_split(torch_cuda, oracle, chans, n_x, F):  # noqa: F811
+@pytest.mark.parametrize("chans,n_x,F,cus", [(1, 64, 128, 8), (1, 64, 128, 0), (4, 64, 128, 8), (2, 16, 64, 0)])
+def test_numbers_that_do_not_split(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
     """Infinities, NaN and numbers near the end of the range reach the rows that name them and no others;
     operands as small as 1e-36 keep their bits (the bf16 instructions take subnormal numbers as zero)."""
     torch = torch_cuda
     b = _batch(80, F, chans)
     X, Ws, biases = _layer(b, n_x, 5, channels=chans)
     owned = _owned(b.c_row_off, b.rows, b.n_c_rows)
-    plan = _plan(b, n_x, chans, compute_units=8)
+    plan = _plan(b, n_x, chans, compute_units=cus)
 
     def run(X, Ws, biases):
         Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
