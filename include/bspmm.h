@@ -171,7 +171,8 @@ typedef struct bspmm_options {
     uint32_t flags;            /* BSPMM_DRY_RUN | BSPMM_BUILD_TRANSPOSE | BSPMM_SPLIT_HUB_ROWS */
     int32_t  force_bin;        /* 0 = automatic; 1+b forces bin b for every op that fits it    */
     int32_t  lds_bytes;        /* LDS per workgroup; <= 160 KiB (all of a CU's).  0 = 20, 24
-                                  or 40 KiB by what bounds the launch,
+                                  or 40 KiB by what bounds the launch (summed
+                                  operations: 40 where 24 would leave sets as fused tasks),
                                   and 80 KiB, then 160 KiB, are tried before a batch whose
                                   summed operations need more is refused with ETOOBIG; 52 KiB
                                   (tiles twice as wide) for F >= 512 when the launch moves

@@ -1085,7 +1085,7 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
     }
     P.n_tasks = sc.grid;
     P.fused_stride = sc.fused_stride;
-    P.lds_floats = p->knobs.lds_words;
+    P.lds_floats = sc.budget_words;
     P.pad = p->knobs.pad;
     P.w = reinterpret_cast<const float*>(p->ws + p->lay.merged[d]);   // see LaunchParams
     P.bias = nullptr;
@@ -1096,7 +1096,7 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
                       (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     if (!sc.whole) {
-        const hipError_t e = launch_bspmm(P, sc.launch_grid, p->knobs.lds_words * 4, vec4, sc.has_slices,
+        const hipError_t e = launch_bspmm(P, sc.launch_grid, sc.budget_words * 4, vec4, sc.has_slices,
                                           p->knobs.hubs, !sc.merged_sets.empty(), s);
         return e == hipSuccess ? BSPMM_OK : hip_fail(e);
     }

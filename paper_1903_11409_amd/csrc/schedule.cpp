@@ -1023,7 +1023,7 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
     DirOps ext;
     std::vector<int> stand_in(outs.size(), -1);
     {
-        bool copied = false;
+        bool copied = false, narrow = false, apart = false;   // a set over the budget; one of scattered blocks
         for (int g = 0; g < outs.size(); ++g) {
             const int cnt = outs.count(g);
             if (cnt < 2 || cnt > kMaxMembers || kn.force_bin == BSPMM_BIN_GENERIC) continue;
@@ -1049,7 +1049,10 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
                 one_block = one_block && ops_in.in_off[mem[j]] == ops_in.in_off[mem[0]] + rows;
                 rows += ops_in.k[mem[j]];
             }
-            if (!one_block || nnz > INT32_MAX || rows > INT32_MAX) continue;
+            if (!one_block || nnz > INT32_MAX || rows > INT32_MAX) {
+                apart = true;
+                continue;
+            }
             if (!copied) {
                 ext = ops_in;
                 copied = true;
@@ -1070,9 +1073,34 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
                 stand_in[g] = v;
                 s.merged_sets.push_back(outs.members(g));
             } else {   // take it back: the set runs as a fused task (or does not fit at all)
+                narrow = true;
+                if (kn.whole_sets) break;
                 ext.m.pop_back(), ext.k.pop_back(), ext.nnz.pop_back(), ext.rpt_off.pop_back();
                 ext.nz_off.pop_back(), ext.in_off.pop_back(), ext.out_off.pop_back();
                 if (!ext.chan.empty()) ext.chan.pop_back();
+            }
+        }
+        if (narrow && kn.whole_sets) {
+            s.error = BSPMM_ETOOBIG;
+            return s;
+        }
+        // One set over the default budget takes the whole launch to the general kernel, its fused tasks with
+        // narrow tiles that each stage the set's merged CSR again.  Where 40 KiB hold every set the launch
+        // runs from compact items instead: us, four channels with dense blocks of their own, molecules: 300
+        // graphs at F = 64 4.9 -> 3.6, 512 at F = 128 9.7 -> 7.0, at F = 50 9.5 -> 5.1, 2048 at F = 64 14.7
+        // -> 12.7, at F = 128 24.6 -> 23.9; three channels, 1000 graphs at F = 128 11.9 -> 10.5.  Past 128 MB
+        // of dense input memory bounds either (2048 graphs of four channels at F = 256, 210 MB: 46.5 before,
+        // 48.5 at 40 KiB).
+        if (narrow && !apart && kn.front == 0 && kn.force_bin < 0 && !kn.lds_given && kn.lds_words == Knobs().lds_words) {
+            int64_t in_rows = 0;
+            for (int i = 0; i < ops_in.size(); ++i) in_rows += ops_in.k[i];
+            if (in_rows * F <= 32000000) {
+                Knobs wide = kn_in;
+                wide.lds_words = 40 * 1024 / 4;
+                wide.capacity_wgs = std::min(kn.capacity_wgs, 4 * kn.compute_units);
+                wide.whole_sets = true;
+                Schedule t = make_schedule(ops_in, F, wide);
+                if (!t.error) return t;
             }
         }
     }

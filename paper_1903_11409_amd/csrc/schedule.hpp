@@ -51,6 +51,7 @@ struct Knobs {
     bool wide_offsets = false;       // the transposed arrays outgrow the compact table's 32-bit offsets
     bool one_front_launch = false;   // whole layers: never the streaming launch
     bool lds_given = false;   // the caller fixed lds_words
+    bool whole_sets = false;  // a set of summed operations over the budget is an error (not a fused task)
     bool device_ok = false;   // planning may ask the current device (occupancy); false: dry runs
     bool need_both = false;   // planning: a transposed product that does not fit is an error too
 };

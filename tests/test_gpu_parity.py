@@ -582,6 +582,39 @@ def test_summed_groups_take_a_larger_lds_budget_when_they_need_it(torch_cuda, or
         assert e.value.code == K.ETOOBIG
 
 
+@pytest.mark.parametrize("F", [64, 63, 256])
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("mirrored", [False, True])
+def test_sums_too_long_for_the_default_budget_run_without_fused_tasks(torch_cuda, oracle, F, fused, mirrored):
+    """Four channels with dense blocks of their own, where 24 KiB leave the larger graph a fused task: at
+    40 KiB all sets are compact items, unless one needs more still (then the plan keeps 24 KiB and the fused
+    tasks).  The products are those of the fixed budget bit for bit, in either direction (mirrored: the
+    transposed product sums into a shared input)."""
+    from random_cases import _random_csr
+    torch = torch_cuda
+    rng = np.random.default_rng(7)
+    ops, blocks, sizes = [], [], []
+    nodes = [20, 120] + [200] * fused
+    for g, m in enumerate(nodes):
+        for _ in range(4):
+            ops.append((m, m, *_random_csr(rng, m, m, m, True)))
+            blocks.append(g)
+            sizes.append(m)
+    one, own = (blocks, list(range(len(ops))))
+    b = W.assemble("long_sums", F, ops, one if mirrored else own, nodes if mirrored else sizes, rng,
+                   with_dY=True, n_graphs=len(nodes), c_block_of_op=own if mirrored else one)
+    opts = K.make_options(flags=K.ACCUMULATE)
+    plan, got = _check_forward(torch, oracle, b, opts, what=f"long sums F={F}")
+    _check_transposed(torch, oracle, b, plan=plan, what=f"long sums F={F}")
+    fixed = K.Plan(b, options=K.make_options(flags=K.ACCUMULATE, lds_bytes=24576))
+    out = [_transposed(torch, b, plan=p)[1] if mirrored else _forward(torch, b, o)[1]
+           for p, o in ((plan, opts), (fixed, K.make_options(flags=K.ACCUMULATE, lds_bytes=24576)))]
+    assert np.array_equal(out[0], out[1])
+    side = 1 if mirrored else 0
+    assert fixed.info().fused_tasks[side] > 0
+    assert (plan.info().fused_tasks[side] > 0) == fused
+
+
 def test_large_batch_of_small_graphs(torch_cuda, oracle):
     """16384 molecule graphs in one launch (many times what the chip holds at once: the
     scheduler packs several small items into a workgroup), forward and transposed."""
