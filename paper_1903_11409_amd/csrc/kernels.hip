@@ -2181,8 +2181,8 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 // cycles of a SIMD's matrix pipe instead of 1024 with v_mfma_f32_16x16x4_f32.  Error against 64 bits,
 // products of uniform numbers, K = 64 / 256 / 512: 4.5e-8 / 8.1e-8 / 1.2e-7 of the result's norm; the fp32
 // instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The bf16 instructions take subnormal numbers as zero, and a split
-// number that is not finite is NaN: blocks with results that are not finite, or all below 2^-60, are made
-// once more without the split.
+// number that is not finite is NaN: blocks with results that are not finite, or all below 2^-60, or not
+// zero and below 2^-100, are made once more without the split.
 //   * W in REGISTERS for the whole launch, split once: wavefront w owns U blocks of 16 columns (12
 //     registers per 32 of K and block); no LDS for W.
 //   * A trip is one block.  While the matrix instructions of block b run, the rows of X that block b + 1
@@ -2622,6 +2622,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         if (!DIRECT && b + 2 < b1) request_csr(b + 2, e_then, buf);
         if (tid == 0) state[buf ^ 1] = 0;                  // (read before the barrier at the top, written after)
         float most = 0.f, poison = 0.f;                    // largest magnitude; NaN if one is not finite
+        uint32_t least = ~0u;                              // twice the smallest magnitude's bits, zeros apart, less one
         {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
@@ -2663,6 +2664,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                     for (int i = 0; i < 4; ++i) {
                         most = fmaxf(most, fabsf(r[u][i]));
                         poison = fmaf(r[u][i], 0.f, poison);
+                        least = min(least, (__float_as_uint(r[u][i]) << 1) - 1);
                     }
                 }
                 if constexpr (U == 2) {
@@ -2683,9 +2685,11 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
             }
         }
         // Split numbers that are not finite (or round to infinity) are NaN, and the bf16 instructions take
-        // subnormal numbers as zero: results that are not finite, or all tiny though neither Z nor the weights
-        // are all zero, are made again without the split, when there are no more blocks.
-        if (__builtin_amdgcn_ballot_w64(poison != poison) != 0 ||
+        // subnormal numbers as zero: results that are not finite, one below 2^-100 that is not zero (of operands
+        // whose third part, 2^-16 of them, may be subnormal), or all tiny though neither Z nor the weights are
+        // all zero, are made again without the split, when there are no more blocks.
+        constexpr uint32_t kTiny = 2 * ((127u - 100u) << 23) - 1;      // `least` of 2^-100
+        if (__builtin_amdgcn_ballot_w64(poison != poison || least < kTiny) != 0 ||
             (weights && __builtin_amdgcn_ballot_w64(most >= 0x1p-60f) == 0 &&
              __builtin_amdgcn_readfirstlane(state[buf]) != 0)) {
             if (wl == 0) redo[(b - b0) >> 5] |= 1u << ((b - b0) & 31);

@@ -159,6 +159,30 @@ def test_numbers_that_do_not_split(torch_cuda, oracle, chans, n_x, F, cus):  # n
         _assert_close(run(X2, Ws, none), ref2, T2, owned, tol, f"scale {scale}")
 
 
+@pytest.mark.parametrize("chans,n_x,F,cus", [(1, 64, 128, 8), (1, 64, 128, 0), (4, 64, 128, 8), (2, 16, 64, 0)])
+def test_tiny_graphs_beside_ordinary_ones(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
+    """Rows of 1e-36, or a column of weights, beside ordinary ones in the same block keep their bits too:
+    the bound is each element's own sum of magnitudes."""
+    torch = torch_cuda
+    b = _batch(80, F, chans)
+    X, Ws, _ = _layer(b, n_x, 6, channels=chans)
+    none = [np.zeros(F, dtype=np.float32)] * chans
+    X2, Ws2 = X.copy(), [w.copy() for w in Ws]
+    for i in range(0, b.batch, 3 * chans):
+        X2[int(b.b_row_off[i]):int(b.b_row_off[i]) + int(b.cols[i])] *= np.float32(1e-36)
+    for w in Ws2:
+        w[:, 5] *= np.float32(1e-36)
+    owned = _owned(b.c_row_off, b.rows, b.n_c_rows)
+    plan = _plan(b, n_x, chans, compute_units=cus)
+    for x, w in ((X2, Ws), (X, Ws2)):
+        Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
+        plan.run_gcn(*_device(torch, x, w, none), Yd)
+        torch.cuda.synchronize()
+        ref, T = _reference(oracle, b, x, w, none)
+        # (products of 1e-36 that come out subnormal: half of the smallest number each)
+        _assert_close(Yd.cpu().numpy(), ref, T + 1e-38, owned, max(1e-5, chans * (n_x + 10) * 2.0 ** -23), "tiny")
+
+
 def test_identity_weights_give_the_plain_product(torch_cuda):  # noqa: F811
     """W = I, bias = 0: a sum of three bf16 numbers is the fp32 number they were made from."""
     torch = torch_cuda
