@@ -403,10 +403,9 @@ def layer_whole(torch, K, W, n_x=64, channels=4, graphs=128):
            "one_fused_launch_per_channel_us": round(timed(run_per_channel), 3),
            "blas_addmm_per_channel_then_summed_product_us": round(timed(run_unfused), 3)}
     out["whole_layer_gflops"] = round(flops / out["whole_layer_us"] * 1e-3, 1)
-    # the layer's dense part, counted as the GEMMs X W[ch] a library runs, against the fp32
-    # matrix-core peak (157.3 TFLOP/s).  The streamed launch issues fewer flops than that: rows of
-    # X W[ch] that no entry of channel ch names are not made (the counter summary under profiles/
-    # has the matrix instructions issued).
+    # the layer's dense part, counted as the GEMMs X W[ch] a library runs, against the peak of the
+    # fp32 matrix instructions (157.3 TFLOP/s).  The gather-first launch does not use those: it adds
+    # six bf16 products per fp32 product (the counter summary under profiles/ has what it issues).
     out["dense_part_as_gemm_frac_of_fp32_mfma_peak"] = round(
         channels * 2 * b.n_b_rows * n_x * F / (out["whole_layer_us"] * 1e-6) / 157.3e12, 3)
     return out

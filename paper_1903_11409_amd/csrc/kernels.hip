@@ -12,8 +12,8 @@
 // bspmm_gcn_kernel  the fused front of the graph-convolution layer (Fig. 7): the dense tile is
 //                   made on the matrix cores from the layer input and the weights, for one
 //                   channel or for all channels of the layer, and gathered as above.
-// bspmm_layer_kernel  the same layer for large batches, gather first: resident workgroups with the
-//                   weights in registers make blocks of 16 output rows.
+// bspmm_layer_kernel  the same layer from a few dozen graphs on, gather first: workgroups with the
+//                   weights in registers make blocks of 16 to 64 output rows.
 // bspmm_coo_kernel  the direct product for COO / SparseTensor operands (Fig. 3, Fig. 5(a,b)).
 // build_sorted      stable CSR -> transposed CSR of every operation (counting sort by column),
 //                   and COO / SparseTensor -> CSR (the same sort by row).

@@ -49,7 +49,7 @@ struct Knobs {
     bool coo_direct = false;  // COO plans: run the direct kernel instead of converting to CSR
     int persistent_wgs = 0;   // > 0: launch only this many workgroups and let them stride
     bool wide_offsets = false;       // the transposed arrays outgrow the compact table's 32-bit offsets
-    bool one_front_launch = false;   // whole layers: never the streaming launch
+    bool one_front_launch = false;   // layers: never the gather-first launch
     bool lds_given = false;   // the caller fixed lds_words
     bool whole_sets = false;  // a set of summed operations over the budget is an error (not a fused task)
     bool device_ok = false;   // planning may ask the current device (occupancy); false: dry runs
