@@ -2194,7 +2194,9 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 //   * The matrix phase computes the transposed block (W^T Z^T): a lane then holds consecutive columns of
 //     an output row.  Results wait in registers and are stored at the top of the next trip, so that the
 //     wait there finds only requests and stores that are a whole trip old; stores write whole 128-byte
-//     lines (half lines: one channel, 2048 graphs, n_X = 64 20.5 us instead of 16.4).
+//     lines (half lines: one channel, 2048 graphs, n_X = 64 20.5 us instead of 16.4).  With U = 1 a wavefront
+//     writes half lines; non-temporal there too: cached stores would let the L2 join them but cost more (2048
+//     graphs, n_X = 64: four channels 28.6 -> 29.9, one channel 15.7 -> 16.8).
 // DIRECT: small layers of one channel, a block of 16 rows of one operation to a workgroup.  X_i, the
 // operation's entries and its row pointers are requested at once and no other launch is needed (128 graphs,
 // n_X = 64, F = 128: 5.3 us; with row pointers, entries and rows of X one after the other 5.7; from arrays
@@ -2203,7 +2205,7 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 // dense tiles graph by graph with fp32 matrix instructions: four channels at n_X = 64, 2048 graphs 43.4 ->
 // 29.6, 512 15.4 -> 12.5, 128 11.6 -> 6.8; n_X = 128, 2048 graphs 85.6 -> 57.3; eight channels at n_X = 64, 1024
 // graphs 39.7 -> 31.7; one channel at n_X = 64, 2048 graphs 21.2 -> 15.7, 512 10.0 -> 7.1.  Bound at four
-// channels (counters): the matrix pipe is busy for a third of the launch, LDS for half; a trip is a chain
+// channels (counters): the matrix pipe is busy for a quarter of the launch, waves wait for 44 %; a trip is a chain
 // of LDS round trips and two barriers that two workgroups per CU hide from each other only in part, and
 // splitting the weights is a fifth of the launch.
 // ---------------------------------------------------------------------------------------
