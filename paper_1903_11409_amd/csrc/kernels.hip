@@ -2182,7 +2182,8 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 // products of uniform numbers, K = 64 / 256 / 512: 4.5e-8 / 8.1e-8 / 1.2e-7 of the result's norm; the fp32
 // instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The bf16 instructions take subnormal numbers as zero, and a split
 // number that is not finite is NaN: blocks with results that are not finite, or all below 2^-60, or not
-// zero and below 2^-100, are made once more without the split.
+// zero and below 2^-100, are made once more without the split, and in the order A (X W + bias): A X can leave the
+// range of fp32 where the layer does not.
 //   * W in REGISTERS for the whole launch, split once: wavefront w owns U blocks of 16 columns (12
 //     registers per 32 of K and block); no LDS for W.
 //   * A trip is one block.  While the matrix instructions of block b run, the rows of X that block b + 1
@@ -2589,7 +2590,6 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         return bits;
     };
 
-    bool again = false;                                       // some blocks are to be made again
     for (int b = b0; b < b1; ++b) {
         const int buf = (b - b0) & 1;
         const char* csr = lds + at.csr + buf * at.csr_bytes;
@@ -2695,7 +2695,6 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
             (weights && __builtin_amdgcn_ballot_w64(most >= 0x1p-60f) == 0 &&
              __builtin_amdgcn_readfirstlane(state[buf]) != 0)) {
             if (wl == 0) redo[(b - b0) >> 5] |= 1u << ((b - b0) & 31);
-            again = true;
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -2705,26 +2704,40 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         e_next = e_then;
     }
     store_pending();
-    if (!again) return;
-    // The blocks that the split does not hold, without it: every lane computes its columns of its row one
-    // product after the other; a channel in which the row has no entries adds nothing.
-    for (int b = b0; b < b1; ++b) {
-        if (!((redo[(b - b0) >> 5] >> ((b - b0) & 31)) & 1)) continue;
-        for (int rb = 0; rb < RB; ++rb)
-        for (int u = 0; u < U; ++u) {
+    lds_barrier();                                            // everyone's marks
+    place();
+    const uint32_t* const marks = reinterpret_cast<const uint32_t*>(state + 4);
+    {
+        static_assert(WV * kLayerRedoWords <= 64, "a word to a lane");
+        if (__builtin_amdgcn_ballot_w64(marks[min(wl, WV * kLayerRedoWords - 1)] != 0) == 0) return;
+    }
+    // The blocks that the split or the order of the sums does not hold: A (X W + bias), as the layer is written,
+    // on fp32 matrix instructions.  One 16 x 16 product makes 16 columns of X W[ch] + bias[ch] for the p-th
+    // entry of each of 16 rows, so the lanes that hold a row's columns add them up in stored order; rows with
+    // fewer entries in the channel leave theirs out.  (k is taken in the order in which a lane's float4 of X
+    // has it.)  The wavefronts take the marked (block, columns) in turn, whoever marked them: one weight that is
+    // not finite marks every block, but of one wavefront.  us, four channels at n_X = 64, F = 128, 2048 molecules:
+    // nothing marked 32, one weight NaN 60, everything marked 204 (each lane on its own, one product after the
+    // other: 977 and 1600; by the wavefront that marked them 156 and 245; two entries at once 62 and 202).  Bound
+    // by the loads of X and W, a row of X and the channel's weights once more for every entry.
+    for (int turn = 0, word = 0; word < WV * kLayerRedoWords; ++word)
+    for (uint32_t left = __builtin_amdgcn_readfirstlane(marks[word]); left != 0; left &= left - 1, ++turn) {
+        if (turn % WV != wave) continue;
+        const int b = b0 + 32 * (word % kLayerRedoWords) + __builtin_ctz(left);
+        const int f1 = (tile * WV + word / kLayerRedoWords) * (16 * U), columns = min(16 * U, S.F - f1);
+        if (columns <= 0) continue;
+        for (int rb = 0; rb < RB; ++rb) {
             const int row = DIRECT ? *reinterpret_cast<const int*>(lds + at.csr + at.rows + 4 * col)
                                    : out_rows[(uint32_t)(R * b + 16 * rb + col)];
-            const int c0 = f0 + 4 * U * g + 4 * u;
-            if (row < 0 || 4 * U * g >= width) continue;
-            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            f32x4 sum[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
             for (int ch = 0; ch < M; ++ch) {
                 const uint32_t vr = (uint32_t)b * V + (uint32_t)((16 * rb + col) * M + ch);
                 const int* st = reinterpret_cast<const int*>(lds + at.csr);
-                const int first = DIRECT ? st[col] : starts[vr], last = DIRECT ? st[col + 1] : starts[vr + 1];
-                if (last <= first) continue;
-                const float* bp = bias + ch * S.bias_stride + c0;
-                float rs = 0.f;
-                auto entry = [&](int i) {                // (row of X, value)
+                const int first = DIRECT ? st[col] : starts[vr], count = (DIRECT ? st[col + 1] : starts[vr + 1]) - first;
+                if (__builtin_amdgcn_ballot_w64(count > 0) == 0) continue;
+                auto entry = [&](int i) {                     // (row of X, value)
                     if constexpr (DIRECT) {
                         const int2 e = reinterpret_cast<const int2*>(lds + at.csr + at.entries)[i];
                         return make_int2((int)it.in_row + (e.x >> row_sh), e.y);
@@ -2732,25 +2745,77 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                         return entries[(uint32_t)i];
                     }
                 };
-                for (int i = first; i < last; ++i) rs += __int_as_float(entry(i).y);
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                Vec<4>::fma(acc, rs, make_float4(bp[0], bp[1], bp[2], bp[3]));
-                for (int k = 0; k < 4 * L; ++k) {
-                    float zv = 0.f;
-                    for (int i = first; i < last; ++i) {
-                        const int2 en = entry(i);
-                        zv = fmaf(__int_as_float(en.y), x[(uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + k], zv);
-                    }
-                    Vec<4>::fma(acc, zv, load_vec<4>(wgt + (int64_t)(ch * 4 * L + k) * S.ld_w + c0));
+                int2 en = make_int2(0, 0);
+                if (count > 0) en = entry(first);
+                f32x4 bias4[U];
+                const float* wp[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c0 = f1 + (16 * u < columns ? 16 * u : 0);          // (past F: the first sixteen again)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bias4[u][i] = bias[ch * S.bias_stride + c0 + 4 * g + i];
+                    wp[u] = wgt + (int64_t)(ch * 4 * L + 4 * g) * S.ld_w + (c0 + col);
                 }
-                sum.x += acc.x, sum.y += acc.y, sum.z += acc.z, sum.w += acc.w;
+                for (int p = 0;; ++p) {
+                    const bool mine = p < count;
+                    const unsigned long long has = __builtin_amdgcn_ballot_w64(mine);
+                    if (has == 0) break;
+                    // (lanes without an entry: the row of X that another one names)
+                    const int other = __builtin_amdgcn_readlane(en.x, __builtin_ctzll(has));
+                    const float* xp = x + ((uint64_t)(uint32_t)(mine ? en.x : other) * (uint32_t)S.ld_x + 4 * g);
+                    const float v = __int_as_float(en.y);
+                    if (p + 1 < count) en = entry(first + p + 1);
+                    f32x4 acc[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) acc[u] = bias4[u];
+                    // (sixteen k a trip, the next ones requested before these are multiplied)
+                    float4 xn = load_vec<4>(xp);
+                    float wn[U][4];
+                    auto weights_at = [&](int k) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) wn[u][j] = wp[u][(uint32_t)(k + j) * (uint32_t)S.ld_w];
+                    };
+                    weights_at(0);
+#pragma unroll 1
+                    for (int k = 16; k <= 4 * L; k += 16) {
+                        const float4 xv = xn;
+                        float w[U][4];
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) w[u][j] = wn[u][j];
+                        if (k < 4 * L) {
+                            xn = load_vec<4>(xp + k);
+                            weights_at(k);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][0], xv.x, acc[u], 0, 0, 0);
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][1], xv.y, acc[u], 0, 0, 0);
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][2], xv.z, acc[u], 0, 0, 0);
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][3], xv.w, acc[u], 0, 0, 0);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (mine) sum[u][i] = fmaf(v, acc[u][i], sum[u][i]);
+                }
             }
-            float* yp = y + ((uint64_t)(uint32_t)row * (uint32_t)S.ld_y + (uint32_t)c0);
-            if (S.accumulate) {
-                const float4 old = *reinterpret_cast<const float4*>(yp);
-                sum.x += old.x, sum.y += old.y, sum.z += old.z, sum.w += old.w;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (row < 0 || 16 * u >= columns) continue;
+                float* yp = y + ((uint64_t)(uint32_t)row * (uint32_t)S.ld_y + (uint32_t)(f1 + 16 * u + 4 * g));
+                float4 v = make_float4(sum[u][0], sum[u][1], sum[u][2], sum[u][3]);
+                if (S.accumulate) {
+                    const float4 old = *reinterpret_cast<const float4*>(yp);
+                    v.x += old.x, v.y += old.y, v.z += old.z, v.w += old.w;
+                }
+                store_out<4>(yp, v);
             }
-            store_out<4>(yp, sum);
         }
     }
 }

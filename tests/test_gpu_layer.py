@@ -183,6 +183,63 @@ def test_tiny_graphs_beside_ordinary_ones(torch_cuda, oracle, chans, n_x, F, cus
         _assert_close(Yd.cpu().numpy(), ref, T + 1e-38, owned, max(1e-5, chans * (n_x + 10) * 2.0 ** -23), "tiny")
 
 
+def _scaled(b, n_x, chans, sx, sw, sa):
+    """Operands of the layer and their values of A, scaled; the bias as large as the products."""
+    X, Ws, biases = _layer(b, n_x, 11, channels=chans)
+    f = np.float32
+    return (dataclasses.replace(b, values=b.values * f(sa)), X * f(sx), [w * f(sw) for w in Ws],
+            [v * f(float(sx) * sw) for v in biases])
+
+
+# every way the blocks are made again: from an operation's own arrays or across graphs, one and two 16-column
+# blocks per wavefront, one to four 16-row blocks, four and eight wavefronts, two launches
+WAYS = [(1, 64, 128, 0), (1, 64, 128, 8), (1, 32, 128, 0), (1, 32, 128, 8), (1, 16, 64, 8), (2, 16, 64, 8),
+        (4, 64, 128, 8), (5, 32, 128, 8), (8, 64, 128, 8), (8, 128, 64, 8)]
+
+
+@pytest.mark.parametrize("chans,n_x,F,cus", WAYS)
+def test_sums_that_only_the_layers_own_order_holds(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
+    """A X is past the largest number, X W and A (X W + bias) are not; also onto what Y holds."""
+    torch = torch_cuda
+    b, X, Ws, biases = _scaled(_batch(80, F, chans), n_x, chans, 1e38, 1e-10, 1e3)
+    ref, T = _reference(oracle, b, X, Ws, biases)
+    owned = _owned(b.c_row_off, b.rows, b.n_c_rows)
+    tol = max(1e-5, chans * (n_x + 10) * 2.0 ** -23)
+    plan = _plan(b, n_x, chans, compute_units=cus)
+    ops = _device(torch, X, Ws, biases)
+    Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
+    plan.run_gcn(*ops, Yd)
+    onto = torch.full_like(Yd, 2.0 ** 100)
+    plan.run_gcn(*ops, onto, accumulate=True)
+    torch.cuda.synchronize()
+    _assert_close(Yd.cpu().numpy(), ref, T, owned, tol, "order of the sums")
+    added = onto.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(added - 2.0 ** 100 - ref)[owned] <= tol * (T + 2.0 ** 100)[owned])
+    assert np.all(added[~owned] == 2.0 ** 100)
+
+
+@pytest.mark.parametrize("chans,n_x,F,cus", WAYS)
+def test_one_weight_that_is_no_number(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
+    """It reaches its column in the rows with entries in its channel, and every block is made again."""
+    torch = torch_cuda
+    b = _batch(80, F, chans)
+    X, Ws, biases = _layer(b, n_x, 12, channels=chans)
+    ref, T = _reference(oracle, b, X, Ws, biases)
+    Ws[-1][n_x - 1, 37] = np.nan
+    plan = _plan(b, n_x, chans, compute_units=cus)
+    Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
+    plan.run_gcn(*_device(torch, X, Ws, biases), Yd)
+    torch.cuda.synchronize()
+    got = Yd.cpu().numpy()
+    last = _channel(b, chans - 1, chans)
+    touched = np.zeros((b.n_c_rows, F), dtype=bool)
+    for i in range(last.batch):
+        touched[int(last.c_row_off[i]):][:int(last.rows[i]), 37] |= np.diff(last.op_csr(i)[0]) > 0
+    assert np.all(np.isnan(got[touched]))
+    _assert_close(np.where(touched, ref, got), ref, T, _owned(b.c_row_off, b.rows, b.n_c_rows),
+                  max(1e-5, chans * (n_x + 10) * 2.0 ** -23), "beside a NaN")
+
+
 def test_identity_weights_give_the_plain_product(torch_cuda):  # noqa: F811
     """W = I, bias = 0: a sum of three bf16 numbers is the fp32 number they were made from."""
     torch = torch_cuda
