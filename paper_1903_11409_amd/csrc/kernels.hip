@@ -2180,10 +2180,13 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 // fp32, the large ones (hi x hi) in an accumulator of their own.  For 16 x 16 x 128 products that is 384
 // cycles of a SIMD's matrix pipe instead of 1024 with v_mfma_f32_16x16x4_f32.  Error against 64 bits,
 // products of uniform numbers, K = 64 / 256 / 512: 4.5e-8 / 8.1e-8 / 1.2e-7 of the result's norm; the fp32
-// instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The bf16 instructions take subnormal numbers as zero, and a split
-// number that is not finite is NaN: blocks with results that are not finite, or all below 2^-60, or not
-// zero and below 2^-100, are made once more without the split, and in the order A (X W + bias): A X can leave the
-// range of fp32 where the layer does not.
+// instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The parts of a small number would be subnormal, or below that: the
+// values of A are taken times 2^60, the weights and the bias times 2^24 and the results times 2^-84, all
+// exactly.  Every fp32 weight then has parts of 2^-125 and more, and what a Z below 2^-162 loses - less than
+// 2^-186 - comes, with 512 weights of at most 2^28, to no more than the smallest fp32 number.  A split number
+// that is not finite is NaN: blocks with results past 2^43 or not finite, and those of a wavefront with weights
+// past 2^28, are made once more without the split, and in the order A (X W + bias): A X can leave the range of
+// fp32 where the layer does not.
 //   * W in REGISTERS for the whole launch, split once: wavefront w owns U blocks of 16 columns (12
 //     registers per 32 of K and block); no LDS for W.
 //   * A trip is one block.  While the matrix instructions of block b run, the rows of X that block b + 1
@@ -2251,6 +2254,8 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t&
     lo = pair(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
 }
 
+constexpr float kValueScale = 0x1p60f, kWeightScale = 0x1p24f;     // (see above)
+
 template <int KS, int U, int RB, int WV, bool DIRECT>
 __global__ void __launch_bounds__(64 * WV, WV == 8 ? (KS > 8 ? 2 : 4) : (KS * U > 8 || (KS > 2 && U * RB > 2) ? 2 : 3))
 bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ entries,
@@ -2314,9 +2319,8 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     const LayerLds at = layer_lds(KS, RB, WV, M, S.slots, DIRECT ? S.entries : S.slots, 4 << lsh);
     char* const lds = reinterpret_cast<char*>(sm);
     char* const xs = lds + at.slots;            // the rows of X that the entries name
-    int* const state = reinterpret_cast<int*>(lds + at.state);   // Z has numbers other than zero (two buffers)
-    uint32_t* const redo = reinterpret_cast<uint32_t*>(state + 4 + wave * kLayerRedoWords);
-    int* const z_place = state + 4 + WV * kLayerRedoWords;        // of every virtual row, in bytes
+    uint32_t* const marks = reinterpret_cast<uint32_t*>(lds + at.marks);
+    int* const z_place = reinterpret_cast<int*>(marks + WV * kLayerRedoWords);     // of every virtual row, in bytes
     const int csr_lds = lds_address(lds + at.csr), xs_lds = csr_lds - (at.csr - at.slots);
 
     // what the gather of block b reads -> csr buffer; its first entry is number e0 (as many entries as there
@@ -2379,7 +2383,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         request_csr(b0, e_cur, 0);
         if (b0 + 1 < b1) request_csr(b0 + 1, e_next, 1);
     }
-    for (int i = tid; i < 4 + WV * kLayerRedoWords; i += T) state[i] = 0;
+    for (int i = tid; i < WV * kLayerRedoWords; i += T) marks[i] = 0;
     for (int i = tid; i < V; i += T) {
         const int r = (i * S.inv_channels) >> 16;
         z_place[i] = r * ZP + ((i - r * M) << (lsh + 3));
@@ -2403,9 +2407,9 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     // ---- the weights, split once
     bf16x8 wh[U][KS], wm[U][KS], wlo[U][KS];
     float bv[U][BQ];
-    bool any_weight;
+    bool huge;                                                // weights past 2^28 in this wavefront
     {
-        uint32_t w_bits = 0;
+        float most = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -2414,8 +2418,8 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 float v[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    v[j] = raw[s][j][u];
-                    w_bits |= __float_as_uint(v[j]);
+                    v[j] = kWeightScale * raw[s][j][u];
+                    most = fmaxf(most, fabsf(v[j]));
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], h[j], m[j], lo[j]);
@@ -2423,17 +2427,16 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 wm[u][s] = __builtin_bit_cast(bf16x8, make_uint4(m[0], m[1], m[2], m[3]));
                 wlo[u][s] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
             }
-        any_weight = (w_bits << 1) != 0;
+        huge = __builtin_amdgcn_ballot_w64(most > 0x1p28f * kWeightScale) != 0;
         // bias as the A operand of v_mfma_f32_16x16x4_f32 (k = channel), the row sums are B
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int q = 0; q < BQ; ++q) {
                 const float t = bias[(int64_t)min(4 * q + g, M - 1) * S.bias_stride + w_col + (width > 0 ? u : 0)];
-                bv[u][q] = 4 * q + g < M ? t : 0.f;
+                bv[u][q] = 4 * q + g < M ? kWeightScale * t : 0.f;
             }
     }
-    const bool weights = __builtin_amdgcn_ballot_w64(any_weight) != 0;     // one of them is not zero
     // The lane's place once more, here and in every trip of the loop below, so that nothing derived from it
     // is kept in registers from trip to trip: the weights leave none to spare.
     auto place = [&]() {
@@ -2471,7 +2474,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     // Z of one block, `Q` virtual rows per lane group at a time, `J` entries of each at once.  (Lane groups
     // past the last virtual row repeat it; entries past a row's end are taken with value zero - where
     // their slot holds an infinity the sum is NaN, and so is the result: see the check behind the matrix
-    // instructions.)  Returns the bits of the lane's numbers.
+    // instructions.)
     auto gather = [&](auto q_tag, auto j_tag, int e0, int e1, const char* csr) {
         constexpr int Q = decltype(q_tag)::value, J = decltype(j_tag)::value;
         static_assert(J <= kLayerSpare, "reads past the last entry");
@@ -2480,7 +2483,6 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         const char* x0 = xs + 16 * l;
         const char* v0 = csr + at.entries + 4;                // the entries' values
         float* const sums = reinterpret_cast<float*>(lds + at.sums);
-        uint32_t bits = 0;
         int p[Q], pe[Q], to[Q];
         auto fetch = [&](int r0) {
 #pragma unroll
@@ -2515,14 +2517,15 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                     for (int t = 0; t < J; ++t) xv[t] = *reinterpret_cast<const float4*>(x0 + en[t].x);
 #pragma unroll
                     for (int t = 0; t < J; ++t) {
-                        const float vt = p[q] + t < pe[q] ? __int_as_float(en[t].y) : 0.f;
+                        const float vt = p[q] + t < pe[q] ? kValueScale * __int_as_float(en[t].y) : 0.f;
                         Vec<4>::fma(acc[q], vt, xv[t]);
                         sum[q] += vt;
                     }
                     for (int i = p[q] + J; i < pe[q]; ++i) {
                         const int2 e = *reinterpret_cast<const int2*>(ep + (i << 3));
-                        Vec<4>::fma(acc[q], __int_as_float(e.y), *reinterpret_cast<const float4*>(x0 + e.x));
-                        sum[q] += __int_as_float(e.y);
+                        const float vt = kValueScale * __int_as_float(e.y);
+                        Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + e.x));
+                        sum[q] += vt;
                     }
                 }
             } else if (e1 - ea <= top) {
@@ -2540,7 +2543,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                     }
 #pragma unroll
                     for (int t = 0; t < J; ++t) {
-                        const float vt = p[q] + t < pe[q] ? v[t] : 0.f;
+                        const float vt = p[q] + t < pe[q] ? kValueScale * v[t] : 0.f;
                         Vec<4>::fma(acc[q], vt, xv[t]);
                         sum[q] += vt;
                     }
@@ -2548,7 +2551,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 if (__any(longest > J))
                     for (int q = 0; q < Q; ++q)
                         for (int i = p[q] + J; i < pe[q]; ++i) {
-                            const float vt = *reinterpret_cast<const float*>(v0 + (i << 3));
+                            const float vt = kValueScale * *reinterpret_cast<const float*>(v0 + (i << 3));
                             Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
                             sum[q] += vt;
                         }
@@ -2558,15 +2561,15 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 const uint32_t c4 = 4 * (here & (L - 1));
                 for (int q = 0; q < Q; ++q) {
                     for (int i = p[q]; i < min(pe[q], top); ++i) {
-                        const float vt = *reinterpret_cast<const float*>(v0 + (i << 3));
+                        const float vt = kValueScale * *reinterpret_cast<const float*>(v0 + (i << 3));
                         Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
                         sum[q] += vt;
                     }
                     for (int i = max(p[q], top); i < pe[q]; ++i) {
                         const int2 en = entries[(uint32_t)(ea + i)];
-                        Vec<4>::fma(acc[q], __int_as_float(en.y),
-                                    load_vec<4>(x + ((uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + c4)));
-                        sum[q] += __int_as_float(en.y);
+                        const float vt = kValueScale * __int_as_float(en.y);
+                        Vec<4>::fma(acc[q], vt, load_vec<4>(x + ((uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + c4)));
+                        sum[q] += vt;
                     }
                 }
             }
@@ -2582,12 +2585,9 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 *reinterpret_cast<uint2*>(zp[q]) = h;
                 *reinterpret_cast<uint2*>(zp[q] + PLANE) = m;
                 *reinterpret_cast<uint2*>(zp[q] + 2 * PLANE) = lo;
-                bits |= __float_as_uint(acc[q].x) | __float_as_uint(acc[q].y) | __float_as_uint(acc[q].z) |
-                        __float_as_uint(acc[q].w);
             }
             if (Q == 1 && r0 + Q * G < V) fetch(r0 + Q * G);
         }
-        return bits;
     };
 
     for (int b = b0; b < b1; ++b) {
@@ -2602,29 +2602,25 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         constexpr int kRows = WV == 8 ? (KS == 8 ? 1 : 2) : (KS * U <= 6 ? 4 : 2);
         std::integral_constant<int, 1> one;
         std::integral_constant<int, 2> two;
-        uint32_t bits;
         if (V <= G || kRows == 1)
-            bits = gather(one, std::integral_constant<int, kRows == 1 ? 2 : 4>(), e_cur, e_next, csr);
+            gather(one, std::integral_constant<int, kRows == 1 ? 2 : 4>(), e_cur, e_next, csr);
         else if (M == 1)
-            bits = gather(two, std::integral_constant<int, kRows == 4 ? 4 : 2>(), e_cur, e_next, csr);
+            gather(two, std::integral_constant<int, kRows == 4 ? 4 : 2>(), e_cur, e_next, csr);
         else if (V <= 2 * G)
-            bits = gather(two, two, e_cur, e_next, csr);
+            gather(two, two, e_cur, e_next, csr);
         else
-            bits = gather(std::integral_constant<int, kRows>(), two, e_cur, e_next, csr);
+            gather(std::integral_constant<int, kRows>(), two, e_cur, e_next, csr);
         // this lane's output rows
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 pend_row[rb][u] = *reinterpret_cast<const int*>(csr + at.rows + 4 * (16 * rb + (U == 2 ? 8 * u + (col & 7) : col)));
-        if (__builtin_amdgcn_ballot_w64((bits << 1) != 0) != 0 && wl == 0) state[buf] = 1;
         lds_barrier();                                     // Z complete, slots and this csr buffer free
         place();
         if (!DIRECT && b + 1 < b1) request_rows(e_next, e_then, buf ^ 1);
         if (!DIRECT && b + 2 < b1) request_csr(b + 2, e_then, buf);
-        if (tid == 0) state[buf ^ 1] = 0;                  // (read before the barrier at the top, written after)
-        float most = 0.f, poison = 0.f;                    // largest magnitude; NaN if one is not finite
-        uint32_t least = ~0u;                              // twice the smallest magnitude's bits, zeros apart, less one
+        float poison = 0.f;                                // NaN if one is not finite
         {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
@@ -2664,9 +2660,8 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                     r[u] = big[u] + small[u];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        most = fmaxf(most, fabsf(r[u][i]));
                         poison = fmaf(r[u][i], 0.f, poison);
-                        least = min(least, (__float_as_uint(r[u][i]) << 1) - 1);
+                        r[u][i] *= 1.f / (kValueScale * kWeightScale);
                     }
                 }
                 if constexpr (U == 2) {
@@ -2686,15 +2681,10 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 }
             }
         }
-        // Split numbers that are not finite (or round to infinity) are NaN, and the bf16 instructions take
-        // subnormal numbers as zero: results that are not finite, one below 2^-100 that is not zero (of operands
-        // whose third part, 2^-16 of them, may be subnormal), or all tiny though neither Z nor the weights are
-        // all zero, are made again without the split, when there are no more blocks.
-        constexpr uint32_t kTiny = 2 * ((127u - 100u) << 23) - 1;      // `least` of 2^-100
-        if (__builtin_amdgcn_ballot_w64(poison != poison || least < kTiny) != 0 ||
-            (weights && __builtin_amdgcn_ballot_w64(most >= 0x1p-60f) == 0 &&
-             __builtin_amdgcn_readfirstlane(state[buf]) != 0)) {
-            if (wl == 0) redo[(b - b0) >> 5] |= 1u << ((b - b0) & 31);
+        // Split numbers that are not finite (or round to infinity) are NaN: results that are not finite are made
+        // again without the split, when there are no more blocks.
+        if (huge || __builtin_amdgcn_ballot_w64(poison != poison) != 0) {
+            if (wl == 0) marks[wave * kLayerRedoWords + ((b - b0) >> 5)] |= 1u << ((b - b0) & 31);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -2706,7 +2696,6 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     store_pending();
     lds_barrier();                                            // everyone's marks
     place();
-    const uint32_t* const marks = reinterpret_cast<const uint32_t*>(state + 4);
     {
         static_assert(WV * kLayerRedoWords <= 64, "a word to a lane");
         if (__builtin_amdgcn_ballot_w64(marks[min(wl, WV * kLayerRedoWords - 1)] != 0) == 0) return;

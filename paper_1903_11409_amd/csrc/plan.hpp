@@ -325,15 +325,14 @@ struct alignas(8) SetRecord {
 
 // LDS of bspmm_layer_kernel, in bytes: three planes of 16 rb rows of Z; the slots and a few to spare; two
 // buffers with what a block's gather reads (starts, output rows, entries); the sums of the virtual rows'
-// values; four words of state, for
-// every wavefront a bit for every block of a range that has to be made again without the split, and the
-// virtual rows' places in Z.
+// values; for every wavefront a bit for every block of a range that has to be made again without the split;
+// and the virtual rows' places in Z.
 constexpr int kLayerRedoWords = 8;
 constexpr int kLayerRangeBlocks = 32 * kLayerRedoWords;     // blocks of a range, at most
 constexpr int kLayerSpare = 4;
 BSPMM_HD constexpr int layer_z_row(int ks) { return 64 * ks + 16; }
 struct LayerLds {
-    int slots, csr, csr_bytes, rows, entries, sums, state, total;    // (rows, entries: inside a buffer)
+    int slots, csr, csr_bytes, rows, entries, sums, marks, total;    // (rows, entries: inside a buffer)
 };
 BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int slots, int entries, int nx)
 {
@@ -344,8 +343,8 @@ BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int 
     L.entries = L.rows + 64 * rb;
     L.csr_bytes = round_up(L.entries + 8 * (entries + kLayerSpare), 16);
     L.sums = L.csr + 2 * L.csr_bytes;
-    L.state = L.sums + 64 * rb * channels;
-    L.total = L.state + 16 + 4 * waves * kLayerRedoWords + 64 * rb * channels;
+    L.marks = L.sums + 64 * rb * channels;
+    L.total = L.marks + 4 * waves * kLayerRedoWords + 64 * rb * channels;
     return L;
 }
 

@@ -1,7 +1,7 @@
 """The gather-first layer kernel (bspmm_layer_kernel) at the sizes where it can go wrong: last blocks that
 are not full, columns that no tile divides, every number of channels, sums over more channels than one
 launch holds, rows with more entries than a block has slots, numbers that the three-way bf16 split does not
-hold, strided operands, replays of a captured run.  Tolerances as in test_gpu_gcn."""
+hold and those it holds only scaled, strided operands, replays of a captured run.  Tolerances as in test_gpu_gcn."""
 import dataclasses
 
 import numpy as np
@@ -104,7 +104,7 @@ def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, cus, n_x):
 @pytest.mark.parametrize("chans,n_x,F,cus", [(1, 64, 128, 8), (1, 64, 128, 0), (4, 64, 128, 8), (2, 16, 64, 0)])
 def test_numbers_that_do_not_split(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
     """Infinities, NaN and numbers near the end of the range reach the rows that name them and no others;
-    operands as small as 1e-36 keep their bits (the bf16 instructions take subnormal numbers as zero)."""
+    operands as small as 1e-36 keep their bits."""
     torch = torch_cuda
     b = _batch(80, F, chans)
     X, Ws, biases = _layer(b, n_x, 5, channels=chans)
@@ -216,6 +216,45 @@ def test_sums_that_only_the_layers_own_order_holds(torch_cuda, oracle, chans, n_
     added = onto.cpu().numpy().astype(np.float64)
     assert np.all(np.abs(added - 2.0 ** 100 - ref)[owned] <= tol * (T + 2.0 ** 100)[owned])
     assert np.all(added[~owned] == 2.0 ** 100)
+
+
+# X, W, A: small operands beside large ones, the result ordinary or tiny, inside the weights that the split
+# takes (2^28) and past them, subnormal ones, and A X below the smallest number
+SCALES = [(1e-36, 1e20, 1), (1e20, 1e-36, 1), (1e-37, 1e30, 1), (1e30, 1e-37, 1), (1e-36, 1e8, 1), (1e8, 1e-36, 1),
+          (1e-37, 1, 1), (1, 1e-37, 1), (1e-41, 1e8, 1e-2), (1e8, 1e-41, 1e-2), (1e-30, 1e30, 1e-30),
+          (1e-30, 1e8, 1e-12), (1, 1e8, 1e-36)]
+
+
+@pytest.mark.parametrize("chans,n_x,F,cus", WAYS)
+def test_small_operands_beside_large_ones(torch_cuda, oracle, chans, n_x, F, cus):  # noqa: F811
+    """No bits are lost at the lower end of the range whatever the other operand is, alone or in a block of
+    ordinary rows, and onto what Y holds: the bound is each element's own sum of magnitudes, and half of the
+    smallest number for every product that comes out subnormal."""
+    torch = torch_cuda
+    batch = _batch(80, F, chans)
+    owned = _owned(batch.c_row_off, batch.rows, batch.n_c_rows)
+    tol = max(1e-5, chans * (n_x + 10) * 2.0 ** -23)
+    for sx, sw, sa in SCALES:
+        for beside in (False, True):
+            b, X, Ws, biases = _scaled(batch, n_x, chans, sx, sw, sa)
+            if beside:                     # every third graph; the others are ordinary
+                ordinary = np.ones(b.n_b_rows, dtype=bool)
+                for i in range(0, b.batch, 3 * chans):
+                    ordinary[int(b.b_row_off[i]):int(b.b_row_off[i]) + int(b.cols[i])] = False
+                X[ordinary] /= np.float32(sx)
+                biases = [np.zeros_like(v) for v in biases]
+            ref, T = _reference(oracle, b, X, Ws, biases)
+            plan = _plan(b, n_x, chans, compute_units=cus)
+            ops = _device(torch, X, Ws, biases)
+            Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
+            plan.run_gcn(*ops, Yd)
+            onto = torch.zeros_like(Yd)
+            plan.run_gcn(*ops, onto, accumulate=True)
+            torch.cuda.synchronize()
+            floor = 2.0 ** -149 * (chans * n_x + 16) / tol
+            for got in (Yd, onto):
+                _assert_close(got.cpu().numpy(), ref, T + floor, owned if got is Yd else np.ones_like(owned), tol,
+                              f"X {sx} W {sw} A {sa}")
 
 
 @pytest.mark.parametrize("chans,n_x,F,cus", WAYS)
