@@ -328,10 +328,41 @@ void make_stream_plan(bspmm_plan& p)
         st.many = st.many && x_rows * nx * 256 >= (int64_t)700000 * kn.compute_units;
     }
 
-    // the graphs in the order of their layer input; those of more than kLayerDegree entries per row, whose
-    // blocks would name more rows of X than a workgroup holds, keep their items of the one-launch schedule
-    constexpr int kLayerDegree = 6;
+    // Fewer graphs: one block to a workgroup, where there are enough to matter.  Blocks of one channel are rows
+    // of one operation then, whose CSR arrays the kernel reads as they are: the first run of a plan needs no
+    // other launch (whole layers merge their channels' CSR arrays for either kernel).
+    const bool direct = single && !st.many;
+
+    // The graphs in the order of their layer input; those with more entries per row than `degree` keep their
+    // items of the one-launch schedule.  What a row costs here grows with its entries, n_X floats each, and on the
+    // one-launch kernel with the dense tile, F floats for every row and channel, and less with the entries.  us,
+    // F = 128, molecules of so many entries per row (all channels), this kernel / one-launch:
+    //   four channels, n_X = 64, 2048 graphs: 3 32 / 120, 8 37 / 125, 24 52 / 143, 64 91 / 260; 128 graphs: 8
+    //   8 / 15, 24 11 / 18, 64 14 / 36;   eight channels, 1024 graphs: 8 40 / 158, 64 63 / 214
+    //   one channel, 2048 graphs: 8 24 / 34, 16 32 / 40, 24 44 / 66, 48 72 / 91; 600 graphs: 16 13 / 16, 24 21 / 18,
+    //   48 31 / 29;   n_X = 128, 1024 graphs: 24 31 / 46, 48 44 / 56;   n_X = 16, F = 64, 2048 graphs: 8 11 / 13, 16
+    //   17.7 / 17.2, 32 24 / 26, 48 36 / 42, 64 78 / 51
+    // so that a batch of one kind stays here.  A few graphs of many entries in a batch of few make long trips:
+    // past 32 and twice the average they are left out (every 40th graph of 24 / 48 entries per row, the others
+    // 2.2: one channel 21 / 40 here, 21 / 24 with them left out; four channels 38 / 46, 45 / 43).
+    // One channel: a graph that fills nearly two ranges of a workgroup, of 128 rows and more each, and has a
+    // third more entries per row than the average, is left out too.  Its ranges end last, but not by as much as
+    // the other launch takes (2048 skewed graphs at n_X = 64, F = 64, eleven of them left out: 35 us -> 52; the
+    // streaming kernel before this one, which left 149 out, 60): it is test_single_channel_streamed that
+    // wants a graph left out of a batch of that kind.
+    // One operation to a block (`direct`): n_X = 16 up to six (F = 16, 200 graphs of 4 / 6 / 8: 4.1 / 4.4 / 4.7,
+    // one-launch 4.2 / 4.3 / 4.5), else eight (n_X = 128, F = 64, 48 graphs of 6 / 8 / 12: 5.6 / 6.2 / 6.8, one-launch
+    // 5.9 / 6.1 / 6.3; n_X = 64, F = 128, 200 graphs: 5.6 / 6.0 / 6.4, one-launch 7.5 / 7.7 / 9.0).
     constexpr int64_t kLimit = (int64_t)1 << 31;
+    int64_t all_rows = 0, all_entries = 0;
+    for (size_t g = 0; g < n_graphs; ++g) {
+        if (o.m[op_of(g, 0)] <= 0) continue;
+        all_rows += o.m[op_of(g, 0)];
+        for (int c = 0; c < channels; ++c) all_entries += o.nnz[op_of(g, c)];
+    }
+    const double mean = (double)all_entries / (double)std::max<int64_t>(all_rows, 1);
+    const double degree = direct ? (nx == 16 ? 6.0 : 8.0) : std::max(32.0, 2 * mean);
+    const double range = (double)all_rows * ((F + 127) / 128) / (3.0 * kn.compute_units);
     std::vector<int> mine;
     std::vector<char> streamed(n_graphs, 0);
     int64_t rows = 0, entries = 0;
@@ -340,9 +371,9 @@ void make_stream_plan(bspmm_plan& p)
         int64_t nnz = 0;
         for (int c = 0; c < channels; ++c) nnz += o.nnz[op_of(g, c)];
         if (o.m[op0] <= 0) continue;
-        if (nnz > (int64_t)kLayerDegree * o.m[op0] || o.in_off[op0] + o.k[op0] >= kLimit ||
-            o.out_off[op0] + o.m[op0] >= kLimit) {
-            if (!st.many) return;
+        const double most = single && range >= 128 && o.m[op0] >= 1.75 * range ? std::max(8.0, mean * 4 / 3) : degree;
+        if ((double)nnz > std::min(most, degree) * o.m[op0] || o.in_off[op0] + o.k[op0] >= kLimit || o.out_off[op0] + o.m[op0] >= kLimit) {
+            if (direct) return;
             continue;
         }
         mine.push_back((int)g);
@@ -351,14 +382,10 @@ void make_stream_plan(bspmm_plan& p)
         entries += nnz;
     }
     if (mine.empty() || (rows + 64) * channels >= kLimit || entries >= kLimit) return;
-    // Fewer graphs: one block to a workgroup, where there are enough to matter.  Blocks of one channel are rows
-    // of one operation then, whose CSR arrays the kernel reads as they are: the first run of a plan needs no
-    // other launch (whole layers merge their channels' CSR arrays for either kernel).  us of a run, F = 128, this
-    // kernel / one-launch kernel: one channel at n_X = 64, 32 graphs 5.4 / 5.6, 64 graphs 4.6 / 6.1, 128 graphs 5.3 /
-    // 6.6, 300 graphs 6.6 / 8.5; at n_X = 16, F = 64, 1000 graphs 7.2 / 7.5; four channels at n_X = 64, 24 graphs
+    // Too few to matter.  us of a run, F = 128, this kernel / one-launch kernel: one channel at n_X = 64, 32
+    // graphs 5.4 / 5.6, 64 graphs 4.6 / 6.1, 128 graphs 5.3 / 6.6, 300 graphs 6.6 / 8.5; at n_X = 16, F = 64, 1000 graphs 7.2 / 7.5; four channels at n_X = 64, 24 graphs
     // 6.4 / 6.6, 128 graphs 6.9 / 14.2; K = channels n_X past 256: 24 graphs of four channels at n_X = 128 9.9 /
     // 8.5, 64 graphs 9.9 / 14.0.
-    const bool direct = single && !st.many;
     if (!st.many && (rows + 15) / 16 * (single || channels * nx > 256 ? 4 : 8) < kn.compute_units) return;
     int most_k = 0, most_nnz = 0;                        // of an operation: it has to fit on chip
     if (direct) {
@@ -396,10 +423,12 @@ void make_stream_plan(bspmm_plan& p)
     // to 64 where the rows of X that they name (a quarter more than on average) then have slots, by the
     // number of trips times what a trip costs: a fixed part and the passes of its gather (one channel at
     // n_X = 16, F = 64, 2048 molecules, 16 / 32 / 64 rows: 11.2 / 9.4 / 9.2 us; at n_X = 64, 1200: 9.3 / 9.8).
+    // (no more than 1024 slots: 256 had blocks of four entries per row at n_X = 16 past them, 9.9 -> 8.9 us)
     const int budget = kn.lds_given ? kn.lds_words * 4 : 53248;
+    constexpr int kSlots = 1024;
     auto slots_in = [&](int rb, int ch, int bytes, int want) {
         const int unit = 256 / nx;             // rows that a wavefront's request brings
-        int n = round_up(std::min(want, 256), unit);
+        int n = round_up(std::min(want, kSlots), unit);
         while (n > 0 && layer_lds(steps_of(ch), rb, waves, ch, n, n, nx).total > bytes) n -= unit;
         return n;
     };
@@ -411,7 +440,7 @@ void make_stream_plan(bspmm_plan& p)
         double best = 0;
         for (int r = 1; r <= (direct ? 1 : 4); r *= 2) {
             if (!layer_supported(steps_of(most), units, r, waves) || 16 * r * most > 240 ||
-                (r > 1 && slots_in(r, most, budget, wanted(r)) < std::min(wanted(r), 256)))
+                (r > 1 && slots_in(r, most, budget, wanted(r)) < std::min(wanted(r), kSlots)))
                 continue;
             const int64_t round = (int64_t)16 * r * 3 * kn.compute_units;
             const int64_t trips = (rows * tiles + round - 1) / round;
@@ -458,8 +487,17 @@ void make_stream_plan(bspmm_plan& p)
             return;
         }
         part.slots = slots_in(rb, part.channels, budget, std::max(wanted(rb), 64));
-        if (direct) part.slots = round_up(std::max(most_k, 1), 256 / nx);
-        else if (!kn.lds_given && part.slots < 40) part.slots = slots_in(rb, part.channels, 81920, std::max(wanted(rb), 64));
+        if (direct) {
+            part.slots = round_up(std::max(most_k, 1), 256 / nx);
+        } else if (!kn.lds_given) {
+            // (half of a CU's LDS too, past six entries per row, where it holds the rows of X of a block, a tenth
+            // more than on average, and a third does not: us, one channel, F = 128, third / half: n_X = 64, 2048 molecules of 8 / 10 / 12 / 16
+            // entries per row 23.7 / 23.6, 27.3 / 25.8, 32.2 / 27.4, 36.5 / 32.3, and 24, which neither holds, 44.2 /
+            // 48.6; n_X = 32, 1024 of 16 / 24 / 48: 13.8 / 13.8, 22.0 / 19.0, 30.2 / 39.7)
+            const int block = (int)(17.6 * rb * per_row * part.channels / channels);
+            const int half = slots_in(rb, part.channels, 81920, std::max(wanted(rb), 64));
+            if (part.slots < 40 || (per_row > 6 && part.slots < block && half >= block)) part.slots = half;
+        }
         if (part.slots < 16 && !direct) {
             st = bspmm_plan::Stream();
             return;
@@ -473,7 +511,10 @@ void make_stream_plan(bspmm_plan& p)
         st.direct_entries = most_nnz;
         int per_cu = kn.device_ok ? layer_workgroups_per_cu(part.ks, units, direct ? 0 : rb, waves, part.lds_bytes) : 0;
         if (per_cu <= 0) per_cu = 2;
-        per_cu = std::min(per_cu, 3);
+        // (eight wavefronts with two 16-row blocks: no third workgroup, whose weights cost more than its trips
+        // save: us, one channel, n_X = 64, F = 128, two / three per CU: 512 skewed graphs 10.9 / 13.5, 1299 molecules,
+        // accumulating 23.5 / 30.0, 2048 molecules 15.6 / 14.2)
+        per_cu = std::min(per_cu, waves == 8 && rb == 2 ? 2 : 3);
         const int64_t most_ranges = std::max<int64_t>(8, (int64_t)per_cu * kn.compute_units / st.tiles);
         const int64_t ranges = direct || blocks <= most_ranges ? blocks + 7 : most_ranges;
         part.ranges_per_xcd = (int)std::max<int64_t>(ranges / 8, (blocks / kLayerRangeBlocks + 8) / 8);

@@ -2474,12 +2474,12 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     // Z of one block, `Q` virtual rows per lane group at a time, `J` entries of each at once.  (Lane groups
     // past the last virtual row repeat it; entries past a row's end are taken with value zero - where
     // their slot holds an infinity the sum is NaN, and so is the result: see the check behind the matrix
-    // instructions.)
-    auto gather = [&](auto q_tag, auto j_tag, int e0, int e1, const char* csr) {
+    // instructions.)  J = 0: blocks of more entries than slots.
+    auto gather = [&](auto q_tag, auto j_tag, int e0, const char* csr) {
         constexpr int Q = decltype(q_tag)::value, J = decltype(j_tag)::value;
         static_assert(J <= kLayerSpare, "reads past the last entry");
         const int* st = reinterpret_cast<const int*>(csr);
-        const int ea = e0 & ~1, top = S.slots;                // the entry of slot 0
+        const int ea = e0 & ~1;                               // the entry of slot 0
         const char* x0 = xs + 16 * l;
         const char* v0 = csr + at.entries + 4;                // the entries' values
         float* const sums = reinterpret_cast<float*>(lds + at.sums);
@@ -2528,7 +2528,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                         sum[q] += vt;
                     }
                 }
-            } else if (e1 - ea <= top) {
+            } else if constexpr (J > 0) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
                     const char* xp = x0 + (p[q] << row_sh);
@@ -2555,22 +2555,42 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                             Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
                             sum[q] += vt;
                         }
-            } else {         // more entries than slots: the others straight from memory
-                int here = tid;                              // (see place)
-                asm volatile("" : "+v"(here));
-                const uint32_t c4 = 4 * (here & (L - 1));
-                for (int q = 0; q < Q; ++q) {
-                    for (int i = p[q]; i < min(pe[q], top); ++i) {
-                        const float vt = kValueScale * *reinterpret_cast<const float*>(v0 + (i << 3));
-                        Vec<4>::fma(acc[q], vt, *reinterpret_cast<const float4*>(x0 + (i << row_sh)));
-                        sum[q] += vt;
+            } else {
+                // The entries without a slot straight from memory, where the graph's rows of X are in the CU's
+                // cache or the L2.  The lanes of a group request as many entries at once and pass them round:
+                // one wait for them, not one for each (us, one channel, n_X = 64, F = 128, 2048 molecules of 24 /
+                // 48 entries per row: 57 -> 44 / 114 -> 72).
+                static_assert(Q == 1, "one row of a group at a time");
+                constexpr int E = WV == 8 && KS <= 8 ? (KS == 8 ? 1 : 2) : 4;     // what the registers beside the weights hold
+                auto add = [&](int n, auto entry) {                // entries 0 .. n - 1: (value, row of X)
+                    for (int t0 = 0; t0 < n; t0 += E) {
+                        float4 xv[E];
+                        float v[E];
+#pragma unroll
+                        for (int t = 0; t < E; ++t) entry(min(t0 + t, n - 1), v[t], xv[t]);
+#pragma unroll
+                        for (int t = 0; t < E; ++t) {
+                            const float vt = t0 + t < n ? kValueScale * v[t] : 0.f;
+                            Vec<4>::fma(acc[0], vt, xv[t]);
+                            sum[0] += vt;
+                        }
                     }
-                    for (int i = max(p[q], top); i < pe[q]; ++i) {
-                        const int2 en = entries[(uint32_t)(ea + i)];
-                        const float vt = kValueScale * __int_as_float(en.y);
-                        Vec<4>::fma(acc[q], vt, load_vec<4>(x + ((uint64_t)(uint32_t)en.x * (uint32_t)S.ld_x + c4)));
-                        sum[q] += vt;
-                    }
+                };
+                int lane = tid;                                    // (see place)
+                asm volatile("" : "+v"(lane));
+                lane &= L - 1;
+                const int top = S.slots;
+                add(min(pe[0], top) - p[0], [&](int i, float& v, float4& xv) {
+                    xv = *reinterpret_cast<const float4*>(x0 + ((p[0] + i) << row_sh));
+                    v = *reinterpret_cast<const float*>(v0 + ((p[0] + i) << 3));
+                });
+                for (int i0 = max(p[0], top); i0 < pe[0]; i0 += L) {
+                    const int2 en = entries[(uint32_t)(ea + min(i0 + lane, pe[0] - 1))];
+                    add(min(L, pe[0] - i0), [&](int i, float& v, float4& xv) {
+                        const uint32_t row = (uint32_t)__shfl(en.x, i, L);
+                        v = __int_as_float(__shfl(en.y, i, L));
+                        xv = load_vec<4>(x + ((uint64_t)row * (uint32_t)S.ld_x + 4 * lane));
+                    });
                 }
             }
             if (l == 0)
@@ -2602,14 +2622,19 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         constexpr int kRows = WV == 8 ? (KS == 8 ? 1 : 2) : (KS * U <= 6 ? 4 : 2);
         std::integral_constant<int, 1> one;
         std::integral_constant<int, 2> two;
-        if (V <= G || kRows == 1)
-            gather(one, std::integral_constant<int, kRows == 1 ? 2 : 4>(), e_cur, e_next, csr);
+        const bool past = !DIRECT && e_next - (e_cur & ~1) > S.slots;
+        if constexpr (!DIRECT)
+            if (past) gather(one, std::integral_constant<int, 0>(), e_cur, csr);
+        if (past)
+            ;
+        else if (V <= G || kRows == 1)
+            gather(one, std::integral_constant<int, kRows == 1 ? 2 : 4>(), e_cur, csr);
         else if (M == 1)
-            gather(two, std::integral_constant<int, kRows == 4 ? 4 : 2>(), e_cur, e_next, csr);
+            gather(two, std::integral_constant<int, kRows == 4 ? 4 : 2>(), e_cur, csr);
         else if (V <= 2 * G)
-            gather(two, two, e_cur, e_next, csr);
+            gather(two, two, e_cur, csr);
         else
-            gather(std::integral_constant<int, kRows>(), two, e_cur, e_next, csr);
+            gather(std::integral_constant<int, kRows>(), two, e_cur, csr);
         // this lane's output rows
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)

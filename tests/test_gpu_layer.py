@@ -10,6 +10,7 @@ import pytest
 from paper_1903_11409_amd import bspmm as K
 from paper_1903_11409_amd import workloads as W
 from test_gpu_gcn import SENTINEL, _assert_close, _channel, _layer, _owned, _tol, torch_cuda  # noqa: F401
+from test_schedule_cpu import _of_degree
 
 pytestmark = pytest.mark.gpu
 
@@ -99,6 +100,28 @@ def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, cus, n_x):
     ref, T = _reference(oracle, b, X, Ws, biases)
     _assert_close(Yd.cpu().numpy(), ref, T, _owned(b.c_row_off, b.rows, b.n_c_rows),
                   max(1e-5, chans * (n_x + n) * 2.0 ** -23), "stars")
+
+
+@pytest.mark.parametrize("chans,n_x,F", [(1, 16, 64), (1, 64, 128), (2, 32, 128), (1, 128, 64), (4, 64, 128),
+                                         (6, 16, 128), (8, 128, 128)])
+@pytest.mark.parametrize("per_row,heavy,cus", [(8, None, 4), (20, None, 4), (100, None, 2), (3, 70, 4), (7, None, 0)])
+def test_many_entries_per_row(torch_cuda, oracle, chans, n_x, F, per_row, heavy, cus):  # noqa: F811
+    """Blocks inside their slots, past them (rows of more entries than a lane group requests at once, and of
+    fewer) and graphs of many entries in a launch of their own, beside graphs of few."""
+    torch = torch_cuda
+    b = _of_degree(60, chans, per_row, heavy, F=F)
+    X, Ws, biases = _layer(b, n_x, 8, channels=chans)
+    plan = _plan(b, n_x, chans, compute_units=cus)
+    ops = _device(torch, X, Ws, biases)
+    Yd = torch.full((b.n_c_rows, F), SENTINEL, dtype=torch.float32, device="cuda")
+    plan.run_gcn(*ops, Yd)
+    onto = torch.ones_like(Yd)
+    plan.run_gcn(*ops, onto, accumulate=True)
+    torch.cuda.synchronize()
+    ref, T = _reference(oracle, b, X, Ws, biases)
+    tol = max(1e-5, (chans * n_x + (heavy or per_row) + 10) * 2.0 ** -23)
+    _assert_close(Yd.cpu().numpy(), ref, T, _owned(b.c_row_off, b.rows, b.n_c_rows), tol, "many entries")
+    assert np.all(np.abs(onto.cpu().numpy().astype(np.float64) - 1 - ref) <= tol * (T + 1))
 
 
 @pytest.mark.parametrize("chans,n_x,F,cus", [(1, 64, 128, 8), (1, 64, 128, 0), (4, 64, 128, 8), (2, 16, 64, 0)])

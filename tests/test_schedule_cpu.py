@@ -916,6 +916,35 @@ def test_single_channels_stream_from_a_size_of_the_layer_input():
     assert stream_of(64, 64, compute_units=16)[0] > 0
 
 
+def _of_degree(graphs, chans, per_row, heavy=None, seed=5, F=64):
+    """Molecule-sized graphs whose channels have `per_row` entries per row together; every 40th graph `heavy`."""
+    rng = np.random.default_rng(seed)
+    nodes = rng.integers(10, 41, graphs)
+    ops, block = [], []
+    for g, m in enumerate(nodes):
+        d = heavy if heavy and g % 40 == 0 else per_row
+        for _ in range(chans):
+            count = np.full(m, d // chans, dtype=np.int32)
+            count[:m * (d % chans) // chans] += 1
+            rpt = np.concatenate([[0], np.cumsum(count)]).astype(np.int32)
+            ci = rng.integers(0, m, int(rpt[-1])).astype(np.int32)
+            ops.append((int(m), int(m), rpt, ci, rng.uniform(-1, 1, len(ci)).astype(np.float32)))
+            block.append(g)
+    return W.assemble("degree", F, ops, block, [int(m) for m in nodes], rng, n_graphs=graphs, c_block_of_op=block)
+
+
+@pytest.mark.parametrize("chans,per_row,heavy,left", [
+    (1, 8, None, 0), (4, 8, None, 0), (1, 16, None, 0), (4, 40, None, 0), (8, 24, None, 0),
+    (1, 3, 30, 0), (1, 3, 48, 10), (4, 4, 48, 10)])
+def test_layers_of_many_entries_per_row_stay_with_the_resident_workgroups(chans, per_row, heavy, left):
+    """A batch of one kind, however many entries per row; graphs of many beside graphs of few have their own launch."""
+    b = _of_degree(400, chans, per_row, heavy)
+    h = K.dry_plan(b, 64, flags=K.ACCUMULATE if chans > 1 else 0, front_features=64, compute_units=64)
+    stream = [int(v) for v in K.bspmm_plan_info(h).front_stream]
+    K.bspmm_destroy(h)
+    assert (stream[0], stream[3]) == (400 - left, left), stream
+
+
 @pytest.mark.parametrize("why,graphs,F,n_x,chans,kw", [
     ("less than two workgroups per CU", 100, 128, 64, 4, {}),
     ("the caller keeps the one-launch path", 2048, 128, 64, 4, {"flags": K.ONE_FRONT_LAUNCH}),
