@@ -331,10 +331,11 @@ int bspmm_run(bspmm_plan* plan, const float* B, float* C, int64_t ldb, int64_t l
  * many graphs are run by RESIDENT workgroups, two or three per CU, that keep the weights of their columns
  * in registers for the whole launch.  The first run then also enqueues a kernel that writes the blocks'
  * row starts and entries (once per plan, like the merged CSR of summed sets; BSPMM_BUILD_TRANSPOSE moves
- * it into bspmm_create).  Graphs of more than 32 entries per row in all channels and
- * twice the batch's average keep the one-launch kernel, which makes the dense tile of a graph on chip and
- * gathers from it, in a launch of their own (bspmm_info.front_stream says how many; layers of one channel and
- * few graphs: one of more than six, with n_X past 16 eight, keeps the whole plan there).  BSPMM_ONE_FRONT_LAUNCH keeps a plan on that kernel.
+ * it into bspmm_create).  Graphs of more than 32 entries per row in all channels and twice the batch's
+ * average keep the one-launch kernel, which makes the dense tile of a graph on chip and gathers from it, in a
+ * launch of their own (bspmm_info.front_stream says how many).  Layers of one channel and few graphs stay on that
+ * kernel altogether where one of them has more than eight entries per row (n_X = 16: six), or, at n_X = 16,
+ * where there are too many of them.  BSPMM_ONE_FRONT_LAUNCH keeps a plan on that kernel.
  * With options.lds_bytes the caller fixes the LDS budget of both.
  */
 int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W, int64_t ldw,

@@ -383,10 +383,10 @@ void make_stream_plan(bspmm_plan& p)
     }
     if (mine.empty() || (rows + 64) * channels >= kLimit || entries >= kLimit) return;
     // Too few to matter.  us of a run, F = 128, this kernel / one-launch kernel: one channel at n_X = 64, 32
-    // graphs 5.4 / 5.6, 64 graphs 4.6 / 6.1, 128 graphs 5.3 / 6.6, 300 graphs 6.6 / 8.5; at n_X = 16, F = 64, 1000 graphs 7.2 / 7.5; four channels at n_X = 64, 24 graphs
-    // 6.4 / 6.6, 128 graphs 6.9 / 14.2; K = channels n_X past 256: 24 graphs of four channels at n_X = 128 9.9 /
-    // 8.5, 64 graphs 9.9 / 14.0.
-    if (!st.many && (rows + 15) / 16 * (single || channels * nx > 256 ? 4 : 8) < kn.compute_units) return;
+    // graphs 5.4 / 5.6, 64 graphs 4.1 / 6.0, 128 graphs 4.8 / 6.6, 300 graphs 6.6 / 8.5; four channels at n_X = 64, 24
+    // graphs 6.4 / 6.6, 128 graphs 7.1 / 14.2; K = channels n_X past 256: 24 graphs of four channels at n_X = 128
+    // 9.9 / 8.5, 64 graphs 10.7 / 14.0; two channels at n_X = 128, 24 graphs 7.3 / 6.5, 32 graphs 7.4 / 7.5.
+    if (!st.many && (rows + 15) / 16 * (single || channels * nx > 256 ? 4 : (nx == 128 ? 6 : 8)) < kn.compute_units) return;
     int most_k = 0, most_nnz = 0;                        // of an operation: it has to fit on chip
     if (direct) {
         int64_t words = 0;                               // (32-bit offsets)
@@ -465,6 +465,16 @@ void make_stream_plan(bspmm_plan& p)
                 st.items.push_back(t);
             }
     if (direct) blocks = (int64_t)st.items.size();
+    // Rows of 16 floats are a quarter of a wavefront's gather each, and a workgroup's start is most of its time:
+    // past so many workgroups per CU the one-launch kernel, a workgroup to a graph, is the faster one.  us, this
+    // kernel / that one, molecules of 2.2 to 6 entries per row: F = 16, 400 graphs (3.2 workgroups per CU) 4.4 to
+    // 4.9 / 4.8 to 5.0, 700 5.6 to 6.0 / 5.1 to 5.6, 1600 9.1 to 10.6 / 6.5 to 6.7; F = 64, 700 (5.6) 6.0 to 6.5 / 6.6
+    // to 7.0, 1000 7.5 to 8.6 / 7.4 to 7.9; F = 128, 1000 (8) 10.4 to 11.5 / 11.1 to 12.0, 1600 14.9 to 16.8 / 15.0
+    // to 15.8; F = 256, 400 (6.5) 9.4 to 10.3 / 9.6 to 10.1, 1600 26.8 to 29.6 / 25.4 to 27.1.
+    if (direct && nx == 16 && 16 * blocks * tiles > (int64_t)kn.compute_units * std::min(F + 40, 136)) {
+        st = bspmm_plan::Stream();
+        return;
+    }
     st.units = units;
     st.rb = rb;
     st.waves = waves;

@@ -945,6 +945,26 @@ def test_layers_of_many_entries_per_row_stay_with_the_resident_workgroups(chans,
     assert (stream[0], stream[3]) == (400 - left, left), stream
 
 
+@pytest.mark.parametrize("n_x,F,graphs,gathers_first", [
+    (16, 16, 300, True), (16, 16, 1000, False), (16, 64, 600, True), (16, 64, 1000, False), (16, 128, 900, True),
+    (16, 256, 1200, False), (32, 64, 700, True), ((128, 128), 128, 22, False), ((128, 128), 128, 40, True)])
+def test_small_layers_that_gather_first(n_x, F, graphs, gathers_first):
+    """Fewer graphs than the resident workgroups take: where the layer gathers first, the plan's blocks are in its
+    workspace.  Not too many workgroups of narrow inputs, not too few of wide ones (two channels of 128)."""
+    chans, n_x = (1, n_x) if isinstance(n_x, int) else (len(n_x), n_x[0])
+    b = (W.config2_molecule(F=F, graphs=graphs) if chans == 1 else
+         W.config3_multichannel(F=F, graphs=graphs, channels=chans, accumulate=True))
+    size = []
+    for flags in (0, K.ONE_FRONT_LAUNCH):
+        flags |= K.ACCUMULATE if chans > 1 else 0
+        h = K.dry_plan(b, F, front_features=n_x, flags=flags)
+        info = K.bspmm_plan_info(h)
+        assert info.front_stream[0] == 0
+        size.append(int(info.workspace_bytes))
+        K.bspmm_destroy(h)
+    assert (size[0] > size[1]) == gathers_first, size
+
+
 @pytest.mark.parametrize("why,graphs,F,n_x,chans,kw", [
     ("less than two workgroups per CU", 100, 128, 64, 4, {}),
     ("the caller keeps the one-launch path", 2048, 128, 64, 4, {"flags": K.ONE_FRONT_LAUNCH}),
