@@ -1100,7 +1100,11 @@ Schedule make_schedule(const DirOps& ops_in, int F, const Knobs& kn_in)
                 wide.capacity_wgs = std::min(kn.capacity_wgs, 4 * kn.compute_units);
                 wide.whole_sets = true;
                 Schedule t = make_schedule(ops_in, F, wide);
-                if (!t.error) return t;
+                // Options that keep a launch from compact items leave it to the general kernel, where 40 KiB are
+                // the better budget too but for columns off 16 bytes (four channels, split hub rows, at 24 /
+                // 40 KiB: 300 graphs at F = 64 4.7 / 4.2, at F = 128 5.9 / 6.7, 512 at F = 128 9.0 / 8.2, 2048 at F = 64
+                // 13.8 / 13.3, 1000 of three at F = 128 11.0 / 10.8; 512 at F = 50 8.3 / 9.9, with lds_pad 7.7 / 8.9).
+                if (!t.error && (t.whole || F % 4 == 0)) return t;
             }
         }
     }
