@@ -860,7 +860,7 @@ def test_lean_kernel_needs_row_indices_of_24_bits(extra):
     (50, {}, 40960), (128, {}, 40960), (128, {"flags": K.SPLIT_HUB_ROWS}, 40960),
     (50, {"flags": K.SPLIT_HUB_ROWS}, 24576), (50, {"lds_pad": 4}, 24576), (50, {"resident_workgroups": 512}, 24576)])
 def test_summed_sets_off_16_bytes_take_more_lds_only_for_compact_items(F, kw, budget):
-    b = W.config3_multichannel(graphs=300, F=F, accumulate=True, own_inputs=True)
+    b = W.config3_multichannel(graphs=512, F=F, accumulate=True, own_inputs=True)
     h = K.dry_plan(b, F, flags=K.ACCUMULATE | kw.get("flags", 0), **{k: v for k, v in kw.items() if k != "flags"})
     info = K.bspmm_plan_info(h)
     K.bspmm_destroy(h)
