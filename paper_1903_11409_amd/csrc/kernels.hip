@@ -3349,7 +3349,7 @@ static LayerFn layer_variant(int ks, int units, int rb, int waves)
         BSPMM_LAYER(3, 2, 1, 4), BSPMM_LAYER(3, 2, 2, 4), BSPMM_LAYER(4, 1, 1, 4), BSPMM_LAYER(4, 1, 2, 4),
         BSPMM_LAYER(4, 2, 1, 4), BSPMM_LAYER(4, 2, 2, 4), BSPMM_LAYER(6, 1, 1, 4), BSPMM_LAYER(6, 2, 1, 4),
         BSPMM_LAYER(8, 1, 1, 4), BSPMM_LAYER(8, 2, 1, 4), BSPMM_LAYER(12, 1, 1, 4), BSPMM_LAYER(16, 1, 1, 4),
-        BSPMM_LAYER(1, 1, 2, 8), BSPMM_LAYER(1, 1, 4, 8), BSPMM_LAYER(2, 1, 2, 8), BSPMM_LAYER(2, 1, 1, 8),
+        BSPMM_LAYER(2, 1, 1, 8), BSPMM_LAYER(2, 1, 2, 8),
         BSPMM_LAYER(3, 1, 1, 8), BSPMM_LAYER(3, 1, 2, 8), BSPMM_LAYER(4, 1, 1, 8), BSPMM_LAYER(4, 1, 2, 8),
         BSPMM_LAYER(6, 1, 1, 8), BSPMM_LAYER(8, 1, 1, 8), BSPMM_LAYER(12, 1, 1, 8), BSPMM_LAYER(16, 1, 1, 8)};
 #undef BSPMM_LAYER
