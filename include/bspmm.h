@@ -413,7 +413,7 @@ int bspmm_validate(bspmm_plan* plan, int32_t* bad_op, void* stream);
 #define BSPMM_KERNEL_BUILD     5  /* transposed-CSR build, 256 lanes                               */
 #define BSPMM_KERNEL_BUILD_L   6  /* transposed-CSR build, 1024 lanes                              */
 #define BSPMM_KERNEL_COO       7  /* direct COO product                                            */
-#define BSPMM_KERNEL_LAYER_STREAM 8 /* bspmm_run_gcn, gather first (K = 256, four wavefronts)          */
+#define BSPMM_KERNEL_LAYER_STREAM 8 /* bspmm_run_gcn, gather first (K = 256, F past 64: four channels of 64) */
 typedef struct bspmm_kernel_resources {
     int32_t vgprs;              /* vector registers per lane                                   */
     int32_t sgprs;              /* scalar registers per wavefront (0: the runtime does not say)*/

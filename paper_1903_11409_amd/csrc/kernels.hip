@@ -3237,7 +3237,10 @@ hipError_t kernel_resources(int which, int lds_bytes, int out[7])
             threads = kBuildThreadsLarge;
             break;
         case 7: fn = reinterpret_cast<const void*>(&bspmm_coo_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void*>(&bspmm_layer_kernel<8, 2, 1, 4, false>); break;
+        case 8:
+            fn = reinterpret_cast<const void*>(&bspmm_layer_kernel<8, 1, 1, 8, false>);
+            threads = 512;
+            break;
         default: return hipErrorInvalidValue;
     }
     hipFuncAttributes a;

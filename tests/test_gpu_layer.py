@@ -302,6 +302,15 @@ def test_one_weight_that_is_no_number(torch_cuda, oracle, chans, n_x, F, cus):  
                   max(1e-5, chans * (n_x + 10) * 2.0 ** -23), "beside a NaN")
 
 
+def test_resources_of_the_layer_kernel_are_those_of_the_variant_that_runs(torch_cuda):  # noqa: F811
+    """Four channels of 64 at F = 128: workgroups of eight wavefronts, nothing spilled."""
+    b = _batch(2048, 128, 4)
+    info = _plan(b, 64, 4).info()
+    kernel = K.bspmm_kernel_info(8, int(info.front_stream[2]))
+    assert (kernel.threads, kernel.scratch_bytes) == (512, 0) and 64 < kernel.vgprs <= 128
+    assert info.front_stream[1] <= kernel.workgroups_per_cu * kernel.compute_units
+
+
 def test_identity_weights_give_the_plain_product(torch_cuda):  # noqa: F811
     """W = I, bias = 0: a sum of three bf16 numbers is the fp32 number they were made from."""
     torch = torch_cuda
