@@ -350,9 +350,9 @@ def test_strides_scattered_blocks_and_a_wide_weight_matrix(torch_cuda, oracle, g
 
 
 @pytest.mark.parametrize("built", [False, True])
-def test_replays_of_a_captured_layer(torch_cuda, built):  # noqa: F811
+def test_replays_of_a_captured_layer(torch_cuda, oracle, built):  # noqa: F811
     """A first run inside a capture records the kernel that writes the blocks' arrays too; replays, with
-    eager runs on other inputs between them, give what an eager run gives."""
+    eager runs between them, give what an eager run gives and what the oracle does."""
     torch = torch_cuda
     b = _batch(200, 128, 4)
     X, Ws, biases = _layer(b, 64, 5, channels=4)
@@ -371,4 +371,10 @@ def test_replays_of_a_captured_layer(torch_cuda, built):  # noqa: F811
         torch.cuda.synchronize()
         plan.run_gcn(Xd, Wd, bd, other)
         torch.cuda.synchronize()
-        assert torch.equal(Y[other != 0], other[other != 0])
+        owned = _owned(b.c_row_off, b.rows, b.n_c_rows)
+        assert torch.equal(Y[owned], other[owned])
+        ref, T = _reference(oracle, b, X * np.float32(i + 1), Ws, biases)
+        got = Y.cpu().numpy()
+        assert np.all(got[~owned] == 0)
+        got[~owned] = SENTINEL
+        _assert_close(got, ref, T, owned, max(1e-5, 4 * (64 + 10) * 2.0 ** -23), f"replay {i}")
