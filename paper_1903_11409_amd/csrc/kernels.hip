@@ -641,11 +641,9 @@ __device__ __forceinline__ void run_fused(const LaunchParams& P, int* sm, int fi
 }
 
 // Merged CSR of one set of summed operations (one workgroup per set, once per plan and
-// direction): row r of the set = row r of member 0, then of member 1, ... (of the members that
-// have such a row: the members of a group of graphs each cover their graph's rows only); an
-// entry becomes (row of the concatenated dense tiles, value).  Row pointers are clamped to the member's entry
-// count and columns outside a member's tile point at its row 0, so malformed input cannot make
-// the product leave its LDS.
+// direction): row r of the set = row r of member 0, then of member 1, ...; an entry becomes (row of the
+// concatenated dense tiles, value).  Row pointers are clamped to the member's entry count and columns
+// outside a member's tile point at its row 0, so malformed input cannot make the product leave its LDS.
 __global__ void __launch_bounds__(kThreads)
 merge_sets_kernel(const SetRecord* __restrict__ sets, const int32_t* __restrict__ rpt,
                   const int32_t* __restrict__ colids, const float* __restrict__ values,
@@ -2181,12 +2179,13 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 // cycles of a SIMD's matrix pipe instead of 1024 with v_mfma_f32_16x16x4_f32.  Error against 64 bits,
 // products of uniform numbers, K = 64 / 256 / 512: 4.5e-8 / 8.1e-8 / 1.2e-7 of the result's norm; the fp32
 // instructions 1.1e-7 / 2.1e-7 / 2.9e-7.  The parts of a small number would be subnormal, or below that: the
-// values of A are taken times 2^60, the weights and the bias times 2^24 and the results times 2^-84, all
-// exactly.  Every fp32 weight then has parts of 2^-125 and more, and what a Z below 2^-162 loses - less than
-// 2^-186 - comes, with 512 weights of at most 2^28, to no more than the smallest fp32 number.  A split number
-// that is not finite is NaN: blocks with results past 2^43 or not finite, and those of a wavefront with weights
-// past 2^28, are made once more without the split, and in the order A (X W + bias): A X can leave the range of
-// fp32 where the layer does not.
+// values of A are taken times 2^48, the weights and the bias times 2^24 and the results times 2^-72, all
+// exactly.  Every fp32 weight then has parts of 2^-125 and more, and what a Z below 2^-150 loses - less than
+// 2^-174, were subnormal parts zero to the instructions - comes, with 512 weights of at most 2^16, to no more
+// than the smallest fp32 number.  A split number that is not finite is NaN: blocks with results past 2^55 or not
+// finite, and those of a wavefront with weights past 2^16, are made once more without the split, and in the order
+// A (X W + bias): A X can leave the range of fp32 where the layer does not.  (A larger factor for A moves both
+// bounds: more weights and fewer results.)
 //   * W in REGISTERS for the whole launch, split once: wavefront w owns U blocks of 16 columns (12
 //     registers per 32 of K and block); no LDS for W.
 //   * A trip is one block.  While the matrix instructions of block b run, the rows of X that block b + 1
@@ -2203,11 +2202,12 @@ __global__ void __launch_bounds__(THREADS) bspmm_gcn_kernel(const LaunchParams P
 //     graphs, n_X = 64: four channels 28.6 -> 29.9, one channel 15.7 -> 16.8).
 // DIRECT: small layers of one channel, a block of 16 rows of one operation to a workgroup.  X_i, the
 // operation's entries and its row pointers are requested at once and no other launch is needed (128 graphs,
-// n_X = 64, F = 128: 5.3 us; with row pointers, entries and rows of X one after the other 5.7; from arrays
-// built once per plan 4.9, but the first run 8 us longer; the one-launch kernel 6.6).
+// n_X = 64, F = 128: 4.8 us; the one-launch kernel 6.6.  With four wavefronts, before it took eight: 5.3; row
+// pointers, entries and rows of X one after the other 5.7; from arrays built once per plan 4.9, but the first run 8
+// us longer).
 // Two barriers a trip.  us of a launch, F = 128, molecules, against the kernel this replaces, which made the
 // dense tiles graph by graph with fp32 matrix instructions: four channels at n_X = 64, 2048 graphs 43.4 ->
-// 29.6, 512 15.4 -> 12.5, 128 11.6 -> 6.8; n_X = 128, 2048 graphs 85.6 -> 57.3; eight channels at n_X = 64, 1024
+// 28.0, 512 15.4 -> 12.5, 128 11.6 -> 7.1; n_X = 128, 2048 graphs 85.6 -> 57.3; eight channels at n_X = 64, 1024
 // graphs 39.7 -> 31.7; one channel at n_X = 64, 2048 graphs 21.2 -> 15.7, 512 10.0 -> 7.1.  Bound at four
 // channels (counters): the matrix pipe is busy for a quarter of the launch, waves wait for 44 %; a trip is a chain
 // of LDS round trips and two barriers that two workgroups per CU hide from each other only in part, and
@@ -2254,7 +2254,7 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t&
     lo = pair(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
 }
 
-constexpr float kValueScale = 0x1p60f, kWeightScale = 0x1p24f;     // (see above)
+constexpr float kValueScale = 0x1p48f, kWeightScale = 0x1p24f;     // (see above)
 
 template <int KS, int U, int RB, int WV, bool DIRECT>
 __global__ void __launch_bounds__(64 * WV, WV == 8 ? (KS > 8 ? 2 : 4) : (KS * U > 8 || (KS > 2 && U * RB > 2) ? 2 : 3))
@@ -2407,7 +2407,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
     // ---- the weights, split once
     bf16x8 wh[U][KS], wm[U][KS], wlo[U][KS];
     float bv[U][BQ];
-    bool huge;                                                // weights past 2^28 in this wavefront
+    bool huge;                                                // weights past 2^16 in this wavefront
     {
         float most = 0.f;
 #pragma unroll
@@ -2427,7 +2427,7 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 wm[u][s] = __builtin_bit_cast(bf16x8, make_uint4(m[0], m[1], m[2], m[3]));
                 wlo[u][s] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
             }
-        huge = __builtin_amdgcn_ballot_w64(most > 0x1p28f * kWeightScale) != 0;
+        huge = __builtin_amdgcn_ballot_w64(most > 0x1p16f * kWeightScale) != 0;
         // bias as the A operand of v_mfma_f32_16x16x4_f32 (k = channel), the row sums are B
 #pragma unroll
         for (int u = 0; u < U; ++u)

@@ -242,10 +242,10 @@ def test_sums_that_only_the_layers_own_order_holds(torch_cuda, oracle, chans, n_
 
 
 # X, W, A: small operands beside large ones, the result ordinary or tiny, inside the weights that the split
-# takes (2^28) and past them, subnormal ones, and A X below the smallest number
-SCALES = [(1e-36, 1e20, 1), (1e20, 1e-36, 1), (1e-37, 1e30, 1), (1e30, 1e-37, 1), (1e-36, 1e8, 1), (1e8, 1e-36, 1),
-          (1e-37, 1, 1), (1, 1e-37, 1), (1e-41, 1e8, 1e-2), (1e8, 1e-41, 1e-2), (1e-30, 1e30, 1e-30),
-          (1e-30, 1e8, 1e-12), (1, 1e8, 1e-36)]
+# takes (2^16) and past them, subnormal ones, and A X below the smallest number
+SCALES = [(1e-36, 1e20, 1), (1e20, 1e-36, 1), (1e-37, 1e30, 1), (1e30, 1e-37, 1), (1e-36, 3e4, 1), (1e8, 1e-36, 1),
+          (1e-37, 1, 1), (1, 1e-37, 1), (1e-41, 3e4, 1e-2), (1e8, 1e-41, 1e-2), (1e-30, 1e30, 1e-30),
+          (1e-30, 3e4, 1e-10), (1, 3e4, 1e-36), (1e14, 3e4, 1e-3), (1e10, 1e5, 1e3)]
 
 
 @pytest.mark.parametrize("chans,n_x,F,cus", WAYS)
