@@ -283,7 +283,8 @@ int bspmm_create(bspmm_plan** plan, const bspmm_batch* b, int32_t F,
  * GPU, so the caller passes none and the call allocates no device memory.  The GPU is the
  * calling thread's current device; `stream` must belong to it.
  *  - ENOSPACE when the plan needs more than BSPMM_STATIC_WORKSPACE_BYTES (bspmm_workspace_bytes
- *    tells in advance); BSPMM_DRY_RUN is EINVAL; otherwise arguments and errors as bspmm_create.
+ *    tells in advance; plans with front_features: with BSPMM_ONE_FRONT_LAUNCH, which such a plan takes by
+ *    itself where it fits only so); BSPMM_DRY_RUN is EINVAL; otherwise arguments and errors as bspmm_create.
  *  - All such plans of a GPU share the one array, which keeps what the last one wrote.  Nothing
  *    in it has to start at zero: every table is written in full before it is read.  Only the
  *    latest static plan of a GPU is valid; run, export and validate calls on an earlier one

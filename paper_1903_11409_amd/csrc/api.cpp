@@ -1760,6 +1760,15 @@ int bspmm_create_static(bspmm_plan** plan, const bspmm_batch* b, int32_t F,
     bspmm_plan* p = new (std::nothrow) bspmm_plan;
     if (!p) return BSPMM_EINVAL;
     rc = plan_with_budget(*p, b, F, options, false, plan_host);
+    if (rc == BSPMM_OK && p->lay.total > (size_t)BSPMM_STATIC_WORKSPACE_BYTES && p->stream.on()) {
+        // (a layer whose gather-first arrays do not fit: without them where that does)
+        bspmm_options one = *options;
+        one.flags |= BSPMM_ONE_FRONT_LAUNCH;
+        delete p;
+        p = new (std::nothrow) bspmm_plan;
+        if (!p) return BSPMM_EINVAL;
+        rc = plan_with_budget(*p, b, F, &one, false, plan_host);
+    }
     if (rc == BSPMM_OK && p->lay.total > (size_t)BSPMM_STATIC_WORKSPACE_BYTES) rc = BSPMM_ENOSPACE;
     if (rc == BSPMM_OK) {
         p->rpt = b->rpt;

@@ -302,6 +302,29 @@ def test_one_weight_that_is_no_number(torch_cuda, oracle, chans, n_x, F, cus):  
                   max(1e-5, chans * (n_x + 10) * 2.0 ** -23), "beside a NaN")
 
 
+def test_static_workspace_holds_layers_without_the_gather_first_arrays(torch_cuda, oracle):  # noqa: F811
+    """Many entries: the static array holds the plan, but not with the layer's arrays beside the transposed CSR."""
+    torch = torch_cuda
+    b, n_x = _of_degree(800, 1, 30), 64
+    options = K.make_options(front_features=n_x)
+    dry = [K.dry_plan(b, b.F, front_features=n_x, flags=flags) for flags in (0, K.ONE_FRONT_LAUNCH)]
+    size = [int(K.bspmm_plan_info(h).workspace_bytes) for h in dry]
+    for h in dry:
+        K.bspmm_destroy(h)
+    assert size[0] > K.STATIC_WORKSPACE_BYTES >= size[1], size
+    arrays = [torch.from_numpy(a).cuda() for a in (b.rpt, b.colids, b.values)]
+    plan = K.bspmm_create_static(K.HostBatch(b.rows, b.cols, b.nnz, b.rpt_off, b.nz_off, b.b_row_off, b.c_row_off,
+                                             *arrays), b.F, options)
+    X, Ws, biases = _layer(b, n_x, 3)
+    Xd, Wd, bd = _device(torch, X, Ws, biases)
+    Yd = torch.full((b.n_c_rows, b.F), SENTINEL, dtype=torch.float32, device="cuda")
+    K.bspmm_run_gcn(plan, Xd, n_x, Wd, b.F, bd, Yd, b.F)
+    torch.cuda.synchronize()
+    ref, T = _reference(oracle, b, X, Ws, biases)
+    _assert_close(Yd.cpu().numpy(), ref, T, _owned(b.c_row_off, b.rows, b.n_c_rows), 1e-5, "static")
+    K.bspmm_destroy(plan)
+
+
 def test_resources_of_the_layer_kernel_are_those_of_the_variant_that_runs(torch_cuda):  # noqa: F811
     """Four channels of 64 at F = 128: workgroups of eight wavefronts, nothing spilled."""
     b = _batch(2048, 128, 4)
