@@ -2740,12 +2740,14 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
         const int b = b0 + 32 * (word % kLayerRedoWords) + __builtin_ctz(left);
         const int f1 = (tile * WV + word / kLayerRedoWords) * (16 * U), columns = min(16 * U, S.F - f1);
         if (columns <= 0) continue;
-        for (int rb = 0; rb < RB; ++rb) {
+        // (one sixteen of columns at a time: two at once would take registers, and so workgroups, from every launch)
+#pragma unroll 1
+        for (int part = 0; part < RB * U; ++part) {
+            const int rb = part / U, c0 = f1 + 16 * (part % U);
+            if (16 * (part % U) >= columns) continue;
             const int row = DIRECT ? *reinterpret_cast<const int*>(lds + at.csr + at.rows + 4 * col)
                                    : out_rows[(uint32_t)(R * b + 16 * rb + col)];
-            f32x4 sum[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
             for (int ch = 0; ch < M; ++ch) {
                 const uint32_t vr = (uint32_t)b * V + (uint32_t)((16 * rb + col) * M + ch);
                 const int* st = reinterpret_cast<const int*>(lds + at.csr);
@@ -2761,15 +2763,10 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                 };
                 int2 en = make_int2(0, 0);
                 if (count > 0) en = entry(first);
-                f32x4 bias4[U];
-                const float* wp[U];
+                f32x4 bias4;
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c0 = f1 + (16 * u < columns ? 16 * u : 0);          // (past F: the first sixteen again)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) bias4[u][i] = bias[ch * S.bias_stride + c0 + 4 * g + i];
-                    wp[u] = wgt + (int64_t)(ch * 4 * L + 4 * g) * S.ld_w + (c0 + col);
-                }
+                for (int i = 0; i < 4; ++i) bias4[i] = bias[ch * S.bias_stride + c0 + 4 * g + i];
+                const float* wp = wgt + (int64_t)(ch * 4 * L + 4 * g) * S.ld_w + (c0 + col);
                 for (int p = 0;; ++p) {
                     const bool mine = p < count;
                     const unsigned long long has = __builtin_amdgcn_ballot_w64(mine);
@@ -2779,57 +2776,43 @@ bspmm_layer_kernel(const int32_t* __restrict__ starts, const int2* __restrict__ 
                     const float* xp = x + ((uint64_t)(uint32_t)(mine ? en.x : other) * (uint32_t)S.ld_x + 4 * g);
                     const float v = __int_as_float(en.y);
                     if (p + 1 < count) en = entry(first + p + 1);
-                    f32x4 acc[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) acc[u] = bias4[u];
+                    f32x4 acc = bias4;
                     // (sixteen k a trip, the next ones requested before these are multiplied)
                     float4 xn = load_vec<4>(xp);
-                    float wn[U][4];
+                    float wn[4];
                     auto weights_at = [&](int k) {
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) wn[u][j] = wp[u][(uint32_t)(k + j) * (uint32_t)S.ld_w];
+                        for (int j = 0; j < 4; ++j) wn[j] = wp[(uint32_t)(k + j) * (uint32_t)S.ld_w];
                     };
                     weights_at(0);
 #pragma unroll 1
                     for (int k = 16; k <= 4 * L; k += 16) {
                         const float4 xv = xn;
-                        float w[U][4];
+                        float w[4];
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) w[u][j] = wn[u][j];
+                        for (int j = 0; j < 4; ++j) w[j] = wn[j];
                         if (k < 4 * L) {
                             xn = load_vec<4>(xp + k);
                             weights_at(k);
                         }
-#pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][0], xv.x, acc[u], 0, 0, 0);
-                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][1], xv.y, acc[u], 0, 0, 0);
-                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][2], xv.z, acc[u], 0, 0, 0);
-                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][3], xv.w, acc[u], 0, 0, 0);
-                        }
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], xv.x, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], xv.y, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], xv.z, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], xv.w, acc, 0, 0, 0);
                     }
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (mine) sum[u][i] = fmaf(v, acc[u][i], sum[u][i]);
+                    for (int i = 0; i < 4; ++i)
+                        if (mine) sum[i] = fmaf(v, acc[i], sum[i]);
                 }
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (row < 0 || 16 * u >= columns) continue;
-                float* yp = y + ((uint64_t)(uint32_t)row * (uint32_t)S.ld_y + (uint32_t)(f1 + 16 * u + 4 * g));
-                float4 v = make_float4(sum[u][0], sum[u][1], sum[u][2], sum[u][3]);
-                if (S.accumulate) {
-                    const float4 old = *reinterpret_cast<const float4*>(yp);
-                    v.x += old.x, v.y += old.y, v.z += old.z, v.w += old.w;
-                }
-                store_out<4>(yp, v);
+            if (row < 0) continue;
+            float* yp = y + ((uint64_t)(uint32_t)row * (uint32_t)S.ld_y + (uint32_t)(c0 + 4 * g));
+            float4 v = make_float4(sum[0], sum[1], sum[2], sum[3]);
+            if (S.accumulate) {
+                const float4 old = *reinterpret_cast<const float4*>(yp);
+                v.x += old.x, v.y += old.y, v.z += old.z, v.w += old.w;
             }
+            store_out<4>(yp, v);
         }
     }
 }
