@@ -363,6 +363,52 @@ void make_stream_plan(bspmm_plan& p)
     const double mean = (double)all_entries / (double)std::max<int64_t>(all_rows, 1);
     const double degree = direct ? (nx == 16 ? 6.0 : 8.0) : std::max(32.0, 2 * mean);
     const double range = (double)all_rows * ((F + 127) / 128) / (3.0 * kn.compute_units);
+    // Fewer columns than the layer input has: here a row still gathers n_X floats for every entry, and wavefronts
+    // past F have no columns to multiply, while the other kernel's dense tile is narrow.  Batches of more entries per
+    // row than `narrow` stay there; the line moves with the 16-row blocks per CU (up to one, up to three, more).  us,
+    // this kernel / one-launch, 100 | 400 | 1500 molecules (0.6 | 2.4 | 9 blocks per CU):
+    //   F = 16, one channel, n_X = 64, 2.2 entries per row 4.3 / 4.7 | 5.0 / 5.7 | 9.7 / 8.7, 5 4.3 / 4.9 | 6.7 / 5.9 |
+    //   11.4 / 9.0;   n_X = 128, 5 5.6 / 6.1 | 9.7 / 11.2 | 18.0 / 13.2;   three, n_X = 64, 2.2 6.0 / 6.6 | 8.5 / 8.9 |
+    //   15.9 / 14.4, 5 6.7 / 6.7 | 9.4 / 8.9 | 18.1 / 14.9;   n_X = 128, 5 9.5 / 9.9 | 17.2 / 12.2 | 32.6 / 24.7
+    //   F = 32, one channel, n_X = 64, 5 4.3 / 5.1 | 6.8 / 6.9 | 11.5 / 11.1, 8 4.6 / 5.1 | 7.5 / 8.2 | 13.7 / 11.5;
+    //   three, n_X = 128, 5 9.6 / 10.0 | 17.3 / 15.7 | 32.7 / 37.3, 16 12.1 / 11.2 | 22.4 / 19.1 | 46.0 / 39.8;   eight,
+    //   n_X = 128, 2.2 18.6 / 15.3 | 33.2 / 35.8 | 61.5 / 112
+    //   F = 48, one channel, n_X = 64, 8 4.6 / 5.6 | 7.5 / 8.8 | 13.9 / 14.8, 16 - | - | 20.7 / 16.4;   three, n_X = 128, 8 10.5
+    //   / 10.5 | 19.2 / 21.0 | 38.0 / 64.1, 16 12.1 / 11.2 | 22.4 / 21.7 | 46.2 / 65.5;   eight, 5 20.2 / 20.4, 8 22.4 / 20.5
+    //   n_X = 32, F = 16, one channel, 2.2 3.8 / 4.4 | 4.8 / 5.2 | 7.0 / 6.9, 5 4.0 / 4.5 | 4.8 / 5.6 | 8.8 / 7.1
+    //   F = 64, 100 molecules: two channels, n_X = 64, 30 9.0 / 7.8;   three, n_X = 64 8.1 / 8.3, n_X = 128 8
+    //   10.6 / 10.7, 16 12.1 / 11.5;   eight, n_X = 128, 5 20.2 / 20.5, 8 22.2 / 20.7
+    // Graphs of hundreds of rows take the other kernel several passes each, one after the other (907 skewed graphs of
+    // up to 500 rows, three channels, n_X = 128, F = 16: 34.9 / 62.9).
+    // Whole layers of half a block per CU and less: six entries per row (us, 45 graphs of three channels, n_X = 32, F = 64,
+    // 30 per row 8.1 / 7.0; 70 of eight, n_X = 128, F = 96, 14 per row 24.1 / 21.7).
+    if (!single && all_rows / 8 <= kn.compute_units && mean > 6) return;
+    // One channel by resident workgroups: up to fourteen where the launch is short (n_X = 64, F = 128, 600 graphs, 3.7 blocks
+    // per CU, 12 / 16 / 24 per row 11.5 / 18.3 / 21.2, one-launch 14.7 / 15.9 / 17.6; 2048 graphs, see above, any) or the rows
+    // are (n_X = 16).
+    if (single && !direct && mean > 14 && (nx == 16 || (nx == 64 && all_rows / 16 <= 6 * kn.compute_units))) return;
+    int64_t most_rows = 0;
+    for (size_t g = 0; g < n_graphs; ++g) most_rows = std::max<int64_t>(most_rows, o.m[op_of(g, 0)]);
+    if (most_rows <= 192 && (F < 64 ? nx > F : F == 64 && nx >= 64)) {
+        const int64_t per_cu = (all_rows / 16 + kn.compute_units - 1) / kn.compute_units;
+        const bool few = per_cu <= 1, many = per_cu > 3;
+        const int K = channels * nx;
+        double narrow = 1e9;
+        if (nx < 64) {
+            if (F <= 16 && many && K <= 128) narrow = single ? 3 : 5;
+        } else if (F <= 16) {
+            narrow = many || K > (few ? 384 : 192) ? 0 : few ? 5 : single ? nx / 16 : 3;
+        } else if (few) {
+            if (!single) narrow = K > 512 ? (F <= 32 ? 0 : 5) : F <= 32 ? 5 : F < 64 ? 8 : nx == 128 ? 10 : 18;
+        } else if (F == 64) {      // (no line found)
+        } else if (many) {
+            if (single) narrow = F <= 32 ? 3 : 10;
+            else if (F <= 32 && nx == 128 && K <= 384) narrow = 8;
+        } else if (nx == 128 && !single) {
+            narrow = F <= 32 ? 3 : 13;
+        }
+        if (mean > narrow) return;
+    }
     std::vector<int> mine;
     std::vector<char> streamed(n_graphs, 0);
     int64_t rows = 0, entries = 0;
@@ -466,12 +512,13 @@ void make_stream_plan(bspmm_plan& p)
             }
     if (direct) blocks = (int64_t)st.items.size();
     // Rows of 16 floats are a quarter of a wavefront's gather each, and a workgroup's start is most of its time:
-    // past so many workgroups per CU the one-launch kernel, a workgroup to a graph, is the faster one.  us, this
-    // kernel / that one, molecules of 2.2 to 6 entries per row: F = 16, 400 graphs (3.2 workgroups per CU) 4.4 to
-    // 4.9 / 4.8 to 5.0, 700 5.6 to 6.0 / 5.1 to 5.6, 1600 9.1 to 10.6 / 6.5 to 6.7; F = 64, 700 (5.6) 6.0 to 6.5 / 6.6
-    // to 7.0, 1000 7.5 to 8.6 / 7.4 to 7.9; F = 128, 1000 (8) 10.4 to 11.5 / 11.1 to 12.0, 1600 14.9 to 16.8 / 15.0
-    // to 15.8; F = 256, 400 (6.5) 9.4 to 10.3 / 9.6 to 10.1, 1600 26.8 to 29.6 / 25.4 to 27.1.
-    if (direct && nx == 16 && 16 * blocks * tiles > (int64_t)kn.compute_units * std::min(F + 40, 136)) {
+    // past so many workgroups per CU the one-launch kernel, a workgroup to a graph, is the faster one up to F = 64.
+    // us, this kernel / that one, molecules of 2.2 to 5.5 entries per row: F = 16, 500 graphs (4.0 workgroups per CU)
+    // 4.6 to 5.1 / 4.9 to 5.3, 800 6.1 to 6.5 / 5.2 to 5.7; F = 32, 500 4.7 to 5.2 / 5.3 to 5.7, 700 (5.6) 5.8 to 6.2 / 5.3
+    // to 5.8; F = 64, 800 (6.4) 6.6 to 7.1 / 7.1 to 7.2, 1000 (8.1) 7.2 to 8.4 / 7.5 to 7.9, 1300 8.7 to 9.6 / 8.6 to 8.9,
+    // skewed graphs 400 (6.7) 11.5 to 13.7 / 12.5 to 15.1, 500 14.3 to 17.0 / 12.6 to 14.9; F = 128, 1600 13.4 to 15.1 /
+    // 15.0 to 16.4; F = 256, 1300 19.3 to 21.6 / 21.7 to 23.7.
+    if (direct && nx == 16 && F <= 64 && 16 * blocks * tiles > (int64_t)kn.compute_units * (F + 56)) {
         st = bspmm_plan::Stream();
         return;
     }

@@ -305,7 +305,7 @@ def test_one_weight_that_is_no_number(torch_cuda, oracle, chans, n_x, F, cus):  
 def test_static_workspace_holds_layers_without_the_gather_first_arrays(torch_cuda, oracle):  # noqa: F811
     """Many entries: the static array holds the plan, but not with the layer's arrays beside the transposed CSR."""
     torch = torch_cuda
-    b, n_x = _of_degree(800, 1, 30), 64
+    b, n_x = _of_degree(800, 1, 30), 128
     options = K.make_options(front_features=n_x)
     dry = [K.dry_plan(b, b.F, front_features=n_x, flags=flags) for flags in (0, K.ONE_FRONT_LAUNCH)]
     size = [int(K.bspmm_plan_info(h).workspace_bytes) for h in dry]

@@ -927,6 +927,18 @@ def test_single_channels_stream_from_a_size_of_the_layer_input():
     assert stream_of(64, 64, compute_units=16)[0] > 0
 
 
+@pytest.mark.parametrize("n_x,F,chans,per_row,resident", [
+    (64, 16, 1, 2, False), (128, 16, 1, 24, False), (64, 32, 1, 2, True), (64, 32, 1, 5, False), (64, 32, 3, 6, True),
+    (128, 32, 3, 12, False), (64, 48, 1, 8, True), (64, 48, 1, 16, False), (32, 16, 1, 2, True), (32, 16, 1, 5, False),
+    (64, 64, 1, 16, True)])
+def test_large_layers_of_fewer_columns_than_their_input(n_x, F, chans, per_row, resident):
+    b = _of_degree(1200, chans, per_row, F=F)
+    h = K.dry_plan(b, F, flags=K.ACCUMULATE if chans > 1 else 0, front_features=n_x, compute_units=32)
+    stream = [int(v) for v in K.bspmm_plan_info(h).front_stream]
+    K.bspmm_destroy(h)
+    assert (stream[0] == 1200) == resident, stream
+
+
 def _of_degree(graphs, chans, per_row, heavy=None, seed=5, F=64):
     """Molecule-sized graphs whose channels have `per_row` entries per row together; every 40th graph `heavy`."""
     rng = np.random.default_rng(seed)
@@ -958,7 +970,10 @@ def test_layers_of_many_entries_per_row_stay_with_the_resident_workgroups(chans,
 
 @pytest.mark.parametrize("n_x,F,graphs,gathers_first", [
     (16, 16, 300, True), (16, 16, 1000, False), (16, 64, 600, True), (16, 64, 1000, False), (16, 128, 900, True),
-    (16, 256, 1200, False), (32, 64, 700, True), ((128, 128), 128, 22, False), ((128, 128), 128, 40, True)])
+    (16, 256, 1200, True), (16, 32, 700, False), (32, 64, 700, True), ((128, 128), 128, 22, False), ((128, 128), 128, 40, True),
+    # fewer columns than the layer input has
+    (64, 16, 100, True), (64, 16, 390, True), (128, 16, 100, True), ((64,) * 3, 16, 100, True),
+    ((128,) * 8, 16, 100, False), ((128,) * 3, 16, 300, False), ((128,) * 8, 32, 100, False), (64, 32, 400, True)])
 def test_small_layers_that_gather_first(n_x, F, graphs, gathers_first):
     """Fewer graphs than the resident workgroups take: where the layer gathers first, the plan's blocks are in its
     workspace.  Not too many workgroups of narrow inputs, not too few of wide ones (two channels of 128)."""
