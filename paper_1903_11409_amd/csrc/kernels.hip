@@ -1436,6 +1436,38 @@ __device__ __forceinline__ void lean_wave_item(const LeanItem& it, char* lds, co
                      gather_row(cv, bcol, sm[r], sm[r + 1]));
 }
 
+// Dense tile of a staged item, straight from global memory into LDS, 1 KiB per wavefront instruction
+// (lane i lands at base + 16*i); a tile no other item reads is streamed.  Offsets inside the item's
+// block are 32-bit (the host launches the lean kernels only when they fit).
+__device__ __forceinline__ void lean_tile(const LeanItem& it, char* lds, const float* __restrict__ in, uint32_t ld_in,
+                                          uint32_t wave, uint32_t wl)
+{
+    const char* __restrict__ src =
+        reinterpret_cast<const char*>(in + ((uint64_t)it.in_row * ld_in + (uint32_t)it.f0));
+    const uint32_t row_bytes = ld_in << 2, total = (uint32_t)it.tile_vecs, nvec = 1u << it.sh;
+    const int sh = it.sh;
+    char* bs = lds + it.b_byte;
+    if (it.flags & 1) {
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
+            const uint32_t e = e0 + wl;
+            if (e < total)
+                __builtin_amdgcn_global_load_lds(
+                    (const void __attribute__((address_space(1)))*)(
+                        src + (__umul24(e >> sh, row_bytes) + ((e & (nvec - 1)) << 4))),
+                    (void __attribute__((address_space(3)))*)(bs + (e0 << 4)), 16, 0, 2);
+        }
+    } else {
+        for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
+            const uint32_t e = e0 + wl;
+            if (e < total)
+                __builtin_amdgcn_global_load_lds(
+                    (const void __attribute__((address_space(1)))*)(
+                        src + (__umul24(e >> sh, row_bytes) + ((e & (nvec - 1)) << 4))),
+                    (void __attribute__((address_space(3)))*)(bs + (e0 << 4)), 16, 0, 0);
+        }
+    }
+}
+
 // MERGED: items with flag bit 2 read their CSR from the merged arrays of summed sets (a template
 // parameter: the selects cost the plain kernel).  512 graphs of four channels with dense blocks of their
 // own, F = 128, summed: 9.1 us, 10.0 through the general kernel.
@@ -1473,35 +1505,7 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
     char* lds = reinterpret_cast<char*>(sm);
 
-    // ---- dense tile, straight from global memory into LDS, 1 KiB per wavefront instruction
-    // (lane i lands at base + 16*i); a tile no other item reads is streamed.  Offsets inside
-    // the item's block are 32-bit (the host launches this kernel only when they fit).
-    {
-        const char* __restrict__ src =
-            reinterpret_cast<const char*>(in + ((uint64_t)it.in_row * ld_in + (uint32_t)it.f0));
-        const uint32_t row_bytes = ld_in << 2;
-        const uint32_t total = (uint32_t)it.tile_vecs;
-        char* bs = lds + it.b_byte;
-        if (it.flags & 1) {
-            for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
-                const uint32_t e = e0 + wl;
-                if (e < total)
-                    __builtin_amdgcn_global_load_lds(
-                        (const void __attribute__((address_space(1)))*)(
-                            src + (__umul24(e >> sh, row_bytes) + ((e & (nvec - 1)) << 4))),
-                        (void __attribute__((address_space(3)))*)(bs + (e0 << 4)), 16, 0, 2);
-            }
-        } else {
-            for (uint32_t e0 = wave << 6; e0 < total; e0 += kThreads) {
-                const uint32_t e = e0 + wl;
-                if (e < total)
-                    __builtin_amdgcn_global_load_lds(
-                        (const void __attribute__((address_space(1)))*)(
-                            src + (__umul24(e >> sh, row_bytes) + ((e & (nvec - 1)) << 4))),
-                        (void __attribute__((address_space(3)))*)(bs + (e0 << 4)), 16, 0, 0);
-            }
-        }
-    }
+    lean_tile(it, lds, in, ld_in, wave, wl);
     // ---- CSR: the row pointers of this lane group's first row (they stay in registers), all
     // row pointers and the entries (on their way to LDS).  Indices are clamped instead of
     // predicated: a lane past the end reads, and later writes, what the last lane does.
@@ -1561,6 +1565,137 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     for (uint32_t r = r_first + groups; r < row_end; r += groups)
         store_out<4>(reinterpret_cast<float*>(dst + (__umul24(r, out_row_bytes) + (l << 4))),
                      gather_row(cv, bcol, sm[r], sm[r + 1]));
+}
+
+// ---------------------------------------------------------------------------------------
+// The first transposed product of a plan whose transposed CSR arrays do not exist yet.  A batch that is
+// new every step used to pay for two launches here, the build (one workgroup per operation, a latency
+// chain of 5 us) and the product, each 3.5 us of host time beside what the GPU takes.  Instead every
+// workgroup of the product sorts its operation itself, in the LDS of its item: entries of
+// A (a column, and the row that its row pointers give) are counted per column, the counts are scanned,
+// the entries' positions are scattered with atomic cursors, and an entry's rank among its column's
+// positions is its place - the stable order of build_sorted_kernel, whatever the order of arrival, so the
+// sums are bit for bit those of the build and bspmm_lean_kernel.  Positions and rows of the
+// entries take the two halves of the words that their (row offset, value) pairs take afterwards.  The
+// workgroup with the first rows and columns of an operation writes its transposed arrays, for every later run.
+// 128 molecules, F = 128, GPU time of build and product 8.7 us, of this kernel 5.4; a step with a new batch (plan, both
+// products) 29.7 -> 25.9 us, 512 from index pairs at F = 64 45.9 -> 42.1.  Bound: the chain of LDS round trips and
+// barriers of the sort, which other workgroups of the CU hide in larger launches.
+// (square operations, arrays of both directions at the same offsets: `it` describes either; at most four entries per lane)
+// ---------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kThreads)
+bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
+                              const int32_t* __restrict__ colids, const float* __restrict__ values,
+                              const float* __restrict__ in, float* __restrict__ out, uint32_t ld_in, uint32_t ld_out,
+                              int32_t* __restrict__ rpt_t, int32_t* __restrict__ colids_t, float* __restrict__ values_t)
+{
+    extern __shared__ __align__(16) int sm[];
+    __shared__ int wave_sum[kWaves];
+    const uint32_t tid = threadIdx.x;
+    const LeanItem it = items[blockIdx.x];
+    if (it.flags & 8) return;  // (small items packed for the lean kernel: this launch has a workgroup for each)
+    const int m = it.m, nnz = min(it.nnz, 4 * kThreads), sh = it.sh;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
+    char* lds = reinterpret_cast<char*>(sm);
+    lean_tile(it, lds, in, ld_in, wave, wl);
+
+    // ---- requests: up to four entries per lane, the two pointers of this lane's first row
+    const int32_t* __restrict__ rp = rpt + it.rpt_off;
+    const int32_t* __restrict__ ci = colids + it.nz_off;
+    const float* __restrict__ va = values + it.nz_off;
+    const uint32_t last = (uint32_t)max(nnz - 1, 0);
+    int key[4] = {-1, -1, -1, -1};
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (nnz > u * kThreads) {                    // (the same for every lane)
+            const uint32_t i = min(tid + u * kThreads, last);
+            key[u] = ci[i];
+            a[u] = va[i];
+        }
+    int r0 = rp[min(tid, (uint32_t)m)], r1 = rp[min(tid + 1, (uint32_t)m)];
+    __builtin_amdgcn_sched_barrier(0);
+
+    int2* cv = reinterpret_cast<int2*>(lds + it.cv_byte);
+    int* pos = reinterpret_cast<int*>(cv);           // positions in A, by column
+    int* row_of = pos + nnz;                         // row of every entry of A
+    for (int c = tid; c <= m; c += kThreads) sm[c] = 0;
+    for (int i = tid; i < m; i += kThreads) {
+        if (i >= kThreads) r0 = rp[i], r1 = rp[i + 1];
+        const int end = min(r1, nnz);
+        for (int p = max(r0, 0); p < end; ++p) row_of[p] = i;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)                      // (entries outside the matrix are skipped, as in the build)
+        if ((int)(tid + u * kThreads) >= nnz || (unsigned)key[u] >= (unsigned)m) key[u] = -1;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (key[u] >= 0) atomicAdd(&sm[key[u] + 1], 1);
+    __syncthreads();
+
+    // ---- inclusive scan of sm[0..m]: afterwards the first position of every column
+    const bool writes = it.row0 == 0 && it.f0 == 0 && m > 0;
+    const int chunk = (m + kThreads) / kThreads;
+    const int lo = tid * chunk, hi = min(lo + chunk, m + 1);
+    int sum = 0;
+    for (int c = lo; c < hi; ++c) sum += sm[c];
+    int incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int n = __shfl_up(incl, d);
+        if ((int)wl >= d) incl += n;
+    }
+    if (wl == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (uint32_t w = 0; w < wave; ++w) run += wave_sum[w];
+    for (int c = lo; c < hi; ++c) {
+        run += sm[c];
+        sm[c] = run;
+        if (writes) rpt_t[it.rpt_off + (uint32_t)c] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)                      // (sm[c] ends as the first position of column c + 1)
+        if (key[u] >= 0) pos[atomicAdd(&sm[key[u]], 1)] = (int)(tid + u * kThreads);
+    __syncthreads();
+    int place[4], row[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        place[u] = row[u] = 0;
+        if (key[u] < 0) continue;
+        const int p = (int)(tid + u * kThreads);
+        const int beg = key[u] > 0 ? sm[key[u] - 1] : 0, end = sm[key[u]];
+        int rank = 0;
+        for (int t = beg; t < end; ++t) rank += pos[t] < p ? 1 : 0;
+        place[u] = beg + rank;
+        row[u] = row_of[p];
+        if ((unsigned)row[u] >= (unsigned)m) row[u] = 0;   // (row pointers that leave the entry out)
+    }
+    __syncthreads();                                 // everyone has read positions and rows
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (key[u] >= 0) cv[place[u]] = make_int2(row[u] << (sh + 4), __float_as_int(a[u]));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // direct-to-LDS loads landed
+    __syncthreads();
+
+    // ---- rows, as in bspmm_lean_kernel
+    const uint32_t l = tid & ((1u << sh) - 1);
+    const char* bcol = lds + it.b_byte + (l << 4);
+    char* __restrict__ dst = reinterpret_cast<char*>(out + ((uint64_t)it.out_row * ld_out + (uint32_t)it.f0));
+    const uint32_t out_row_bytes = ld_out << 2;
+    const uint32_t row_end = (uint32_t)(it.row0 + it.nrows);
+    for (uint32_t r = (uint32_t)it.row0 + (tid >> sh); r < row_end; r += kThreads >> sh)
+        store_out<4>(reinterpret_cast<float*>(dst + (__umul24(r, out_row_bytes) + (l << 4))),
+                     gather_row(cv, bcol, r > 0 ? sm[r - 1] : 0, sm[r]));
+    if (writes)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (key[u] >= 0) {
+                colids_t[it.nz_off + (uint32_t)place[u]] = row[u];
+                values_t[it.nz_off + (uint32_t)place[u]] = a[u];
+            }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -3265,6 +3400,14 @@ hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int g
     return launch(merged ? bspmm_lean_kernel<true> : bspmm_lean_kernel<false>, grid, kThreads, lds_bytes, stream, items,
                   P.rpt, P.colids, P.values, P.in, P.out, (uint32_t)P.ld_in, (uint32_t)P.ld_out,
                   (uint32_t)(lds_bytes / 4), reinterpret_cast<const int32_t*>(P.w));
+}
+
+hipError_t launch_first_transposed(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, int32_t* rpt_t,
+                                   int32_t* colids_t, float* values_t, hipStream_t stream)
+{
+    if (grid <= 0) return hipSuccess;
+    return launch(bspmm_first_transposed_kernel, grid, kThreads, lds_bytes, stream, items, P.rpt, P.colids, P.values,
+                  P.in, P.out, (uint32_t)P.ld_in, (uint32_t)P.ld_out, rpt_t, colids_t, values_t);
 }
 
 // aligned: F % 4 == 0 and every row of every tile is float4 on 16 bytes; quads: F % 4 == 0 (the schedule

@@ -172,6 +172,44 @@ def test_transposed_csr_bit_exact(torch_cuda, oracle, maker):
     _check_transposed(torch_cuda, oracle, b, plan=plan)
 
 
+@pytest.mark.parametrize("F,sizes", [
+    # one row, nothing, one to four entries per lane and the edges between them, more rows than lanes,
+    # every entry in one column
+    (64, [(1, 1), (1, 7), (5, 0), (2, 256), (30, 257), (40, 512), (90, 513), (256, 300), (300, 1024), (700, 40)]),
+    (128, [(25, 90)] * 40), (100, [(33, 1000), (32, 100)]), (4, [(60, 700)] * 3),
+    (16, [(20, 60)] * 9000),                       # small operations packed four to a workgroup elsewhere
+])
+@pytest.mark.parametrize("one_column", [False, True])
+def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, one_column):
+    """Square operations whose transposed arrays do not exist yet: the product is bit for bit the one that
+    runs on built arrays, the arrays it leaves behind are the stable transpose, and replays of a captured
+    first run give it again."""
+    torch = torch_cuda
+    b = W.random_general(len(sizes) + F, F=F, shapes=[(n, n, z) for n, z in sizes])
+    if one_column:
+        b.colids[:] = 0
+    plan, built = K.Plan(b), K.Plan(b, options=K.make_options(flags=K.BUILD_TRANSPOSE))
+    dY = torch.from_numpy(b.dY).cuda()
+    want = built.run_transposed(dY, torch.zeros((b.n_b_rows, F), device="cuda"))
+    graph, replayed = torch.cuda.CUDAGraph(), torch.zeros((b.n_b_rows, F), device="cuda")
+    with torch.cuda.graph(graph):
+        plan.run_transposed(dY, replayed)
+    assert plan.info().transposed_built == 0
+    for _ in range(3):
+        replayed.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(replayed, want)
+    for _ in range(2):                             # the first run, and one on the arrays it built
+        got = plan.run_transposed(dY, torch.full((b.n_b_rows, F), float("nan"), device="cuda"))
+        torch.cuda.synchronize()
+        assert plan.info().transposed_built == 1 and torch.equal(got, want)
+    _, *arrays = oracle.csr_transpose(b.rows, b.cols, b.nnz, b.rpt_off, b.nz_off, b.rpt, b.colids, b.values)
+    for mine, ref in zip(plan.export_transposed(), arrays):
+        assert np.array_equal(mine.cpu().numpy(), ref)
+    _check_transposed(torch, oracle, b, plan=plan)
+
+
 # ---------------------------------------------------------------------------------------------
 # edge cases
 # ---------------------------------------------------------------------------------------------
