@@ -1045,12 +1045,16 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
 // copied as such.  Only a dense input that does not start on 16 bytes is copied word by word.
 //
 // Rows.  A row takes ceil(fw / 4) lanes of four floats, no power of two; the last lane stores what
-// is left of the row.  Operations whose rows average more than kLongRow entries take a lane per
-// float instead: the additions of a row are a serial chain, and four per entry and lane made
-// the chain of a row of 660 entries 2 us longer.
+// is left of the row.  Where rows average more than kLongRow entries and there are fewer of them than
+// lane groups, the groups share a row's entries (any_long_rows): the additions of a row are a serial chain of
+// LDS reads, and a row of 660 entries kept a launch waiting for 4 us (a lane per float of the row, as it
+// was before: transposed launches of 200 / 300 operations of 1 to 220 rows at F = 50 / 127 8.0 to 10.3 / 15.9 to 17.0
+// us, now 7.4 / 12.4, as long as the forward ones).
 // Bound: small launches the chain of item, staging and gather, large ones memory (900 operations of 1 to
 // 220 rows, F = 127: 100 MB in 22 us).  200 of them at F = 50: forward 15.9 -> 6.0 us, transposed (rows of up
-// to 660 entries) 33 -> 7.3 us against the general kernel's scalar path.
+// to 660 entries) 33 -> 6.5 us against the general kernel's scalar path.  Both directions of 200 at F = 50 / 800 at
+// F = 50 / 300 at F = 127 / 900 at F = 17, before and after the groups shared rows: 14.1 -> 13.1 / 31.7 -> 27.7 / 27.1 -> 24.1 /
+// 18.1 -> 16.1.
 // ---------------------------------------------------------------------------------------
 enum AnyMode {
     kAnyWindows = 1,   // the dense input starts on 16 bytes: rows are copied as 16-byte words
@@ -1064,36 +1068,33 @@ __device__ __forceinline__ uint32_t div_small(uint32_t n, float inv_d)
     return (uint32_t)(((float)n + 0.5f) * inv_d);
 }
 
-template <int VEC> struct Floats { typedef float type __attribute__((ext_vector_type(VEC))); };
-template <int VEC> struct FloatsAt4 { typedef float type __attribute__((ext_vector_type(VEC), aligned(4))); };
+typedef float Floats __attribute__((ext_vector_type(4)));
+typedef float FloatsAt4 __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int VEC, bool ALIGNED>
-__device__ __forceinline__ typename Floats<VEC>::type any_load(const void* p)
+template <bool ALIGNED> __device__ __forceinline__ Floats any_load(const void* p)
 {
-    using VT = typename Floats<VEC>::type;
     if constexpr (ALIGNED)
-        return *reinterpret_cast<const VT*>(p);
+        return *reinterpret_cast<const Floats*>(p);
     else
-        return *reinterpret_cast<const typename FloatsAt4<VEC>::type*>(p);
+        return *reinterpret_cast<const FloatsAt4*>(p);
 }
 
 // Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's floats of the
-// entry's dense row.  N entries in flight while there are as many, then four at a time with the
+// entry's dense row.  Eight entries in flight while there are as many, then four at a time with the
 // entries past the end left out (see gather_row).
-template <int VEC, typename Entry, typename Dense>
-__device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
+template <typename Entry, typename Dense>
+__device__ __forceinline__ Floats any_row(int p0, int p1, Entry entry, Dense dense)
 {
-    using VT = typename Floats<VEC>::type;
-    constexpr int N = VEC == 4 ? 8 : 16;
-    VT acc = 0.f;
+    constexpr int N = 8;
+    Floats acc = 0.f;
     int p = p0;
-    auto fma = [&](float a, const VT& b) {
+    auto fma = [&](float a, const Floats& b) {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(a, b[i], acc[i]);
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(a, b[i], acc[i]);
     };
     for (; p + N <= p1; p += N) {
         int2 e[N];
-        VT b[N];
+        Floats b[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) e[u] = entry(p + u);
 #pragma unroll
@@ -1104,41 +1105,29 @@ __device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, En
     const int last = p1 - 1;
     for (; p < p1; p += 4) {
         int2 e[4];
-        VT b[4];
+        Floats b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) e[u] = entry(min(p + u, last));
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = dense(e[u].x);
         fma(__int_as_float(e[0].y), b[0]);
-        if constexpr (VEC == 4) {
-            auto f4 = [](const VT& v) { return make_float4(v[0], v[1], v[2], v[3]); };
-            float4 sum = f4(acc);
-            add_rest(sum, p1 - p, __int_as_float(e[1].y), f4(b[1]), __int_as_float(e[2].y), f4(b[2]),
-                     __int_as_float(e[3].y), f4(b[3]));
-            acc[0] = sum.x, acc[1] = sum.y, acc[2] = sum.z, acc[3] = sum.w;
-        } else {
-#pragma unroll
-            for (int u = 1; u < 4; ++u) {
-                const VT old = acc;
-                fma(__int_as_float(e[u].y), b[u]);
-                if (p + u >= p1) acc = old;
-            }
-        }
+        auto f4 = [](const Floats& v) { return make_float4(v[0], v[1], v[2], v[3]); };
+        float4 sum = f4(acc);
+        add_rest(sum, p1 - p, __int_as_float(e[1].y), f4(b[1]), __int_as_float(e[2].y), f4(b[2]),
+                 __int_as_float(e[3].y), f4(b[3]));
+        acc[0] = sum.x, acc[1] = sum.y, acc[2] = sum.z, acc[3] = sum.w;
     }
     return acc;
 }
 
-// The lane's `n` floats of an output row (n < VEC on the last lane of a row only).  Rows off 16
+// The lane's `n` floats of an output row (n < 4 on the last lane of a row only).  Rows off 16
 // bytes share lines with their neighbours, so only aligned rows are stored past the caches.
-template <int VEC, bool ALIGNED>
-__device__ __forceinline__ void any_store(float* p, const typename Floats<VEC>::type& v, int n)
+template <bool ALIGNED> __device__ __forceinline__ void any_store(float* p, const Floats& v, int n)
 {
-    if constexpr (VEC == 1) {
-        *p = v[0];
-    } else if constexpr (ALIGNED) {
-        __builtin_nontemporal_store(v, reinterpret_cast<typename Floats<VEC>::type*>(p));
-    } else if (n >= VEC) {
-        *reinterpret_cast<typename FloatsAt4<VEC>::type*>(p) = v;
+    if constexpr (ALIGNED) {
+        __builtin_nontemporal_store(v, reinterpret_cast<Floats*>(p));
+    } else if (n >= 4) {
+        *reinterpret_cast<FloatsAt4*>(p) = v;
     } else {
         p[0] = v[0];
         if (n > 1) p[1] = v[1];
@@ -1146,49 +1135,86 @@ __device__ __forceinline__ void any_store(float* p, const typename Floats<VEC>::
     }
 }
 
-// Rows [0, nrows) of an item in lanes of VEC floats: row(i, p0, p1) gives row i's entries, entry(p) the
+// Rows [0, nrows) of an item in lanes of four floats: row(i, p0, p1) gives row i's entries, entry(p) the
 // (key, value) of one, dense(key, l, n) the floats at l of the dense row it names, n of them in the row.
-template <int VEC, bool ALIGNED, typename Row, typename Entry, typename Dense>
+template <bool ALIGNED, typename Row, typename Entry, typename Dense>
 __device__ __forceinline__ void any_rows(uint32_t fw, int nrows, float* __restrict__ dst, int64_t ld_out, Row row,
                                          Entry entry, Dense dense)
 {
-    const uint32_t nvec = (fw + VEC - 1) / VEC, groups = kThreads / nvec;
+    const uint32_t nvec = (fw + 3) / 4, groups = kThreads / nvec;
     const uint32_t g = div_small(threadIdx.x, 1.f / (float)nvec), l = threadIdx.x - g * nvec;
     if (g >= groups) return;
-    const int n = (int)(fw - VEC * l);
-    float* p = dst + (g * ld_out + VEC * l);
+    const int n = (int)(fw - 4 * l);
+    float* p = dst + (g * ld_out + 4 * l);
     const int64_t step = groups * ld_out;
     for (int i = g; i < nrows; i += groups, p += step) {
         int p0, p1;
         row(i, p0, p1);
-        any_store<VEC, ALIGNED>(p, any_row<VEC>(p0, p1, entry, [&](int key) {
-            return dense.template operator()<VEC>(key, (int)(VEC * l), n);
-        }), n);
+        any_store<ALIGNED>(p, any_row(p0, p1, entry, [&](int key) { return dense(key, (int)(4 * l), n); }), n);
     }
+}
+
+// The same for few long rows: `parts` lane groups share a row, each with its share of the entries, and the
+// first of them adds up the partial sums, in order, from `sums` (LDS that nobody reads any more once the
+// workgroup has met).  Every lane of the workgroup comes here; nrows parts <= groups of lanes.
+template <bool ALIGNED, typename Row, typename Entry, typename Dense>
+__device__ __forceinline__ void any_long_rows(uint32_t fw, int nrows, int parts, float* __restrict__ dst, int64_t ld_out,
+                                              float4* sums, Row row, Entry entry, Dense dense)
+{
+    const uint32_t nvec = (fw + 3) / 4;
+    const uint32_t g = div_small(threadIdx.x, 1.f / (float)nvec), l = threadIdx.x - g * nvec;
+    const uint32_t i = div_small(g, 1.f / (float)parts), part = g - i * parts;
+    const int n = (int)(fw - 4 * l);
+    Floats acc = 0.f;
+    const bool mine = i < (uint32_t)nrows;
+    if (mine) {
+        int p0, p1;
+        row((int)i, p0, p1);
+        const float share = (float)(p1 - p0) / (float)parts;
+        const int from = p0 + (int)(share * (float)part);
+        const int to = part + 1 == (uint32_t)parts ? p1 : p0 + (int)(share * (float)(part + 1));
+        acc = any_row(from, to, entry, [&](int key) { return dense(key, (int)(4 * l), n); });
+    }
+    __syncthreads();
+    float4* const at = sums + threadIdx.x;
+    if (mine) *at = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (!mine || part != 0) return;
+    for (int s = 1; s < parts; ++s) {
+        const float4 more = at[s * nvec];
+        acc[0] += more.x, acc[1] += more.y, acc[2] += more.z, acc[3] += more.w;
+    }
+    any_store<ALIGNED>(dst + ((int64_t)i * ld_out + 4 * l), acc, n);
+}
+
+// Lane groups to a row of an item of long rows: what the workgroup has, up to sixteen; one where the partial sums
+// have no room in `bytes` of LDS.
+__device__ __forceinline__ int long_row_parts(uint32_t fw, int nrows, int bytes)
+{
+    const uint32_t groups = kThreads / ((fw + 3) / 4);
+    return bytes < (int)(kThreads * sizeof(float4)) ? 1 : (int)min(groups / (uint32_t)max(nrows, 1), 16u);
 }
 
 // A lane's floats out of the LDS tile (the last lane of a row may read up to three words past
 // the row: LDS of this item) and out of global memory (nothing past the row's end is read).
 template <bool ALIGNED> struct TileRows {
     const char* tile;
-    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int off, int l, int) const
+    __device__ __forceinline__ Floats operator()(int off, int l, int) const
     {
-        return any_load<VEC, ALIGNED>(tile + off + 4 * l);
+        return any_load<ALIGNED>(tile + off + 4 * l);
     }
 };
 template <bool ALIGNED> struct GlobalRows {
     const float* src;
     int64_t ld;
-    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int c, int l, int n) const
+    __device__ __forceinline__ Floats operator()(int c, int l, int n) const
     {
         const float* p = src + (c * ld + l);
-        if (ALIGNED || n >= VEC) return any_load<VEC, ALIGNED>(p);
-        typename Floats<VEC>::type v = 0.f;
+        if (ALIGNED || n >= 4) return any_load<ALIGNED>(p);
+        Floats v = 0.f;
         v[0] = p[0];
-        if constexpr (VEC == 4) {
-            if (n > 1) v[1] = p[1];
-            if (n > 2) v[2] = p[2];
-        }
+        if (n > 1) v[1] = p[1];
+        if (n > 2) v[2] = p[2];
         return v;
     }
 };
@@ -1227,13 +1253,14 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const
         p0 = min(max(sm[i] - pbeg, 0), p1);
     };
     auto lds_entry = [&](int p) { return cv[p]; };
-    const bool long_rows = cnt > kLongRow * nrows;
+    const uint32_t sums = (uint32_t)round_up((int)cv_off, 4);
+    const int parts = fits && cnt > kLongRow * nrows ? long_row_parts(fw, nrows, 4 * ((int)lds_words - (int)sums)) : 1;
     if (!fits)
-        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, global_entry, dense);
-    else if (long_rows)
-        any_rows<1, false>(fw, nrows, dst, ld_out, row, lds_entry, dense);
+        any_rows<ALIGNED>(fw, nrows, dst, ld_out, row, global_entry, dense);
+    else if (parts > 1)
+        any_long_rows<ALIGNED>(fw, nrows, parts, dst, ld_out, reinterpret_cast<float4*>(sm + sums), row, lds_entry, dense);
     else
-        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, lds_entry, dense);
+        any_rows<ALIGNED>(fw, nrows, dst, ld_out, row, lds_entry, dense);
 }
 
 // mode: kAnyWindows, kAnyTight (ALIGNED implies both).
@@ -1355,10 +1382,13 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
         p1 = sm[it.row0 + i + 1];
     };
     auto lds_entry = [&](int p) { return cv[p]; };
-    if (nnz > kLongRow * m)
-        any_rows<1, false>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<false>{bs});
+    const int sums = round_up(it.cv_byte, 16);
+    const int parts = nnz > kLongRow * m ? long_row_parts(fw, it.nrows, it.b_byte - sums + 4 * k * (int)stride) : 1;
+    if (parts > 1)
+        any_long_rows<ALIGNED>(fw, it.nrows, parts, dst, ld_out, reinterpret_cast<float4*>(lds + sums), row, lds_entry,
+                               TileRows<ALIGNED>{bs});
     else
-        any_rows<4, ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
+        any_rows<ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
 }
 
 // Once per plan and direction: the position of every row block's entries goes into its item.

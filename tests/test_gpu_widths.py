@@ -51,6 +51,23 @@ def test_every_width_both_directions(oracle, F):
         _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
 
 
+@pytest.mark.parametrize("F", [1, 3, 17, 50, 127, 301])
+def test_lane_groups_share_long_rows(oracle, F):
+    """Around the line from which a row counts as long (sixteen entries on average), around one and two lane
+    groups per row, with and without room for the partial sums, an empty row and one that holds everything,
+    rows gathered from memory."""
+    import torch
+    shapes = [(m, k, z) for m in (1, 2, 3, 9, 10, 19, 37, 128, 129) for k, z in ((1, 16 * m), (3, 17 * m), (90, 40 * m))]
+    b = W.random_general(31 + F, F=F, shapes=shapes + [(2, 6000, 900), (1, 6000, 33)], with_dY=False)
+    skew = W.random_general(32 + F, F=F, shapes=[(4, 150, 660)], with_dY=False)
+    skew.rpt[:] = [0, 0, 659, 660, 660]
+    for b in (b, skew):
+        plan = K.Plan(b)
+        got = _run(torch, plan, b, False, 0, 0, 0, 0)
+        ref, S = oracle.forward_batch(b)
+        _check(got, ref, S, b.c_row_off, b.rows)
+
+
 @pytest.mark.parametrize("F", [1, 3, 50, 127])
 def test_operations_without_columns_read_nothing(F):
     """No operation has columns, so there is no dense input at all, wherever the (empty) blocks start."""
