@@ -7,16 +7,25 @@
 // stream come straight from PyTorch's C++ objects.  Making a plan from a data loader's host arrays
 // took 110 us for 128 graphs: three blocking copies, ctypes views of ten arrays, and the host
 // schedule; now the arrays and the plan's tables go over in one copy (staging.hpp) behind one call.
+// The differentiable product (autograd.py) is here for the same reason.
 // Only argument marshalling: no step of the path is here.
 #define PY_SSIZE_T_CLEAN
 #define NPY_NO_DEPRECATED_API NPY_1_7_API_VERSION
 #include <Python.h>
 #include <numpy/arrayobject.h>
 
+#include <ATen/core/grad_mode.h>
 #include <ATen/ops/empty.h>
+#include <ATen/ops/zeros.h>
+#include <c10/core/impl/PyInterpreter.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 
 #include <cstdint>
 #include <cstring>
@@ -28,6 +37,7 @@ namespace {
 
 PyObject* s_data_ptr;        // interned method names
 PyObject* s_cuda_stream;
+PyObject* s_handle;
 PyObject* g_check;           // bspmm._check(code, where): raises BspmmError
 PyObject* g_ld;              // bspmm._ld(tensor, width): every case the fast path below leaves out
 
@@ -404,6 +414,94 @@ PyObject* create_coo(PyObject* const* a, Py_ssize_t n)
     return rc == BSPMM_OK ? made(plan, b, memory, 0) : finish(rc, where, Py_None);
 }
 
+// ---- the differentiable product
+
+// Room for a product: the rows that belong to no operation are zero (autograd.py, _output).
+at::Tensor room(bspmm_plan* plan, bool transposed, int64_t rows, int64_t F, const at::Device& device)
+{
+    const auto options = at::TensorOptions().dtype(at::kFloat).device(device);
+    return plan && bspmm::covered_rows(plan, transposed) >= rows ? at::empty({rows, F}, options) : at::zeros({rows, F}, options);
+}
+
+// The backward pass of autograd.py's BatchedSpMM.  It has the plan object, not its handle: a plan that was closed
+// in between is an error there as here.
+struct BatchedSpmmBackward : torch::autograd::Node {
+    PyObject* plan;
+    int64_t F, n_b_rows, n_c_rows;
+    BatchedSpmmBackward(PyObject* p, int64_t f, int64_t nb, int64_t nc) : plan(Py_NewRef(p)), F(f), n_b_rows(nb), n_c_rows(nc) {}
+    ~BatchedSpmmBackward() override
+    {
+        if (!Py_IsInitialized()) return;
+        const PyGILState_STATE lock = PyGILState_Ensure();
+        Py_DECREF(plan);
+        PyGILState_Release(lock);
+    }
+    std::string name() const override { return "BatchedSpMMBackward"; }
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override
+    {
+        const at::Device device = input_metadata(0).device();
+        at::Tensor dY = grads.at(0).defined() ? grads[0].contiguous()
+                                              : at::zeros({n_c_rows, F}, at::TensorOptions().dtype(at::kFloat).device(device));
+        struct Lock {
+            PyGILState_STATE state = PyGILState_Ensure();
+            ~Lock() { PyGILState_Release(state); }
+        } lock;
+        void* handle = nullptr;
+        PyObject* h = PyObject_GetAttr(plan, s_handle);
+        const bool ok = h && get_ptr(h, &handle);
+        Py_XDECREF(h);
+        if (ok) {
+            at::Tensor G = room(static_cast<bspmm_plan*>(handle), true, n_b_rows, F, device);
+            void* const in = dY.data_ptr();
+            void* const out = G.data_ptr();
+            PyObject* r = finish(call<bspmm_run_transposed>(handle, in, out, dY.size(0) >= 2 ? dY.stride(0) : F, F,
+                                                            c10::hip::getCurrentHIPStream().stream()),
+                                 "bspmm_run_transposed", Py_None);
+            Py_XDECREF(r);
+            if (r) return {G};
+        }
+        python_error e;
+        e.persist();
+        throw e;
+    }
+};
+
+// (plan object, its handle, F, B, rows of C or None) -> C, or None for what BatchedSpMM.apply decides: other
+// types and devices, tensor subclasses, active modes, tracing, forward-mode gradients.
+PyObject* batched_spmm(PyObject* const* a, Py_ssize_t n)
+{
+    void *plan, *stream;
+    int64_t F, rows;
+    if (!arity("batched_spmm", n, 5) || !get_ptr(a[1], &plan) || !get_i64(a[2], &F)) return nullptr;
+    if (!is_tensor(a[3]) || (a[4] != Py_None && !PyLong_CheckExact(a[4]))) Py_RETURN_NONE;
+    const at::Tensor& given = THPVariable_Unpack(a[3]);
+    if (!given.is_cuda() || given.scalar_type() != at::kFloat || given.layout() != at::kStrided || given.dim() != 2 ||
+        given.size(0) < 2 || given._fw_grad(0).defined() || c10::impl::dispatch_mode_enabled() ||
+        at::impl::torch_function_mode_enabled() || torch::jit::tracer::isTracing() || given.unsafeGetTensorImpl()->is_python_dispatch())
+        Py_RETURN_NONE;
+    if (a[4] == Py_None)
+        rows = given.size(0);
+    else if (!get_i64(a[4], &rows))
+        return nullptr;
+    if (!get_stream(Py_None, &stream)) return nullptr;
+    const bool differentiable = at::GradMode::is_enabled() && given.requires_grad();
+    at::Tensor B, C;
+    {
+        at::NoGradGuard none;
+        B = given.contiguous();
+        C = room(static_cast<bspmm_plan*>(plan), false, rows, F, B.device());
+    }
+    const int rc = call<bspmm_run>(plan, B.data_ptr(), C.data_ptr(), B.stride(0), F, stream);
+    if (rc != BSPMM_OK) return finish(rc, "bspmm_run", Py_None);
+    if (differentiable) {
+        auto node = std::shared_ptr<BatchedSpmmBackward>(new BatchedSpmmBackward(a[0], F, given.size(0), rows),
+                                                         torch::autograd::deleteNode);
+        node->set_next_edges(torch::autograd::collect_next_edges(given));
+        torch::autograd::set_history(C, node);
+    }
+    return THPVariable_Wrap(std::move(C));
+}
+
 // (plan, transposed) -> rows from the first on that every product writes
 PyObject* covered_rows(PyObject* const* a, Py_ssize_t n)
 {
@@ -452,6 +550,7 @@ PyMethodDef methods[] = {
     fast<plan_run>("plan_run"), fast<plan_run_transposed>("plan_run_transposed"), fast<plan_run_gcn>("plan_run_gcn"),
     fast<run>("run"), fast<run_transposed>("run_transposed"), fast<run_gcn>("run_gcn"),
     fast<covered_rows>("covered_rows"), fast<takes_lean_kernel>("takes_lean_kernel"), fast<create>("create"), fast<create_coo>("create_coo"),
+    fast<batched_spmm>("batched_spmm"),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Plan creation and run calls of libbspmm.", -1, methods,
                       nullptr, nullptr, nullptr, nullptr};
@@ -463,6 +562,7 @@ PyMODINIT_FUNC PyInit__native(void)
     import_array();
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    if (!s_data_ptr || !s_cuda_stream) return nullptr;
+    s_handle = PyUnicode_InternFromString("handle");
+    if (!s_data_ptr || !s_cuda_stream || !s_handle) return nullptr;
     return PyModule_Create(&module);
 }

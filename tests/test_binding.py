@@ -369,3 +369,62 @@ def test_plan_made_on_another_stream_waits_for_what_used_its_memory_before(coo):
     plan.run(B, C, side)
     torch.cuda.synchronize()
     assert np.all(np.abs(C.cpu().numpy() - C0) <= 1e-5 * S)
+
+
+@pytest.mark.gpu
+def test_native_autograd_is_the_class():
+    """batched_spmm on plain tensors gives what BatchedSpMM.apply gives, and leaves to it what it does not take."""
+    import torch
+    from paper_1903_11409_amd import autograd as A
+    b = W.config5_skewed(graphs=40, F=64, asymmetric=True)
+    plan = K.Plan(b)
+    B = torch.from_numpy(b.B).cuda()
+    dY = torch.from_numpy(b.dY).cuda()
+    wide = torch.zeros((b.n_b_rows, 80), device="cuda")
+    wide[:, :64] = B
+    inputs = [B, wide[:, :64], B.t().contiguous().t(), torch.nn.Parameter(B.clone())]
+    grads = [dY, torch.ones((1, 1), device="cuda").expand_as(dY), dY.t().contiguous().t()]
+    for x in inputs:
+        for g in grads:
+            out = []
+            for f in (A.batched_spmm, A.BatchedSpMM.apply):
+                leaf = x.detach().requires_grad_()
+                C = f(plan, leaf * 2.0)
+                assert C.grad_fn.name() == "BatchedSpMMBackward"
+                C.backward(g, retain_graph=True)
+                C.backward(g)
+                out.append((C.detach(), leaf.grad))
+            torch.cuda.synchronize()
+            assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    with torch.no_grad():
+        assert A.batched_spmm(plan, inputs[3]).grad_fn is None
+    assert A.batched_spmm(plan, B, b.n_c_rows + 3).shape == (b.n_c_rows + 3, 64)
+    assert not A.batched_spmm(plan, B).requires_grad
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):                       # backward on the stream of forward
+        leaf = B.clone().requires_grad_()
+        A.batched_spmm(plan, leaf).backward(dY)
+    side.synchronize()
+    assert torch.equal(leaf.grad, plan.run_transposed(dY, torch.empty_like(B)))
+
+    def message(f, *args):
+        with pytest.raises(Exception) as e:
+            f(plan, *args)
+        return str(e.value).splitlines()[0]
+
+    for x in (B.cpu(), B.double(), B[:, :32]):
+        assert message(A.batched_spmm, x) == message(A.BatchedSpMM.apply, x)
+    under = lambda f: lambda p: torch.func.grad(lambda x: f(p, x).sum())(B)
+    assert message(under(A.batched_spmm)) == message(under(A.BatchedSpMM.apply))
+
+    def forward_mode(f):
+        def go(p):
+            with torch.autograd.forward_ad.dual_level():
+                f(p, torch.autograd.forward_ad.make_dual(B, B))
+        return go
+    assert message(forward_mode(A.batched_spmm)) == message(forward_mode(A.BatchedSpMM.apply))
+    C = A.batched_spmm(plan, B.clone().requires_grad_())
+    plan.close()
+    with pytest.raises(K.BspmmError):
+        C.backward(dY)
