@@ -934,12 +934,27 @@ __device__ __forceinline__ float4 gather_row_global(const int2* cv, const char* 
     return acc;
 }
 
+// Entries of a row block: its first one and how many, as its item has them.  The first run of a plan and
+// direction finds them in the row pointers, a round trip to memory more, and leaves them in the item (a launch of
+// its own for that cost a batch that is new every step 3.5 us of the host's time for each direction: 239 graphs
+// of 8 to 500 nodes at F = 256 62.5 -> 57.5 us, 100 at F = 128 38 -> 33).  Both in one 8-byte store: whoever reads the item meanwhile has none or both.
+__device__ __forceinline__ int2 block_entries(const LeanItem& it, const LeanItem* item, const int32_t* __restrict__ rpt)
+{
+    if (it.count >= 0) return make_int2(it.tile_vecs, it.count);
+    const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
+    const int from = min(max(rp[0], 0), it.nnz), to = min(max(rp[it.nrows], 0), it.nnz);
+    const int2 range = make_int2(from, max(to - from, 0));
+    static_assert(offsetof(LeanItem, tile_vecs) % 8 == 0 && offsetof(LeanItem, count) == offsetof(LeanItem, tile_vecs) + 4, "one store");
+    if (threadIdx.x == 0) *reinterpret_cast<int2*>(const_cast<int32_t*>(&item->tile_vecs)) = range;
+    return range;
+}
+
 // Row block of the generic bin in a lean launch.  ONE round trip to memory brings the block's
-// row pointers and its entries: their position comes with the item (lean_hints_kernel wrote it
-// there once), where bspmm_kernel needs the row pointers before it can ask for the entries.
+// row pointers and its entries: their position comes with the item (see block_entries), where
+// bspmm_kernel needs the row pointers before it can ask for the entries.
 // (Fetching the block's share of the dense rows into L2 ahead of the gathers was measured and
 // changed nothing: the gathers are bound by L2 throughput.)
-__device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
+__device__ __forceinline__ void lean_row_block(const LeanItem& it, const LeanItem* item, int* sm,
                                                const int32_t* __restrict__ rpt,
                                                const int32_t* __restrict__ colids,
                                                const float* __restrict__ values,
@@ -951,8 +966,9 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, int* sm,
     const int sh = it.sh;
     const uint32_t nvec = 1u << sh;
     const uint32_t l = tid & (nvec - 1), g = tid >> sh, groups = kThreads >> sh;
-    const int pbeg = min(max(it.tile_vecs, 0), nnz);
-    const int cnt = min(max(it.count, 0), nnz - pbeg);
+    const int2 range = block_entries(it, item, rpt);
+    const int pbeg = min(max(range.x, 0), nnz);
+    const int cnt = min(max(range.y, 0), nnz - pbeg);
     const uint32_t row_bytes = ld_in << 2;
     const char* __restrict__ src =
         reinterpret_cast<const char*>(in + ((uint64_t)it.in_row * ld_in + (uint32_t)it.f0));
@@ -1221,7 +1237,8 @@ template <bool ALIGNED> struct GlobalRows {
 
 // Row block of the generic bin (see lean_row_block): dense rows gathered from global memory.
 template <bool ALIGNED>
-__device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const int32_t* __restrict__ rpt,
+__device__ __forceinline__ void any_row_block(const LeanItem& it, const LeanItem* item, int* sm,
+                                              const int32_t* __restrict__ rpt,
                                               const int32_t* __restrict__ colids,
                                               const float* __restrict__ values, const float* __restrict__ in,
                                               float* __restrict__ out, int64_t ld_in, int64_t ld_out,
@@ -1230,8 +1247,9 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, int* sm, const
     const uint32_t tid = threadIdx.x;
     const int nrows = it.nrows, k = it.k, nnz = it.nnz;
     const uint32_t fw = max((uint32_t)it.flags >> 8, 1u);
-    const int pbeg = min(max(it.tile_vecs, 0), nnz);
-    const int cnt = min(max(it.count, 0), nnz - pbeg);
+    const int2 range = block_entries(it, item, rpt);
+    const int pbeg = min(max(range.x, 0), nnz);
+    const int cnt = min(max(range.y, 0), nnz - pbeg);
     const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
     const int32_t* __restrict__ ci = colids + it.nz_off + (uint32_t)pbeg;
     const float* __restrict__ va = values + it.nz_off + (uint32_t)pbeg;
@@ -1276,7 +1294,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     const LeanItem it = items[blockIdx.x];
     if (it.flags & 8) return;  // (small items packed for the lean kernel: this launch has a workgroup for each)
     if (it.flags & 2) {        // (the same for the whole workgroup)
-        any_row_block<ALIGNED>(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+        any_row_block<ALIGNED>(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         return;
     }
     const int m = it.m, k = it.k, nnz = it.nnz;
@@ -1389,20 +1407,6 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
                                TileRows<ALIGNED>{bs});
     else
         any_rows<ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
-}
-
-// Once per plan and direction: the position of every row block's entries goes into its item.
-__global__ void lean_hints_kernel(LeanItem* items, int n, const int32_t* __restrict__ rpt)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    LeanItem& it = items[i];
-    if ((it.flags & 2) == 0 || it.nrows <= 0) return;
-    const int32_t* rp = rpt + it.rpt_off;
-    const int a = min(max(rp[it.row0], 0), it.nnz);
-    const int b = min(max(rp[it.row0 + it.nrows], 0), it.nnz);
-    it.tile_vecs = a;
-    it.count = max(b - a, 0);
 }
 
 // A small operation on one wavefront of a lean launch (four of them share a workgroup, see plain_schedule):
@@ -1518,7 +1522,7 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     asm volatile("" ::"s"(out), "s"(ld_out));
     if (it.flags & 10) {       // (the same for the whole workgroup)
         if (it.flags & 2) {
-            lean_row_block(it, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+            lean_row_block(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         } else {
             const int w = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
             if (w < it.count) {
@@ -3450,12 +3454,6 @@ hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool a
     return launch(aligned ? bspmm_any_kernel<true> : bspmm_any_kernel<false>, grid, kThreads, lds_bytes, stream, items,
                   P.rpt, P.colids, P.values, P.in, P.out, P.ld_in, P.ld_out, (uint32_t)(lds_bytes / 4),
                   (windows ? kAnyWindows : 0) | (quads ? kAnyTight : 0), reinterpret_cast<const int32_t*>(P.w));
-}
-
-hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream)
-{
-    if (n <= 0) return hipSuccess;
-    return launch(lean_hints_kernel, (n + 255) / 256, 256, 0, stream, items, n, rpt);
 }
 
 using FrontFn = void (*)(const LaunchParams);

@@ -210,6 +210,36 @@ def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, on
     _check_transposed(torch, oracle, b, plan=plan)
 
 
+@pytest.mark.parametrize("F", [50, 64, 300])
+@pytest.mark.parametrize("captured_first", [False, True])
+def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, captured_first):
+    """Operations too large for LDS: the first run of a direction reads the entry ranges of its row blocks from
+    the row pointers, later ones from the items; both the same, eager or replayed, one row of all entries and
+    empty blocks among them."""
+    torch = torch_cuda
+    b = W.random_general(41, F=F, shapes=[(1200, 1500, 4000), (600, 3000, 40), (9, 9, 20), (2000, 700, 0)])
+    b.rpt[1:600] = 0                               # of the first operation: blocks without entries, then a full row
+    plan = K.Plan(b)
+    sides = [(plan.run, b.B, b.n_c_rows, oracle.forward_batch, b.c_row_off, b.rows),
+             (plan.run_transposed, b.dY, b.n_b_rows, oracle.transposed_batch, b.b_row_off, b.cols)]
+    for run, operand, rows, reference, off, length in sides:
+        X = torch.from_numpy(operand).cuda()
+        results = []
+        if captured_first:
+            graph, out = torch.cuda.CUDAGraph(), torch.full((rows, F), SENTINEL, device="cuda")
+            with torch.cuda.graph(graph):
+                run(X, out)
+            for _ in range(3):
+                out.fill_(SENTINEL)
+                graph.replay()
+                results.append(out.clone())
+        results += [run(X, torch.full((rows, F), SENTINEL, device="cuda")) for _ in range(3)]
+        torch.cuda.synchronize()
+        assert all(torch.equal(r, results[0]) for r in results)
+        ref, S = reference(b)
+        _assert_close(results[0].cpu().numpy(), ref, S, _owned_rows(off, length, rows), f"row blocks F={F}")
+
+
 # ---------------------------------------------------------------------------------------------
 # edge cases
 # ---------------------------------------------------------------------------------------------
