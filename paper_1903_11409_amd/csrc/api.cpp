@@ -21,10 +21,11 @@
 namespace bspmm {
 hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec4, bool slices,
                         bool hubs, bool merged, hipStream_t stream);
-hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged,
+hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged, bool first,
                              hipStream_t stream);
-hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, int grid,
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, bool first, int grid,
                             int lds_bytes, hipStream_t stream);
+hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream);
 hipError_t launch_first_transposed(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, int32_t* rpt_t,
                                    int32_t* colids_t, float* values_t, hipStream_t stream);
 hipError_t launch_bspmm_gcn(const LaunchParams& P, int grid, int lds_bytes, bool accumulate,
@@ -125,7 +126,8 @@ struct bspmm_plan {
     bool sorts_in_run = false;             // ... and the first transposed run may build the transposed arrays itself
     int32_t lean_rows[2] = {0, 0};         // most input rows / output rows of an operation, or of a summed
     int32_t lean_out_rows[2] = {0, 0};     // set that is one item: bounds of the lean kernel's 32-bit offsets
-    bool lean_blocks[2] = {false, false};  // the lean table has row blocks of the generic bin
+    bool lean_blocks[2] = {false, false};  // the lean table has row blocks of the generic bin ...
+    bool lean_ranges[2] = {false, false};  // ... and a run has left their entry ranges in it
     StagedCopy upload;          // the copy of the tables from pinned memory, until it is known to have run ...
     hipStream_t upload_stream = nullptr;   // ... and the stream it was enqueued on
     hipEvent_t copied = nullptr;           // ... or the event behind the copy from pageable memory
@@ -666,7 +668,6 @@ void make_lean_items(bspmm_plan& p, int d)
                 t.tile_vecs = w.k << sh;
             } else {
                 t.flags |= 2;    // a row block: its entry range is filled in on the device
-                t.count = -1;
                 p.lean_blocks[d] = true;
             }
         }
@@ -1136,6 +1137,22 @@ int enqueue_layer_rows(bspmm_plan* p, hipStream_t s)
     return BSPMM_OK;
 }
 
+// The entry ranges of row blocks ahead of the first run, which finds them itself otherwise (for d = 1 after the
+// transposed CSR is built).
+int enqueue_ranges(bspmm_plan* p, int d, hipStream_t s)
+{
+    if (p->lean_ranges[d] || !p->lean_blocks[d] || p->lean_items[d].empty()) return BSPMM_OK;
+    const int32_t* rpt;
+    const int32_t* colids;
+    const float* values;
+    csr_of_direction(p, d, &rpt, &colids, &values);
+    const hipError_t e = launch_lean_hints(reinterpret_cast<LeanItem*>(p->ws + p->lay.lean[d]),
+                                           (int)p->lean_items[d].size(), rpt, s);
+    if (e != hipSuccess) return hip_fail(e);
+    p->lean_ranges[d] = !capturing(s);
+    return BSPMM_OK;
+}
+
 // Rows of both operands are whole float4 on 16 bytes.
 bool on_quads(const bspmm_plan* p, const float* in, const float* out, int64_t ld_in, int64_t ld_out)
 {
@@ -1210,14 +1227,16 @@ int run_direction(bspmm_plan* p, int d, const float* in, float* out, int64_t ld_
         return e == hipSuccess ? BSPMM_OK : hip_fail(e);
     }
     const LeanItem* items = reinterpret_cast<const LeanItem*>(p->ws + p->lay.lean[d]);
+    const bool first = p->lean_blocks[d] && !p->lean_ranges[d];
     hipError_t e;
     if (vec4 && takes_lean_kernel(p, d, ld_in, ld_out)) {
-        e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, !sc.merged_sets.empty(), s);
+        e = launch_bspmm_lean(items, P, sc.launch_grid, sc.lds_words * 4, !sc.merged_sets.empty(), first, s);
     } else {
         // (the table's packed items follow the launch's own: here each is a workgroup)
         const int grid = (int)p->lean_items[p->lean_shared ? 0 : d].size();
-        e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, grid, sc.lds_words * 4, s);
+        e = launch_bspmm_any(items, P, vec4, p->F % 4 == 0, first, grid, sc.lds_words * 4, s);
     }
+    if (e == hipSuccess && first) p->lean_ranges[d] = !capturing(s);
     return e == hipSuccess ? BSPMM_OK : hip_fail(e);
 }
 
@@ -1466,6 +1485,8 @@ int upload_plan(bspmm_plan* p, const bspmm_options* options, void* workspace,
         if (rc == BSPMM_OK) rc = enqueue_layer_rows(p, s);
         if (rc == BSPMM_OK && p->transposed_supported) rc = enqueue_build(p, s);
         if (rc == BSPMM_OK && p->transposed_supported) rc = enqueue_merge(p, 1, s);
+        if (rc == BSPMM_OK) rc = enqueue_ranges(p, 0, s);
+        if (rc == BSPMM_OK && p->transposed_supported) rc = enqueue_ranges(p, 1, s);
         return rc;
     }
     return BSPMM_OK;

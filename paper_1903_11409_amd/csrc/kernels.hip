@@ -935,17 +935,27 @@ __device__ __forceinline__ float4 gather_row_global(const int2* cv, const char* 
 }
 
 // Entries of a row block: its first one and how many, as its item has them.  The first run of a plan and
-// direction finds them in the row pointers, a round trip to memory more, and leaves them in the item (a launch of
-// its own for that cost a batch that is new every step 3.5 us of the host's time for each direction: 239 graphs
-// of 8 to 500 nodes at F = 256 62.5 -> 57.5 us, 100 at F = 128 38 -> 33).  Both in one 8-byte store: whoever reads the item meanwhile has none or both.
-__device__ __forceinline__ int2 block_entries(const LeanItem& it, const LeanItem* item, const int32_t* __restrict__ rpt)
+// direction (FIRST) finds them in the row pointers, a round trip to memory more, and leaves them in the item (a
+// launch of its own for that cost a batch that is new every step 3.5 us of the host's time for each direction:
+// 239 graphs of 8 to 500 nodes at F = 256 62.5 -> 57.5 us, 100 at F = 128 38 -> 33).  A kernel of its own: one that asks
+// its items whether they have been filled in costs later runs 2 to 6 % (1333 graphs at F = 32 14.7 -> 15.6).
+__device__ __forceinline__ int2 row_block_range(const LeanItem& it, const int32_t* __restrict__ rpt)
 {
-    if (it.count >= 0) return make_int2(it.tile_vecs, it.count);
     const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
     const int from = min(max(rp[0], 0), it.nnz), to = min(max(rp[it.nrows], 0), it.nnz);
-    const int2 range = make_int2(from, max(to - from, 0));
-    static_assert(offsetof(LeanItem, tile_vecs) % 8 == 0 && offsetof(LeanItem, count) == offsetof(LeanItem, tile_vecs) + 4, "one store");
-    if (threadIdx.x == 0) *reinterpret_cast<int2*>(const_cast<int32_t*>(&item->tile_vecs)) = range;
+    return make_int2(from, max(to - from, 0));
+}
+
+template <bool FIRST>
+__device__ __forceinline__ int2 block_entries(const LeanItem& it, const LeanItem* item, const int32_t* __restrict__ rpt)
+{
+    if constexpr (!FIRST) return make_int2(it.tile_vecs, it.count);
+    const int2 range = row_block_range(it, rpt);
+    if (threadIdx.x == 0) {
+        LeanItem* const mine = const_cast<LeanItem*>(item);
+        mine->tile_vecs = range.x;
+        mine->count = range.y;
+    }
     return range;
 }
 
@@ -954,6 +964,7 @@ __device__ __forceinline__ int2 block_entries(const LeanItem& it, const LeanItem
 // bspmm_kernel needs the row pointers before it can ask for the entries.
 // (Fetching the block's share of the dense rows into L2 ahead of the gathers was measured and
 // changed nothing: the gathers are bound by L2 throughput.)
+template <bool FIRST>
 __device__ __forceinline__ void lean_row_block(const LeanItem& it, const LeanItem* item, int* sm,
                                                const int32_t* __restrict__ rpt,
                                                const int32_t* __restrict__ colids,
@@ -966,7 +977,7 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, const LeanIte
     const int sh = it.sh;
     const uint32_t nvec = 1u << sh;
     const uint32_t l = tid & (nvec - 1), g = tid >> sh, groups = kThreads >> sh;
-    const int2 range = block_entries(it, item, rpt);
+    const int2 range = block_entries<FIRST>(it, item, rpt);
     const int pbeg = min(max(range.x, 0), nnz);
     const int cnt = min(max(range.y, 0), nnz - pbeg);
     const uint32_t row_bytes = ld_in << 2;
@@ -1236,7 +1247,7 @@ template <bool ALIGNED> struct GlobalRows {
 };
 
 // Row block of the generic bin (see lean_row_block): dense rows gathered from global memory.
-template <bool ALIGNED>
+template <bool ALIGNED, bool FIRST>
 __device__ __forceinline__ void any_row_block(const LeanItem& it, const LeanItem* item, int* sm,
                                               const int32_t* __restrict__ rpt,
                                               const int32_t* __restrict__ colids,
@@ -1247,7 +1258,7 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, const LeanItem
     const uint32_t tid = threadIdx.x;
     const int nrows = it.nrows, k = it.k, nnz = it.nnz;
     const uint32_t fw = max((uint32_t)it.flags >> 8, 1u);
-    const int2 range = block_entries(it, item, rpt);
+    const int2 range = block_entries<FIRST>(it, item, rpt);
     const int pbeg = min(max(range.x, 0), nnz);
     const int cnt = min(max(range.y, 0), nnz - pbeg);
     const int32_t* __restrict__ rp = rpt + it.rpt_off + (uint32_t)it.row0;
@@ -1282,7 +1293,7 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, const LeanItem
 }
 
 // mode: kAnyWindows, kAnyTight (ALIGNED implies both).
-template <bool ALIGNED>
+template <bool ALIGNED, bool FIRST = false>
 __global__ void __launch_bounds__(kThreads)
 bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                  const int32_t* __restrict__ colids, const float* __restrict__ values,
@@ -1294,7 +1305,7 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     const LeanItem it = items[blockIdx.x];
     if (it.flags & 8) return;  // (small items packed for the lean kernel: this launch has a workgroup for each)
     if (it.flags & 2) {        // (the same for the whole workgroup)
-        any_row_block<ALIGNED>(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+        any_row_block<ALIGNED, FIRST>(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         return;
     }
     const int m = it.m, k = it.k, nnz = it.nnz;
@@ -1409,6 +1420,18 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
         any_rows<ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
 }
 
+// The entry range of every row block into its item, for plans whose builds are wanted ahead of the first run.
+__global__ void lean_hints_kernel(LeanItem* items, int n, const int32_t* __restrict__ rpt)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    LeanItem& it = items[i];
+    if ((it.flags & 2) == 0 || it.nrows <= 0) return;
+    const int2 range = row_block_range(it, rpt);
+    it.tile_vecs = range.x;
+    it.count = range.y;
+}
+
 // A small operation on one wavefront of a lean launch (four of them share a workgroup, see plain_schedule):
 // the staged path of bspmm_lean_kernel with 64 lanes and its own quarter of the LDS; the wavefront waits for
 // itself only.
@@ -1505,7 +1528,7 @@ __device__ __forceinline__ void lean_tile(const LeanItem& it, char* lds, const f
 // MERGED: items with flag bit 2 read their CSR from the merged arrays of summed sets (a template
 // parameter: the selects cost the plain kernel).  512 graphs of four channels with dense blocks of their
 // own, F = 128, summed: 9.1 us, 10.0 through the general kernel.
-template <bool MERGED>
+template <bool MERGED, bool FIRST = false>
 __global__ void __launch_bounds__(kThreads)
 bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                   const int32_t* __restrict__ colids, const float* __restrict__ values,
@@ -1522,7 +1545,7 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
     asm volatile("" ::"s"(out), "s"(ld_out));
     if (it.flags & 10) {       // (the same for the whole workgroup)
         if (it.flags & 2) {
-            lean_row_block(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
+            lean_row_block<FIRST>(it, items + blockIdx.x, sm, rpt, colids, values, in, out, ld_in, ld_out, lds_words);
         } else {
             const int w = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
             if (w < it.count) {
@@ -3427,11 +3450,14 @@ hipError_t launch_bspmm(const LaunchParams& P, int grid, int lds_bytes, bool vec
     return launch(kernel_variant(vec4, slices, hubs, merged), grid, kThreads, lds_bytes, stream, P);
 }
 
-hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged,
+// first: the row blocks of these items have no entry ranges yet (see block_entries).
+hipError_t launch_bspmm_lean(const LeanItem* items, const LaunchParams& P, int grid, int lds_bytes, bool merged, bool first,
                              hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
-    return launch(merged ? bspmm_lean_kernel<true> : bspmm_lean_kernel<false>, grid, kThreads, lds_bytes, stream, items,
+    auto* const fn = merged ? (first ? bspmm_lean_kernel<true, true> : bspmm_lean_kernel<true>)
+                            : (first ? bspmm_lean_kernel<false, true> : bspmm_lean_kernel<false>);
+    return launch(fn, grid, kThreads, lds_bytes, stream, items,
                   P.rpt, P.colids, P.values, P.in, P.out, (uint32_t)P.ld_in, (uint32_t)P.ld_out,
                   (uint32_t)(lds_bytes / 4), reinterpret_cast<const int32_t*>(P.w));
 }
@@ -3446,14 +3472,22 @@ hipError_t launch_first_transposed(const LeanItem* items, const LaunchParams& P,
 
 // aligned: F % 4 == 0 and every row of every tile is float4 on 16 bytes; quads: F % 4 == 0 (the schedule
 // then left no room for rows off 16 bytes in LDS).
-hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, int grid,
+hipError_t launch_bspmm_any(const LeanItem* items, const LaunchParams& P, bool aligned, bool quads, bool first, int grid,
                             int lds_bytes, hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
     const bool windows = (reinterpret_cast<uintptr_t>(P.in) & 15) == 0 && (!quads || P.ld_in % 4 == 0);
-    return launch(aligned ? bspmm_any_kernel<true> : bspmm_any_kernel<false>, grid, kThreads, lds_bytes, stream, items,
+    auto* const fn = aligned ? (first ? bspmm_any_kernel<true, true> : bspmm_any_kernel<true>)
+                             : (first ? bspmm_any_kernel<false, true> : bspmm_any_kernel<false>);
+    return launch(fn, grid, kThreads, lds_bytes, stream, items,
                   P.rpt, P.colids, P.values, P.in, P.out, P.ld_in, P.ld_out, (uint32_t)(lds_bytes / 4),
                   (windows ? kAnyWindows : 0) | (quads ? kAnyTight : 0), reinterpret_cast<const int32_t*>(P.w));
+}
+
+hipError_t launch_lean_hints(LeanItem* items, int n, const int32_t* rpt, hipStream_t stream)
+{
+    if (n <= 0) return hipSuccess;
+    return launch(lean_hints_kernel, (n + 255) / 256, 256, 0, stream, items, n, rpt);
 }
 
 using FrontFn = void (*)(const LaunchParams);

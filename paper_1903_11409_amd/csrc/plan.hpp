@@ -78,7 +78,7 @@ struct alignas(16) LeanItem {
     int32_t tile_vecs;    // staged: float4 in the tile, k << sh (lean kernel)
                           // row block: its first entry, rpt[row0] (filled on the device)
     int32_t count;        // row block: its entries, rpt[row0 + nrows] - rpt[row0] (filled on the
-                          // device, -1 until then)
+                          // device)
 };
 static_assert(sizeof(LeanItem) == 64, "LeanItem must be 64 bytes");
 

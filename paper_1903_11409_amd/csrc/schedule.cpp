@@ -880,7 +880,6 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
                     const bool once = ranges == 1 && first[u + 1] - first[u] == 1 && (F % 32 == 0 || y.width == F);
                     t.flags = y.width << 8 | (staged ? (once ? 1 : 0) : 2);
                     t.tile_vecs = staged ? t.k << y.sh : 0;
-                    t.count = staged ? 0 : -1;
                 }
                 const int list = (base + group) & 7;
                 load[list] += here;

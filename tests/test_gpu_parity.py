@@ -219,7 +219,7 @@ def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, c
     torch = torch_cuda
     b = W.random_general(41, F=F, shapes=[(1200, 1500, 4000), (600, 3000, 40), (9, 9, 20), (2000, 700, 0)])
     b.rpt[1:600] = 0                               # of the first operation: blocks without entries, then a full row
-    plan = K.Plan(b)
+    plan, ahead = K.Plan(b), K.Plan(b, options=K.make_options(flags=K.BUILD_TRANSPOSE))
     sides = [(plan.run, b.B, b.n_c_rows, oracle.forward_batch, b.c_row_off, b.rows),
              (plan.run_transposed, b.dY, b.n_b_rows, oracle.transposed_batch, b.b_row_off, b.cols)]
     for run, operand, rows, reference, off, length in sides:
@@ -233,7 +233,8 @@ def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, c
                 out.fill_(SENTINEL)
                 graph.replay()
                 results.append(out.clone())
-        results += [run(X, torch.full((rows, F), SENTINEL, device="cuda")) for _ in range(3)]
+        early = ahead.run if run == plan.run else ahead.run_transposed
+        results += [r(X, torch.full((rows, F), SENTINEL, device="cuda")) for r in (run, run, run, early)]
         torch.cuda.synchronize()
         assert all(torch.equal(r, results[0]) for r in results)
         ref, S = reference(b)
