@@ -767,8 +767,38 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     int narrow = -1;
     for (int c = std::min(nc, 2) - 1; c >= 0; --c)
         if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
-    const Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
-                             : search_shape(kn, vec, (size_t)nc, count);
+    Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
+                       : search_shape(kn, vec, (size_t)nc, count);
+    // Longer row blocks where the launch does not fit the chip: from 24 rows on, four passes at most, no more than make it
+    // seven eighths of what the chip holds.  Not where most of the dense input belongs to row blocks, whose gathers then want
+    // every workgroup there can be, nor past 48 MB of it, which bounds either, nor below F = 64 (a pass has 32 rows; 600 graphs at
+    // F = 32 9.1 -> 10.1).  us, both directions, operands from memory,
+    // before / after, heavy-tailed graphs: 500 at F = 64 11.7 / 11.1, 1333 24.4 / 21.5; 500 at F = 128 20.2 / 16.2; 200 at
+    // F = 256 15.4 / 14.2, 500 32.3 / 31.3; 200 at F = 512 26.4 / 24.7; 66 at F = 1024 20.2 / 16.5.  Random matrices of three
+    // entries a row (three quarters of the input in row blocks) lose: 100 at F = 512 23.8 -> 29.1.
+    if (open && F % 4 == 0 && F >= 64) {
+        std::vector<int> blocked;
+        int64_t in_words = 0, blocked_words = 0;
+        for (int i = 0; i < n; ++i) {
+            in_words += (int64_t)o.k[i] * F;
+            if (o.m[i] <= 0 || std::max((int)shape.chosen, (int)fit[i]) < nc) continue;
+            blocked.push_back(o.m[i]);
+            blocked_words += (int64_t)o.k[i] * F;
+        }
+        auto pieces = [&](int rows) {
+            int w = 0;
+            for (int m : blocked) w += (m + rows - 1) / rows;
+            return w * (tile[blocks].nfull + (tile[blocks].tail.width > 0));
+        };
+        const int others = shape.wgs - pieces(generic_rows), most = std::min(64, 4 * tile[blocks].full.rows[0]);
+        const int room = 7 * (kMaxLdsBytes / 4 / lds_words) * kn.compute_units / 8;
+        if (!kn.generic_given && !blocked.empty() && in_words <= 12000000 && 2 * blocked_words <= in_words &&
+            shape.wgs > room) {
+            generic_rows = std::max(generic_rows, std::min(24, most));
+            while (generic_rows + 8 <= most && others + pieces(generic_rows) > room) generic_rows += 8;
+        }
+        shape.wgs = others + pieces(generic_rows);
+    }
     if (!open) s.uncut_wgs = shape.wgs;
 
     // A unit is a dense block and the operations that read it; the items of a unit that read the same

@@ -1000,3 +1000,19 @@ def test_what_the_streaming_launch_does_not_do_stays_on_the_one_launch_path(why,
                                                                             chans, kw):
     stream, _ = _stream_of(graphs, F, n_x, chans, **kw)
     assert stream == [0, 0, 0, 0], why
+
+
+@pytest.mark.parametrize("graphs,F,rows", [(500, 128, 24), (66, 1024, 24), (1333, 64, 64), (60, 128, 32), (1333, 32, 32),
+                                           (1600, 256, 8)])
+def test_row_blocks_of_launches_past_the_chip_are_longer(graphs, F, rows):
+    """Heavy-tailed batches: row blocks of 24 rows and more where the launch does not fit the chip, a pass's rows (of its
+    tile: 32 columns where it fits at once) where it does, below F = 64 and past 48 MB of dense input; random
+    matrices, most of them in row blocks, keep theirs."""
+    batches = [(W.config5_skewed(graphs=graphs, F=F), rows)]
+    if F == 128 and graphs == 500:
+        batches.append((W.random_square(5, F, 200, (32, 256), 3), 8))
+    for b, want in batches:
+        h = K.dry_plan(b, compute_units=256)
+        for transposed in (False, True):
+            assert max(x.nrows for x in K.bspmm_plan_items(h, transposed) if x.bin == K.BIN_GENERIC) == want
+        K.bspmm_destroy(h)
