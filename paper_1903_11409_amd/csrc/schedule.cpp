@@ -612,6 +612,14 @@ Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narr
         fit(kn.lds_words, 0);
     }
     bool pow2 = narrow == 0;
+    // (with row blocks past 40 MB: 1167 heavy-tailed graphs at F = 192 61.3 -> 51.7 us both directions, 2700 at F = 96 76 -> 61,
+    // 486 random matrices at F = 192 60.5 -> 54.5; 208 of them, 23 MB, 21.2 -> 24.6)
+    if (narrow > 0 && lines && n.row_blocks && n.in_words > 10000000) {
+        pow2 = true;
+        fit(kn.lds_words, narrow);
+        s = {(size_t)narrow, 0, count((size_t)narrow, 0).wgs};
+        *uncut_wgs = s.wgs;
+    }
     if (narrow > 0 && lines && !small && !n.row_blocks) {
         const Count t = count((size_t)narrow, 0);
         if (streams || 4 * (int64_t)t.wgs <= 5 * (int64_t)n.wgs) {
@@ -769,13 +777,15 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
     Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
                        : search_shape(kn, vec, (size_t)nc, count);
-    // Longer row blocks where the launch does not fit the chip: from 24 rows on, four passes at most, no more than make it
-    // seven eighths of what the chip holds.  Not where most of the dense input belongs to row blocks, whose gathers then want
-    // every workgroup there can be, nor past 48 MB of it, which bounds either, nor below F = 64 (a pass has 32 rows; 600 graphs at
-    // F = 32 9.1 -> 10.1).  us, both directions, operands from memory,
-    // before / after, heavy-tailed graphs: 500 at F = 64 11.7 / 11.1, 1333 24.4 / 21.5; 500 at F = 128 20.2 / 16.2; 200 at
-    // F = 256 15.4 / 14.2, 500 32.3 / 31.3; 200 at F = 512 26.4 / 24.7; 66 at F = 1024 20.2 / 16.5.  Random matrices of three
-    // entries a row (three quarters of the input in row blocks) lose: 100 at F = 512 23.8 -> 29.1.
+    // Longer row blocks where the launch does not fit the chip (seven eighths of it on tiles that are powers of two): from 24
+    // rows on, four passes at most, no more than make it seven eighths.  Where most of the dense input belongs to row
+    // blocks, whose gathers want every workgroup there can be, two passes, if it then fits.  Not past 104 MB of dense
+    // input (48 at 40 KiB), which bounds either, nor below F = 64 (a pass has 32 rows; 600 graphs at F = 32 9.1 -> 10.1).
+    // us, both directions, operands from memory, before / after, heavy-tailed graphs: 500 at F = 64 11.7 / 11.0, 1333
+    // 24.4 / 21.5; 500 at F = 128 20.2 / 16.2, 2700 78.2 / 72.4; 240 at F = 256 19.4 / 15.9, 500 33.1 / 31.5; 200 at F =
+    // 512 26.4 / 24.7; 66 at F = 1024 20.2 / 16.5.  Random matrices of three entries a row (three quarters of the input
+    // in row blocks): 97 at F = 256 15.0 / 13.5, 41 at F = 512 13.7 / 11.6; four passes where two do not fit lose: 100
+    // at F = 512 23.8 -> 29.1.
     if (open && F % 4 == 0 && F >= 64) {
         std::vector<int> blocked;
         int64_t in_words = 0, blocked_words = 0;
@@ -792,8 +802,11 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         };
         const int others = shape.wgs - pieces(generic_rows), most = std::min(64, 4 * tile[blocks].full.rows[0]);
         const int room = 7 * (kMaxLdsBytes / 4 / lds_words) * kn.compute_units / 8;
-        if (!kn.generic_given && !blocked.empty() && in_words <= 12000000 && 2 * blocked_words <= in_words &&
-            shape.wgs > room) {
+        const int passes2 = std::min(64, 2 * tile[blocks].full.rows[0]);
+        if (kn.generic_given || blocked.empty() || generic_rows >= 24 || shape.wgs <= (tile[blocks].full.pow2 ? room : kn.capacity_wgs)) {
+        } else if (2 * blocked_words > in_words) {
+            if (generic_rows < 16 && others + pieces(passes2) <= kn.capacity_wgs) generic_rows = std::max(generic_rows, passes2);
+        } else if (in_words <= (lds_words > kn.lds_words ? 12000000 : 26000000)) {
             generic_rows = std::max(generic_rows, std::min(24, most));
             while (generic_rows + 8 <= most && others + pieces(generic_rows) > room) generic_rows += 8;
         }

@@ -1003,14 +1003,14 @@ def test_what_the_streaming_launch_does_not_do_stays_on_the_one_launch_path(why,
 
 
 @pytest.mark.parametrize("graphs,F,rows", [(500, 128, 24), (66, 1024, 24), (1333, 64, 64), (60, 128, 32), (1333, 32, 32),
-                                           (1600, 256, 8)])
+                                           (1600, 256, 8), (2700, 128, 32)])
 def test_row_blocks_of_launches_past_the_chip_are_longer(graphs, F, rows):
     """Heavy-tailed batches: row blocks of 24 rows and more where the launch does not fit the chip, a pass's rows (of its
-    tile: 32 columns where it fits at once) where it does, below F = 64 and past 48 MB of dense input; random
-    matrices, most of them in row blocks, keep theirs."""
+    tile: 32 columns where it fits at once) where it does, below F = 64 and past 48 MB of dense input at 40 KiB; random
+    matrices, most of them in row blocks, take two passes where the launch then fits."""
     batches = [(W.config5_skewed(graphs=graphs, F=F), rows)]
     if F == 128 and graphs == 500:
-        batches.append((W.random_square(5, F, 200, (32, 256), 3), 8))
+        batches += [(W.random_square(5, F, 400, (32, 256), 3), 8), (W.random_square(5, F, 160, (32, 256), 3), 16)]
     for b, want in batches:
         h = K.dry_plan(b, compute_units=256)
         for transposed in (False, True):
