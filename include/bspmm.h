@@ -345,8 +345,8 @@ int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W,
 /*
  * G_i = A_i^T . dY_i for every operation (backward product with respect to the dense input).
  * dY is indexed like C (rows_i rows at c_row_off[i]), G like B (cols_i rows at b_row_off[i]).
- * The first call enqueues the on-device transposed-CSR build (one extra launch, once per
- * plan) unless bspmm_create already did.  Returns ESTATE when two operations share or
+ * The first call builds the transposed CSR on the device unless bspmm_create already did: inside the product's
+ * own launch for square operations of at most 1024 entries, else in one extra launch, once per plan.  Returns ESTATE when two operations share or
  * overlap a B block and the plan was not created with BSPMM_ACCUMULATE (each would have to
  * add into the same gradient rows), or when B blocks overlap without being identical.
  */

@@ -473,6 +473,8 @@ void make_stream_plan(bspmm_plan& p)
     // number of trips times what a trip costs: a fixed part and the passes of its gather (one channel at
     // n_X = 16, F = 64, 2048 molecules, 16 / 32 / 64 rows: 11.2 / 9.4 / 9.2 us; at n_X = 64, 1200: 9.3 / 9.8).
     // (no more than 1024 slots: 256 had blocks of four entries per row at n_X = 16 past them, 9.9 -> 8.9 us)
+    // (eight wavefronts past K = 256 hold so many registers that a CU has one workgroup whatever its LDS: us, four channels at
+    // n_X = 128, F = 128, 53 / 128 KiB: 1500 molecules 47.0 / 44.5, 300 15.3 / 14.7; three channels, eight at n_X = 64 level)
     const int budget = kn.lds_given ? kn.lds_words * 4 : waves == 8 && !direct && steps_of(most) > 8 ? 131072 : 53248;
     constexpr int kSlots = 1024;
     auto slots_in = [&](int rb, int ch, int bytes, int want) {

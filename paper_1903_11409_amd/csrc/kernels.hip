@@ -9,6 +9,7 @@
 // bspmm_lean_kernel the same product for launches made only of whole-workgroup items on the
 //                   float4 path: items carry what the general kernel derives, the dense tile
 //                   goes global -> LDS directly.
+// bspmm_first_transposed_kernel  the first transposed product of a plan, which sorts the operations itself.
 // bspmm_gcn_kernel  the fused front of the graph-convolution layer (Fig. 7): the dense tile is
 //                   made on the matrix cores from the layer input and the weights, for one
 //                   channel or for all channels of the layer, and gathered as above.
