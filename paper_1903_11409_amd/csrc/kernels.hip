@@ -1648,7 +1648,6 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
                               int32_t* __restrict__ rpt_t, int32_t* __restrict__ colids_t, float* __restrict__ values_t)
 {
     extern __shared__ __align__(16) int sm[];
-    __shared__ int wave_sum[kWaves];
     const uint32_t tid = threadIdx.x;
     const LeanItem it = items[blockIdx.x];
     if (it.flags & 8) return;  // (small items packed for the lean kernel: this launch has a workgroup for each)
@@ -1692,7 +1691,9 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
         if (key[u] >= 0) atomicAdd(&sm[key[u] + 1], 1);
     __syncthreads();
 
-    // ---- inclusive scan of sm[0..m]: afterwards the first position of every column
+    // ---- inclusive scan of sm[0..m]: afterwards the first position of every column.  A wavefront adds up the
+    // counts in front of its own itself: the items' LDS may be all that a workgroup can have, so that there is
+    // none beside it.
     const bool writes = it.row0 == 0 && it.f0 == 0 && m > 0;
     const int chunk = (m + kThreads) / kThreads;
     const int lo = tid * chunk, hi = min(lo + chunk, m + 1);
@@ -1704,10 +1705,15 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
         const int n = __shfl_up(incl, d);
         if ((int)wl >= d) incl += n;
     }
-    if (wl == 63) wave_sum[wave] = incl;
+    const int front = (int)wave * 64 * chunk;
+    int before = 0;
+    if (front <= m) {
+        for (int c = wl; c < front; c += 64) before += sm[c];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) before += __shfl_xor(before, d);
+    }
     __syncthreads();
-    int run = incl - sum;
-    for (uint32_t w = 0; w < wave; ++w) run += wave_sum[w];
+    int run = before + incl - sum;
     for (int c = lo; c < hi; ++c) {
         run += sm[c];
         sm[c] = run;

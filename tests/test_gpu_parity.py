@@ -210,6 +210,16 @@ def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, on
     _check_transposed(torch, oracle, b, plan=plan)
 
 
+def test_first_transposed_run_in_all_the_lds_of_a_cu(torch_cuda, oracle):
+    """Operations that take 160 KiB, the rows of one more than a wavefront has lanes: the first transposed run
+    has no LDS beside the plan's."""
+    for n, z, count, F, options in ((313, 280, 20, 128, dict(min_tile=128)), (152, 930, 1, 256, dict(min_tile=256))):
+        b = W.random_general(5, F=F, shapes=[(n, n, z)] * count)
+        plan = K.Plan(b, options=K.make_options(lds_bytes=163840, **options))
+        _check_transposed(torch_cuda, oracle, b, plan=plan)
+        assert plan.info().transposed_built == 1
+
+
 @pytest.mark.parametrize("F", [50, 64, 300])
 @pytest.mark.parametrize("captured_first", [False, True])
 def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, captured_first):

@@ -4,6 +4,7 @@ staged items fit their LDS share, workgroups are well formed)."""
 import ctypes
 import os
 import re
+import struct
 
 import dataclasses
 
@@ -1016,3 +1017,37 @@ def test_row_blocks_of_launches_past_the_chip_are_longer(graphs, F, rows):
         for transposed in (False, True):
             assert max(x.nrows for x in K.bspmm_plan_items(h, transposed) if x.bin == K.BIN_GENERIC) == want
         K.bspmm_destroy(h)
+
+
+def _static_lds():
+    """Bytes of LDS that every kernel of the built library has beside a launch's own, from its code objects' metadata."""
+    msgpack = pytest.importorskip("msgpack")
+    data, magic, found = open(K.LIB_PATH, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    at = data.find(magic)
+    while at >= 0:
+        (entries,), p = struct.unpack_from("<Q", data, at + 24), at + 32
+        for _ in range(entries):
+            start, size, length = struct.unpack_from("<QQQ", data, p)
+            p += 24 + length
+            elf = data[at + start:at + start + size]
+            note = elf.find(b"AMDGPU\0\0")
+            if elf[:4] == b"\x7fELF" and note >= 0:
+                (length,) = struct.unpack_from("<I", elf, note - 8)
+                for k in msgpack.unpackb(elf[note + 8:note + 8 + length])["amdhsa.kernels"]:
+                    found[k[".name"]] = k[".group_segment_fixed_size"]
+        at = data.find(magic, at + 1)
+    return found
+
+
+@pytest.mark.parametrize("n,z,count,F,options", [(313, 280, 1024, 128, {}), (152, 930, 1, 256, dict(min_tile=256))])
+def test_plans_that_take_all_the_lds_of_a_cu_leave_none_beside_it(n, z, count, F, options):
+    """Square operations whose items take 160 KiB: the kernels that run from their table, the first transposed run's
+    among them, have no LDS of their own on top."""
+    b = W.random_general(5, F=F, shapes=[(n, n, z)] * count, with_dY=False)
+    h = K.dry_plan(b, compute_units=256, lds_bytes=163840, **options)
+    info = K.bspmm_plan_info(h)
+    assert info.lds_bytes == 163840 and info.lean[1] == 1 and info.items_in_bin[1][K.BIN_GENERIC] == 0
+    K.bspmm_destroy(h)
+    static = {name: size for name, size in _static_lds().items() if "bspmm_lean_kernel" in name or
+              "bspmm_any_kernel" in name or "bspmm_first_transposed_kernel" in name}
+    assert len(static) >= 3 and not any(static.values()), static
