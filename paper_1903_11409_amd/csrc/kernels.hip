@@ -1679,8 +1679,9 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
     for (int c = tid; c <= m; c += kThreads) sm[c] = 0;
     for (int i = tid; i < m; i += kThreads) {
         if (i >= kThreads) r0 = rp[i], r1 = rp[i + 1];
-        const int end = min(r1, nnz);
-        for (int p = max(r0, 0); p < end; ++p) row_of[p] = i;
+        // (entries outside what the row pointers cover: the first row and the last, as in the build)
+        const int end = i + 1 < m ? min(r1, nnz) : nnz;
+        for (int p = i > 0 ? max(r0, 0) : 0; p < end; ++p) row_of[p] = i;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)                      // (entries outside the matrix are skipped, as in the build)
@@ -1735,7 +1736,7 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
         for (int t = beg; t < end; ++t) rank += pos[t] < p ? 1 : 0;
         place[u] = beg + rank;
         row[u] = row_of[p];
-        if ((unsigned)row[u] >= (unsigned)m) row[u] = 0;   // (row pointers that leave the entry out)
+        if ((unsigned)row[u] >= (unsigned)m) row[u] = 0;   // (decreasing row pointers may leave an entry out)
     }
     __syncthreads();                                 // everyone has read positions and rows
 #pragma unroll

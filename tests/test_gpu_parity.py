@@ -220,6 +220,23 @@ def test_first_transposed_run_in_all_the_lds_of_a_cu(torch_cuda, oracle):
         assert plan.info().transposed_built == 1
 
 
+def test_first_transposed_run_with_entries_outside_the_row_pointers(torch_cuda):
+    """Row pointers that start late and end early, which the calls do not look for: the entries outside belong to the
+    first row and the last, in the build and in the first transposed run alike, whatever the LDS held before."""
+    torch = torch_cuda
+    b = W.random_general(8, F=64, shapes=[(25, 25, 90)] * 64)
+    starts = b.rpt_off[:, None] + np.arange(26)
+    b.rpt[starts] = np.clip(b.rpt[starts], 5, 60)
+    plan, built = K.Plan(b), K.Plan(b, options=K.make_options(flags=K.BUILD_TRANSPOSE))
+    dY = torch.from_numpy(b.dY).cuda()
+    want = built.run_transposed(dY, torch.zeros((b.n_b_rows, 64), device="cuda"))
+    got = plan.run_transposed(dY, torch.zeros((b.n_b_rows, 64), device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    for mine, ref in zip(plan.export_transposed(), built.export_transposed()):
+        assert torch.equal(mine, ref)
+
+
 @pytest.mark.parametrize("F", [50, 64, 300])
 @pytest.mark.parametrize("captured_first", [False, True])
 def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, captured_first):
