@@ -1806,6 +1806,15 @@ build_sorted_kernel(const OpRecord* __restrict__ ops, const int32_t* __restrict_
         const int c = ci[p];
         return (unsigned)c < (unsigned)k ? c : -1;
     };
+    // Pairs outside their matrix leave room behind the others: no column there, so that the transposed build, which
+    // asks every entry that the operation was planned for, leaves them out too.
+    auto close = [&](int placed) {
+        if (FROM_COO)
+            for (int p = placed + tid; p < nnz; p += T) {
+                colids_t[o.nz_t_off + p] = -1;
+                values_t[o.nz_t_off + p] = 0.f;
+            }
+    };
 
     // ---- small operations (flagged by the host: everything in LDS, at most four entries per
     // lane): one round trip to memory reads the operation into registers (and the row
@@ -1897,6 +1906,7 @@ build_sorted_kernel(const OpRecord* __restrict__ ops, const int32_t* __restrict_
             colids_t[o.nz_t_off + beg + rank] = a;
             values_t[o.nz_t_off + beg + rank] = val[u];
         }
+        close(cnt[k]);
         return;
     }
 
@@ -1995,6 +2005,7 @@ build_sorted_kernel(const OpRecord* __restrict__ ops, const int32_t* __restrict_
             colids_t[o.nz_t_off + beg + rank] = (int)(kr >> kb);
             values_t[o.nz_t_off + beg + rank] = v;
         }
+        close(cnt[k]);
         return;
     }
 
@@ -2059,6 +2070,7 @@ build_sorted_kernel(const OpRecord* __restrict__ ops, const int32_t* __restrict_
         colids_t[o.nz_t_off + beg + rank] = a;
         values_t[o.nz_t_off + beg + rank] = va[p];
     }
+    close(placed);
 }
 
 // Index pairs of a COO operation inside their matrix?

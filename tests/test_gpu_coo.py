@@ -125,6 +125,35 @@ def test_entry_offsets_with_gaps_in_any_order(torch_cuda, oracle):
     _check(torch_cuda, oracle, b2, ids2, vals2)
 
 
+@pytest.mark.parametrize("shapes", [[(25, 25, 90)] * 64, [(20, 40, 200), (300, 200, 5000), (4000, 3000, 20000)]])
+def test_pairs_outside_their_matrix_are_left_out_of_both_directions(torch_cuda, oracle, shapes):
+    """The conversion leaves such pairs out, and what the workspace held in their place before - here the arrays of a plan
+    with every pair inside - stays out of the transposed product too."""
+    torch = torch_cuda
+    b = W.random_general(4, F=16, shapes=shapes)
+    ids, vals = W.coo_view(b, seed=2)
+    bad = ids.copy()
+    bad.reshape(-1, 2)[1::3, 0] = 1 << 20
+    bad.reshape(-1, 2)[2::9, 1] = -1
+    keep = np.ones(len(vals), dtype=bool)
+    keep[1::3] = keep[2::9] = False
+    workspace = torch.empty((1 << 22,), dtype=torch.int32, device="cuda")
+    dY = torch.from_numpy(b.dY).cuda()
+    for pairs in (ids, bad):
+        hb = K.HostCooBatch(b.rows, b.cols, b.nnz, b.nz_off, b.b_row_off, b.c_row_off,
+                            torch.from_numpy(pairs).cuda(), torch.from_numpy(vals).cuda())
+        assert K.bspmm_workspace_bytes_coo(hb, b.F) <= workspace.numel() * 4
+        plan = K.bspmm_create_coo(hb, b.F, workspace=workspace, workspace_bytes=workspace.numel() * 4)
+        G = torch.full((b.n_b_rows, b.F), SENTINEL, device="cuda")
+        K.bspmm_run_transposed(plan, dY, G, b.F, b.F)
+        torch.cuda.synchronize()
+        K.bspmm_destroy(plan)
+    inside = np.where(np.repeat(keep, 2), bad, 0).astype(np.int32)
+    ref, S = oracle.coo_product(b.rows, b.cols, b.nnz, b.nz_off, b.b_row_off, b.c_row_off, inside,
+                                np.where(keep, vals, 0).astype(np.float32), b.dY, b.n_b_rows, transposed_=True)
+    _assert_close(G.cpu().numpy(), ref, S, _owned(b.b_row_off, b.cols, b.n_b_rows), "pairs left out")
+
+
 def test_conversion_falls_back_to_global_scratch(torch_cuda, oracle):
     """An operation whose counters and positions exceed LDS sorts through device scratch."""
     b = W.random_general(78, F=8, shapes=[(4000, 3000, 20000), (10, 10, 30)])
