@@ -1631,16 +1631,23 @@ bspmm_lean_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict_
 // chain of 5 us) and the product, each 3.5 us of host time beside what the GPU takes.  Instead every
 // workgroup of the product sorts its operation itself, in the LDS of its item: entries of
 // A (a column, and the row that its row pointers give) are counted per column, the counts are scanned,
-// the entries' positions are scattered with atomic cursors, and an entry's rank among its column's
-// positions is its place - the stable order of build_sorted_kernel, whatever the order of arrival, so the
-// sums are bit for bit those of the build and bspmm_lean_kernel.  Positions and rows of the
-// entries take the two halves of the words that their (row offset, value) pairs take afterwards.  The
+// the entries' positions are scattered in the order in which they were counted, and an entry's rank among its
+// column's positions is its place - the stable order of build_sorted_kernel, whatever the order of arrival, so
+// the sums are bit for bit those of the build and bspmm_lean_kernel.  Positions and rows of the
+// entries take the two halves of the words that their (row offset, value) pairs take afterwards.  Every
+// workgroup of an operation sorts, so hub nodes must not make it long: long columns keep their positions as one
+// bit each, whose ranks are at most 32 words away, and a wavefront writes the rows of a long row's entries together.  The
 // workgroup with the first rows and columns of an operation writes its transposed arrays, for every later run.
-// 128 molecules, F = 128, GPU time of build and product 8.7 us, of this kernel 5.4; a step with a new batch (plan, both
-// products) 29.7 -> 25.9 us, 512 from index pairs at F = 64 45.9 -> 42.1.  Bound: the chain of LDS round trips and
-// barriers of the sort, which other workgroups of the CU hide in larger launches.
+// 128 molecules, F = 128, GPU time of build and product 8.7 us, of this kernel 5.6; a step with a new batch (plan, both
+// products) 29.7 -> 25.9 us, 512 from index pairs at F = 64 45.9 to 47.3 -> 42.1 to 44.4.  Bound: the chain of LDS round
+// trips and barriers of the sort, which other workgroups of the CU hide in larger launches.
+// Star graphs, between events around the first run, us, build and product / every lane through its row and column
+// alone / as it is: 512 of 100 nodes at F = 64 27.4 / 26.2 / 14.9, at F = 512 55 / 100 / 53; 4000 of 150 at F = 64 121 /
+// 186 / 84; 512 of 190 at F = 512 129 / 320 / 113; batches without hubs 0.2 us longer for it (128 molecules 11.2 / 7.6 / 7.9).
 // (square operations, arrays of both directions at the same offsets: `it` describes either; at most four entries per lane)
 // ---------------------------------------------------------------------------------------
+constexpr int kHubEntries = 16;   // entries of a row or column that one lane goes through on its own
+
 __global__ void __launch_bounds__(kThreads)
 bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__ rpt,
                               const int32_t* __restrict__ colids, const float* __restrict__ values,
@@ -1677,24 +1684,34 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
     int* pos = reinterpret_cast<int*>(cv);           // positions in A, by column
     int* row_of = pos + nnz;                         // row of every entry of A
     for (int c = tid; c <= m; c += kThreads) sm[c] = 0;
-    for (int i = tid; i < m; i += kThreads) {
-        if (i >= kThreads) r0 = rp[i], r1 = rp[i + 1];
+    for (int i0 = (int)wave * 64; i0 < m; i0 += kThreads) {          // (the same for every lane of a wavefront)
+        const int i = i0 + (int)wl;
+        if (i0 >= kThreads) r0 = rp[min(i, m)], r1 = rp[min(i + 1, m)];
         // (entries outside what the row pointers cover: the first row and the last, as in the build)
-        const int end = i + 1 < m ? min(r1, nnz) : nnz;
-        for (int p = i > 0 ? max(r0, 0) : 0; p < end; ++p) row_of[p] = i;
+        const int from = i > 0 ? max(r0, 0) : 0, end = i + 1 < m ? min(r1, nnz) : nnz;
+        const bool hub = i < m && end - from > kHubEntries;
+        if (i < m && !hub)
+            for (int p = from; p < end; ++p) row_of[p] = i;
+        for (uint64_t rows = __ballot(hub); rows != 0; rows &= rows - 1) {
+            const int lane = __builtin_ctzll(rows), first = __shfl(from, lane), past = __shfl(end, lane);
+            for (int p = first + (int)wl; p < past; p += 64) row_of[p] = i0 + lane;
+        }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)                      // (entries outside the matrix are skipped, as in the build)
         if ((int)(tid + u * kThreads) >= nnz || (unsigned)key[u] >= (unsigned)m) key[u] = -1;
     __syncthreads();
+    int place[4], row[4];                            // (first: how many entries of its column came before)
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (key[u] >= 0) atomicAdd(&sm[key[u] + 1], 1);
+    for (int u = 0; u < 4; ++u) {
+        place[u] = row[u] = 0;
+        if (key[u] >= 0) place[u] = atomicAdd(&sm[key[u] + 1], 1);
+    }
     __syncthreads();
 
-    // ---- inclusive scan of sm[0..m]: afterwards the first position of every column.  A wavefront adds up the
-    // counts in front of its own itself: the items' LDS may be all that a workgroup can have, so that there is
-    // none beside it.
+    // ---- inclusive scan of sm[0..m]: afterwards the first position of every column.  The wavefronts' sums go through
+    // the words of the positions, of which an operation without four entries has too few: the items' LDS may be
+    // all that a workgroup can have, so that there is none beside it.
     const bool writes = it.row0 == 0 && it.f0 == 0 && m > 0;
     const int chunk = (m + kThreads) / kThreads;
     const int lo = tid * chunk, hi = min(lo + chunk, m + 1);
@@ -1706,14 +1723,31 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
         const int n = __shfl_up(incl, d);
         if ((int)wl >= d) incl += n;
     }
-    const int front = (int)wave * 64 * chunk;
+    const int words = (nnz + 31) >> 5, from_long = max(words + kWaves, kHubEntries);   // bits, and entries of a long column
     int before = 0;
-    if (front <= m) {
+    bool hubs = false;                               // a column is long
+    if (nnz >= kWaves) {
+        const bool mine = max(max(place[0], place[1]), max(place[2], place[3])) >= from_long - 1;
+        const int bit = __ballot(mine) != 0 ? 1 << 16 : 0;
+        if (wl == 63) pos[wave] = incl | bit;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const int of = pos[w];
+            all |= of;
+            before += w < (int)wave ? of & 0xffff : 0;
+        }
+        hubs = __builtin_amdgcn_readfirstlane(all) >> 16 != 0;
+        if (hubs)                                    // (a long column's bits are its last words: not the sums')
+            for (int p = kWaves + (int)tid; p < nnz; p += kThreads) pos[p] = 0;
+    } else {
+        const int front = min((int)wave * 64 * chunk, m + 1);
         for (int c = wl; c < front; c += 64) before += sm[c];
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) before += __shfl_xor(before, d);
+        __syncthreads();
     }
-    __syncthreads();
     int run = before + incl - sum;
     for (int c = lo; c < hi; ++c) {
         run += sm[c];
@@ -1722,18 +1756,30 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u)                      // (sm[c] ends as the first position of column c + 1)
-        if (key[u] >= 0) pos[atomicAdd(&sm[key[u]], 1)] = (int)(tid + u * kThreads);
+    for (int u = 0; u < 4; ++u)
+        if (key[u] >= 0) {
+            const int p = (int)(tid + u * kThreads), beg = sm[key[u]];
+            int* at = pos + beg + place[u];
+            if (hubs) {
+                const int end = sm[key[u] + 1];
+                if (end - beg >= from_long) at = nullptr, atomicOr(&pos[end - words + (p >> 5)], 1 << (p & 31));
+            }
+            if (at) *at = p;
+        }
     __syncthreads();
-    int place[4], row[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        place[u] = row[u] = 0;
         if (key[u] < 0) continue;
         const int p = (int)(tid + u * kThreads);
-        const int beg = key[u] > 0 ? sm[key[u] - 1] : 0, end = sm[key[u]];
-        int rank = 0;
-        for (int t = beg; t < end; ++t) rank += pos[t] < p ? 1 : 0;
+        const int beg = sm[key[u]], end = sm[key[u] + 1];
+        int rank = 0, t = beg;
+        if (hubs && end - beg >= from_long) {
+            const int last_word = end - words + (p >> 5);
+            rank = __popc(pos[last_word] & ((1u << (p & 31)) - 1u));
+            for (t = end - words; t < last_word; ++t) rank += __popc(pos[t]);
+            t = end;
+        }
+        for (; t < end; ++t) rank += pos[t] < p ? 1 : 0;
         place[u] = beg + rank;
         row[u] = row_of[p];
         if ((unsigned)row[u] >= (unsigned)m) row[u] = 0;   // (decreasing row pointers may leave an entry out)
@@ -1753,7 +1799,7 @@ bspmm_first_transposed_kernel(const LeanItem* __restrict__ items, const int32_t*
     const uint32_t row_end = (uint32_t)(it.row0 + it.nrows);
     for (uint32_t r = (uint32_t)it.row0 + (tid >> sh); r < row_end; r += kThreads >> sh)
         store_out<4>(reinterpret_cast<float*>(dst + (__umul24(r, out_row_bytes) + (l << 4))),
-                     gather_row(cv, bcol, r > 0 ? sm[r - 1] : 0, sm[r]));
+                     gather_row(cv, bcol, sm[r], sm[r + 1]));
     if (writes)
 #pragma unroll
         for (int u = 0; u < 4; ++u)

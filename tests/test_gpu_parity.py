@@ -172,22 +172,8 @@ def test_transposed_csr_bit_exact(torch_cuda, oracle, maker):
     _check_transposed(torch_cuda, oracle, b, plan=plan)
 
 
-@pytest.mark.parametrize("F,sizes", [
-    # one row, nothing, one to four entries per lane and the edges between them, more rows than lanes,
-    # every entry in one column
-    (64, [(1, 1), (1, 7), (5, 0), (2, 256), (30, 257), (40, 512), (90, 513), (256, 300), (300, 1024), (700, 40)]),
-    (128, [(25, 90)] * 40), (100, [(33, 1000), (32, 100)]), (4, [(60, 700)] * 3),
-    (16, [(20, 60)] * 9000),                       # small operations packed four to a workgroup elsewhere
-])
-@pytest.mark.parametrize("one_column", [False, True])
-def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, one_column):
-    """Square operations whose transposed arrays do not exist yet: the product is bit for bit the one that
-    runs on built arrays, the arrays it leaves behind are the stable transpose, and replays of a captured
-    first run give it again."""
-    torch = torch_cuda
-    b = W.random_general(len(sizes) + F, F=F, shapes=[(n, n, z) for n, z in sizes])
-    if one_column:
-        b.colids[:] = 0
+def _check_first_transposed(torch, oracle, b):
+    F = b.F
     plan, built = K.Plan(b), K.Plan(b, options=K.make_options(flags=K.BUILD_TRANSPOSE))
     dY = torch.from_numpy(b.dY).cuda()
     want = built.run_transposed(dY, torch.zeros((b.n_b_rows, F), device="cuda"))
@@ -208,6 +194,59 @@ def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, on
     for mine, ref in zip(plan.export_transposed(), arrays):
         assert np.array_equal(mine.cpu().numpy(), ref)
     _check_transposed(torch, oracle, b, plan=plan)
+    return plan
+
+
+@pytest.mark.parametrize("F,sizes", [
+    # one row, nothing, one to four entries per lane and the edges between them, more rows than lanes,
+    # every entry in one column
+    (64, [(1, 1), (1, 7), (5, 0), (2, 256), (30, 257), (40, 512), (90, 513), (256, 300), (300, 1024), (700, 40)]),
+    (128, [(25, 90)] * 40), (100, [(33, 1000), (32, 100)]), (4, [(60, 700)] * 3),
+    (16, [(20, 60)] * 9000),                       # small operations packed four to a workgroup elsewhere
+])
+@pytest.mark.parametrize("one_column", [False, True])
+def test_first_transposed_run_builds_the_arrays(torch_cuda, oracle, F, sizes, one_column):
+    """Square operations whose transposed arrays do not exist yet: the product is bit for bit the one that
+    runs on built arrays, the arrays it leaves behind are the stable transpose, and replays of a captured
+    first run give it again."""
+    b = W.random_general(len(sizes) + F, F=F, shapes=[(n, n, z) for n, z in sizes])
+    if one_column:
+        b.colids[:] = 0
+    _check_first_transposed(torch_cuda, oracle, b)
+
+
+def _columns_of(n, z, lengths):
+    """A square operation whose first columns have the given numbers of entries, the others about as many each, in
+    an order that mixes them."""
+    rng = np.random.default_rng(z)
+    c = np.concatenate([np.full(x, i) for i, x in enumerate(lengths)] + [len(lengths) + np.arange(z - sum(lengths)) % (n - len(lengths))])
+    b = W.random_general(z, F=4, shapes=[(n, n, z)])
+    b.colids[:] = rng.permutation(c)
+    return b
+
+
+@pytest.mark.parametrize("maker", [
+    # as above, in one launch: whole workgroups, no row blocks; more columns than lanes among them
+    lambda: W.random_general(9, F=4, shapes=[(n, n, z) for n, z in (
+        (1, 1), (1, 3), (1, 4), (1, 7), (5, 0), (2, 256), (30, 257), (40, 512), (90, 513), (256, 300), (257, 300), (300, 1024),
+        (700, 2), (700, 3), (700, 40), (900, 500))]),
+    lambda: W.random_general(10, F=128, shapes=[(90, 90, 360)] * 40),         # row ranges and column tiles
+    lambda: W.random_general(11, F=512, shapes=[(60, 60, 240)] * 10),
+    # hub rows and columns: around the entries that one lane takes, past a wavefront's lanes, and all there can be
+    lambda: W.hub_batch(1, F=4, n=15), lambda: W.hub_batch(2, F=4, n=17), lambda: W.hub_batch(3, F=64, n=64),
+    lambda: W.hub_batch(4, F=128, n=82), lambda: W.hub_batch(5, F=4, n=512),
+    # columns around the line from which they count as long, where it is sixteen entries and where it is more
+    lambda: _columns_of(30, 200, (15, 16, 17)), lambda: _columns_of(50, 1024, (35, 36, 37, 300)),
+    lambda: _columns_of(9, 20, (15, 0, 1)), lambda: _columns_of(9, 36, (0, 16, 17)),
+])
+def test_first_transposed_run_sorts_in_the_product(torch_cuda, oracle, maker):
+    """The same for batches that all meet the conditions of the launch that sorts and multiplies."""
+    b = maker()
+    plan = _check_first_transposed(torch_cuda, oracle, b)
+    info = plan.info()
+    assert list(info.lean) == [1, 1] and info.items_in_bin[1][K.BIN_GENERIC] == 0
+    assert np.all(b.rows == b.cols) and b.rows.min() > 0 and b.nnz.max() <= 1024 and b.F % 4 == 0
+    assert np.array_equal(b.nz_off, np.cumsum(b.nnz) - b.nnz) and np.array_equal(b.b_row_off, b.c_row_off)
 
 
 def test_first_transposed_run_in_all_the_lds_of_a_cu(torch_cuda, oracle):
