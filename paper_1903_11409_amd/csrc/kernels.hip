@@ -1073,16 +1073,21 @@ __device__ __forceinline__ void lean_row_block(const LeanItem& it, const LeanIte
 // copied as such.  Only a dense input that does not start on 16 bytes is copied word by word.
 //
 // Rows.  A row takes ceil(fw / 4) lanes of four floats, no power of two; the last lane stores what
-// is left of the row.  Where rows average more than kLongRow entries and there are fewer of them than
-// lane groups, the groups share a row's entries (any_long_rows): the additions of a row are a serial chain of
-// LDS reads, and a row of 660 entries kept a launch waiting for 4 us (a lane per float of the row, as it
-// was before: transposed launches of 200 / 300 operations of 1 to 220 rows at F = 50 / 127 8.0 to 10.3 / 15.9 to 17.0
-// us, now 7.4 / 12.4, as long as the forward ones).
+// is left of the row.  The additions of a row are a serial chain of LDS reads, so rows of more than kLongRow
+// entries on average are different.  Where they are fewer than the lane groups, the groups share a row's entries
+// (any_long_rows): a row of 660 entries otherwise keeps a launch waiting for 4 us.  Off 16 bytes a read of four
+// floats costs a CU as much as four reads of one and more: long rows take a lane per float there, unless that leaves half
+// of the lanes idle and a row has 2 kSharedEntries entries on average; groups then share it, kSharedEntries each at least.
+// us, both directions, a lane per float / four floats, shared from sixteen entries on / as it is: F = 127, 2000 operations of 4 to
+// 40 rows of 20 entries 68 / 80 / 68, 1500 of 2 to 30 rows of 100 195 / 233 / 195, 800 of 1 to 120 rows of 20 119 / 137 / 120;
+// F = 50, the same 36 / 39 / 36, 119 / 112 / 97, 89 / 85 / 69; F = 17, the last two 94 / 52 / 45, 71 / 33 / 33; F = 1, 5000 of
+// 4 to 40 rows of 20 17.9 / 22.5 / 19.3.  On 16 bytes groups share from sixteen entries on: F = 100, 2000 of 4 to 40 rows of 20
+// 64 / 33, 1500 of 100 154 / 67.
 // Bound: small launches the chain of item, staging and gather, large ones memory (900 operations of 1 to
-// 220 rows, F = 127: 100 MB in 22 us).  200 of them at F = 50: forward 15.9 -> 6.0 us, transposed (rows of up
-// to 660 entries) 33 -> 6.5 us against the general kernel's scalar path.  Both directions of 200 at F = 50 / 800 at
-// F = 50 / 300 at F = 127 / 900 at F = 17, before and after the groups shared rows: 14.1 -> 13.1 / 31.7 -> 27.7 / 27.1 -> 24.1 /
-// 18.1 -> 16.1.
+// 220 rows, F = 127: 100 MB in 22 us).  200 of them at F = 50: forward 15.9 -> 6.0 us, transposed 33 -> 6.5 us against
+// the general kernel's scalar path.  Both directions with operations of one to three columns among them (rows of up to
+// 660 entries in the transposed one), a lane per float / shared: 200 at F = 50 17.4 / 13.3, 800 32.7 / 27.5, 200 at F =
+// 127 23.7 / 19.9, 800 at F = 17 18.9 / 14.0.
 // ---------------------------------------------------------------------------------------
 enum AnyMode {
     kAnyWindows = 1,   // the dense input starts on 16 bytes: rows are copied as 16-byte words
@@ -1096,33 +1101,36 @@ __device__ __forceinline__ uint32_t div_small(uint32_t n, float inv_d)
     return (uint32_t)(((float)n + 0.5f) * inv_d);
 }
 
-typedef float Floats __attribute__((ext_vector_type(4)));
-typedef float FloatsAt4 __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC> struct Floats { typedef float type __attribute__((ext_vector_type(VEC))); };
+template <int VEC> struct FloatsAt4 { typedef float type __attribute__((ext_vector_type(VEC), aligned(4))); };
 
-template <bool ALIGNED> __device__ __forceinline__ Floats any_load(const void* p)
+template <int VEC, bool ALIGNED>
+__device__ __forceinline__ typename Floats<VEC>::type any_load(const void* p)
 {
+    using VT = typename Floats<VEC>::type;
     if constexpr (ALIGNED)
-        return *reinterpret_cast<const Floats*>(p);
+        return *reinterpret_cast<const VT*>(p);
     else
-        return *reinterpret_cast<const FloatsAt4*>(p);
+        return *reinterpret_cast<const typename FloatsAt4<VEC>::type*>(p);
 }
 
 // Sum of a row's entries [p0, p1): entry(p) gives (key, value), dense(key) this lane's floats of the
-// entry's dense row.  Eight entries in flight while there are as many, then four at a time with the
+// entry's dense row.  N entries in flight while there are as many, then four at a time with the
 // entries past the end left out (see gather_row).
-template <typename Entry, typename Dense>
-__device__ __forceinline__ Floats any_row(int p0, int p1, Entry entry, Dense dense)
+template <int VEC, typename Entry, typename Dense>
+__device__ __forceinline__ typename Floats<VEC>::type any_row(int p0, int p1, Entry entry, Dense dense)
 {
-    constexpr int N = 8;
-    Floats acc = 0.f;
+    using VT = typename Floats<VEC>::type;
+    constexpr int N = VEC == 4 ? 8 : 16;
+    VT acc = 0.f;
     int p = p0;
-    auto fma = [&](float a, const Floats& b) {
+    auto fma = [&](float a, const VT& b) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = fmaf(a, b[i], acc[i]);
+        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(a, b[i], acc[i]);
     };
     for (; p + N <= p1; p += N) {
         int2 e[N];
-        Floats b[N];
+        VT b[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) e[u] = entry(p + u);
 #pragma unroll
@@ -1133,29 +1141,41 @@ __device__ __forceinline__ Floats any_row(int p0, int p1, Entry entry, Dense den
     const int last = p1 - 1;
     for (; p < p1; p += 4) {
         int2 e[4];
-        Floats b[4];
+        VT b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) e[u] = entry(min(p + u, last));
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = dense(e[u].x);
         fma(__int_as_float(e[0].y), b[0]);
-        auto f4 = [](const Floats& v) { return make_float4(v[0], v[1], v[2], v[3]); };
-        float4 sum = f4(acc);
-        add_rest(sum, p1 - p, __int_as_float(e[1].y), f4(b[1]), __int_as_float(e[2].y), f4(b[2]),
-                 __int_as_float(e[3].y), f4(b[3]));
-        acc[0] = sum.x, acc[1] = sum.y, acc[2] = sum.z, acc[3] = sum.w;
+        if constexpr (VEC == 4) {
+            auto f4 = [](const VT& v) { return make_float4(v[0], v[1], v[2], v[3]); };
+            float4 sum = f4(acc);
+            add_rest(sum, p1 - p, __int_as_float(e[1].y), f4(b[1]), __int_as_float(e[2].y), f4(b[2]),
+                     __int_as_float(e[3].y), f4(b[3]));
+            acc[0] = sum.x, acc[1] = sum.y, acc[2] = sum.z, acc[3] = sum.w;
+        } else {
+#pragma unroll
+            for (int u = 1; u < 4; ++u) {
+                const VT old = acc;
+                fma(__int_as_float(e[u].y), b[u]);
+                if (p + u >= p1) acc = old;
+            }
+        }
     }
     return acc;
 }
 
-// The lane's `n` floats of an output row (n < 4 on the last lane of a row only).  Rows off 16
+// The lane's `n` floats of an output row (n < VEC on the last lane of a row only).  Rows off 16
 // bytes share lines with their neighbours, so only aligned rows are stored past the caches.
-template <bool ALIGNED> __device__ __forceinline__ void any_store(float* p, const Floats& v, int n)
+template <int VEC, bool ALIGNED>
+__device__ __forceinline__ void any_store(float* p, const typename Floats<VEC>::type& v, int n)
 {
-    if constexpr (ALIGNED) {
-        __builtin_nontemporal_store(v, reinterpret_cast<Floats*>(p));
-    } else if (n >= 4) {
-        *reinterpret_cast<FloatsAt4*>(p) = v;
+    if constexpr (VEC == 1) {
+        *p = v[0];
+    } else if constexpr (ALIGNED) {
+        __builtin_nontemporal_store(v, reinterpret_cast<typename Floats<VEC>::type*>(p));
+    } else if (n >= VEC) {
+        *reinterpret_cast<typename FloatsAt4<VEC>::type*>(p) = v;
     } else {
         p[0] = v[0];
         if (n > 1) p[1] = v[1];
@@ -1163,22 +1183,24 @@ template <bool ALIGNED> __device__ __forceinline__ void any_store(float* p, cons
     }
 }
 
-// Rows [0, nrows) of an item in lanes of four floats: row(i, p0, p1) gives row i's entries, entry(p) the
+// Rows [0, nrows) of an item in lanes of VEC floats: row(i, p0, p1) gives row i's entries, entry(p) the
 // (key, value) of one, dense(key, l, n) the floats at l of the dense row it names, n of them in the row.
-template <bool ALIGNED, typename Row, typename Entry, typename Dense>
+template <int VEC, bool ALIGNED, typename Row, typename Entry, typename Dense>
 __device__ __forceinline__ void any_rows(uint32_t fw, int nrows, float* __restrict__ dst, int64_t ld_out, Row row,
                                          Entry entry, Dense dense)
 {
-    const uint32_t nvec = (fw + 3) / 4, groups = kThreads / nvec;
+    const uint32_t nvec = (fw + VEC - 1) / VEC, groups = kThreads / nvec;
     const uint32_t g = div_small(threadIdx.x, 1.f / (float)nvec), l = threadIdx.x - g * nvec;
     if (g >= groups) return;
-    const int n = (int)(fw - 4 * l);
-    float* p = dst + (g * ld_out + 4 * l);
+    const int n = (int)(fw - VEC * l);
+    float* p = dst + (g * ld_out + VEC * l);
     const int64_t step = groups * ld_out;
     for (int i = g; i < nrows; i += groups, p += step) {
         int p0, p1;
         row(i, p0, p1);
-        any_store<ALIGNED>(p, any_row(p0, p1, entry, [&](int key) { return dense(key, (int)(4 * l), n); }), n);
+        any_store<VEC, ALIGNED>(p, any_row<VEC>(p0, p1, entry, [&](int key) {
+            return dense.template operator()<VEC>(key, (int)(VEC * l), n);
+        }), n);
     }
 }
 
@@ -1193,7 +1215,7 @@ __device__ __forceinline__ void any_long_rows(uint32_t fw, int nrows, int parts,
     const uint32_t g = div_small(threadIdx.x, 1.f / (float)nvec), l = threadIdx.x - g * nvec;
     const uint32_t i = div_small(g, 1.f / (float)parts), part = g - i * parts;
     const int n = (int)(fw - 4 * l);
-    Floats acc = 0.f;
+    typename Floats<4>::type acc = 0.f;
     const bool mine = i < (uint32_t)nrows;
     if (mine) {
         int p0, p1;
@@ -1201,7 +1223,7 @@ __device__ __forceinline__ void any_long_rows(uint32_t fw, int nrows, int parts,
         const float share = (float)(p1 - p0) / (float)parts;
         const int from = p0 + (int)(share * (float)part);
         const int to = part + 1 == (uint32_t)parts ? p1 : p0 + (int)(share * (float)(part + 1));
-        acc = any_row(from, to, entry, [&](int key) { return dense(key, (int)(4 * l), n); });
+        acc = any_row<4>(from, to, entry, [&](int key) { return dense.template operator()<4>(key, (int)(4 * l), n); });
     }
     __syncthreads();
     float4* const at = sums + threadIdx.x;
@@ -1212,37 +1234,42 @@ __device__ __forceinline__ void any_long_rows(uint32_t fw, int nrows, int parts,
         const float4 more = at[s * nvec];
         acc[0] += more.x, acc[1] += more.y, acc[2] += more.z, acc[3] += more.w;
     }
-    any_store<ALIGNED>(dst + ((int64_t)i * ld_out + 4 * l), acc, n);
+    any_store<4, ALIGNED>(dst + ((int64_t)i * ld_out + 4 * l), acc, n);
 }
 
-// Lane groups to a row of an item of long rows: what the workgroup has, up to sixteen; one where the partial sums
-// have no room in `bytes` of LDS.
-__device__ __forceinline__ int long_row_parts(uint32_t fw, int nrows, int bytes)
+// Lane groups to a row of an item of long rows (`entries` in `rows` of them): what the workgroup has, up to sixteen,
+// off 16 bytes with kSharedEntries each; one where the partial sums have no room in `bytes` of LDS.
+template <bool ALIGNED>
+__device__ __forceinline__ int long_row_parts(uint32_t fw, int nrows, int entries, int rows, int bytes)
 {
-    const uint32_t groups = kThreads / ((fw + 3) / 4);
-    return bytes < (int)(kThreads * sizeof(float4)) ? 1 : (int)min(groups / (uint32_t)max(nrows, 1), 16u);
+    if (entries <= kLongRow * rows || (!ALIGNED && (entries < 2 * kSharedEntries * rows || 2 * nrows * (int)fw > kThreads)) || bytes < (int)(kThreads * sizeof(float4)))
+        return 1;
+    const uint32_t groups = kThreads / ((fw + 3) / 4), most = ALIGNED ? 16u : min((uint32_t)(entries / (kSharedEntries * max(rows, 1))), 16u);
+    return (int)min(groups / (uint32_t)max(nrows, 1), most);
 }
 
 // A lane's floats out of the LDS tile (the last lane of a row may read up to three words past
 // the row: LDS of this item) and out of global memory (nothing past the row's end is read).
 template <bool ALIGNED> struct TileRows {
     const char* tile;
-    __device__ __forceinline__ Floats operator()(int off, int l, int) const
+    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int off, int l, int) const
     {
-        return any_load<ALIGNED>(tile + off + 4 * l);
+        return any_load<VEC, ALIGNED>(tile + off + 4 * l);
     }
 };
 template <bool ALIGNED> struct GlobalRows {
     const float* src;
     int64_t ld;
-    __device__ __forceinline__ Floats operator()(int c, int l, int n) const
+    template <int VEC> __device__ __forceinline__ typename Floats<VEC>::type operator()(int c, int l, int n) const
     {
         const float* p = src + (c * ld + l);
-        if (ALIGNED || n >= 4) return any_load<ALIGNED>(p);
-        Floats v = 0.f;
+        if (ALIGNED || n >= VEC) return any_load<VEC, ALIGNED>(p);
+        typename Floats<VEC>::type v = 0.f;
         v[0] = p[0];
-        if (n > 1) v[1] = p[1];
-        if (n > 2) v[2] = p[2];
+        if constexpr (VEC == 4) {
+            if (n > 1) v[1] = p[1];
+            if (n > 2) v[2] = p[2];
+        }
         return v;
     }
 };
@@ -1284,13 +1311,15 @@ __device__ __forceinline__ void any_row_block(const LeanItem& it, const LeanItem
     };
     auto lds_entry = [&](int p) { return cv[p]; };
     const uint32_t sums = (uint32_t)round_up((int)cv_off, 4);
-    const int parts = fits && cnt > kLongRow * nrows ? long_row_parts(fw, nrows, 4 * ((int)lds_words - (int)sums)) : 1;
+    const int parts = fits ? long_row_parts<ALIGNED>(fw, nrows, cnt, nrows, 4 * ((int)lds_words - (int)sums)) : 1;
     if (!fits)
-        any_rows<ALIGNED>(fw, nrows, dst, ld_out, row, global_entry, dense);
+        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, global_entry, dense);
     else if (parts > 1)
         any_long_rows<ALIGNED>(fw, nrows, parts, dst, ld_out, reinterpret_cast<float4*>(sm + sums), row, lds_entry, dense);
+    else if (!ALIGNED && cnt > kLongRow * nrows)
+        any_rows<1, false>(fw, nrows, dst, ld_out, row, lds_entry, dense);
     else
-        any_rows<ALIGNED>(fw, nrows, dst, ld_out, row, lds_entry, dense);
+        any_rows<4, ALIGNED>(fw, nrows, dst, ld_out, row, lds_entry, dense);
 }
 
 // mode: kAnyWindows, kAnyTight (ALIGNED implies both).
@@ -1413,12 +1442,14 @@ bspmm_any_kernel(const LeanItem* __restrict__ items, const int32_t* __restrict__
     };
     auto lds_entry = [&](int p) { return cv[p]; };
     const int sums = round_up(it.cv_byte, 16);
-    const int parts = nnz > kLongRow * m ? long_row_parts(fw, it.nrows, it.b_byte - sums + 4 * k * (int)stride) : 1;
+    const int parts = long_row_parts<ALIGNED>(fw, it.nrows, nnz, m, it.b_byte - sums + 4 * k * (int)stride);
     if (parts > 1)
         any_long_rows<ALIGNED>(fw, it.nrows, parts, dst, ld_out, reinterpret_cast<float4*>(lds + sums), row, lds_entry,
                                TileRows<ALIGNED>{bs});
+    else if (!ALIGNED && nnz > kLongRow * m)
+        any_rows<1, false>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<false>{bs});
     else
-        any_rows<ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
+        any_rows<4, ALIGNED>(fw, it.nrows, dst, ld_out, row, lds_entry, TileRows<ALIGNED>{bs});
 }
 
 // The entry range of every row block into its item, for plans whose builds are wanted ahead of the first run.

@@ -351,7 +351,8 @@ BSPMM_HD inline LayerLds layer_lds(int ks, int rb, int waves, int channels, int 
 // bspmm_any_kernel: words from one row of the LDS tile to the next.  A row off 16 bytes is copied as
 // the 16-byte words it lies in and starts up to three words into the first.
 BSPMM_HD inline int tile_stride(int fw, bool aligned) { return round_up(aligned ? fw : fw + 3, 4); }
-constexpr int kLongRow = 16;   // entries per row from which lane groups without a row of their own share long ones
+constexpr int kLongRow = 16;   // entries per row from which rows count as long: lane groups share them, or a lane takes a float
+constexpr int kSharedEntries = 32;   // entries of a row that a lane group takes at least where rows are off 16 bytes
 
 // LDS words of an item of bspmm_any_kernel (a lane may read up to three words past the tile).
 BSPMM_HD inline int64_t any_words(int m, int k, int nnz, int fw, bool aligned)

@@ -67,8 +67,8 @@ bool general_only(const Knobs& kn)
     return kn.front > 0 || kn.hubs || kn.pad != 0 || kn.persistent_wgs > 0 || kn.wide_offsets;
 }
 
-// Output rows of operation i that a whole workgroup has in flight (see bspmm_any_kernel; operations of long
-// rows count a lane per float, so that more workgroups share their entries); in launches that
+// Output rows of operation i that a whole workgroup has in flight (see bspmm_any_kernel; long rows off 16
+// bytes take a lane per float); in launches that
 // run in bspmm_kernel, which gives a row a power of two of lanes, at most four of its passes (200 operations
 // of 1 to 220 rows with hub rows split: F = 17 10.2 -> 9.1 us, F = 50 10.5 -> 9.8, F = 127 17.6 -> 14.8; one
 // pass instead of four: F = 17 8.3, but F = 127 18.3 and F = 301 37.0 against 26.4).

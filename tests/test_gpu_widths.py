@@ -68,6 +68,27 @@ def test_lane_groups_share_long_rows(oracle, F):
         _check(got, ref, S, b.c_row_off, b.rows)
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("F", [1, 3, 12, 17, 50, 100, 127, 300])
+def test_long_rows_on_and_off_16_bytes(oracle, F, extra):
+    """Around the lines at which rows are shared by lane groups or take a lane per float: 16, 64 and 100 entries on
+    average, rows whose floats are half of the lanes and one row more, staged and in row blocks; widths that are a
+    multiple of four floats with rows on 16 bytes and, one float further apart, off them."""
+    import torch
+    half = min(max(1, 128 // F), 20)
+    shapes = [(m, k, z) for m in sorted({1, 2, half, half + 1, 2 * half + 1}) for k in (2, 90)
+              for z in (16 * m, 16 * m + 1, 64 * m - 1, 64 * m, 100 * m)] + [(1, 90, 1500)]
+    blocks = [(1, 6000, 900), (half, 6000, 64 * half), (half + 1, 6000, 65 * (half + 1)), (2, 6000, 33)]
+    b = W.random_general(51 + F, F=F, shapes=shapes + blocks)
+    plan = K.Plan(b)
+    info = plan.info()
+    assert info.items_in_bin[0][K.BIN_GENERIC] > 0 and info.items_in_bin[0][K.BIN_WORKGROUP] > len(shapes) // 2
+    for transposed in (False, True):
+        got = _run(torch, plan, b, transposed, 0, 0, extra, extra)
+        ref, S = (oracle.transposed_batch if transposed else oracle.forward_batch)(b)
+        _check(got, ref, S, b.b_row_off if transposed else b.c_row_off, b.cols if transposed else b.rows)
+
+
 @pytest.mark.parametrize("F", [1, 3, 50, 127])
 def test_operations_without_columns_read_nothing(F):
     """No operation has columns, so there is no dense input at all, wherever the (empty) blocks start."""
