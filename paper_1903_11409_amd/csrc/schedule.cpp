@@ -438,7 +438,15 @@ struct Count {
     int64_t tile_words;
     bool row_blocks;      // some operations are cut into row blocks that gather from memory
     int64_t in_words;     // of the dense blocks of all operations
+    int blocked;          // operations in row blocks, and the dense blocks of those
+    int64_t blocked_words;
 };
+// Whether the operations in row blocks are the tail of the others' sizes, not a few giants among small ones: at most
+// six times their dense input on average (heavy-tailed graphs have 5, uniformly random matrices 2).
+bool one_tail(const Count& t, int n)
+{
+    return t.blocked >= n || t.blocked_words * (n - t.blocked) <= 6 * (t.in_words - t.blocked_words) * t.blocked;
+}
 struct Shape {
     size_t chosen;
     int cap, wgs;
@@ -736,7 +744,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
                 chunk[c][0][l] = cap * tile[c].full.rows[l], chunk[c][1][l] = cap * tile[c].tail.rows[l];
                 for (int t = 0; t < 2; ++t) inv[c][t][l] = 1.0 / chunk[c][t][l];
             }
-        Count t = {0, 0, false, 0};
+        Count t = {0, 0, false, 0, 0, 0};
         int64_t k_sum = 0;
         for (int i = 0; i < n; ++i) {
             const int m = o.m[i];
@@ -746,6 +754,8 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
             if (c >= nc) {
                 t.wgs += (tile[blocks].nfull + (tile[blocks].tail.width > 0)) * ((m + generic_rows - 1) / generic_rows);
                 t.row_blocks = true;
+                ++t.blocked;
+                t.blocked_words += (int64_t)o.k[i] * F;
                 continue;
             }
             const Tile& x = tile[c];
@@ -777,36 +787,47 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
         if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
     Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
                        : search_shape(kn, vec, (size_t)nc, count);
-    // Longer row blocks where the launch does not fit the chip (seven eighths of it on tiles that are powers of two): from 24
-    // rows on, four passes at most, no more than make it seven eighths.  Where most of the dense input belongs to row
-    // blocks, whose gathers want every workgroup there can be, two passes, if it then fits.  Not past 104 MB of dense
-    // input (48 at 40 KiB), which bounds either, nor below F = 64 (a pass has 32 rows; 600 graphs at F = 32 9.1 -> 10.1).
-    // us, both directions, operands from memory, before / after, heavy-tailed graphs: 500 at F = 64 11.7 / 11.0, 1333
-    // 24.4 / 21.5; 500 at F = 128 20.2 / 16.2, 2700 78.2 / 72.4; 240 at F = 256 19.4 / 15.9, 500 33.1 / 31.5; 200 at F =
-    // 512 26.4 / 24.7; 66 at F = 1024 20.2 / 16.5.  Random matrices of three entries a row (three quarters of the input
-    // in row blocks): 97 at F = 256 15.0 / 13.5, 41 at F = 512 13.7 / 11.6; four passes where two do not fit lose: 100
-    // at F = 512 23.8 -> 29.1.
+    // Longer row blocks where the launch does not fit the chip: from 24 rows on, four passes at most, no more than
+    // make it seven eighths.  Where most of the dense input belongs to row blocks, whose gathers want every workgroup
+    // there can be, two passes, if it then fits.  Not past 104 MB of dense input (48 at 40 KiB), which bounds either, nor
+    // below F = 64 (a pass has 32 rows; 600 graphs at F = 32 9.1 -> 10.1).  us, both directions, operands from memory,
+    // before / after, heavy-tailed graphs: 1333 at F = 64 24.8 / 22.2; 500 at F = 128 20.7 / 16.1, 2700 82.8 / 75.0; 240 at
+    // F = 256 20.2 / 15.9; 200 at F = 512 27.2 / 25.5; 66 at F = 1024 20.7 / 16.1.  Random matrices of three entries a row
+    // (most of the input in row blocks): 160 at F = 128 13.8 / 11.3, 41 at F = 512 13.9 / 11.3; four passes where two
+    // do not fit lose: 100 at F = 512 23.8 -> 29.1.
+    // Only where the large operations are the tail of the others, no more than six times their columns on average: a few
+    // giants among small ones lose (30 of 500 rows among 400 of 60 at F = 128 15.8 -> 20.6, 60 of 400 among 1500 of 40 31.2
+    // -> 37.5, 100 of 250 to 500 among 3000 molecules 47 -> 52), nor where the launch is between seven eighths of the chip
+    // and all of it (239 heavy-tailed graphs at F = 128 11.3 -> 12.2).  A block's entries take half of the LDS on average:
+    // what does not fit is read from memory entry by entry (60 of 400 rows of 60 entries among 1500 of 40 at F = 64 46
+    // -> 80), and blocks of more entries are fewer workgroups than the gathers want (30 of 500 rows of 100 37 -> 44.6).
+    const int short_rows = generic_rows;
+    auto block_rows = [&](int i, int rows) {
+        return std::min((int64_t)rows, std::max((int64_t)short_rows, (int64_t)lds_words / 2 * o.m[i] / (o.m[i] + 2 * (int64_t)o.nnz[i]) / 8 * 8));
+    };
     if (open && F % 4 == 0 && F >= 64) {
         std::vector<int> blocked;
-        int64_t in_words = 0, blocked_words = 0;
+        Count t = {0, 0, true, 0, 0, 0};
         for (int i = 0; i < n; ++i) {
-            in_words += (int64_t)o.k[i] * F;
+            t.in_words += (int64_t)o.k[i] * F;
             if (o.m[i] <= 0 || std::max((int)shape.chosen, (int)fit[i]) < nc) continue;
-            blocked.push_back(o.m[i]);
-            blocked_words += (int64_t)o.k[i] * F;
+            blocked.push_back(i);
+            t.blocked_words += (int64_t)o.k[i] * F;
         }
+        t.blocked = (int)blocked.size();
         auto pieces = [&](int rows) {
-            int w = 0;
-            for (int m : blocked) w += (m + rows - 1) / rows;
-            return w * (tile[blocks].nfull + (tile[blocks].tail.width > 0));
+            int64_t w = 0;
+            for (int i : blocked) w += (o.m[i] + block_rows(i, rows) - 1) / block_rows(i, rows);
+            return (int)w * (tile[blocks].nfull + (tile[blocks].tail.width > 0));
         };
         const int others = shape.wgs - pieces(generic_rows), most = std::min(64, 4 * tile[blocks].full.rows[0]);
+        const int chip = tile[blocks].full.pow2 ? kMaxLdsBytes / 4 / lds_words * kn.compute_units : kn.capacity_wgs;
         const int room = 7 * (kMaxLdsBytes / 4 / lds_words) * kn.compute_units / 8;
         const int passes2 = std::min(64, 2 * tile[blocks].full.rows[0]);
-        if (kn.generic_given || blocked.empty() || generic_rows >= 24 || shape.wgs <= (tile[blocks].full.pow2 ? room : kn.capacity_wgs)) {
-        } else if (2 * blocked_words > in_words) {
+        if (kn.generic_given || blocked.empty() || generic_rows >= 24 || shape.wgs <= chip || !one_tail(t, n)) {
+        } else if (2 * t.blocked_words > t.in_words) {
             if (generic_rows < 16 && others + pieces(passes2) <= kn.capacity_wgs) generic_rows = std::max(generic_rows, passes2);
-        } else if (in_words <= (lds_words > kn.lds_words ? 12000000 : 26000000)) {
+        } else if (t.in_words <= (lds_words > kn.lds_words ? 12000000 : 26000000)) {
             generic_rows = std::max(generic_rows, std::min(24, most));
             while (generic_rows + 8 <= most && others + pieces(generic_rows) > room) generic_rows += 8;
         }
@@ -830,7 +851,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     // bytes an item of one row range moves (as item_cost(), the entries spread evenly over the ranges)
     auto ranges_of = [](int m, int chunk) { return chunk >= m ? 1 : (int)((unsigned)(m + chunk - 1) / (unsigned)chunk); };
     auto chunk_of = [&](int i, const Columns& y, bool staged) {
-        return !staged ? generic_rows : (shape.cap > 0 ? shape.cap * y.rows[long_rows(i)] : o.m[i]);
+        return !staged ? (int)block_rows(i, generic_rows) : (shape.cap > 0 ? shape.cap * y.rows[long_rows(i)] : o.m[i]);
     };
     auto cost_of = [&](int i, const Columns& y, int chunk, int ranges, bool staged) {
         const int nrows = std::min(chunk, o.m[i]);

@@ -307,6 +307,27 @@ def test_row_blocks_find_their_entries_in_the_first_run(torch_cuda, oracle, F, c
         _assert_close(results[0].cpu().numpy(), ref, S, _owned_rows(off, length, rows), f"row blocks F={F}")
 
 
+@pytest.mark.parametrize("maker,rows", [
+    (lambda: W.config5_skewed(graphs=500, F=128, asymmetric=True), 24),                # of launches past the chip
+    (lambda: W.config5_skewed(graphs=1333, F=64, asymmetric=True), 64),
+    (lambda: W.random_general(6, F=64, shapes=[(60, 60, 240)] * 1400 + [(300, 300, 14400)] * 80), 24),   # half of the LDS
+    (lambda: W.random_square(5, 128, 160, (32, 256), 3), 16),                          # two passes
+    (lambda: W.config5_skewed(graphs=1000, F=192, asymmetric=True), None),             # tiles of powers of two past 40 MB
+    (lambda: W.config5_skewed(graphs=2000, F=96, asymmetric=True), None),
+])
+def test_longer_row_blocks(torch_cuda, oracle, maker, rows):
+    """Row blocks of more rows than a pass or than eight, and widths that are no power of two in tiles that are."""
+    b = maker()
+    if b.dY is None:
+        b.dY = np.random.default_rng(7).standard_normal((b.n_c_rows, b.F)).astype(np.float32)
+    plan, _ = _check_forward(torch_cuda, oracle, b)
+    _check_transposed(torch_cuda, oracle, b, plan=plan)
+    _check_transposed(torch_cuda, oracle, b, plan=plan)          # (the entry ranges come from the items now)
+    items = [x for x in plan.items(True) if x.bin == K.BIN_GENERIC]
+    assert items and (rows is None or max(x.nrows for x in items) == rows)
+    assert rows is not None or {x.fw for x in plan.items(True)} <= {32, 64, 128}
+
+
 # ---------------------------------------------------------------------------------------------
 # edge cases
 # ---------------------------------------------------------------------------------------------

@@ -1051,3 +1051,33 @@ def test_plans_that_take_all_the_lds_of_a_cu_leave_none_beside_it(n, z, count, F
     static = {name: size for name, size in _static_lds().items() if "bspmm_lean_kernel" in name or
               "bspmm_any_kernel" in name or "bspmm_first_transposed_kernel" in name}
     assert len(static) >= 3 and not any(static.values()), static
+
+
+def _two_sizes(count, per_row, F, giants=0, small=None, large=400):
+    """Square operations of heavy-tailed sizes (median 40, at most 500), or of one small size with a few large ones."""
+    n = np.clip(np.rint(40 * np.exp(0.9 * np.random.default_rng(3).standard_normal(count))), 8, 500).astype(int)
+    n = list(n) if small is None else [small] * count + [large] * giants
+    return W.random_general(3, F=F, shapes=[(x, x, (4 if small and x == small else per_row) * x) for x in n], with_dY=False)
+
+
+@pytest.mark.parametrize("batch,F,rows", [
+    # a few giants among small operations keep a pass's rows (or the eight they had)
+    (dict(count=1500, per_row=60, giants=60, small=40), 64, 16), (dict(count=1500, per_row=5, giants=60, small=40), 128, 8),
+    (dict(count=400, per_row=3, giants=30, small=60), 128, 8),
+    # launches between seven eighths of the chip and all of it fit as they are
+    (dict(count=250, per_row=6), 128, 8),
+    # half of the LDS for a block's entries on average (20 KiB)
+    (dict(count=1333, per_row=6), 64, 64), (dict(count=1400, per_row=20, giants=80, small=60, large=300), 64, 56),
+    (dict(count=1400, per_row=24, giants=80, small=60, large=300), 64, 48),
+    (dict(count=1400, per_row=48, giants=80, small=60, large=300), 64, 24),
+    (dict(count=1400, per_row=100, giants=80, small=60, large=300), 64, 16),
+])
+def test_row_blocks_are_bounded_by_their_entries_and_the_other_operations(batch, F, rows):
+    b = _two_sizes(F=F, **batch)
+    h = K.dry_plan(b, compute_units=256)
+    items = [x for x in K.bspmm_plan_items(h) if x.bin == K.BIN_GENERIC]
+    words = K.bspmm_plan_info(h).lds_bytes // 4
+    assert max(x.nrows for x in items) == rows
+    for x in items:                                    # (a pass has that many rows whatever their entries)
+        assert x.nrows <= max(8, 1024 // F) or x.nrows + 2 * x.nrows * int(b.nnz[x.op]) / int(b.rows[x.op]) <= words / 2 + 8
+    K.bspmm_destroy(h)
