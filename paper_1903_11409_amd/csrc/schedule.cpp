@@ -586,9 +586,9 @@ WorkItem empty_item()
 //    get 40 once the launch does not fit the chip at once anyway, where that saves a quarter of the
 //    tiles and none are row blocks, and ranges of four passes (2000 graphs of 20-100 nodes 26.1 / 20.4
 //    against 40.0 / 39.7; 2000 molecules, of which few need it, 9.7 -> 11.0: not taken).
-// narrow: the first candidate from which on all tiles are powers of two (-1: none).
+// narrow: the first candidate from which on all tiles are powers of two (-1: none); ops: operations of the batch.
 template <typename CountFn, typename FitFn>
-Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narrow, bool shared, CountFn count, FitFn fit,
+Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narrow, int ops, bool shared, CountFn count, FitFn fit,
                   int* uncut_wgs)
 {
     Shape s = {0, 0, 0};
@@ -620,9 +620,10 @@ Shape plain_shape(const Knobs& kn, int F, const std::vector<int>& cand, int narr
         fit(kn.lds_words, 0);
     }
     bool pow2 = narrow == 0;
-    // (with row blocks past 40 MB: 1167 heavy-tailed graphs at F = 192 61.3 -> 51.7 us both directions, 2700 at F = 96 76 -> 61,
-    // 486 random matrices at F = 192 60.5 -> 54.5; 208 of them, 23 MB, 21.2 -> 24.6)
-    if (narrow > 0 && lines && n.row_blocks && n.in_words > 10000000) {
+    // (with row blocks past 40 MB, where they are the tail of the others: 1167 heavy-tailed graphs at F = 192 62.8 -> 51.0 us both
+    // directions, 2700 at F = 96 79 -> 64, 486 random matrices at F = 192 59 -> 54; 208 of them, 23 MB, 21.2 -> 24.6; one graph
+    // of 400 nodes among 3000 molecules at F = 192 40.0 -> 47.9, among 6000 at F = 96 42.2 -> 51.3)
+    if (narrow > 0 && lines && n.row_blocks && n.in_words > 10000000 && one_tail(n, ops)) {
         pow2 = true;
         fit(kn.lds_words, narrow);
         s = {(size_t)narrow, 0, count((size_t)narrow, 0).wgs};
@@ -785,7 +786,7 @@ bool plain_schedule(const DirOps& o, int F, const Knobs& kn, int vec, const std:
     int narrow = -1;
     for (int c = std::min(nc, 2) - 1; c >= 0; --c)
         if (tile[c].full.pow2 && tile[c].tail.pow2) narrow = c;
-    Shape shape = open ? plain_shape(kn, F, cand, narrow, 2 * units <= n, count, fit_all, &s.uncut_wgs)
+    Shape shape = open ? plain_shape(kn, F, cand, narrow, n, 2 * units <= n, count, fit_all, &s.uncut_wgs)
                        : search_shape(kn, vec, (size_t)nc, count);
     // Longer row blocks where the launch does not fit the chip: from 24 rows on, four passes at most, no more than
     // make it seven eighths.  Where most of the dense input belongs to row blocks, whose gathers want every workgroup

@@ -1081,3 +1081,18 @@ def test_row_blocks_are_bounded_by_their_entries_and_the_other_operations(batch,
     for x in items:                                    # (a pass has that many rows whatever their entries)
         assert x.nrows <= max(8, 1024 // F) or x.nrows + 2 * x.nrows * int(b.nnz[x.op]) / int(b.rows[x.op]) <= words / 2 + 8
     K.bspmm_destroy(h)
+
+
+@pytest.mark.parametrize("F,molecules", [(192, 3000), (96, 6000), (160, 3000)])
+@pytest.mark.parametrize("giants", [0, 1, 20])
+def test_a_few_giants_leave_the_tiles_of_the_others_alone(F, molecules, giants):
+    """Molecules at widths that are no power of two run in one tile of the whole row; a few operations in row blocks past 40 MB
+    do not change that, as the tail of heavy-tailed graphs does."""
+    n = np.clip(np.rint(23 * np.exp(0.5 * np.random.default_rng(1).standard_normal(molecules))), 3, 60).astype(int)
+    shapes = [(x, x, 3 * x) for x in n] + [(400, 400, 2000)] * giants
+    b = W.random_general(2, F=F, shapes=shapes, with_dY=False)
+    assert b.n_b_rows * F > 10000000
+    h = K.dry_plan(b, compute_units=256)
+    widths = [x.fw for x in K.bspmm_plan_items(h) if x.op < molecules]
+    assert max(widths) == F and 2 * widths.count(F) > len(widths)
+    K.bspmm_destroy(h)
