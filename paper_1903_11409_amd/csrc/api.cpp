@@ -474,8 +474,11 @@ void make_stream_plan(bspmm_plan& p)
     // n_X = 16, F = 64, 2048 molecules, 16 / 32 / 64 rows: 11.2 / 9.4 / 9.2 us; at n_X = 64, 1200: 9.3 / 9.8).
     // (no more than 1024 slots: 256 had blocks of four entries per row at n_X = 16 past them, 9.9 -> 8.9 us)
     // (eight wavefronts past K = 256 hold so many registers that a CU has one workgroup whatever its LDS: us, four channels at
-    // n_X = 128, F = 128, 53 / 128 KiB: 1500 molecules 47.0 / 44.5, 300 15.3 / 14.7; three channels, eight at n_X = 64 level)
-    const int budget = kn.lds_given ? kn.lds_words * 4 : waves == 8 && !direct && steps_of(most) > 8 ? 131072 : 53248;
+    // n_X = 128, F = 128, 53 / 128 KiB: 1500 molecules 47.0 / 44.5, 300 15.3 / 14.7; three channels, eight at n_X = 64 level.
+    // By the channels of the launch: five of 128 run as three and two, whose K = 256 leaves room for two workgroups; 1500
+    // graphs of 9 / 17 entries per row, 53 / 128 KiB in both launches / as it is 73.0 / 79.7 / 73.2, 81.0 / 87.8 / 80.5)
+    auto lds_budget = [&](int ch) { return kn.lds_given ? kn.lds_words * 4 : waves == 8 && !direct && steps_of(ch) > 8 ? 131072 : 53248; };
+    const int budget = lds_budget(most);
     constexpr int kSlots = 1024;
     auto slots_in = [&](int rb, int ch, int bytes, int want) {
         const int unit = 256 / nx;             // rows that a wavefront's request brings
@@ -548,7 +551,7 @@ void make_stream_plan(bspmm_plan& p)
             st = bspmm_plan::Stream();
             return;
         }
-        part.slots = slots_in(rb, part.channels, budget, std::max(wanted(rb), 64));
+        part.slots = slots_in(rb, part.channels, lds_budget(part.channels), std::max(wanted(rb), 64));
         if (direct) {
             part.slots = round_up(std::max(most_k, 1), 256 / nx);
         } else if (!kn.lds_given) {

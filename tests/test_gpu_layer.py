@@ -103,7 +103,7 @@ def test_rows_with_more_entries_than_slots(torch_cuda, oracle, chans, cus, n_x):
 
 
 @pytest.mark.parametrize("chans,n_x,F", [(1, 16, 64), (1, 64, 128), (2, 32, 128), (1, 128, 64), (4, 64, 128),
-                                         (6, 16, 128), (8, 128, 128)])
+                                         (5, 128, 128), (6, 16, 128), (8, 128, 128)])
 @pytest.mark.parametrize("per_row,heavy,cus", [(8, None, 4), (20, None, 4), (100, None, 2), (3, 70, 4), (7, None, 0)])
 def test_many_entries_per_row(torch_cuda, oracle, chans, n_x, F, per_row, heavy, cus):  # noqa: F811
     """Blocks inside their slots, past them (rows of more entries than a lane group requests at once, and of
