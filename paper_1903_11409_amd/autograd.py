@@ -42,6 +42,23 @@ class BatchedSpMM(torch.autograd.Function):
         return None, G, None
 
 
+class _Node(BatchedSpMM):
+    """A node of the class without its product."""
+
+    @staticmethod
+    def forward(ctx, plan, B, n_c_rows):
+        ctx.plan = plan
+        ctx.n_b_rows = int(B.shape[0])
+        return B.detach()[:1].expand(n_c_rows, plan.F)
+
+
+def _node_of_class(plan, n_b_rows, n_c_rows):
+    """A tensor whose node is the class's, for what traces the backward pass of a native one (compiled autograd)."""
+    with torch.enable_grad():
+        B = torch.empty((1, plan.F), dtype=torch.float32, device=plan.device).expand(n_b_rows, plan.F).requires_grad_()
+        return _Node.apply(plan, B, n_c_rows)
+
+
 def batched_spmm(plan: K.Plan, B, n_c_rows=None):
     """Functional form of :class:`BatchedSpMM`.  Rows of the output that belong to no operation
     are zero (``n_c_rows`` defaults to the number of rows of ``B``).
@@ -50,10 +67,10 @@ def batched_spmm(plan: K.Plan, B, n_c_rows=None):
     the engine's thread enters for the backward pass, a step of 47 graphs at F = 64 took the host 63 us, and takes
     23 to 43 now (1024 graphs of 8 to 500 nodes at F = 256: 63 -> 55, the time of the two launches).  What the native
     code leaves out - tensor subclasses, active modes, tracing, forward-mode gradients, function
-    transforms - goes through the class."""
+    transforms - goes through the class, and compiled autograd finds the class's node in the native one."""
     if (type(plan) is K.Plan and not torch._C._are_functorch_transforms_active()
             and not torch.compiler.is_compiling()):
-        C = K._native.batched_spmm(plan, plan.handle, plan.F, B, n_c_rows)
+        C = K._native.batched_spmm(plan, plan.handle, plan.F, B, n_c_rows, _node_of_class)
         if C is not None:
             return C
     return BatchedSpMM.apply(plan, B, n_c_rows)

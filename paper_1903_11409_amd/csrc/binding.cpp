@@ -424,17 +424,39 @@ at::Tensor room(bspmm_plan* plan, bool transposed, int64_t rows, int64_t F, cons
 }
 
 // The backward pass of autograd.py's BatchedSpMM.  It has the plan object, not its handle: a plan that was closed
-// in between is an error there as here.
+// in between is an error there as here.  Compiled autograd traces nodes instead of running them: there it has the
+// node that the class would have made (`traced`, a callable that gives a tensor with it).
 struct BatchedSpmmBackward : torch::autograd::Node {
-    PyObject* plan;
+    PyObject *plan, *traced;
     int64_t F, n_b_rows, n_c_rows;
-    BatchedSpmmBackward(PyObject* p, int64_t f, int64_t nb, int64_t nc) : plan(Py_NewRef(p)), F(f), n_b_rows(nb), n_c_rows(nc) {}
+    mutable std::shared_ptr<torch::autograd::Node> twin;
+    BatchedSpmmBackward(PyObject* p, PyObject* t, int64_t f, int64_t nb, int64_t nc)
+        : plan(Py_NewRef(p)), traced(Py_NewRef(t)), F(f), n_b_rows(nb), n_c_rows(nc) {}
     ~BatchedSpmmBackward() override
     {
         if (!Py_IsInitialized()) return;
         const PyGILState_STATE lock = PyGILState_Ensure();
         Py_DECREF(plan);
+        Py_DECREF(traced);
         PyGILState_Release(lock);
+    }
+    torch::autograd::Node& of_class() const
+    {
+        if (twin) return *twin;
+        const PyGILState_STATE lock = PyGILState_Ensure();
+        PyObject* t = PyObject_CallFunction(traced, "OLL", plan, (long long)n_b_rows, (long long)n_c_rows);
+        if (t && is_tensor(t)) twin = THPVariable_Unpack(t).grad_fn();
+        Py_XDECREF(t);
+        PyErr_Clear();
+        PyGILState_Release(lock);
+        TORCH_CHECK(twin, "BatchedSpMM: no node for compiled autograd");
+        return *twin;
+    }
+    void compiled_args(torch::dynamo::autograd::CompiledNodeArgs& args) const override { of_class().compiled_args(args); }
+    torch::autograd::variable_list apply_with_saved(const torch::autograd::variable_list& inputs,
+                                                    torch::dynamo::autograd::SwapSavedVariables& saved) override
+    {
+        return of_class().apply_with_saved(inputs, saved);
     }
     std::string name() const override { return "BatchedSpMMBackward"; }
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override
@@ -466,13 +488,13 @@ struct BatchedSpmmBackward : torch::autograd::Node {
     }
 };
 
-// (plan object, its handle, F, B, rows of C or None) -> C, or None for what BatchedSpMM.apply decides: other
+// (plan object, its handle, F, B, rows of C or None, BatchedSpmmBackward::traced) -> C, or None for what BatchedSpMM.apply decides: other
 // types and devices, tensor subclasses, active modes, tracing, forward-mode gradients.
 PyObject* batched_spmm(PyObject* const* a, Py_ssize_t n)
 {
     void *plan, *stream;
     int64_t F, rows;
-    if (!arity("batched_spmm", n, 5) || !get_ptr(a[1], &plan) || !get_i64(a[2], &F)) return nullptr;
+    if (!arity("batched_spmm", n, 6) || !get_ptr(a[1], &plan) || !get_i64(a[2], &F)) return nullptr;
     if (!is_tensor(a[3]) || (a[4] != Py_None && !PyLong_CheckExact(a[4]))) Py_RETURN_NONE;
     const at::Tensor& given = THPVariable_Unpack(a[3]);
     if (!given.is_cuda() || given.scalar_type() != at::kFloat || given.layout() != at::kStrided || given.dim() != 2 ||
@@ -494,7 +516,7 @@ PyObject* batched_spmm(PyObject* const* a, Py_ssize_t n)
     const int rc = call<bspmm_run>(plan, B.data_ptr(), C.data_ptr(), B.stride(0), F, stream);
     if (rc != BSPMM_OK) return finish(rc, "bspmm_run", Py_None);
     if (differentiable) {
-        auto node = std::shared_ptr<BatchedSpmmBackward>(new BatchedSpmmBackward(a[0], F, given.size(0), rows),
+        auto node = std::shared_ptr<BatchedSpmmBackward>(new BatchedSpmmBackward(a[0], a[5], F, given.size(0), rows),
                                                          torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(given));
         torch::autograd::set_history(C, node);

@@ -428,3 +428,30 @@ def test_native_autograd_is_the_class():
     plan.close()
     with pytest.raises(K.BspmmError):
         C.backward(dY)
+
+
+@pytest.mark.gpu
+@pytest.mark.filterwarnings("ignore")
+def test_compiled_autograd_traces_the_native_node():
+    """A backward pass that compiled autograd traces gives what the class gives there, for plans one after the other."""
+    import torch
+    import torch._dynamo.compiled_autograd as traced
+    from paper_1903_11409_amd import autograd as A
+    batches = [W.config5_skewed(seed=s, graphs=20 + s, F=64, asymmetric=True) for s in range(3)]
+    results = []
+    for f in (A.batched_spmm, A.BatchedSpMM.apply):
+        for b in batches + batches[:1]:
+            plan = K.Plan(b)
+            leaf = torch.from_numpy(b.B).cuda().requires_grad_()
+            C = f(plan, leaf * 2.0) + f(plan, leaf)
+            with traced._enable(torch.compile(backend="eager")):
+                C.backward(torch.from_numpy(b.dY).cuda())
+            torch.cuda.synchronize()
+            results.append(leaf.grad)
+        torch._dynamo.reset()
+    for native, of_class in zip(results, results[len(batches) + 1:]):
+        assert torch.equal(native, of_class)
+    plan = K.Plan(batches[0])
+    leaf = torch.from_numpy(batches[0].B).cuda().requires_grad_()
+    A.batched_spmm(plan, leaf).backward(torch.from_numpy(batches[0].dY).cuda())
+    assert torch.allclose(results[0], 3.0 * leaf.grad, rtol=1e-5, atol=1e-5)
