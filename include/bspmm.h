@@ -189,7 +189,9 @@ typedef struct bspmm_options {
     int32_t  lds_pad;          /* floats added to each staged B row, 0 = default, -1 = none    */
     int32_t  max_passes;       /* row passes a sub-workgroup slot may take, 0 = default (1)    */
     int32_t  generic_rows;     /* rows per generic row block, 0 = default (8; up to 64 at narrow
-                                  widths, as many as a workgroup has in flight)               */
+                                  widths, as many as a workgroup has in flight; in launches that
+                                  do not fit the chip 16, or 24 to 64, by the rest of the batch and
+                                  by the entries of the block's rows)                         */
     int32_t  wg_passes;        /* row passes of a workgroup item before it is cut into row
                                   ranges: 0 = cut only while the launch is short of
                                   target_workgroups, N > 0 = always cap at N, -1 = never cut   */
@@ -223,7 +225,17 @@ typedef struct bspmm_info {
     int32_t items_in_bin[2][BSPMM_NUM_BINS];
     int32_t fused_tasks[2];                  /* tasks that add up several operations          */
     int32_t transposed_supported;            /* 0 when input-gradient blocks overlap          */
-    int32_t transposed_built;                /* the build kernel has been enqueued            */
+    int32_t transposed_built;                /* the transposed CSR arrays have been enqueued: by
+                                                a build kernel, or by the first transposed product
+                                                itself, one launch less, where every operation is
+                                                square with at most 1024 entries and at least
+                                                one row, its CSR packed in operation order
+                                                and its B and C blocks at the same rows, no part of
+                                                the batch is cut into row blocks, lean[1] is set,
+                                                both operands are on 16 bytes, the batch has no
+                                                more than 10000 workgroups beside two per
+                                                operation, and neither BSPMM_SYMMETRIC nor
+                                                BSPMM_FLOOR_PROBE is given                    */
     int32_t lean[2];                         /* 1: every task is one staged workgroup item with a
                                                 power-of-two tile, so runs with 16-byte aligned
                                                 operands launch the lean kernel                */
@@ -346,8 +358,8 @@ int bspmm_run_gcn(bspmm_plan* plan, const float* X, int64_t ldx, const float* W,
  * G_i = A_i^T . dY_i for every operation (backward product with respect to the dense input).
  * dY is indexed like C (rows_i rows at c_row_off[i]), G like B (cols_i rows at b_row_off[i]).
  * The first call builds the transposed CSR on the device unless bspmm_create already did: inside the product's
- * own launch for square operations of at most 1024 entries, else in one extra launch, once per plan.  Returns ESTATE when two operations share or
- * overlap a B block and the plan was not created with BSPMM_ACCUMULATE (each would have to
+ * own launch where that allows it (see bspmm_info.transposed_built), else in one extra launch, once per plan.
+ * Returns ESTATE when two operations share or overlap a B block and the plan was not created with BSPMM_ACCUMULATE (each would have to
  * add into the same gradient rows), or when B blocks overlap without being identical.
  */
 int bspmm_run_transposed(bspmm_plan* plan, const float* dY, float* G, int64_t ldy, int64_t ldg,

@@ -198,10 +198,12 @@ def _check_first_transposed(torch, oracle, b):
 
 
 @pytest.mark.parametrize("F,sizes", [
-    # one row, nothing, one to four entries per lane and the edges between them, more rows than lanes,
-    # every entry in one column
+    # what keeps the build's launch: a batch with row blocks (one row, nothing, one to four entries per lane and the edges
+    # between them, more rows than lanes), a tile that is no power of two; every entry in one column
     (64, [(1, 1), (1, 7), (5, 0), (2, 256), (30, 257), (40, 512), (90, 513), (256, 300), (300, 1024), (700, 40)]),
-    (128, [(25, 90)] * 40), (100, [(33, 1000), (32, 100)]), (4, [(60, 700)] * 3),
+    (100, [(33, 1000), (32, 100)]),
+    # what sorts inside the product
+    (128, [(25, 90)] * 40), (4, [(60, 700)] * 3),
     (16, [(20, 60)] * 9000),                       # small operations packed four to a workgroup elsewhere
 ])
 @pytest.mark.parametrize("one_column", [False, True])
