@@ -806,9 +806,10 @@ int plan_host(bspmm_plan& p, const bspmm_batch* b, int32_t F, const Knobs& kn)
             p.lean_shared = same_place && !p.lean_blocks[0];
             // Every workgroup of the product then sorts its operation: 0.5 to 0.9 us per thousand workgroups, against
             // a launch of its own (3.5 us of the host's time, 1.5 between two kernels) for the build, 5 us and 1.5 per
-            // thousand operations.  GPU time, build + product / one launch: 60 molecules at F = 64 (128 workgroups) 8.1 /
-            // 4.7 us, 128 at F = 128 (632) 8.7 / 5.4, 2000 tiny graphs (2000) 13.8 / 8.4, 16384 molecules (20507) 115 / 91,
-            // 300 random matrices at F = 512 (3344) 45 / 44, 512 wide graphs at F = 1024 (11184) 57 / 60.
+            // thousand operations.  us between events around the first run, build + product / one launch: 60 molecules at
+            // F = 64 (136 workgroups) 10.5 / 7.4, 128 at F = 128 (624) 10.9 / 7.9, 2000 tiny graphs (2000) 15.1 / 11.7, 16384
+            // molecules (20515) 113.5 / 96.6, 300 random matrices at F = 512 (1592) 24.8 / 21.0, 512 wide graphs at F = 512 (2480)
+            // 33.6 / 33.7, 400 at F = 1024 (9016) 49.1 / 52.2, which the launch that the host saves makes level.
             p.sorts_in_run = n > 0 && p.lean_shared && !kn.symmetric && p.build_threads == kThreads &&
                              *std::min_element(b->rows, b->rows + n) > 0 &&
                              (int64_t)p.lean_items[0].size() <= 10000 + 2 * (int64_t)n;
